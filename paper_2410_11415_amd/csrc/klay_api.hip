@@ -139,11 +139,16 @@ struct klay_circuit {
     const int32_t *d_pos_row = nullptr, *d_neg_row = nullptr, *d_root_pos = nullptr, *d_top_ptr = nullptr,
                   *d_top_root = nullptr;
     int32_t true_row = -1, false_row = -1;
-    const klay::SlabLayer* d_tail = nullptr;   // descriptors of layers plan.tail_first .. L
+    const klay::ColLayer* d_tail = nullptr;    // where the streams of the layers plan.tail_first .. L start
+    const klay::Line* d_blocks[2] = {nullptr, nullptr};   // streams of the persistent kernels, forward and reverse
+    int32_t n_blocks[2] = {0, 0};
+    const klay::Desc* d_tables = nullptr;
     const int32_t* d_leaf_code = nullptr;      // layer 0: literal / constant code of every row
     size_t tail_lds_bytes = 0;                 // LDS a workgroup of the persistent kernels may use (0: kernels unusable)
     int64_t tail_rows = 0;                     // T: rows of all tail candidate layers (one column of the tail buffer)
     int32_t last_tail_first = 0;               // first layer the last forward ran in the persistent kernel (0: none)
+    int32_t last_tail_T = 0;                   // floats in a column of its value buffer
+    bool last_tail_staged = false;             // the layer below it is part of that buffer
     // real-semiring reverse sweep (built at its first use): per AND layer the plain by-parent index
     // vectors (for prod_parent_kernel); for the layers below alias_top also the by-child pass over the
     // parents in all higher layers up to alias_top, whose entries tell AND parents from plain adjoint rows
@@ -471,59 +476,39 @@ klay_status upload(klay_circuit* c) {
     const klay::CircuitPlan& p = c->plan;
     Packer pk;
     const int L = p.num_layers;
-    // tail candidates first (their descriptors hold 32-bit offsets, and these arrays are small):
-    // plain index vectors by parent and by child, then the descriptor array
-    size_t o_tail = 0;
+    // Streams of the persistent kernels: per wave and direction the lines and descriptors of all candidate layers
+    // back to back, in the order the sweep visits them.
+    size_t o_tail = 0, o_blocks[2] = {0, 0}, o_tables = 0;
     if (p.tail_first > 0) {
-        std::vector<klay::SlabLayer> descs;
-        int64_t row0 = 0, tb_off = 0;
-        for (int l = 0; l < p.tail_first; ++l) row0 += p.layers[(size_t)l].n;
+        std::vector<klay::ColLayer> starts((size_t)(L - p.tail_first + 1));
+        std::vector<uint32_t> blocks[2], tables;
         for (int l = p.tail_first; l <= L; ++l) {
-            const klay::LayerPlan& lay = p.layers[(size_t)l];
-            klay::SlabLayer t{};
-            t.n = (int32_t)lay.n;
-            t.n_below = (int32_t)p.layers[(size_t)l - 1].n;
-            t.row0 = row0;
-            t.row0_below = row0 - t.n_below;
-            t.tb_off = (int32_t)tb_off;
-            tb_off += lay.n;
-            row0 += lay.n;
-            descs.push_back(t);
+            starts[(size_t)(l - p.tail_first)].n = (int32_t)p.layers[(size_t)l].n;
+            starts[(size_t)(l - p.tail_first)].at = (int32_t)p.col_off[(size_t)l];
         }
-        // One stream of lines per wave and direction: the wave's runs of all candidate layers back to
-        // back, in the order the sweep visits them, closed by a block of padding lines (the kernels fetch
-        // one block ahead of the one they work on).
-        auto add_streams = [&](bool backward) {
-            const int lo = backward ? p.tail_bwd_first : p.tail_first;
-            if (lo <= 0) return;
-            std::vector<uint32_t> stream;
-            std::vector<int64_t> start((size_t)(L + 1) * klay::kSlabWaves, 0);
-            for (int w = 0; w < klay::kSlabWaves; ++w) {
-                for (int step = 0; step <= L - lo; ++step) {
-                    const int l = backward ? L - step : lo + step;
-                    const klay::SlabPlan& sp = backward ? p.layers[(size_t)l].slab_bwd : p.layers[(size_t)l].slab_fwd;
-                    start[(size_t)l * klay::kSlabWaves + w] = (int64_t)stream.size();
-                    stream.insert(stream.end(), sp.ent.begin() + (size_t)sp.wave_line[w] * 64,
-                                  sp.ent.begin() + (size_t)sp.wave_line[w + 1] * 64);
+        constexpr size_t kTableWords = (size_t)klay::kDescTable * klay::kDescWords;
+        for (int backward = 0; backward < 2; ++backward) {
+            std::vector<uint32_t>& out = blocks[backward];
+            for (int w = 0; w < klay::kSlabWaves; ++w)
+                for (int step = 0; step <= L - p.tail_first; ++step) {
+                    const int l = backward ? L - step : p.tail_first + step;
+                    const klay::ColPlan& cp = backward ? p.layers[(size_t)l].col_bwd : p.layers[(size_t)l].col_fwd;
+                    klay::ColLayer& at = starts[(size_t)(l - p.tail_first)];
+                    (backward ? at.bwd_block : at.fwd_block)[w] = (int32_t)(out.size() / klay::kBlockWords);
+                    (backward ? at.bwd_table : at.fwd_table)[w] = (int32_t)(tables.size() / kTableWords);
+                    out.insert(out.end(), cp.blocks.begin() + (size_t)cp.block_at[w] * klay::kBlockWords,
+                               cp.blocks.begin() + (size_t)cp.block_at[w + 1] * klay::kBlockWords);
+                    tables.insert(tables.end(), cp.tables.begin() + (size_t)cp.table_at[w] * kTableWords,
+                                  cp.tables.begin() + (size_t)cp.table_at[w + 1] * kTableWords);
                 }
-                stream.insert(stream.end(), (size_t)klay::kSlabBlock * 64, 0u);
-            }
-            const size_t base_off = pk.add(stream);
-            for (int l = lo; l <= L; ++l) {
-                klay::SlabLayer& t = descs[(size_t)(l - p.tail_first)];
-                const klay::SlabPlan& sp = backward ? p.layers[(size_t)l].slab_bwd : p.layers[(size_t)l].slab_fwd;
-                for (int w = 0; w < klay::kSlabWaves; ++w) {
-                    const int32_t at = (int32_t)(base_off + (size_t)start[(size_t)l * klay::kSlabWaves + w]);
-                    const int32_t cnt = sp.wave_line[w + 1] - sp.wave_line[w];
-                    if (backward) { t.bwd_start[w] = at; t.bwd_count[w] = cnt; }
-                    else { t.fwd_start[w] = at; t.fwd_count[w] = cnt; }
-                }
-            }
-        };
-        add_streams(false);
-        add_streams(true);
-        static_assert(sizeof(klay::SlabLayer) % sizeof(int32_t) == 0, "descriptor must pack into ints");
-        o_tail = pk.add(reinterpret_cast<const int32_t*>(descs.data()), descs.size() * sizeof(klay::SlabLayer) / sizeof(int32_t));
+            c->n_blocks[backward] = (int32_t)(out.size() / klay::kBlockWords);
+            out.resize(out.size() + klay::kBlockWords, 0u);      // the waves read one block and one table ahead
+        }
+        tables.resize(tables.size() + kTableWords, 0u);
+        static_assert(sizeof(klay::ColLayer) % sizeof(int32_t) == 0, "must pack into ints");
+        for (int i = 0; i < 2; ++i) o_blocks[i] = pk.add(blocks[i]);
+        o_tables = pk.add(tables);
+        o_tail = pk.add(reinterpret_cast<const int32_t*>(starts.data()), starts.size() * sizeof(klay::ColLayer) / sizeof(int32_t));
     }
     const size_t o_leaf_code = pk.add(p.leaf_code);
     std::vector<PassOffsets> fo((size_t)L + 1), bo((size_t)L + 1), fko((size_t)L + 1), f2o((size_t)L + 1);
@@ -581,7 +566,11 @@ klay_status upload(klay_circuit* c) {
     c->d_root_pos = base + o_root;
     c->d_top_ptr = base + o_tptr;
     c->d_top_root = base + o_troot;
-    if (p.tail_first > 0) c->d_tail = reinterpret_cast<const klay::SlabLayer*>(base + o_tail);
+    if (p.tail_first > 0) {
+        c->d_tail = reinterpret_cast<const klay::ColLayer*>(base + o_tail);
+        for (int i = 0; i < 2; ++i) c->d_blocks[i] = reinterpret_cast<const klay::Line*>(base + o_blocks[i]);
+        c->d_tables = reinterpret_cast<const klay::Desc*>(base + o_tables);
+    }
     c->d_leaf_code = base + o_leaf_code;
     return KLAY_OK;
 }
@@ -782,25 +771,27 @@ void run_pass_set(int op, int combine_op, const DevPass& dp, const float* src, c
 // ---- persistent kernels for the top layers -----------------------------------------------------
 struct TailChoice {
     int first = 0;       // first layer run by the persistent kernel (0: not used)
-    int ct = 1;          // batch columns per workgroup
-    int nmax = 0;        // LDS rows per buffer
+    int ct = 1;          // batch columns that share the LDS in the rule below
+    int nmax = 0;        // longest of the layers
 };
 
-// Batch columns per workgroup: one column per workgroup until the batch needs more workgroups
-// than the chip has compute units; few columns mean few rows per lane and a short layer time.
+// The layers the persistent kernels take: as many as fit when `ct` columns share the LDS of a compute unit.  Up to 256
+// columns every workgroup (a column) has a compute unit of its own; beyond, the launches of the wider layers, which
+// fill the chip, are left to the ordinary kernels.
 int tail_ct(int B) {
     int ct = 1;
     while (ct < 8 && (B + ct - 1) / ct > 256) ct *= 2;
     return ct;
 }
 
-// Largest suffix of the candidate layers, not starting below `lowest`, whose `buffers` value arrays of
-// CT columns fit the LDS of a workgroup.  The arrays hold the layers first .. L, and layer 0 as well
+// Largest suffix of the candidate layers whose two value arrays of ct columns fit the LDS of a workgroup.  The arrays
+// hold the layers first .. L, and layer 0 as well
 // when the kernel starts at layer 1 and evaluates the leaf layer itself.  At least two layers,
 // otherwise a kernel of its own is not worth it.
-TailChoice choose_tail(const klay_circuit* c, int B, int buffers, int lowest) {
+TailChoice choose_tail_fwd(const klay_circuit* c, int B) {
     TailChoice t;
     const klay::CircuitPlan& p = c->plan;
+    const int lowest = p.tail_first;
     if (lowest <= 0 || c->tail_lds_bytes == 0) return t;
     t.ct = tail_ct(B);
     const int L = p.num_layers;
@@ -810,7 +801,9 @@ TailChoice choose_tail(const klay_circuit* c, int B, int buffers, int lowest) {
     for (int l = L; l >= lowest; --l) {
         int64_t n2 = std::max(nmax, p.layers[(size_t)l].n);
         if (l == 1) n2 = std::max(n2, p.layers[0].n);
-        if ((int64_t)buffers * (n2 + 1) * t.ct > words) break;      // + 1: the padding slot of every array
+        if (2 * (n2 + 1) * t.ct > words) break;
+        // the layer below is loaded into LDS as well
+        if (2 * (std::max(n2, p.layers[(size_t)l - 1].n) + klay::kColSlots + 3) > words) break;
         nmax = n2;
         first = l;
     }
@@ -820,12 +813,9 @@ TailChoice choose_tail(const klay_circuit* c, int B, int buffers, int lowest) {
     return t;
 }
 
-// the layers the forward sweep runs in the persistent kernel ...
-TailChoice choose_tail_fwd(const klay_circuit* c, int B) { return choose_tail(c, B, 2, c->plan.tail_first); }
-
-// Rows of the layer below the forward kernel's first one if the kernel reads that layer from the column-major
-// stage buffer: it then has to fit an LDS array (the arrays are made as long as it, if the LDS has the room).
-// 0: no stage buffer (the kernel evaluates the leaf layer itself, or gathers from the rows).
+// Rows of the layer below the forward kernel's first one if that layer gets a place in the column-major buffer (where
+// the kernel reads it as one run per column, and the reverse kernel its values): where ct arrays of its length fit the
+// LDS too.  0: no place (the kernel evaluates the leaf layer itself, or reads the layer from its rows).
 int64_t tail_stage_rows(const klay_circuit* c, const TailChoice& t) {
     if (t.first < 2) return 0;
     const int64_t nb = c->plan.layers[(size_t)t.first - 1].n;
@@ -833,20 +823,14 @@ int64_t tail_stage_rows(const klay_circuit* c, const TailChoice& t) {
     return (size_t)2 * (size_t)(rows + 1) * t.ct * sizeof(float) <= c->tail_lds_bytes ? nb : 0;
 }
 int64_t tail_stage_rows(const klay_circuit* c, int B) { return tail_stage_rows(c, choose_tail_fwd(c, B)); }
-// ... and the layers the reverse sweep does, given the forward choice (fewer where a layer has a node with more
-// than kTailFanCap parents)
-TailChoice choose_tail_bwd(const klay_circuit* c, int B, int fwd_first) {
-    if (fwd_first <= 0 || c->plan.tail_bwd_first <= 0) return TailChoice();
-    return choose_tail(c, B, 2, std::max(fwd_first, c->plan.tail_bwd_first));
-}
 
-template <int CT>
-hipError_t tail_attr(int bytes) {
-    hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(&klay::slab_fwd_kernel<CT>),
-                                       hipFuncAttributeMaxDynamicSharedMemorySize, bytes);
-    if (e != hipSuccess) return e;
-    return hipFuncSetAttribute(reinterpret_cast<const void*>(&klay::slab_bwd_kernel<CT>),
-                               hipFuncAttributeMaxDynamicSharedMemorySize, bytes);
+// floats of the two LDS arrays that hold the layers lowest .. L by turns; [0]: the one with layer `zero` in it
+void tail_lds(const klay::CircuitPlan& p, int lowest, int zero, int64_t (&size)[2]) {
+    size[0] = size[1] = 0;
+    for (int l = lowest; l <= p.num_layers; ++l) {
+        int64_t& n = size[(l - zero) & 1];
+        n = std::max(n, (p.layers[(size_t)l].n + klay::kColSlots + 3) / 4 * 4);
+    }
 }
 
 // LDS bytes a workgroup of the persistent kernels may use: the largest of 160, 128 and 64 KB that the
@@ -855,76 +839,76 @@ size_t enable_tail_lds() {
     static_assert(kTailLdsMax == 160 * 1024, "the first size tried is the largest");
     for (int kb : {160, 128, 64}) {
         const int bytes = kb * 1024;
-        hipError_t e = tail_attr<8>(bytes);
-        if (e == hipSuccess) e = tail_attr<4>(bytes);
-        if (e == hipSuccess) e = tail_attr<2>(bytes);
-        if (e == hipSuccess) e = tail_attr<1>(bytes);
+        hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(&klay::col_fwd_kernel), hipFuncAttributeMaxDynamicSharedMemorySize, bytes);
+        if (e == hipSuccess)
+            e = hipFuncSetAttribute(reinterpret_cast<const void*>(&klay::col_bwd_kernel), hipFuncAttributeMaxDynamicSharedMemorySize, bytes);
         if (e == hipSuccess) return (size_t)bytes;
         (void)hipGetLastError();
     }
     return 0;
 }
 
-// `stage`: room for the layer below the kernel's first one in column-major form.  When that layer fits an LDS
-// array (the arrays are made as long as it, if the LDS has the room) it is transposed there first, so that a
-// workgroup reads its column as one run instead of one float per row.
-void launch_tail_fwd(const klay_circuit* c, const TailChoice& t, const float* act, float* tb, float* stage, int B, int ld,
-                     int semiring, const klay::SlabLeaf& leaf, float* out, hipStream_t s) {
-    const klay::CircuitPlan& p = c->plan;
-    const float* staged = nullptr;
-    int nmax = t.nmax;
-    if (!leaf.w) {
-        const int64_t nb = tail_stage_rows(c, t);
-        if (nb > 0) {
-            nmax = (int)std::max<int64_t>(nb, t.nmax);
-            dim3 tg((unsigned)((nb + 31) / 32), (unsigned)((B + 31) / 32));
-            hipLaunchKernelGGL(klay::rows_to_cols_kernel, tg, dim3(256), 0, s,
-                               act + (size_t)c->dl[(size_t)t.first - 1].row0 * ld, (int)nb, B, ld, stage);
-            staged = stage;
-        }
+// The column-major value buffer of a persistent forward launch: `T` floats a column.  `at`: entry of the layer below
+// its first one, -1 if that layer has no place there.
+struct TailBuffer {
+    int64_t T = 0, at = -1;
+};
+TailBuffer tail_buffer(const klay_circuit* c, const TailChoice& t) {
+    TailBuffer b;
+    b.T = c->tail_rows;
+    const int64_t staged = tail_stage_rows(c, t);
+    if (staged > 0) {
+        b.at = c->plan.col_off[(size_t)t.first - 1];
+        if (t.first == c->plan.tail_first) b.T += staged;       // after the layers that take part
     }
-    const klay::SlabLayer* descs = c->d_tail + (t.first - p.tail_first);
-    const int n_layers = p.num_layers - t.first + 1;
-    const int first_is_and = t.first & 1;
-    const size_t lds = (size_t)2 * (nmax + 1) * t.ct * sizeof(float);
-    dim3 grid((unsigned)((B + t.ct - 1) / t.ct));
-#define KLAY_TAIL_FWD(CT)                                                                              \
-    hipLaunchKernelGGL((klay::slab_fwd_kernel<CT>), grid, dim3(klay::kSlabThreads), lds, s, descs,     \
-                       n_layers, first_is_and, c->d_index, act, B, ld, semiring, nmax, tb, (int)c->tail_rows, leaf, \
-                       c->d_root_pos, p.num_roots, out, staged)
-    switch (t.ct) {
-    case 8: KLAY_TAIL_FWD(8); break;
-    case 4: KLAY_TAIL_FWD(4); break;
-    case 2: KLAY_TAIL_FWD(2); break;
-    default: KLAY_TAIL_FWD(1); break;
-    }
-#undef KLAY_TAIL_FWD
+    return b;
 }
 
-// The kernel leaves the adjoints of its first layer column-major in `g_cols` (B runs of n_first floats); they are
-// transposed into the rows of g_out afterwards.
-void launch_tail_bwd(const klay_circuit* c, const TailChoice& t, const float* tb, const float* dout,
-                     float* g_cols, float* g_out, const uint32_t* top_multi, int B, int ld, hipStream_t s) {
+// tb: the column-major buffer; its last columns' room is followed by that of the layer below (workspace_layout), so
+// T may count that layer.  keep: the values are kept there for a reverse sweep (otherwise only that layer goes there).
+void launch_tail_fwd(const klay_circuit* c, const TailChoice& t, const float* act, float* tb, bool keep, int B, int ld,
+                     int semiring, const klay::SlabLeaf& leaf, float* out, hipStream_t s) {
     const klay::CircuitPlan& p = c->plan;
-    const klay::SlabLayer* descs = c->d_tail + (t.first - p.tail_first);
-    const int n_layers = p.num_layers - t.first + 1;
-    const int first_is_and = t.first & 1;
-    const size_t lds = (size_t)2 * (t.nmax + 1) * t.ct * sizeof(float);
-    dim3 grid((unsigned)((B + t.ct - 1) / t.ct));
-#define KLAY_TAIL_BWD(CT)                                                                              \
-    hipLaunchKernelGGL((klay::slab_bwd_kernel<CT>), grid, dim3(klay::kSlabThreads), lds, s, descs,     \
-                       n_layers, first_is_and, c->d_index, dout, c->d_top_ptr, c->d_top_root,          \
-                       p.num_roots, g_cols, B, t.nmax, tb, (int)c->tail_rows, top_multi)
-    switch (t.ct) {
-    case 8: KLAY_TAIL_BWD(8); break;
-    case 4: KLAY_TAIL_BWD(4); break;
-    case 2: KLAY_TAIL_BWD(2); break;
-    default: KLAY_TAIL_BWD(1); break;
+    const TailBuffer buf = tail_buffer(c, t);
+    const int nb = (int)p.layers[(size_t)t.first - 1].n;
+    const float* start = act + (size_t)c->dl[(size_t)t.first - 1].row0 * ld;
+    int start_T = 0;
+    if (!leaf.w && buf.at >= 0) {
+        dim3 tg((unsigned)((nb + 31) / 32), (unsigned)((B + 31) / 32));
+        hipLaunchKernelGGL(klay::rows_to_cols_kernel, tg, dim3(256), 0, s, start, nb, B, ld, tb + buf.at, (int)buf.T);
+        start = tb + buf.at;
+        start_T = (int)buf.T;
     }
-#undef KLAY_TAIL_BWD
-    const int n_first = (int)p.layers[(size_t)t.first].n;
-    dim3 tgrid((unsigned)((n_first + 31) / 32), (unsigned)((ld + 31) / 32));
-    hipLaunchKernelGGL(klay::tb_to_rows_kernel, tgrid, dim3(256), 0, s, g_cols, n_first, 0, n_first, B, ld, g_out);
+    int64_t size[2];
+    tail_lds(p, t.first - 1, t.first - 1, size);
+    hipLaunchKernelGGL(klay::col_fwd_kernel, dim3((unsigned)B), dim3(klay::kColThreads), (size_t)(size[0] + size[1]) * sizeof(float), s,
+                       c->d_tail + (t.first - p.tail_first), p.num_layers - t.first + 1, t.first & 1, c->d_blocks[0], c->n_blocks[0], c->d_tables, start,
+                       nb, start_T, B, ld, semiring, (int)size[0], keep ? tb : nullptr, (int)buf.T, leaf, c->d_root_pos, p.num_roots, out);
+}
+
+// Reverse sweep of the layers L .. first into layer `last` (first, or the layer below it); last_at: its entry in a
+// column of the value buffer (-1: layer 0, whose values the sweep does not need).
+void launch_tail_bwd(const klay_circuit* c, int last, int last_at, const float* tb, int T, const float* dout, const uint32_t* top_multi,
+                     const klay::ColBwdOut& res, int B, int ld, hipStream_t s) {
+    const klay::CircuitPlan& p = c->plan;
+    const int L = p.num_layers;
+    int64_t size[2];
+    tail_lds(p, last, L, size);
+    // The own values of the first steps (narrow layers) are loaded at once, into LDS that only the wider layers
+    // further down need: as many steps as fit behind the rows of one of the two arrays.
+    int cached = 0, cache_at = 0;
+    int64_t rows[2] = {0, 0}, sum = 0;
+    for (int l = L; l > last + 1; --l) {                  // step from layer l into layer l - 1
+        for (int m : {l, l - 1}) rows[(L - m) & 1] = std::max(rows[(L - m) & 1], p.layers[(size_t)m].n + klay::kColSlots);
+        sum += p.layers[(size_t)l - 1].n;
+        const int a = size[0] - rows[0] > size[1] - rows[1] ? 0 : 1;
+        if (sum > size[a] - rows[a]) break;
+        cached = L - l + 1;
+        cache_at = (int)((a ? size[0] : 0) + size[a] - sum);
+    }
+    hipLaunchKernelGGL(klay::col_bwd_kernel, dim3((unsigned)B), dim3(klay::kColThreads), (size_t)(size[0] + size[1]) * sizeof(float), s,
+                       c->d_tail + (L - p.tail_first), L - last, last_at, L & 1, c->d_blocks[1], c->n_blocks[1], c->d_tables, dout, c->d_top_ptr,
+                       c->d_top_root, p.num_roots, B, ld, (int)size[0], cached, cache_at, tb, T, top_multi, res);
 }
 
 // Values of layers first .. last (all run by the persistent forward kernel) from the column-major
@@ -936,7 +920,7 @@ void launch_tb_to_rows(const klay_circuit* c, int first, int last, const float* 
     for (int l = first; l <= last; ++l) n_rows += p.layers[(size_t)l].n;
     if (n_rows <= 0) return;
     dim3 grid((unsigned)((n_rows + 31) / 32), (unsigned)((ld + 31) / 32));
-    hipLaunchKernelGGL(klay::tb_to_rows_kernel, grid, dim3(256), 0, s, tb, (int)c->tail_rows, (int)tb_first, (int)n_rows, B,
+    hipLaunchKernelGGL(klay::tb_to_rows_kernel, grid, dim3(256), 0, s, tb, (int)c->last_tail_T, (int)tb_first, (int)n_rows, B,
                        ld, act + (size_t)c->dl[(size_t)first].row0 * ld);
 }
 
@@ -961,7 +945,7 @@ double tail_min_bytes(const klay_circuit* c, int first, int B, bool backward) {
     double bytes = 0;
     for (int l = first; l <= c->plan.num_layers; ++l) {
         const klay::LayerPlan& lay = c->plan.layers[(size_t)l];
-        bytes += 4.0 * B * (double)lay.n + 4.0 * (double)(backward ? lay.slab_bwd.ent.size() : lay.slab_fwd.ent.size());
+        bytes += 4.0 * B * (double)lay.n + 4.0 * (double)(backward ? lay.col_bwd.blocks.size() : lay.col_fwd.blocks.size());
     }
     bytes += 4.0 * B * (double)(backward ? c->plan.layers[(size_t)first].n : c->plan.layers[(size_t)first - 1].n);
     return bytes;
@@ -1344,7 +1328,7 @@ klay_status klay_build_ex(int32_t num_vars, int64_t num_nodes, const uint8_t* no
     if (c->plan.tail_first > 0) {
         // sizes of the persistent kernels' buffers (part of the workspace, so host-only handles know them too)
         const klay::CircuitPlan& p = c->plan;
-        for (int l = p.tail_first; l <= p.num_layers; ++l) c->tail_rows += p.layers[(size_t)l].n;
+        c->tail_rows = p.col_rows;
     }
     if (device >= 0) {
         int ndev = 0;
@@ -1662,7 +1646,7 @@ static klay_status forward_impl(klay_circuit* c, const float* leaf_weights, cons
         }
         prof.begin(KLAY_K_TAIL_FWD, tail_alg_bytes(c, tail.first, B, false) + 8.0 * B * p.num_roots,
                    tail_min_bytes(c, tail.first, B, false) + 4.0 * B * p.num_roots);
-        launch_tail_fwd(c, tail, act, ws + lay.tb, ws + lay.stage, B, g.ld, (int)semiring, leaf, out, s);
+        launch_tail_fwd(c, tail, act, ws + lay.tb, !static_ws, B, g.ld, (int)semiring, leaf, out, s);
         prof.end();
     } else {
         prof.begin(KLAY_K_ROOT, 8.0 * B * p.num_roots);
@@ -1681,6 +1665,9 @@ static klay_status forward_impl(klay_circuit* c, const float* leaf_weights, cons
     c->last_neg_explicit = neg_weights != nullptr;
     c->last_ws_has_bwd = with_bwd;
     c->last_tail_first = tail.first;
+    const TailBuffer buf = tail.first > 0 ? tail_buffer(c, tail) : TailBuffer();
+    c->last_tail_T = (int32_t)buf.T;
+    c->last_tail_staged = buf.at >= 0;
     return KLAY_OK;
 }
 
@@ -1792,24 +1779,51 @@ static klay_status backward_impl(klay_circuit* c, const float* dout, float* dlea
         const bool one = kOneGather && c->one_gather;
         auto encoded = [&](int l) { return one && l >= 2 && (l & 1) == 0 && c->dl[(size_t)l].has_multi; };
 
-        // the layers the forward pass ran in the persistent kernel are swept by its reverse counterpart,
-        // which seeds the adjoints itself and leaves those of its first layer in gcur
+        // The layers the forward pass ran in the persistent kernel are swept by its reverse counterpart, which
+        // seeds the adjoints itself.  Where it can it also takes the step into the layer below them: to the leaves,
+        // whose gradients it then writes itself, or into a layer whose values are in the column-major buffer.
         int top = L;
+        const int first = c->last_tail_first;
         // (its adjoints of OR nodes are in the one-gather form throughout, so it needs that form to be in use)
-        const TailChoice tail = one ? choose_tail_bwd(c, B, c->last_tail_first) : TailChoice();
-        if (c->last_tail_first > 0) {
-            // the ordinary launches below read values of layers last_tail_first .. top as rows of the
-            // activation buffer; the persistent forward kernel kept them column-major
-            const int last_needed = tail.first > 0 ? tail.first : L;
-            launch_tb_to_rows(c, c->last_tail_first, last_needed, ws + lay.tb, act, B, g.ld, s);
-        }
-        if (tail.first > 0) {
-            prof.begin(KLAY_K_TAIL_BWD, tail_alg_bytes(c, tail.first, B, true) + 4.0 * B * R,
-                       tail_min_bytes(c, tail.first, B, true) + 4.0 * B * R);
-            launch_tail_bwd(c, tail, ws + lay.tb, dout, gnext, gcur, encoded(L) ? c->dl[(size_t)L].multi : nullptr, B, g.ld, s);
+        if (one && first > 0) {
+            int last = first;
+            float* cols = gnext;                       // its last layer's adjoints, column-major
+            if (first == 1) last = 0;
+            else if (c->last_tail_staged) {
+                const int64_t nb = c->dl[(size_t)first - 1].n;
+                if (nb <= top_layer_rows(p)) last = first - 1;
+                else if (first - 1 == B0 && nb <= c->dl[(size_t)B0].row0) { last = first - 1; cols = G; }      // rows not written yet
+            }
+            klay::ColBwdOut res{};
+            res.n_last = (int32_t)c->dl[(size_t)last].n;
+            if (last == 0) {
+                res.wT = wT;
+                res.pos_row = c->d_pos_row;
+                res.neg_row = c->d_neg_row;
+                res.dleaf = dleaf;
+                res.dneg = dneg;
+                res.V = V;
+                res.mode = lits ? 2 : 1;
+            } else {
+                res.g_cols = cols;
+            }
+            prof.begin(KLAY_K_TAIL_BWD, tail_alg_bytes(c, first, B, true) + 4.0 * B * R, tail_min_bytes(c, first, B, true) + 4.0 * B * R);
+            launch_tail_bwd(c, last, last > 0 ? (int)p.col_off[(size_t)last] : -1, ws + lay.tb, c->last_tail_T, dout, encoded(L) ? c->dl[(size_t)L].multi : nullptr, res, B, g.ld, s);
+            if (last > 0) {
+                dim3 tgrid((unsigned)((res.n_last + 31) / 32), (unsigned)((g.ld + 31) / 32));
+                hipLaunchKernelGGL(klay::tb_to_rows_kernel, tgrid, dim3(256), 0, s, cols, res.n_last, 0, res.n_last, B, g.ld,
+                                   last == B0 ? grow(B0) : gcur);
+            }
             prof.end();
-            top = tail.first;
+            if (last == 0) {
+                KLAY_HIP(hipGetLastError());
+                return KLAY_OK;
+            }
+            top = last;
         } else {
+            // the ordinary launches below read the values the persistent forward kernel kept column-major as rows
+            // of the activation buffer
+            if (first > 0) launch_tb_to_rows(c, first, L, ws + lay.tb, act, B, g.ld, s);
             const bool enc = encoded(L);
             prof.begin(KLAY_K_SEED, 4.0 * B * R + 4.0 * B * (double)c->dl[(size_t)L].n * (enc ? 2.0 : 1.0));
             dim3 grid((unsigned)c->dl[(size_t)L].n);

@@ -729,150 +729,285 @@ __global__ __launch_bounds__(256) void stream_combine_kernel(const int2* __restr
 
 // ---------------------------------------------------------------------------------------------
 // Persistent kernels for the top of the circuit (the layers that taper to the roots; for a small
-// circuit every layer): instead of one launch per layer, a workgroup owns CT batch columns, keeps
-// the values (forward) or the adjoints (reverse) of the current and the previous layer in LDS and
+// circuit every layer): instead of one launch per layer, a workgroup of 16 waves owns one batch column, keeps
+// the values (forward) or the adjoints (reverse) of the layer in hand and of the one below or above in LDS and
 // walks the layers with a barrier in between.  Batch columns are independent, so no grid-wide
-// barrier is needed.
-//   Index vectors stay in global memory, in the form the host builds for these layers: rows in chunks
-// of 64 (one row per lane), a chunk as long as its longest row, and the lines of 64 words that make
-// up the chunks of one wave stored back to back.  A wave therefore streams through one contiguous
-// run of lines per layer, a block of kSlabBlock lines at a time, fetches the next block (at the end
-// of a run: the first block of the next layer's run, so the fetch is in flight across the barrier)
-// before it works on the one in hand, and learns from the end-of-chunk bit of a line, which is the
-// same in all its words, when to close the 64 rows it is working on.  Padding words name the slot one
-// past the last source row, where the identity of the layer's operation is kept, so the inner loop has
-// no test for them.  The rows of these layers are stored sorted by fan-in group, so the rows of a
-// chunk have similar lengths; the 16 waves take the chunks round-robin.
-//   One compute unit evaluates a whole column, so the instruction count per line, not memory, bounds
-// these kernels: a line costs its fetch, one LDS gather and the accumulation.
+// barrier is needed.  Above 256 columns the workgroups take turns on the compute units.
+//   Index vectors stay in global memory, as blocks and tables of runs (ColPlan, layerize.h): one stream of each per
+// wave, contiguous over all layers, so a wave fetches the next block and the next table ahead of the ones it works
+// on, also across the layer barriers.  A table is read one descriptor per lane and broadcast to scalars
+// (readlane); scalar loads would share their wait counter with the LDS gathers.
+//   What bounds these kernels: one compute unit evaluates a whole column, so first the longest wave of each layer
+// (hence several lanes per long row, and shares of equal cost), then the latency of the dependent steps of a row and
+// the control flow around it (hence runs of one kind, 16 gathers of a lane in flight together) and then the
+// instructions per entry, of which a
+// logsumexp entry has most (hence whole rows: one maximum, one exponential per entry, no running rescale).
+//   Measured against one lane per row, chunks dealt in turn and a running logsumexp (forward / forward + backward, log
+// semiring): 85000 nodes, 263000 edges, 20 layers at B = 128: 52 -> 42 us / 211 -> 109 us (there the reverse kernel
+// could not take layers with nodes of more than 64 parents); 467 nodes, 22 layers at B = 4: 19.5 -> 16.4 us.  A
+// narrow layer costs about 2000 cycles of dependent steps, a wide one 5 ns per 64 entries.
 //   A lane owns rows of one batch column, so writing values into the row-major activation buffer
 // would cost one cache line per lane.  The values go to a column-major buffer tb[column][T] instead
 // (T = rows of all candidate layers), where consecutive lanes write consecutive floats; the reverse
 // kernel reads it the same way, and rows that an ordinary launch needs are transposed back on demand
 // (tb_to_rows_kernel).
-//   LDS (floats): forward 2 * (nmax + 1) * CT, reverse 4 * (nmax + 1) * CT.
 // ---------------------------------------------------------------------------------------------
-constexpr int kSlabThreads = 64 * kSlabWaves;      // kSlabWaves, kSlabBlock: the plan's format constants (layerize.h)
-constexpr int kSlabD = kSlabBlock;
-
-struct SlabLayer {
-    int32_t n, n_below;            // nodes of this layer and of the layer below
-    int32_t tb_off;                // first entry of this layer in a column of tb
-    int32_t reserved;
-    // Per wave: where its run of lines for this layer starts (offset in ints into the index buffer) and
-    // how many lines it has (a multiple of kSlabD).  The runs of one wave for consecutive layers are
-    // stored back to back, bottom-up for the forward sweep and top-down for the reverse one, with a
-    // block of padding lines after the last, so a wave fetches ahead through one contiguous stream.
-    int32_t fwd_start[kSlabWaves], fwd_count[kSlabWaves];
-    int32_t bwd_start[kSlabWaves], bwd_count[kSlabWaves];
-    int64_t row0, row0_below;      // first activation rows
+constexpr int kColThreads = 64 * kSlabWaves;
+// a layer: its nodes, its first entry in a column of the value buffer, and where the streams of the 16 waves start
+// (blocks, tables; bwd: of the step into the layer below)
+struct ColLayer {
+    int32_t n, at;
+    int32_t fwd_block[kSlabWaves], fwd_table[kSlabWaves];
+    int32_t bwd_block[kSlabWaves], bwd_table[kSlabWaves];
 };
 
-// identity of a layer's forward operation: the value kept in the padding slot of its source array
-__device__ __forceinline__ float slab_identity(int semiring, bool is_and) {
-    if (semiring == 0) return is_and ? 1.0f : 0.0f;
-    return is_and ? 0.0f : -INFINITY;
-}
+typedef uint32_t Line __attribute__((ext_vector_type(4)));       // a lane's 16 bytes of a line
+typedef uint32_t Desc __attribute__((ext_vector_type(2)));
 
-// one block of lines starting at p (this lane's word of the first of them)
-__device__ __forceinline__ void slab_fetch(uint32_t (&a)[kSlabD], const uint32_t* p) {
-#pragma unroll
-    for (int u = 0; u < kSlabD; ++u) a[u] = p[u * 64];
-}
+// a wave's place in its two streams: the block and the table in flight
+struct ColWalk {
+    const Line* q;
+    const Desc* d;
+    Line r0, r1;
+    Desc ahead;
 
-// One block of one layer, forward: works on the lines in `a` while the block at `fetch` travels into `b`.
-template <int OP, int CT, bool FG>
-__device__ __forceinline__ void slab_fwd_block(const uint32_t (&a)[kSlabD], uint32_t (&b)[kSlabD], const uint32_t* fetch,
-                                               int n_rows, int n_below, int& q, float (&acc)[CT], float (&mx)[CT],
-                                               const float* prev, float* cur, const float* __restrict__ below, int ld,
-                                               int nact, float* __restrict__ tb_col, int T) {
-    slab_fetch(b, fetch);
-    float x[kSlabD][CT];
-#pragma unroll
-    for (int u = 0; u < kSlabD; ++u) {
-        const int ch = (int)(a[u] & kIdMask);
-#pragma unroll
-        for (int k = 0; k < CT; ++k) {
-            if (FG) {
-                // sources in global memory: a padding word (source n_below) must not be followed
-                const bool live = ch != n_below && k < nact;
-                const float v = below[(size_t)(live ? ch : 0) * ld + (live ? k : 0)];
-                x[u][k] = live ? v : dead_value<OP>();
-            } else {
-                // byte offset of the source's CT values: the shift drops the end-of-chunk bit, the only flag
-                // of a forward stream (CT = 1, 2, 4, 8: at least the top two bits go)
-                constexpr int kShift = CT == 1 ? 2 : (CT == 2 ? 3 : (CT == 4 ? 4 : 5));
-                x[u][k] = *reinterpret_cast<const float*>(reinterpret_cast<const char*>(prev) + (a[u] << kShift) + 4 * k);
-            }
-        }
+    __device__ __forceinline__ void start(const Line* blocks, const Desc* tables) {
+        q = blocks;
+        d = tables;
+        r0 = q[0];
+        r1 = q[64];
+        ahead = *d;
     }
+    __device__ __forceinline__ void block(Line& w0, Line& w1) {
+        w0 = r0;
+        w1 = r1;
+        q += 128;
+        r0 = q[0];
+        r1 = q[64];
+    }
+    __device__ __forceinline__ Desc table() {
+        const Desc t = ahead;
+        d += kDescTable;
+        ahead = *d;
+        return t;
+    }
+};
+
+// a run, from its descriptor in the table
+struct ColRun {
+    int slot, rows, k, kind, blocks;
+    __device__ __forceinline__ bool read(ColWalk& walk, Desc& table, int& i) {
+        i = __builtin_amdgcn_readfirstlane(i);
+        uint32_t a = (uint32_t)__builtin_amdgcn_readlane((int)table.x, i), b = (uint32_t)__builtin_amdgcn_readlane((int)table.y, i);
+        if ((b & 0xFFFFu) == 0) {
+            if (a == 0) return false;
+            table = walk.table();
+            i = 0;
+            a = (uint32_t)__builtin_amdgcn_readlane((int)table.x, 0);
+            b = (uint32_t)__builtin_amdgcn_readlane((int)table.y, 0);
+        }
+        ++i;
+        slot = (int)a;
+        rows = (int)(b & 0xFFFFu);
+        k = (int)((b >> 16) & 15u);
+        kind = (int)((b >> 20) & 15u);
+        blocks = (int)(b >> 24);
+        return true;
+    }
+};
+
+__device__ __forceinline__ float col_at(const float* values, uint32_t slot) { return values[slot]; }
+
+__device__ __forceinline__ float max3(float a, float b, float c) {
+    float r;
+    asm("v_max3_f32 %0, %1, %2, %3" : "=v"(r) : "v"(a), "v"(b), "v"(c));
+    return r;
+}
+
+// lane i's value from lane i ^ (1 << step), for reductions in which the lanes below that distance already agree
+template <int STEP>
+__device__ __forceinline__ float fly(float x) {
+    constexpr int kCtrl = STEP == 0 ? 0xB1 : STEP == 1 ? 0x4E : STEP == 2 ? 0x141 : 0x140;      // quad_perm, half mirror, mirror
+    if (STEP < 4) return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(x), kCtrl, 0xF, 0xF, true));
+    return __shfl_xor(x, 1 << STEP);
+}
+
+template <int OP>
+__device__ __forceinline__ float col_join(float a, float b) {
+    if (OP == OP_PROD) return a * b;
+    if (OP == OP_MAX || OP == OP_LSE) return b > a ? b : a;      // (OP_LSE: the maxima)
+    return a + b;
+}
+
+// reduce over the 2^k lanes of a row; every lane of the row ends with the result
+template <int OP>
+__device__ __forceinline__ float col_fly(float x, int k) {
+    if (k >= 1) x = col_join<OP>(x, fly<0>(x));
+    if (k >= 2) x = col_join<OP>(x, fly<1>(x));
+    if (k >= 3) x = col_join<OP>(x, fly<2>(x));
+    if (k >= 4) x = col_join<OP>(x, fly<3>(x));
+    if (k >= 5) x = col_join<OP>(x, fly<4>(x));
+    if (k >= 6) x = col_join<OP>(x, fly<5>(x));
+    return x;
+}
+
+// Logsumexp in the persistent kernel: m = maximum so far, kept finite (between -FLT_MAX and FLT_MAX, so that no
+// difference is inf - inf: a row of impossible children ends as -FLT_MAX + log(0) = -inf, an infinite weight as inf),
+// s = sum of exp(x - m).
+constexpr float kFltMax = 3.402823466e+38f;
+
+__device__ __forceinline__ float finite(float m) { return __builtin_amdgcn_fmed3f(m, -kFltMax, kFltMax); }
+
+// the value of a row of two, of four entries
+template <int OP>
+__device__ __forceinline__ float col_two(float x, float y) {
+    if (OP != OP_LSE) return col_join<OP>(x, y);
+    const float hi = y > x ? y : x, lo = y > x ? x : y;
+    return hi + flog(1.0f + fexp(lo - finite(hi)));
+}
+template <int OP>
+__device__ __forceinline__ float col_four(float x0, float x1, float x2, float x3) {
+    if (OP != OP_LSE) return col_join<OP>(col_join<OP>(x0, x1), col_join<OP>(x2, x3));
+    const float m = finite(max3(max3(x0, x1, x2), x3, -kFltMax));
+    return m + flog((fexp(x0 - m) + fexp(x1 - m)) + (fexp(x2 - m) + fexp(x3 - m)));
+}
+
+// Reads one word of every 128 bytes of the blocks, shared out among the workgroups of an XCD (every eighth one), so that
+// they are in its L2 when the waves get to them: the workgroups walk the layers in step, and without this the first
+// one to reach a block would wait for the memory behind the L2, a few thousand cycles, at every layer.
+__device__ __forceinline__ void col_touch(const Line* blocks, int n_blocks) {
+    const uint32_t* words = reinterpret_cast<const uint32_t*>(blocks);
+    const int n = n_blocks * 16, share = ((int)gridDim.x + 7) / 8 * kColThreads;
+    for (int i = ((int)blockIdx.x / 8) * kColThreads + (int)threadIdx.x; i < n; i += 4 * share) {
+        uint32_t x[4];
+#pragma unroll
+        for (int j = 0; j < 4; ++j) x[j] = words[(size_t)(i + j * share < n ? i + j * share : i) * 32];
+        asm volatile("" ::"v"(x[0] | x[1] | x[2] | x[3]));
+    }
+}
+
+// The values of the rows that two words (four entries) of a lane stand for: four rows of one entry, two of two, one of four.
+template <int OP, int KIND>
+__device__ __forceinline__ void col_rows(const float* below, uint32_t a, uint32_t b, float* v) {
+    const float x0 = col_at(below, a & 0xFFFFu), x1 = col_at(below, a >> 16), x2 = col_at(below, b & 0xFFFFu), x3 = col_at(below, b >> 16);
+    if (KIND == 0) { v[0] = x0; v[1] = x1; v[2] = x2; v[3] = x3; }
+    if (KIND == 1) { v[0] = col_two<OP>(x0, x1); v[1] = col_two<OP>(x2, x3); }
+    if (KIND == 2) v[0] = col_four<OP>(x0, x1, x2, x3);
+}
+
+// the last rows of a run, in one quarter of a block
+template <int OP, int KIND>
+__device__ __forceinline__ void col_fwd_rest(const float* below, uint32_t a, uint32_t b, float* out, int rows) {
+    constexpr int N = 4 >> KIND;
     const int lane = threadIdx.x & 63;
+    float v[N];
+    col_rows<OP, KIND>(below, a, b, v);
 #pragma unroll
-    for (int u = 0; u < kSlabD; ++u) {
+    for (int i = 0; i < N; ++i) {
+        if (rows >= 64 * (i + 1)) out[64 * i] = v[i];
+        else if (lane + 64 * i < rows) out[64 * i] = v[i];
+    }
+}
+
+// a run of kind 0, 1 or 2
+template <int OP, int KIND>
+__device__ __forceinline__ void col_fwd_short(ColWalk& walk, const float* below, float* out, int rows) {
+    constexpr int N = 4 >> KIND;                     // rows of a lane in a quarter of a block
+    out += threadIdx.x & 63;
+    Line w0, w1;
+    for (; rows >= 256 * N; rows -= 256 * N, out += 256 * N) {
+        walk.block(w0, w1);
+        float v[4 * N];
+        col_rows<OP, KIND>(below, w0.x, w0.y, v);
+        col_rows<OP, KIND>(below, w0.z, w0.w, v + N);
+        col_rows<OP, KIND>(below, w1.x, w1.y, v + 2 * N);
+        col_rows<OP, KIND>(below, w1.z, w1.w, v + 3 * N);
 #pragma unroll
-        for (int k = 0; k < CT; ++k) { float none = 0.0f; accumulate<OP>(acc[k], mx[k], x[u][k], 0.0f, none); }
-        // the end-of-chunk bit is the same in all words of a line
-        if (__builtin_amdgcn_readfirstlane((int)a[u]) & (int)kLast) {
-            const int r = q * 64 + lane;
-            if (r < n_rows) {
-#pragma unroll
-                for (int k = 0; k < CT; ++k) {
-                    const float o = finish<OP>(acc[k], mx[k]);
-                    cur[r * CT + k] = o;
-                    if (k < nact) tb_col[(size_t)k * T + r] = o;
-                }
-            }
-#pragma unroll
-            for (int k = 0; k < CT; ++k) { acc[k] = identity<OP>(); mx[k] = -INFINITY; }
-            q += kSlabWaves;
+        for (int i = 0; i < 4 * N; ++i) out[64 * i] = v[i];
+    }
+    if (rows > 0) {
+        walk.block(w0, w1);
+        col_fwd_rest<OP, KIND>(below, w0.x, w0.y, out, rows);
+        if (rows > 64 * N) col_fwd_rest<OP, KIND>(below, w0.z, w0.w, out + 64 * N, rows - 64 * N);
+        if (rows > 128 * N) {
+            col_fwd_rest<OP, KIND>(below, w1.x, w1.y, out + 128 * N, rows - 128 * N);
+            if (rows > 192 * N) col_fwd_rest<OP, KIND>(below, w1.z, w1.w, out + 192 * N, rows - 192 * N);
         }
     }
 }
 
-// One layer, forward: the `lines` lines at sp (this wave's run).  `a` holds the first block on entry and
-// the block that follows the run (the next layer's first, or padding) on exit.  FG: the sources are rows
-// of the activation buffer in global memory (the layer below the first persistent one), otherwise the
-// previous layer's values in LDS.
-template <int OP, int CT, bool FG>
-__device__ __forceinline__ void slab_fwd_rows(int n_rows, int n_below, const uint32_t* sp, int lines,
-                                              uint32_t (&a)[kSlabD], const float* prev, float* cur,
-                                              const float* __restrict__ below, int ld, int nact,
-                                              float* __restrict__ tb_col, int T) {
-    if (lines <= 0) return;
-    int q = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));      // chunk in hand
-    float acc[CT], mx[CT];
-#pragma unroll
-    for (int k = 0; k < CT; ++k) { acc[k] = identity<OP>(); mx[k] = -INFINITY; }
-    uint32_t b[kSlabD];
-    for (int i = 0;;) {       // two blocks per turn, the two register sets change roles
-        slab_fwd_block<OP, CT, FG>(a, b, sp + (size_t)(i + kSlabD) * 64, n_rows, n_below, q, acc, mx, prev, cur, below, ld, nact, tb_col, T);
-        i += kSlabD;
-        if (i >= lines) {
-#pragma unroll
-            for (int u = 0; u < kSlabD; ++u) a[u] = b[u];
-            break;
-        }
-        slab_fwd_block<OP, CT, FG>(b, a, sp + (size_t)(i + kSlabD) * 64, n_rows, n_below, q, acc, mx, prev, cur, below, ld, nact, tb_col, T);
-        i += kSlabD;
-        if (i >= lines) break;
+// the lanes of a row have (m, s): its value
+__device__ __forceinline__ float col_lse_fly(float m, float s, int k) {
+    if (k > 0) {
+        const float m2 = col_fly<OP_LSE>(m, k);
+        s = col_fly<OP_SUM>(s * fexp(m - m2), k);
+        m = m2;
     }
+    return m + flog(s);
 }
 
-template <int CT, bool FG>
-__device__ __forceinline__ void slab_fwd_layer(int semiring, bool is_and, int n_rows, int n_below, const uint32_t* sp,
-                                               int lines, uint32_t (&a)[kSlabD], const float* prev, float* cur,
-                                               const float* __restrict__ below, int ld, int nact,
-                                               float* __restrict__ tb_col, int T) {
-    if (semiring == 2) {           // (max, +) on log weights
-        if (is_and) slab_fwd_rows<OP_SUM, CT, FG>(n_rows, n_below, sp, lines, a, prev, cur, below, ld, nact, tb_col, T);
-        else slab_fwd_rows<OP_MAX, CT, FG>(n_rows, n_below, sp, lines, a, prev, cur, below, ld, nact, tb_col, T);
-    } else if (semiring == 1) {    // (logsumexp, +)
-        if (is_and) slab_fwd_rows<OP_SUM, CT, FG>(n_rows, n_below, sp, lines, a, prev, cur, below, ld, nact, tb_col, T);
-        else slab_fwd_rows<OP_LSE, CT, FG>(n_rows, n_below, sp, lines, a, prev, cur, below, ld, nact, tb_col, T);
+// one line of a row that takes several lanes or lines, joined to what the lines before gave
+template <int OP>
+__device__ __forceinline__ void col_long(const float* below, Line w, bool fresh, float& m, float& s) {
+    const float x0 = col_at(below, w.x & 0xFFFFu), x1 = col_at(below, w.x >> 16), x2 = col_at(below, w.y & 0xFFFFu), x3 = col_at(below, w.y >> 16);
+    const float x4 = col_at(below, w.z & 0xFFFFu), x5 = col_at(below, w.z >> 16), x6 = col_at(below, w.w & 0xFFFFu), x7 = col_at(below, w.w >> 16);
+    if (OP == OP_LSE) {
+        const float m2 = finite(max3(max3(max3(x0, x1, x2), x3, x4), max3(x5, x6, x7), m));
+        const float s2 = ((fexp(x0 - m2) + fexp(x1 - m2)) + (fexp(x2 - m2) + fexp(x3 - m2))) +
+                         ((fexp(x4 - m2) + fexp(x5 - m2)) + (fexp(x6 - m2) + fexp(x7 - m2)));
+        s = fresh ? s2 : fmaf(s, fexp(m - m2), s2);
+        m = m2;
     } else {
-        if (is_and) slab_fwd_rows<OP_PROD, CT, FG>(n_rows, n_below, sp, lines, a, prev, cur, below, ld, nact, tb_col, T);
-        else slab_fwd_rows<OP_SUM, CT, FG>(n_rows, n_below, sp, lines, a, prev, cur, below, ld, nact, tb_col, T);
+        const float x = col_join<OP>(col_four<OP>(x0, x1, x2, x3), col_four<OP>(x4, x5, x6, x7));
+        s = fresh ? x : col_join<OP>(s, x);
     }
+}
+
+// one layer, forward
+template <int OP>
+__device__ __forceinline__ void col_fwd_layer(ColWalk& walk, const float* below, float* here) {
+    const int lane = threadIdx.x & 63;
+    Desc table = walk.table();
+    ColRun run;
+    for (int i = 0; run.read(walk, table, i);) {
+        float* out = here + run.slot;
+        if (run.kind == 0) col_fwd_short<OP, 0>(walk, below, out, run.rows);
+        else if (run.kind == 1) col_fwd_short<OP, 1>(walk, below, out, run.rows);
+        else if (run.kind == 2) col_fwd_short<OP, 2>(walk, below, out, run.rows);
+        else {
+            const int r = lane >> run.k, per = 64 >> run.k;
+            const bool writes = (lane & ((1 << run.k) - 1)) == 0;
+            for (int rows = run.rows; rows > 0; rows -= per, out += per) {
+                float m = -kFltMax, s = 0.0f;
+                Line w0, w1;
+                walk.block(w0, w1);
+                col_long<OP>(below, w0, true, m, s);
+                if (run.kind == 3) {
+                    col_long<OP>(below, w1, false, m, s);
+                    for (int b = 1; b < run.blocks; ++b) {
+                        walk.block(w0, w1);
+                        col_long<OP>(below, w0, false, m, s);
+                        col_long<OP>(below, w1, false, m, s);
+                    }
+                }
+                s = OP == OP_LSE ? col_lse_fly(m, s, run.k) : col_fly<OP>(s, run.k);
+                if (writes && r < rows) out[r] = s;
+            }
+        }
+    }
+}
+
+// a finished layer's values from LDS to the column-major buffer, by one wave, 16 bytes a lane
+__device__ __forceinline__ void col_move(const float* values, int n, float* __restrict__ to) {
+    typedef float f4u __attribute__((ext_vector_type(4), aligned(4)));
+    const int lane = threadIdx.x & 63;
+    const int whole = n / 4 * 4;
+#pragma unroll 4
+    for (int i = lane * 4; i < whole; i += 256) {
+        const float4 v = *reinterpret_cast<const float4*>(values + i);
+        *reinterpret_cast<f4u*>(to + i) = f4u{v.x, v.y, v.z, v.w};
+    }
+    if (whole + lane < n) to[whole + lane] = values[whole + lane];
 }
 
 __device__ __forceinline__ float log1mexp_f(float x) {
@@ -890,240 +1025,325 @@ struct SlabLeaf {
     int32_t V, n0;
 };
 
-template <int CT>
-__global__ __launch_bounds__(kSlabThreads) void slab_fwd_kernel(const SlabLayer* __restrict__ layers, int n_layers,
-                                                                int first_is_and, const int32_t* __restrict__ ibase,
-                                                                const float* __restrict__ act, int B, int ld,
-                                                                int semiring, int nmax, float* __restrict__ tb, int T,
-                                                                SlabLeaf leaf, const int32_t* __restrict__ root_pos,
-                                                                int R, float* __restrict__ out,
-                                                                const float* __restrict__ stage) {
+// LDS: two value arrays, slots kColSlots + position; size0 floats for the layer below the first one and every second
+// layer from there, the rest for the others.  start_rows / start_at: the layer below the first one (start_rows of them),
+// column-major, T floats a column, from entry start_at on if start_T > 0, otherwise rows of the activation buffer.
+// tb (or null): every layer's values are kept there.
+__global__ __launch_bounds__(kColThreads) void col_fwd_kernel(const ColLayer* __restrict__ first, int n_layers, int first_is_and,
+                                                              const Line* __restrict__ blocks, int n_blocks, const Desc* __restrict__ tables,
+                                                              const float* __restrict__ start, int start_rows, int start_T,
+                                                              int B, int ld, int semiring, int size0, float* __restrict__ tb, int T,
+                                                              SlabLeaf leaf, const int32_t* __restrict__ root_pos, int R,
+                                                              float* __restrict__ out) {
     extern __shared__ float smem[];
-    float* prev = smem;
-    float* cur = smem + (size_t)(nmax + 1) * CT;
+    float* below = smem;
+    float* here = smem + size0;
     const int lane = threadIdx.x & 63;
     const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
-    const int col0 = (int)blockIdx.x * CT;
-    const int nact = B - col0 < CT ? B - col0 : CT;          // active columns of this workgroup (>= 1)
-    float* tb0 = tb + (size_t)col0 * T;
+    const int col = (int)blockIdx.x;
     const bool log_domain = semiring != 0;
-    // this wave's stream of lines; its first block is on its way while the leaf layer is evaluated
-    const uint32_t* sp = reinterpret_cast<const uint32_t*>(ibase) + layers[0].fwd_start[wave] + lane;
-    uint32_t a[kSlabD];
-    slab_fetch(a, sp);
+    ColWalk walk;
+    walk.start(blocks + (size_t)first->fwd_block[wave] * 128 + lane, tables + (size_t)first->fwd_table[wave] * kDescTable + lane);
+    col_touch(blocks, n_blocks);
+    if (threadIdx.x < 2) {
+        // identities of the two kinds of layers, in the slots that padding names
+        float* a = threadIdx.x == 0 ? below : here;
+        a[kColPadAnd] = log_domain ? 0.0f : 1.0f;
+        a[kColPadOr] = log_domain ? -INFINITY : 0.0f;
+    }
     if (leaf.w) {
         // leaf layer into LDS; the transposed weights and the rows of layer 0 also go to global memory
         // for the reverse sweep (every column of [0, ld): the last workgroup zeroes the padding columns)
-        for (int i = threadIdx.x; i < leaf.n0; i += kSlabThreads) {
+        for (int i = threadIdx.x; i < leaf.n0; i += kColThreads) {
             const int code = leaf.leaf_code[i];
-#pragma unroll
-            for (int k = 0; k < CT; ++k) {
-                float v = 0.0f;
-                if (k < nact) {
-                    if (code == INT32_MAX) v = log_domain ? 0.0f : 1.0f;
-                    else if (code == INT32_MIN) v = log_domain ? -INFINITY : 0.0f;
-                    else {
-                        const int var = (code > 0 ? code : -code) - 1;
-                        const size_t at = (size_t)(col0 + k) * leaf.V + var;
-                        if (code > 0) v = leaf.w[at];
-                        else if (leaf.wneg) v = leaf.wneg[at];
-                        else v = log_domain ? log1mexp_f(leaf.w[at]) : 1.0f - leaf.w[at];
-                    }
-                    leaf.act0[(size_t)i * ld + col0 + k] = v;
-                }
-                prev[i * CT + k] = v;
+            float v;
+            if (code == INT32_MAX) v = log_domain ? 0.0f : 1.0f;
+            else if (code == INT32_MIN) v = log_domain ? -INFINITY : 0.0f;
+            else {
+                const int var = (code > 0 ? code : -code) - 1;
+                const size_t at = (size_t)col * leaf.V + var;
+                if (code > 0) v = leaf.w[at];
+                else if (leaf.wneg) v = leaf.wneg[at];
+                else v = log_domain ? log1mexp_f(leaf.w[at]) : 1.0f - leaf.w[at];
             }
-            if (blockIdx.x == gridDim.x - 1)
-                for (int b = B; b < ld; ++b) leaf.act0[(size_t)i * ld + b] = 0.0f;
+            below[kColSlots + i] = v;
+            if (tb) {
+                leaf.act0[(size_t)i * ld + col] = v;
+                if (col == B - 1)
+                    for (int b = B; b < ld; ++b) leaf.act0[(size_t)i * ld + b] = 0.0f;
+            }
         }
-        for (int v = threadIdx.x; v < leaf.V; v += kSlabThreads) {
-            for (int k = 0; k < nact; ++k) leaf.wT[(size_t)v * ld + col0 + k] = leaf.w[(size_t)(col0 + k) * leaf.V + v];
-            if (blockIdx.x == gridDim.x - 1)
-                for (int b = B; b < ld; ++b) leaf.wT[(size_t)v * ld + b] = 0.0f;
-        }
-        if (threadIdx.x < CT) prev[leaf.n0 * CT + threadIdx.x] = slab_identity(semiring, first_is_and != 0);
-        __syncthreads();
+        if (tb)
+            for (int v = threadIdx.x; v < leaf.V; v += kColThreads) {
+                leaf.wT[(size_t)v * ld + col] = leaf.w[(size_t)col * leaf.V + v];
+                if (col == B - 1)
+                    for (int b = B; b < ld; ++b) leaf.wT[(size_t)v * ld + b] = 0.0f;
+            }
+    } else {
+        for (int i = threadIdx.x; i < start_rows; i += kColThreads)
+            below[kColSlots + i] = start_T > 0 ? start[(size_t)col * start_T + i] : start[(size_t)i * ld + col];
     }
-    if (!leaf.w && stage) {
-        // the layer below the first one, column-major in `stage` (B runs of n_below floats, written by
-        // rows_to_cols_kernel): into LDS with consecutive lanes reading consecutive floats
-        const int nb0 = layers[0].n_below;
-        for (int i = threadIdx.x; i < nb0; i += kSlabThreads)
-#pragma unroll
-            for (int k = 0; k < CT; ++k) prev[i * CT + k] = k < nact ? stage[(size_t)(col0 + k) * nb0 + i] : 0.0f;
-        if (threadIdx.x < CT) prev[nb0 * CT + threadIdx.x] = slab_identity(semiring, first_is_and != 0);
-        __syncthreads();
-    }
-    // the few numbers a layer needs are read a layer ahead
-    int lines = layers[0].fwd_count[wave], n_rows = layers[0].n, n_below = layers[0].n_below, tb_off = layers[0].tb_off;
+    float* tbc = tb ? tb + (size_t)col * T : nullptr;
     for (int t = 0; t < n_layers; ++t) {
         const bool is_and = ((t & 1) == 0) == (first_is_and != 0);
-        const int tn = t + 1 < n_layers ? t + 1 : t;
-        const int lines2 = layers[tn].fwd_count[wave], n_rows2 = layers[tn].n, n_below2 = layers[tn].n_below,
-                  tb_off2 = layers[tn].tb_off;
-        float* tb_col = tb0 + tb_off;
-        // the padding slot of this layer's values, for the layer above (the other operation)
-        if (threadIdx.x < CT) cur[n_rows * CT + threadIdx.x] = slab_identity(semiring, !is_and);
-        if (t == 0 && !leaf.w && !stage)
-            slab_fwd_layer<CT, true>(semiring, is_and, n_rows, n_below, sp, lines, a, prev, cur,
-                                     act + (size_t)layers[0].row0_below * ld + col0, ld, nact, tb_col, T);
-        else
-            slab_fwd_layer<CT, false>(semiring, is_and, n_rows, n_below, sp, lines, a, prev, cur, nullptr, ld, nact, tb_col, T);
-        sp += (size_t)lines * 64;
-        lines = lines2; n_rows = n_rows2; n_below = n_below2; tb_off = tb_off2;
         __syncthreads();
-        float* tmp = prev; prev = cur; cur = tmp;
+        if (wave == kColFwdWaves) {
+            // the wave that keeps the values, a layer behind the others (in a wave that computes, the wait for the next
+            // lines would wait for the stores as well)
+            if (tbc && t > 0) col_move(below + kColSlots, first[t - 1].n, tbc + first[t - 1].at);
+        } else if (is_and) {
+            if (log_domain) col_fwd_layer<OP_SUM>(walk, below, here);
+            else col_fwd_layer<OP_PROD>(walk, below, here);
+        } else if (semiring == 1) col_fwd_layer<OP_LSE>(walk, below, here);
+        else if (semiring == 2) col_fwd_layer<OP_MAX>(walk, below, here);
+        else col_fwd_layer<OP_SUM>(walk, below, here);
+        float* tmp = below; below = here; here = tmp;
     }
+    __syncthreads();
+    if (wave == kColFwdWaves && tbc) col_move(below + kColSlots, first[n_layers - 1].n, tbc + first[n_layers - 1].at);
     // roots: the top layer is in LDS
-    for (int i = threadIdx.x; i < R * CT; i += kSlabThreads) {
-        const int r = i / CT, k = i % CT;
-        if (k < nact) out[(size_t)(col0 + k) * R + r] = prev[root_pos[r] * CT + k];
-    }
+    for (int r = threadIdx.x; r < R; r += kColThreads) out[(size_t)col * R + r] = below[kColSlots + root_pos[r]];
 }
 
-// One block of one step of the reverse sweep.  OR: the step goes through an OR layer; its weighted edges read the
+// One step of the reverse sweep.  OR: the step goes through an OR layer; its weighted edges (bit 15 of an entry) read the
 // parent's adjoint in the one-gather form (see encode_h) and need the value of the row they belong to.
-// Otherwise every edge passes the adjoint on, and a row that is an OR node with more than one child (kRowFlag
-// on the word the lane holds when the chunk closes) is stored in that form, again with the row's own value.
-// `own` is that value for the row in hand, read from the column-major value buffer (consecutive lanes,
-// consecutive floats) when a chunk opens.
-template <int CT, bool OR>
-__device__ __forceinline__ void slab_bwd_block(const uint32_t (&a)[kSlabD], uint32_t (&b)[kSlabD], const uint32_t* fetch,
-                                               int n_below, int& q, float (&acc)[CT], float (&own)[CT],
-                                               const float* cur, float* nxt, const float* __restrict__ tb_below, int T,
-                                               int nact) {
-    slab_fetch(b, fetch);
-    float g[kSlabD][CT];
+// Otherwise every edge passes the adjoint on, and a row that is an OR node with more than one child (bit 15 of its
+// entries) is stored in that form, again with the row's own value.
+// own: the values of the rows by slot; it may be the array the adjoints go to (a slot is read by the lanes of its row only).
+template <bool OR>
+__device__ __forceinline__ float col_bwd_entry(const float* above, uint32_t e, float own) {
+    const float g = col_at(above, e & 0x7FFFu);
+    return OR && (e & 0x8000u) ? decode_h(g, own) : g;
+}
+
+// the adjoints of the rows that two words (four entries) of a lane stand for; own: their values
+template <bool OR, int KIND>
+__device__ __forceinline__ void col_bwd_rows(const float* above, uint32_t a, uint32_t b, const float* own, float* v) {
+    constexpr int N = 4 >> KIND;
+    const float o0 = own[0], o1 = own[KIND == 0 ? 1 : 0], o2 = own[KIND == 0 ? 2 : KIND == 1 ? 1 : 0], o3 = own[KIND == 0 ? 3 : KIND == 1 ? 1 : 0];
+    const float x0 = col_bwd_entry<OR>(above, a & 0xFFFFu, o0), x1 = col_bwd_entry<OR>(above, a >> 16, o1);
+    const float x2 = col_bwd_entry<OR>(above, b & 0xFFFFu, o2), x3 = col_bwd_entry<OR>(above, b >> 16, o3);
+    if (KIND == 0) { v[0] = x0; v[1] = x1; v[2] = x2; v[3] = x3; }
+    if (KIND == 1) { v[0] = x0 + x1; v[1] = x2 + x3; }
+    if (KIND == 2) v[0] = (x0 + x1) + (x2 + x3);
+    if (!OR) {
+        const uint32_t e[4] = {a, KIND == 0 ? a >> 16 : b, b, b >> 16};
 #pragma unroll
-    for (int u = 0; u < kSlabD; ++u) {
-        const int p = (int)(a[u] & kIdMask);          // a padding word names the slot past the last parent: adjoint 0
-#pragma unroll
-        for (int k = 0; k < CT; ++k) g[u][k] = cur[p * CT + k];
+        for (int i = 0; i < N; ++i) v[i] = (e[i] & 0x8000u) ? encode_h(v[i], own[i]) : v[i];
     }
+}
+
+// a quarter of a block (FULL: all its rows are there)
+template <bool OR, int KIND, bool FULL>
+__device__ __forceinline__ void col_bwd_quarter(const float* above, uint32_t a, uint32_t b, const float* own_at, float* out, int rows) {
+    constexpr int N = 4 >> KIND;
     const int lane = threadIdx.x & 63;
+    float v[N], own[N];
 #pragma unroll
-    for (int u = 0; u < kSlabD; ++u) {
-        // an unweighted edge (chain node or single-child OR above) passes the adjoint unchanged
-        const bool weighted = OR && (a[u] & kWeighted) != 0;
+    for (int i = 0; i < N; ++i) own[i] = own_at[FULL || lane + 64 * i < rows ? 64 * i : -lane];
+    col_bwd_rows<OR, KIND>(above, a, b, own, v);
 #pragma unroll
-        for (int k = 0; k < CT; ++k) acc[k] += weighted ? decode_h(g[u][k], own[k]) : g[u][k];
-        if (__builtin_amdgcn_readfirstlane((int)a[u]) & (int)kLast) {
-            const int r = q * 64 + lane;
-            if (r < n_below) {
-                const bool enc = !OR && (a[u] & kRowFlag) != 0;
-#pragma unroll
-                for (int k = 0; k < CT; ++k) nxt[r * CT + k] = enc ? encode_h(acc[k], own[k]) : acc[k];
-            }
-            q += kSlabWaves;
-            const int r2 = q * 64 + lane;
-#pragma unroll
-            for (int k = 0; k < CT; ++k) {
-                acc[k] = 0.0f;
-                own[k] = (r2 < n_below && k < nact) ? tb_below[(size_t)k * T + r2] : 0.0f;
+    for (int i = 0; i < N; ++i) {
+        if (FULL || rows >= 64 * (i + 1)) out[64 * i] = v[i];
+        else if (lane + 64 * i < rows) out[64 * i] = v[i];
+    }
+}
+
+// a run of kind 0, 1 or 2
+template <bool OR, int KIND>
+__device__ __forceinline__ void col_bwd_short(ColWalk& walk, const float* above, const float* own_at, float* out, int rows) {
+    constexpr int N = 4 >> KIND;
+    out += threadIdx.x & 63;
+    own_at += threadIdx.x & 63;
+    Line w0, w1;
+    for (; rows >= 256 * N; rows -= 256 * N, out += 256 * N, own_at += 256 * N) {
+        walk.block(w0, w1);
+        col_bwd_quarter<OR, KIND, true>(above, w0.x, w0.y, own_at, out, 0);
+        col_bwd_quarter<OR, KIND, true>(above, w0.z, w0.w, own_at + 64 * N, out + 64 * N, 0);
+        col_bwd_quarter<OR, KIND, true>(above, w1.x, w1.y, own_at + 128 * N, out + 128 * N, 0);
+        col_bwd_quarter<OR, KIND, true>(above, w1.z, w1.w, own_at + 192 * N, out + 192 * N, 0);
+    }
+    if (rows > 0) {
+        walk.block(w0, w1);
+        col_bwd_quarter<OR, KIND, false>(above, w0.x, w0.y, own_at, out, rows);
+        if (rows > 64 * N) col_bwd_quarter<OR, KIND, false>(above, w0.z, w0.w, own_at + 64 * N, out + 64 * N, rows - 64 * N);
+        if (rows > 128 * N) {
+            col_bwd_quarter<OR, KIND, false>(above, w1.x, w1.y, own_at + 128 * N, out + 128 * N, rows - 128 * N);
+            if (rows > 192 * N) col_bwd_quarter<OR, KIND, false>(above, w1.z, w1.w, own_at + 192 * N, out + 192 * N, rows - 192 * N);
+        }
+    }
+}
+
+template <bool OR>
+__device__ __forceinline__ float col_bwd_long(const float* above, Line w, float own) {
+    return ((col_bwd_entry<OR>(above, w.x & 0xFFFFu, own) + col_bwd_entry<OR>(above, w.x >> 16, own)) +
+            (col_bwd_entry<OR>(above, w.y & 0xFFFFu, own) + col_bwd_entry<OR>(above, w.y >> 16, own))) +
+           ((col_bwd_entry<OR>(above, w.z & 0xFFFFu, own) + col_bwd_entry<OR>(above, w.z >> 16, own)) +
+            (col_bwd_entry<OR>(above, w.w & 0xFFFFu, own) + col_bwd_entry<OR>(above, w.w >> 16, own)));
+}
+
+template <bool OR>
+__device__ __forceinline__ void col_bwd_layer(ColWalk& walk, const float* above, float* here, const float* owns) {
+    const int lane = threadIdx.x & 63;
+    Desc table = walk.table();
+    ColRun run;
+    for (int i = 0; run.read(walk, table, i);) {
+        float* out = here + run.slot;
+        const float* own_at = owns + run.slot;
+        if (run.kind == 0) col_bwd_short<OR, 0>(walk, above, own_at, out, run.rows);
+        else if (run.kind == 1) col_bwd_short<OR, 1>(walk, above, own_at, out, run.rows);
+        else if (run.kind == 2) col_bwd_short<OR, 2>(walk, above, own_at, out, run.rows);
+        else {
+            const int r = lane >> run.k, per = 64 >> run.k;
+            const bool writes = (lane & ((1 << run.k) - 1)) == 0;
+            for (int rows = run.rows; rows > 0; rows -= per, out += per, own_at += per) {
+                const float own = own_at[r < rows ? r : 0];
+                Line w0, w1;
+                walk.block(w0, w1);
+                const uint32_t flag = w0.x & 0x8000u;
+                float acc = col_bwd_long<OR>(above, w0, own);
+                if (run.kind == 3) {
+                    acc += col_bwd_long<OR>(above, w1, own);
+                    for (int b = 1; b < run.blocks; ++b) {
+                        walk.block(w0, w1);
+                        acc += col_bwd_long<OR>(above, w0, own) + col_bwd_long<OR>(above, w1, own);
+                    }
+                }
+                acc = col_fly<OP_SUM>(acc, run.k);
+                if (!OR && flag) acc = encode_h(acc, own);
+                if (writes && r < rows) out[r] = acc;
             }
         }
     }
 }
 
-template <int CT, bool OR>
-__device__ __forceinline__ void slab_bwd_rows(int n_below, const uint32_t* sp, int lines, uint32_t (&a)[kSlabD],
-                                              const float* cur, float* nxt, const float* __restrict__ tb_below, int T,
-                                              int nact) {
-    if (lines <= 0) return;
-    int q = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
-    const int lane = threadIdx.x & 63;
-    float acc[CT], own[CT];
-#pragma unroll
-    for (int k = 0; k < CT; ++k) {
-        acc[k] = 0.0f;
-        const int r = q * 64 + lane;
-        own[k] = (r < n_below && k < nact) ? tb_below[(size_t)k * T + r] : 0.0f;
-    }
-    uint32_t b[kSlabD];
-    for (int i = 0;;) {
-        slab_bwd_block<CT, OR>(a, b, sp + (size_t)(i + kSlabD) * 64, n_below, q, acc, own, cur, nxt, tb_below, T, nact);
-        i += kSlabD;
-        if (i >= lines) {
-#pragma unroll
-            for (int u = 0; u < kSlabD; ++u) a[u] = b[u];
-            break;
-        }
-        slab_bwd_block<CT, OR>(b, a, sp + (size_t)(i + kSlabD) * 64, n_below, q, acc, own, cur, nxt, tb_below, T, nact);
-        i += kSlabD;
-        if (i >= lines) break;
-    }
-}
+// Where the reverse kernel leaves its last layer's adjoints: the leaf gradients themselves (w_T != null, the last
+// layer is layer 0), or g_cols[B][n_last], column-major (a lane owns rows of one column, so row-major stores would be
+// 4 bytes per cache line; tb_to_rows_kernel transposes afterwards).
+struct ColBwdOut {
+    float* g_cols;
+    int32_t n_last;
+    const float* wT;            // [V, ld] transposed leaf weights
+    const int32_t *pos_row, *neg_row;
+    float *dleaf, *dneg;
+    int32_t V, mode;            // mode: as for leaf_bwd_kernel
+};
 
-// Reverse sweep over the same layers (log semiring): seeds the top layer's adjoints from dout, walks
-// down to the first layer of the launch and leaves that layer's adjoints in g_out[B][n_first] (column-major).
-// LDS: the adjoints of the layer in hand and of the one below (two arrays, as in the forward kernel, so both
-// kernels take the same layers); node values come from the column-major buffer tb, once per row.  The adjoints
-// of OR nodes with more than one child are kept in the one-gather form throughout, also in g_out; top_multi
+// Reverse sweep over the same layers (log semiring): seeds the top layer's adjoints from dout and walks n_steps layers
+// down.  LDS: the adjoints of the layer in hand and of the one below, size0 floats for the top layer and every second
+// one from there.  Node values come from the column-major buffer tb, once per row, and are far away (a read of them
+// takes about 2000 cycles, twice as long as a narrow layer): those of the first `cached` steps are loaded at once to
+// cache_at, into LDS that only later steps use; from there on those of the next step's rows are
+// fetched into registers during a step (kColOwn times four per thread: any layer that fits) and put into the slots of the
+// array that the step frees.  (Four at a time: a load instruction of one float a lane takes the memory pipe as long.)  last_at: entry of the last layer in tb (-1: its values are not needed).  The adjoints
+// of OR nodes with more than one child are kept in the one-gather form throughout, also on the way out; top_multi
 // (or null) flags such nodes of the top layer for the seed.
-template <int CT>
-__global__ __launch_bounds__(kSlabThreads) void slab_bwd_kernel(const SlabLayer* __restrict__ layers, int n_layers,
-                                                                int first_is_and, const int32_t* __restrict__ ibase,
-                                                                const float* __restrict__ dout,
-                                                                const int32_t* __restrict__ top_ptr,
-                                                                const int32_t* __restrict__ top_root, int R,
-                                                                float* __restrict__ g_out, int B, int nmax,
-                                                                const float* __restrict__ tb, int T,
-                                                                const uint32_t* __restrict__ top_multi) {
+// (tb is not __restrict__: a load known to be invariant would be moved down past the barrier to its use.)
+constexpr int kColOwn = (int)((kTailRowsCap + 4 * kColThreads - 1) / (4 * kColThreads));
+
+__global__ __launch_bounds__(kColThreads) void col_bwd_kernel(const ColLayer* __restrict__ top, int n_steps, int last_at,
+                                                              int top_is_and, const Line* __restrict__ blocks, int n_blocks,
+                                                              const Desc* __restrict__ tables, const float* __restrict__ dout,
+                                                              const int32_t* __restrict__ top_ptr, const int32_t* __restrict__ top_root,
+                                                              int R, int B, int ld, int size0, int cached, int cache_at,
+                                                              const float* tb, int T,
+                                                              const uint32_t* __restrict__ top_multi, ColBwdOut res) {
     extern __shared__ float smem[];
-    const size_t stride = (size_t)(nmax + 1) * CT;
-    float* cur = smem;
-    float* nxt = smem + stride;
+    float* above = smem;
+    float* here = smem + size0;
     const int lane = threadIdx.x & 63;
     const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
-    const int col0 = (int)blockIdx.x * CT;
-    const int nact = B - col0 < CT ? B - col0 : CT;
-    const float* tb0 = tb + (size_t)col0 * T;
-    // this wave's stream of lines, from the top layer's step downwards
-    const uint32_t* sp = reinterpret_cast<const uint32_t*>(ibase) + layers[n_layers - 1].bwd_start[wave] + lane;
-    uint32_t a[kSlabD];
-    slab_fetch(a, sp);
-    {   // adjoint seed of the top layer
-        const SlabLayer& L = layers[n_layers - 1];
-        for (int i = threadIdx.x; i < L.n; i += kSlabThreads) {
-            const bool enc = top_multi && ((top_multi[i >> 5] >> (i & 31)) & 1u);
+    const int col = (int)blockIdx.x;
+    const float* tbc = tb + (size_t)col * T;
+    ColWalk walk;
+    walk.start(blocks + (size_t)top->bwd_block[wave] * 128 + lane, tables + (size_t)top->bwd_table[wave] * kDescTable + lane);
+    col_touch(blocks, n_blocks);
+    // own values of the rows of step t (the t-th layer below the top one): how many and where
+    auto own_of = [&](int t, int& n, int& at) {
+        n = at = 0;
+        if (t + 1 < n_steps) { n = top[-1 - t].n; at = top[-1 - t].at; }
+        else if (t < n_steps && last_at >= 0) { n = res.n_last; at = last_at; }
+    };
+    if (threadIdx.x < 2) (threadIdx.x == 0 ? above : here)[kColPadAnd] = 0.0f;       // what padding names: adjoint 0
+    const int n_top = top->n, top_at = top->at;
+    int cache_low = 0;
+    if (cached > 0) {
+        // the cached layers follow one another in tb
+        cache_low = top[-cached].at;
+        const int n = top_at - cache_low;
+        for (int i = threadIdx.x; i < n; i += kColThreads) smem[cache_at + i] = tbc[cache_low + i];
+    } else {
+        int n, at;
+        own_of(0, n, at);
+        for (int i = threadIdx.x; i < n; i += kColThreads) here[kColSlots + i] = tbc[at + i];
+    }
+    for (int i = threadIdx.x; i < n_top; i += kColThreads) {      // adjoint seed of the top layer
+        float acc = 0.0f;
+        for (int t = top_ptr[i]; t < top_ptr[i + 1]; ++t) acc += dout[(size_t)col * R + top_root[t]];
+        if (top_multi && ((top_multi[i >> 5] >> (i & 31)) & 1u)) acc = encode_h(acc, tbc[top_at + i]);
+        above[kColSlots + i] = acc;
+    }
+    int t = 0;
+    for (; t + 1 < cached; ++t) {
+        const float* owns = smem + cache_at + (top[-1 - t].at - cache_low) - kColSlots;
+        __syncthreads();
+        if (((t & 1) == 0) == (top_is_and != 0)) col_bwd_layer<false>(walk, above, here, owns);
+        else col_bwd_layer<true>(walk, above, here, owns);
+        float* tmp = above; above = here; here = tmp;
+    }
+    for (; t < n_steps; ++t) {
+        int own_n, own_at;
+        own_of(t + 1, own_n, own_at);
+        // (the last rows are read, and written, by a lane that steps back to them; a layer of less than four rows reads
+        // up to three floats past its own, still inside the workspace)
+        typedef float f4u __attribute__((ext_vector_type(4), aligned(4)));
+        f4u own[kColOwn];
 #pragma unroll
-            for (int k = 0; k < CT; ++k) {
-                float acc = 0.0f;
-                if (k < nact) {
-                    for (int t = top_ptr[i]; t < top_ptr[i + 1]; ++t) acc += dout[(size_t)(col0 + k) * R + top_root[t]];
-                    if (enc) acc = encode_h(acc, tb0[(size_t)k * T + L.tb_off + i]);
-                }
-                cur[i * CT + k] = acc;
+        for (int i = 0; i < kColOwn; ++i) {
+            const int at = 4 * ((int)threadIdx.x + i * kColThreads), back = own_n - 4 < 0 ? 0 : own_n - 4;
+            own[i] = *reinterpret_cast<const f4u*>(tbc + own_at + (at < back ? at : at < own_n ? back : 0));
+        }
+        const float* owns = t < cached ? smem + cache_at + (top[-1 - t].at - cache_low) - kColSlots : here;
+        __syncthreads();
+        if (((t & 1) == 0) == (top_is_and != 0)) col_bwd_layer<false>(walk, above, here, owns);
+        else col_bwd_layer<true>(walk, above, here, owns);
+        __syncthreads();
+        // the adjoints above are done with: their array takes the next step's own values
+#pragma unroll
+        for (int i = 0; i < kColOwn; ++i) {
+            const int at = 4 * ((int)threadIdx.x + i * kColThreads);
+            if (at + 4 <= own_n) {
+                *reinterpret_cast<float4*>(above + kColSlots + at) = make_float4(own[i].x, own[i].y, own[i].z, own[i].w);
+            } else if (at < own_n) {
+                const int back = own_n - 4 < 0 ? 0 : own_n - 4;
+                for (int j = 0; j < 4; ++j)
+                    if (back + j < own_n) above[kColSlots + back + j] = own[i][j];
             }
         }
-        if (threadIdx.x < CT) cur[L.n * CT + threadIdx.x] = 0.0f;       // padding slot: adjoint 0
+        float* tmp = above; above = here; here = tmp;
     }
-    for (int t = n_layers - 1; t >= 1; --t) {      // adjoints of layer t -> layer t - 1
-        const SlabLayer& L = layers[t];
-        const bool is_and = ((t & 1) == 0) == (first_is_and != 0);
-        const int lines = L.bwd_count[wave];
-        const float* tb_below = tb0 + layers[t - 1].tb_off;
-        __syncthreads();
-        if (is_and) slab_bwd_rows<CT, false>(L.n_below, sp, lines, a, cur, nxt, tb_below, T, nact);
-        else slab_bwd_rows<CT, true>(L.n_below, sp, lines, a, cur, nxt, tb_below, T, nact);
-        sp += (size_t)lines * 64;
-        if (threadIdx.x < CT) nxt[L.n_below * CT + threadIdx.x] = 0.0f;  // padding slot of the next step
-        __syncthreads();
-        float* tmp = cur; cur = nxt; nxt = tmp;
+    __syncthreads();
+    if (!res.wT) {
+        for (int r = threadIdx.x; r < res.n_last; r += kColThreads) res.g_cols[(size_t)col * res.n_last + r] = above[kColSlots + r];
+        return;
     }
-    // column-major, like tb: a lane owns rows of one column, so row-major stores would be 4 bytes per cache line
-    // (measured: 40 us of 163 on the headline workload); tb_to_rows_kernel transposes afterwards
-    const int n_first = layers[0].n;
-    for (int r = threadIdx.x; r < n_first; r += kSlabThreads)
-#pragma unroll
-        for (int k = 0; k < CT; ++k)
-            if (k < nact) g_out[(size_t)(col0 + k) * n_first + r] = cur[r * CT + k];
+    for (int v = threadIdx.x; v < res.V; v += kColThreads) {
+        const int pr = res.pos_row[v], nr = res.neg_row[v];
+        float d = pr >= 0 ? above[kColSlots + pr] : 0.0f, dn = 0.0f;
+        if (nr >= 0) {
+            const float gn = above[kColSlots + nr];
+            if (res.mode == 2) dn = gn;
+            else if (gn != 0.0f) d += res.mode == 1 ? -gn / expm1f(-res.wT[(size_t)v * ld + col]) : -gn;
+        }
+        res.dleaf[(size_t)col * res.V + v] = d;
+        if (res.mode == 2 && res.dneg) res.dneg[(size_t)col * res.V + v] = dn;
+    }
 }
 
-// cols[b, r] = rows[r, b] for r < n_rows, b < B: the rows of a layer of the activation buffer into the column-major
+// cols[b * T + r] = rows[r, b] for r < n_rows, b < B: the rows of a layer of the activation buffer into the column-major
 // form in which a workgroup of the persistent forward kernel reads its column (32 x 32 tiles through LDS).
 __global__ __launch_bounds__(256) void rows_to_cols_kernel(const float* __restrict__ rows, int n_rows, int B, int ld,
-                                                           float* __restrict__ cols) {
+                                                           float* __restrict__ cols, int T) {
     __shared__ float tile[32][33];
     const int r0 = blockIdx.x * 32, b0 = blockIdx.y * 32;
     const int tx = threadIdx.x & 31, ty = threadIdx.x >> 5;       // 32 x 8
@@ -1136,7 +1356,7 @@ __global__ __launch_bounds__(256) void rows_to_cols_kernel(const float* __restri
 #pragma unroll
     for (int j = 0; j < 4; ++j) {
         const int b = b0 + ty + 8 * j, r = r0 + tx;
-        if (b < B && r < n_rows) cols[(size_t)b * n_rows + r] = tile[tx][ty + 8 * j];
+        if (b < B && r < n_rows) cols[(size_t)b * T + r] = tile[tx][ty + 8 * j];
     }
 }
 

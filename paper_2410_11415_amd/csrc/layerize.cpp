@@ -220,6 +220,136 @@ void make_slab(int64_t n, int64_t n_src, const int32_t* ptr, const int32_t* idx,
 }
 }  // namespace
 
+void make_cols(int64_t n, const int32_t* ptr, const int32_t* idx, const uint32_t* flags, const uint32_t* row_bits,
+               int waves, int pad, ColStep step, ColPlan& out) {
+    out = ColPlan();
+    // Cycles of a wave with 15 others beside it, fitted to the times of the waves of both sweeps of a circuit of 85000 nodes
+    // (per wave and layer, 640 samples, to within 10%): a chunk of kind 0, 1, 2, a unit of kind 3 or 4, a line of it, a
+    // step of its butterfly, and what a run costs before its first row.
+    struct Cost { int64_t chunk[3], unit, line, fly, run; };
+    static const Cost kCosts[4] = {{{120, 140, 195}, 600, 65, 5, 550}, {{200, 370, 380}, 300, 350, 60, 620},
+                                   {{255, 335, 350}, 60, 470, 45, 790}, {{210, 360, 560}, 670, 890, 10, 540}};
+    const Cost& cost = kCosts[step];
+    struct Piece { int64_t row, rows, cost; int kind, k; int32_t blocks; };
+    // longest[k][r]: the longest row among the 64 >> k rows from r on
+    std::vector<int32_t> longest[7];
+    longest[6].resize((size_t)n);
+    for (int64_t r = 0; r < n; ++r) longest[6][(size_t)r] = ptr[r + 1] - ptr[r];
+    for (int k = 5; k >= 0; --k) {
+        longest[k] = longest[k + 1];
+        const int64_t half = 64 >> (k + 1);
+        for (int64_t r = 0; r + half < n; ++r) longest[k][(size_t)r] = std::max(longest[k][(size_t)r], longest[k + 1][(size_t)(r + half)]);
+    }
+    // cheapest cut, then again without pieces that take longer than a wave's share of it
+    std::vector<int64_t> best((size_t)n + 1, 0);
+    std::vector<Piece> pick((size_t)n);
+    int64_t cap = INT64_MAX;
+    for (int turn = 0; turn < 2; ++turn) {
+        for (int64_t r = n - 1; r >= 0; --r) {
+            Piece b{}, least{};
+            int64_t total = INT64_MAX;
+            least.cost = INT64_MAX;
+            auto consider = [&](int kind, int k, int32_t blocks, int64_t cost) {
+                const Piece u{r, std::min<int64_t>(64 >> k, n - r), cost, kind, k, blocks};
+                if (cost < least.cost) least = u;
+                if (cost <= cap && cost + best[(size_t)(r + u.rows)] < total) { total = cost + best[(size_t)(r + u.rows)]; b = u; }
+            };
+            const int32_t most = longest[0][(size_t)r];
+            if (most <= 4) {
+                const int kind = most <= 1 ? 0 : most <= 2 ? 1 : 2;
+                consider(kind, 0, 1, cost.chunk[kind]);
+            }
+            for (int k = 0; k <= 6; ++k) {
+                const int32_t e = std::max(1, (longest[k][(size_t)r] + (1 << k) - 1) >> k), blocks = (e + 15) / 16;
+                if (blocks > 255 && k < 6) continue;
+                consider(e <= 8 ? 4 : 3, k, blocks, cost.unit + (e + 7) / 8 * cost.line + k * cost.fly);
+            }
+            if (total == INT64_MAX) { b = least; total = b.cost + best[(size_t)(r + b.rows)]; }
+            best[(size_t)r] = total;
+            pick[(size_t)r] = b;
+        }
+        cap = std::max<int64_t>(best[0] / waves, cost.unit + cost.line + 6 * cost.fly);
+    }
+    std::vector<Piece> pieces;
+    for (int64_t r = 0; r < n; r += pick[(size_t)r].rows) pieces.push_back(pick[(size_t)r]);
+    // contiguous shares: the smallest bound (in steps of a thirty-second) under which they number at most `waves`; a share
+    // pays for each of its runs
+    auto joins = [](const Piece& a, const Piece& b) { return a.kind == b.kind && a.k == b.k && a.blocks == b.blocks; };
+    auto share_end = [&](size_t from, int64_t bound) {
+        int64_t load = 0;
+        size_t i = from;
+        for (; i < pieces.size(); ++i) {
+            const int64_t more = pieces[i].cost + (i > from && joins(pieces[i - 1], pieces[i]) ? 0 : cost.run);
+            if (i > from && load + more > bound) break;
+            load += more;
+        }
+        return i;
+    };
+    int64_t bound = best[0] / waves + 1;
+    for (const Piece& u : pieces) bound = std::max(bound, u.cost + cost.run);
+    for (;; bound += bound / 32 + 1) {
+        size_t at = 0;
+        int used = 0;
+        for (; at < pieces.size() && used < waves; ++used) at = share_end(at, bound);
+        if (at == pieces.size()) break;
+    }
+    const uint32_t pads = (uint32_t)pad | (uint32_t)pad << 16;
+    size_t next = 0;
+    for (int w = 0; w < kSlabWaves; ++w) {
+        out.block_at[w] = (int32_t)(out.blocks.size() / kBlockWords);
+        out.table_at[w] = (int32_t)(out.tables.size() / (kDescTable * kDescWords));
+        const size_t end = share_end(next, bound);
+        int in_table = 0;
+        auto describe = [&](uint32_t a, uint32_t b) {
+            out.tables.push_back(a);
+            out.tables.push_back(b);
+            ++in_table;
+        };
+        while (next < end) {
+            // the longest run of pieces that go on as the first one does
+            const Piece& u = pieces[next];
+            size_t stop = next + 1;
+            int64_t rows = u.rows;
+            while (stop < end && joins(u, pieces[stop])) rows += pieces[stop++].rows;
+            if (in_table == kDescTable - 1) { describe(1u, 0u); in_table = 0; }
+            describe((uint32_t)(kColSlots + u.row), (uint32_t)rows | (uint32_t)u.k << 16 | (uint32_t)u.kind << 20 | (uint32_t)u.blocks << 24);
+            const size_t at = out.blocks.size();
+            const int64_t per_block = u.kind < 3 ? 1024 >> u.kind : 64 >> u.k;
+            out.blocks.resize(at + (size_t)((rows + per_block - 1) / per_block * u.blocks) * kBlockWords, pads);
+            // entry e (0 .. 15) of a lane in block i of the run
+            auto put = [&](int64_t i, int lane, int e, uint32_t entry) {
+                uint32_t& word = out.blocks[at + (size_t)i * kBlockWords + (size_t)(e / 8) * kLineWords + (size_t)lane * 4 + (size_t)((e & 7) / 2)];
+                word = (e & 1) ? (word & 0xFFFFu) | entry << 16 : (word & 0xFFFF0000u) | entry;
+            };
+            auto entry_of = [&](int64_t r, int64_t j) -> uint32_t {       // entry j of row r, or padding
+                const bool flagged = row_bits && ((row_bits[(size_t)r >> 5] >> (r & 31)) & 1u);
+                uint32_t x = (uint32_t)pad;
+                if (ptr[r] + j < ptr[r + 1])
+                    x = (uint32_t)(kColSlots + idx[ptr[r] + j]) | (flags && (flags[ptr[r] + j] & kWeightedEdge) ? 0x8000u : 0u);
+                return flagged ? x | 0x8000u : x;
+            };
+            for (int64_t r = 0; r < rows; ++r) {
+                if (u.kind < 3) {
+                    const int64_t chunk = r / 64;
+                    for (int e = 0; e < (1 << u.kind); ++e)
+                        put(r / per_block, (int)(r & 63), (int)((chunk << u.kind) & 15) + e, entry_of(u.row + r, e));
+                } else {
+                    const int per_line = u.kind == 4 ? 8 : 16;
+                    for (int sub = 0; sub < (1 << u.k); ++sub)
+                        for (int64_t e = 0; e < (int64_t)per_line * u.blocks; ++e)
+                            put(r / per_block * u.blocks + e / per_line, (int)((r % per_block) << u.k) + sub, (int)(e % per_line),
+                                entry_of(u.row + r, sub + (e << u.k)));
+                }
+            }
+            next = stop;
+        }
+        describe(0u, 0u);
+        while (out.tables.size() % (kDescTable * kDescWords)) out.tables.push_back(0u);
+    }
+    out.block_at[kSlabWaves] = (int32_t)(out.blocks.size() / kBlockWords);
+    out.table_at[kSlabWaves] = (int32_t)(out.tables.size() / (kDescTable * kDescWords));
+}
+
 int layerize(int32_t V, int64_t N, const uint8_t* node_type, const int32_t* node_lit,
              const int64_t* child_ptr, const int32_t* child_idx_in, int32_t R, const int32_t* roots_in,
              const Options& opt, CircuitPlan& plan, std::string& err) {
@@ -605,7 +735,8 @@ int layerize(int32_t V, int64_t N, const uint8_t* node_type, const int32_t* node
                 // A layer small enough for the persistent top-of-circuit kernels: there a thread walks a whole
                 // row and a wave waits for its longest one, while locality is irrelevant (the layer sits in
                 // LDS).  Group rows by fan-in (powers of two) and order each group by fan-out, so that the 64
-                // rows of a wave have similar lengths in the forward and in the reverse sweep.
+                // rows of a wave have similar lengths in the forward and in the reverse sweep.  The few rows of
+                // many parents come first, so that they do not stretch the chunks of the others.
                 std::vector<int32_t> fan_in((size_t)lay.n), fan_out((size_t)lay.n, 0);
                 for (int64_t s2 = 0; s2 < lay.n; ++s2) {
                     const int32_t c = lay.origin[(size_t)s2];
@@ -621,9 +752,12 @@ int layerize(int32_t V, int64_t N, const uint8_t* node_type, const int32_t* node
                     }
                 }
                 auto bucket = [](int32_t k) { int b = 0; while ((1 << b) < k) ++b; return b; };
+                constexpr int32_t kManyParents = 16;
                 std::stable_sort(order.begin(), order.end(), [&](int32_t a, int32_t b) {
+                    const bool ma = fan_out[(size_t)a] > kManyParents, mb = fan_out[(size_t)b] > kManyParents;
+                    if (ma != mb) return ma;
                     const int ba = bucket(fan_in[(size_t)a]), bb = bucket(fan_in[(size_t)b]);
-                    if (ba != bb) return ba > bb;
+                    if (!ma && ba != bb) return ba > bb;
                     return fan_out[(size_t)a] > fan_out[(size_t)b];
                 });
             }
@@ -801,6 +935,11 @@ int layerize(int32_t V, int64_t N, const uint8_t* node_type, const int32_t* node
             if (fan_in <= kTailFanCap) {
                 make_slab(lay.n, nc, lay.row_ptr.data(), lay.child.data(), nullptr, lay.slab_fwd);
                 lay.tail_fwd_ok = true;
+                const bool is_and = (l & 1) != 0;
+                make_cols(lay.n, lay.row_ptr.data(), lay.child.data(), nullptr, nullptr, kColFwdWaves,
+                          is_and ? kColPadAnd : kColPadOr, is_and ? kColFwdAnd : kColFwdOr, lay.col_fwd);
+                make_cols(nc, cptr.data(), cpar.data(), cflag.data(), is_and && l >= 3 ? plan.layers[(size_t)l - 1].multi.data() : nullptr,
+                          kColBwdWaves, kColPadAnd, is_and ? kColBwdAnd : kColBwdOr, lay.col_bwd);
                 if (fan_out <= kTailFanCap) {
                     make_slab(nc, lay.n, cptr.data(), cpar.data(), cflag.data(), lay.slab_bwd,
                               (l & 1) && l >= 3 ? plan.layers[(size_t)l - 1].multi.data() : nullptr);
@@ -866,6 +1005,11 @@ int layerize(int32_t V, int64_t N, const uint8_t* node_type, const int32_t* node
         t = L + 1;
         while (t - 1 >= 1 && plan.layers[(size_t)t - 1].tail_bwd_ok) --t;
         if (t <= L) plan.tail_bwd_first = t;
+    }
+    plan.col_off.assign((size_t)L + 1, -1);
+    if (plan.tail_first > 0) {
+        for (int32_t l = plan.tail_first; l <= L; ++l) { plan.col_off[(size_t)l] = plan.col_rows; plan.col_rows += plan.layers[(size_t)l].n; }
+        plan.col_off[(size_t)plan.tail_first - 1] = plan.col_rows;
     }
 
     // ---------------------------------------------------------------- leaf layer and roots

@@ -24,29 +24,49 @@ struct Options {
 
 // Layers at the top of the circuit with at most this many nodes are candidates for the persistent
 // kernels, which keep two layers of one batch column in LDS (values forward, adjoints in the reverse sweep):
-// 20000 rows is what two arrays in 160 KB hold.  In those kernels a lane walks a whole row, so a candidate
-// layer has no row with more sources than kTailFanCap (the reverse plan: no node with more parents).
+// 20000 rows is what two arrays in 160 KB hold.  A candidate layer has no row with more sources than kTailFanCap: a
+// narrow layer of long rows has more entries than one compute unit walks in the time of a launch.
 constexpr int64_t kTailRowsCap = 20000;
 constexpr int64_t kTailFanCap = 64;
 
-// Index vectors of one layer for the persistent kernels.  Rows are taken in chunks of 64 consecutive
+// Index vectors of one layer of the narrow top, one row per lane: rows are taken in chunks of 64 consecutive
 // rows (one per lane of a wave); a chunk has as many steps as its longest row, and step i of a chunk
-// is one line of 64 words: lane j holds the i-th source of row 64 * chunk + j, or a padding word when
-// that row is shorter or does not exist.  A padding word names source n_src, one past the last source
-// row: the kernels keep the identity of the layer's operation in that slot, so padding needs no test.
-// In the reverse plan the word that a lane holds in the last line of a chunk carries kRowFlag when the lane's row
-// is an OR node with more than one child (its adjoint is stored in the one-gather form).
-// The 16 waves of the workgroup take the chunks round-robin, and the lines of the chunks of one wave
-// are stored back to back in the order the wave walks them, so a wave streams through one contiguous
-// run of lines and can fetch them far ahead.  Every word of the last line of a chunk carries
-// kLastEdge: the wave then closes the 64 rows of the chunk and moves on to its next one (16 chunks
-// further).  Runs are padded with lines of padding words to a multiple of kSlabBlock lines, the unit
-// the kernels fetch.
+// is one line of 64 words: lane j holds the i-th source of row 64 * chunk + j, or a padding word (source n_src)
+// when that row is shorter or does not exist.  In the reverse plan the word that a lane holds in the last line of a
+// chunk carries kRowFlag when the lane's row is an OR node with more than one child.  The 16 waves of a workgroup take
+// the chunks round-robin; every word of the last line of a chunk carries kLastEdge; runs are padded to a multiple of
+// kSlabBlock lines.  The layers that have this form are the candidates for the persistent kernels, which walk the
+// same rows in the form of ColPlan below; the lines themselves serve the host check of the plans only.
 constexpr int kSlabWaves = 16;
 constexpr int kSlabBlock = 8;
 struct SlabPlan {
     int32_t wave_line[kSlabWaves + 1] = {};   // first line of each wave's run (wave_line[16] = all lines)
     std::vector<uint32_t> ent;                // 64 words per line: source row | flags
+};
+
+// The same index vectors in the form the persistent kernels walk: runs of consecutive rows of one kind, read in blocks of
+// 64 lanes x 16 entries of 16 bits (32 bytes per lane in two lines of 1 KB).
+//   Kinds 0, 1, 2: rows of at most 1, 2 or 4 entries, in chunks of 64 rows: a block holds 16, 8 or 4 chunks, row
+// 64 i + lane of the run has the lane's entries from i << kind on.  Kinds 3, 4: units of 64 >> k rows, 2^k lanes
+// per row (k chosen per run): lane j works for row j >> k and holds that row's entries (j mod 2^k) + i * 2^k, and the
+// lanes of a row meet in a butterfly at the end.  A unit of kind 4 has at most 8 entries per lane (the first line of
+// one block), one of kind 3 as many blocks as its run says.  A row of many entries
+// therefore spreads over the wave instead of making 63 lanes wait for one, and there is no limit on the entries of a row.
+//   An entry is an LDS slot (kColSlots + position of the source: the first slots of a value array hold the identities
+// that padding names, kColPadAnd for AND layers and the reverse sweep, kColPadOr for OR layers).  Bit 15 is a flag of the
+// reverse sweep: weighted edge, or (steps through an AND layer, on every entry of the row) the row's adjoint is
+// stored in the one-gather form.  Slots stay below 2^15.
+//   Descriptor of a run, 2 words: [0] LDS slot of its first row, [1] rows | k << 16 | kind << 20 | blocks per unit << 24.
+// The descriptors of a wave in a layer come in tables of 64: up to 63 runs and one of no rows (word 0 = 1: another
+// table follows, 0: the end).  The rows of a layer are cut into chunks and units by a shortest-path search over their
+// cost, and every wave gets a contiguous share of about the same cost, so that the waves reach the layer's barrier together.
+//   The forward kernel has one wave less for this: its last wave moves the values to the column-major buffer.
+constexpr int kColSlots = 4, kColPadAnd = 0, kColPadOr = 1;
+constexpr int kColFwdWaves = kSlabWaves - 1, kColBwdWaves = kSlabWaves;
+constexpr int kBlockWords = 512, kLineWords = 256, kDescWords = 2, kDescTable = 64;
+struct ColPlan {
+    int32_t block_at[kSlabWaves + 1] = {}, table_at[kSlabWaves + 1] = {};   // first block / table of each wave
+    std::vector<uint32_t> blocks, tables;
 };
 
 // One gather-reduce pass set over a CSR whose rows are the outputs.
@@ -101,6 +121,7 @@ struct LayerPlan {
     bool tail_bwd_ok = false;        // slab_bwd is built as well
     SlabPlan slab_fwd;               // rows = nodes of this layer, sources = positions in layer - 1
     SlabPlan slab_bwd;               // rows = nodes of layer - 1, sources = parents in this layer (| kWeightedEdge)
+    ColPlan col_fwd, col_bwd;        // the persistent kernels' form, for the layers tail_first .. num_layers (col_bwd: rows of layer - 1)
     PassPlan fwd;                    // outputs = nodes of this layer, sources = layer - 1
     PassPlan bwd;                    // outputs = nodes of layer - 1, sources = this layer
     // Fused AND rows (padding-free part only).  An AND node below layer alias_top that has at most one child
@@ -126,6 +147,10 @@ struct CircuitPlan {
     int64_t max_fwd_seg = 0, max_bwd_seg = 0;   // scratch rows needed by split passes
     int32_t tail_first = 0;              // layers tail_first..num_layers may run in the persistent forward kernel (0: none)
     int32_t tail_bwd_first = 0;          // layers tail_bwd_first..num_layers also in the reverse one (>= tail_first; 0: none)
+    // Column-major value buffer of the persistent kernels: first entry of each layer in a column (-1: none).  The
+    // layers tail_first .. num_layers follow one another from 0, the layer below tail_first comes after them.
+    std::vector<int64_t> col_off;
+    int64_t col_rows = 0;                // entries of the layers tail_first .. num_layers
     // Padding-free lower part (Options::alias_chains): layers 1 .. alias_top hold no chain nodes, except
     // that layer alias_top holds a stand-in for every node read from above it.  Their child entries are
     // rows of the whole activation buffer (row0[l] = first row of layer l), and layers[l].bwd for
@@ -151,5 +176,11 @@ int layerize(int32_t num_vars, int64_t num_nodes, const uint8_t* node_type, cons
 // `skip` (optional, a byte per row): rows to leave out; like a split row such a row is one kSkipRow entry.
 void make_pass_plan(int64_t n, const int32_t* ptr, const int32_t* idx, const Options& opt, PassPlan& out,
                     const uint32_t* flags = nullptr, const uint32_t* row_bits = nullptr, const uint8_t* skip = nullptr);
+
+// Runs (see ColPlan) of a CSR of n rows for `waves` waves.  pad: slot that padding names; step: whose costs to
+// cut by.  flags and row_bits as for make_pass_plan.
+enum ColStep { kColFwdAnd, kColFwdOr, kColBwdAnd, kColBwdOr };
+void make_cols(int64_t n, const int32_t* ptr, const int32_t* idx, const uint32_t* flags, const uint32_t* row_bits,
+               int waves, int pad, ColStep step, ColPlan& out);
 
 }  // namespace klay

@@ -1,0 +1,69 @@
+"""The persistent kernels at the edges of their runs (GPU): layers of 1 to 5000 rows around the chunk and block sizes, rows of
+1, 2, 3-4, 5-8 and up to 60 children, literals with thousands of parents, batches of 1 and 257, impossible and certain
+literals; against the oracle, in the three semirings, with gradients."""
+import numpy as np
+import pytest
+
+from klay_synth import as_inputs
+from klay_synth.circuits import Circuit
+from tests.gpu_util import assert_grad_close, assert_log_close, assert_real_close, gpu_eval, oracle_eval
+
+pytestmark = pytest.mark.gpu
+REAL, LOG, MAXLOG = 0, 1, 2
+
+
+def stack(rng, num_vars, widths, fan, hub):
+    """Alternating AND / OR layers of the given widths; every gate draws fan(rng) distinct children of the layer below
+    (and, with probability `hub`, one of the first four literals in an AND gate, which then have many parents)."""
+    types, lits, kids = [0] * (2 * num_vars), [s * (v + 1) for v in range(num_vars) for s in (1, -1)], [[] for _ in range(2 * num_vars)]
+    below = list(range(2 * num_vars))
+    for depth, n in enumerate(widths):
+        here = []
+        for i in range(n):
+            # every node below gets a parent where the layer is wide enough
+            c = {below[i % len(below)]} | {int(x) for x in rng.choice(below, size=min(len(below), fan(rng)), replace=False)}
+            if depth % 2 == 0 and rng.random() < hub:
+                c.add(int(rng.integers(4)))
+            here.append(len(types))
+            types.append(1 if depth % 2 == 0 else 2)
+            lits.append(0)
+            kids.append(sorted(c))
+        below = here
+    ptr = np.concatenate([[0], np.cumsum([len(k) for k in kids])]).astype(np.int64)
+    idx = np.array([x for k in kids for x in k], dtype=np.int32)
+    return Circuit(num_vars, np.array(types, np.uint8), np.array(lits, np.int32), ptr, idx, np.array(below, np.int32))
+
+
+FANS = {"one": lambda r: 1, "two": lambda r: 1 + int(r.integers(2)), "few": lambda r: 1 + int(r.integers(4)),
+        "eight": lambda r: 1 + int(r.integers(8)), "long": lambda r: 1 + int(r.integers(60)) if r.random() < 0.1 else 1}
+
+
+@pytest.mark.parametrize("widths,fan,batch", [
+    ((1, 1), "two", 1), ((63, 64, 65, 3), "two", 3), ((64, 128, 129, 127), "few", 2), ((255, 256, 257, 5), "eight", 257),
+    ((1023, 1024, 1025, 40), "one", 5), ((1025, 511, 513, 9), "two", 2), ((2049, 2047, 300, 2), "few", 3), ((5000, 3000, 700, 64), "long", 2),
+])
+def test_layers_around_chunk_and_block_sizes(widths, fan, batch):
+    import torch
+    import paper_2410_11415_amd as klay
+    rng = np.random.default_rng(len(widths) * 1000 + widths[0])
+    c = stack(rng, 24, widths, FANS[fan], 0.6)
+    k = klay.Circuit(*c.arrays(), device=0)
+    assert k.info()["tail_first_layer"] == 1
+    p = rng.uniform(0.05, 0.95, size=(batch, 24))
+    p[0, 0], p[-1, 1] = 0.0, 1.0
+    dout = rng.normal(size=(batch, c.roots.shape[0])).astype(np.float32)
+    for semiring in (LOG, REAL, MAXLOG):
+        with np.errstate(divide="ignore"):
+            w = as_inputs(p, semiring != REAL)
+        d = None if semiring == MAXLOG else dout
+        out, grad = gpu_eval(k, w, semiring, d)
+        ref, rgrad = oracle_eval(c, w, semiring, d, or_levels=k.num_layers // 2)
+        (assert_real_close if semiring == REAL else assert_log_close)(out, ref, "values")
+        if d is not None:
+            assert_grad_close(grad, rgrad, "gradients", real=semiring == REAL)
+    # a second reverse sweep of the same pass, and the entry point with no buffer for values
+    w = torch.from_numpy(as_inputs(np.clip(p, 1e-6, 1 - 1e-6), True)).cuda()
+    out = k.forward(w, LOG)
+    g = [k.backward(torch.from_numpy(dout).cuda()) for _ in range(2)]
+    assert torch.equal(g[0], g[1]) and torch.equal(out, k.forward_static(w, LOG))
+    k.close()
