@@ -66,14 +66,14 @@ def kernel_symbol(cls, B, edges=False, fused_op=10):
         w = 1
         while w < B:
             w *= 2
-        return ("klay::edge_kernel<%d, %d>" if edges else "klay::pass_kernel<%d, 1, %d>") % (ops[cls], w)
+        return "klay::edge_kernel<%d, %d>" % (ops[cls], w) if edges else "klay::pass_kernel<%d, *>" % ops[cls]
     w_small = 1
     while w_small < B:
         w_small *= 2
     fixed = {"tail_fwd": "klay::col_fwd_kernel", "tail_bwd": "klay::col_bwd_kernel",
              "leaf": "klay::leaf_fwd_kernel" if B > 32 else "klay::leaf_fwd_small_kernel", "bwd_leaf": "klay::leaf_bwd_kernel", "root": "klay::root_out_kernel",
              "seed": "klay::seed_kernel", "split": "klay::pass_kernel<*> (segments of split rows)",
-             "combine": "klay::combine_kernel<*>" if B > 32 else "klay::pass_kernel<*> (combine rows of split rows)",
+             "combine": "klay::combine_kernel<*>" if B > 32 else "klay::combine_small_kernel<*>",
              "main_combine": "klay::stream_combine_kernel<*>",
              "fwd_or_fused": "klay::stream_kernel<%d, %d>" % (fused_op, vec),
              "prod_edges": "klay::prod_parent_kernel<%d, %d>" % (vec, 64 if B > 32 else w_small)}

@@ -219,52 +219,50 @@ Workspace workspace_layout(const klay_circuit* c, int B, bool need_bwd) {
     return w;
 }
 
-template <int OP, int VEC, int W>
-void launch_one(const klay::PassArgs& a, dim3 grid, hipStream_t s) {
-    hipLaunchKernelGGL((klay::pass_kernel<OP, VEC, W>), grid, dim3(256), 0, s, a);
-}
+// Waves from which on a lane of the generic kernels takes more than one column (1024, 2048 and 4096 measured: a power-law
+// circuit of 62000 nodes at B = 9, training step 161 / 123 / 126 us, other workloads within 1%; always four columns: 210 us).
+constexpr int64_t kFillWaves = 2048;
+
+// Lanes per row of the generic kernels for `vec` columns a lane; a wave takes 64 / lanes rows.
+int row_lanes(int B, int vec) { return std::min(64, (B + vec - 1) / vec); }
+uint32_t row_inverse(int lanes) { return (uint32_t)((65536 + lanes - 1) / lanes); }
 
 template <int OP>
-void launch_op(const klay::PassArgs& a, const Geometry& g, dim3 grid, hipStream_t s) {
-    if (g.w == 64) {
-        if (g.vec == 4) launch_one<OP, 4, 64>(a, grid, s);
-        else if (g.vec == 2) launch_one<OP, 2, 64>(a, grid, s);
-        else launch_one<OP, 1, 64>(a, grid, s);
-        return;
-    }
-    switch (g.w) {                      // B <= 32: one column per lane, a lane group per row
-    case 32: launch_one<OP, 1, 32>(a, grid, s); break;
-    case 16: launch_one<OP, 1, 16>(a, grid, s); break;
-    case 8: launch_one<OP, 1, 8>(a, grid, s); break;
-    case 4: launch_one<OP, 1, 4>(a, grid, s); break;
-    case 2: launch_one<OP, 1, 2>(a, grid, s); break;
-    default: launch_one<OP, 1, 1>(a, grid, s); break;
-    }
+void launch_op(const klay::PassArgs& a, int vec, dim3 grid, hipStream_t s) {
+    if (vec == 4) hipLaunchKernelGGL((klay::pass_kernel<OP, 4>), grid, dim3(256), 0, s, a);
+    else if (vec == 2) hipLaunchKernelGGL((klay::pass_kernel<OP, 2>), grid, dim3(256), 0, s, a);
+    else hipLaunchKernelGGL((klay::pass_kernel<OP, 1>), grid, dim3(256), 0, s, a);
+}
+
+// workgroups of 4 waves for `rows` rows, a multiple of 8 (see xcd_block)
+unsigned row_blocks(int64_t rows, int lanes) {
+    const int64_t per_block = 4 * (64 / lanes);
+    return (unsigned)(((rows + per_block - 1) / per_block + 7) / 8 * 8);
 }
 
 // Launch one gather-reduce pass over `n_total` rows.
-void launch_pass(int op, klay::PassArgs a, const Geometry& g, hipStream_t s) {
+void launch_pass(int op, klay::PassArgs a, hipStream_t s) {
     const int64_t rows = (int64_t)a.n_total - a.row_begin;
     if (rows <= 0) return;
-    const int rpw = 64 / g.w;
-    const int64_t groups = (rows + rpw - 1) / rpw;                    // row groups = wave work items
-    // enough waves to fill 256 CUs several times over before a wave takes more than one group
-    int iters = (int)std::min<int64_t>(8, std::max<int64_t>(1, groups / 32768));
-    a.iters = iters;
-    int64_t blocks = (groups + (int64_t)4 * iters - 1) / ((int64_t)4 * iters);
-    blocks = (blocks + 7) / 8 * 8;
-    dim3 grid((unsigned)blocks, (unsigned)g.tiles);
+    // as many columns per lane as leave 8 waves for every compute unit: a smaller launch waits for its longest rows, and
+    // a row takes less time the fewer columns a lane has
+    int vec = a.B >= 4 ? 4 : (a.B >= 2 ? 2 : 1);
+    while (vec > 1 && rows * row_lanes(a.B, vec) < 64 * kFillWaves) vec /= 2;
+    a.lanes = row_lanes(a.B, vec);
+    a.per_wave = 64 / a.lanes;
+    a.inverse = row_inverse(a.lanes);
+    dim3 grid(row_blocks(rows, a.lanes), (unsigned)((a.B + a.lanes * vec - 1) / (a.lanes * vec)));
     switch (op) {
-    case klay::OP_SUM: launch_op<klay::OP_SUM>(a, g, grid, s); break;
-    case klay::OP_PROD: launch_op<klay::OP_PROD>(a, g, grid, s); break;
-    case klay::OP_LSE: launch_op<klay::OP_LSE>(a, g, grid, s); break;
-    case klay::OP_MAX: launch_op<klay::OP_MAX>(a, g, grid, s); break;
-    case klay::OP_PROD_BWD: launch_op<klay::OP_PROD_BWD>(a, g, grid, s); break;
-    case klay::OP_SUM_H: launch_op<klay::OP_SUM_H>(a, g, grid, s); break;
-    case klay::OP_SOFTMAX_H: launch_op<klay::OP_SOFTMAX_H>(a, g, grid, s); break;
-    case klay::OP_SUM_P: launch_op<klay::OP_SUM_P>(a, g, grid, s); break;
-    case klay::OP_PROD_BWD_P: launch_op<klay::OP_PROD_BWD_P>(a, g, grid, s); break;
-    default: launch_op<klay::OP_SOFTMAX_BWD>(a, g, grid, s); break;
+    case klay::OP_SUM: launch_op<klay::OP_SUM>(a, vec, grid, s); break;
+    case klay::OP_PROD: launch_op<klay::OP_PROD>(a, vec, grid, s); break;
+    case klay::OP_LSE: launch_op<klay::OP_LSE>(a, vec, grid, s); break;
+    case klay::OP_MAX: launch_op<klay::OP_MAX>(a, vec, grid, s); break;
+    case klay::OP_PROD_BWD: launch_op<klay::OP_PROD_BWD>(a, vec, grid, s); break;
+    case klay::OP_SUM_H: launch_op<klay::OP_SUM_H>(a, vec, grid, s); break;
+    case klay::OP_SOFTMAX_H: launch_op<klay::OP_SOFTMAX_H>(a, vec, grid, s); break;
+    case klay::OP_SUM_P: launch_op<klay::OP_SUM_P>(a, vec, grid, s); break;
+    case klay::OP_PROD_BWD_P: launch_op<klay::OP_PROD_BWD_P>(a, vec, grid, s); break;
+    default: launch_op<klay::OP_SOFTMAX_BWD>(a, vec, grid, s); break;
     }
 }
 
@@ -603,9 +601,34 @@ void launch_combine_op(const klay::PassArgs& a, const Geometry& g, hipStream_t s
     else hipLaunchKernelGGL((klay::combine_kernel<OP, 1, NW>), grid, dim3(NW * 64), 0, s, a);
 }
 
+// B <= 32: a workgroup of four waves per split row as well, 64 / W partial rows at a time in a wave
+template <int OP>
+void launch_combine_small(const klay::PassArgs& a, const Geometry& g, hipStream_t s) {
+    dim3 grid((unsigned)a.n_main);
+    switch (g.w) {
+    case 32: hipLaunchKernelGGL((klay::combine_small_kernel<OP, 32>), grid, dim3(256), 0, s, a); break;
+    case 16: hipLaunchKernelGGL((klay::combine_small_kernel<OP, 16>), grid, dim3(256), 0, s, a); break;
+    case 8: hipLaunchKernelGGL((klay::combine_small_kernel<OP, 8>), grid, dim3(256), 0, s, a); break;
+    case 4: hipLaunchKernelGGL((klay::combine_small_kernel<OP, 4>), grid, dim3(256), 0, s, a); break;
+    case 2: hipLaunchKernelGGL((klay::combine_small_kernel<OP, 2>), grid, dim3(256), 0, s, a); break;
+    default: hipLaunchKernelGGL((klay::combine_small_kernel<OP, 1>), grid, dim3(256), 0, s, a); break;
+    }
+}
+
 void launch_combine(int op, const klay::PassArgs& a, const Geometry& g, hipStream_t s) {
     if (a.n_main <= 0) return;
-    if (g.w != 64) { launch_pass(op, a, g, s); return; }
+    if (g.w != 64) {
+        switch (op) {
+        case klay::OP_SUM: launch_combine_small<klay::OP_SUM>(a, g, s); break;
+        case klay::OP_PROD: launch_combine_small<klay::OP_PROD>(a, g, s); break;
+        case klay::OP_LSE: launch_combine_small<klay::OP_LSE>(a, g, s); break;
+        case klay::OP_MAX: launch_combine_small<klay::OP_MAX>(a, g, s); break;
+        case klay::OP_SUM_H: launch_combine_small<klay::OP_SUM_H>(a, g, s); break;
+        case klay::OP_SUM_P: launch_combine_small<klay::OP_SUM_P>(a, g, s); break;
+        default: launch_pass(op, a, s); break;
+        }
+        return;
+    }
     switch (op) {
     case klay::OP_SUM: launch_combine_op<klay::OP_SUM>(a, g, s); break;
     case klay::OP_PROD: launch_combine_op<klay::OP_PROD>(a, g, s); break;
@@ -613,7 +636,7 @@ void launch_combine(int op, const klay::PassArgs& a, const Geometry& g, hipStrea
     case klay::OP_MAX: launch_combine_op<klay::OP_MAX>(a, g, s); break;
     case klay::OP_SUM_H: launch_combine_op<klay::OP_SUM_H>(a, g, s); break;
     case klay::OP_SUM_P: launch_combine_op<klay::OP_SUM_P>(a, g, s); break;
-    default: launch_pass(op, a, g, s); break;
+    default: launch_pass(op, a, s); break;
     }
 }
 
@@ -712,7 +735,7 @@ void run_pass_set(int op, int combine_op, const DevPass& dp, const float* src, c
             prof.begin(cls, pass_bytes(op, (double)(dp.main_entries + dp.seg_entries), light_rows + dp.n_seg, B),
                        pass_min_bytes(op, (double)(dp.main_entries + dp.seg_entries), light_rows + dp.n_seg, (double)dp.n_src, B));
             a.row_begin = 0;
-            launch_pass(op, a, g, s);
+            launch_pass(op, a, s);
             prof.end();
         } else if (!merged && dp.n_seg > 0 && dp.n_heavy > 0 && dp.n_tasks > 0 && stream_combine_pair(op, combine_op)) {
             // One column per lane and a layer too large for one generic launch: the segments first, then the
@@ -720,7 +743,7 @@ void run_pass_set(int op, int combine_op, const DevPass& dp, const float* src, c
             prof.begin(KLAY_K_SPLIT, pass_bytes(op, (double)dp.seg_entries, (double)dp.n_seg, B),
                        pass_min_bytes(op, (double)dp.seg_entries, (double)dp.n_seg, 0.0, B));
             a.row_begin = dp.n_main;
-            launch_pass(op, a, g, s);
+            launch_pass(op, a, s);
             prof.end();
             prof.begin(KLAY_K_MAIN_COMBINE,
                        pass_bytes(op, (double)dp.main_entries, light_rows, B) + pass_bytes(combine_op, (double)dp.n_seg, (double)dp.n_heavy, B),
@@ -744,7 +767,7 @@ void run_pass_set(int op, int combine_op, const DevPass& dp, const float* src, c
             prof.begin(KLAY_K_SPLIT, pass_bytes(op, (double)dp.seg_entries, (double)dp.n_seg, B),
                        pass_min_bytes(op, (double)dp.seg_entries, (double)dp.n_seg, 0.0, B));
             a.row_begin = dp.n_main;
-            launch_pass(op, a, g, s);
+            launch_pass(op, a, s);
             prof.end();
         }
         }
@@ -756,7 +779,7 @@ void run_pass_set(int op, int combine_op, const DevPass& dp, const float* src, c
             launch_edge(op, dp, g, src, src2, own, dst, seg_rows - (ptrdiff_t)dp.n_main * g.ld, B, s, zero_flag);
         } else {
             a.row_begin = 0;
-            launch_pass(op, a, g, s);
+            launch_pass(op, a, s);
         }
         prof.end();
     }
@@ -839,13 +862,22 @@ size_t enable_tail_lds() {
     static_assert(kTailLdsMax == 160 * 1024, "the first size tried is the largest");
     for (int kb : {160, 128, 64}) {
         const int bytes = kb * 1024;
-        hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(&klay::col_fwd_kernel), hipFuncAttributeMaxDynamicSharedMemorySize, bytes);
-        if (e == hipSuccess)
-            e = hipFuncSetAttribute(reinterpret_cast<const void*>(&klay::col_bwd_kernel), hipFuncAttributeMaxDynamicSharedMemorySize, bytes);
+        hipError_t e = hipSuccess;
+        for (const void* kernel : {reinterpret_cast<const void*>(&klay::col_fwd_kernel<1>), reinterpret_cast<const void*>(&klay::col_bwd_kernel<1>),
+                                   reinterpret_cast<const void*>(&klay::col_fwd_kernel<2>), reinterpret_cast<const void*>(&klay::col_bwd_kernel<2>)})
+            if (e == hipSuccess) e = hipFuncSetAttribute(kernel, hipFuncAttributeMaxDynamicSharedMemorySize, bytes);
         if (e == hipSuccess) return (size_t)bytes;
         (void)hipGetLastError();
     }
     return 0;
+}
+
+// Columns per workgroup: two once there are more columns than compute units and two fit the LDS (a column of its own
+// round would wait for the same dependent steps again; two cost little more than one).
+int tail_columns(int B, const int64_t (&size)[2], size_t lds_bytes) {
+    // (the reverse kernel holds kColOwn<2> times four values per thread of a layer)
+    return B > 256 && std::max(size[0], size[1]) <= 4 * klay::kColOwn<2> * klay::kColThreads &&
+                   (size_t)(size[0] + size[1]) * 2 * sizeof(float) <= lds_bytes ? 2 : 1;
 }
 
 // The column-major value buffer of a persistent forward launch: `T` floats a column.  `at`: entry of the layer below
@@ -881,8 +913,9 @@ void launch_tail_fwd(const klay_circuit* c, const TailChoice& t, const float* ac
     }
     int64_t size[2];
     tail_lds(p, t.first - 1, t.first - 1, size);
-    hipLaunchKernelGGL(klay::col_fwd_kernel, dim3((unsigned)B), dim3(klay::kColThreads), (size_t)(size[0] + size[1]) * sizeof(float), s,
-                       c->d_tail + (t.first - p.tail_first), p.num_layers - t.first + 1, t.first & 1, c->d_blocks[0], c->n_blocks[0], c->d_tables, start,
+    const int ct = tail_columns(B, size, c->tail_lds_bytes);
+    hipLaunchKernelGGL((ct == 2 ? klay::col_fwd_kernel<2> : klay::col_fwd_kernel<1>), dim3((unsigned)((B + ct - 1) / ct)), dim3(klay::kColThreads),
+                       (size_t)(size[0] + size[1]) * ct * sizeof(float), s, c->d_tail + (t.first - p.tail_first), p.num_layers - t.first + 1, t.first & 1, c->d_blocks[0], c->n_blocks[0], c->d_tables, start,
                        nb, start_T, B, ld, semiring, (int)size[0], keep ? tb : nullptr, (int)buf.T, leaf, c->d_root_pos, p.num_roots, out);
 }
 
@@ -906,8 +939,9 @@ void launch_tail_bwd(const klay_circuit* c, int last, int last_at, const float* 
         cached = L - l + 1;
         cache_at = (int)((a ? size[0] : 0) + size[a] - sum);
     }
-    hipLaunchKernelGGL(klay::col_bwd_kernel, dim3((unsigned)B), dim3(klay::kColThreads), (size_t)(size[0] + size[1]) * sizeof(float), s,
-                       c->d_tail + (L - p.tail_first), L - last, last_at, L & 1, c->d_blocks[1], c->n_blocks[1], c->d_tables, dout, c->d_top_ptr,
+    const int ct = tail_columns(B, size, c->tail_lds_bytes);
+    hipLaunchKernelGGL((ct == 2 ? klay::col_bwd_kernel<2> : klay::col_bwd_kernel<1>), dim3((unsigned)((B + ct - 1) / ct)), dim3(klay::kColThreads),
+                       (size_t)(size[0] + size[1]) * ct * sizeof(float), s, c->d_tail + (L - p.tail_first), L - last, last_at, L & 1, c->d_blocks[1], c->n_blocks[1], c->d_tables, dout, c->d_top_ptr,
                        c->d_top_root, p.num_roots, B, ld, (int)size[0], cached, cache_at, tb, T, top_multi, res);
 }
 
@@ -1073,16 +1107,24 @@ Workspace64 workspace_layout64(const klay_circuit* c, int ld) {
     return w;
 }
 
-// two columns per lane (16-byte loads) once the batch is wider than a wave; ld is even then
+// Two columns per lane (16-byte loads) where that leaves enough waves (as in the fp32 kernel); one where an entry takes an
+// exponential and a wave has room for the row (up to 64 columns): those passes wait for arithmetic, and twice the waves
+// hide it (85000 nodes at B = 33, per launch: logsumexp 8.0 us with two and 6.8 with one, plain sums 5.1 us with one and 4.4 with
+// two).
 template <int OP>
-void launch_pass64(const klay::f64::PassArgs& a, hipStream_t s) {
+void launch_pass64(klay::f64::PassArgs a, hipStream_t s) {
     if (a.n_total <= 0) return;
-    const unsigned rows = (unsigned)(((int64_t)a.n_total + 3) / 4);
-    if (a.B > 64) {
-        hipLaunchKernelGGL((klay::f64::pass_kernel<OP, 2>), dim3(rows, (unsigned)((a.B + 127) / 128)), dim3(256), 0, s, a);
-    } else {
-        hipLaunchKernelGGL((klay::f64::pass_kernel<OP, 1>), dim3(rows, 1), dim3(256), 0, s, a);
-    }
+    const bool arithmetic = OP == klay::OP_LSE || OP == klay::OP_SOFTMAX_BWD;
+    const int vec = a.B == 1 || (arithmetic && a.B <= 64) || (int64_t)a.n_total * row_lanes(a.B, 2) < 64 * kFillWaves ? 1 : 2;
+    a.lanes = row_lanes(a.B, vec);
+    a.per_wave = 64 / a.lanes;
+    a.inverse = row_inverse(a.lanes);
+    const dim3 grid(row_blocks(a.n_total, a.lanes), (unsigned)((a.B + a.lanes * vec - 1) / (a.lanes * vec)));
+    const bool one = a.per_wave == 1;
+    if (vec == 2 && one) hipLaunchKernelGGL((klay::f64::pass_kernel<OP, 2, true>), grid, dim3(256), 0, s, a);
+    else if (vec == 2) hipLaunchKernelGGL((klay::f64::pass_kernel<OP, 2, false>), grid, dim3(256), 0, s, a);
+    else if (one) hipLaunchKernelGGL((klay::f64::pass_kernel<OP, 1, true>), grid, dim3(256), 0, s, a);
+    else hipLaunchKernelGGL((klay::f64::pass_kernel<OP, 1, false>), grid, dim3(256), 0, s, a);
 }
 
 void launch_pass64(int op, const klay::f64::PassArgs& a, hipStream_t s) {

@@ -51,12 +51,13 @@ struct PassArgs {
     const int32_t* out_row;    // optional output row map for rows < n_main (combine pass)
     float* dst;                // output rows for rows < n_main
     float* dst_seg;            // scratch rows for rows >= n_main
+    int32_t lanes, per_wave;   // generic kernel: lanes per row, rows per wave
+    uint32_t inverse;          // see lane_group
     int32_t row_begin;         // first row this launch evaluates
     int32_t n_main;
     int32_t n_total;
     int32_t B;
     int32_t ld;
-    int32_t iters;             // row groups per wave
     int* zero_flag;            // OP_SUM_P, OP_PROD_BWD_P: set to 1 when an output row's own value is zero in some column
 };
 
@@ -71,6 +72,13 @@ constexpr float kLn2 = 0.6931471805599453f;
 // fexp are <= 0 here, so the rounding of x*log2(e) costs at most |x| e^x 2^-24 absolute.
 __device__ __forceinline__ float fexp(float x) { return __builtin_amdgcn_exp2f(x * kLog2e); }
 __device__ __forceinline__ float flog(float x) { return __builtin_amdgcn_logf(x) * kLn2; }
+
+__device__ __forceinline__ float max3(float a, float b, float c) {
+    float r;
+    asm("v_max3_f32 %0, %1, %2, %3" : "=v"(r) : "v"(a), "v"(b), "v"(c));
+    return r;
+}
+constexpr float kFltMax = 3.402823466e+38f;
 
 template <int VEC> struct Pack;
 template <> struct Pack<1> { using T = float; };
@@ -535,94 +543,154 @@ __global__ __launch_bounds__(256) void edge_kernel(const int2* __restrict__ task
 }
 
 // ---------------------------------------------------------------------------------------------
-// Generic gather-reduce: a lane group of W lanes owns one output row (W < 64: several rows per
-// wave, for small batches).  Also evaluates the segments of split rows (rows >= n_main, written
+// Generic gather-reduce: a group of a.lanes lanes owns one output row, VEC batch columns per lane,
+// so a wave takes 64 / lanes rows (any number of lanes: 21 rows at B = 10 with four columns a lane, 4 at B = 64).  Also evaluates the segments of split rows (rows >= n_main, written
 // to scratch rows) and the combine pass (out_row map).
+//   What bounds it is the number of vector memory instructions: a compute unit takes 16 cycles for each, whatever it
+// fetches, and the rows of a small batch are short.  Hence four columns per lane also where that leaves rows unaligned
+// (the loads need four bytes) or the batch is no multiple of four (the last lane steps back and shares columns with its
+// neighbour, computing the same values), the offsets of a row in one load, its entries four at a time, and
+// the second four gathers only where a row of the wave has more than four entries.  (800000 nodes at B = 10, free
+// literals, training step: 381 -> 301 us; power-law fan-ins, 1e7 edges at B = 64: 515 -> 472 us.  One column per lane and
+// eight gathers for every row before.)  A launch of few rows takes fewer columns per lane (launch_pass).
 // ---------------------------------------------------------------------------------------------
-template <int OP, int VEC, int W>
-__global__ __launch_bounds__(256) void pass_kernel(PassArgs a) {
-    constexpr int RPW = 64 / W;                       // rows per wave
-    constexpr int CH = (OP == OP_SOFTMAX_BWD) ? 4 : 8;    // sources in flight per lane
-    constexpr bool OWN = OpTraits<OP>::own;
-    const int lane = threadIdx.x & 63;
-    int wave = threadIdx.x >> 6;
-    if (W == 64) wave = __builtin_amdgcn_readfirstlane(wave);
-    const int sub = (W == 64) ? 0 : lane / W;
-    const int col = ((int)blockIdx.y * W + (lane % W)) * VEC;
-    if (col >= a.B) return;
-    const int blk = xcd_block((int)blockIdx.x, (int)gridDim.x);
-    const int64_t first_group = ((int64_t)blk * 4 + wave) * a.iters;
+template <int VEC>
+__device__ __forceinline__ void load_cols(float (&x)[VEC], const float* p) {
+    typedef float vf __attribute__((ext_vector_type(VEC), aligned(4)));
+    const vf t = *reinterpret_cast<const vf*>(p);
+#pragma unroll
+    for (int v = 0; v < VEC; ++v) x[v] = t[v];
+}
+template <>
+__device__ __forceinline__ void load_cols<1>(float (&x)[1], const float* p) { x[0] = *p; }
+template <int VEC>
+__device__ __forceinline__ void store_cols(float* p, const float (&x)[VEC]) {
+    typedef float vf __attribute__((ext_vector_type(VEC), aligned(4)));
+    vf t;
+#pragma unroll
+    for (int v = 0; v < VEC; ++v) t[v] = x[v];
+    *reinterpret_cast<vf*>(p) = t;
+}
+template <>
+__device__ __forceinline__ void store_cols<1>(float* p, const float (&x)[1]) { *p = x[0]; }
 
-    for (int it = 0; it < a.iters; ++it) {
-        const int64_t row64 = (first_group + it) * RPW + sub + a.row_begin;
-        if (row64 >= a.n_total) break;
-        const int row = (int)row64;
-        const int beg = a.ptr[row], end = a.ptr[row + 1];
-        if (a.idx[beg] == kSkip) continue;            // split row: evaluated by segments + combine
+// Which row of the wave a lane works for and its first column; false: none.  inverse = ceil(65536 / lanes), so that the
+// product below is lane / lanes for every lane of a wave.
+template <class Args>
+__device__ __forceinline__ bool lane_group(const Args& a, int vec, int& sub, int& col) {
+    const uint32_t lane = threadIdx.x & 63;
+    sub = (int)(lane * a.inverse >> 16);
+    col = ((int)blockIdx.y * a.lanes + (int)lane - sub * a.lanes) * vec;
+    return sub < a.per_wave && col < a.B;
+}
 
-        float nc[VEC];                                // OP_SOFTMAX_BWD: own value
-#pragma unroll
-        for (int v = 0; v < VEC; ++v) nc[v] = 0.0f;
-        if (OWN) {
-            // the row whose value this output belongs to: itself, the row a combine pass writes, or a segment's owner
-            const int owner = row < a.n_main ? (a.out_row ? a.out_row[row] : row) : a.seg_owner[row - a.n_main];
-            load_vec<VEC>(nc, a.own + (size_t)owner * a.ld + col);
-        }
-        float acc[VEC], mx[VEC];
-#pragma unroll
-        for (int v = 0; v < VEC; ++v) { acc[v] = identity<OP>(); mx[v] = -INFINITY; }
+typedef uint32_t Entries4 __attribute__((ext_vector_type(4), aligned(4)));
+typedef int32_t Offsets2 __attribute__((ext_vector_type(2), aligned(4)));
 
-        for (int j = beg; j < end; j += CH) {
-            const int n = end - j;
-            uint32_t id[CH];
-            bool wt[CH];
+__device__ __forceinline__ float finite(float m) { return __builtin_amdgcn_fmed3f(m, -kFltMax, kFltMax); }
+
+// four entries of a row joined to its state; `live` of them are part of the row
+template <int OP, int VEC>
+__device__ __forceinline__ void accumulate4(float (&acc)[VEC], float (&mx)[VEC], const float (&x)[4][VEC], const float (&y)[4][VEC],
+                                            float (&nc)[VEC], Entries4 e, int live) {
 #pragma unroll
-            for (int i = 0; i < CH; ++i) {                                    // padded array: always in bounds
-                const uint32_t raw = a.idx[j + i];
-                id[i] = raw == kSkip ? 0u : (raw & kIdMask);
-                wt[i] = (raw & kWeighted) != 0;
-            }
-            // all gathers are issued unconditionally: entries past the row's end are valid entries of
-            // later rows (or zero padding); their data is ignored below
-            float x[CH][VEC], y[CH][VEC];
+    for (int v = 0; v < VEC; ++v) {
+        if (OP == OP_LSE) {
+            // (mx kept finite, see the persistent kernels: one maximum for the four, no test for -inf)
+            const float x0 = live > 0 ? x[0][v] : -INFINITY, x1 = live > 1 ? x[1][v] : -INFINITY;
+            const float x2 = live > 2 ? x[2][v] : -INFINITY, x3 = live > 3 ? x[3][v] : -INFINITY;
+            const float m = finite(max3(max3(x0, x1, x2), x3, mx[v]));
+            acc[v] = fmaf(acc[v], fexp(mx[v] - m), (fexp(x0 - m) + fexp(x1 - m)) + (fexp(x2 - m) + fexp(x3 - m)));
+            mx[v] = m;
+        } else {
 #pragma unroll
-            for (int i = 0; i < CH; ++i) {
-                load_vec<VEC>(x[i], a.src + (size_t)id[i] * a.ld + col);
-                if (OP == OP_SOFTMAX_BWD) load_vec<VEC>(y[i], (wt[i] ? a.src2 : a.src) + (size_t)id[i] * a.ld + col);
-            }
-            // branch-free accumulation (a conditional use would let the compiler sink each load into
-            // its branch and serialise the gathers): a dead entry contributes the identity
-#pragma unroll
-            for (int i = 0; i < CH; ++i) {
-                const bool live = i < n;
-#pragma unroll
-                for (int v = 0; v < VEC; ++v) {
-                    const float dead = OP == OP_PROD ? 1.0f : ((OP == OP_LSE || OP == OP_MAX) ? -INFINITY : 0.0f);
-                    const float xv = live ? x[i][v] : dead;
-                    const float yv = OP == OP_SOFTMAX_BWD ? (live ? y[i][v] : -INFINITY) : 0.0f;
-                    accumulate<OP>(acc[v], mx[v], xv, yv, nc[v], live && wt[i]);
-                }
+            for (int i = 0; i < 4; ++i) {
+                const float xv = i < live ? x[i][v] : dead_value<OP>();
+                const float yv = OP == OP_SOFTMAX_BWD ? (i < live ? y[i][v] : -INFINITY) : 0.0f;
+                accumulate<OP>(acc[v], mx[v], xv, yv, nc[v], i < live && (e[i] & kWeighted) != 0);
             }
         }
-        float o[VEC];
-#pragma unroll
-        for (int v = 0; v < VEC; ++v) o[v] = finish<OP>(acc[v], mx[v]);
-        if (OP == OP_SUM_H && row < a.n_main && (a.idx[end - 1] & kRowFlag)) {
-#pragma unroll
-            for (int v = 0; v < VEC; ++v) o[v] = encode_h(o[v], nc[v]);
-        }
-        if (OpTraits<OP>::premul && row < a.n_main) {
-#pragma unroll
-            for (int v = 0; v < VEC; ++v) {
-                if (nc[v] == 0.0f && a.zero_flag) *a.zero_flag = 1;
-                o[v] = premultiply(o[v], nc[v]);
-            }
-        }
-        float* out;
-        if (row < a.n_main) out = a.dst + (size_t)(a.out_row ? a.out_row[row] : row) * a.ld + col;
-        else out = a.dst_seg + (size_t)(row - a.n_main) * a.ld + col;
-        store_vec<VEC>(out, o);
     }
+}
+
+template <int OP, int VEC>
+__global__ __launch_bounds__(256) void pass_kernel(PassArgs a) {
+    constexpr bool OWN = OpTraits<OP>::own;
+    int sub, colu;
+    if (!lane_group(a, VEC, sub, colu)) return;
+    const int col = colu <= a.B - VEC ? colu : a.B - VEC;
+    const int64_t row64 = ((int64_t)xcd_block((int)blockIdx.x, (int)gridDim.x) * 4 + (threadIdx.x >> 6)) * a.per_wave + sub + a.row_begin;
+    if (row64 >= a.n_total) return;
+    const int row = (int)row64;
+    const Offsets2 range = *reinterpret_cast<const Offsets2*>(a.ptr + row);
+    const int end = range.y;
+    int j = range.x;
+    // (entries past the row's end are entries of later rows or zero padding: they can be followed, their data is ignored)
+    Entries4 e0 = *reinterpret_cast<const Entries4*>(a.idx + j), e1 = *reinterpret_cast<const Entries4*>(a.idx + j + 4);
+    if (e0.x == kSkip) return;                        // split row: evaluated by segments + combine
+    float nc[VEC];
+#pragma unroll
+    for (int v = 0; v < VEC; ++v) nc[v] = 0.0f;
+    if (OWN) {
+        // the row whose value this output belongs to: itself, the row a combine pass writes, or a segment's owner
+        const int owner = row < a.n_main ? (a.out_row ? a.out_row[row] : row) : a.seg_owner[row - a.n_main];
+        load_cols<VEC>(nc, a.own + (size_t)owner * a.ld + col);
+    }
+    float acc[VEC], mx[VEC];
+#pragma unroll
+    for (int v = 0; v < VEC; ++v) { acc[v] = identity<OP>(); mx[v] = OP == OP_LSE ? -kFltMax : -INFINITY; }
+    uint32_t last = 0;
+    for (;;) {
+        float x0[4][VEC], x1[4][VEC], y0[4][VEC], y1[4][VEC];
+        auto gather = [&](Entries4 e, float (&x)[4][VEC], float (&y)[4][VEC]) {
+#pragma unroll
+            for (int i = 0; i < 4; ++i) {
+                const size_t off = (size_t)(e[i] == kSkip ? 0u : e[i] & kIdMask) * a.ld + col;
+                load_cols<VEC>(x[i], a.src + off);
+                if (OP == OP_SOFTMAX_BWD) load_cols<VEC>(y[i], ((e[i] & kWeighted) ? a.src2 : a.src) + off);
+            }
+        };
+        const bool second = __any(j + 4 < end), more = __any(j + 8 < end);
+        Entries4 n0 = e0, n1 = e1;
+        gather(e0, x0, y0);
+        if (second) gather(e1, x1, y1);
+        if (more) {
+            const int at = j + 8 < end ? j + 8 : range.x;        // (a row that has ended reads its first entries again)
+            n0 = *reinterpret_cast<const Entries4*>(a.idx + at);
+            n1 = *reinterpret_cast<const Entries4*>(a.idx + at + 4);
+        }
+        if (j < end) accumulate4<OP, VEC>(acc, mx, x0, y0, nc, e0, end - j);
+        if (second && j + 4 < end) accumulate4<OP, VEC>(acc, mx, x1, y1, nc, e1, end - j - 4);
+        if (j < end && OP == OP_SUM_H) {
+            const int at = end - j - 1;               // the row's last entry carries its flag
+            if (at < 8) {
+                const Entries4 e = at < 4 ? e0 : e1;
+                last = (at & 3) == 0 ? e.x : (at & 3) == 1 ? e.y : (at & 3) == 2 ? e.z : e.w;
+            }
+        }
+        j += 8;
+        if (!more) break;
+        e0 = n0;
+        e1 = n1;
+    }
+    float o[VEC];
+#pragma unroll
+    for (int v = 0; v < VEC; ++v) o[v] = OP == OP_LSE ? mx[v] + flog(acc[v]) : finish<OP>(acc[v], mx[v]);
+    if (OP == OP_SUM_H && row < a.n_main && (last & kRowFlag)) {
+#pragma unroll
+        for (int v = 0; v < VEC; ++v) o[v] = encode_h(o[v], nc[v]);
+    }
+    if (OpTraits<OP>::premul && row < a.n_main) {
+#pragma unroll
+        for (int v = 0; v < VEC; ++v) {
+            if (nc[v] == 0.0f && a.zero_flag) *a.zero_flag = 1;
+            o[v] = premultiply(o[v], nc[v]);
+        }
+    }
+    float* out;
+    if (row < a.n_main) out = a.dst + (size_t)(a.out_row ? a.out_row[row] : row) * a.ld + col;
+    else out = a.dst_seg + (size_t)(row - a.n_main) * a.ld + col;
+    store_cols<VEC>(out, o);
 }
 
 // ---------------------------------------------------------------------------------------------
@@ -704,6 +772,59 @@ __device__ __forceinline__ void combine_body(int row, const PassArgs& a) {
 template <int OP, int VEC, int NW>
 __global__ __launch_bounds__(NW * 64) void combine_kernel(PassArgs a) {
     combine_body<OP, VEC, NW>((int)blockIdx.x, a);
+}
+
+// The same for B <= 32: W lanes (a power of two) hold the columns of a partial row, so a wave takes 64 / W partial rows at
+// a time, four of them in flight; the lane groups meet in a butterfly, the four waves in LDS, in a fixed order.  (A lane
+// group per split row walked the partial rows of the widest row, up to a few hundred, alone.)
+template <int OP, int W>
+__global__ __launch_bounds__(256) void combine_small_kernel(PassArgs a) {
+    constexpr int G = 64 / W, CH = 4;
+    constexpr bool LSE = OP == OP_LSE;
+    __shared__ float part_v[4][W], part_m[LSE ? 4 : 1][LSE ? W : 1];
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    const int sub = lane / W, c = lane % W;
+    const int col = c < a.B ? c : a.B - 1;
+    const int row = (int)blockIdx.x;
+    const int beg = a.ptr[row], end = a.ptr[row + 1];
+    // (accm, accs): the reduction, or (maximum, sum of exp(x - maximum))
+    float accm = LSE ? -INFINITY : identity<OP>(), accs = 0.0f;
+    for (int j = beg + wave * G + sub; __any(j < end); j += 4 * G * CH) {
+        float x[CH];
+#pragma unroll
+        for (int i = 0; i < CH; ++i) {
+            const int at = j + i * 4 * G < end ? j + i * 4 * G : beg;
+            x[i] = a.src[(size_t)(a.idx[at] & kIdMask) * a.ld + col];
+        }
+#pragma unroll
+        for (int i = 0; i < CH; ++i) {
+            const bool live = j + i * 4 * G < end;
+            edge_combine<OP>(accm, accs, live ? x[i] : (LSE ? -INFINITY : identity<OP>()), live ? 1.0f : 0.0f);
+        }
+    }
+#pragma unroll
+    for (int d = W; d < 64; d <<= 1) {
+        const float om = __shfl_xor(accm, d), os = LSE ? __shfl_xor(accs, d) : 0.0f;
+        edge_combine<OP>(accm, accs, om, os);
+    }
+    if (sub == 0) {
+        part_v[wave][c] = LSE ? accs : accm;
+        if (LSE) part_m[wave][c] = accm;
+    }
+    __syncthreads();
+    if (threadIdx.x >= W || (int)threadIdx.x >= a.B) return;
+    for (int w = 1; w < 4; ++w) edge_combine<OP>(accm, accs, LSE ? part_m[w][c] : part_v[w][c], LSE ? part_v[w][c] : 0.0f);
+    const int out_row = a.out_row[row];
+    float o = LSE ? (accm == -INFINITY ? -INFINITY : accm + flog(accs)) : accm;
+    if (OP == OP_SUM_H || OP == OP_SUM_P) {
+        const float own = a.own[(size_t)out_row * a.ld + c];
+        if (OP == OP_SUM_H && (a.idx[end - 1] & kRowFlag)) o = encode_h(o, own);
+        if (OP == OP_SUM_P) {
+            if (own == 0.0f && a.zero_flag) *a.zero_flag = 1;
+            o = premultiply(o, own);
+        }
+    }
+    a.dst[(size_t)out_row * a.ld + c] = o;
 }
 
 // The main rows of a layer and the combine rows of its split rows in one launch, for the tiles whose segments
@@ -816,32 +937,61 @@ struct ColRun {
     }
 };
 
-__device__ __forceinline__ float col_at(const float* values, uint32_t slot) { return values[slot]; }
+// The values of a node in the CT columns of a workgroup.
+template <int CT> struct ColValue;
+template <> struct ColValue<1> { using T = float; };
+template <> struct ColValue<2> { typedef float T __attribute__((ext_vector_type(2))); };
 
-__device__ __forceinline__ float max3(float a, float b, float c) {
-    float r;
-    asm("v_max3_f32 %0, %1, %2, %3" : "=v"(r) : "v"(a), "v"(b), "v"(c));
-    return r;
-}
+// f of each column
+template <class F>
+__device__ __forceinline__ float each(F f, float a) { return f(a); }
+template <class F>
+__device__ __forceinline__ float each(F f, float a, float b) { return f(a, b); }
+template <class F>
+__device__ __forceinline__ float each(F f, float a, float b, float c) { return f(a, b, c); }
+using Float2 = ColValue<2>::T;
+template <class F>
+__device__ __forceinline__ Float2 each(F f, Float2 a) { return Float2{f(a.x), f(a.y)}; }
+template <class F>
+__device__ __forceinline__ Float2 each(F f, Float2 a, Float2 b) { return Float2{f(a.x, b.x), f(a.y, b.y)}; }
+template <class F>
+__device__ __forceinline__ Float2 each(F f, Float2 a, Float2 b, Float2 c) { return Float2{f(a.x, b.x, c.x), f(a.y, b.y, c.y)}; }
+__device__ __forceinline__ Float2 fexp(Float2 x) { return each([](float a) { return fexp(a); }, x); }
+__device__ __forceinline__ Float2 flog(Float2 x) { return each([](float a) { return flog(a); }, x); }
+__device__ __forceinline__ Float2 finite(Float2 x) { return each([](float a) { return finite(a); }, x); }
+__device__ __forceinline__ Float2 max3(Float2 a, Float2 b, Float2 c) { return each([](float x, float y, float z) { return max3(x, y, z); }, a, b, c); }
+__device__ __forceinline__ float bigger(float a, float b) { return b > a ? b : a; }
+__device__ __forceinline__ Float2 bigger(Float2 a, Float2 b) { return each([](float x, float y) { return bigger(x, y); }, a, b); }
+__device__ __forceinline__ float smaller(float a, float b) { return b > a ? a : b; }
+__device__ __forceinline__ Float2 smaller(Float2 a, Float2 b) { return each([](float x, float y) { return smaller(x, y); }, a, b); }
+__device__ __forceinline__ float muladd(float a, float b, float c) { return fmaf(a, b, c); }
+__device__ __forceinline__ Float2 muladd(Float2 a, Float2 b, Float2 c) { return each([](float x, float y, float z) { return fmaf(x, y, z); }, a, b, c); }
+
+template <class V>
+__device__ __forceinline__ V col_at(const V* values, uint32_t slot) { return values[slot]; }
 
 // lane i's value from lane i ^ (1 << step), for reductions in which the lanes below that distance already agree
+template <int STEP>
+__device__ __forceinline__ Float2 fly(Float2 x);
 template <int STEP>
 __device__ __forceinline__ float fly(float x) {
     constexpr int kCtrl = STEP == 0 ? 0xB1 : STEP == 1 ? 0x4E : STEP == 2 ? 0x141 : 0x140;      // quad_perm, half mirror, mirror
     if (STEP < 4) return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(x), kCtrl, 0xF, 0xF, true));
     return __shfl_xor(x, 1 << STEP);
 }
+template <int STEP>
+__device__ __forceinline__ Float2 fly(Float2 x) { return Float2{fly<STEP>(x.x), fly<STEP>(x.y)}; }
 
-template <int OP>
-__device__ __forceinline__ float col_join(float a, float b) {
-    if (OP == OP_PROD) return a * b;
-    if (OP == OP_MAX || OP == OP_LSE) return b > a ? b : a;      // (OP_LSE: the maxima)
-    return a + b;
+template <int OP, class V>
+__device__ __forceinline__ V col_join(V a, V b) {
+    if constexpr (OP == OP_PROD) return a * b;
+    else if constexpr (OP == OP_MAX || OP == OP_LSE) return bigger(a, b);      // (OP_LSE: the maxima)
+    else return a + b;
 }
 
 // reduce over the 2^k lanes of a row; every lane of the row ends with the result
-template <int OP>
-__device__ __forceinline__ float col_fly(float x, int k) {
+template <int OP, class V>
+__device__ __forceinline__ V col_fly(V x, int k) {
     if (k >= 1) x = col_join<OP>(x, fly<0>(x));
     if (k >= 2) x = col_join<OP>(x, fly<1>(x));
     if (k >= 3) x = col_join<OP>(x, fly<2>(x));
@@ -854,27 +1004,24 @@ __device__ __forceinline__ float col_fly(float x, int k) {
 // Logsumexp in the persistent kernel: m = maximum so far, kept finite (between -FLT_MAX and FLT_MAX, so that no
 // difference is inf - inf: a row of impossible children ends as -FLT_MAX + log(0) = -inf, an infinite weight as inf),
 // s = sum of exp(x - m).
-constexpr float kFltMax = 3.402823466e+38f;
-
-__device__ __forceinline__ float finite(float m) { return __builtin_amdgcn_fmed3f(m, -kFltMax, kFltMax); }
-
 // the value of a row of two, of four entries
-template <int OP>
-__device__ __forceinline__ float col_two(float x, float y) {
+template <int OP, class V>
+__device__ __forceinline__ V col_two(V x, V y) {
     if (OP != OP_LSE) return col_join<OP>(x, y);
-    const float hi = y > x ? y : x, lo = y > x ? x : y;
+    const V hi = bigger(x, y), lo = smaller(x, y);
     return hi + flog(1.0f + fexp(lo - finite(hi)));
 }
-template <int OP>
-__device__ __forceinline__ float col_four(float x0, float x1, float x2, float x3) {
+template <int OP, class V>
+__device__ __forceinline__ V col_four(V x0, V x1, V x2, V x3) {
     if (OP != OP_LSE) return col_join<OP>(col_join<OP>(x0, x1), col_join<OP>(x2, x3));
-    const float m = finite(max3(max3(x0, x1, x2), x3, -kFltMax));
+    const V m = finite(max3(max3(x0, x1, x2), x3, V(-kFltMax)));
     return m + flog((fexp(x0 - m) + fexp(x1 - m)) + (fexp(x2 - m) + fexp(x3 - m)));
 }
 
 // Reads one word of every 128 bytes of the blocks, shared out among the workgroups of an XCD (every eighth one), so that
 // they are in its L2 when the waves get to them: the workgroups walk the layers in step, and without this the first
-// one to reach a block would wait for the memory behind the L2, a few thousand cycles, at every layer.
+// one to reach a block would wait for the memory behind the L2, a few thousand cycles, at every layer (1m nodes at B = 256:
+// 413 -> 390 us; a few workgroups alone read more than they save, so only from 64 on).
 __device__ __forceinline__ void col_touch(const Line* blocks, int n_blocks) {
     const uint32_t* words = reinterpret_cast<const uint32_t*>(blocks);
     const int n = n_blocks * 16, share = ((int)gridDim.x + 7) / 8 * kColThreads;
@@ -887,20 +1034,20 @@ __device__ __forceinline__ void col_touch(const Line* blocks, int n_blocks) {
 }
 
 // The values of the rows that two words (four entries) of a lane stand for: four rows of one entry, two of two, one of four.
-template <int OP, int KIND>
-__device__ __forceinline__ void col_rows(const float* below, uint32_t a, uint32_t b, float* v) {
-    const float x0 = col_at(below, a & 0xFFFFu), x1 = col_at(below, a >> 16), x2 = col_at(below, b & 0xFFFFu), x3 = col_at(below, b >> 16);
+template <int OP, int KIND, class V>
+__device__ __forceinline__ void col_rows(const V* below, uint32_t a, uint32_t b, V* v) {
+    const V x0 = col_at(below, a & 0xFFFFu), x1 = col_at(below, a >> 16), x2 = col_at(below, b & 0xFFFFu), x3 = col_at(below, b >> 16);
     if (KIND == 0) { v[0] = x0; v[1] = x1; v[2] = x2; v[3] = x3; }
     if (KIND == 1) { v[0] = col_two<OP>(x0, x1); v[1] = col_two<OP>(x2, x3); }
     if (KIND == 2) v[0] = col_four<OP>(x0, x1, x2, x3);
 }
 
 // the last rows of a run, in one quarter of a block
-template <int OP, int KIND>
-__device__ __forceinline__ void col_fwd_rest(const float* below, uint32_t a, uint32_t b, float* out, int rows) {
+template <int OP, int KIND, class V>
+__device__ __forceinline__ void col_fwd_rest(const V* below, uint32_t a, uint32_t b, V* out, int rows) {
     constexpr int N = 4 >> KIND;
     const int lane = threadIdx.x & 63;
-    float v[N];
+    V v[N];
     col_rows<OP, KIND>(below, a, b, v);
 #pragma unroll
     for (int i = 0; i < N; ++i) {
@@ -910,14 +1057,14 @@ __device__ __forceinline__ void col_fwd_rest(const float* below, uint32_t a, uin
 }
 
 // a run of kind 0, 1 or 2
-template <int OP, int KIND>
-__device__ __forceinline__ void col_fwd_short(ColWalk& walk, const float* below, float* out, int rows) {
+template <int OP, int KIND, class V>
+__device__ __forceinline__ void col_fwd_short(ColWalk& walk, const V* below, V* out, int rows) {
     constexpr int N = 4 >> KIND;                     // rows of a lane in a quarter of a block
     out += threadIdx.x & 63;
     Line w0, w1;
     for (; rows >= 256 * N; rows -= 256 * N, out += 256 * N) {
         walk.block(w0, w1);
-        float v[4 * N];
+        V v[4 * N];
         col_rows<OP, KIND>(below, w0.x, w0.y, v);
         col_rows<OP, KIND>(below, w0.z, w0.w, v + N);
         col_rows<OP, KIND>(below, w1.x, w1.y, v + 2 * N);
@@ -937,9 +1084,10 @@ __device__ __forceinline__ void col_fwd_short(ColWalk& walk, const float* below,
 }
 
 // the lanes of a row have (m, s): its value
-__device__ __forceinline__ float col_lse_fly(float m, float s, int k) {
+template <class V>
+__device__ __forceinline__ V col_lse_fly(V m, V s, int k) {
     if (k > 0) {
-        const float m2 = col_fly<OP_LSE>(m, k);
+        const V m2 = col_fly<OP_LSE>(m, k);
         s = col_fly<OP_SUM>(s * fexp(m - m2), k);
         m = m2;
     }
@@ -947,30 +1095,30 @@ __device__ __forceinline__ float col_lse_fly(float m, float s, int k) {
 }
 
 // one line of a row that takes several lanes or lines, joined to what the lines before gave
-template <int OP>
-__device__ __forceinline__ void col_long(const float* below, Line w, bool fresh, float& m, float& s) {
-    const float x0 = col_at(below, w.x & 0xFFFFu), x1 = col_at(below, w.x >> 16), x2 = col_at(below, w.y & 0xFFFFu), x3 = col_at(below, w.y >> 16);
-    const float x4 = col_at(below, w.z & 0xFFFFu), x5 = col_at(below, w.z >> 16), x6 = col_at(below, w.w & 0xFFFFu), x7 = col_at(below, w.w >> 16);
+template <int OP, class V>
+__device__ __forceinline__ void col_long(const V* below, Line w, bool fresh, V& m, V& s) {
+    const V x0 = col_at(below, w.x & 0xFFFFu), x1 = col_at(below, w.x >> 16), x2 = col_at(below, w.y & 0xFFFFu), x3 = col_at(below, w.y >> 16);
+    const V x4 = col_at(below, w.z & 0xFFFFu), x5 = col_at(below, w.z >> 16), x6 = col_at(below, w.w & 0xFFFFu), x7 = col_at(below, w.w >> 16);
     if (OP == OP_LSE) {
-        const float m2 = finite(max3(max3(max3(x0, x1, x2), x3, x4), max3(x5, x6, x7), m));
-        const float s2 = ((fexp(x0 - m2) + fexp(x1 - m2)) + (fexp(x2 - m2) + fexp(x3 - m2))) +
+        const V m2 = finite(max3(max3(max3(x0, x1, x2), x3, x4), max3(x5, x6, x7), m));
+        const V s2 = ((fexp(x0 - m2) + fexp(x1 - m2)) + (fexp(x2 - m2) + fexp(x3 - m2))) +
                          ((fexp(x4 - m2) + fexp(x5 - m2)) + (fexp(x6 - m2) + fexp(x7 - m2)));
-        s = fresh ? s2 : fmaf(s, fexp(m - m2), s2);
+        s = fresh ? s2 : muladd(s, fexp(m - m2), s2);
         m = m2;
     } else {
-        const float x = col_join<OP>(col_four<OP>(x0, x1, x2, x3), col_four<OP>(x4, x5, x6, x7));
+        const V x = col_join<OP>(col_four<OP>(x0, x1, x2, x3), col_four<OP>(x4, x5, x6, x7));
         s = fresh ? x : col_join<OP>(s, x);
     }
 }
 
 // one layer, forward
-template <int OP>
-__device__ __forceinline__ void col_fwd_layer(ColWalk& walk, const float* below, float* here) {
+template <int OP, class V>
+__device__ __forceinline__ void col_fwd_layer(ColWalk& walk, const V* below, V* here) {
     const int lane = threadIdx.x & 63;
     Desc table = walk.table();
     ColRun run;
     for (int i = 0; run.read(walk, table, i);) {
-        float* out = here + run.slot;
+        V* out = here + run.slot;
         if (run.kind == 0) col_fwd_short<OP, 0>(walk, below, out, run.rows);
         else if (run.kind == 1) col_fwd_short<OP, 1>(walk, below, out, run.rows);
         else if (run.kind == 2) col_fwd_short<OP, 2>(walk, below, out, run.rows);
@@ -978,7 +1126,7 @@ __device__ __forceinline__ void col_fwd_layer(ColWalk& walk, const float* below,
             const int r = lane >> run.k, per = 64 >> run.k;
             const bool writes = (lane & ((1 << run.k) - 1)) == 0;
             for (int rows = run.rows; rows > 0; rows -= per, out += per) {
-                float m = -kFltMax, s = 0.0f;
+                V m = V(-kFltMax), s = V(0.0f);
                 Line w0, w1;
                 walk.block(w0, w1);
                 col_long<OP>(below, w0, true, m, s);
@@ -1009,6 +1157,17 @@ __device__ __forceinline__ void col_move(const float* values, int n, float* __re
     }
     if (whole + lane < n) to[whole + lane] = values[whole + lane];
 }
+// (two columns, T floats apart, `columns` of them there)
+__device__ __forceinline__ void col_move(const float* values, int n, float* __restrict__ to, int T, int columns) {
+    if (columns < 0) { col_move(values, n, to); return; }
+    const Float2* pairs = reinterpret_cast<const Float2*>(values);
+#pragma unroll 4
+    for (int i = threadIdx.x & 63; i < n; i += 64) {
+        const Float2 v = pairs[i];
+        to[i] = v.x;
+        if (columns > 1) to[(size_t)T + i] = v.y;
+    }
+}
 
 __device__ __forceinline__ float log1mexp_f(float x) {
     return x > -0.69314718f ? logf(-expm1f(x)) : log1pf(-expf(x));
@@ -1028,81 +1187,99 @@ struct SlabLeaf {
 // LDS: two value arrays, slots kColSlots + position; size0 floats for the layer below the first one and every second
 // layer from there, the rest for the others.  start_rows / start_at: the layer below the first one (start_rows of them),
 // column-major, T floats a column, from entry start_at on if start_T > 0, otherwise rows of the activation buffer.
-// tb (or null): every layer's values are kept there.
+// tb (or null): every layer's values are kept there.  CT: columns of a workgroup.
+template <int CT>
 __global__ __launch_bounds__(kColThreads) void col_fwd_kernel(const ColLayer* __restrict__ first, int n_layers, int first_is_and,
                                                               const Line* __restrict__ blocks, int n_blocks, const Desc* __restrict__ tables,
                                                               const float* __restrict__ start, int start_rows, int start_T,
                                                               int B, int ld, int semiring, int size0, float* __restrict__ tb, int T,
                                                               SlabLeaf leaf, const int32_t* __restrict__ root_pos, int R,
                                                               float* __restrict__ out) {
+    using V = typename ColValue<CT>::T;
     extern __shared__ float smem[];
-    float* below = smem;
-    float* here = smem + size0;
+    V* below = reinterpret_cast<V*>(smem);
+    V* here = below + size0;
     const int lane = threadIdx.x & 63;
     const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
-    const int col = (int)blockIdx.x;
+    const int col0 = (int)blockIdx.x * CT, columns = B - col0 < CT ? B - col0 : CT;      // (a column that is not there repeats the last one)
     const bool log_domain = semiring != 0;
     ColWalk walk;
     walk.start(blocks + (size_t)first->fwd_block[wave] * 128 + lane, tables + (size_t)first->fwd_table[wave] * kDescTable + lane);
-    col_touch(blocks, n_blocks);
+    if (gridDim.x >= 64) col_touch(blocks, n_blocks);
     if (threadIdx.x < 2) {
         // identities of the two kinds of layers, in the slots that padding names
-        float* a = threadIdx.x == 0 ? below : here;
-        a[kColPadAnd] = log_domain ? 0.0f : 1.0f;
-        a[kColPadOr] = log_domain ? -INFINITY : 0.0f;
+        V* a = threadIdx.x == 0 ? below : here;
+        a[kColPadAnd] = V(log_domain ? 0.0f : 1.0f);
+        a[kColPadOr] = V(log_domain ? -INFINITY : 0.0f);
     }
     if (leaf.w) {
         // leaf layer into LDS; the transposed weights and the rows of layer 0 also go to global memory
         // for the reverse sweep (every column of [0, ld): the last workgroup zeroes the padding columns)
         for (int i = threadIdx.x; i < leaf.n0; i += kColThreads) {
             const int code = leaf.leaf_code[i];
-            float v;
-            if (code == INT32_MAX) v = log_domain ? 0.0f : 1.0f;
-            else if (code == INT32_MIN) v = log_domain ? -INFINITY : 0.0f;
-            else {
-                const int var = (code > 0 ? code : -code) - 1;
-                const size_t at = (size_t)col * leaf.V + var;
-                if (code > 0) v = leaf.w[at];
-                else if (leaf.wneg) v = leaf.wneg[at];
-                else v = log_domain ? log1mexp_f(leaf.w[at]) : 1.0f - leaf.w[at];
-            }
-            below[kColSlots + i] = v;
-            if (tb) {
-                leaf.act0[(size_t)i * ld + col] = v;
-                if (col == B - 1)
-                    for (int b = B; b < ld; ++b) leaf.act0[(size_t)i * ld + b] = 0.0f;
+            float* slot = reinterpret_cast<float*>(below + kColSlots + i);
+#pragma unroll
+            for (int c = 0; c < CT; ++c) {
+                const int col = col0 + (c < columns ? c : columns - 1);
+                float v;
+                if (code == INT32_MAX) v = log_domain ? 0.0f : 1.0f;
+                else if (code == INT32_MIN) v = log_domain ? -INFINITY : 0.0f;
+                else {
+                    const int var = (code > 0 ? code : -code) - 1;
+                    const size_t at = (size_t)col * leaf.V + var;
+                    if (code > 0) v = leaf.w[at];
+                    else if (leaf.wneg) v = leaf.wneg[at];
+                    else v = log_domain ? log1mexp_f(leaf.w[at]) : 1.0f - leaf.w[at];
+                }
+                slot[c] = v;
+                if (tb) {
+                    leaf.act0[(size_t)i * ld + col] = v;
+                    if (col == B - 1)
+                        for (int b = B; b < ld; ++b) leaf.act0[(size_t)i * ld + b] = 0.0f;
+                }
             }
         }
         if (tb)
-            for (int v = threadIdx.x; v < leaf.V; v += kColThreads) {
-                leaf.wT[(size_t)v * ld + col] = leaf.w[(size_t)col * leaf.V + v];
-                if (col == B - 1)
-                    for (int b = B; b < ld; ++b) leaf.wT[(size_t)v * ld + b] = 0.0f;
-            }
+            for (int v = threadIdx.x; v < leaf.V; v += kColThreads)
+                for (int c = 0; c < columns; ++c) {
+                    const int col = col0 + c;
+                    leaf.wT[(size_t)v * ld + col] = leaf.w[(size_t)col * leaf.V + v];
+                    if (col == B - 1)
+                        for (int b = B; b < ld; ++b) leaf.wT[(size_t)v * ld + b] = 0.0f;
+                }
     } else {
-        for (int i = threadIdx.x; i < start_rows; i += kColThreads)
-            below[kColSlots + i] = start_T > 0 ? start[(size_t)col * start_T + i] : start[(size_t)i * ld + col];
+        for (int i = threadIdx.x; i < start_rows; i += kColThreads) {
+            float* slot = reinterpret_cast<float*>(below + kColSlots + i);
+#pragma unroll
+            for (int c = 0; c < CT; ++c) {
+                const int col = col0 + (c < columns ? c : columns - 1);
+                slot[c] = start_T > 0 ? start[(size_t)col * start_T + i] : start[(size_t)i * ld + col];
+            }
+        }
     }
-    float* tbc = tb ? tb + (size_t)col * T : nullptr;
+    float* tbc = tb ? tb + (size_t)col0 * T : nullptr;
     for (int t = 0; t < n_layers; ++t) {
         const bool is_and = ((t & 1) == 0) == (first_is_and != 0);
         __syncthreads();
         if (wave == kColFwdWaves) {
             // the wave that keeps the values, a layer behind the others (in a wave that computes, the wait for the next
             // lines would wait for the stores as well)
-            if (tbc && t > 0) col_move(below + kColSlots, first[t - 1].n, tbc + first[t - 1].at);
+            if (tbc && t > 0) col_move(reinterpret_cast<const float*>(below + kColSlots), first[t - 1].n, tbc + first[t - 1].at, T, CT == 1 ? -1 : columns);
         } else if (is_and) {
             if (log_domain) col_fwd_layer<OP_SUM>(walk, below, here);
             else col_fwd_layer<OP_PROD>(walk, below, here);
         } else if (semiring == 1) col_fwd_layer<OP_LSE>(walk, below, here);
         else if (semiring == 2) col_fwd_layer<OP_MAX>(walk, below, here);
         else col_fwd_layer<OP_SUM>(walk, below, here);
-        float* tmp = below; below = here; here = tmp;
+        V* tmp = below; below = here; here = tmp;
     }
     __syncthreads();
-    if (wave == kColFwdWaves && tbc) col_move(below + kColSlots, first[n_layers - 1].n, tbc + first[n_layers - 1].at);
+    if (wave == kColFwdWaves && tbc) col_move(reinterpret_cast<const float*>(below + kColSlots), first[n_layers - 1].n, tbc + first[n_layers - 1].at, T, CT == 1 ? -1 : columns);
     // roots: the top layer is in LDS
-    for (int r = threadIdx.x; r < R; r += kColThreads) out[(size_t)col * R + r] = below[kColSlots + root_pos[r]];
+    for (int r = threadIdx.x; r < R; r += kColThreads) {
+        const float* slot = reinterpret_cast<const float*>(below + kColSlots + root_pos[r]);
+        for (int c = 0; c < columns; ++c) out[(size_t)(col0 + c) * R + r] = slot[c];
+    }
 }
 
 // One step of the reverse sweep.  OR: the step goes through an OR layer; its weighted edges (bit 15 of an entry) read the
@@ -1110,35 +1287,37 @@ __global__ __launch_bounds__(kColThreads) void col_fwd_kernel(const ColLayer* __
 // Otherwise every edge passes the adjoint on, and a row that is an OR node with more than one child (bit 15 of its
 // entries) is stored in that form, again with the row's own value.
 // own: the values of the rows by slot; it may be the array the adjoints go to (a slot is read by the lanes of its row only).
-template <bool OR>
-__device__ __forceinline__ float col_bwd_entry(const float* above, uint32_t e, float own) {
-    const float g = col_at(above, e & 0x7FFFu);
-    return OR && (e & 0x8000u) ? decode_h(g, own) : g;
+template <bool OR, class V>
+__device__ __forceinline__ V col_bwd_entry(const V* above, uint32_t e, V own) {
+    const V g = col_at(above, e & 0x7FFFu);
+    return OR && (e & 0x8000u) ? each([](float a, float b) { return decode_h(a, b); }, g, own) : g;
 }
+template <class V>
+__device__ __forceinline__ V col_encode(V g, V own) { return each([](float a, float b) { return encode_h(a, b); }, g, own); }
 
 // the adjoints of the rows that two words (four entries) of a lane stand for; own: their values
-template <bool OR, int KIND>
-__device__ __forceinline__ void col_bwd_rows(const float* above, uint32_t a, uint32_t b, const float* own, float* v) {
+template <bool OR, int KIND, class V>
+__device__ __forceinline__ void col_bwd_rows(const V* above, uint32_t a, uint32_t b, const V* own, V* v) {
     constexpr int N = 4 >> KIND;
-    const float o0 = own[0], o1 = own[KIND == 0 ? 1 : 0], o2 = own[KIND == 0 ? 2 : KIND == 1 ? 1 : 0], o3 = own[KIND == 0 ? 3 : KIND == 1 ? 1 : 0];
-    const float x0 = col_bwd_entry<OR>(above, a & 0xFFFFu, o0), x1 = col_bwd_entry<OR>(above, a >> 16, o1);
-    const float x2 = col_bwd_entry<OR>(above, b & 0xFFFFu, o2), x3 = col_bwd_entry<OR>(above, b >> 16, o3);
+    const V o0 = own[0], o1 = own[KIND == 0 ? 1 : 0], o2 = own[KIND == 0 ? 2 : KIND == 1 ? 1 : 0], o3 = own[KIND == 0 ? 3 : KIND == 1 ? 1 : 0];
+    const V x0 = col_bwd_entry<OR>(above, a & 0xFFFFu, o0), x1 = col_bwd_entry<OR>(above, a >> 16, o1);
+    const V x2 = col_bwd_entry<OR>(above, b & 0xFFFFu, o2), x3 = col_bwd_entry<OR>(above, b >> 16, o3);
     if (KIND == 0) { v[0] = x0; v[1] = x1; v[2] = x2; v[3] = x3; }
     if (KIND == 1) { v[0] = x0 + x1; v[1] = x2 + x3; }
     if (KIND == 2) v[0] = (x0 + x1) + (x2 + x3);
     if (!OR) {
         const uint32_t e[4] = {a, KIND == 0 ? a >> 16 : b, b, b >> 16};
 #pragma unroll
-        for (int i = 0; i < N; ++i) v[i] = (e[i] & 0x8000u) ? encode_h(v[i], own[i]) : v[i];
+        for (int i = 0; i < N; ++i) v[i] = (e[i] & 0x8000u) ? col_encode(v[i], own[i]) : v[i];
     }
 }
 
 // a quarter of a block (FULL: all its rows are there)
-template <bool OR, int KIND, bool FULL>
-__device__ __forceinline__ void col_bwd_quarter(const float* above, uint32_t a, uint32_t b, const float* own_at, float* out, int rows) {
+template <bool OR, int KIND, bool FULL, class V>
+__device__ __forceinline__ void col_bwd_quarter(const V* above, uint32_t a, uint32_t b, const V* own_at, V* out, int rows) {
     constexpr int N = 4 >> KIND;
     const int lane = threadIdx.x & 63;
-    float v[N], own[N];
+    V v[N], own[N];
 #pragma unroll
     for (int i = 0; i < N; ++i) own[i] = own_at[FULL || lane + 64 * i < rows ? 64 * i : -lane];
     col_bwd_rows<OR, KIND>(above, a, b, own, v);
@@ -1150,8 +1329,8 @@ __device__ __forceinline__ void col_bwd_quarter(const float* above, uint32_t a, 
 }
 
 // a run of kind 0, 1 or 2
-template <bool OR, int KIND>
-__device__ __forceinline__ void col_bwd_short(ColWalk& walk, const float* above, const float* own_at, float* out, int rows) {
+template <bool OR, int KIND, class V>
+__device__ __forceinline__ void col_bwd_short(ColWalk& walk, const V* above, const V* own_at, V* out, int rows) {
     constexpr int N = 4 >> KIND;
     out += threadIdx.x & 63;
     own_at += threadIdx.x & 63;
@@ -1174,22 +1353,22 @@ __device__ __forceinline__ void col_bwd_short(ColWalk& walk, const float* above,
     }
 }
 
-template <bool OR>
-__device__ __forceinline__ float col_bwd_long(const float* above, Line w, float own) {
+template <bool OR, class V>
+__device__ __forceinline__ V col_bwd_long(const V* above, Line w, V own) {
     return ((col_bwd_entry<OR>(above, w.x & 0xFFFFu, own) + col_bwd_entry<OR>(above, w.x >> 16, own)) +
             (col_bwd_entry<OR>(above, w.y & 0xFFFFu, own) + col_bwd_entry<OR>(above, w.y >> 16, own))) +
            ((col_bwd_entry<OR>(above, w.z & 0xFFFFu, own) + col_bwd_entry<OR>(above, w.z >> 16, own)) +
             (col_bwd_entry<OR>(above, w.w & 0xFFFFu, own) + col_bwd_entry<OR>(above, w.w >> 16, own)));
 }
 
-template <bool OR>
-__device__ __forceinline__ void col_bwd_layer(ColWalk& walk, const float* above, float* here, const float* owns) {
+template <bool OR, class V>
+__device__ __forceinline__ void col_bwd_layer(ColWalk& walk, const V* above, V* here, const V* owns) {
     const int lane = threadIdx.x & 63;
     Desc table = walk.table();
     ColRun run;
     for (int i = 0; run.read(walk, table, i);) {
-        float* out = here + run.slot;
-        const float* own_at = owns + run.slot;
+        V* out = here + run.slot;
+        const V* own_at = owns + run.slot;
         if (run.kind == 0) col_bwd_short<OR, 0>(walk, above, own_at, out, run.rows);
         else if (run.kind == 1) col_bwd_short<OR, 1>(walk, above, own_at, out, run.rows);
         else if (run.kind == 2) col_bwd_short<OR, 2>(walk, above, own_at, out, run.rows);
@@ -1197,11 +1376,11 @@ __device__ __forceinline__ void col_bwd_layer(ColWalk& walk, const float* above,
             const int r = lane >> run.k, per = 64 >> run.k;
             const bool writes = (lane & ((1 << run.k) - 1)) == 0;
             for (int rows = run.rows; rows > 0; rows -= per, out += per, own_at += per) {
-                const float own = own_at[r < rows ? r : 0];
+                const V own = own_at[r < rows ? r : 0];
                 Line w0, w1;
                 walk.block(w0, w1);
                 const uint32_t flag = w0.x & 0x8000u;
-                float acc = col_bwd_long<OR>(above, w0, own);
+                V acc = col_bwd_long<OR>(above, w0, own);
                 if (run.kind == 3) {
                     acc += col_bwd_long<OR>(above, w1, own);
                     for (int b = 1; b < run.blocks; ++b) {
@@ -1210,7 +1389,7 @@ __device__ __forceinline__ void col_bwd_layer(ColWalk& walk, const float* above,
                     }
                 }
                 acc = col_fly<OP_SUM>(acc, run.k);
-                if (!OR && flag) acc = encode_h(acc, own);
+                if (!OR && flag) acc = col_encode(acc, own);
                 if (writes && r < rows) out[r] = acc;
             }
         }
@@ -1239,8 +1418,9 @@ struct ColBwdOut {
 // of OR nodes with more than one child are kept in the one-gather form throughout, also on the way out; top_multi
 // (or null) flags such nodes of the top layer for the seed.
 // (tb is not __restrict__: a load known to be invariant would be moved down past the barrier to its use.)
-constexpr int kColOwn = (int)((kTailRowsCap + 4 * kColThreads - 1) / (4 * kColThreads));
+template <int CT> constexpr int kColOwn = CT == 1 ? (int)((kTailRowsCap + 4 * kColThreads - 1) / (4 * kColThreads)) : 3;      // (two columns: where no layer is longer)
 
+template <int CT>
 __global__ __launch_bounds__(kColThreads) void col_bwd_kernel(const ColLayer* __restrict__ top, int n_steps, int last_at,
                                                               int top_is_and, const Line* __restrict__ blocks, int n_blocks,
                                                               const Desc* __restrict__ tables, const float* __restrict__ dout,
@@ -1248,48 +1428,59 @@ __global__ __launch_bounds__(kColThreads) void col_bwd_kernel(const ColLayer* __
                                                               int R, int B, int ld, int size0, int cached, int cache_at,
                                                               const float* tb, int T,
                                                               const uint32_t* __restrict__ top_multi, ColBwdOut res) {
+    using V = typename ColValue<CT>::T;
     extern __shared__ float smem[];
-    float* above = smem;
-    float* here = smem + size0;
+    V* above = reinterpret_cast<V*>(smem);
+    V* here = above + size0;
+    V* const cache = above + cache_at;
     const int lane = threadIdx.x & 63;
     const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
-    const int col = (int)blockIdx.x;
-    const float* tbc = tb + (size_t)col * T;
+    const int col0 = (int)blockIdx.x * CT, columns = B - col0 < CT ? B - col0 : CT;      // (a column that is not there repeats the last one)
+    const float* tbc = tb + (size_t)col0 * T;
+    const int second = columns > 1 ? T : 0;               // where the second column's values are, from the first one's
     ColWalk walk;
     walk.start(blocks + (size_t)top->bwd_block[wave] * 128 + lane, tables + (size_t)top->bwd_table[wave] * kDescTable + lane);
-    col_touch(blocks, n_blocks);
+    if (gridDim.x >= 64) col_touch(blocks, n_blocks);
+    auto value_at = [&](int at) {
+        if constexpr (CT == 1) return tbc[at];
+        else return V{tbc[at], tbc[second + at]};
+    };
     // own values of the rows of step t (the t-th layer below the top one): how many and where
     auto own_of = [&](int t, int& n, int& at) {
         n = at = 0;
         if (t + 1 < n_steps) { n = top[-1 - t].n; at = top[-1 - t].at; }
         else if (t < n_steps && last_at >= 0) { n = res.n_last; at = last_at; }
     };
-    if (threadIdx.x < 2) (threadIdx.x == 0 ? above : here)[kColPadAnd] = 0.0f;       // what padding names: adjoint 0
+    if (threadIdx.x < 2) (threadIdx.x == 0 ? above : here)[kColPadAnd] = V(0.0f);       // what padding names: adjoint 0
     const int n_top = top->n, top_at = top->at;
     int cache_low = 0;
     if (cached > 0) {
         // the cached layers follow one another in tb
         cache_low = top[-cached].at;
         const int n = top_at - cache_low;
-        for (int i = threadIdx.x; i < n; i += kColThreads) smem[cache_at + i] = tbc[cache_low + i];
+        for (int i = threadIdx.x; i < n; i += kColThreads) cache[i] = value_at(cache_low + i);
     } else {
         int n, at;
         own_of(0, n, at);
-        for (int i = threadIdx.x; i < n; i += kColThreads) here[kColSlots + i] = tbc[at + i];
+        for (int i = threadIdx.x; i < n; i += kColThreads) here[kColSlots + i] = value_at(at + i);
     }
     for (int i = threadIdx.x; i < n_top; i += kColThreads) {      // adjoint seed of the top layer
-        float acc = 0.0f;
-        for (int t = top_ptr[i]; t < top_ptr[i + 1]; ++t) acc += dout[(size_t)col * R + top_root[t]];
-        if (top_multi && ((top_multi[i >> 5] >> (i & 31)) & 1u)) acc = encode_h(acc, tbc[top_at + i]);
+        V acc = V(0.0f);
+        for (int t = top_ptr[i]; t < top_ptr[i + 1]; ++t) {
+            const float* from = dout + (size_t)col0 * R + top_root[t];
+            if constexpr (CT == 1) acc += from[0];
+            else acc += V{from[0], from[columns > 1 ? R : 0]};
+        }
+        if (top_multi && ((top_multi[i >> 5] >> (i & 31)) & 1u)) acc = col_encode(acc, value_at(top_at + i));
         above[kColSlots + i] = acc;
     }
     int t = 0;
     for (; t + 1 < cached; ++t) {
-        const float* owns = smem + cache_at + (top[-1 - t].at - cache_low) - kColSlots;
+        const V* owns = cache + (top[-1 - t].at - cache_low) - kColSlots;
         __syncthreads();
         if (((t & 1) == 0) == (top_is_and != 0)) col_bwd_layer<false>(walk, above, here, owns);
         else col_bwd_layer<true>(walk, above, here, owns);
-        float* tmp = above; above = here; here = tmp;
+        V* tmp = above; above = here; here = tmp;
     }
     for (; t < n_steps; ++t) {
         int own_n, own_at;
@@ -1297,46 +1488,58 @@ __global__ __launch_bounds__(kColThreads) void col_bwd_kernel(const ColLayer* __
         // (the last rows are read, and written, by a lane that steps back to them; a layer of less than four rows reads
         // up to three floats past its own, still inside the workspace)
         typedef float f4u __attribute__((ext_vector_type(4), aligned(4)));
-        f4u own[kColOwn];
+        f4u own[kColOwn<CT>][CT];
 #pragma unroll
-        for (int i = 0; i < kColOwn; ++i) {
+        for (int i = 0; i < kColOwn<CT>; ++i) {
             const int at = 4 * ((int)threadIdx.x + i * kColThreads), back = own_n - 4 < 0 ? 0 : own_n - 4;
-            own[i] = *reinterpret_cast<const f4u*>(tbc + own_at + (at < back ? at : at < own_n ? back : 0));
+            const float* from = tbc + own_at + (at < back ? at : at < own_n ? back : 0);
+#pragma unroll
+            for (int c = 0; c < CT; ++c) own[i][c] = *reinterpret_cast<const f4u*>(from + (c ? second : 0));
         }
-        const float* owns = t < cached ? smem + cache_at + (top[-1 - t].at - cache_low) - kColSlots : here;
+        const V* owns = t < cached ? cache + (top[-1 - t].at - cache_low) - kColSlots : here;
         __syncthreads();
         if (((t & 1) == 0) == (top_is_and != 0)) col_bwd_layer<false>(walk, above, here, owns);
         else col_bwd_layer<true>(walk, above, here, owns);
         __syncthreads();
         // the adjoints above are done with: their array takes the next step's own values
 #pragma unroll
-        for (int i = 0; i < kColOwn; ++i) {
-            const int at = 4 * ((int)threadIdx.x + i * kColThreads);
+        for (int i = 0; i < kColOwn<CT>; ++i) {
+            const int at = 4 * ((int)threadIdx.x + i * kColThreads), back = own_n - 4 < 0 ? 0 : own_n - 4;
+            float* slot = reinterpret_cast<float*>(above + kColSlots + (at + 4 <= own_n ? at : back));
             if (at + 4 <= own_n) {
-                *reinterpret_cast<float4*>(above + kColSlots + at) = make_float4(own[i].x, own[i].y, own[i].z, own[i].w);
+                if constexpr (CT == 1) {
+                    *reinterpret_cast<float4*>(slot) = make_float4(own[i][0].x, own[i][0].y, own[i][0].z, own[i][0].w);
+                } else {
+                    *reinterpret_cast<float4*>(slot) = make_float4(own[i][0].x, own[i][CT - 1].x, own[i][0].y, own[i][CT - 1].y);
+                    *reinterpret_cast<float4*>(slot + 4) = make_float4(own[i][0].z, own[i][CT - 1].z, own[i][0].w, own[i][CT - 1].w);
+                }
             } else if (at < own_n) {
-                const int back = own_n - 4 < 0 ? 0 : own_n - 4;
                 for (int j = 0; j < 4; ++j)
-                    if (back + j < own_n) above[kColSlots + back + j] = own[i][j];
+                    if (back + j < own_n)
+                        for (int c = 0; c < CT; ++c) slot[j * CT + c] = own[i][c][j];
             }
         }
-        float* tmp = above; above = here; here = tmp;
+        V* tmp = above; above = here; here = tmp;
     }
     __syncthreads();
-    if (!res.wT) {
-        for (int r = threadIdx.x; r < res.n_last; r += kColThreads) res.g_cols[(size_t)col * res.n_last + r] = above[kColSlots + r];
-        return;
-    }
-    for (int v = threadIdx.x; v < res.V; v += kColThreads) {
-        const int pr = res.pos_row[v], nr = res.neg_row[v];
-        float d = pr >= 0 ? above[kColSlots + pr] : 0.0f, dn = 0.0f;
-        if (nr >= 0) {
-            const float gn = above[kColSlots + nr];
-            if (res.mode == 2) dn = gn;
-            else if (gn != 0.0f) d += res.mode == 1 ? -gn / expm1f(-res.wT[(size_t)v * ld + col]) : -gn;
+    const float* slots = reinterpret_cast<const float*>(above + kColSlots);
+    for (int c = 0; c < columns; ++c) {
+        const int col = col0 + c;
+        if (!res.wT) {
+            for (int r = threadIdx.x; r < res.n_last; r += kColThreads) res.g_cols[(size_t)col * res.n_last + r] = slots[r * CT + c];
+            continue;
         }
-        res.dleaf[(size_t)col * res.V + v] = d;
-        if (res.mode == 2 && res.dneg) res.dneg[(size_t)col * res.V + v] = dn;
+        for (int v = threadIdx.x; v < res.V; v += kColThreads) {
+            const int pr = res.pos_row[v], nr = res.neg_row[v];
+            float d = pr >= 0 ? slots[pr * CT + c] : 0.0f, dn = 0.0f;
+            if (nr >= 0) {
+                const float gn = slots[nr * CT + c];
+                if (res.mode == 2) dn = gn;
+                else if (gn != 0.0f) d += res.mode == 1 ? -gn / expm1f(-res.wT[(size_t)v * ld + col]) : -gn;
+            }
+            res.dleaf[(size_t)col * res.V + v] = d;
+            if (res.mode == 2 && res.dneg) res.dneg[(size_t)col * res.V + v] = dn;
+        }
     }
 }
 

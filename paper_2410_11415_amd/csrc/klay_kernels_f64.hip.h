@@ -28,6 +28,8 @@ struct PassArgs {
     int32_t n_total;
     int32_t B;
     int32_t ld;
+    int32_t lanes, per_wave;   // lanes per row, rows per wave
+    uint32_t inverse;          // see lane_group
 };
 
 template <int OP>
@@ -65,9 +67,10 @@ __device__ __forceinline__ double finish(double acc, double mx) {
 }
 
 template <int VEC>
-__device__ __forceinline__ void load_vec(double (&x)[VEC], const double* p) {
+__device__ __forceinline__ void load_cols(double (&x)[VEC], const double* p) {
     if (VEC == 2) {
-        const double2 t = *reinterpret_cast<const double2*>(p);
+        typedef double v2 __attribute__((ext_vector_type(2), aligned(8)));
+        const v2 t = *reinterpret_cast<const v2*>(p);
         x[0] = t.x;
         x[VEC - 1] = t.y;
     } else {
@@ -75,55 +78,91 @@ __device__ __forceinline__ void load_vec(double (&x)[VEC], const double* p) {
     }
 }
 
-// VEC batch columns per lane (2 needs an even ld): a wave spans 64 * VEC columns of one row
-template <int OP, int VEC>
+// As the fp32 generic kernel: a lane group of W lanes per row, VEC batch columns per lane (two from B = 2 on; the last
+// lane of an odd batch shares a column with its neighbour), offsets and entries in wide loads, four gathers in flight
+// and four more where a row of the wave is that long.
+//   ONE: a wave has one row (more than half of its lanes), so offsets and entries are the same for all lanes and come by
+// scalar loads.
+template <int OP, int VEC, bool ONE>
 __global__ __launch_bounds__(256) void pass_kernel(PassArgs a) {
-    constexpr int CH = 4;
-    const int lane = threadIdx.x & 63;
-    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    const int col = ((int)blockIdx.y * 64 + lane) * VEC;
-    if (col >= a.B) return;
-    const int64_t row64 = (int64_t)blockIdx.x * 4 + wave;
+    constexpr bool TWO = OP != OP_SOFTMAX_BWD;        // (two values per entry: four entries are enough registers)
+    constexpr int STEP = TWO ? 8 : 4;
+    int sub, colu;
+    if (!lane_group(a, VEC, sub, colu)) return;
+    const int col = colu <= a.B - VEC ? colu : a.B - VEC;
+    const int wave = ONE ? __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6)) : (int)(threadIdx.x >> 6);
+    const int64_t row64 = ((int64_t)xcd_block((int)blockIdx.x, (int)gridDim.x) * 4 + wave) * (ONE ? 1 : a.per_wave) + (ONE ? 0 : sub);
     if (row64 >= a.n_total) return;
     const int row = (int)row64;
-    const int beg = a.ptr[row], end = a.ptr[row + 1];
-    if (a.idx[beg] == kSkip) return;                  // split row: evaluated by segments + combine
+    const Offsets2 range = *reinterpret_cast<const Offsets2*>(a.ptr + row);
+    const int end = range.y;
+    int j = range.x;
+    Entries4 e0 = *reinterpret_cast<const Entries4*>(a.idx + j), e1 = *reinterpret_cast<const Entries4*>(a.idx + j + 4);
+    if (e0.x == kSkip) return;                        // split row: evaluated by segments + combine
     double nc[VEC], acc[VEC], mx[VEC];
 #pragma unroll
     for (int v = 0; v < VEC; ++v) { nc[v] = 0.0; acc[v] = identity<OP>(); mx[v] = -INFINITY; }
     if (OP == OP_SOFTMAX_BWD || OP == OP_PROD_BWD) {
         const int owner = row < a.n_main ? row : a.seg_owner[row - a.n_main];
-        load_vec<VEC>(nc, a.own + (size_t)owner * a.ld + col);
+        load_cols<VEC>(nc, a.own + (size_t)owner * a.ld + col);
     }
-    for (int j = beg; j < end; j += CH) {
-        const int n = end - j;
-        double x[CH][VEC], y[CH][VEC];
-        bool wt[CH];
+    for (;;) {
+        double x0[4][VEC], x1[4][VEC], y0[4][VEC], y1[4][VEC];
         // entries past the row's end are valid entries of later rows (or zero padding): the gathers
         // are issued unconditionally and their data ignored
+        auto gather = [&](Entries4 e, double (&x)[4][VEC], double (&y)[4][VEC]) {
 #pragma unroll
-        for (int i = 0; i < CH; ++i) {
-            const uint32_t raw = a.idx[j + i];
-            const uint32_t id = raw == kSkip ? 0u : (raw & kIdMask);
-            wt[i] = (raw & kWeighted) != 0;
-            load_vec<VEC>(x[i], a.src + (size_t)id * a.ld + col);
-            if (OP == OP_SOFTMAX_BWD) load_vec<VEC>(y[i], (wt[i] ? a.src2 : a.src) + (size_t)id * a.ld + col);
+            for (int i = 0; i < 4; ++i) {
+                const size_t off = (size_t)(e[i] == kSkip ? 0u : e[i] & kIdMask) * a.ld + col;
+                load_cols<VEC>(x[i], a.src + off);
+                if (OP == OP_SOFTMAX_BWD) load_cols<VEC>(y[i], ((e[i] & kWeighted) ? a.src2 : a.src) + off);
+            }
+        };
+        auto take = [&](Entries4 e, const double (&x)[4][VEC], const double (&y)[4][VEC], int live) {
+            if (live <= 0) return;
+#pragma unroll
+            for (int v = 0; v < VEC; ++v) {
+                if (OP == OP_LSE) {
+                    // one maximum and one exponential per entry, four independent ones at a time
+                    const double v0 = x[0][v], v1 = live > 1 ? x[1][v] : -INFINITY, v2 = live > 2 ? x[2][v] : -INFINITY,
+                                 v3 = live > 3 ? x[3][v] : -INFINITY;
+                    const double hi = fmax(fmax(fmax(v0, v1), fmax(v2, v3)), mx[v]);
+                    const double m = fmin(fmax(hi, -1.7976931348623157e308), 1.7976931348623157e308);      // finite: no inf - inf
+                    double t = (exp(v0 - m) + exp(v1 - m)) + (exp(v2 - m) + exp(v3 - m));
+                    if (mx[v] != -INFINITY) t = fma(acc[v], exp(mx[v] - m), t);
+                    acc[v] = t;
+                    mx[v] = m;
+                } else {
+#pragma unroll
+                    for (int i = 0; i < 4; ++i) {
+                        const double dead = OP == OP_PROD ? 1.0 : (OP == OP_MAX ? -INFINITY : 0.0);
+                        accumulate<OP>(acc[v], mx[v], i < live ? x[i][v] : dead,
+                                       OP == OP_SOFTMAX_BWD ? (i < live ? y[i][v] : -INFINITY) : 0.0, nc[v], (e[i] & kWeighted) != 0);
+                    }
+                }
+            }
+        };
+        const bool second = TWO && (ONE ? j + 4 < end : __any(j + 4 < end)), more = ONE ? j + STEP < end : __any(j + STEP < end);
+        Entries4 n0 = e0, n1 = e1;
+        gather(e0, x0, y0);
+        if (second) gather(e1, x1, y1);
+        if (more) {
+            const int at = j + STEP < end ? j + STEP : range.x;        // (a row that has ended reads its first entries again)
+            n0 = *reinterpret_cast<const Entries4*>(a.idx + at);
+            if (TWO) n1 = *reinterpret_cast<const Entries4*>(a.idx + at + 4);
         }
-#pragma unroll
-        for (int i = 0; i < CH; ++i) {
-            const bool live = i < n;
-            const double dead = OP == OP_PROD ? 1.0 : ((OP == OP_LSE || OP == OP_MAX) ? -INFINITY : 0.0);
-#pragma unroll
-            for (int v = 0; v < VEC; ++v)
-                accumulate<OP>(acc[v], mx[v], live ? x[i][v] : dead,
-                               OP == OP_SOFTMAX_BWD ? (live ? y[i][v] : -INFINITY) : 0.0, nc[v], wt[i]);
-        }
+        take(e0, x0, y0, end - j);
+        if (second) take(e1, x1, y1, end - j - 4);
+        j += STEP;
+        if (!more) break;
+        e0 = n0;
+        e1 = n1;
     }
     double* out;
     if (row < a.n_main) out = a.dst + (size_t)(a.out_row ? a.out_row[row] : row) * a.ld + col;
     else out = a.dst_seg + (size_t)(row - a.n_main) * a.ld + col;
-    if (VEC == 2) *reinterpret_cast<double2*>(out) = make_double2(finish<OP>(acc[0], mx[0]), finish<OP>(acc[VEC - 1], mx[VEC - 1]));
-    else *out = finish<OP>(acc[0], mx[0]);
+#pragma unroll
+    for (int v = 0; v < VEC; ++v) out[v] = OP == OP_LSE ? mx[v] + log(acc[v]) : finish<OP>(acc[v], mx[v]);
 }
 
 __device__ __forceinline__ double log1mexp(double x) {
