@@ -1633,7 +1633,7 @@ static klay_status forward_impl(klay_circuit* c, const float* leaf_weights, cons
                                leaf_weights, neg_weights, (int)B, V, c->d_pos_row, c->d_neg_row, wT, act, log_domain ? 1 : 0);
         } else if (V > 0) {
             dim3 grid((unsigned)((V + 31) / 32), (unsigned)((g.ld + 63) / 64));
-            hipLaunchKernelGGL(klay::leaf_fwd_kernel, grid, dim3(256), 0, s, leaf_weights, neg_weights, (int)B, V, g.ld,
+            hipLaunchKernelGGL(klay::leaf_fwd_kernel, grid, dim3(klay::kLeafThreads), 0, s, leaf_weights, neg_weights, (int)B, V, g.ld,
                                c->d_pos_row, c->d_neg_row, wT, act, log_domain ? 1 : 0);
         }
         if (c->true_row >= 0)
@@ -1912,7 +1912,7 @@ static klay_status backward_impl(klay_circuit* c, const float* dout, float* dlea
     prof.begin(KLAY_K_BWD_LEAF, 4.0 * B * (3.0 * V));
     if (V > 0) {
         dim3 grid((unsigned)((V + 31) / 32), (unsigned)((B + 63) / 64));
-        hipLaunchKernelGGL(klay::leaf_bwd_kernel, grid, dim3(256), 0, s, G, wT, c->d_pos_row, c->d_neg_row, B, V, g.ld,
+        hipLaunchKernelGGL(klay::leaf_bwd_kernel, grid, dim3(klay::kLeafThreads), 0, s, G, wT, c->d_pos_row, c->d_neg_row, B, V, g.ld,
                            lits ? 2 : (real ? 0 : 1), dleaf, dneg);
     }
     prof.end();
