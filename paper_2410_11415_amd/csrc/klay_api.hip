@@ -155,6 +155,7 @@ struct klay_circuit {
     struct RealLayer { const int32_t* ptr = nullptr; const int32_t* child = nullptr; DevPass by_child; };
     std::vector<RealLayer> real_layers;
     int32_t* d_real_index = nullptr;
+    const int32_t *d_real_ptr = nullptr, *d_real_child = nullptr;      // persistent kernel: offsets in it by depth under the top layer (null: too large)
     void* ws_own = nullptr;
     size_t ws_own_bytes = 0;
     void* ws_user = nullptr;
@@ -863,8 +864,9 @@ size_t enable_tail_lds() {
     for (int kb : {160, 128, 64}) {
         const int bytes = kb * 1024;
         hipError_t e = hipSuccess;
-        for (const void* kernel : {reinterpret_cast<const void*>(&klay::col_fwd_kernel<1>), reinterpret_cast<const void*>(&klay::col_bwd_kernel<1>),
-                                   reinterpret_cast<const void*>(&klay::col_fwd_kernel<2>), reinterpret_cast<const void*>(&klay::col_bwd_kernel<2>)})
+        for (const void* kernel : {reinterpret_cast<const void*>(&klay::col_fwd_kernel<1>), reinterpret_cast<const void*>(&klay::col_bwd_kernel<1, false>),
+                                   reinterpret_cast<const void*>(&klay::col_bwd_kernel<1, true>), reinterpret_cast<const void*>(&klay::col_bwd_kernel<2, true>),
+                                   reinterpret_cast<const void*>(&klay::col_fwd_kernel<2>), reinterpret_cast<const void*>(&klay::col_bwd_kernel<2, false>)})
             if (e == hipSuccess) e = hipFuncSetAttribute(kernel, hipFuncAttributeMaxDynamicSharedMemorySize, bytes);
         if (e == hipSuccess) return (size_t)bytes;
         (void)hipGetLastError();
@@ -922,7 +924,7 @@ void launch_tail_fwd(const klay_circuit* c, const TailChoice& t, const float* ac
 // Reverse sweep of the layers L .. first into layer `last` (first, or the layer below it); last_at: its entry in a
 // column of the value buffer (-1: layer 0, whose values the sweep does not need).
 void launch_tail_bwd(const klay_circuit* c, int last, int last_at, const float* tb, int T, const float* dout, const uint32_t* top_multi,
-                     const klay::ColBwdOut& res, int B, int ld, hipStream_t s) {
+                     const klay::ColBwdOut& res, const klay::ColReal* real, int B, int ld, hipStream_t s) {
     const klay::CircuitPlan& p = c->plan;
     const int L = p.num_layers;
     int64_t size[2];
@@ -940,9 +942,11 @@ void launch_tail_bwd(const klay_circuit* c, int last, int last_at, const float* 
         cache_at = (int)((a ? size[0] : 0) + size[a] - sum);
     }
     const int ct = tail_columns(B, size, c->tail_lds_bytes);
-    hipLaunchKernelGGL((ct == 2 ? klay::col_bwd_kernel<2> : klay::col_bwd_kernel<1>), dim3((unsigned)((B + ct - 1) / ct)), dim3(klay::kColThreads),
+    auto* kernel = real ? (ct == 2 ? klay::col_bwd_kernel<2, true> : klay::col_bwd_kernel<1, true>)
+                        : (ct == 2 ? klay::col_bwd_kernel<2, false> : klay::col_bwd_kernel<1, false>);
+    hipLaunchKernelGGL(kernel, dim3((unsigned)((B + ct - 1) / ct)), dim3(klay::kColThreads),
                        (size_t)(size[0] + size[1]) * ct * sizeof(float), s, c->d_tail + (L - p.tail_first), L - last, last_at, L & 1, c->d_blocks[1], c->n_blocks[1], c->d_tables, dout, c->d_top_ptr,
-                       c->d_top_root, p.num_roots, B, ld, (int)size[0], cached, cache_at, tb, T, top_multi, res);
+                       c->d_top_root, p.num_roots, B, ld, (int)size[0], cached, cache_at, tb, T, top_multi, res, real ? *real : klay::ColReal{});
 }
 
 // Values of layers first .. last (all run by the persistent forward kernel) from the column-major
@@ -1035,6 +1039,17 @@ klay_status ensure_real_bwd(klay_circuit* c) {
             o.pass = pack_pass(pk, o.plan);
         }
     }
+    size_t o_ptr = 0, o_child = 0;
+    const bool offsets = pk.buf.size() < (size_t)INT32_MAX - 4096 - 4 * (size_t)L;
+    if (offsets) {
+        std::vector<int32_t> ptr_at((size_t)L + 1, 0), child_at((size_t)L + 1, 0);
+        for (int l = L - ((L + 1) & 1); l >= 1; l -= 2) {
+            ptr_at[(size_t)(L - l)] = (int32_t)offs[(size_t)l].ptr;
+            child_at[(size_t)(L - l)] = (int32_t)offs[(size_t)l].child;
+        }
+        o_ptr = pk.add(ptr_at);
+        o_child = pk.add(child_at);
+    }
     const size_t bytes = pk.buf.size() * sizeof(int32_t);
     if (hipMalloc(reinterpret_cast<void**>(&c->d_real_index), bytes) != hipSuccess) {
         (void)hipGetLastError();
@@ -1045,6 +1060,10 @@ klay_status ensure_real_bwd(klay_circuit* c) {
         c->d_real_index = nullptr;
         return fail(KLAY_EHIP, std::string("klay_backward: upload of the real-semiring index arrays: ") +
                                    hipGetErrorString(e));
+    }
+    if (offsets) {
+        c->d_real_ptr = c->d_real_index + o_ptr;
+        c->d_real_child = c->d_real_index + o_child;
     }
     c->real_layers.resize((size_t)L + 1);
     for (int l = 0; l <= L; ++l) {
@@ -1763,6 +1782,43 @@ static klay_status backward_impl(klay_circuit* c, const float* dout, float* dlea
         c->last_fused = false;
     }
 
+    // The layers the forward pass ran in the persistent kernel, swept by its reverse counterpart; returns the layer whose
+    // adjoint rows it leaves (0: it wrote the leaf gradients).
+    auto tail_sweep = [&](const uint32_t* top_multi, const klay::ColReal* real_args) {
+        const int first = c->last_tail_first;
+        int last = first;
+        float* cols = gnext;                       // its last layer's adjoints, column-major
+        if (first == 1) last = 0;
+        else if (c->last_tail_staged) {
+            const int64_t nb = c->dl[(size_t)first - 1].n;
+            if (nb <= top_layer_rows(p)) last = first - 1;
+            else if (first - 1 == B0 && nb <= c->dl[(size_t)B0].row0) { last = first - 1; cols = G; }      // rows not written yet
+        }
+        klay::ColBwdOut res{};
+        res.n_last = (int32_t)c->dl[(size_t)last].n;
+        if (last == 0) {
+            res.wT = wT;
+            res.pos_row = c->d_pos_row;
+            res.neg_row = c->d_neg_row;
+            res.dleaf = dleaf;
+            res.dneg = dneg;
+            res.V = V;
+            res.mode = lits ? 2 : (real ? 0 : 1);
+        } else {
+            res.g_cols = cols;
+        }
+        prof.begin(KLAY_K_TAIL_BWD, tail_alg_bytes(c, first, B, true) + 4.0 * B * R, tail_min_bytes(c, first, B, true) + 4.0 * B * R);
+        launch_tail_bwd(c, last, last > 0 ? (int)p.col_off[(size_t)last] : -1, ws + lay.tb, c->last_tail_T, dout, top_multi, res,
+                        real_args, B, g.ld, s);
+        if (last > 0) {
+            dim3 tgrid((unsigned)((res.n_last + 31) / 32), (unsigned)((g.ld + 31) / 32));
+            hipLaunchKernelGGL(klay::tb_to_rows_kernel, tgrid, dim3(256), 0, s, cols, res.n_last, 0, res.n_last, B, g.ld,
+                               last == B0 ? grow(B0) : gcur);
+        }
+        prof.end();
+        return last;
+    };
+
     if (real) {
         // Real semiring: a sum layer passes adjoints through (plain by-child sums).  For a product layer
         // the adjoint rows of its nodes are first turned, in place, into P rows (adjoint times the product
@@ -1770,9 +1826,27 @@ static klay_status backward_impl(klay_circuit* c, const float* dout, float* dlea
         // child its share, using the child's own value.  Nothing is stored per edge.
         klay_status rs = ensure_real_bwd(c);
         if (rs != KLAY_OK) return rs;
-        // this sweep runs layer by layer on rows of the activation buffer: bring back the values the
-        // persistent forward kernel kept column-major
-        if (c->last_tail_first > 0) launch_tb_to_rows(c, c->last_tail_first, L, ws + lay.tb, act, B, g.ld, s);
+        // The layers of the persistent forward kernel go to its reverse counterpart (whose product rows arrive below as
+        // finished P rows); without it the sweep runs layer by layer on rows of the activation buffer.
+        const bool columns = c->last_tail_first > 0 && c->d_real_ptr;
+        int top = L;
+        if (columns) {
+            klay::ColReal args{};
+            args.index = c->d_real_index;
+            args.ptr = c->d_real_ptr;
+            args.child = c->d_real_child;
+            args.rows = values(c->last_tail_first - 1);
+            const int below = c->last_tail_first - 1;
+            args.low_rows = below <= B0 ? act : values(below - 1);
+            args.lowest = L - below;
+            top = tail_sweep(nullptr, &args);
+            if (top == 0) {
+                KLAY_HIP(hipGetLastError());
+                return KLAY_OK;
+            }
+        } else if (c->last_tail_first > 0) {
+            launch_tb_to_rows(c, c->last_tail_first, L, ws + lay.tb, act, B, g.ld, s);
+        }
         // `pre`: the rows arrive premultiplied by the pass that produced them (OP_SUM_P, OP_PROD_BWD_P), and the
         // kernel only repairs the columns whose node value is zero; the seed's rows are plain adjoints
         // flags[l]: raised by the pass that writes the rows of product layer l when it meets a node value of zero
@@ -1784,12 +1858,14 @@ static klay_status backward_impl(klay_circuit* c, const float* dout, float* dlea
             launch_prod_parent(c->real_layers[(size_t)l], (int)d.n, below, gl, pre ? values(l) : nullptr, flags + l, g, B, s);
             prof.end();
         };
-        prof.begin(KLAY_K_SEED, 4.0 * B * R + 4.0 * B * (double)c->dl[(size_t)L].n);
-        hipLaunchKernelGGL(klay::seed_kernel, dim3((unsigned)c->dl[(size_t)L].n), dim3(256), 0, s, dout, c->d_top_ptr,
-                           c->d_top_root, B, R, g.ld, L == B0 ? grow(L) : gcur, (const uint32_t*)nullptr,
-                           (const float*)nullptr);
-        prof.end();
-        for (int l = L; l > B0; --l) {
+        if (!columns) {
+            prof.begin(KLAY_K_SEED, 4.0 * B * R + 4.0 * B * (double)c->dl[(size_t)L].n);
+            hipLaunchKernelGGL(klay::seed_kernel, dim3((unsigned)c->dl[(size_t)L].n), dim3(256), 0, s, dout, c->d_top_ptr,
+                               c->d_top_root, B, R, g.ld, L == B0 ? grow(L) : gcur, (const uint32_t*)nullptr,
+                               (const float*)nullptr);
+            prof.end();
+        }
+        for (int l = top; l > B0; --l) {
             const DevLayer& d = c->dl[(size_t)l];
             float* dst = l - 1 == B0 ? grow(B0) : gnext;
             if ((l & 1) == 0) {
@@ -1797,7 +1873,7 @@ static klay_status backward_impl(klay_circuit* c, const float* dout, float* dlea
                 run_pass_set(klay::OP_SUM_P, klay::OP_SUM_P, d.bwd, gcur, nullptr, values(l - 1), dst, seg_rows, g, B, s,
                              prof, KLAY_K_BWD_SUM_MUL, flags + (l - 1));
             } else {
-                prod_parent(l, values(l - 1), gcur, l != L);
+                if (!(columns && l == top)) prod_parent(l, values(l - 1), gcur, l != L);
                 // the by-child plan of an AND layer carries no weighted bit: every entry is a P row
                 run_pass_set(klay::OP_PROD_BWD, klay::OP_SUM, d.bwd, gcur, nullptr, values(l - 1), dst, seg_rows, g, B, s,
                              prof, KLAY_K_BWD_PROD);
@@ -1805,7 +1881,7 @@ static klay_status backward_impl(klay_circuit* c, const float* dout, float* dlea
             std::swap(gcur, gnext);
         }
         // below B0 the entries of a by-child plan tell P rows (AND parents) from plain adjoint rows
-        if (B0 > 0 && (B0 & 1)) prod_parent(B0, act, grow(B0), B0 != L);
+        if (B0 > 0 && (B0 & 1) && !(columns && top == B0)) prod_parent(B0, act, grow(B0), B0 != L);
         for (int l = B0 - 1; l >= 0; --l) {
             const bool and_rows = (l & 1) != 0;
             run_pass_set(and_rows ? klay::OP_PROD_BWD_P : klay::OP_PROD_BWD, and_rows ? klay::OP_SUM_P : klay::OP_SUM,
@@ -1828,40 +1904,11 @@ static klay_status backward_impl(klay_circuit* c, const float* dout, float* dlea
         const int first = c->last_tail_first;
         // (its adjoints of OR nodes are in the one-gather form throughout, so it needs that form to be in use)
         if (one && first > 0) {
-            int last = first;
-            float* cols = gnext;                       // its last layer's adjoints, column-major
-            if (first == 1) last = 0;
-            else if (c->last_tail_staged) {
-                const int64_t nb = c->dl[(size_t)first - 1].n;
-                if (nb <= top_layer_rows(p)) last = first - 1;
-                else if (first - 1 == B0 && nb <= c->dl[(size_t)B0].row0) { last = first - 1; cols = G; }      // rows not written yet
-            }
-            klay::ColBwdOut res{};
-            res.n_last = (int32_t)c->dl[(size_t)last].n;
-            if (last == 0) {
-                res.wT = wT;
-                res.pos_row = c->d_pos_row;
-                res.neg_row = c->d_neg_row;
-                res.dleaf = dleaf;
-                res.dneg = dneg;
-                res.V = V;
-                res.mode = lits ? 2 : 1;
-            } else {
-                res.g_cols = cols;
-            }
-            prof.begin(KLAY_K_TAIL_BWD, tail_alg_bytes(c, first, B, true) + 4.0 * B * R, tail_min_bytes(c, first, B, true) + 4.0 * B * R);
-            launch_tail_bwd(c, last, last > 0 ? (int)p.col_off[(size_t)last] : -1, ws + lay.tb, c->last_tail_T, dout, encoded(L) ? c->dl[(size_t)L].multi : nullptr, res, B, g.ld, s);
-            if (last > 0) {
-                dim3 tgrid((unsigned)((res.n_last + 31) / 32), (unsigned)((g.ld + 31) / 32));
-                hipLaunchKernelGGL(klay::tb_to_rows_kernel, tgrid, dim3(256), 0, s, cols, res.n_last, 0, res.n_last, B, g.ld,
-                                   last == B0 ? grow(B0) : gcur);
-            }
-            prof.end();
-            if (last == 0) {
+            top = tail_sweep(encoded(L) ? c->dl[(size_t)L].multi : nullptr, nullptr);
+            if (top == 0) {
                 KLAY_HIP(hipGetLastError());
                 return KLAY_OK;
             }
-            top = last;
         } else {
             // the ordinary launches below read the values the persistent forward kernel kept column-major as rows
             // of the activation buffer

@@ -1282,115 +1282,152 @@ __global__ __launch_bounds__(kColThreads) void col_fwd_kernel(const ColLayer* __
     }
 }
 
-// One step of the reverse sweep.  OR: the step goes through an OR layer; its weighted edges (bit 15 of an entry) read the
+// One step of the reverse sweep.  Log semiring, through an OR layer (LogOr): the weighted edges (bit 15 of an entry) read the
 // parent's adjoint in the one-gather form (see encode_h) and need the value of the row they belong to.
-// Otherwise every edge passes the adjoint on, and a row that is an OR node with more than one child (bit 15 of its
-// entries) is stored in that form, again with the row's own value.
+// Through an AND layer (LogAnd) every edge passes the adjoint on, and a row that is an OR node with more than one child (bit 15
+// of its entries) is stored in that form, again with the row's own value.
+// Real semiring, through a sum layer (RealOr): plain sums, and the finished adjoint G of a product node leaves as the row P of
+// prod_parent_kernel (G times the product of the other children, whichever they are; ColRepair does the rows that
+// hold a zero).  Through a product layer (RealAnd): a child gets the sum of its parents' P over its own value, or, if it
+// is zero, the sum of the P of those parents whose one zero it is (see OP_PROD_BWD; one quotient per row here).
 // own: the values of the rows by slot; it may be the array the adjoints go to (a slot is read by the lanes of its row only).
-template <bool OR, class V>
-__device__ __forceinline__ V col_bwd_entry(const V* above, uint32_t e, V own) {
-    const V g = col_at(above, e & 0x7FFFu);
-    return OR && (e & 0x8000u) ? each([](float a, float b) { return decode_h(a, b); }, g, own) : g;
-}
-template <class V>
-__device__ __forceinline__ V col_encode(V g, V own) { return each([](float a, float b) { return encode_h(a, b); }, g, own); }
+enum ColMode { kLogAnd, kLogOr, kRealOr, kRealAnd };
 
-// the adjoints of the rows that two words (four entries) of a lane stand for; own: their values
-template <bool OR, int KIND, class V>
-__device__ __forceinline__ void col_bwd_rows(const V* above, uint32_t a, uint32_t b, const V* own, V* v) {
-    constexpr int N = 4 >> KIND;
-    const V o0 = own[0], o1 = own[KIND == 0 ? 1 : 0], o2 = own[KIND == 0 ? 2 : KIND == 1 ? 1 : 0], o3 = own[KIND == 0 ? 3 : KIND == 1 ? 1 : 0];
-    const V x0 = col_bwd_entry<OR>(above, a & 0xFFFFu, o0), x1 = col_bwd_entry<OR>(above, a >> 16, o1);
-    const V x2 = col_bwd_entry<OR>(above, b & 0xFFFFu, o2), x3 = col_bwd_entry<OR>(above, b >> 16, o3);
-    if (KIND == 0) { v[0] = x0; v[1] = x1; v[2] = x2; v[3] = x3; }
-    if (KIND == 1) { v[0] = x0 + x1; v[1] = x2 + x3; }
-    if (KIND == 2) v[0] = (x0 + x1) + (x2 + x3);
-    if (!OR) {
-        const uint32_t e[4] = {a, KIND == 0 ? a >> 16 : b, b, b >> 16};
-#pragma unroll
-        for (int i = 0; i < N; ++i) v[i] = (e[i] & 0x8000u) ? col_encode(v[i], own[i]) : v[i];
+// the adjoints of a row so far: their sum (RealAnd: of the parents without a zero child, and of those with exactly one)
+template <int MODE, class V> struct ColSum {
+    V a = V(0.0f), b = V(0.0f);
+    __device__ __forceinline__ void add(const V* above, uint32_t e, V own) {
+        const V g = col_at(above, e & 0x7FFFu);
+        if constexpr (MODE == kRealAnd) {
+            a += each([](float x) { return __float_as_uint(x) & 1u ? 0.0f : x; }, g);
+            b += each([](float x) { return __float_as_uint(x) & 1u ? __uint_as_float(__float_as_uint(x) & ~1u) : 0.0f; }, g);
+        } else if (MODE == kLogOr && (e & 0x8000u)) a += each([](float x, float y) { return decode_h(x, y); }, g, own);
+        else a += g;
     }
+    __device__ __forceinline__ void add2(const V* above, uint32_t w, V own) {
+        add(above, w & 0xFFFFu, own);
+        add(above, w >> 16, own);
+    }
+    __device__ __forceinline__ void add8(const V* above, Line w, V own) {
+        ColSum x, y, z;
+        add2(above, w.x, own); x.add2(above, w.y, own); y.add2(above, w.z, own); z.add2(above, w.w, own);
+        a += x.a + (y.a + z.a);
+        if (MODE == kRealAnd) b += x.b + (y.b + z.b);
+    }
+    __device__ __forceinline__ void meet(int k) {
+        a = col_fly<OP_SUM>(a, k);
+        if (MODE == kRealAnd) b = col_fly<OP_SUM>(b, k);
+    }
+};
+
+// Product rows that hold a zero: the product of a row's non-zero children and how many are zero, per column, from the
+// node values (rare, so straight from global memory).
+struct ColRepair {
+    const int32_t *ptr, *child;       // index vectors of the layer, by parent
+    const float* values;              // values of the layer below, first column; child c of column i at values[c * by_child + i * by_column]
+    size_t by_child, by_column;
+    __device__ __forceinline__ float row(float g, float own, int r, int column) const {
+        if (own != 0.0f) return premultiply(g, own);
+        float q = 1.0f;
+        int zeros = 0;
+        for (int j = ptr[r]; j < ptr[r + 1]; ++j) {
+            const float x = values[(size_t)child[j] * by_child + column * by_column];
+            if (x == 0.0f) ++zeros;
+            else q *= x;
+        }
+        const float p = zeros >= 2 ? 0.0f : g * q;
+        return __uint_as_float((__float_as_uint(p) & ~1u) | (zeros == 1 ? 1u : 0u));
+    }
+};
+
+// what a row leaves; r: its position in the layer
+template <int MODE, class V>
+__device__ __forceinline__ V col_finish(const ColSum<MODE, V>& s, V own, bool flagged, const ColRepair& repair, int r) {
+    if constexpr (MODE == kLogAnd) return flagged ? each([](float a, float b) { return encode_h(a, b); }, s.a, own) : s.a;
+    else if constexpr (MODE == kRealAnd) return each([](float a, float b, float n) { return n != 0.0f ? a / n : b; }, s.a, s.b, own);
+    else if constexpr (MODE == kRealOr) {
+        if constexpr (sizeof(V) == 4) return repair.row(s.a, own, r, 0);
+        else return V{repair.row(s.a.x, own.x, r, 0), repair.row(s.a.y, own.y, r, 1)};
+    } else return s.a;
 }
 
-// a quarter of a block (FULL: all its rows are there)
-template <bool OR, int KIND, bool FULL, class V>
-__device__ __forceinline__ void col_bwd_quarter(const V* above, uint32_t a, uint32_t b, const V* own_at, V* out, int rows) {
+// a quarter of a block (FULL: all its rows are there); r: position of the lane's first row
+template <int MODE, int KIND, bool FULL, class V>
+__device__ __forceinline__ void col_bwd_quarter(const V* above, uint32_t a, uint32_t b, const V* own_at, V* out, int rows,
+                                                const ColRepair& repair, int r) {
     constexpr int N = 4 >> KIND;
     const int lane = threadIdx.x & 63;
-    V v[N], own[N];
+    V own[N];
+    ColSum<MODE, V> v[N];
 #pragma unroll
     for (int i = 0; i < N; ++i) own[i] = own_at[FULL || lane + 64 * i < rows ? 64 * i : -lane];
-    col_bwd_rows<OR, KIND>(above, a, b, own, v);
+    const uint32_t e[4] = {a & 0xFFFFu, a >> 16, b & 0xFFFFu, b >> 16};
 #pragma unroll
-    for (int i = 0; i < N; ++i) {
-        if (FULL || rows >= 64 * (i + 1)) out[64 * i] = v[i];
-        else if (lane + 64 * i < rows) out[64 * i] = v[i];
-    }
+    for (int i = 0; i < 4; ++i) v[i >> KIND].add(above, e[i], own[i >> KIND]);
+#pragma unroll
+    for (int i = 0; i < N; ++i)
+        if (FULL || lane + 64 * i < rows) out[64 * i] = col_finish<MODE>(v[i], own[i], (e[i << KIND] & 0x8000u) != 0, repair, r + 64 * i);
 }
 
-// a run of kind 0, 1 or 2
-template <bool OR, int KIND, class V>
-__device__ __forceinline__ void col_bwd_short(ColWalk& walk, const V* above, const V* own_at, V* out, int rows) {
+// a run of kind 0, 1 or 2, from position r of the layer on
+template <int MODE, int KIND, class V>
+__device__ __forceinline__ void col_bwd_short(ColWalk& walk, const V* above, const V* own_at, V* out, int rows, const ColRepair& repair, int r) {
     constexpr int N = 4 >> KIND;
-    out += threadIdx.x & 63;
-    own_at += threadIdx.x & 63;
+    const int lane = threadIdx.x & 63;
+    out += lane;
+    own_at += lane;
+    r += lane;
     Line w0, w1;
-    for (; rows >= 256 * N; rows -= 256 * N, out += 256 * N, own_at += 256 * N) {
+    for (; rows >= 256 * N; rows -= 256 * N, out += 256 * N, own_at += 256 * N, r += 256 * N) {
         walk.block(w0, w1);
-        col_bwd_quarter<OR, KIND, true>(above, w0.x, w0.y, own_at, out, 0);
-        col_bwd_quarter<OR, KIND, true>(above, w0.z, w0.w, own_at + 64 * N, out + 64 * N, 0);
-        col_bwd_quarter<OR, KIND, true>(above, w1.x, w1.y, own_at + 128 * N, out + 128 * N, 0);
-        col_bwd_quarter<OR, KIND, true>(above, w1.z, w1.w, own_at + 192 * N, out + 192 * N, 0);
+        col_bwd_quarter<MODE, KIND, true>(above, w0.x, w0.y, own_at, out, 0, repair, r);
+        col_bwd_quarter<MODE, KIND, true>(above, w0.z, w0.w, own_at + 64 * N, out + 64 * N, 0, repair, r + 64 * N);
+        col_bwd_quarter<MODE, KIND, true>(above, w1.x, w1.y, own_at + 128 * N, out + 128 * N, 0, repair, r + 128 * N);
+        col_bwd_quarter<MODE, KIND, true>(above, w1.z, w1.w, own_at + 192 * N, out + 192 * N, 0, repair, r + 192 * N);
     }
     if (rows > 0) {
         walk.block(w0, w1);
-        col_bwd_quarter<OR, KIND, false>(above, w0.x, w0.y, own_at, out, rows);
-        if (rows > 64 * N) col_bwd_quarter<OR, KIND, false>(above, w0.z, w0.w, own_at + 64 * N, out + 64 * N, rows - 64 * N);
+        col_bwd_quarter<MODE, KIND, false>(above, w0.x, w0.y, own_at, out, rows, repair, r);
+        if (rows > 64 * N) col_bwd_quarter<MODE, KIND, false>(above, w0.z, w0.w, own_at + 64 * N, out + 64 * N, rows - 64 * N, repair, r + 64 * N);
         if (rows > 128 * N) {
-            col_bwd_quarter<OR, KIND, false>(above, w1.x, w1.y, own_at + 128 * N, out + 128 * N, rows - 128 * N);
-            if (rows > 192 * N) col_bwd_quarter<OR, KIND, false>(above, w1.z, w1.w, own_at + 192 * N, out + 192 * N, rows - 192 * N);
+            col_bwd_quarter<MODE, KIND, false>(above, w1.x, w1.y, own_at + 128 * N, out + 128 * N, rows - 128 * N, repair, r + 128 * N);
+            if (rows > 192 * N) col_bwd_quarter<MODE, KIND, false>(above, w1.z, w1.w, own_at + 192 * N, out + 192 * N, rows - 192 * N, repair, r + 192 * N);
         }
     }
 }
 
-template <bool OR, class V>
-__device__ __forceinline__ V col_bwd_long(const V* above, Line w, V own) {
-    return ((col_bwd_entry<OR>(above, w.x & 0xFFFFu, own) + col_bwd_entry<OR>(above, w.x >> 16, own)) +
-            (col_bwd_entry<OR>(above, w.y & 0xFFFFu, own) + col_bwd_entry<OR>(above, w.y >> 16, own))) +
-           ((col_bwd_entry<OR>(above, w.z & 0xFFFFu, own) + col_bwd_entry<OR>(above, w.z >> 16, own)) +
-            (col_bwd_entry<OR>(above, w.w & 0xFFFFu, own) + col_bwd_entry<OR>(above, w.w >> 16, own)));
-}
-
-template <bool OR, class V>
-__device__ __forceinline__ void col_bwd_layer(ColWalk& walk, const V* above, V* here, const V* owns) {
+template <int MODE, class V>
+__device__ __forceinline__ void col_bwd_layer(ColWalk& walk, const V* above, V* here, const V* owns, const ColRepair& repair) {
     const int lane = threadIdx.x & 63;
     Desc table = walk.table();
     ColRun run;
     for (int i = 0; run.read(walk, table, i);) {
         V* out = here + run.slot;
         const V* own_at = owns + run.slot;
-        if (run.kind == 0) col_bwd_short<OR, 0>(walk, above, own_at, out, run.rows);
-        else if (run.kind == 1) col_bwd_short<OR, 1>(walk, above, own_at, out, run.rows);
-        else if (run.kind == 2) col_bwd_short<OR, 2>(walk, above, own_at, out, run.rows);
+        int first = run.slot - kColSlots;
+        if (run.kind == 0) col_bwd_short<MODE, 0>(walk, above, own_at, out, run.rows, repair, first);
+        else if (run.kind == 1) col_bwd_short<MODE, 1>(walk, above, own_at, out, run.rows, repair, first);
+        else if (run.kind == 2) col_bwd_short<MODE, 2>(walk, above, own_at, out, run.rows, repair, first);
         else {
             const int r = lane >> run.k, per = 64 >> run.k;
             const bool writes = (lane & ((1 << run.k) - 1)) == 0;
-            for (int rows = run.rows; rows > 0; rows -= per, out += per, own_at += per) {
+            for (int rows = run.rows; rows > 0; rows -= per, out += per, own_at += per, first += per) {
                 const V own = own_at[r < rows ? r : 0];
                 Line w0, w1;
                 walk.block(w0, w1);
-                const uint32_t flag = w0.x & 0x8000u;
-                V acc = col_bwd_long<OR>(above, w0, own);
+                const bool flagged = (w0.x & 0x8000u) != 0;
+                ColSum<MODE, V> acc;
+                acc.add8(above, w0, own);
                 if (run.kind == 3) {
-                    acc += col_bwd_long<OR>(above, w1, own);
+                    acc.add8(above, w1, own);
                     for (int b = 1; b < run.blocks; ++b) {
                         walk.block(w0, w1);
-                        acc += col_bwd_long<OR>(above, w0, own) + col_bwd_long<OR>(above, w1, own);
+                        acc.add8(above, w0, own);
+                        acc.add8(above, w1, own);
                     }
                 }
-                acc = col_fly<OP_SUM>(acc, run.k);
-                if (!OR && flag) acc = col_encode(acc, own);
-                if (writes && r < rows) out[r] = acc;
+                acc.meet(run.k);
+                if (writes && r < rows) out[r] = col_finish<MODE>(acc, own, flagged, repair, first + r);
             }
         }
     }
@@ -1408,7 +1445,17 @@ struct ColBwdOut {
     int32_t V, mode;            // mode: as for leaf_bwd_kernel
 };
 
-// Reverse sweep over the same layers (log semiring): seeds the top layer's adjoints from dout and walks n_steps layers
+// Real semiring only: index vectors by parent of the product layers (offsets into `index` by depth under the top layer; see
+// ColRepair), and where the values below the column-major buffer are.
+struct ColReal {
+    const int32_t* index;
+    const int32_t *ptr, *child;
+    const float* rows;          // activation rows of the layer below the first one the forward kernel ran
+    const float* low_rows;      // activation rows that the index vectors of that layer name
+    int32_t lowest;             // its depth
+};
+
+// Reverse sweep over the same layers: seeds the top layer's adjoints from dout and walks n_steps layers
 // down.  LDS: the adjoints of the layer in hand and of the one below, size0 floats for the top layer and every second
 // one from there.  Node values come from the column-major buffer tb, once per row, and are far away (a read of them
 // takes about 2000 cycles, twice as long as a narrow layer): those of the first `cached` steps are loaded at once to
@@ -1420,14 +1467,14 @@ struct ColBwdOut {
 // (tb is not __restrict__: a load known to be invariant would be moved down past the barrier to its use.)
 template <int CT> constexpr int kColOwn = CT == 1 ? (int)((kTailRowsCap + 4 * kColThreads - 1) / (4 * kColThreads)) : 3;      // (two columns: where no layer is longer)
 
-template <int CT>
+template <int CT, bool REAL>
 __global__ __launch_bounds__(kColThreads) void col_bwd_kernel(const ColLayer* __restrict__ top, int n_steps, int last_at,
                                                               int top_is_and, const Line* __restrict__ blocks, int n_blocks,
                                                               const Desc* __restrict__ tables, const float* __restrict__ dout,
                                                               const int32_t* __restrict__ top_ptr, const int32_t* __restrict__ top_root,
                                                               int R, int B, int ld, int size0, int cached, int cache_at,
                                                               const float* tb, int T,
-                                                              const uint32_t* __restrict__ top_multi, ColBwdOut res) {
+                                                              const uint32_t* __restrict__ top_multi, ColBwdOut res, ColReal real) {
     using V = typename ColValue<CT>::T;
     extern __shared__ float smem[];
     V* above = reinterpret_cast<V*>(smem);
@@ -1453,6 +1500,27 @@ __global__ __launch_bounds__(kColThreads) void col_bwd_kernel(const ColLayer* __
     };
     if (threadIdx.x < 2) (threadIdx.x == 0 ? above : here)[kColPadAnd] = V(0.0f);       // what padding names: adjoint 0
     const int n_top = top->n, top_at = top->at;
+    // how to repair the rows of the layer `depth` below the top one (a product layer)
+    auto repair_of = [&](int depth) {
+        ColRepair r{};
+        if (REAL) {
+            r.ptr = real.index + real.ptr[depth];
+            r.child = real.index + real.child[depth];
+            const bool stored = depth + 1 < real.lowest;       // the layer below that one is in tb, otherwise in rows
+            r.values = stored ? tbc + top[-1 - depth].at : (depth < real.lowest ? real.rows : real.low_rows) + col0;
+            r.by_child = stored ? 1 : (size_t)ld;
+            r.by_column = stored ? (size_t)second : (columns > 1 ? 1 : 0);
+        }
+        return r;
+    };
+    // the leaves' own values (real semiring; they are not in tb)
+    auto leaf_values = [&](V* to) {
+        for (int i = threadIdx.x; i < res.n_last; i += kColThreads) {
+            const float* from = real.rows + (size_t)i * ld + col0;
+            if constexpr (CT == 1) to[kColSlots + i] = from[0];
+            else to[kColSlots + i] = V{from[0], from[columns > 1 ? 1 : 0]};
+        }
+    };
     int cache_low = 0;
     if (cached > 0) {
         // the cached layers follow one another in tb
@@ -1463,6 +1531,7 @@ __global__ __launch_bounds__(kColThreads) void col_bwd_kernel(const ColLayer* __
         int n, at;
         own_of(0, n, at);
         for (int i = threadIdx.x; i < n; i += kColThreads) here[kColSlots + i] = value_at(at + i);
+        if (REAL && n_steps == 1 && last_at < 0) leaf_values(here);
     }
     for (int i = threadIdx.x; i < n_top; i += kColThreads) {      // adjoint seed of the top layer
         V acc = V(0.0f);
@@ -1471,15 +1540,20 @@ __global__ __launch_bounds__(kColThreads) void col_bwd_kernel(const ColLayer* __
             if constexpr (CT == 1) acc += from[0];
             else acc += V{from[0], from[columns > 1 ? R : 0]};
         }
-        if (top_multi && ((top_multi[i >> 5] >> (i & 31)) & 1u)) acc = col_encode(acc, value_at(top_at + i));
+        if (REAL && top_is_and) {
+            ColSum<kRealOr, V> g;
+            g.a = acc;
+            acc = col_finish<kRealOr>(g, value_at(top_at + i), false, repair_of(0), i);
+        }
+        if (!REAL && top_multi && ((top_multi[i >> 5] >> (i & 31)) & 1u)) acc = each([](float a, float b) { return encode_h(a, b); }, acc, value_at(top_at + i));
         above[kColSlots + i] = acc;
     }
     int t = 0;
     for (; t + 1 < cached; ++t) {
         const V* owns = cache + (top[-1 - t].at - cache_low) - kColSlots;
         __syncthreads();
-        if (((t & 1) == 0) == (top_is_and != 0)) col_bwd_layer<false>(walk, above, here, owns);
-        else col_bwd_layer<true>(walk, above, here, owns);
+        if (((t & 1) == 0) == (top_is_and != 0)) col_bwd_layer<REAL ? kRealAnd : kLogAnd>(walk, above, here, owns, ColRepair{});
+        else col_bwd_layer<REAL ? kRealOr : kLogOr>(walk, above, here, owns, repair_of(t + 1));
         V* tmp = above; above = here; here = tmp;
     }
     for (; t < n_steps; ++t) {
@@ -1498,8 +1572,8 @@ __global__ __launch_bounds__(kColThreads) void col_bwd_kernel(const ColLayer* __
         }
         const V* owns = t < cached ? cache + (top[-1 - t].at - cache_low) - kColSlots : here;
         __syncthreads();
-        if (((t & 1) == 0) == (top_is_and != 0)) col_bwd_layer<false>(walk, above, here, owns);
-        else col_bwd_layer<true>(walk, above, here, owns);
+        if (((t & 1) == 0) == (top_is_and != 0)) col_bwd_layer<REAL ? kRealAnd : kLogAnd>(walk, above, here, owns, ColRepair{});
+        else col_bwd_layer<REAL ? kRealOr : kLogOr>(walk, above, here, owns, repair_of(t + 1));
         __syncthreads();
         // the adjoints above are done with: their array takes the next step's own values
 #pragma unroll
@@ -1519,6 +1593,7 @@ __global__ __launch_bounds__(kColThreads) void col_bwd_kernel(const ColLayer* __
                         for (int c = 0; c < CT; ++c) slot[j * CT + c] = own[i][c][j];
             }
         }
+        if (REAL && t + 2 == n_steps && last_at < 0) leaf_values(above);
         V* tmp = above; above = here; here = tmp;
     }
     __syncthreads();

@@ -67,3 +67,26 @@ def test_layers_around_chunk_and_block_sizes(widths, fan, batch):
     g = [k.backward(torch.from_numpy(dout).cuda()) for _ in range(2)]
     assert torch.equal(g[0], g[1]) and torch.equal(out, k.forward_static(w, LOG))
     k.close()
+
+
+@pytest.mark.parametrize("widths,batch,cap", [((40, 30, 20, 10), 3, 0), ((300, 500, 200, 90, 40), 5, 0), ((700, 400, 260, 130, 60, 20), 4, 200),
+                                              ((700, 400, 260, 130, 60, 20), 4, 300), ((90, 70, 33), 259, 0), ((2000, 900, 500, 30), 1, 1000)])
+def test_real_gradients_with_zeros_everywhere(widths, batch, cap):
+    """products with no, one and several zero children in every layer the persistent reverse kernel takes, tops of both
+    kinds, boundaries at odd and even layers"""
+    import paper_2410_11415_amd as klay
+    rng = np.random.default_rng(sum(widths))
+    c = stack(rng, 10, widths, FANS["two"], 0.3)
+    k = klay.Circuit(*c.arrays(), device=0, tail_rows_cap=cap)
+    p = rng.uniform(0.2, 0.9, size=(batch, 10))
+    p[rng.random(p.shape) < 0.3] = 0.0
+    p[rng.random(p.shape) < 0.2] = 1.0
+    w = as_inputs(p, False)
+    dout = rng.normal(size=(batch, c.roots.shape[0])).astype(np.float32)
+    for _ in range(2):
+        out, grad = gpu_eval(k, w, REAL, dout)
+    ref, rgrad = oracle_eval(c, w, REAL, dout, or_levels=k.num_layers // 2)
+    assert (ref == 0).any() or (rgrad == 0).any()
+    assert_real_close(out, ref, "values")
+    assert_grad_close(grad, rgrad, "gradients", real=True)
+    k.close()
