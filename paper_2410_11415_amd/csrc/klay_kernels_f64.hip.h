@@ -1,8 +1,8 @@
 // Double-precision evaluation of the same launch plans (accuracy build): one generic gather-reduce
-// kernel, a wave per output row and one or two batch columns per lane, plus the small leaf / root / seed
+// kernel, one or two batch columns per lane and as many rows per wave as that leaves room for, plus the small leaf / root / seed
 // kernels.  Same index arrays, same order of layers and the same split-row scheme as the fp32
 // kernels (paper Section 4, Alg. 1 / Appendix C, Alg. 4); exp and log are the full-precision
-// library routines.  Not tuned: the rows are twice as long and OR layers pay a double-precision
+// library routines.  The rows are twice as long as in fp32 and OR layers pay a double-precision
 // exponential per edge.
 #pragma once
 
