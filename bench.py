@@ -70,7 +70,8 @@ def kernel_symbol(cls, B, edges=False, fused_op=10):
     w_small = 1
     while w_small < B:
         w_small *= 2
-    fixed = {"tail_fwd": "klay::col_fwd_kernel", "tail_bwd": "klay::col_bwd_kernel",
+    fixed = {"tail_fwd": "klay::col_fwd_kernel<%d>" % (1 if B <= 256 else 2),
+             "tail_bwd": "klay::col_bwd_kernel<%d, %s>" % (1 if B <= 256 else 2, "true" if fused_op == 12 else "false"),
              "leaf": "klay::leaf_fwd_kernel" if B > 32 else "klay::leaf_fwd_small_kernel", "bwd_leaf": "klay::leaf_bwd_kernel", "root": "klay::root_out_kernel",
              "seed": "klay::seed_kernel", "split": "klay::pass_kernel<*> (segments of split rows)",
              "combine": "klay::combine_kernel<*>" if B > 32 else "klay::combine_small_kernel<*>",
