@@ -928,11 +928,11 @@ struct ColRun {
             b = (uint32_t)__builtin_amdgcn_readlane((int)table.y, 0);
         }
         ++i;
-        slot = (int)a;
+        slot = (int)(a & 0x7FFFu);
         rows = (int)(b & 0xFFFFu);
         k = (int)((b >> 16) & 15u);
         kind = (int)((b >> 20) & 15u);
-        blocks = (int)(b >> 24);
+        blocks = (int)(a >> 15);
         return true;
     }
 };

@@ -261,7 +261,7 @@ void make_cols(int64_t n, const int32_t* ptr, const int32_t* idx, const uint32_t
             }
             for (int k = 0; k <= 6; ++k) {
                 const int32_t e = std::max(1, (longest[k][(size_t)r] + (1 << k) - 1) >> k), blocks = (e + 15) / 16;
-                if (blocks > 255 && k < 6) continue;
+                if (blocks > kColBlocksMax) continue;
                 consider(e <= 8 ? 4 : 3, k, blocks, cost.unit + (e + 7) / 8 * cost.line + k * cost.fly);
             }
             if (total == INT64_MAX) { b = least; total = b.cost + best[(size_t)(r + b.rows)]; }
@@ -312,7 +312,7 @@ void make_cols(int64_t n, const int32_t* ptr, const int32_t* idx, const uint32_t
             int64_t rows = u.rows;
             while (stop < end && joins(u, pieces[stop])) rows += pieces[stop++].rows;
             if (in_table == kDescTable - 1) { describe(1u, 0u); in_table = 0; }
-            describe((uint32_t)(kColSlots + u.row), (uint32_t)rows | (uint32_t)u.k << 16 | (uint32_t)u.kind << 20 | (uint32_t)u.blocks << 24);
+            describe((uint32_t)(kColSlots + u.row) | (uint32_t)u.blocks << 15, (uint32_t)rows | (uint32_t)u.k << 16 | (uint32_t)u.kind << 20);
             const size_t at = out.blocks.size();
             const int64_t per_block = u.kind < 3 ? 1024 >> u.kind : 64 >> u.k;
             out.blocks.resize(at + (size_t)((rows + per_block - 1) / per_block * u.blocks) * kBlockWords, pads);
@@ -932,7 +932,7 @@ int layerize(int32_t V, int64_t N, const uint8_t* node_type, const int32_t* node
             int64_t fan_in = 0, fan_out = 0;
             for (int64_t i = 0; i < lay.n; ++i) fan_in = std::max<int64_t>(fan_in, lay.row_ptr[(size_t)i + 1] - lay.row_ptr[(size_t)i]);
             for (int64_t i = 0; i < nc; ++i) fan_out = std::max<int64_t>(fan_out, cptr[(size_t)i + 1] - cptr[(size_t)i]);
-            if (fan_in <= kTailFanCap) {
+            if (fan_in <= kTailFanCap && fan_out <= kColRowEntries) {
                 make_slab(lay.n, nc, lay.row_ptr.data(), lay.child.data(), nullptr, lay.slab_fwd);
                 lay.tail_fwd_ok = true;
                 const bool is_and = (l & 1) != 0;

@@ -51,12 +51,12 @@ struct SlabPlan {
 // per row (k chosen per run): lane j works for row j >> k and holds that row's entries (j mod 2^k) + i * 2^k, and the
 // lanes of a row meet in a butterfly at the end.  A unit of kind 4 has at most 8 entries per lane (the first line of
 // one block), one of kind 3 as many blocks as its run says.  A row of many entries
-// therefore spreads over the wave instead of making 63 lanes wait for one, and there is no limit on the entries of a row.
+// therefore spreads over the wave instead of making 63 lanes wait for one; a row may have up to kColRowEntries entries.
 //   An entry is an LDS slot (kColSlots + position of the source: the first slots of a value array hold the identities
 // that padding names, kColPadAnd for AND layers and the reverse sweep, kColPadOr for OR layers).  Bit 15 is a flag of the
 // reverse sweep: weighted edge, or (steps through an AND layer, on every entry of the row) the row's adjoint is
 // stored in the one-gather form.  Slots stay below 2^15.
-//   Descriptor of a run, 2 words: [0] LDS slot of its first row, [1] rows | k << 16 | kind << 20 | blocks per unit << 24.
+//   Descriptor of a run, 2 words: [0] LDS slot of its first row | blocks per unit << 15, [1] rows | k << 16 | kind << 20.
 // The descriptors of a wave in a layer come in tables of 64: up to 63 runs and one of no rows (word 0 = 1: another
 // table follows, 0: the end).  The rows of a layer are cut into chunks and units by a shortest-path search over their
 // cost, and every wave gets a contiguous share of about the same cost, so that the waves reach the layer's barrier together.
@@ -64,6 +64,8 @@ struct SlabPlan {
 constexpr int kColSlots = 4, kColPadAnd = 0, kColPadOr = 1;
 constexpr int kColFwdWaves = kSlabWaves - 1, kColBwdWaves = kSlabWaves;
 constexpr int kBlockWords = 512, kLineWords = 256, kDescWords = 2, kDescTable = 64;
+constexpr int64_t kColBlocksMax = (1 << 17) - 1;             // blocks of a unit: what the descriptor holds
+constexpr int64_t kColRowEntries = kColBlocksMax * 16 * 64;  // a row that takes a whole wave
 struct ColPlan {
     int32_t block_at[kSlabWaves + 1] = {}, table_at[kSlabWaves + 1] = {};   // first block / table of each wave
     std::vector<uint32_t> blocks, tables;

@@ -1,5 +1,5 @@
-// Host check of the persistent kernels' streams (ColPlan), with no GPU: random index vectors with long and short
-// rows are cut into runs, blocks and tables, and the walk of the kernels over them (16 waves, blocks
+// Host check of the persistent kernels' streams (ColPlan), with no GPU: random index vectors with long (up to 300000
+// entries, more than 255 blocks of a unit) and short rows are cut into runs, blocks and tables, and the walk of the kernels over them (16 waves, blocks
 // taken in order, 2^k lanes per row, padding by name) is executed here on integer "values".
 #include <cstdio>
 #include <cstdlib>
@@ -15,9 +15,10 @@ static u64 mix(u64 x) { x += 0x9E3779B97F4A7C15ull; x = (x ^ (x >> 30)) * 0xBF58
 int main() {
     std::mt19937_64 rng(7);
     const int64_t sizes[] = {1, 2, 3, 63, 64, 65, 127, 128, 129, 1000, 1024, 1025, 5000, 20000};
+    int most_blocks = 0;
     long wide = 0, runs = 0, tables = 0, kinds[5] = {0, 0, 0, 0, 0};
     for (int64_t n : sizes)
-        for (int shape = 0; shape < 7; ++shape) {
+        for (int shape = 0; shape < (n == 3 || n == 1000 ? 8 : 7); ++shape) {
             const int64_t n_src = 1 + (int64_t)(rng() % 20000);
             std::vector<int32_t> ptr{0}, idx;
             std::vector<uint32_t> flags;
@@ -30,6 +31,7 @@ int main() {
                 case 3: k = r % 97 == 0 ? 700 + (int64_t)(rng() % 3000) : 1 + (int64_t)(rng() % 3); break;
                 case 6: k = (r / 64) % 2 ? 1 + (int64_t)(rng() % 2) : 5 + (int64_t)((r / 128) % 5) * 9; break;
                 case 4: k = r == n / 2 ? 20000 : 2; break;
+                case 7: k = r == n / 2 ? 300000 : 1 + (int64_t)(rng() % 3); break;
                 default: k = 1 + (int64_t)(2.0 / (1e-3 + (double)(rng() % 1000) / 1000.0)); break;
                 }
                 for (int64_t j = 0; j < k; ++j) { idx.push_back((int32_t)(rng() % (u64)n_src)); flags.push_back(rng() % 3 == 0 ? klay::kWeightedEdge : 0u); }
@@ -61,8 +63,9 @@ int main() {
                             continue;
                         }
                         CHECK(++i < klay::kDescTable, "a table without an end");
-                        const int64_t first = (int64_t)ds[0] - klay::kColSlots;
-                        const int k = (ds[1] >> 16) & 15, kind = (ds[1] >> 20) & 15, blocks = (int)(ds[1] >> 24);
+                        const int64_t first = (int64_t)(ds[0] & 0x7FFFu) - klay::kColSlots;
+                        const int k = (ds[1] >> 16) & 15, kind = (ds[1] >> 20) & 15, blocks = (int)(ds[0] >> 15);
+                        if (blocks > most_blocks) most_blocks = blocks;
                         CHECK(w < waves, "a run for a wave that does not take part");
                         CHECK(blocks >= 1 && k <= 6 && kind <= 4 && first >= 0 && first + rows <= n, "shape");
                         CHECK(kind == 3 || blocks == 1, "blocks of a unit");
@@ -108,6 +111,7 @@ int main() {
                 for (int64_t r = 0; r < n; ++r) CHECK(written[(size_t)r] == 1, "row %lld written %d times", (long long)r, written[(size_t)r]);
             }
         }
+    CHECK(most_blocks > 255, "units of many blocks");
     CHECK(wide > 0 && tables > 0 && kinds[0] > 0 && kinds[1] > 0 && kinds[2] > 0 && kinds[3] > 0 && kinds[4] > 0, "kinds of runs seen");
     std::printf("ok: %ld runs (%ld with several lanes per row, %ld tables more)\n", runs, wide, tables);
     return 0;

@@ -90,3 +90,40 @@ def test_real_gradients_with_zeros_everywhere(widths, batch, cap):
     assert_real_close(out, ref, "values")
     assert_grad_close(grad, rgrad, "gradients", real=True)
     k.close()
+
+
+def test_literal_with_hundreds_of_thousands_of_parents():
+    """a leaf row of 287300 entries in the reverse kernel (281 blocks of one unit): every AND gate counts 20 leaf nodes of one
+    literal next to two literals of its own"""
+    import paper_2410_11415_amd as klay
+    n = 170
+    types, lits, kids = [0] * (n + 19), [v + 1 for v in range(n)] + [1] * 19, [[] for _ in range(n + 19)]
+    ones = [0] + list(range(n, n + 19))
+    gates = [(i, j) for i in range(1, n) for j in range(1, i)]
+    gates += [(0, j) for j in range(1, n)]
+    for i, j in gates:
+        types.append(1)
+        lits.append(0)
+        kids.append(sorted(set(ones + [i, j])))
+    first = n + 19
+    roots = []
+    for a in range(0, len(gates), 64):
+        roots.append(len(types))
+        types.append(2)
+        lits.append(0)
+        kids.append(list(range(first + a, first + min(a + 64, len(gates)))))
+    ptr = np.concatenate([[0], np.cumsum([len(k) for k in kids])]).astype(np.int64)
+    c = Circuit(n, np.array(types, np.uint8), np.array(lits, np.int32), ptr, np.array([x for k in kids for x in k], np.int32), np.array(roots, np.int32))
+    k = klay.Circuit(*c.arrays(), device=0)
+    info = k.info()
+    assert info["tail_first_layer"] == 1 and info["max_fan_out"] > 255 * 1024
+    rng = np.random.default_rng(5)
+    p = rng.uniform(0.8, 0.99, size=(2, n))
+    dout = rng.uniform(0.5, 1.5, size=(2, len(roots))).astype(np.float32)
+    for semiring in (LOG, REAL):
+        w = as_inputs(p, semiring != REAL)
+        out, grad = gpu_eval(k, w, semiring, dout)
+        ref, rgrad = oracle_eval(c, w, semiring, dout, or_levels=1)
+        (assert_real_close if semiring == REAL else assert_log_close)(out, ref, "values")
+        assert_grad_close(grad, rgrad, "gradients", real=semiring == REAL)
+    k.close()
