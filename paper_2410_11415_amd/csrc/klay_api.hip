@@ -929,23 +929,32 @@ void launch_tail_bwd(const klay_circuit* c, int last, int last_at, const float* 
     const int L = p.num_layers;
     int64_t size[2];
     tail_lds(p, last, L, size);
-    // The own values of the first steps (narrow layers) are loaded at once, into LDS that only the wider layers
-    // further down need: as many steps as fit behind the rows of one of the two arrays.
+    const int ct = tail_columns(B, size, c->tail_lds_bytes);
+    // The own values of the first steps are loaded at once: as many steps as fit behind the rows of one of the two arrays,
+    // into LDS that only the wider layers further down need, or behind both arrays, up to all that a compute unit has (a
+    // workgroup takes one anyway).
+    const int64_t all = (int64_t)(c->tail_lds_bytes / sizeof(float)) / ct;
     int cached = 0, cache_at = 0;
-    int64_t rows[2] = {0, 0}, sum = 0;
+    int64_t rows[2] = {0, 0}, sum = 0, words = size[0] + size[1];
     for (int l = L; l > last + 1; --l) {                  // step from layer l into layer l - 1
         for (int m : {l, l - 1}) rows[(L - m) & 1] = std::max(rows[(L - m) & 1], p.layers[(size_t)m].n + klay::kColSlots);
         sum += p.layers[(size_t)l - 1].n;
-        const int a = size[0] - rows[0] > size[1] - rows[1] ? 0 : 1;
-        if (sum > size[a] - rows[a]) break;
+        const int64_t at = (size[0] + rows[1] + 3) / 4 * 4;
+        if (sum <= size[0] - (rows[0] + 3) / 4 * 4) {
+            cache_at = (int)((rows[0] + 3) / 4 * 4);
+            words = size[0] + size[1];
+        } else if (sum <= all - at) {
+            cache_at = (int)at;
+            words = std::max(size[0] + size[1], at + sum);
+        } else {
+            break;
+        }
         cached = L - l + 1;
-        cache_at = (int)((a ? size[0] : 0) + size[a] - sum);
     }
-    const int ct = tail_columns(B, size, c->tail_lds_bytes);
     auto* kernel = real ? (ct == 2 ? klay::col_bwd_kernel<2, true> : klay::col_bwd_kernel<1, true>)
                         : (ct == 2 ? klay::col_bwd_kernel<2, false> : klay::col_bwd_kernel<1, false>);
     hipLaunchKernelGGL(kernel, dim3((unsigned)((B + ct - 1) / ct)), dim3(klay::kColThreads),
-                       (size_t)(size[0] + size[1]) * ct * sizeof(float), s, c->d_tail + (L - p.tail_first), L - last, last_at, L & 1, c->d_blocks[1], c->n_blocks[1], c->d_tables, dout, c->d_top_ptr,
+                       (size_t)words * ct * sizeof(float), s, c->d_tail + (L - p.tail_first), L - last, last_at, L & 1, c->d_blocks[1], c->n_blocks[1], c->d_tables, dout, c->d_top_ptr,
                        c->d_top_root, p.num_roots, B, ld, (int)size[0], cached, cache_at, tb, T, top_multi, res, real ? *real : klay::ColReal{});
 }
 

@@ -1459,13 +1459,45 @@ struct ColReal {
 // down.  LDS: the adjoints of the layer in hand and of the one below, size0 floats for the top layer and every second
 // one from there.  Node values come from the column-major buffer tb, once per row, and are far away (a read of them
 // takes about 2000 cycles, twice as long as a narrow layer): those of the first `cached` steps are loaded at once to
-// cache_at, into LDS that only later steps use; from there on those of the next step's rows are
+// cache_at, into LDS that only later steps use or that lies behind both arrays (launch_tail_bwd; 67000 nodes in 48 layers of
+// about 1400, log training step at B = 4: 143 -> 116 us by what lies behind, 29000 nodes in 30 layers 91 -> 68); from there on those of the next step's rows are
 // fetched into registers during a step (kColOwn times four per thread: any layer that fits) and put into the slots of the
 // array that the step frees.  (Four at a time: a load instruction of one float a lane takes the memory pipe as long.)  last_at: entry of the last layer in tb (-1: its values are not needed).  The adjoints
 // of OR nodes with more than one child are kept in the one-gather form throughout, also on the way out; top_multi
 // (or null) flags such nodes of the top layer for the seed.
 // (tb is not __restrict__: a load known to be invariant would be moved down past the barrier to its use.)
 template <int CT> constexpr int kColOwn = CT == 1 ? (int)((kTailRowsCap + 4 * kColThreads - 1) / (4 * kColThreads)) : 3;      // (two columns: where no layer is longer)
+
+// n node values of the CT columns of a workgroup (the second `second` floats after the first) into LDS, 16-byte aligned,
+// sixteen values of a column per thread in flight
+template <int CT, class V>
+__device__ __forceinline__ void col_load(V* to, const float* from, int second, int n) {
+    typedef float f4u __attribute__((ext_vector_type(4), aligned(4)));
+    const int whole = n / 4 * 4;
+    for (int i0 = 4 * (int)threadIdx.x; i0 < whole; i0 += 16 * kColThreads) {
+        f4u v[4][CT];
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+            const int i = i0 + 4 * j * kColThreads < whole ? i0 + 4 * j * kColThreads : i0;
+#pragma unroll
+            for (int c = 0; c < CT; ++c) v[j][c] = *reinterpret_cast<const f4u*>(from + (c ? second : 0) + i);
+        }
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+            const int i = i0 + 4 * j * kColThreads < whole ? i0 + 4 * j * kColThreads : i0;
+            float* slot = reinterpret_cast<float*>(to + i);
+            if constexpr (CT == 1) {
+                *reinterpret_cast<float4*>(slot) = make_float4(v[j][0].x, v[j][0].y, v[j][0].z, v[j][0].w);
+            } else {
+                *reinterpret_cast<float4*>(slot) = make_float4(v[j][0].x, v[j][CT - 1].x, v[j][0].y, v[j][CT - 1].y);
+                *reinterpret_cast<float4*>(slot + 4) = make_float4(v[j][0].z, v[j][CT - 1].z, v[j][0].w, v[j][CT - 1].w);
+            }
+        }
+    }
+    const int rest = whole + (int)threadIdx.x;
+    if (rest < n)
+        for (int c = 0; c < CT; ++c) reinterpret_cast<float*>(to + rest)[c] = from[(c ? second : 0) + rest];
+}
 
 template <int CT, bool REAL>
 __global__ __launch_bounds__(kColThreads) void col_bwd_kernel(const ColLayer* __restrict__ top, int n_steps, int last_at,
@@ -1525,8 +1557,7 @@ __global__ __launch_bounds__(kColThreads) void col_bwd_kernel(const ColLayer* __
     if (cached > 0) {
         // the cached layers follow one another in tb
         cache_low = top[-cached].at;
-        const int n = top_at - cache_low;
-        for (int i = threadIdx.x; i < n; i += kColThreads) cache[i] = value_at(cache_low + i);
+        col_load<CT>(cache, tbc + cache_low, second, top_at - cache_low);
     } else {
         int n, at;
         own_of(0, n, at);

@@ -127,3 +127,47 @@ def test_literal_with_hundreds_of_thousands_of_parents():
         (assert_real_close if semiring == REAL else assert_log_close)(out, ref, "values")
         assert_grad_close(grad, rgrad, "gradients", real=semiring == REAL)
     k.close()
+
+
+def covered_stack(rng, num_vars, widths, and_extra=0.02, or_fan=2):
+    """Alternating AND / OR layers of exactly the given widths (build with no_merge): gate i of n has the nodes i, i + n, ..
+    of the layer below, so every node has a parent; an AND gate has one more with probability `and_extra`, an OR gate
+    or_fan - 1 more."""
+    types, lits, kids = [0] * (2 * num_vars), [s * (v + 1) for v in range(num_vars) for s in (1, -1)], [[] for _ in range(2 * num_vars)]
+    first, m = 0, 2 * num_vars
+    for depth, n in enumerate(widths):
+        at = len(types)
+        for i in range(n):
+            more = int(rng.random() < and_extra) if depth % 2 == 0 else or_fan - 1
+            c = set(range(i % m, m, n)) | {int(x) for x in rng.integers(m, size=more)}
+            types.append(1 if depth % 2 == 0 else 2)
+            lits.append(0)
+            kids.append(sorted(first + x for x in c))
+        first, m = at, n
+    ptr = np.concatenate([[0], np.cumsum([len(k) for k in kids])]).astype(np.int64)
+    idx = np.array([x for k in kids for x in k], dtype=np.int32)
+    return Circuit(num_vars, np.array(types, np.uint8), np.array(lits, np.int32), ptr, idx, np.arange(first, first + m, dtype=np.int32))
+
+
+@pytest.mark.parametrize("widths,batch", [
+    ([900] * 24, 3),                                   # own values of every step behind the two arrays
+    ([900] * 24, 258),                                 # the same with two columns per workgroup
+    ([2500] * 20 + [1300, 700], 2),                    # of some steps only: the rest a step ahead
+    ([5000, 5000] + [600] * 10, 2),                    # in the part of an array that only the wide layers need
+    ([6000, 6000] + [2999] * 7 + [60, 60, 20], 259),
+])
+def test_own_values_wherever_the_reverse_kernel_keeps_them(widths, batch):
+    import paper_2410_11415_amd as klay
+    rng = np.random.default_rng(sum(widths) + batch)
+    c = covered_stack(rng, 300, widths)
+    k = klay.Circuit(*c.arrays(), device=0, no_merge=True)
+    assert k.info()["num_nodes"] == 600 + sum(widths) and k.info()["tail_first_layer"] == 1
+    p = rng.uniform(0.3, 0.7, size=(batch, 300))
+    dout = rng.normal(size=(batch, widths[-1])).astype(np.float32)
+    for semiring in (LOG, REAL):
+        w = as_inputs(p, semiring != REAL)
+        out, grad = gpu_eval(k, w, semiring, dout)
+        ref, rgrad = oracle_eval(c, w, semiring, dout, or_levels=len(widths) // 2)
+        (assert_real_close if semiring == REAL else assert_log_close)(out, ref, "values")
+        assert_grad_close(grad, rgrad, "gradients", real=semiring == REAL)
+    k.close()
