@@ -173,7 +173,8 @@ klay_status klay_build_ex(int32_t num_vars, int64_t num_nodes, const uint8_t* no
 /*
  * klay_forward -- evaluate all layers (Alg. 1 for KLAY_REAL, Alg. 4 for KLAY_LOG).
  *   leaf_weights  device [B, V] row-major fp32: p_v (REAL) or log p_v (LOG, MAXLOG).  The negated literal
- *                 of v gets 1 - p_v resp. log(1 - exp(x_v)).
+ *                 of v gets 1 - p_v resp. log(1 - exp(x_v)).  LOG, MAXLOG: a child that is NaN (a NaN weight, or the
+ *                 negated literal of x_v > 0) counts as impossible in an OR gate and makes an AND gate NaN.
  *   B             batch size >= 1
  *   out           device [B, R] row-major fp32; out[b, r] = value of roots[r] on sample b
  *   stream        hipStream_t (as void*), may be NULL for the default stream
@@ -242,6 +243,7 @@ klay_status klay_backward_lits(klay_circuit* c, const float* dout, float* dpos, 
  *   pos_weights, neg_weights, out, dout, dpos, dneg   as for klay_forward_lits / klay_backward_lits,
  *                 in double; neg_weights = NULL derives the negated literals from pos_weights, and
  *                 dneg must then be NULL as well.
+ * A NaN child makes an OR gate NaN here (LOG), unless every other child is impossible: then the gate is too.
  * All three semirings are evaluated; KLAY_LOG and KLAY_REAL are differentiated (KLAY_MAXLOG is not:
  * KLAY_EINVAL).  In double the real semiring reaches circuits whose values underflow fp32.
  * The activations live in a library-owned workspace of their own (klay_set_workspace and

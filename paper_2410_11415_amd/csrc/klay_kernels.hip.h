@@ -73,12 +73,26 @@ constexpr float kLn2 = 0.6931471805599453f;
 __device__ __forceinline__ float fexp(float x) { return __builtin_amdgcn_exp2f(x * kLog2e); }
 __device__ __forceinline__ float flog(float x) { return __builtin_amdgcn_logf(x) * kLn2; }
 
+// the largest of those that are no NaN
 __device__ __forceinline__ float max3(float a, float b, float c) {
     float r;
     asm("v_max3_f32 %0, %1, %2, %3" : "=v"(r) : "v"(a), "v"(b), "v"(c));
     return r;
 }
+__device__ __forceinline__ float bigger(float a, float b) {
+    float r;
+    asm("v_max_f32 %0, %1, %2" : "=v"(r) : "v"(a), "v"(b));
+    return r;
+}
 constexpr float kFltMax = 3.402823466e+38f;
+
+// A NaN in the log domain (a weight above 0 leaves one for its negated literal) is an impossible child of an OR row, in every
+// fp32 kernel: its term counts 0, the maximum passes it by, and a row of nothing else is -inf.  (An AND row with one
+// is NaN.)
+// exp of a term of a logsumexp, x = term - finite(maximum): at most 1; 1 for an infinite weight, 0 for a NaN.  The clamp is
+// a bit of the exponential's own instruction.
+__device__ __forceinline__ float term_exp(float x) { return __builtin_amdgcn_fmed3f(fexp(x), 0.0f, 1.0f); }
+__device__ __forceinline__ float finite(float m) { return __builtin_amdgcn_fmed3f(m, -kFltMax, kFltMax); }
 
 template <int VEC> struct Pack;
 template <> struct Pack<1> { using T = float; };
@@ -168,7 +182,7 @@ __device__ __forceinline__ float premultiply(float g, float n) {
 // one element of a running logsumexp: (mx, acc) = (maximum so far, sum of exp(x - mx)), one exp per element
 __device__ __forceinline__ void lse_step(float& acc, float& mx, float x) {
     // d is +inf on the first finite element (e = 0, acc = 1), -inf for an impossible child under a finite
-    // maximum (e = 0), and NaN only for -inf - -inf, where the maximum of NaN and 0 is 0 and the comparison fails
+    // maximum (e = 0), and NaN only for -inf - -inf and for a NaN, where the maximum of NaN and 0 is 0 and the comparison fails
     const float d = x - mx;
     const float e = fmaxf(fexp(-fabsf(d)), 0.0f);
     const bool up = d > 0.0f;                                 // the same as x > mx
@@ -206,7 +220,7 @@ __device__ __forceinline__ void accumulate(float& acc, float& mx, float x, float
     }
     if (OP == OP_SUM) acc += x;
     else if (OP == OP_PROD) acc *= x;
-    else if (OP == OP_MAX) acc = x > acc ? x : acc;               // no NaN reaches here: two instructions, fmaxf takes three
+    else if (OP == OP_MAX) acc = x > acc ? x : acc;               // (acc is no NaN: two instructions, fmaxf takes three)
     else if (OP == OP_LSE) lse_step(acc, mx, x);
     else {
         const float wgt = !weighted ? 1.0f : ((y == -INFINITY) ? 0.0f : fexp(nc - y));
@@ -397,10 +411,8 @@ __device__ __forceinline__ void edge_combine(float& am, float& as, float bm, flo
     else if (OP == OP_PROD) am *= bm;
     else if (OP == OP_MAX) am = fmaxf(am, bm);
     else {
-        const float M = fmaxf(am, bm);
-        const float ea = (am == -INFINITY) ? 0.0f : fexp(am - M);
-        const float eb = (bm == -INFINITY) ? 0.0f : fexp(bm - M);
-        as = as * ea + bs * eb;
+        const float M = fmaxf(am, bm), m = finite(M);
+        as = as * term_exp(am - m) + bs * term_exp(bm - m);
         am = M;
     }
 }
@@ -493,10 +505,10 @@ __global__ __launch_bounds__(256) void edge_kernel(const int2* __restrict__ task
                 accumulate<OP_PROD_BWD>(part, unused, x[i], 0.0f, z[i], (id[i] & kWeighted) != 0);
                 vm = live ? part : 0.0f;
             } else if (LSE) {
-                vm = live ? x[i] : -INFINITY;
+                vm = live ? fmaxf(x[i], -INFINITY) : -INFINITY;
                 vs = live ? 1.0f : 0.0f;
             } else {
-                vm = live ? x[i] : dead_value<OP>();
+                vm = live ? (OP == OP_MAX ? fmaxf(x[i], -INFINITY) : x[i]) : dead_value<OP>();
             }
             if (lm[i] == 0ull) {                      // no row ends in this step
                 edge_combine<OP>(accm, accs, vm, vs);
@@ -587,8 +599,6 @@ __device__ __forceinline__ bool lane_group(const Args& a, int vec, int& sub, int
 typedef uint32_t Entries4 __attribute__((ext_vector_type(4), aligned(4)));
 typedef int32_t Offsets2 __attribute__((ext_vector_type(2), aligned(4)));
 
-__device__ __forceinline__ float finite(float m) { return __builtin_amdgcn_fmed3f(m, -kFltMax, kFltMax); }
-
 // four entries of a row joined to its state; `live` of them are part of the row
 template <int OP, int VEC>
 __device__ __forceinline__ void accumulate4(float (&acc)[VEC], float (&mx)[VEC], const float (&x)[4][VEC], const float (&y)[4][VEC],
@@ -596,12 +606,12 @@ __device__ __forceinline__ void accumulate4(float (&acc)[VEC], float (&mx)[VEC],
 #pragma unroll
     for (int v = 0; v < VEC; ++v) {
         if (OP == OP_LSE) {
-            // (mx kept finite, see the persistent kernels: one maximum for the four, no test for -inf)
+            // (one maximum for the four, no test for -inf: see the persistent kernels)
             const float x0 = live > 0 ? x[0][v] : -INFINITY, x1 = live > 1 ? x[1][v] : -INFINITY;
             const float x2 = live > 2 ? x[2][v] : -INFINITY, x3 = live > 3 ? x[3][v] : -INFINITY;
-            const float m = finite(max3(max3(x0, x1, x2), x3, mx[v]));
-            acc[v] = fmaf(acc[v], fexp(mx[v] - m), (fexp(x0 - m) + fexp(x1 - m)) + (fexp(x2 - m) + fexp(x3 - m)));
-            mx[v] = m;
+            const float hi = max3(max3(x0, x1, x2), x3, mx[v]), m = finite(hi);
+            acc[v] = fmaf(acc[v], term_exp(mx[v] - m), (term_exp(x0 - m) + term_exp(x1 - m)) + (term_exp(x2 - m) + term_exp(x3 - m)));
+            mx[v] = hi;
         } else {
 #pragma unroll
             for (int i = 0; i < 4; ++i) {
@@ -638,7 +648,7 @@ __global__ __launch_bounds__(256) void pass_kernel(PassArgs a) {
     }
     float acc[VEC], mx[VEC];
 #pragma unroll
-    for (int v = 0; v < VEC; ++v) { acc[v] = identity<OP>(); mx[v] = OP == OP_LSE ? -kFltMax : -INFINITY; }
+    for (int v = 0; v < VEC; ++v) { acc[v] = identity<OP>(); mx[v] = -INFINITY; }
     uint32_t last = 0;
     for (;;) {
         float x0[4][VEC], x1[4][VEC], y0[4][VEC], y1[4][VEC];
@@ -956,14 +966,13 @@ template <class F>
 __device__ __forceinline__ Float2 each(F f, Float2 a, Float2 b) { return Float2{f(a.x, b.x), f(a.y, b.y)}; }
 template <class F>
 __device__ __forceinline__ Float2 each(F f, Float2 a, Float2 b, Float2 c) { return Float2{f(a.x, b.x, c.x), f(a.y, b.y, c.y)}; }
-__device__ __forceinline__ Float2 fexp(Float2 x) { return each([](float a) { return fexp(a); }, x); }
+__device__ __forceinline__ Float2 term_exp(Float2 x) { return each([](float a) { return term_exp(a); }, x); }
 __device__ __forceinline__ Float2 flog(Float2 x) { return each([](float a) { return flog(a); }, x); }
 __device__ __forceinline__ Float2 finite(Float2 x) { return each([](float a) { return finite(a); }, x); }
 __device__ __forceinline__ Float2 max3(Float2 a, Float2 b, Float2 c) { return each([](float x, float y, float z) { return max3(x, y, z); }, a, b, c); }
-__device__ __forceinline__ float bigger(float a, float b) { return b > a ? b : a; }
 __device__ __forceinline__ Float2 bigger(Float2 a, Float2 b) { return each([](float x, float y) { return bigger(x, y); }, a, b); }
-__device__ __forceinline__ float smaller(float a, float b) { return b > a ? a : b; }
-__device__ __forceinline__ Float2 smaller(Float2 a, Float2 b) { return each([](float x, float y) { return smaller(x, y); }, a, b); }
+__device__ __forceinline__ float apart(float a, float b) { return fabsf(a - b); }
+__device__ __forceinline__ Float2 apart(Float2 a, Float2 b) { return each([](float x, float y) { return apart(x, y); }, a, b); }
 __device__ __forceinline__ float muladd(float a, float b, float c) { return fmaf(a, b, c); }
 __device__ __forceinline__ Float2 muladd(Float2 a, Float2 b, Float2 c) { return each([](float x, float y, float z) { return fmaf(x, y, z); }, a, b, c); }
 
@@ -1001,21 +1010,28 @@ __device__ __forceinline__ V col_fly(V x, int k) {
     return x;
 }
 
-// Logsumexp in the persistent kernel: m = maximum so far, kept finite (between -FLT_MAX and FLT_MAX, so that no
-// difference is inf - inf: a row of impossible children ends as -FLT_MAX + log(0) = -inf, an infinite weight as inf),
-// s = sum of exp(x - m).
-// the value of a row of two, of four entries
+// Logsumexp in the persistent kernel: m = maximum so far, s = sum of exp(x - finite(m)), where finite() keeps the
+// subtrahend between -FLT_MAX and FLT_MAX, so that no difference is inf - inf: a row of impossible children ends as
+// -inf + log(0) = -inf, one with an infinite weight as inf.
+// the value of a row of one entry, of two, of four
+template <int OP, class V>
+__device__ __forceinline__ V col_one(V x) {
+    if (OP != OP_LSE && OP != OP_MAX) return x;
+    return bigger(x, V(-INFINITY));
+}
 template <int OP, class V>
 __device__ __forceinline__ V col_two(V x, V y) {
-    if (OP != OP_LSE) return col_join<OP>(x, y);
-    const V hi = bigger(x, y), lo = smaller(x, y);
-    return hi + flog(1.0f + fexp(lo - finite(hi)));
+    if (OP != OP_LSE && OP != OP_MAX) return col_join<OP>(x, y);
+    const V hi = max3(x, y, V(-INFINITY));
+    return OP == OP_MAX ? hi : hi + flog(1.0f + term_exp(-apart(x, y)));      // (apart: NaN for two equal infinities too, a term of 0)
 }
 template <int OP, class V>
 __device__ __forceinline__ V col_four(V x0, V x1, V x2, V x3) {
-    if (OP != OP_LSE) return col_join<OP>(col_join<OP>(x0, x1), col_join<OP>(x2, x3));
-    const V m = finite(max3(max3(x0, x1, x2), x3, V(-kFltMax)));
-    return m + flog((fexp(x0 - m) + fexp(x1 - m)) + (fexp(x2 - m) + fexp(x3 - m)));
+    if (OP != OP_LSE && OP != OP_MAX) return col_join<OP>(col_join<OP>(x0, x1), col_join<OP>(x2, x3));
+    const V hi = max3(max3(x0, x1, x2), x3, V(-INFINITY));
+    if (OP == OP_MAX) return hi;
+    const V m = finite(hi);
+    return hi + flog((term_exp(x0 - m) + term_exp(x1 - m)) + (term_exp(x2 - m) + term_exp(x3 - m)));
 }
 
 // Reads one word of every 128 bytes of the blocks, shared out among the workgroups of an XCD (every eighth one), so that
@@ -1037,7 +1053,7 @@ __device__ __forceinline__ void col_touch(const Line* blocks, int n_blocks) {
 template <int OP, int KIND, class V>
 __device__ __forceinline__ void col_rows(const V* below, uint32_t a, uint32_t b, V* v) {
     const V x0 = col_at(below, a & 0xFFFFu), x1 = col_at(below, a >> 16), x2 = col_at(below, b & 0xFFFFu), x3 = col_at(below, b >> 16);
-    if (KIND == 0) { v[0] = x0; v[1] = x1; v[2] = x2; v[3] = x3; }
+    if (KIND == 0) { v[0] = col_one<OP>(x0); v[1] = col_one<OP>(x1); v[2] = col_one<OP>(x2); v[3] = col_one<OP>(x3); }
     if (KIND == 1) { v[0] = col_two<OP>(x0, x1); v[1] = col_two<OP>(x2, x3); }
     if (KIND == 2) v[0] = col_four<OP>(x0, x1, x2, x3);
 }
@@ -1088,7 +1104,7 @@ template <class V>
 __device__ __forceinline__ V col_lse_fly(V m, V s, int k) {
     if (k > 0) {
         const V m2 = col_fly<OP_LSE>(m, k);
-        s = col_fly<OP_SUM>(s * fexp(m - m2), k);
+        s = col_fly<OP_SUM>(s * term_exp(m - finite(m2)), k);
         m = m2;
     }
     return m + flog(s);
@@ -1100,11 +1116,11 @@ __device__ __forceinline__ void col_long(const V* below, Line w, bool fresh, V& 
     const V x0 = col_at(below, w.x & 0xFFFFu), x1 = col_at(below, w.x >> 16), x2 = col_at(below, w.y & 0xFFFFu), x3 = col_at(below, w.y >> 16);
     const V x4 = col_at(below, w.z & 0xFFFFu), x5 = col_at(below, w.z >> 16), x6 = col_at(below, w.w & 0xFFFFu), x7 = col_at(below, w.w >> 16);
     if (OP == OP_LSE) {
-        const V m2 = finite(max3(max3(max3(x0, x1, x2), x3, x4), max3(x5, x6, x7), m));
-        const V s2 = ((fexp(x0 - m2) + fexp(x1 - m2)) + (fexp(x2 - m2) + fexp(x3 - m2))) +
-                         ((fexp(x4 - m2) + fexp(x5 - m2)) + (fexp(x6 - m2) + fexp(x7 - m2)));
-        s = fresh ? s2 : muladd(s, fexp(m - m2), s2);
-        m = m2;
+        const V hi = max3(max3(max3(x0, x1, x2), x3, x4), max3(x5, x6, x7), m), m2 = finite(hi);
+        const V s2 = ((term_exp(x0 - m2) + term_exp(x1 - m2)) + (term_exp(x2 - m2) + term_exp(x3 - m2))) +
+                         ((term_exp(x4 - m2) + term_exp(x5 - m2)) + (term_exp(x6 - m2) + term_exp(x7 - m2)));
+        s = fresh ? s2 : muladd(s, term_exp(m - m2), s2);
+        m = hi;
     } else {
         const V x = col_join<OP>(col_four<OP>(x0, x1, x2, x3), col_four<OP>(x4, x5, x6, x7));
         s = fresh ? x : col_join<OP>(s, x);
@@ -1126,7 +1142,7 @@ __device__ __forceinline__ void col_fwd_layer(ColWalk& walk, const V* below, V* 
             const int r = lane >> run.k, per = 64 >> run.k;
             const bool writes = (lane & ((1 << run.k) - 1)) == 0;
             for (int rows = run.rows; rows > 0; rows -= per, out += per) {
-                V m = V(-kFltMax), s = V(0.0f);
+                V m = V(-INFINITY), s = V(0.0f);
                 Line w0, w1;
                 walk.block(w0, w1);
                 col_long<OP>(below, w0, true, m, s);

@@ -165,7 +165,11 @@ __global__ __launch_bounds__(256) void pass_kernel(PassArgs a) {
     else out = a.dst_seg + (size_t)(row - a.n_main) * a.ld + col;
     double o[VEC];
 #pragma unroll
-    for (int v = 0; v < VEC; ++v) o[v] = OP == OP_LSE ? mx[v] + log(acc[v]) : finish<OP>(acc[v], mx[v]);
+    for (int v = 0; v < VEC; ++v) {
+        // (a row with nothing above -inf is -inf, also with a NaN among its children, which any other row passes on)
+        if (OP == OP_LSE) o[v] = mx[v] == -1.7976931348623157e308 || mx[v] == -INFINITY ? -INFINITY : mx[v] + log(acc[v]);
+        else o[v] = finish<OP>(acc[v], mx[v]);
+    }
     if (VEC == 2) {
         typedef double v2 __attribute__((ext_vector_type(2), aligned(8)));
         *reinterpret_cast<v2*>(out) = v2{o[0], o[VEC - 1]};
