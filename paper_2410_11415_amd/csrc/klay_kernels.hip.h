@@ -1309,32 +1309,33 @@ __global__ __launch_bounds__(kColThreads) void col_fwd_kernel(const ColLayer* __
 // own: the values of the rows by slot; it may be the array the adjoints go to (a slot is read by the lanes of its row only).
 enum ColMode { kLogAnd, kLogOr, kRealOr, kRealAnd };
 
-// the adjoints of a row so far: their sum (RealAnd: of the parents without a zero child, and of those with exactly one)
+// what a row's parents pass down: the sum (RealAnd: of the parents without a zero child, and of those with exactly one).
+// Sums are balanced over the entries of a line and the two lines of a block: shorter chains and fewer roundings than one
+// entry after another.
 template <int MODE, class V> struct ColSum {
     V a = V(0.0f), b = V(0.0f);
-    __device__ __forceinline__ void add(const V* above, uint32_t e, V own) {
-        const V g = col_at(above, e & 0x7FFFu);
-        if constexpr (MODE == kRealAnd) {
-            a += each([](float x) { return __float_as_uint(x) & 1u ? 0.0f : x; }, g);
-            b += each([](float x) { return __float_as_uint(x) & 1u ? __uint_as_float(__float_as_uint(x) & ~1u) : 0.0f; }, g);
-        } else if (MODE == kLogOr && (e & 0x8000u)) a += each([](float x, float y) { return decode_h(x, y); }, g, own);
-        else a += g;
-    }
-    __device__ __forceinline__ void add2(const V* above, uint32_t w, V own) {
-        add(above, w & 0xFFFFu, own);
-        add(above, w >> 16, own);
-    }
-    __device__ __forceinline__ void add8(const V* above, Line w, V own) {
-        ColSum x, y, z;
-        add2(above, w.x, own); x.add2(above, w.y, own); y.add2(above, w.z, own); z.add2(above, w.w, own);
-        a += x.a + (y.a + z.a);
-        if (MODE == kRealAnd) b += x.b + (y.b + z.b);
-    }
-    __device__ __forceinline__ void meet(int k) {
-        a = col_fly<OP_SUM>(a, k);
-        if (MODE == kRealAnd) b = col_fly<OP_SUM>(b, k);
-    }
 };
+template <int MODE, class V>
+__device__ __forceinline__ ColSum<MODE, V> operator+(const ColSum<MODE, V>& x, const ColSum<MODE, V>& y) {
+    if constexpr (MODE == kRealAnd) return {x.a + y.a, x.b + y.b};
+    else return {x.a + y.a, x.b};
+}
+template <int MODE, class V>
+__device__ __forceinline__ ColSum<MODE, V> col_entry(const V* above, uint32_t e, V own) {
+    const V g = col_at(above, e & 0x7FFFu);
+    if constexpr (MODE == kRealAnd)
+        return {each([](float x) { return __float_as_uint(x) & 1u ? 0.0f : x; }, g),
+                each([](float x) { return __float_as_uint(x) & 1u ? __uint_as_float(__float_as_uint(x) & ~1u) : 0.0f; }, g)};
+    else return {MODE == kLogOr && (e & 0x8000u) ? each([](float x, float y) { return decode_h(x, y); }, g, own) : g, V(0.0f)};
+}
+template <int MODE, class V>
+__device__ __forceinline__ ColSum<MODE, V> col_pair(const V* above, uint32_t w, V own) {
+    return col_entry<MODE>(above, w & 0xFFFFu, own) + col_entry<MODE>(above, w >> 16, own);
+}
+template <int MODE, class V>
+__device__ __forceinline__ ColSum<MODE, V> col_line(const V* above, Line w, V own) {
+    return (col_pair<MODE>(above, w.x, own) + col_pair<MODE>(above, w.y, own)) + (col_pair<MODE>(above, w.z, own) + col_pair<MODE>(above, w.w, own));
+}
 
 // Product rows that hold a zero: the product of a row's non-zero children and how many are zero, per column, from the
 // node values (rare, so straight from global memory).
@@ -1378,8 +1379,15 @@ __device__ __forceinline__ void col_bwd_quarter(const V* above, uint32_t a, uint
 #pragma unroll
     for (int i = 0; i < N; ++i) own[i] = own_at[FULL || lane + 64 * i < rows ? 64 * i : -lane];
     const uint32_t e[4] = {a & 0xFFFFu, a >> 16, b & 0xFFFFu, b >> 16};
+    if constexpr (KIND == 0) {
 #pragma unroll
-    for (int i = 0; i < 4; ++i) v[i >> KIND].add(above, e[i], own[i >> KIND]);
+        for (int i = 0; i < 4; ++i) v[i] = col_entry<MODE>(above, e[i], own[i]);
+    } else if constexpr (KIND == 1) {
+        v[0] = col_pair<MODE>(above, a, own[0]);
+        v[1] = col_pair<MODE>(above, b, own[1]);
+    } else {
+        v[0] = col_pair<MODE>(above, a, own[0]) + col_pair<MODE>(above, b, own[0]);
+    }
 #pragma unroll
     for (int i = 0; i < N; ++i)
         if (FULL || lane + 64 * i < rows) out[64 * i] = col_finish<MODE>(v[i], own[i], (e[i << KIND] & 0x8000u) != 0, repair, r + 64 * i);
@@ -1432,17 +1440,16 @@ __device__ __forceinline__ void col_bwd_layer(ColWalk& walk, const V* above, V* 
                 Line w0, w1;
                 walk.block(w0, w1);
                 const bool flagged = (w0.x & 0x8000u) != 0;
-                ColSum<MODE, V> acc;
-                acc.add8(above, w0, own);
+                ColSum<MODE, V> acc = col_line<MODE>(above, w0, own);
                 if (run.kind == 3) {
-                    acc.add8(above, w1, own);
+                    acc = acc + col_line<MODE>(above, w1, own);
                     for (int b = 1; b < run.blocks; ++b) {
                         walk.block(w0, w1);
-                        acc.add8(above, w0, own);
-                        acc.add8(above, w1, own);
+                        acc = acc + (col_line<MODE>(above, w0, own) + col_line<MODE>(above, w1, own));
                     }
                 }
-                acc.meet(run.k);
+                acc.a = col_fly<OP_SUM>(acc.a, run.k);
+                if (MODE == kRealAnd) acc.b = col_fly<OP_SUM>(acc.b, run.k);
                 if (writes && r < rows) out[r] = col_finish<MODE>(acc, own, flagged, repair, first + r);
             }
         }

@@ -171,3 +171,30 @@ def test_own_values_wherever_the_reverse_kernel_keeps_them(widths, batch):
         (assert_real_close if semiring == REAL else assert_log_close)(out, ref, "values")
         assert_grad_close(grad, rgrad, "gradients", real=semiring == REAL)
     k.close()
+
+
+def test_sums_of_long_rows_are_balanced():
+    """A literal with 15000 parents whose adjoints are 2^27 once and 1 otherwise: an addition with the large number in it is
+    off by at most 8.  With the 8 entries of a line summed as pairs, and the two lines of a block (16 ones, exact) before they
+    join, the seven ones of its line are lost, and up to 8 in its block, in the partial last block and in each of the 6
+    steps over the lanes: 71.  Adding a line's entries or pairs one after another loses all 8 of every line: up to 234."""
+    import torch
+    import paper_2410_11415_amd as klay
+    n = 15000
+    types = [0] * (n + 1) + [1] * n + [2] * n
+    lits = [v + 1 for v in range(n + 1)] + [0] * (2 * n)
+    ptr = np.concatenate([np.zeros(n + 1), 2 * np.arange(n + 1), 2 * n + 1 + np.arange(n)]).astype(np.int64)
+    pairs = np.stack([np.zeros(n, np.int32), 1 + np.arange(n, dtype=np.int32)], axis=1).ravel()
+    idx = np.concatenate([pairs, n + 1 + np.arange(n)]).astype(np.int32)
+    c = Circuit(n + 1, np.array(types, np.uint8), np.array(lits, np.int32), ptr, idx, 2 * n + 1 + np.arange(n, dtype=np.int32))
+    k = klay.Circuit(*c.arrays(), device=0)
+    assert k.info()["tail_first_layer"] == 1 and k.info()["max_fan_out"] == n
+    batch = 16
+    dout = np.ones((batch, n), np.float32)
+    for b in range(batch):
+        dout[b, n * b // batch] = 2.0 ** 27
+    k.forward(torch.full((batch, n + 1), -0.5, device="cuda"), LOG)
+    got = k.backward(torch.from_numpy(dout).cuda()).cpu().numpy().astype(np.float64)
+    np.testing.assert_array_equal(got[:, 1:], dout)
+    assert np.abs(got[:, 0] - (2.0 ** 27 + n - 1)).max() <= 71, got[:, 0] - 2.0 ** 27
+    k.close()
