@@ -488,7 +488,7 @@ klay_status upload(klay_circuit* c) {
         constexpr size_t kTableWords = (size_t)klay::kDescTable * klay::kDescWords;
         for (int backward = 0; backward < 2; ++backward) {
             std::vector<uint32_t>& out = blocks[backward];
-            for (int w = 0; w < klay::kSlabWaves; ++w)
+            for (int w = 0; w < klay::kColWaves; ++w)
                 for (int step = 0; step <= L - p.tail_first; ++step) {
                     const int l = backward ? L - step : p.tail_first + step;
                     const klay::ColPlan& cp = backward ? p.layers[(size_t)l].col_bwd : p.layers[(size_t)l].col_fwd;

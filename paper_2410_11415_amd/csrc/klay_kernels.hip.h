@@ -883,13 +883,13 @@ __global__ __launch_bounds__(256) void stream_combine_kernel(const int2* __restr
 // kernel reads it the same way, and rows that an ordinary launch needs are transposed back on demand
 // (tb_to_rows_kernel).
 // ---------------------------------------------------------------------------------------------
-constexpr int kColThreads = 64 * kSlabWaves;
+constexpr int kColThreads = 64 * kColWaves;
 // a layer: its nodes, its first entry in a column of the value buffer, and where the streams of the 16 waves start
 // (blocks, tables; bwd: of the step into the layer below)
 struct ColLayer {
     int32_t n, at;
-    int32_t fwd_block[kSlabWaves], fwd_table[kSlabWaves];
-    int32_t bwd_block[kSlabWaves], bwd_table[kSlabWaves];
+    int32_t fwd_block[kColWaves], fwd_table[kColWaves];
+    int32_t bwd_block[kColWaves], bwd_table[kColWaves];
 };
 
 typedef uint32_t Line __attribute__((ext_vector_type(4)));       // a lane's 16 bytes of a line

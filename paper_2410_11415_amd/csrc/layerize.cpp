@@ -181,45 +181,6 @@ void make_pass_plan(int64_t n, const int32_t* ptr, const int32_t* idx_in, const 
     out.n_seg_tasks = cut_tasks(n, n + n_seg, out.seg_tasks);
 }
 
-namespace {
-// chunked, lane-interleaved index vectors of a CSR with n_src source rows, one run of lines per wave
-// (see SlabPlan)
-void make_slab(int64_t n, int64_t n_src, const int32_t* ptr, const int32_t* idx, const uint32_t* flags, SlabPlan& out,
-               const uint32_t* row_bits = nullptr) {
-    const int64_t chunks = (n + 63) / 64;
-    std::vector<int32_t> width((size_t)chunks, 0);
-    for (int64_t q = 0; q < chunks; ++q)
-        for (int64_t r = q * 64; r < std::min<int64_t>(n, q * 64 + 64); ++r)
-            width[(size_t)q] = std::max(width[(size_t)q], ptr[r + 1] - ptr[r]);
-    for (int32_t& w : width) w = std::max(w, 1);      // every chunk has a last line, also one of empty rows
-    int64_t lines = 0;
-    for (int w = 0; w < kSlabWaves; ++w) {
-        out.wave_line[w] = (int32_t)lines;
-        for (int64_t q = w; q < chunks; q += kSlabWaves) lines += width[(size_t)q];
-        lines = (lines + kSlabBlock - 1) / kSlabBlock * kSlabBlock;
-    }
-    out.wave_line[kSlabWaves] = (int32_t)lines;
-    out.ent.assign((size_t)lines * 64, (uint32_t)n_src);
-    for (int w = 0; w < kSlabWaves; ++w) {
-        int64_t line = out.wave_line[w];
-        for (int64_t q = w; q < chunks; q += kSlabWaves) {
-            const int32_t wq = width[(size_t)q];
-            for (int64_t r = q * 64; r < std::min<int64_t>(n, q * 64 + 64); ++r)
-                for (int32_t j = ptr[r]; j < ptr[r + 1]; ++j)
-                    out.ent[(size_t)(line + (j - ptr[r])) * 64 + (size_t)(r - q * 64)] = (uint32_t)idx[j] | (flags ? flags[j] : 0u);
-            for (int lane = 0; lane < 64; ++lane) {
-                uint32_t& last = out.ent[(size_t)(line + wq - 1) * 64 + (size_t)lane];
-                last |= kLastEdge;
-                // the word a lane holds when its chunk closes also tells whether its row is flagged
-                const int64_t r = q * 64 + lane;
-                if (row_bits && r < n && ((row_bits[(size_t)r >> 5] >> (r & 31)) & 1u)) last |= kRowFlag;
-            }
-            line += wq;
-        }
-    }
-}
-}  // namespace
-
 void make_cols(int64_t n, const int32_t* ptr, const int32_t* idx, const uint32_t* flags, const uint32_t* row_bits,
                int waves, int pad, ColStep step, ColPlan& out) {
     out = ColPlan();
@@ -295,7 +256,7 @@ void make_cols(int64_t n, const int32_t* ptr, const int32_t* idx, const uint32_t
     }
     const uint32_t pads = (uint32_t)pad | (uint32_t)pad << 16;
     size_t next = 0;
-    for (int w = 0; w < kSlabWaves; ++w) {
+    for (int w = 0; w < kColWaves; ++w) {
         out.block_at[w] = (int32_t)(out.blocks.size() / kBlockWords);
         out.table_at[w] = (int32_t)(out.tables.size() / (kDescTable * kDescWords));
         const size_t end = share_end(next, bound);
@@ -346,8 +307,8 @@ void make_cols(int64_t n, const int32_t* ptr, const int32_t* idx, const uint32_t
         describe(0u, 0u);
         while (out.tables.size() % (kDescTable * kDescWords)) out.tables.push_back(0u);
     }
-    out.block_at[kSlabWaves] = (int32_t)(out.blocks.size() / kBlockWords);
-    out.table_at[kSlabWaves] = (int32_t)(out.tables.size() / (kDescTable * kDescWords));
+    out.block_at[kColWaves] = (int32_t)(out.blocks.size() / kBlockWords);
+    out.table_at[kColWaves] = (int32_t)(out.tables.size() / (kDescTable * kDescWords));
 }
 
 int layerize(int32_t V, int64_t N, const uint8_t* node_type, const int32_t* node_lit,
@@ -933,18 +894,12 @@ int layerize(int32_t V, int64_t N, const uint8_t* node_type, const int32_t* node
             for (int64_t i = 0; i < lay.n; ++i) fan_in = std::max<int64_t>(fan_in, lay.row_ptr[(size_t)i + 1] - lay.row_ptr[(size_t)i]);
             for (int64_t i = 0; i < nc; ++i) fan_out = std::max<int64_t>(fan_out, cptr[(size_t)i + 1] - cptr[(size_t)i]);
             if (fan_in <= kTailFanCap && fan_out <= kColRowEntries) {
-                make_slab(lay.n, nc, lay.row_ptr.data(), lay.child.data(), nullptr, lay.slab_fwd);
-                lay.tail_fwd_ok = true;
+                lay.tail_ok = true;
                 const bool is_and = (l & 1) != 0;
                 make_cols(lay.n, lay.row_ptr.data(), lay.child.data(), nullptr, nullptr, kColFwdWaves,
                           is_and ? kColPadAnd : kColPadOr, is_and ? kColFwdAnd : kColFwdOr, lay.col_fwd);
                 make_cols(nc, cptr.data(), cpar.data(), cflag.data(), is_and && l >= 3 ? plan.layers[(size_t)l - 1].multi.data() : nullptr,
                           kColBwdWaves, kColPadAnd, is_and ? kColBwdAnd : kColBwdOr, lay.col_bwd);
-                if (fan_out <= kTailFanCap) {
-                    make_slab(nc, lay.n, cptr.data(), cpar.data(), cflag.data(), lay.slab_bwd,
-                              (l & 1) && l >= 3 ? plan.layers[(size_t)l - 1].multi.data() : nullptr);
-                    lay.tail_bwd_ok = true;
-                }
             }
         }
         plan.num_split_rows += lay.bwd.n_heavy;
@@ -996,15 +951,13 @@ int layerize(int32_t V, int64_t N, const uint8_t* node_type, const int32_t* node
         plan.max_layer_nodes = std::max(plan.max_layer_nodes, plan.layers[(size_t)l].n);
     }
 
-    // the narrow top: the longest suffix of layers that all kept their plain index vectors
-    plan.tail_first = plan.tail_bwd_first = 0;
+    // the narrow top: the longest suffix of candidate layers
+    plan.tail_first = 0;
     if (!opt.no_tail) {
         int32_t t = L + 1;
-        while (t - 1 >= 1 && plan.layers[(size_t)t - 1].tail_fwd_ok) --t;
+        while (t - 1 >= 1 && plan.layers[(size_t)t - 1].tail_ok) --t;
         if (t <= L) plan.tail_first = t;
-        t = L + 1;
-        while (t - 1 >= 1 && plan.layers[(size_t)t - 1].tail_bwd_ok) --t;
-        if (t <= L) plan.tail_bwd_first = t;
+        for (--t; t >= 1; --t) plan.layers[(size_t)t].col_fwd = plan.layers[(size_t)t].col_bwd = ColPlan();      // candidates below a layer that is none
     }
     plan.col_off.assign((size_t)L + 1, -1);
     if (plan.tail_first > 0) {

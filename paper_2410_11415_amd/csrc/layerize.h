@@ -24,27 +24,16 @@ struct Options {
 
 // Layers at the top of the circuit with at most this many nodes are candidates for the persistent
 // kernels, which keep two layers of one batch column in LDS (values forward, adjoints in the reverse sweep):
-// 20000 rows is what two arrays in 160 KB hold.  A candidate layer has no row with more sources than kTailFanCap: a
-// narrow layer of long rows has more entries than one compute unit walks in the time of a launch.
+// 20000 rows is what two arrays in 160 KB hold.  A candidate layer has no row with more sources than kTailFanCap
+// (set when a lane walked a whole row; rows are cut over the lanes now, and a larger cap has not been measured); the nodes
+// below it may have any number of parents, up to kColRowEntries.
 constexpr int64_t kTailRowsCap = 20000;
 constexpr int64_t kTailFanCap = 64;
 
-// Index vectors of one layer of the narrow top, one row per lane: rows are taken in chunks of 64 consecutive
-// rows (one per lane of a wave); a chunk has as many steps as its longest row, and step i of a chunk
-// is one line of 64 words: lane j holds the i-th source of row 64 * chunk + j, or a padding word (source n_src)
-// when that row is shorter or does not exist.  In the reverse plan the word that a lane holds in the last line of a
-// chunk carries kRowFlag when the lane's row is an OR node with more than one child.  The 16 waves of a workgroup take
-// the chunks round-robin; every word of the last line of a chunk carries kLastEdge; runs are padded to a multiple of
-// kSlabBlock lines.  The layers that have this form are the candidates for the persistent kernels, which walk the
-// same rows in the form of ColPlan below; the lines themselves serve the host check of the plans only.
-constexpr int kSlabWaves = 16;
-constexpr int kSlabBlock = 8;
-struct SlabPlan {
-    int32_t wave_line[kSlabWaves + 1] = {};   // first line of each wave's run (wave_line[16] = all lines)
-    std::vector<uint32_t> ent;                // 64 words per line: source row | flags
-};
+// Waves of a workgroup of those kernels.
+constexpr int kColWaves = 16;
 
-// The same index vectors in the form the persistent kernels walk: runs of consecutive rows of one kind, read in blocks of
+// Index vectors of one layer in the form the persistent kernels walk: runs of consecutive rows of one kind, read in blocks of
 // 64 lanes x 16 entries of 16 bits (32 bytes per lane in two lines of 1 KB).
 //   Kinds 0, 1, 2: rows of at most 1, 2 or 4 entries, in chunks of 64 rows: a block holds 16, 8 or 4 chunks, row
 // 64 i + lane of the run has the lane's entries from i << kind on.  Kinds 3, 4: units of 64 >> k rows, 2^k lanes
@@ -62,12 +51,12 @@ struct SlabPlan {
 // cost, and every wave gets a contiguous share of about the same cost, so that the waves reach the layer's barrier together.
 //   The forward kernel has one wave less for this: its last wave moves the values to the column-major buffer.
 constexpr int kColSlots = 4, kColPadAnd = 0, kColPadOr = 1;
-constexpr int kColFwdWaves = kSlabWaves - 1, kColBwdWaves = kSlabWaves;
+constexpr int kColFwdWaves = kColWaves - 1, kColBwdWaves = kColWaves;
 constexpr int kBlockWords = 512, kLineWords = 256, kDescWords = 2, kDescTable = 64;
 constexpr int64_t kColBlocksMax = (1 << 17) - 1;             // blocks of a unit: what the descriptor holds
 constexpr int64_t kColRowEntries = kColBlocksMax * 16 * 64;  // a row that takes a whole wave
 struct ColPlan {
-    int32_t block_at[kSlabWaves + 1] = {}, table_at[kSlabWaves + 1] = {};   // first block / table of each wave
+    int32_t block_at[kColWaves + 1] = {}, table_at[kColWaves + 1] = {};   // first block / table of each wave
     std::vector<uint32_t> blocks, tables;
 };
 
@@ -119,11 +108,10 @@ struct LayerPlan {
     std::vector<uint8_t> is_pad;     // [n] 1 for unary chain nodes
     std::vector<uint32_t> multi;     // [(n + 31) / 32] bit i: row i has more than one child (OR layers: the rows
                                      // whose edges carry a softmax weight in the reverse sweep)
-    bool tail_fwd_ok = false;        // slab_fwd is built: the layer may run in the persistent forward kernel
-    bool tail_bwd_ok = false;        // slab_bwd is built as well
-    SlabPlan slab_fwd;               // rows = nodes of this layer, sources = positions in layer - 1
-    SlabPlan slab_bwd;               // rows = nodes of layer - 1, sources = parents in this layer (| kWeightedEdge)
-    ColPlan col_fwd, col_bwd;        // the persistent kernels' form, for the layers tail_first .. num_layers (col_bwd: rows of layer - 1)
+    bool tail_ok = false;            // the layer may run in the persistent kernels
+    // for those, in the layers tail_first .. num_layers: rows = nodes of this layer, sources = positions in layer - 1; rows =
+    // nodes of layer - 1, sources = parents in this layer
+    ColPlan col_fwd, col_bwd;
     PassPlan fwd;                    // outputs = nodes of this layer, sources = layer - 1
     PassPlan bwd;                    // outputs = nodes of layer - 1, sources = this layer
     // Fused AND rows (padding-free part only).  An AND node below layer alias_top that has at most one child
@@ -147,8 +135,7 @@ struct CircuitPlan {
     int64_t max_layer_nodes = 0, max_fan_in = 0, max_fan_out = 0, num_split_rows = 0;
     int64_t num_merged = 0;              // input gates identified with an identical gate
     int64_t max_fwd_seg = 0, max_bwd_seg = 0;   // scratch rows needed by split passes
-    int32_t tail_first = 0;              // layers tail_first..num_layers may run in the persistent forward kernel (0: none)
-    int32_t tail_bwd_first = 0;          // layers tail_bwd_first..num_layers also in the reverse one (>= tail_first; 0: none)
+    int32_t tail_first = 0;              // layers tail_first..num_layers may run in the persistent kernels (0: none)
     // Column-major value buffer of the persistent kernels: first entry of each layer in a column (-1: none).  The
     // layers tail_first .. num_layers follow one another from 0, the layer below tail_first comes after them.
     std::vector<int64_t> col_off;

@@ -4,21 +4,12 @@
 // device kernels take, and compared with the sums over the plain per-layer index vectors
 // (paper Section 4: E_l = N_{l-1}[S_l], N_l = scatter(E_l, R_l)).  Built with the address and
 // undefined-behaviour sanitizers by tests/test_host_plans.py.
-#include <cstdio>
-#include <cstdlib>
 #include <random>
-#include <string>
-#include <vector>
 
-#include "../paper_2410_11415_amd/csrc/layerize.h"
+#include "host_col_walk.h"
 
 using klay::PassPlan;
-using u64 = unsigned long long;
-
-static u64 mix(u64 x) { x += 0x9E3779B97F4A7C15ull; x = (x ^ (x >> 30)) * 0xBF58476D1CE4E5B9ull; x = (x ^ (x >> 27)) * 0x94D049BB133111EBull; return x ^ (x >> 31); }
 static constexpr uint32_t kMask = klay::kRowFlag - 1u;
-
-#define CHECK(cond, ...) do { if (!(cond)) { std::printf("FAILED %s:%d: ", __FILE__, __LINE__); std::printf(__VA_ARGS__); std::printf("\n"); std::exit(1); } } while (0)
 
 // value of source row i, and weight tag of an entry (so that a wrong weighted flag changes the sum)
 static u64 val(int64_t i) { return mix((u64)i); }
@@ -128,57 +119,10 @@ static void check_plan(const PassPlan& p, int64_t n_out, int64_t n_src, const st
     }
 }
 
-// the walk of the persistent kernels over a chunked plan: each of the 16 waves streams through its run
-// of lines, one word per lane; the end-of-chunk bit (the same in all 64 words of a line) closes the 64
-// rows of the chunk in hand, and the wave's next chunk is 16 chunks further; padding words add nothing
-static void check_slab(const klay::SlabPlan& sp, int64_t n_out, int64_t n_src, const std::vector<u64>& want, const char* what,
-                       const std::vector<uint32_t>* row_bits = nullptr) {
-    const int64_t chunks = (n_out + 63) / 64;
-    CHECK(sp.wave_line[0] == 0 && (int64_t)sp.ent.size() == (int64_t)sp.wave_line[klay::kSlabWaves] * 64, "%s: sizes", what);
-    std::vector<int> written((size_t)n_out, 0);
-    for (int w = 0; w < klay::kSlabWaves; ++w) {
-        int64_t q = w;
-        std::vector<u64> acc(64, 0);
-        std::vector<int> ended(64, 0);
-        CHECK(sp.wave_line[w + 1] >= sp.wave_line[w], "%s: run bounds", what);
-        CHECK((sp.wave_line[w + 1] - sp.wave_line[w]) % klay::kSlabBlock == 0, "%s: run is not a whole number of blocks", what);
-        for (int64_t line = sp.wave_line[w]; line < sp.wave_line[w + 1]; ++line) {
-            const uint32_t* e = sp.ent.data() + (size_t)line * 64;
-            if (q >= chunks) {       // lines that fill the run up to a whole block: padding only, no end-of-chunk bit
-                for (int lane = 0; lane < 64; ++lane) CHECK((int64_t)e[lane] == n_src, "%s: filler line of wave %d", what, w);
-                continue;
-            }
-            for (int lane = 0; lane < 64; ++lane) {
-                CHECK((e[lane] & klay::kLastEdge) == (e[0] & klay::kLastEdge), "%s: end-of-chunk bit differs within a line", what);
-                {   // the row flag sits on the word a lane holds when its chunk closes, for flagged rows only
-                    const int64_t r = q * 64 + lane;
-                    const bool expect = (e[0] & klay::kLastEdge) && row_bits && r < n_out && (((*row_bits)[(size_t)r >> 5] >> (r & 31)) & 1u);
-                    CHECK(((e[lane] & klay::kRowFlag) != 0) == expect, "%s: row flag of row %lld", what, (long long)r);
-                }
-                const uint32_t src = e[lane] & kMask;
-                if ((int64_t)src == n_src) { CHECK(!(e[lane] & klay::kWeightedEdge), "%s: flag on padding", what); ended[(size_t)lane] = 1; continue; }
-                CHECK(!ended[(size_t)lane], "%s: source after padding", what);
-                CHECK(q * 64 + lane < n_out, "%s: source in a lane past the last row", what);
-                CHECK((int64_t)src < n_src, "%s: source out of range", what);
-                acc[(size_t)lane] += entry(e[lane] & ~klay::kLastEdge);
-            }
-            if (e[0] & klay::kLastEdge) {
-                for (int lane = 0; lane < 64; ++lane) {
-                    const int64_t r = q * 64 + lane;
-                    if (r < n_out) { CHECK(acc[(size_t)lane] == want[(size_t)r], "%s: row %lld value", what, (long long)r); ++written[(size_t)r]; }
-                    acc[(size_t)lane] = 0; ended[(size_t)lane] = 0;
-                }
-                q += klay::kSlabWaves;
-            }
-        }
-        CHECK(q >= chunks && q < chunks + klay::kSlabWaves, "%s: wave %d ends at chunk %lld of %lld", what, w, (long long)q, (long long)chunks);
-    }
-    for (int64_t r = 0; r < n_out; ++r) CHECK(written[(size_t)r] == 1, "%s: row %lld closed %d times", what, (long long)r, written[(size_t)r]);
-}
-
 int main(int argc, char** argv) {
     const int trials = argc > 1 ? std::atoi(argv[1]) : 120;
     std::mt19937_64 rng(12345);
+    ColSeen cols;
     long plans = 0, fused_plans = 0, b0_seen[3] = {0, 0, 0};
     for (int trial = 0; trial < trials; ++trial) {
         const int V = 1 + (int)(rng() % 12), nl = 2 * V;
@@ -226,6 +170,15 @@ int main(int argc, char** argv) {
             if (!o.alias_chains) CHECK(B0 == 0, "chains asked for");
             if (o.alias_chains && o.no_tail) CHECK(B0 == L, "no persistent top: padding-free throughout");
             ++b0_seen[B0 == 0 ? 0 : (B0 == L ? 2 : 1)];
+            // the column-major value buffer: the layers of the persistent kernels one after another, the one below them last
+            int64_t col = 0;
+            for (int l = plan.tail_first; plan.tail_first > 0 && l <= L; ++l) {
+                CHECK(plan.col_off[(size_t)l] == col, "entry of layer %d in a column", l);
+                col += plan.layers[(size_t)l].n;
+            }
+            CHECK(plan.col_rows == col, "entries of a column");
+            for (int l = 0; l <= L && (plan.tail_first == 0 || l < plan.tail_first); ++l)
+                CHECK(plan.col_off[(size_t)l] == (l == plan.tail_first - 1 ? col : -1), "layer %d has no place in a column", l);
             // layers above B0: edges to the layer directly below, reverse plans layer by layer
             for (int l = B0 + 1; l <= L; ++l) {
                 const klay::LayerPlan& lay = plan.layers[(size_t)l];
@@ -241,17 +194,23 @@ int main(int argc, char** argv) {
                 }
                 check_plan(lay.fwd, lay.n, nb, fwd, "forward plan"); ++plans;
                 check_plan(lay.bwd, nb, lay.n, bwd, "backward plan", (l % 2 == 1 && l >= 3) ? &plan.layers[(size_t)l - 1].multi : nullptr); ++plans;
-                CHECK(!lay.tail_bwd_ok || lay.tail_fwd_ok, "reverse persistent plan without the forward one");
-                if (lay.tail_fwd_ok) { check_slab(lay.slab_fwd, lay.n, nb, fwd, "persistent forward plan"); ++plans; }
-                if (lay.tail_bwd_ok) { check_slab(lay.slab_bwd, nb, lay.n, bwd, "persistent reverse plan",
-                                                  (l % 2 == 1 && l >= 3) ? &plan.layers[(size_t)l - 1].multi : nullptr); ++plans; }
+                if (plan.tail_first > 0 && l >= plan.tail_first) {
+                    // (an OR layer's padding names its own identity; adjoints of a step through an AND layer are flagged by row,
+                    // through an OR layer by edge)
+                    const bool is_and = l % 2 == 1;
+                    walk_cols(lay.col_fwd, lay.n, nb, klay::kColFwdWaves, is_and ? klay::kColPadAnd : klay::kColPadOr, false, nullptr, fwd, nullptr, "persistent forward plan", cols);
+                    walk_cols(lay.col_bwd, nb, lay.n, klay::kColBwdWaves, klay::kColPadAnd, !is_and, is_and && l >= 3 ? &plan.layers[(size_t)l - 1].multi : nullptr, bwd, nullptr,
+                              "persistent reverse plan", cols);
+                    plans += 2;
+                } else {
+                    CHECK(lay.col_fwd.blocks.empty() && lay.col_bwd.blocks.empty(), "a persistent plan that nothing walks");
+                }
             }
             for (int l = 1; l <= L; ++l) {
                 const klay::LayerPlan& lay = plan.layers[(size_t)l];
                 for (int64_t r = 0; r < lay.n; ++r)
                     CHECK(((lay.multi[(size_t)r >> 5] >> (r & 31)) & 1u) == (lay.row_ptr[(size_t)r + 1] - lay.row_ptr[(size_t)r] > 1 ? 1u : 0u), "multi-child bit");
-                if (plan.tail_first > 0 && l >= plan.tail_first) CHECK(lay.tail_fwd_ok && l > B0, "candidate suffix");
-                if (plan.tail_bwd_first > 0 && l >= plan.tail_bwd_first) CHECK(lay.tail_bwd_ok && plan.tail_bwd_first >= plan.tail_first, "reverse candidate suffix");
+                if (plan.tail_first > 0 && l >= plan.tail_first) CHECK(lay.tail_ok && l > B0, "candidate suffix");
                 if (l < B0) for (int64_t r = 0; r < lay.n; ++r) CHECK(!lay.is_pad[(size_t)r], "chain node below the boundary layer");
             }
             if (B0 > 0) {
@@ -347,6 +306,7 @@ int main(int argc, char** argv) {
     }
     CHECK(b0_seen[0] > 0 && b0_seen[1] > 0 && b0_seen[2] > 0, "boundary layer cases seen: %ld %ld %ld", b0_seen[0], b0_seen[1], b0_seen[2]);
     CHECK(fused_plans > 0, "no fused forward plan was built");
+    CHECK(cols.runs > 0 && cols.wide > 0, "no persistent plan was walked");
     std::printf("ok: %ld plans checked (%ld fused forward plans)\n", plans, fused_plans);
     return 0;
 }

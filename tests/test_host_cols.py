@@ -1,4 +1,4 @@
-"""Host check of the persistent kernels' streams: tests/host_col_check.cpp cuts random index vectors (rows of 1 to 20000
+"""Host check of the persistent kernels' streams: tests/host_col_check.cpp cuts random index vectors (rows of 1 to 300000
 entries, 1 to 20000 rows) into units and executes the walk of the kernels over them, against sums over the plain index
 vectors.  Compiled with the address and undefined-behaviour sanitizers.  No GPU needed."""
 import os

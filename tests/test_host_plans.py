@@ -1,5 +1,5 @@
-"""Host check of the launch plans (tasks, segments of split rows, combine lists) that klay_build
-uploads: tests/host_plan_check.cpp layerizes random DAGs under many option sets and executes every
+"""Host check of the launch plans (tasks, segments of split rows, combine lists, streams of the persistent kernels and the
+layout of their value buffer) that klay_build uploads: tests/host_plan_check.cpp layerizes random DAGs under many option sets and executes every
 plan in plain C++ the way the kernels walk it, against sums over the plain index vectors.  Compiled
 with the address and undefined-behaviour sanitizers, so it also sweeps the layerizer for memory
 errors.  No GPU needed."""
