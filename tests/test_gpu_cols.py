@@ -1,6 +1,7 @@
-"""The persistent kernels at the edges of their runs (GPU): layers of 1 to 5000 rows around the chunk and block sizes, rows of
-1, 2, 3-4, 5-8 and up to 60 children, literals with thousands of parents, batches of 1 and 257, impossible and certain
-literals; against the oracle, in the three semirings, with gradients."""
+"""The persistent kernels (GPU) against the oracle, in the three semirings, with gradients: runs of every kind at the edges of
+their chunks, quarters and blocks (EDGES; tests/test_host_cols.py checks on the host that these circuits have such runs),
+circuits that merge to a few hundred gates, rows of 1 to 60 children, literals with thousands of parents, one and two columns
+per workgroup, impossible and certain literals."""
 import numpy as np
 import pytest
 
@@ -38,11 +39,72 @@ FANS = {"one": lambda r: 1, "two": lambda r: 1 + int(r.integers(2)), "few": lamb
         "eight": lambda r: 1 + int(r.integers(8)), "long": lambda r: 1 + int(r.integers(60)) if r.random() < 0.1 else 1}
 
 
+# (number of variables, layers from the bottom up: gates, times every node below is a child, gates with further random children and
+# how many of those)
+EDGES = {
+    "wide": (8224, [(16385, 1, 0, 0), (4161, 1, 0, 0), (8321, 2, 0, 0), (8321, 2, 0, 0), (8321, 2, 0, 0), (8256, 2, 0, 0)]),
+    "wide_odd": (8192, [(16383, 1, 0, 0), (16383, 1, 0, 0), (4223, 1, 0, 0), (8255, 2, 0, 0), (4161, 2, 0, 0), (4223, 3, 0, 0),
+                        (4161, 3, 0, 0), (4223, 3, 0, 0)]),
+    "long": (100, [(1999, 10, 1500, 40), (1983, 1, 1900, 50), (1951, 1, 0, 0), (129, 1, 0, 0)]),
+    "two_columns": (2500, [(10239, 3, 0, 0), (8193, 1, 0, 0), (8193, 2, 0, 0), (8193, 2, 0, 0), (9025, 2, 1500, 20), (7743, 1, 1400, 18),
+                           (4161, 1, 0, 0), (4097, 3, 0, 0)]),
+}
+
+
+def edge_circuit(name):
+    """Alternating AND / OR layers of exactly these sizes (build with no_merge)"""
+    rng = np.random.default_rng(1)
+    num_vars, layers = EDGES[name]
+    types, lits, kids = [0] * (2 * num_vars), [s * (v + 1) for v in range(num_vars) for s in (1, -1)], [[] for _ in range(2 * num_vars)]
+    first, m = 0, 2 * num_vars
+    for depth, (n, times, long_gates, more) in enumerate(layers):
+        at = len(types)
+        shares = np.array_split(np.concatenate([rng.permutation(m) for _ in range(times)]), n)
+        for i in range(n):
+            c = {int(x) for x in shares[i]}
+            if i < long_gates:
+                c |= {int(x) for x in rng.permutation(m)[:more]}
+            types.append(1 if depth % 2 == 0 else 2)
+            lits.append(0)
+            kids.append(sorted(first + x for x in c))
+        first, m = at, n
+    ptr = np.concatenate([[0], np.cumsum([len(k) for k in kids])]).astype(np.int64)
+    idx = np.array([x for k in kids for x in k], dtype=np.int32)
+    return Circuit(num_vars, np.array(types, np.uint8), np.array(lits, np.int32), ptr, idx, np.arange(first, first + m, dtype=np.int32))
+
+
+@pytest.mark.parametrize("name,batch,zeros,cap,first", [
+    ("wide", 2, 0.02, 0, 1), ("wide_odd", 1, 0.02, 0, 1), ("long", 3, 0.004, 0, 1), ("long", 258, 0.004, 0, 1), ("two_columns", 2, 0.01, 0, 1),
+    ("two_columns", 257, 0.01, 0, 1), ("two_columns", 3, 0.01, 9100, 3), ("two_columns", 300, 0.01, 9100, 3), ("long", 5, 0.004, 1990, 3),
+    ("wide_odd", 2, 0.02, 8300, 4)])
+def test_runs_at_their_edges(name, batch, zeros, cap, first):
+    import paper_2410_11415_amd as klay
+    rng = np.random.default_rng(batch)
+    c = edge_circuit(name)
+    k = klay.Circuit(*c.arrays(), device=0, no_merge=True, tail_rows_cap=cap)
+    assert k.info()["num_nodes"] == c.num_nodes and k.info()["tail_first_layer"] == first
+    p = rng.uniform(0.5, 0.9, size=(batch, c.num_vars))
+    u = rng.random(p.shape)
+    p[u < zeros], p[u > 1 - zeros / 2] = 0.0, 1.0          # products with no, one and several zero children
+    dout = rng.normal(size=(batch, c.roots.shape[0])).astype(np.float32)
+    for semiring in (LOG, REAL, MAXLOG):
+        with np.errstate(divide="ignore"):
+            w = as_inputs(p, semiring != REAL)
+        d = None if semiring == MAXLOG else dout
+        out, grad = gpu_eval(k, w, semiring, d)
+        ref, rgrad = oracle_eval(c, w, semiring, d, or_levels=k.num_layers // 2)
+        (assert_real_close if semiring == REAL else assert_log_close)(out, ref, "values")
+        if d is not None:
+            assert_grad_close(grad, rgrad, "gradients", real=semiring == REAL)
+    k.close()
+
+
 @pytest.mark.parametrize("widths,fan,batch", [
     ((1, 1), "two", 1), ((63, 64, 65, 3), "two", 3), ((64, 128, 129, 127), "few", 2), ((255, 256, 257, 5), "eight", 257),
     ((1023, 1024, 1025, 40), "one", 5), ((1025, 511, 513, 9), "two", 2), ((2049, 2047, 300, 2), "few", 3), ((5000, 3000, 700, 64), "long", 2),
 ])
 def test_layers_around_chunk_and_block_sizes(widths, fan, batch):
+    """(gates that name the same children merge and gates without a parent go: a few hundred rows in the widest layer at most)"""
     import torch
     import paper_2410_11415_amd as klay
     rng = np.random.default_rng(len(widths) * 1000 + widths[0])
