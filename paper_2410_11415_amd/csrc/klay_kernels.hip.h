@@ -1173,15 +1173,23 @@ __device__ __forceinline__ void col_move(const float* values, int n, float* __re
     }
     if (whole + lane < n) to[whole + lane] = values[whole + lane];
 }
-// (two columns, T floats apart, `columns` of them there)
+// (two columns, T floats apart, `columns` of them there; also 16 bytes a lane and column: with a float a lane the wave took
+// longer than the others took for layers of short rows, 131000 nodes in 48 layers forward at B = 400: 141 us)
 __device__ __forceinline__ void col_move(const float* values, int n, float* __restrict__ to, int T, int columns) {
     if (columns < 0) { col_move(values, n, to); return; }
-    const Float2* pairs = reinterpret_cast<const Float2*>(values);
+    typedef float f4u __attribute__((ext_vector_type(4), aligned(4)));
+    const int lane = threadIdx.x & 63;
+    const int whole = n / 4 * 4;
+    float* second = to + (columns > 1 ? T : 0);           // (a second column that is not there: the first one again)
 #pragma unroll 4
-    for (int i = threadIdx.x & 63; i < n; i += 64) {
-        const Float2 v = pairs[i];
-        to[i] = v.x;
-        if (columns > 1) to[(size_t)T + i] = v.y;
+    for (int i = lane * 4; i < whole; i += 256) {
+        const float4 a = *reinterpret_cast<const float4*>(values + 2 * i), b = *reinterpret_cast<const float4*>(values + 2 * i + 4);
+        *reinterpret_cast<f4u*>(to + i) = f4u{a.x, a.z, b.x, b.z};
+        *reinterpret_cast<f4u*>(second + i) = f4u{a.y, a.w, b.y, b.w};
+    }
+    if (whole + lane < n) {
+        to[whole + lane] = values[2 * (whole + lane)];
+        second[whole + lane] = values[2 * (whole + lane) + 1];
     }
 }
 
