@@ -1627,6 +1627,7 @@ __global__ __launch_bounds__(kColThreads) void col_bwd_kernel(const ColLayer* __
         f4u own[kColOwn<CT>][CT];
 #pragma unroll
         for (int i = 0; i < kColOwn<CT>; ++i) {
+            if (i > 0 && 4 * i * kColThreads >= own_n) continue;           // (the same for all threads)
             const int at = 4 * ((int)threadIdx.x + i * kColThreads), back = own_n - 4 < 0 ? 0 : own_n - 4;
             const float* from = tbc + own_at + (at < back ? at : at < own_n ? back : 0);
 #pragma unroll
@@ -1640,6 +1641,7 @@ __global__ __launch_bounds__(kColThreads) void col_bwd_kernel(const ColLayer* __
         // the adjoints above are done with: their array takes the next step's own values
 #pragma unroll
         for (int i = 0; i < kColOwn<CT>; ++i) {
+            if (i > 0 && 4 * i * kColThreads >= own_n) continue;
             const int at = 4 * ((int)threadIdx.x + i * kColThreads), back = own_n - 4 < 0 ? 0 : own_n - 4;
             float* slot = reinterpret_cast<float*>(above + kColSlots + (at + 4 <= own_n ? at : back));
             if (at + 4 <= own_n) {
