@@ -866,7 +866,7 @@ size_t enable_tail_lds() {
         hipError_t e = hipSuccess;
         for (const void* kernel : {reinterpret_cast<const void*>(&klay::col_fwd_kernel<1>), reinterpret_cast<const void*>(&klay::col_bwd_kernel<1, false>),
                                    reinterpret_cast<const void*>(&klay::col_bwd_kernel<1, true>), reinterpret_cast<const void*>(&klay::col_bwd_kernel<2, true>),
-                                   reinterpret_cast<const void*>(&klay::col_fwd_kernel<2>), reinterpret_cast<const void*>(&klay::col_bwd_kernel<2, false>)})
+                                   reinterpret_cast<const void*>(&klay::col_fwd_kernel<2>), reinterpret_cast<const void*>(&klay::col_fwd_kernel<4>), reinterpret_cast<const void*>(&klay::col_bwd_kernel<4, false>), reinterpret_cast<const void*>(&klay::col_bwd_kernel<4, true>), reinterpret_cast<const void*>(&klay::col_bwd_kernel<2, false>)})
             if (e == hipSuccess) e = hipFuncSetAttribute(kernel, hipFuncAttributeMaxDynamicSharedMemorySize, bytes);
         if (e == hipSuccess) return (size_t)bytes;
         (void)hipGetLastError();
@@ -874,12 +874,15 @@ size_t enable_tail_lds() {
     return 0;
 }
 
-// Columns per workgroup: two once there are more columns than compute units and two fit the LDS (a column of its own
-// round would wait for the same dependent steps again; two cost little more than one).
-int tail_columns(int B, const int64_t (&size)[2], size_t lds_bytes) {
-    // (the reverse kernel holds kColOwn<2> times four values per thread of a layer)
-    return B > 256 && std::max(size[0], size[1]) <= 4 * klay::kColOwn<2> * klay::kColThreads &&
-                   (size_t)(size[0] + size[1]) * 2 * sizeof(float) <= lds_bytes ? 2 : 1;
+// Columns per workgroup: two once there are more columns than compute units, four once there are more than twice as many, as
+// far as they fit the LDS (a column of its own round would wait for the same dependent steps again; two cost little more
+// than one).
+int tail_columns(int B, const int64_t (&size)[2], size_t lds_bytes, bool reverse) {
+    // (the reverse kernel holds kColOwn<ct> times four values per thread of a layer)
+    const int64_t widest = reverse ? std::max(size[0], size[1]) : 0;
+    auto fits = [&](int ct, int own) { return widest <= 4 * own * klay::kColThreads && (size_t)(size[0] + size[1]) * ct * sizeof(float) <= lds_bytes; };
+    if (B > 512 && fits(4, klay::kColOwn<4>)) return 4;
+    return B > 256 && fits(2, klay::kColOwn<2>) ? 2 : 1;
 }
 
 // The column-major value buffer of a persistent forward launch: `T` floats a column.  `at`: entry of the layer below
@@ -915,8 +918,8 @@ void launch_tail_fwd(const klay_circuit* c, const TailChoice& t, const float* ac
     }
     int64_t size[2];
     tail_lds(p, t.first - 1, t.first - 1, size);
-    const int ct = tail_columns(B, size, c->tail_lds_bytes);
-    hipLaunchKernelGGL((ct == 2 ? klay::col_fwd_kernel<2> : klay::col_fwd_kernel<1>), dim3((unsigned)((B + ct - 1) / ct)), dim3(klay::kColThreads),
+    const int ct = tail_columns(B, size, c->tail_lds_bytes, false);
+    hipLaunchKernelGGL((ct == 4 ? klay::col_fwd_kernel<4> : ct == 2 ? klay::col_fwd_kernel<2> : klay::col_fwd_kernel<1>), dim3((unsigned)((B + ct - 1) / ct)), dim3(klay::kColThreads),
                        (size_t)(size[0] + size[1]) * ct * sizeof(float), s, c->d_tail + (t.first - p.tail_first), p.num_layers - t.first + 1, t.first & 1, c->d_blocks[0], c->n_blocks[0], c->d_tables, start,
                        nb, start_T, B, ld, semiring, (int)size[0], keep ? tb : nullptr, (int)buf.T, leaf, c->d_root_pos, p.num_roots, out);
 }
@@ -929,7 +932,7 @@ void launch_tail_bwd(const klay_circuit* c, int last, int last_at, const float* 
     const int L = p.num_layers;
     int64_t size[2];
     tail_lds(p, last, L, size);
-    const int ct = tail_columns(B, size, c->tail_lds_bytes);
+    const int ct = tail_columns(B, size, c->tail_lds_bytes, true);
     // The own values of the first steps are loaded at once: as many steps as fit behind the rows of one of the two arrays,
     // into LDS that only the wider layers further down need, or behind both arrays, up to all that a compute unit has (a
     // workgroup takes one anyway).
@@ -951,8 +954,8 @@ void launch_tail_bwd(const klay_circuit* c, int last, int last_at, const float* 
         }
         cached = L - l + 1;
     }
-    auto* kernel = real ? (ct == 2 ? klay::col_bwd_kernel<2, true> : klay::col_bwd_kernel<1, true>)
-                        : (ct == 2 ? klay::col_bwd_kernel<2, false> : klay::col_bwd_kernel<1, false>);
+    auto* kernel = real ? (ct == 4 ? klay::col_bwd_kernel<4, true> : ct == 2 ? klay::col_bwd_kernel<2, true> : klay::col_bwd_kernel<1, true>)
+                        : (ct == 4 ? klay::col_bwd_kernel<4, false> : ct == 2 ? klay::col_bwd_kernel<2, false> : klay::col_bwd_kernel<1, false>);
     hipLaunchKernelGGL(kernel, dim3((unsigned)((B + ct - 1) / ct)), dim3(klay::kColThreads),
                        (size_t)words * ct * sizeof(float), s, c->d_tail + (L - p.tail_first), L - last, last_at, L & 1, c->d_blocks[1], c->n_blocks[1], c->d_tables, dout, c->d_top_ptr,
                        c->d_top_root, p.num_roots, B, ld, (int)size[0], cached, cache_at, tb, T, top_multi, res, real ? *real : klay::ColReal{});

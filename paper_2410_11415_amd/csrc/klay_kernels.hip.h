@@ -948,9 +948,8 @@ struct ColRun {
 };
 
 // The values of a node in the CT columns of a workgroup.
-template <int CT> struct ColValue;
+template <int CT> struct ColValue { typedef float T __attribute__((ext_vector_type(CT))); };
 template <> struct ColValue<1> { using T = float; };
-template <> struct ColValue<2> { typedef float T __attribute__((ext_vector_type(2))); };
 
 // f of each column
 template <class F>
@@ -959,37 +958,54 @@ template <class F>
 __device__ __forceinline__ float each(F f, float a, float b) { return f(a, b); }
 template <class F>
 __device__ __forceinline__ float each(F f, float a, float b, float c) { return f(a, b, c); }
-using Float2 = ColValue<2>::T;
-template <class F>
-__device__ __forceinline__ Float2 each(F f, Float2 a) { return Float2{f(a.x), f(a.y)}; }
-template <class F>
-__device__ __forceinline__ Float2 each(F f, Float2 a, Float2 b) { return Float2{f(a.x, b.x), f(a.y, b.y)}; }
-template <class F>
-__device__ __forceinline__ Float2 each(F f, Float2 a, Float2 b, Float2 c) { return Float2{f(a.x, b.x, c.x), f(a.y, b.y, c.y)}; }
-__device__ __forceinline__ Float2 term_exp(Float2 x) { return each([](float a) { return term_exp(a); }, x); }
-__device__ __forceinline__ Float2 flog(Float2 x) { return each([](float a) { return flog(a); }, x); }
-__device__ __forceinline__ Float2 finite(Float2 x) { return each([](float a) { return finite(a); }, x); }
-__device__ __forceinline__ Float2 max3(Float2 a, Float2 b, Float2 c) { return each([](float x, float y, float z) { return max3(x, y, z); }, a, b, c); }
-__device__ __forceinline__ Float2 bigger(Float2 a, Float2 b) { return each([](float x, float y) { return bigger(x, y); }, a, b); }
-__device__ __forceinline__ float apart(float a, float b) { return fabsf(a - b); }
-__device__ __forceinline__ Float2 apart(Float2 a, Float2 b) { return each([](float x, float y) { return apart(x, y); }, a, b); }
-__device__ __forceinline__ float muladd(float a, float b, float c) { return fmaf(a, b, c); }
-__device__ __forceinline__ Float2 muladd(Float2 a, Float2 b, Float2 c) { return each([](float x, float y, float z) { return fmaf(x, y, z); }, a, b, c); }
+template <class F, class V, int N = (int)(sizeof(V) / sizeof(float)), class = decltype(V().x)>
+__device__ __forceinline__ V each(F f, V a) {
+    V r;
+#pragma unroll
+    for (int i = 0; i < N; ++i) r[i] = f(a[i]);
+    return r;
+}
+template <class F, class V, int N = (int)(sizeof(V) / sizeof(float)), class = decltype(V().x)>
+__device__ __forceinline__ V each(F f, V a, V b) {
+    V r;
+#pragma unroll
+    for (int i = 0; i < N; ++i) r[i] = f(a[i], b[i]);
+    return r;
+}
+template <class F, class V, int N = (int)(sizeof(V) / sizeof(float)), class = decltype(V().x)>
+__device__ __forceinline__ V each(F f, V a, V b, V c) {
+    V r;
+#pragma unroll
+    for (int i = 0; i < N; ++i) r[i] = f(a[i], b[i], c[i]);
+    return r;
+}
+template <class V, class = decltype(V().x)>
+__device__ __forceinline__ V term_exp(V x) { return each([](float a) { return term_exp(a); }, x); }
+template <class V, class = decltype(V().x)>
+__device__ __forceinline__ V flog(V x) { return each([](float a) { return flog(a); }, x); }
+template <class V, class = decltype(V().x)>
+__device__ __forceinline__ V finite(V x) { return each([](float a) { return finite(a); }, x); }
+template <class V, class = decltype(V().x)>
+__device__ __forceinline__ V max3(V a, V b, V c) { return each([](float x, float y, float z) { return max3(x, y, z); }, a, b, c); }
+template <class V, class = decltype(V().x)>
+__device__ __forceinline__ V bigger(V a, V b) { return each([](float x, float y) { return bigger(x, y); }, a, b); }
+template <class V>
+__device__ __forceinline__ V apart(V a, V b) { return each([](float x, float y) { return fabsf(x - y); }, a, b); }
+template <class V>
+__device__ __forceinline__ V muladd(V a, V b, V c) { return each([](float x, float y, float z) { return fmaf(x, y, z); }, a, b, c); }
 
 template <class V>
 __device__ __forceinline__ V col_at(const V* values, uint32_t slot) { return values[slot]; }
 
 // lane i's value from lane i ^ (1 << step), for reductions in which the lanes below that distance already agree
 template <int STEP>
-__device__ __forceinline__ Float2 fly(Float2 x);
-template <int STEP>
 __device__ __forceinline__ float fly(float x) {
     constexpr int kCtrl = STEP == 0 ? 0xB1 : STEP == 1 ? 0x4E : STEP == 2 ? 0x141 : 0x140;      // quad_perm, half mirror, mirror
     if (STEP < 4) return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(x), kCtrl, 0xF, 0xF, true));
     return __shfl_xor(x, 1 << STEP);
 }
-template <int STEP>
-__device__ __forceinline__ Float2 fly(Float2 x) { return Float2{fly<STEP>(x.x), fly<STEP>(x.y)}; }
+template <int STEP, class V, class = decltype(V().x)>
+__device__ __forceinline__ V fly(V x) { return each([](float a) { return fly<STEP>(a); }, x); }
 
 template <int OP, class V>
 __device__ __forceinline__ V col_join(V a, V b) {
@@ -1080,13 +1096,26 @@ __device__ __forceinline__ void col_fwd_short(ColWalk& walk, const V* below, V* 
     Line w0, w1;
     for (; rows >= 256 * N; rows -= 256 * N, out += 256 * N) {
         walk.block(w0, w1);
-        V v[4 * N];
-        col_rows<OP, KIND>(below, w0.x, w0.y, v);
-        col_rows<OP, KIND>(below, w0.z, w0.w, v + N);
-        col_rows<OP, KIND>(below, w1.x, w1.y, v + 2 * N);
-        col_rows<OP, KIND>(below, w1.z, w1.w, v + 3 * N);
+        if constexpr (sizeof(V) <= 8) {
+            V v[4 * N];
+            col_rows<OP, KIND>(below, w0.x, w0.y, v);
+            col_rows<OP, KIND>(below, w0.z, w0.w, v + N);
+            col_rows<OP, KIND>(below, w1.x, w1.y, v + 2 * N);
+            col_rows<OP, KIND>(below, w1.z, w1.w, v + 3 * N);
 #pragma unroll
-        for (int i = 0; i < 4 * N; ++i) out[64 * i] = v[i];
+            for (int i = 0; i < 4 * N; ++i) out[64 * i] = v[i];
+        } else {
+            // (four columns: half a block, so that the values fit the registers)
+            V v[2 * N];
+            col_rows<OP, KIND>(below, w0.x, w0.y, v);
+            col_rows<OP, KIND>(below, w0.z, w0.w, v + N);
+#pragma unroll
+            for (int i = 0; i < 2 * N; ++i) out[64 * i] = v[i];
+            col_rows<OP, KIND>(below, w1.x, w1.y, v);
+            col_rows<OP, KIND>(below, w1.z, w1.w, v + N);
+#pragma unroll
+            for (int i = 0; i < 2 * N; ++i) out[64 * (2 * N + i)] = v[i];
+        }
     }
     if (rows > 0) {
         walk.block(w0, w1);
@@ -1173,23 +1202,30 @@ __device__ __forceinline__ void col_move(const float* values, int n, float* __re
     }
     if (whole + lane < n) to[whole + lane] = values[whole + lane];
 }
-// (two columns, T floats apart, `columns` of them there; also 16 bytes a lane and column: with a float a lane the wave took
-// longer than the others took for layers of short rows, 131000 nodes in 48 layers forward at B = 400: 141 us)
+// (CT columns, T floats apart, `columns` of them there; also 16 bytes a lane and column: with a float a lane the wave took
+// longer than the others took for layers of short rows, 131000 nodes in 48 layers forward at B = 400: 141 us, so 106)
+template <int CT>
 __device__ __forceinline__ void col_move(const float* values, int n, float* __restrict__ to, int T, int columns) {
-    if (columns < 0) { col_move(values, n, to); return; }
-    typedef float f4u __attribute__((ext_vector_type(4), aligned(4)));
-    const int lane = threadIdx.x & 63;
-    const int whole = n / 4 * 4;
-    float* second = to + (columns > 1 ? T : 0);           // (a second column that is not there: the first one again)
-#pragma unroll 4
-    for (int i = lane * 4; i < whole; i += 256) {
-        const float4 a = *reinterpret_cast<const float4*>(values + 2 * i), b = *reinterpret_cast<const float4*>(values + 2 * i + 4);
-        *reinterpret_cast<f4u*>(to + i) = f4u{a.x, a.z, b.x, b.z};
-        *reinterpret_cast<f4u*>(second + i) = f4u{a.y, a.w, b.y, b.w};
-    }
-    if (whole + lane < n) {
-        to[whole + lane] = values[2 * (whole + lane)];
-        second[whole + lane] = values[2 * (whole + lane) + 1];
+    if constexpr (CT == 1) {
+        col_move(values, n, to);
+    } else {
+        typedef float f4u __attribute__((ext_vector_type(4), aligned(4)));
+        const int lane = threadIdx.x & 63;
+        const int whole = n / 4 * 4;
+        float* column[CT];                                // (one that is not there: the last one again)
+#pragma unroll
+        for (int c = 0; c < CT; ++c) column[c] = to + (size_t)(c < columns ? c : columns - 1) * T;
+#pragma unroll (8 / CT)
+        for (int i = lane * 4; i < whole; i += 256) {
+            float4 v[CT];
+#pragma unroll
+            for (int j = 0; j < CT; ++j) v[j] = *reinterpret_cast<const float4*>(values + CT * i + 4 * j);
+            const float* x = reinterpret_cast<const float*>(v);
+#pragma unroll
+            for (int c = 0; c < CT; ++c) *reinterpret_cast<f4u*>(column[c] + i) = f4u{x[c], x[CT + c], x[2 * CT + c], x[3 * CT + c]};
+        }
+        if (whole + lane < n)
+            for (int c = 0; c < CT; ++c) column[c][whole + lane] = values[CT * (whole + lane) + c];
     }
 }
 
@@ -1288,7 +1324,7 @@ __global__ __launch_bounds__(kColThreads) void col_fwd_kernel(const ColLayer* __
         if (wave == kColFwdWaves) {
             // the wave that keeps the values, a layer behind the others (in a wave that computes, the wait for the next
             // lines would wait for the stores as well)
-            if (tbc && t > 0) col_move(reinterpret_cast<const float*>(below + kColSlots), first[t - 1].n, tbc + first[t - 1].at, T, CT == 1 ? -1 : columns);
+            if (tbc && t > 0) col_move<CT>(reinterpret_cast<const float*>(below + kColSlots), first[t - 1].n, tbc + first[t - 1].at, T, columns);
         } else if (is_and) {
             if (log_domain) col_fwd_layer<OP_SUM>(walk, below, here);
             else col_fwd_layer<OP_PROD>(walk, below, here);
@@ -1298,7 +1334,7 @@ __global__ __launch_bounds__(kColThreads) void col_fwd_kernel(const ColLayer* __
         V* tmp = below; below = here; here = tmp;
     }
     __syncthreads();
-    if (wave == kColFwdWaves && tbc) col_move(reinterpret_cast<const float*>(below + kColSlots), first[n_layers - 1].n, tbc + first[n_layers - 1].at, T, CT == 1 ? -1 : columns);
+    if (wave == kColFwdWaves && tbc) col_move<CT>(reinterpret_cast<const float*>(below + kColSlots), first[n_layers - 1].n, tbc + first[n_layers - 1].at, T, columns);
     // roots: the top layer is in LDS
     for (int r = threadIdx.x; r < R; r += kColThreads) {
         const float* slot = reinterpret_cast<const float*>(below + kColSlots + root_pos[r]);
@@ -1351,8 +1387,10 @@ struct ColRepair {
     const int32_t *ptr, *child;       // index vectors of the layer, by parent
     const float* values;              // values of the layer below, first column; child c of column i at values[c * by_child + i * by_column]
     size_t by_child, by_column;
+    int last;                         // column (one past it: that one again)
     __device__ __forceinline__ float row(float g, float own, int r, int column) const {
         if (own != 0.0f) return premultiply(g, own);
+        if (column > last) column = last;
         float q = 1.0f;
         int zeros = 0;
         for (int j = ptr[r]; j < ptr[r + 1]; ++j) {
@@ -1371,8 +1409,14 @@ __device__ __forceinline__ V col_finish(const ColSum<MODE, V>& s, V own, bool fl
     if constexpr (MODE == kLogAnd) return flagged ? each([](float a, float b) { return encode_h(a, b); }, s.a, own) : s.a;
     else if constexpr (MODE == kRealAnd) return each([](float a, float b, float n) { return n != 0.0f ? a / n : b; }, s.a, s.b, own);
     else if constexpr (MODE == kRealOr) {
-        if constexpr (sizeof(V) == 4) return repair.row(s.a, own, r, 0);
-        else return V{repair.row(s.a.x, own.x, r, 0), repair.row(s.a.y, own.y, r, 1)};
+        if constexpr (sizeof(V) == sizeof(float)) {
+            return repair.row(s.a, own, r, 0);
+        } else {
+            V p;
+#pragma unroll
+            for (int c = 0; c < (int)(sizeof(V) / sizeof(float)); ++c) p[c] = repair.row(s.a[c], own[c], r, c);
+            return p;
+        }
     } else return s.a;
 }
 
@@ -1497,37 +1541,48 @@ struct ColReal {
 // of OR nodes with more than one child are kept in the one-gather form throughout, also on the way out; top_multi
 // (or null) flags such nodes of the top layer for the seed.
 // (tb is not __restrict__: a load known to be invariant would be moved down past the barrier to its use.)
-template <int CT> constexpr int kColOwn = CT == 1 ? (int)((kTailRowsCap + 4 * kColThreads - 1) / (4 * kColThreads)) : 3;      // (two columns: where no layer is longer)
+// (two and four columns: where no layer is longer)
+template <int CT> constexpr int kColOwn = CT == 1 ? (int)((kTailRowsCap + 4 * kColThreads - 1) / (4 * kColThreads)) : CT == 2 ? 3 : 1;
 
-// n node values of the CT columns of a workgroup (the second `second` floats after the first) into LDS, 16-byte aligned,
-// sixteen values of a column per thread in flight
+// Where the values of the CT columns of a workgroup are in the column-major buffer: T floats apart, `columns` of them there (one
+// that is not: the last one again).
+struct ColColumns {
+    int T, columns;
+    __device__ __forceinline__ int operator()(int c) const { return (c < columns ? c : columns - 1) * T; }
+};
+
+// four rows of the columns to their slots
+typedef float Float4u __attribute__((ext_vector_type(4), aligned(4)));
 template <int CT, class V>
-__device__ __forceinline__ void col_load(V* to, const float* from, int second, int n) {
-    typedef float f4u __attribute__((ext_vector_type(4), aligned(4)));
+__device__ __forceinline__ void col_put4(V* to, const Float4u (&v)[CT]) {
+    float x[4 * CT];
+#pragma unroll
+    for (int j = 0; j < 4; ++j)
+#pragma unroll
+        for (int c = 0; c < CT; ++c) x[j * CT + c] = v[c][j];
+#pragma unroll
+    for (int i = 0; i < CT; ++i) reinterpret_cast<float4*>(to)[i] = make_float4(x[4 * i], x[4 * i + 1], x[4 * i + 2], x[4 * i + 3]);
+}
+
+// n node values of the columns into LDS, 16-byte aligned, sixteen values of a column per thread in flight
+template <int CT, class V>
+__device__ __forceinline__ void col_load(V* to, const float* from, ColColumns column, int n) {
+    constexpr int kFlight = CT == 4 ? 2 : 4;
     const int whole = n / 4 * 4;
-    for (int i0 = 4 * (int)threadIdx.x; i0 < whole; i0 += 16 * kColThreads) {
-        f4u v[4][CT];
+    for (int i0 = 4 * (int)threadIdx.x; i0 < whole; i0 += 4 * kFlight * kColThreads) {
+        Float4u v[kFlight][CT];
 #pragma unroll
-        for (int j = 0; j < 4; ++j) {
+        for (int j = 0; j < kFlight; ++j) {
             const int i = i0 + 4 * j * kColThreads < whole ? i0 + 4 * j * kColThreads : i0;
 #pragma unroll
-            for (int c = 0; c < CT; ++c) v[j][c] = *reinterpret_cast<const f4u*>(from + (c ? second : 0) + i);
+            for (int c = 0; c < CT; ++c) v[j][c] = *reinterpret_cast<const Float4u*>(from + column(c) + i);
         }
 #pragma unroll
-        for (int j = 0; j < 4; ++j) {
-            const int i = i0 + 4 * j * kColThreads < whole ? i0 + 4 * j * kColThreads : i0;
-            float* slot = reinterpret_cast<float*>(to + i);
-            if constexpr (CT == 1) {
-                *reinterpret_cast<float4*>(slot) = make_float4(v[j][0].x, v[j][0].y, v[j][0].z, v[j][0].w);
-            } else {
-                *reinterpret_cast<float4*>(slot) = make_float4(v[j][0].x, v[j][CT - 1].x, v[j][0].y, v[j][CT - 1].y);
-                *reinterpret_cast<float4*>(slot + 4) = make_float4(v[j][0].z, v[j][CT - 1].z, v[j][0].w, v[j][CT - 1].w);
-            }
-        }
+        for (int j = 0; j < kFlight; ++j) col_put4<CT>(to + (i0 + 4 * j * kColThreads < whole ? i0 + 4 * j * kColThreads : i0), v[j]);
     }
     const int rest = whole + (int)threadIdx.x;
     if (rest < n)
-        for (int c = 0; c < CT; ++c) reinterpret_cast<float*>(to + rest)[c] = from[(c ? second : 0) + rest];
+        for (int c = 0; c < CT; ++c) reinterpret_cast<float*>(to + rest)[c] = from[column(c) + rest];
 }
 
 template <int CT, bool REAL>
@@ -1547,13 +1602,19 @@ __global__ __launch_bounds__(kColThreads) void col_bwd_kernel(const ColLayer* __
     const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
     const int col0 = (int)blockIdx.x * CT, columns = B - col0 < CT ? B - col0 : CT;      // (a column that is not there repeats the last one)
     const float* tbc = tb + (size_t)col0 * T;
-    const int second = columns > 1 ? T : 0;               // where the second column's values are, from the first one's
+    const ColColumns column{T, columns};
     ColWalk walk;
     walk.start(blocks + (size_t)top->bwd_block[wave] * 128 + lane, tables + (size_t)top->bwd_table[wave] * kDescTable + lane);
     if (gridDim.x >= 64) col_touch(blocks, n_blocks);
     auto value_at = [&](int at) {
-        if constexpr (CT == 1) return tbc[at];
-        else return V{tbc[at], tbc[second + at]};
+        if constexpr (CT == 1) {
+            return tbc[at];
+        } else {
+            V v;
+#pragma unroll
+            for (int c = 0; c < CT; ++c) v[c] = tbc[column(c) + at];
+            return v;
+        }
     };
     // own values of the rows of step t (the t-th layer below the top one): how many and where
     auto own_of = [&](int t, int& n, int& at) {
@@ -1572,7 +1633,8 @@ __global__ __launch_bounds__(kColThreads) void col_bwd_kernel(const ColLayer* __
             const bool stored = depth + 1 < real.lowest;       // the layer below that one is in tb, otherwise in rows
             r.values = stored ? tbc + top[-1 - depth].at : (depth < real.lowest ? real.rows : real.low_rows) + col0;
             r.by_child = stored ? 1 : (size_t)ld;
-            r.by_column = stored ? (size_t)second : (columns > 1 ? 1 : 0);
+            r.by_column = stored ? (size_t)T : 1;
+            r.last = columns - 1;
         }
         return r;
     };
@@ -1580,15 +1642,15 @@ __global__ __launch_bounds__(kColThreads) void col_bwd_kernel(const ColLayer* __
     auto leaf_values = [&](V* to) {
         for (int i = threadIdx.x; i < res.n_last; i += kColThreads) {
             const float* from = real.rows + (size_t)i * ld + col0;
-            if constexpr (CT == 1) to[kColSlots + i] = from[0];
-            else to[kColSlots + i] = V{from[0], from[columns > 1 ? 1 : 0]};
+#pragma unroll
+            for (int c = 0; c < CT; ++c) reinterpret_cast<float*>(to + kColSlots + i)[c] = from[c < columns ? c : columns - 1];
         }
     };
     int cache_low = 0;
     if (cached > 0) {
         // the cached layers follow one another in tb
         cache_low = top[-cached].at;
-        col_load<CT>(cache, tbc + cache_low, second, top_at - cache_low);
+        col_load<CT>(cache, tbc + cache_low, column, top_at - cache_low);
     } else {
         int n, at;
         own_of(0, n, at);
@@ -1599,8 +1661,14 @@ __global__ __launch_bounds__(kColThreads) void col_bwd_kernel(const ColLayer* __
         V acc = V(0.0f);
         for (int t = top_ptr[i]; t < top_ptr[i + 1]; ++t) {
             const float* from = dout + (size_t)col0 * R + top_root[t];
-            if constexpr (CT == 1) acc += from[0];
-            else acc += V{from[0], from[columns > 1 ? R : 0]};
+            if constexpr (CT == 1) {
+                acc += from[0];
+            } else {
+                V g;
+#pragma unroll
+                for (int c = 0; c < CT; ++c) g[c] = from[(size_t)(c < columns ? c : columns - 1) * R];
+                acc += g;
+            }
         }
         if (REAL && top_is_and) {
             ColSum<kRealOr, V> g;
@@ -1623,15 +1691,14 @@ __global__ __launch_bounds__(kColThreads) void col_bwd_kernel(const ColLayer* __
         own_of(t + 1, own_n, own_at);
         // (the last rows are read, and written, by a lane that steps back to them; a layer of less than four rows reads
         // up to three floats past its own, still inside the workspace)
-        typedef float f4u __attribute__((ext_vector_type(4), aligned(4)));
-        f4u own[kColOwn<CT>][CT];
+        Float4u own[kColOwn<CT>][CT];
 #pragma unroll
         for (int i = 0; i < kColOwn<CT>; ++i) {
             if (i > 0 && 4 * i * kColThreads >= own_n) continue;           // (the same for all threads)
             const int at = 4 * ((int)threadIdx.x + i * kColThreads), back = own_n - 4 < 0 ? 0 : own_n - 4;
             const float* from = tbc + own_at + (at < back ? at : at < own_n ? back : 0);
 #pragma unroll
-            for (int c = 0; c < CT; ++c) own[i][c] = *reinterpret_cast<const f4u*>(from + (c ? second : 0));
+            for (int c = 0; c < CT; ++c) own[i][c] = *reinterpret_cast<const Float4u*>(from + column(c));
         }
         const V* owns = t < cached ? cache + (top[-1 - t].at - cache_low) - kColSlots : here;
         __syncthreads();
@@ -1643,17 +1710,14 @@ __global__ __launch_bounds__(kColThreads) void col_bwd_kernel(const ColLayer* __
         for (int i = 0; i < kColOwn<CT>; ++i) {
             if (i > 0 && 4 * i * kColThreads >= own_n) continue;
             const int at = 4 * ((int)threadIdx.x + i * kColThreads), back = own_n - 4 < 0 ? 0 : own_n - 4;
-            float* slot = reinterpret_cast<float*>(above + kColSlots + (at + 4 <= own_n ? at : back));
             if (at + 4 <= own_n) {
-                if constexpr (CT == 1) {
-                    *reinterpret_cast<float4*>(slot) = make_float4(own[i][0].x, own[i][0].y, own[i][0].z, own[i][0].w);
-                } else {
-                    *reinterpret_cast<float4*>(slot) = make_float4(own[i][0].x, own[i][CT - 1].x, own[i][0].y, own[i][CT - 1].y);
-                    *reinterpret_cast<float4*>(slot + 4) = make_float4(own[i][0].z, own[i][CT - 1].z, own[i][0].w, own[i][CT - 1].w);
-                }
+                col_put4<CT>(above + kColSlots + at, own[i]);
             } else if (at < own_n) {
+                float* slot = reinterpret_cast<float*>(above + kColSlots + back);
+#pragma unroll
                 for (int j = 0; j < 4; ++j)
                     if (back + j < own_n)
+#pragma unroll
                         for (int c = 0; c < CT; ++c) slot[j * CT + c] = own[i][c][j];
             }
         }

@@ -1,6 +1,6 @@
 """The persistent kernels (GPU) against the oracle, in the three semirings, with gradients: runs of every kind at the edges of
 their chunks, quarters and blocks (EDGES; tests/test_host_cols.py checks on the host that these circuits have such runs),
-circuits that merge to a few hundred gates, rows of 1 to 60 children, literals with thousands of parents, one and two columns
+circuits that merge to a few hundred gates, rows of 1 to 60 children, literals with thousands of parents, one, two and four columns
 per workgroup, impossible and certain literals."""
 import numpy as np
 import pytest
@@ -48,6 +48,8 @@ EDGES = {
     "long": (100, [(1999, 10, 1500, 40), (1983, 1, 1900, 50), (1951, 1, 0, 0), (129, 1, 0, 0)]),
     "two_columns": (2500, [(10239, 3, 0, 0), (8193, 1, 0, 0), (8193, 2, 0, 0), (8193, 2, 0, 0), (9025, 2, 1500, 20), (7743, 1, 1400, 18),
                            (4161, 1, 0, 0), (4097, 3, 0, 0)]),
+    "four_columns": (1200, [(4031, 3, 0, 0), (2111, 1, 0, 0), (2047, 2, 0, 0), (2049, 2, 0, 0), (3009, 3, 500, 20), (2431, 1, 450, 18),
+                            (1087, 1, 0, 0), (961, 3, 0, 0)]),
 }
 
 
@@ -75,7 +77,8 @@ def edge_circuit(name):
 
 @pytest.mark.parametrize("name,batch,zeros,cap,first", [
     ("wide", 2, 0.02, 0, 1), ("wide_odd", 1, 0.02, 0, 1), ("long", 3, 0.004, 0, 1), ("long", 258, 0.004, 0, 1), ("two_columns", 2, 0.01, 0, 1),
-    ("two_columns", 257, 0.01, 0, 1), ("two_columns", 3, 0.01, 9100, 3), ("two_columns", 300, 0.01, 9100, 3), ("long", 5, 0.004, 1990, 3),
+    ("two_columns", 257, 0.01, 0, 1), ("long", 514, 0.004, 0, 1), ("long", 1025, 0.004, 1990, 3), ("four_columns", 515, 0.01, 0, 1),
+    ("four_columns", 1027, 0.01, 3100, 3), ("four_columns", 300, 0.01, 0, 1), ("four_columns", 2, 0.01, 0, 1), ("two_columns", 3, 0.01, 9100, 3), ("two_columns", 300, 0.01, 9100, 3), ("long", 5, 0.004, 1990, 3),
     ("wide_odd", 2, 0.02, 8300, 4)])
 def test_runs_at_their_edges(name, batch, zeros, cap, first):
     import paper_2410_11415_amd as klay
@@ -217,6 +220,7 @@ def covered_stack(rng, num_vars, widths, and_extra=0.02, or_fan=2):
     ([2500] * 20 + [1300, 700], 2),                    # of some steps only: the rest a step ahead
     ([5000, 5000] + [600] * 10, 2),                    # in the part of an array that only the wide layers need
     ([6000, 6000] + [2999] * 7 + [60, 60, 20], 259),
+    ([900] * 24, 514), ([2999] * 9 + [60, 60, 20], 517),                 # four columns
 ])
 def test_own_values_wherever_the_reverse_kernel_keeps_them(widths, batch):
     import paper_2410_11415_amd as klay
