@@ -801,10 +801,12 @@ struct TailChoice {
 
 // The layers the persistent kernels take: as many as fit when `ct` columns share the LDS of a compute unit.  Up to 256
 // columns every workgroup (a column) has a compute unit of its own; beyond, the launches of the wider layers, which
-// fill the chip, are left to the ordinary kernels.
-int tail_ct(int B) {
+// fill the chip, are left to the ordinary kernels.  At most 4, as the kernels have (tail_columns).  us with 2 / 4 / 8 at most:
+// 30000 nodes in 24 layers training B = 1800 297 / 296 / 417, 100k nodes forward B = 520 182 / 152 / 152, B = 4096
+// 976 / 867 / 840, 131000 nodes in 48 layers training B = 2048 1044 / 1181 / 1293, forward B = 520 188 / 178 / 178.
+int tail_ct(int B, int most) {
     int ct = 1;
-    while (ct < 8 && (B + ct - 1) / ct > 256) ct *= 2;
+    while (ct < most && (B + ct - 1) / ct > 256) ct *= 2;
     return ct;
 }
 
@@ -812,12 +814,12 @@ int tail_ct(int B) {
 // hold the layers first .. L, and layer 0 as well
 // when the kernel starts at layer 1 and evaluates the leaf layer itself.  At least two layers,
 // otherwise a kernel of its own is not worth it.
-TailChoice choose_tail_fwd(const klay_circuit* c, int B) {
+TailChoice choose_tail(const klay_circuit* c, int ct) {
     TailChoice t;
     const klay::CircuitPlan& p = c->plan;
     const int lowest = p.tail_first;
     if (lowest <= 0 || c->tail_lds_bytes == 0) return t;
-    t.ct = tail_ct(B);
+    t.ct = ct;
     const int L = p.num_layers;
     const int64_t words = (int64_t)(c->tail_lds_bytes / sizeof(float));
     int64_t nmax = 0;
@@ -837,6 +839,8 @@ TailChoice choose_tail_fwd(const klay_circuit* c, int B) {
     return t;
 }
 
+TailChoice choose_tail_fwd(const klay_circuit* c, int B) { return choose_tail(c, tail_ct(B, 4)); }
+
 // Rows of the layer below the forward kernel's first one if that layer gets a place in the column-major buffer (where
 // the kernel reads it as one run per column, and the reverse kernel its values): where ct arrays of its length fit the
 // LDS too.  0: no place (the kernel evaluates the leaf layer itself, or reads the layer from its rows).
@@ -846,7 +850,9 @@ int64_t tail_stage_rows(const klay_circuit* c, const TailChoice& t) {
     const int64_t rows = std::max<int64_t>(nb, t.nmax);
     return (size_t)2 * (size_t)(rows + 1) * t.ct * sizeof(float) <= c->tail_lds_bytes ? nb : 0;
 }
-int64_t tail_stage_rows(const klay_circuit* c, int B) { return tail_stage_rows(c, choose_tail_fwd(c, B)); }
+// What the workspace holds for it.  (Up to 8 columns here: klay_workspace_bytes, and with it the batches that the entry point
+// with a fixed buffer takes, stay what they were before the limit of 4.)
+int64_t tail_stage_rows(const klay_circuit* c, int B) { return tail_stage_rows(c, choose_tail(c, tail_ct(B, 8))); }
 
 // floats of the two LDS arrays that hold the layers lowest .. L by turns; [0]: the one with layer `zero` in it
 void tail_lds(const klay::CircuitPlan& p, int lowest, int zero, int64_t (&size)[2]) {
@@ -876,7 +882,8 @@ size_t enable_tail_lds() {
 
 // Columns per workgroup: two once there are more columns than compute units, four once there are more than twice as many, as
 // far as they fit the LDS (a column of its own round would wait for the same dependent steps again; two cost little more
-// than one).
+// than one: 30000 nodes in 24 layers, real semiring forward, B = 1024 70 us with two and 46 with four, 14000 nodes training
+// B = 365 181 with one and 101 with two).
 int tail_columns(int B, const int64_t (&size)[2], size_t lds_bytes, bool reverse) {
     // (the reverse kernel holds kColOwn<ct> times four values per thread of a layer)
     const int64_t widest = reverse ? std::max(size[0], size[1]) : 0;
@@ -890,13 +897,14 @@ int tail_columns(int B, const int64_t (&size)[2], size_t lds_bytes, bool reverse
 struct TailBuffer {
     int64_t T = 0, at = -1;
 };
-TailBuffer tail_buffer(const klay_circuit* c, const TailChoice& t) {
+TailBuffer tail_buffer(const klay_circuit* c, const TailChoice& t, int B) {
     TailBuffer b;
     b.T = c->tail_rows;
     const int64_t staged = tail_stage_rows(c, t);
-    if (staged > 0) {
+    const bool after = t.first == c->plan.tail_first;           // its place is after the layers that take part
+    if (staged > 0 && !(after && staged > tail_stage_rows(c, B))) {
         b.at = c->plan.col_off[(size_t)t.first - 1];
-        if (t.first == c->plan.tail_first) b.T += staged;       // after the layers that take part
+        if (after) b.T += staged;
     }
     return b;
 }
@@ -906,7 +914,7 @@ TailBuffer tail_buffer(const klay_circuit* c, const TailChoice& t) {
 void launch_tail_fwd(const klay_circuit* c, const TailChoice& t, const float* act, float* tb, bool keep, int B, int ld,
                      int semiring, const klay::SlabLeaf& leaf, float* out, hipStream_t s) {
     const klay::CircuitPlan& p = c->plan;
-    const TailBuffer buf = tail_buffer(c, t);
+    const TailBuffer buf = tail_buffer(c, t, B);
     const int nb = (int)p.layers[(size_t)t.first - 1].n;
     const float* start = act + (size_t)c->dl[(size_t)t.first - 1].row0 * ld;
     int start_T = 0;
@@ -1738,7 +1746,7 @@ static klay_status forward_impl(klay_circuit* c, const float* leaf_weights, cons
     c->last_neg_explicit = neg_weights != nullptr;
     c->last_ws_has_bwd = with_bwd;
     c->last_tail_first = tail.first;
-    const TailBuffer buf = tail.first > 0 ? tail_buffer(c, tail) : TailBuffer();
+    const TailBuffer buf = tail.first > 0 ? tail_buffer(c, tail, B) : TailBuffer();
     c->last_tail_T = (int32_t)buf.T;
     c->last_tail_staged = buf.at >= 0;
     return KLAY_OK;
