@@ -70,8 +70,10 @@ def kernel_symbol(cls, B, edges=False, fused_op=10):
     w_small = 1
     while w_small < B:
         w_small *= 2
-    fixed = {"tail_fwd": "klay::col_fwd_kernel<%d>" % (1 if B <= 256 else 2),
-             "tail_bwd": "klay::col_bwd_kernel<%d, %s>" % (1 if B <= 256 else 2, "true" if fused_op == 12 else "false"),
+    # (above 256 columns a launch of the persistent kernels has 1, 2 or 4 of them per workgroup, as its layers fit)
+    columns = "1" if B <= 256 else "*"
+    fixed = {"tail_fwd": "klay::col_fwd_kernel<%s>" % columns,
+             "tail_bwd": "klay::col_bwd_kernel<%s, %s>" % (columns, "true" if fused_op == 12 else "false"),
              "leaf": "klay::leaf_fwd_kernel" if B > 32 else "klay::leaf_fwd_small_kernel", "bwd_leaf": "klay::leaf_bwd_kernel", "root": "klay::root_out_kernel",
              "seed": "klay::seed_kernel", "split": "klay::pass_kernel<*> (segments of split rows)",
              "combine": "klay::combine_kernel<*>" if B > 32 else "klay::combine_small_kernel<*>",

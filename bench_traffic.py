@@ -41,6 +41,7 @@ RUNS = collections.OrderedDict([
     ("layered_1m_log", ["--workload", "layered_1m"]),
     ("layered_1m_real", ["--workload", "layered_1m", "--semiring", "real"]),
     ("layered_1m_real_fwd_bwd", ["--workload", "layered_1m", "--semiring", "real", "--backward", "on"]),
+    ("layered_1m_max_b100", ["--workload", "layered_1m", "--semiring", "maxlog", "--batch", "100"]),
     ("layered_1m_b1", ["--workload", "layered_1m", "--batch", "1"]),
     ("powerlaw_10m", ["--workload", "powerlaw_10m"]),
     ("powerlaw_1m_nodes", ["--workload", "powerlaw_1m_nodes"]),

@@ -1694,7 +1694,7 @@ __global__ __launch_bounds__(kColThreads) void col_bwd_kernel(const ColLayer* __
         Float4u own[kColOwn<CT>][CT];
 #pragma unroll
         for (int i = 0; i < kColOwn<CT>; ++i) {
-            if (i > 0 && 4 * i * kColThreads >= own_n) continue;           // (the same for all threads)
+            if (4 * (wave * 64 + i * kColThreads) >= own_n) continue;      // (the same for all lanes of a wave)
             const int at = 4 * ((int)threadIdx.x + i * kColThreads), back = own_n - 4 < 0 ? 0 : own_n - 4;
             const float* from = tbc + own_at + (at < back ? at : at < own_n ? back : 0);
 #pragma unroll
@@ -1708,7 +1708,7 @@ __global__ __launch_bounds__(kColThreads) void col_bwd_kernel(const ColLayer* __
         // the adjoints above are done with: their array takes the next step's own values
 #pragma unroll
         for (int i = 0; i < kColOwn<CT>; ++i) {
-            if (i > 0 && 4 * i * kColThreads >= own_n) continue;
+            if (4 * (wave * 64 + i * kColThreads) >= own_n) continue;
             const int at = 4 * ((int)threadIdx.x + i * kColThreads), back = own_n - 4 < 0 ? 0 : own_n - 4;
             if (at + 4 <= own_n) {
                 col_put4<CT>(above + kColSlots + at, own[i]);

@@ -78,9 +78,9 @@ __device__ __forceinline__ void load_cols(double (&x)[VEC], const double* p) {
     }
 }
 
-// As the fp32 generic kernel: a lane group of W lanes per row, VEC batch columns per lane (two from B = 2 on; the last
-// lane of an odd batch shares a column with its neighbour), offsets and entries in wide loads, four gathers in flight
-// and four more where a row of the wave is that long.  Workgroups take the rows in turn over the XCDs (a contiguous eighth
+// As the fp32 generic kernel: a group of a.lanes lanes per row, VEC batch columns per lane (launch_pass64 chooses; the last
+// lane of an odd batch shares a column with its neighbour), offsets and entries in wide loads, four gathers in flight and,
+// but for OP_SOFTMAX_BWD, four more where a row of the wave is that long.  Workgroups take the rows in turn over the XCDs (a contiguous eighth
 // each, as in the fp32 kernels, leaves the longest rows to one XCD where rows are sorted by length: 37000 nodes at B = 258
 // 163 against 130 us, 322000 nodes, training step at B = 395 2522 against 2243).
 //   ONE: a wave has one row (more than half of its lanes), so offsets and entries are the same for all lanes and come by

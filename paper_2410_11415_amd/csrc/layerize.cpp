@@ -713,6 +713,8 @@ int layerize(int32_t V, int64_t N, const uint8_t* node_type, const int32_t* node
                     }
                 }
                 auto bucket = [](int32_t k) { int b = 0; while ((1 << b) < k) ++b; return b; };
+                // (8, 16, 64 and no such limit measured on 13 training steps: within 2%, 48 layers of 43000 nodes at B = 4
+                // 123.1 / 123.6 / 124.0 / 124.5 us)
                 constexpr int32_t kManyParents = 16;
                 std::stable_sort(order.begin(), order.end(), [&](int32_t a, int32_t b) {
                     const bool ma = fan_out[(size_t)a] > kManyParents, mb = fan_out[(size_t)b] > kManyParents;
