@@ -250,6 +250,11 @@ void launch_pass(int op, klay::PassArgs a, hipStream_t s) {
     int vec = a.B >= 4 ? 4 : (a.B >= 2 ? 2 : 1);
     while (vec > 1 && rows * row_lanes(a.B, vec) < 64 * kFillWaves) vec /= 2;
     a.lanes = row_lanes(a.B, vec);
+    // with one column a lane a power of two: rows whose lanes straddle the groups of 16 that a load is taken in wait
+    // longer, and there are waves to spare (power-law fan-ins, us: 12000 nodes forward B = 6 300 -> 283, 2800 nodes
+    // max B = 5 130 -> 123; with more columns a lane it is the other way round: 800000 nodes training B = 10 290 against 294)
+    if (vec == 1)
+        for (a.lanes = 1; a.lanes < std::min(64, a.B); a.lanes *= 2) {}
     a.per_wave = 64 / a.lanes;
     a.inverse = row_inverse(a.lanes);
     dim3 grid(row_blocks(rows, a.lanes), (unsigned)((a.B + a.lanes * vec - 1) / (a.lanes * vec)));
