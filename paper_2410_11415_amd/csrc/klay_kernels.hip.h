@@ -623,9 +623,18 @@ __device__ __forceinline__ void accumulate4(float (&acc)[VEC], float (&mx)[VEC],
     }
 }
 
+// All arguments in one go: left to the compiler their reads sit behind the branches before their first use, one line after
+// another, and a launch of few rows is a chain of such reads (with the entries, see below, us: 2800 nodes max B = 5, 39
+// launches, 121 -> 116; 800000 nodes B = 1 108 -> 105, training B = 10 289 -> 281).
+__device__ __forceinline__ void arguments_now(const PassArgs& a) {
+    asm volatile("" ::"s"(a.ptr), "s"(a.idx), "s"(a.src), "s"(a.own), "s"(a.seg_owner), "s"(a.out_row), "s"(a.dst), "s"(a.dst_seg),
+                 "s"(a.per_wave), "s"(a.row_begin), "s"(a.n_main), "s"(a.n_total), "s"(a.B), "s"(a.ld), "s"(gridDim.x));
+}
+
 template <int OP, int VEC>
 __global__ __launch_bounds__(256) void pass_kernel(PassArgs a) {
     constexpr bool OWN = OpTraits<OP>::own;
+    arguments_now(a);
     int sub, colu;
     if (!lane_group(a, VEC, sub, colu)) return;
     const int col = colu <= a.B - VEC ? colu : a.B - VEC;
@@ -637,6 +646,7 @@ __global__ __launch_bounds__(256) void pass_kernel(PassArgs a) {
     int j = range.x;
     // (entries past the row's end are entries of later rows or zero padding: they can be followed, their data is ignored)
     Entries4 e0 = *reinterpret_cast<const Entries4*>(a.idx + j), e1 = *reinterpret_cast<const Entries4*>(a.idx + j + 4);
+    asm volatile("" ::"v"(e0.x), "v"(e1.x));           // (both now: the second load would move behind the return)
     if (e0.x == kSkip) return;                        // split row: evaluated by segments + combine
     float nc[VEC];
 #pragma unroll
@@ -791,6 +801,7 @@ template <int OP, int W>
 __global__ __launch_bounds__(256) void combine_small_kernel(PassArgs a) {
     constexpr int G = 64 / W, CH = 4;
     constexpr bool LSE = OP == OP_LSE;
+    arguments_now(a);
     __shared__ float part_v[4][W], part_m[LSE ? 4 : 1][LSE ? W : 1];
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     const int sub = lane / W, c = lane % W;
