@@ -72,6 +72,7 @@ struct DevPass {
                   *seg_tasks = nullptr;
     const uint32_t *idx = nullptr, *comb_idx = nullptr;
     int32_t n_main = 0, n_seg = 0, n_heavy = 0, n_tasks = 0, n_seg_tasks = 0;
+    int32_t longest_comb = 0;                    // partial rows of the split row with most of them
     bool has_weighted = false;
     int64_t edges = 0;
     int64_t main_entries = 0, seg_entries = 0;   // index entries of light main rows / of segments
@@ -465,6 +466,7 @@ void bind_pass(DevPass& d, const klay::PassPlan& p, const PassOffsets& o, const 
     d.n_main = p.n_main;
     d.n_seg = p.n_seg;
     d.n_heavy = p.n_heavy;
+    for (int32_t h = 0; h < p.n_heavy; ++h) d.longest_comb = std::max(d.longest_comb, p.comb_ptr[(size_t)h + 1] - p.comb_ptr[(size_t)h]);
     d.edges = p.edges;
     // distinct source rows (for the compulsory-byte count of the profile)
     uint32_t max_id = 0;
@@ -607,7 +609,11 @@ void launch_combine_op(const klay::PassArgs& a, const Geometry& g, hipStream_t s
     else hipLaunchKernelGGL((klay::combine_kernel<OP, 1, NW>), grid, dim3(NW * 64), 0, s, a);
 }
 
-// B <= 32: a workgroup of four waves per split row as well, 64 / W partial rows at a time in a wave
+// B <= 32: a workgroup of four waves per split row as well, 64 / W partial rows at a time in a wave, where a row has more than
+// kShortComb partial rows; shorter lists take a lane group each (launch_pass), which needs fewer workgroups.  us with a limit of
+// 0 / 4 / 8 / 16 / 32 (power-law fan-ins): 9400 nodes max B = 1 216 / 183 / 184 / 185 / 184, 12000 nodes forward B = 6
+// 288 / 266 / 265 / 267 / 278, 29000 nodes training B = 18 316 / 316 / 317 / 317 / 330
+constexpr int32_t kShortComb = 8;
 template <int OP>
 void launch_combine_small(const klay::PassArgs& a, const Geometry& g, hipStream_t s) {
     dim3 grid((unsigned)a.n_main);
@@ -621,8 +627,12 @@ void launch_combine_small(const klay::PassArgs& a, const Geometry& g, hipStream_
     }
 }
 
-void launch_combine(int op, const klay::PassArgs& a, const Geometry& g, hipStream_t s) {
+void launch_combine(int op, const klay::PassArgs& a, const Geometry& g, int32_t longest, hipStream_t s) {
     if (a.n_main <= 0) return;
+    if (g.w != 64 && longest <= kShortComb) {
+        launch_pass(op, a, s);
+        return;
+    }
     if (g.w != 64) {
         switch (op) {
         case klay::OP_SUM: launch_combine_small<klay::OP_SUM>(a, g, s); break;
@@ -792,7 +802,7 @@ void run_pass_set(int op, int combine_op, const DevPass& dp, const float* src, c
     if (dp.n_heavy > 0) {
         const klay::PassArgs cmb = combine_args(dp, seg_rows, own, dst, g, B, zero_flag);
         prof.begin(KLAY_K_COMBINE, pass_bytes(combine_op, (double)dp.n_seg, (double)dp.n_heavy, B));
-        launch_combine(combine_op, cmb, g, s);
+        launch_combine(combine_op, cmb, g, dp.longest_comb, s);
         prof.end();
     }
 }

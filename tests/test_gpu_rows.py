@@ -47,6 +47,12 @@ def test_few_rows_with_split_rows(batch):
     check(layered_random(3, 60, 8, 3000, fanin=("zipf", 1.6, 400), groups=1), batch, heavy_fan=20, min_segment=7)
 
 
+@pytest.mark.parametrize("batch", [1, 3, 5, 32])
+def test_split_rows_of_few_segments(batch):
+    """(at most 8 partial rows: a lane group per split row instead of four waves)"""
+    check(layered_random(5, 60, 8, 3000, fanin=("geom", 2.2), groups=1), batch, heavy_fan=6, min_segment=5)
+
+
 @pytest.mark.parametrize("batch", [6, 10, 30, 61])
 def test_many_rows(batch):
     check(layered_random(4, 128, 6, 150_000, fanin=("geom", 2.0), groups=2), batch)
