@@ -563,7 +563,7 @@ __global__ __launch_bounds__(256) void edge_kernel(const int2* __restrict__ task
 // (the loads need four bytes) or the batch is no multiple of four (the last lane steps back and shares columns with its
 // neighbour, computing the same values), the offsets of a row in one load, its entries four at a time, and
 // the second four gathers only where a row of the wave has more than four entries.  (800000 nodes at B = 10, free
-// literals, training step: 381 -> 301 us; power-law fan-ins, 1e7 edges at B = 64: 515 -> 472 us.  One column per lane and
+// literals, training step: 381 -> 280 us; power-law fan-ins, 1e7 edges at B = 64: 515 -> 457 us.  One column per lane and
 // eight gathers for every row before.)  A launch of few rows takes fewer columns per lane (launch_pass).
 // ---------------------------------------------------------------------------------------------
 template <int VEC>
@@ -794,7 +794,7 @@ __global__ __launch_bounds__(NW * 64) void combine_kernel(PassArgs a) {
     combine_body<OP, VEC, NW>((int)blockIdx.x, a);
 }
 
-// The same for B <= 32: W lanes (a power of two) hold the columns of a partial row, so a wave takes 64 / W partial rows at
+// The same for B <= 32 and split rows of many partial rows (kShortComb): W lanes (a power of two) hold the columns of a partial row, so a wave takes 64 / W partial rows at
 // a time, four of them in flight; the lane groups meet in a butterfly, the four waves in LDS, in a fixed order.  (A lane
 // group per split row walked the partial rows of the widest row, up to a few hundred, alone.)
 template <int OP, int W>
@@ -871,24 +871,25 @@ __global__ __launch_bounds__(256) void stream_combine_kernel(const int2* __restr
 
 // ---------------------------------------------------------------------------------------------
 // Persistent kernels for the top of the circuit (the layers that taper to the roots; for a small
-// circuit every layer): instead of one launch per layer, a workgroup of 16 waves owns one batch column, keeps
+// circuit every layer): instead of one launch per layer, a workgroup of 16 waves owns CT batch columns (1, 2 or 4, see
+// tail_columns), keeps
 // the values (forward) or the adjoints (reverse) of the layer in hand and of the one below or above in LDS and
 // walks the layers with a barrier in between.  Batch columns are independent, so no grid-wide
-// barrier is needed.  Above 256 columns the workgroups take turns on the compute units.
+// barrier is needed.  More than 256 workgroups take turns on the compute units (one needs the registers of a whole one).
 //   Index vectors stay in global memory, as blocks and tables of runs (ColPlan, layerize.h): one stream of each per
 // wave, contiguous over all layers, so a wave fetches the next block and the next table ahead of the ones it works
 // on, also across the layer barriers.  A table is read one descriptor per lane and broadcast to scalars
 // (readlane); scalar loads would share their wait counter with the LDS gathers.
-//   What bounds these kernels: one compute unit evaluates a whole column, so first the longest wave of each layer
+//   What bounds these kernels: one compute unit evaluates whole columns, so first the longest wave of each layer
 // (hence several lanes per long row, and shares of equal cost), then the latency of the dependent steps of a row and
 // the control flow around it (hence runs of one kind, 16 gathers of a lane in flight together) and then the
 // instructions per entry, of which a
 // logsumexp entry has most (hence whole rows: one maximum, one exponential per entry, no running rescale).
 //   Measured against one lane per row, chunks dealt in turn and a running logsumexp (forward / forward + backward, log
-// semiring): 85000 nodes, 263000 edges, 20 layers at B = 128: 52 -> 42 us / 211 -> 109 us (there the reverse kernel
-// could not take layers with nodes of more than 64 parents); 467 nodes, 22 layers at B = 4: 19.5 -> 16.4 us.  A
+// semiring): 85000 nodes, 263000 edges, 20 layers at B = 128: 52 -> 42 us / 211 -> 100 us (there the reverse kernel
+// could not take layers with nodes of more than 64 parents); 467 nodes, 22 layers at B = 4: 19.5 -> 16.6 us.  A
 // narrow layer costs about 2000 cycles of dependent steps, a wide one 5 ns per 64 entries.
-//   A lane owns rows of one batch column, so writing values into the row-major activation buffer
+//   A lane owns rows of few batch columns, so writing values into the row-major activation buffer
 // would cost one cache line per lane.  The values go to a column-major buffer tb[column][T] instead
 // (T = rows of all candidate layers), where consecutive lanes write consecutive floats; the reverse
 // kernel reads it the same way, and rows that an ordinary launch needs are transposed back on demand
@@ -1546,9 +1547,10 @@ struct ColReal {
 // one from there.  Node values come from the column-major buffer tb, once per row, and are far away (a read of them
 // takes about 2000 cycles, twice as long as a narrow layer): those of the first `cached` steps are loaded at once to
 // cache_at, into LDS that only later steps use or that lies behind both arrays (launch_tail_bwd; 67000 nodes in 48 layers of
-// about 1400, log training step at B = 4: 143 -> 116 us by what lies behind, 29000 nodes in 30 layers 91 -> 68); from there on those of the next step's rows are
-// fetched into registers during a step (kColOwn times four per thread: any layer that fits) and put into the slots of the
-// array that the step frees.  (Four at a time: a load instruction of one float a lane takes the memory pipe as long.)  last_at: entry of the last layer in tb (-1: its values are not needed).  The adjoints
+// about 1400, log training step at B = 4: 143 -> 116 us by what lies behind, 29000 nodes in 30 layers 91 -> 68); from there
+// on those of the next step's rows are fetched into registers during a step (up to kColOwn times four per thread: any
+// layer that fits; as many as the layer has, 116 -> 109 us there) and put into the slots of the array that the step
+// frees.  (Four at a time: a load instruction of one float a lane takes the memory pipe as long.)  last_at: entry of the last layer in tb (-1: its values are not needed).  The adjoints
 // of OR nodes with more than one child are kept in the one-gather form throughout, also on the way out; top_multi
 // (or null) flags such nodes of the top layer for the seed.
 // (tb is not __restrict__: a load known to be invariant would be moved down past the barrier to its use.)
