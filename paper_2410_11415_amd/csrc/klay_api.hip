@@ -22,7 +22,9 @@
 // ends.  In host code the name below is only a handle for hipGetSymbolAddress; the kernels get the
 // address that call returned (kept per device in g_static_ws).
 constexpr size_t kStaticWorkspaceBytes = KLAY_STATIC_WORKSPACE_BYTES;
-static __device__ __align__(256) unsigned char scratch[kStaticWorkspaceBytes];
+// The second half is for the stage buffer of a TopPlan, which the limit of a call does not count: one level of the circuit,
+// never more rows than the activation rows in the first half.
+static __device__ __align__(256) unsigned char scratch[2 * kStaticWorkspaceBytes];
 
 // Layers with split rows and at most this many index entries run main rows and segments in one generic
 // launch (measured at B = 64 on the two power-law workloads, ms per step: this threshold 0.69 / 0.76, ten times
@@ -95,6 +97,27 @@ struct DevLayer {
     bool has_multi = false;
 };
 
+// The layers that the persistent kernels may run, first .. L: those of the circuit plan itself (klay_circuit::tail) or of its
+// TopPlan.
+struct ColTail {
+    int32_t first = 0;                   // lowest one (0: none)
+    std::vector<int64_t> n, kept, at;    // by layer from first - 1 on (index l): rows, rows kept for the reverse sweep, first entry in a column
+    std::vector<int64_t> e, words[2];    // edges; words of the streams, forward and reverse
+    int64_t rows = 0;                    // kept rows of the layers first .. L
+    const klay::ColLayer* layers = nullptr;    // where the streams of the layers first .. L start
+    const klay::Line* blocks[2] = {nullptr, nullptr};
+    int32_t n_blocks[2] = {0, 0};
+    const klay::Desc* tables = nullptr;
+    const int32_t *root_pos = nullptr, *top_ptr = nullptr, *top_root = nullptr;
+    // TopPlan only: activation row of every row (of level l from own_at[l] on), of every kept row; flags of the top level (null: no
+    // layer of OR nodes); what the layers take otherwise
+    const int32_t *own = nullptr, *act_row = nullptr;
+    std::vector<int64_t> own_at;
+    const uint32_t* multi = nullptr;
+    std::vector<int32_t> launches;
+    std::vector<int64_t> share;
+};
+
 struct Geometry {            // how a batch of B columns is mapped onto lanes
     int vec = 1, w = 64, ld = 0, tiles = 1;
 };
@@ -119,6 +142,7 @@ size_t align_floats(size_t n) { return (n + 63) / 64 * 64; }
 
 struct Workspace {
     size_t act = 0, wT = 0, seg_rows = 0, g0 = 0, g1 = 0, g2 = 0, tb = 0, stage = 0, flags = 0, total = 0;   // offsets in floats
+    size_t counted = 0, top_stage = 0, top_tb = 0, top_g = 0;      // the parts of a TopPlan follow the others (`counted` floats)
 };
 
 struct EventRec {
@@ -140,14 +164,12 @@ struct klay_circuit {
     const int32_t *d_pos_row = nullptr, *d_neg_row = nullptr, *d_root_pos = nullptr, *d_top_ptr = nullptr,
                   *d_top_root = nullptr;
     int32_t true_row = -1, false_row = -1;
-    const klay::ColLayer* d_tail = nullptr;    // where the streams of the layers plan.tail_first .. L start
-    const klay::Line* d_blocks[2] = {nullptr, nullptr};   // streams of the persistent kernels, forward and reverse
-    int32_t n_blocks[2] = {0, 0};
-    const klay::Desc* d_tables = nullptr;
+    ColTail tail, top;                         // what the persistent kernels may run: layers of the plan, and of its TopPlan
     const int32_t* d_leaf_code = nullptr;      // layer 0: literal / constant code of every row
     size_t tail_lds_bytes = 0;                 // LDS a workgroup of the persistent kernels may use (0: kernels unusable)
     int64_t tail_rows = 0;                     // T: rows of all tail candidate layers (one column of the tail buffer)
     int32_t last_tail_first = 0;               // first layer the last forward ran in the persistent kernel (0: none)
+    int32_t last_top_first = 0;                // the same, from the TopPlan
     int32_t last_tail_T = 0;                   // floats in a column of its value buffer
     bool last_tail_staged = false;             // the layer below it is part of that buffer
     // real-semiring reverse sweep (built at its first use): per AND layer the plain by-parent index
@@ -194,6 +216,8 @@ int64_t top_layer_rows(const klay::CircuitPlan& p) {
 }
 
 int64_t tail_stage_rows(const klay_circuit* c, int B);
+int choose_top(const klay_circuit* c, int B);
+int tail_columns(int B, const int64_t (&size)[2], size_t lds_bytes, bool reverse);
 
 Workspace workspace_layout(const klay_circuit* c, int B, bool need_bwd) {
     const Geometry g = geometry(B);
@@ -216,6 +240,13 @@ Workspace workspace_layout(const klay_circuit* c, int B, bool need_bwd) {
         w.g2 = off; off += align_floats((size_t)top_layer_rows(p) * g.ld);
         // one word per layer: the real-semiring sweep's "a node value of this product layer is zero" flags
         w.flags = off; off += align_floats((size_t)p.num_layers + 1);
+    }
+    w.counted = off;
+    if (const int first = choose_top(c, B); first > 0) {
+        // the level below its first one, the values of the others, their adjoints: column-major
+        w.top_stage = off; off += align_floats((size_t)c->top.n[(size_t)first - 1] * (size_t)B);
+        w.top_tb = off; off += align_floats((size_t)c->top.rows * (size_t)B);
+        if (need_bwd) { w.top_g = off; off += align_floats((size_t)c->top.rows * (size_t)B); }
     }
     w.total = off;
     return w;
@@ -478,28 +509,73 @@ void bind_pass(DevPass& d, const klay::PassPlan& p, const PassOffsets& o, const 
         if (p.idx[j] != klay::kSkipRow && !seen[p.idx[j] & klay::kIdMask]) { seen[p.idx[j] & klay::kIdMask] = 1; ++d.n_src; }
 }
 
+// sizes of the layers that the persistent kernels may run
+void describe_tails(klay_circuit* c) {
+    const klay::CircuitPlan& p = c->plan;
+    const size_t layers = (size_t)p.num_layers + 1;
+    auto room = [&](ColTail& t) {
+        for (std::vector<int64_t>* v : {&t.n, &t.kept, &t.at, &t.e, &t.words[0], &t.words[1], &t.own_at, &t.share}) v->assign(layers, 0);
+        t.launches.assign(layers, 0);
+    };
+    if (p.tail_first > 0) {
+        ColTail& t = c->tail;
+        room(t);
+        t.first = p.tail_first;
+        t.rows = p.col_rows;
+        for (size_t l = (size_t)t.first - 1; l < layers; ++l) {
+            const klay::LayerPlan& lay = p.layers[l];
+            t.n[l] = t.kept[l] = lay.n;
+            t.at[l] = p.col_off[l];
+            t.e[l] = lay.e;
+            t.words[0][l] = (int64_t)lay.col_fwd.blocks.size();
+            t.words[1][l] = (int64_t)lay.col_bwd.blocks.size();
+        }
+    }
+    if (p.top.first > 0) {
+        ColTail& t = c->top;
+        room(t);
+        t.first = p.top.first;
+        t.rows = p.top.rows;
+        int64_t own = 0;
+        for (size_t l = (size_t)t.first - 1; l < layers; ++l) {
+            const klay::TopPlan::Level& lev = p.top.level((int32_t)l);
+            t.n[l] = lev.n;
+            t.kept[l] = lev.kept;
+            t.at[l] = lev.at;
+            t.e[l] = lev.e;
+            t.words[0][l] = (int64_t)lev.fwd.blocks.size();
+            t.words[1][l] = (int64_t)lev.bwd.blocks.size();
+            t.own_at[l] = own;
+            own += lev.n;
+            t.launches[l] = lev.launches;
+            t.share[l] = lev.fwd.share;
+        }
+    }
+}
+
 klay_status upload(klay_circuit* c) {
     const klay::CircuitPlan& p = c->plan;
     Packer pk;
     const int L = p.num_layers;
     // Streams of the persistent kernels: per wave and direction the lines and descriptors of all candidate layers
     // back to back, in the order the sweep visits them.
-    size_t o_tail = 0, o_blocks[2] = {0, 0}, o_tables = 0;
-    if (p.tail_first > 0) {
-        std::vector<klay::ColLayer> starts((size_t)(L - p.tail_first + 1));
+    struct TailOffsets { size_t layers = 0, blocks[2] = {0, 0}, tables = 0; };
+    auto pack_tail = [&](ColTail& t, auto plan_of) {
+        TailOffsets o;
+        std::vector<klay::ColLayer> starts((size_t)(L - t.first + 1));
         std::vector<uint32_t> blocks[2], tables;
-        for (int l = p.tail_first; l <= L; ++l) {
-            starts[(size_t)(l - p.tail_first)].n = (int32_t)p.layers[(size_t)l].n;
-            starts[(size_t)(l - p.tail_first)].at = (int32_t)p.col_off[(size_t)l];
+        for (int l = t.first; l <= L; ++l) {
+            starts[(size_t)(l - t.first)].n = (int32_t)t.kept[(size_t)l];
+            starts[(size_t)(l - t.first)].at = (int32_t)t.at[(size_t)l];
         }
         constexpr size_t kTableWords = (size_t)klay::kDescTable * klay::kDescWords;
         for (int backward = 0; backward < 2; ++backward) {
             std::vector<uint32_t>& out = blocks[backward];
             for (int w = 0; w < klay::kColWaves; ++w)
-                for (int step = 0; step <= L - p.tail_first; ++step) {
-                    const int l = backward ? L - step : p.tail_first + step;
-                    const klay::ColPlan& cp = backward ? p.layers[(size_t)l].col_bwd : p.layers[(size_t)l].col_fwd;
-                    klay::ColLayer& at = starts[(size_t)(l - p.tail_first)];
+                for (int step = 0; step <= L - t.first; ++step) {
+                    const int l = backward ? L - step : t.first + step;
+                    const klay::ColPlan& cp = plan_of(l, backward);
+                    klay::ColLayer& at = starts[(size_t)(l - t.first)];
                     (backward ? at.bwd_block : at.fwd_block)[w] = (int32_t)(out.size() / klay::kBlockWords);
                     (backward ? at.bwd_table : at.fwd_table)[w] = (int32_t)(tables.size() / kTableWords);
                     out.insert(out.end(), cp.blocks.begin() + (size_t)cp.block_at[w] * klay::kBlockWords,
@@ -507,14 +583,33 @@ klay_status upload(klay_circuit* c) {
                     tables.insert(tables.end(), cp.tables.begin() + (size_t)cp.table_at[w] * kTableWords,
                                   cp.tables.begin() + (size_t)cp.table_at[w + 1] * kTableWords);
                 }
-            c->n_blocks[backward] = (int32_t)(out.size() / klay::kBlockWords);
+            t.n_blocks[backward] = (int32_t)(out.size() / klay::kBlockWords);
             out.resize(out.size() + klay::kBlockWords, 0u);      // the waves read one block and one table ahead
         }
         tables.resize(tables.size() + kTableWords, 0u);
         static_assert(sizeof(klay::ColLayer) % sizeof(int32_t) == 0, "must pack into ints");
-        for (int i = 0; i < 2; ++i) o_blocks[i] = pk.add(blocks[i]);
-        o_tables = pk.add(tables);
-        o_tail = pk.add(reinterpret_cast<const int32_t*>(starts.data()), starts.size() * sizeof(klay::ColLayer) / sizeof(int32_t));
+        for (int i = 0; i < 2; ++i) o.blocks[i] = pk.add(blocks[i]);
+        o.tables = pk.add(tables);
+        o.layers = pk.add(reinterpret_cast<const int32_t*>(starts.data()), starts.size() * sizeof(klay::ColLayer) / sizeof(int32_t));
+        return o;
+    };
+    TailOffsets o_tail, o_top;
+    if (c->tail.first > 0)
+        o_tail = pack_tail(c->tail, [&](int l, int backward) -> const klay::ColPlan& {
+            return backward ? p.layers[(size_t)l].col_bwd : p.layers[(size_t)l].col_fwd;
+        });
+    size_t o_own = 0, o_act_row = 0, o_top_root_pos = 0, o_top_top_ptr = 0, o_top_top_root = 0, o_top_multi = 0;
+    if (c->top.first > 0) {
+        const klay::TopPlan& top = p.top;
+        o_top = pack_tail(c->top, [&](int l, int backward) -> const klay::ColPlan& { return backward ? top.level(l).bwd : top.level(l).fwd; });
+        std::vector<int32_t> own;
+        for (const klay::TopPlan::Level& lev : top.levels) own.insert(own.end(), lev.own.begin(), lev.own.end());
+        o_own = pk.add(own);
+        o_act_row = pk.add(top.act_row);
+        o_top_root_pos = pk.add(top.root_pos);
+        o_top_top_ptr = pk.add(top.top_ptr);
+        o_top_top_root = pk.add(top.top_root);
+        o_top_multi = pk.add(top.multi);
     }
     const size_t o_leaf_code = pk.add(p.leaf_code);
     std::vector<PassOffsets> fo((size_t)L + 1), bo((size_t)L + 1), fko((size_t)L + 1), f2o((size_t)L + 1);
@@ -572,10 +667,25 @@ klay_status upload(klay_circuit* c) {
     c->d_root_pos = base + o_root;
     c->d_top_ptr = base + o_tptr;
     c->d_top_root = base + o_troot;
-    if (p.tail_first > 0) {
-        c->d_tail = reinterpret_cast<const klay::ColLayer*>(base + o_tail);
-        for (int i = 0; i < 2; ++i) c->d_blocks[i] = reinterpret_cast<const klay::Line*>(base + o_blocks[i]);
-        c->d_tables = reinterpret_cast<const klay::Desc*>(base + o_tables);
+    auto bind_tail = [&](ColTail& t, const TailOffsets& o) {
+        t.layers = reinterpret_cast<const klay::ColLayer*>(base + o.layers);
+        for (int i = 0; i < 2; ++i) t.blocks[i] = reinterpret_cast<const klay::Line*>(base + o.blocks[i]);
+        t.tables = reinterpret_cast<const klay::Desc*>(base + o.tables);
+    };
+    if (c->tail.first > 0) {
+        bind_tail(c->tail, o_tail);
+        c->tail.root_pos = c->d_root_pos;
+        c->tail.top_ptr = c->d_top_ptr;
+        c->tail.top_root = c->d_top_root;
+    }
+    if (c->top.first > 0) {
+        bind_tail(c->top, o_top);
+        c->top.own = base + o_own;
+        c->top.act_row = base + o_act_row;
+        c->top.root_pos = base + o_top_root_pos;
+        c->top.top_ptr = base + o_top_top_ptr;
+        c->top.top_root = base + o_top_top_root;
+        if ((L & 1) == 0) c->top.multi = reinterpret_cast<const uint32_t*>(base + o_top_multi);
     }
     c->d_leaf_code = base + o_leaf_code;
     return KLAY_OK;
@@ -854,6 +964,44 @@ TailChoice choose_tail(const klay_circuit* c, int ct) {
     return t;
 }
 
+// The first layer that the forward kernel takes from the TopPlan at a batch of B (0: none, the layers of the plan itself go the
+// other ways): the choice with the least time by a rough account.  In the persistent kernels a layer takes the time of its longest
+// wave and about 2000 cycles; a launch takes 3.5 us and what it gathers, from the caches, at 10 TB/s.  us, launches throughout / this
+// choice (first layer), forward and training step:
+//   290000 nodes in 30 layers, 1e7 edges, B = 1 230 / 206 (13), 412 / 368; B = 64 457 / 411 (13), 965 / 900; B = 500 1895 / 1777 (16),
+//   3830 / 3670; 92000 nodes in 40 layers, 1e6 edges, B = 1 178 / 116 (1), 325 / 284; B = 64 243 / 125, 484 / 286; B = 1000 646 / 492,
+//   1277 / 1178; 20000 nodes in 16 layers, 1.7e5 edges, B = 64 87 / 35 (1), 174 / 80.
+// First layers above 1 only up to B = 1024: 23200 nodes in 30 layers at B = 2000 536 / 483 (2), but 1080 / 1181 in training.  (The
+// reverse kernel could leave the sweep to the launches earlier; that gains at most 8%, 92000 nodes training B = 1 284 against 259,
+// and loses for B >= 64.)
+int choose_top(const klay_circuit* c, int B) {
+    const ColTail& t = c->top;
+    if (t.first <= 0 || c->tail_lds_bytes == 0) return 0;
+    const int L = c->plan.num_layers;
+    double inside = 0, outside = 0, best = 0;          // us of the layers from l on, in the kernel and outside; what the best choice saves
+    int first = 0;
+    int64_t size[2] = {0, 0};                          // as tail_lds
+    auto room = [&](int l) { size[l & 1] = std::max(size[l & 1], (t.n[(size_t)l] + klay::kColSlots + 3) / 4 * 4); };
+    room(L);
+    for (int l = L; l >= t.first; --l) {
+        inside += (2000.0 + (double)t.share[(size_t)l]) / 2000.0;
+        outside += 3.5 * t.launches[(size_t)l] + (double)t.e[(size_t)l] * B / 2.5e6;
+        room(l - 1);
+        if (l > std::min(c->plan.alias_top, L - 1)) continue;
+        if ((size_t)(size[0] + size[1]) * sizeof(float) > c->tail_lds_bytes) break;
+        // columns in turns, several at once take longer than one
+        const int ct = tail_columns(B, size, c->tail_lds_bytes, false), turns = (B + 256 * ct - 1) / (256 * ct);
+        // from rows to columns and, in a reverse sweep, back
+        const double transposed = l > 1 ? 5.0 + (double)(t.n[(size_t)l - 1] + t.rows - t.at[(size_t)l]) * B * 2e-6 : 0.0;
+        const double saved = outside - turns * (4.0 + (ct == 4 ? 1.9 : ct == 2 ? 1.3 : 1.0) * inside) - transposed;
+        if (saved > best && (l == 1 || B <= 1024)) {
+            best = saved;
+            first = l;
+        }
+    }
+    return first;
+}
+
 TailChoice choose_tail_fwd(const klay_circuit* c, int B) { return choose_tail(c, tail_ct(B, 4)); }
 
 // Rows of the layer below the forward kernel's first one if that layer gets a place in the column-major buffer (where
@@ -869,12 +1017,12 @@ int64_t tail_stage_rows(const klay_circuit* c, const TailChoice& t) {
 // with a fixed buffer takes, stay what they were before the limit of 4.)
 int64_t tail_stage_rows(const klay_circuit* c, int B) { return tail_stage_rows(c, choose_tail(c, tail_ct(B, 8))); }
 
-// floats of the two LDS arrays that hold the layers lowest .. L by turns; [0]: the one with layer `zero` in it
-void tail_lds(const klay::CircuitPlan& p, int lowest, int zero, int64_t (&size)[2]) {
+// floats of the two LDS arrays that hold `n` values of the layers lowest .. L by turns; [0]: the one with layer `zero` in it
+void tail_lds(const std::vector<int64_t>& n, int lowest, int zero, int64_t (&size)[2]) {
     size[0] = size[1] = 0;
-    for (int l = lowest; l <= p.num_layers; ++l) {
-        int64_t& n = size[(l - zero) & 1];
-        n = std::max(n, (p.layers[(size_t)l].n + klay::kColSlots + 3) / 4 * 4);
+    for (int l = lowest; l < (int)n.size(); ++l) {
+        int64_t& most = size[(l - zero) & 1];
+        most = std::max(most, (n[(size_t)l] + klay::kColSlots + 3) / 4 * 4);
     }
 }
 
@@ -885,9 +1033,12 @@ size_t enable_tail_lds() {
     for (int kb : {160, 128, 64}) {
         const int bytes = kb * 1024;
         hipError_t e = hipSuccess;
-        for (const void* kernel : {reinterpret_cast<const void*>(&klay::col_fwd_kernel<1>), reinterpret_cast<const void*>(&klay::col_bwd_kernel<1, false>),
-                                   reinterpret_cast<const void*>(&klay::col_bwd_kernel<1, true>), reinterpret_cast<const void*>(&klay::col_bwd_kernel<2, true>),
-                                   reinterpret_cast<const void*>(&klay::col_fwd_kernel<2>), reinterpret_cast<const void*>(&klay::col_fwd_kernel<4>), reinterpret_cast<const void*>(&klay::col_bwd_kernel<4, false>), reinterpret_cast<const void*>(&klay::col_bwd_kernel<4, true>), reinterpret_cast<const void*>(&klay::col_bwd_kernel<2, false>)})
+        for (const void* kernel : {reinterpret_cast<const void*>(&klay::col_fwd_kernel<1>), reinterpret_cast<const void*>(&klay::col_fwd_kernel<2>),
+                                   reinterpret_cast<const void*>(&klay::col_fwd_kernel<4>), reinterpret_cast<const void*>(&klay::col_bwd_kernel<1, false, false>),
+                                   reinterpret_cast<const void*>(&klay::col_bwd_kernel<2, false, false>), reinterpret_cast<const void*>(&klay::col_bwd_kernel<4, false, false>),
+                                   reinterpret_cast<const void*>(&klay::col_bwd_kernel<1, true, false>), reinterpret_cast<const void*>(&klay::col_bwd_kernel<2, true, false>),
+                                   reinterpret_cast<const void*>(&klay::col_bwd_kernel<4, true, false>), reinterpret_cast<const void*>(&klay::col_bwd_kernel<1, false, true>),
+                                   reinterpret_cast<const void*>(&klay::col_bwd_kernel<2, false, true>), reinterpret_cast<const void*>(&klay::col_bwd_kernel<4, false, true>)})
             if (e == hipSuccess) e = hipFuncSetAttribute(kernel, hipFuncAttributeMaxDynamicSharedMemorySize, bytes);
         if (e == hipSuccess) return (size_t)bytes;
         (void)hipGetLastError();
@@ -924,6 +1075,17 @@ TailBuffer tail_buffer(const klay_circuit* c, const TailChoice& t, int B) {
     return b;
 }
 
+// The forward kernel over the layers first .. L of `t`; start: see the kernel.
+void launch_col_fwd(const klay_circuit* c, const ColTail& t, int first, const float* start, int start_T, const int32_t* start_map, float* tb, int T,
+                    int B, int ld, int semiring, const klay::SlabLeaf& leaf, float* out, hipStream_t s) {
+    int64_t size[2];
+    tail_lds(t.n, first - 1, first - 1, size);
+    const int ct = tail_columns(B, size, c->tail_lds_bytes, false);
+    hipLaunchKernelGGL((ct == 4 ? klay::col_fwd_kernel<4> : ct == 2 ? klay::col_fwd_kernel<2> : klay::col_fwd_kernel<1>), dim3((unsigned)((B + ct - 1) / ct)), dim3(klay::kColThreads),
+                       (size_t)(size[0] + size[1]) * ct * sizeof(float), s, t.layers + (first - t.first), c->plan.num_layers - first + 1, first & 1, t.blocks[0], t.n_blocks[0], t.tables, start,
+                       (int)t.n[(size_t)first - 1], start_T, start_map, B, ld, semiring, (int)size[0], tb, T, leaf, t.root_pos, c->plan.num_roots, out);
+}
+
 // tb: the column-major buffer; its last columns' room is followed by that of the layer below (workspace_layout), so
 // T may count that layer.  keep: the values are kept there for a reverse sweep (otherwise only that layer goes there).
 void launch_tail_fwd(const klay_circuit* c, const TailChoice& t, const float* act, float* tb, bool keep, int B, int ld,
@@ -935,26 +1097,43 @@ void launch_tail_fwd(const klay_circuit* c, const TailChoice& t, const float* ac
     int start_T = 0;
     if (!leaf.w && buf.at >= 0) {
         dim3 tg((unsigned)((nb + 31) / 32), (unsigned)((B + 31) / 32));
-        hipLaunchKernelGGL(klay::rows_to_cols_kernel, tg, dim3(256), 0, s, start, nb, B, ld, tb + buf.at, (int)buf.T);
+        hipLaunchKernelGGL(klay::rows_to_cols_kernel<false>, tg, dim3(256), 0, s, start, nb, B, ld, tb + buf.at, (int)buf.T, (const int32_t*)nullptr);
         start = tb + buf.at;
         start_T = (int)buf.T;
     }
-    int64_t size[2];
-    tail_lds(p, t.first - 1, t.first - 1, size);
-    const int ct = tail_columns(B, size, c->tail_lds_bytes, false);
-    hipLaunchKernelGGL((ct == 4 ? klay::col_fwd_kernel<4> : ct == 2 ? klay::col_fwd_kernel<2> : klay::col_fwd_kernel<1>), dim3((unsigned)((B + ct - 1) / ct)), dim3(klay::kColThreads),
-                       (size_t)(size[0] + size[1]) * ct * sizeof(float), s, c->d_tail + (t.first - p.tail_first), p.num_layers - t.first + 1, t.first & 1, c->d_blocks[0], c->n_blocks[0], c->d_tables, start,
-                       nb, start_T, B, ld, semiring, (int)size[0], keep ? tb : nullptr, (int)buf.T, leaf, c->d_root_pos, p.num_roots, out);
+    launch_col_fwd(c, c->tail, t.first, start, start_T, nullptr, keep ? tb : nullptr, (int)buf.T, B, ld, semiring, leaf, out, s);
+}
+
+// Levels above which a workgroup reads the level below the first one from its rows: fewer columns are not worth the launch that
+// makes columns of them.
+constexpr int kTopStageB = 16;
+
+// The same over the TopPlan.  tb: as above, or null (the values are not kept).
+void launch_top_fwd(const klay_circuit* c, int first, const float* act, float* stage, float* tb, int B, int ld, int semiring, const klay::SlabLeaf& leaf,
+                    float* out, hipStream_t s) {
+    const int nb = (int)c->top.n[(size_t)first - 1];
+    const int32_t* own = c->top.own + c->top.own_at[(size_t)first - 1];
+    const int32_t* map = own;
+    const float* start = act;
+    int start_T = 0;
+    if (first > 1 && B > kTopStageB) {
+        dim3 tg((unsigned)((nb + 31) / 32), (unsigned)((B + 31) / 32));
+        hipLaunchKernelGGL(klay::rows_to_cols_kernel<true>, tg, dim3(256), 0, s, act, nb, B, ld, stage, nb, own);
+        start = stage;
+        start_T = nb;
+        map = nullptr;
+    }
+    launch_col_fwd(c, c->top, first, start, start_T, map, tb, (int)c->top.rows, B, ld, semiring, leaf, out, s);
 }
 
 // Reverse sweep of the layers L .. first into layer `last` (first, or the layer below it); last_at: its entry in a
 // column of the value buffer (-1: layer 0, whose values the sweep does not need).
-void launch_tail_bwd(const klay_circuit* c, int last, int last_at, const float* tb, int T, const float* dout, const uint32_t* top_multi,
+void launch_tail_bwd(const klay_circuit* c, const ColTail& tail, int last, int last_at, const float* tb, int T, const float* dout, const uint32_t* top_multi,
                      const klay::ColBwdOut& res, const klay::ColReal* real, int B, int ld, hipStream_t s) {
     const klay::CircuitPlan& p = c->plan;
     const int L = p.num_layers;
     int64_t size[2];
-    tail_lds(p, last, L, size);
+    tail_lds(tail.kept, last, L, size);
     const int ct = tail_columns(B, size, c->tail_lds_bytes, true);
     // The own values of the first steps are loaded at once: as many steps as fit behind the rows of one of the two arrays,
     // into LDS that only the wider layers further down need, or behind both arrays, up to all that a compute unit has (a
@@ -963,8 +1142,8 @@ void launch_tail_bwd(const klay_circuit* c, int last, int last_at, const float* 
     int cached = 0, cache_at = 0;
     int64_t rows[2] = {0, 0}, sum = 0, words = size[0] + size[1];
     for (int l = L; l > last + 1; --l) {                  // step from layer l into layer l - 1
-        for (int m : {l, l - 1}) rows[(L - m) & 1] = std::max(rows[(L - m) & 1], p.layers[(size_t)m].n + klay::kColSlots);
-        sum += p.layers[(size_t)l - 1].n;
+        for (int m : {l, l - 1}) rows[(L - m) & 1] = std::max(rows[(L - m) & 1], tail.kept[(size_t)m] + klay::kColSlots);
+        sum += tail.kept[(size_t)l - 1];
         const int64_t at = (size[0] + rows[1] + 3) / 4 * 4;
         if (sum <= size[0] - (rows[0] + 3) / 4 * 4) {
             cache_at = (int)((rows[0] + 3) / 4 * 4);
@@ -977,11 +1156,12 @@ void launch_tail_bwd(const klay_circuit* c, int last, int last_at, const float* 
         }
         cached = L - l + 1;
     }
-    auto* kernel = real ? (ct == 4 ? klay::col_bwd_kernel<4, true> : ct == 2 ? klay::col_bwd_kernel<2, true> : klay::col_bwd_kernel<1, true>)
-                        : (ct == 4 ? klay::col_bwd_kernel<4, false> : ct == 2 ? klay::col_bwd_kernel<2, false> : klay::col_bwd_kernel<1, false>);
+    auto* kernel = real ? (ct == 4 ? klay::col_bwd_kernel<4, true, false> : ct == 2 ? klay::col_bwd_kernel<2, true, false> : klay::col_bwd_kernel<1, true, false>)
+                   : res.keep ? (ct == 4 ? klay::col_bwd_kernel<4, false, true> : ct == 2 ? klay::col_bwd_kernel<2, false, true> : klay::col_bwd_kernel<1, false, true>)
+                              : (ct == 4 ? klay::col_bwd_kernel<4, false, false> : ct == 2 ? klay::col_bwd_kernel<2, false, false> : klay::col_bwd_kernel<1, false, false>);
     hipLaunchKernelGGL(kernel, dim3((unsigned)((B + ct - 1) / ct)), dim3(klay::kColThreads),
-                       (size_t)words * ct * sizeof(float), s, c->d_tail + (L - p.tail_first), L - last, last_at, L & 1, c->d_blocks[1], c->n_blocks[1], c->d_tables, dout, c->d_top_ptr,
-                       c->d_top_root, p.num_roots, B, ld, (int)size[0], cached, cache_at, tb, T, top_multi, res, real ? *real : klay::ColReal{});
+                       (size_t)words * ct * sizeof(float), s, tail.layers + (L - tail.first), L - last, last_at, L & 1, tail.blocks[1], tail.n_blocks[1], tail.tables, dout, tail.top_ptr,
+                       tail.top_root, p.num_roots, B, ld, (int)size[0], cached, cache_at, tb, T, top_multi, res, real ? *real : klay::ColReal{});
 }
 
 // Values of layers first .. last (all run by the persistent forward kernel) from the column-major
@@ -993,20 +1173,28 @@ void launch_tb_to_rows(const klay_circuit* c, int first, int last, const float* 
     for (int l = first; l <= last; ++l) n_rows += p.layers[(size_t)l].n;
     if (n_rows <= 0) return;
     dim3 grid((unsigned)((n_rows + 31) / 32), (unsigned)((ld + 31) / 32));
-    hipLaunchKernelGGL(klay::tb_to_rows_kernel, grid, dim3(256), 0, s, tb, (int)c->last_tail_T, (int)tb_first, (int)n_rows, B,
-                       ld, act + (size_t)c->dl[(size_t)first].row0 * ld);
+    hipLaunchKernelGGL(klay::tb_to_rows_kernel<false>, grid, dim3(256), 0, s, tb, (int)c->last_tail_T, (int)tb_first, (int)n_rows, B,
+                       ld, act + (size_t)c->dl[(size_t)first].row0 * ld, (const int32_t*)nullptr);
 }
 
-double tail_alg_bytes(const klay_circuit* c, int first, int B, bool backward) {
+// Values or adjoints of the levels first .. last of the TopPlan (in a column-major buffer) into the activation or adjoint rows
+// that they stand for.
+void launch_top_to_rows(const klay_circuit* c, int first, int last, const float* cols, float* rows, int B, int ld, hipStream_t s) {
+    const ColTail& t = c->top;
+    const int64_t from = t.at[(size_t)first], n = t.at[(size_t)last] + t.kept[(size_t)last] - from;
+    if (n <= 0) return;
+    dim3 grid((unsigned)((n + 31) / 32), (unsigned)((ld + 31) / 32));
+    hipLaunchKernelGGL(klay::tb_to_rows_kernel<true>, grid, dim3(256), 0, s, cols, (int)t.rows, (int)from, (int)n, B, ld, rows, t.act_row + from);
+}
+
+double tail_alg_bytes(const ColTail& t, int first, int B, bool backward) {
     double bytes = 0;
-    for (int l = first; l <= c->plan.num_layers; ++l) {
-        const klay::LayerPlan& lay = c->plan.layers[(size_t)l];
-        const double below = (double)c->plan.layers[(size_t)l - 1].n;
-        if (!backward) bytes += 4.0 * B * ((double)lay.e + (double)lay.n) + 4.0 * ((double)lay.e + (double)lay.n);
+    for (int l = first; l < (int)t.n.size(); ++l) {
+        const double n = (double)t.n[(size_t)l], e = (double)t.e[(size_t)l], below = (double)t.kept[(size_t)l - 1];
+        if (!backward) bytes += 4.0 * B * (e + n) + 4.0 * (e + n);
         else if (l > first) {
             const bool is_and = (l & 1) != 0;
-            bytes += 4.0 * B * ((is_and ? 1.0 : 2.0) * (double)lay.e + (is_and ? 1.0 : 2.0) * below) +
-                     4.0 * ((double)lay.e + below);
+            bytes += 4.0 * B * ((is_and ? 1.0 : 2.0) * e + (is_and ? 1.0 : 2.0) * below) + 4.0 * (e + below);
         }
     }
     return bytes;
@@ -1014,13 +1202,10 @@ double tail_alg_bytes(const klay_circuit* c, int first, int B, bool backward) {
 
 // what a persistent launch has to move through memory: the values it writes (forward) or reads (reverse)
 // once, its index vectors, the rows it reads from or leaves in the activation buffer
-double tail_min_bytes(const klay_circuit* c, int first, int B, bool backward) {
+double tail_min_bytes(const ColTail& t, int first, int B, bool backward) {
     double bytes = 0;
-    for (int l = first; l <= c->plan.num_layers; ++l) {
-        const klay::LayerPlan& lay = c->plan.layers[(size_t)l];
-        bytes += 4.0 * B * (double)lay.n + 4.0 * (double)(backward ? lay.col_bwd.blocks.size() : lay.col_fwd.blocks.size());
-    }
-    bytes += 4.0 * B * (double)(backward ? c->plan.layers[(size_t)first].n : c->plan.layers[(size_t)first - 1].n);
+    for (int l = first; l < (int)t.n.size(); ++l) bytes += 4.0 * B * (double)t.kept[(size_t)l] + 4.0 * (double)t.words[backward][(size_t)l];
+    bytes += 4.0 * B * (double)(backward ? t.kept[(size_t)first] : t.n[(size_t)first - 1]);
     return bytes;
 }
 
@@ -1426,6 +1611,12 @@ klay_status klay_build_ex(int32_t num_vars, int64_t num_nodes, const uint8_t* no
         const klay::CircuitPlan& p = c->plan;
         c->tail_rows = p.col_rows;
     }
+    try {
+        describe_tails(c.get());
+    } catch (const std::bad_alloc&) {
+        return fail(KLAY_ENOMEM, "klay_build: out of host memory");
+    }
+    const bool persistent = c->tail.first > 0 || c->top.first > 0;
     if (device >= 0) {
         int ndev = 0;
         if (hipGetDeviceCount(&ndev) != hipSuccess || device >= ndev) {
@@ -1442,10 +1633,10 @@ klay_status klay_build_ex(int32_t num_vars, int64_t num_nodes, const uint8_t* no
             if (c->d_index) (void)hipFree(c->d_index);
             return st;
         }
-        c->tail_lds_bytes = c->plan.tail_first > 0 ? enable_tail_lds() : 0;
+        c->tail_lds_bytes = persistent ? enable_tail_lds() : 0;
     } else {
         // a host-only handle sizes workspaces for a device that grants the whole LDS of a compute unit
-        c->tail_lds_bytes = c->plan.tail_first > 0 ? kTailLdsMax : 0;
+        c->tail_lds_bytes = persistent ? kTailLdsMax : 0;
     }
     *out = c.release();
     return KLAY_OK;
@@ -1656,9 +1847,9 @@ static klay_status forward_impl(klay_circuit* c, const float* leaf_weights, cons
     if (static_ws) {
         with_bwd = false;
         lay = workspace_layout(c, B, false);
-        if (lay.total * sizeof(float) > kStaticWorkspaceBytes)
+        if (lay.counted * sizeof(float) > kStaticWorkspaceBytes)
             return fail(KLAY_ENOMEM, "klay_forward_static: this circuit at B = " + std::to_string(B) + " needs " +
-                                         std::to_string(lay.total * sizeof(float)) + " workspace bytes, the fixed buffer holds " +
+                                         std::to_string(lay.counted * sizeof(float)) + " workspace bytes, the fixed buffer holds " +
                                          std::to_string(kStaticWorkspaceBytes));
         KLAY_HIP(static_workspace(c->device, &ws));
     } else {
@@ -1676,8 +1867,9 @@ static klay_status forward_impl(klay_circuit* c, const float* leaf_weights, cons
 
     // the top layers run in one persistent kernel; when that kernel starts at layer 1 it evaluates the
     // leaf layer itself (a workgroup reads its own rows of the weight arrays)
-    const TailChoice tail = choose_tail_fwd(c, B);
-    const bool fused_leaf = tail.first == 1;
+    const int top_first = choose_top(c, B);
+    const TailChoice tail = top_first > 0 ? TailChoice() : choose_tail_fwd(c, B);
+    const bool fused_leaf = tail.first == 1 || top_first == 1;
 
     // leaf layer
     if (!fused_leaf) {
@@ -1706,7 +1898,7 @@ static klay_status forward_impl(klay_circuit* c, const float* leaf_weights, cons
     // needs every value, so this pass writes them all (klay_backward would otherwise evaluate the fused rows first).
     const bool fused = g.w == 64 && g.vec >= 2 && p.num_fused > 0 && !c->no_fusion &&
                        (static_ws || !c->bwd_followed);
-    const int last_regular = tail.first > 0 ? tail.first - 1 : L;
+    const int last_regular = top_first > 0 ? top_first - 1 : tail.first > 0 ? tail.first - 1 : L;
     for (int l = 1; l <= last_regular; ++l) {
         const DevLayer& d = c->dl[(size_t)l];
         const bool is_and = (l & 1) != 0;
@@ -1728,7 +1920,7 @@ static klay_status forward_impl(klay_circuit* c, const float* leaf_weights, cons
         }
     }
 
-    if (tail.first > 0) {
+    if (tail.first > 0 || top_first > 0) {
         // the persistent kernel also writes out[B, R]: the top layer is in its LDS
         klay::SlabLeaf leaf{};
         if (fused_leaf) {
@@ -1740,9 +1932,14 @@ static klay_status forward_impl(klay_circuit* c, const float* leaf_weights, cons
             leaf.V = V;
             leaf.n0 = (int32_t)p.layers[0].n;
         }
-        prof.begin(KLAY_K_TAIL_FWD, tail_alg_bytes(c, tail.first, B, false) + 8.0 * B * p.num_roots,
-                   tail_min_bytes(c, tail.first, B, false) + 4.0 * B * p.num_roots);
-        launch_tail_fwd(c, tail, act, ws + lay.tb, !static_ws, B, g.ld, (int)semiring, leaf, out, s);
+        const ColTail& which = top_first > 0 ? c->top : c->tail;
+        const int first = top_first > 0 ? top_first : tail.first;
+        prof.begin(KLAY_K_TAIL_FWD, tail_alg_bytes(which, first, B, false) + 8.0 * B * p.num_roots,
+                   tail_min_bytes(which, first, B, false) + 4.0 * B * p.num_roots);
+        if (top_first > 0)
+            launch_top_fwd(c, top_first, act, ws + lay.top_stage, static_ws ? nullptr : ws + lay.top_tb, B, g.ld, (int)semiring, leaf, out, s);
+        else
+            launch_tail_fwd(c, tail, act, ws + lay.tb, !static_ws, B, g.ld, (int)semiring, leaf, out, s);
         prof.end();
     } else {
         prof.begin(KLAY_K_ROOT, 8.0 * B * p.num_roots);
@@ -1761,6 +1958,7 @@ static klay_status forward_impl(klay_circuit* c, const float* leaf_weights, cons
     c->last_neg_explicit = neg_weights != nullptr;
     c->last_ws_has_bwd = with_bwd;
     c->last_tail_first = tail.first;
+    c->last_top_first = top_first;
     const TailBuffer buf = tail.first > 0 ? tail_buffer(c, tail, B) : TailBuffer();
     c->last_tail_T = (int32_t)buf.T;
     c->last_tail_staged = buf.at >= 0;
@@ -1841,18 +2039,25 @@ static klay_status backward_impl(klay_circuit* c, const float* dout, float* dlea
             res.mode = lits ? 2 : (real ? 0 : 1);
         } else {
             res.g_cols = cols;
+            res.g_T = res.n_last;
         }
-        prof.begin(KLAY_K_TAIL_BWD, tail_alg_bytes(c, first, B, true) + 4.0 * B * R, tail_min_bytes(c, first, B, true) + 4.0 * B * R);
-        launch_tail_bwd(c, last, last > 0 ? (int)p.col_off[(size_t)last] : -1, ws + lay.tb, c->last_tail_T, dout, top_multi, res,
+        prof.begin(KLAY_K_TAIL_BWD, tail_alg_bytes(c->tail, first, B, true) + 4.0 * B * R, tail_min_bytes(c->tail, first, B, true) + 4.0 * B * R);
+        launch_tail_bwd(c, c->tail, last, last > 0 ? (int)p.col_off[(size_t)last] : -1, ws + lay.tb, c->last_tail_T, dout, top_multi, res,
                         real_args, B, g.ld, s);
         if (last > 0) {
             dim3 tgrid((unsigned)((res.n_last + 31) / 32), (unsigned)((g.ld + 31) / 32));
-            hipLaunchKernelGGL(klay::tb_to_rows_kernel, tgrid, dim3(256), 0, s, cols, res.n_last, 0, res.n_last, B, g.ld,
-                               last == B0 ? grow(B0) : gcur);
+            hipLaunchKernelGGL(klay::tb_to_rows_kernel<false>, tgrid, dim3(256), 0, s, cols, res.n_last, 0, res.n_last, B, g.ld,
+                               last == B0 ? grow(B0) : gcur, (const int32_t*)nullptr);
         }
         prof.end();
         return last;
     };
+
+    const bool one = kOneGather && c->one_gather;
+    if (c->last_top_first > 0 && (real || !one)) {
+        // this sweep runs layer by layer on rows of the activation buffer
+        launch_top_to_rows(c, c->last_top_first, L, ws + lay.top_tb, act, B, g.ld, s);
+    }
 
     if (real) {
         // Real semiring: a sum layer passes adjoints through (plain by-child sums).  For a product layer
@@ -1929,14 +2134,47 @@ static klay_status backward_impl(klay_circuit* c, const float* dout, float* dlea
         // step that produces them (OP_SUM_H, the seed, or the persistent kernel's last write) folds the
         // node's own value in, and the step through the OR layer (OP_SOFTMAX_H) gathers that one row per
         // edge instead of the adjoint row and the parent's value row.
-        const bool one = kOneGather && c->one_gather;
         auto encoded = [&](int l) { return one && l >= 2 && (l & 1) == 0 && c->dl[(size_t)l].has_multi; };
 
         // The layers the forward pass ran in the persistent kernel are swept by its reverse counterpart, which
         // seeds the adjoints itself.  Where it can it also takes the step into the layer below them: to the leaves,
         // whose gradients it then writes itself, or into a layer whose values are in the column-major buffer.
-        int top = L;
+        int top = L, low = B0 - 1;        // the layers top .. B0 + 1 one by one, then the rows of the layers low .. 0
         const int first = c->last_tail_first;
+        if (one && c->last_top_first > 0) {
+            // the levels of a TopPlan down to its first one, whose adjoints and those above it (as far as they have rows) go
+            // to their rows; the launches go on below.  From layer 1 on it takes the step to the leaves, too.
+            const int top_first = c->last_top_first;
+            klay::ColBwdOut res{};
+            int last = top_first;
+            if (top_first == 1) {
+                last = 0;
+                res.wT = wT;
+                res.pos_row = c->d_pos_row;
+                res.neg_row = c->d_neg_row;
+                res.dleaf = dleaf;
+                res.dneg = dneg;
+                res.V = V;
+                res.mode = lits ? 2 : 1;
+            } else {
+                res.keep = ws + lay.top_g;
+                res.keep_from = L - B0;
+                res.g_cols = ws + lay.top_g + c->top.at[(size_t)last];
+                res.g_T = (int32_t)c->top.rows;
+            }
+            res.n_last = (int32_t)c->top.kept[(size_t)last];
+            prof.begin(KLAY_K_TAIL_BWD, tail_alg_bytes(c->top, top_first, B, true) + 4.0 * B * R, tail_min_bytes(c->top, top_first, B, true) + 4.0 * B * R);
+            launch_tail_bwd(c, c->top, last, last > 0 ? (int)c->top.at[(size_t)last] : -1, ws + lay.top_tb, (int)c->top.rows, dout, c->top.multi, res,
+                            nullptr, B, g.ld, s);
+            if (last > 0) launch_top_to_rows(c, last, B0, ws + lay.top_g, G, B, g.ld, s);
+            prof.end();
+            if (last == 0) {
+                KLAY_HIP(hipGetLastError());
+                return KLAY_OK;
+            }
+            top = B0;
+            low = last - 1;
+        } else
         // (its adjoints of OR nodes are in the one-gather form throughout, so it needs that form to be in use)
         if (one && first > 0) {
             top = tail_sweep(encoded(L) ? c->dl[(size_t)L].multi : nullptr, nullptr);
@@ -1974,7 +2212,7 @@ static klay_status backward_impl(klay_circuit* c, const float* dout, float* dlea
             }
             std::swap(gcur, gnext);
         }
-        for (int l = B0 - 1; l >= 0; --l) {
+        for (int l = low; l >= 0; --l) {
             // rows of even layers are OR nodes, whose parents are AND nodes (plain sums; encoded on the way
             // out where the node has more than one child); rows of odd layers and leaves read weighted edges
             const DevPass& dp = c->dl[(size_t)l + 1].bwd;

@@ -1258,12 +1258,12 @@ struct SlabLeaf {
 
 // LDS: two value arrays, slots kColSlots + position; size0 floats for the layer below the first one and every second
 // layer from there, the rest for the others.  start_rows / start_at: the layer below the first one (start_rows of them),
-// column-major, T floats a column, from entry start_at on if start_T > 0, otherwise rows of the activation buffer.
+// column-major, start_T floats a column, if start_T > 0 (and start_map is null), otherwise rows of the activation buffer (start_map[i], or null: one after another).
 // tb (or null): every layer's values are kept there.  CT: columns of a workgroup.
 template <int CT>
 __global__ __launch_bounds__(kColThreads) void col_fwd_kernel(const ColLayer* __restrict__ first, int n_layers, int first_is_and,
                                                               const Line* __restrict__ blocks, int n_blocks, const Desc* __restrict__ tables,
-                                                              const float* __restrict__ start, int start_rows, int start_T,
+                                                              const float* __restrict__ start, int start_rows, int start_T, const int32_t* __restrict__ start_map,
                                                               int B, int ld, int semiring, int size0, float* __restrict__ tb, int T,
                                                               SlabLeaf leaf, const int32_t* __restrict__ root_pos, int R,
                                                               float* __restrict__ out) {
@@ -1319,6 +1319,13 @@ __global__ __launch_bounds__(kColThreads) void col_fwd_kernel(const ColLayer* __
                     if (col == B - 1)
                         for (int b = B; b < ld; ++b) leaf.wT[(size_t)v * ld + b] = 0.0f;
                 }
+    } else if (start_map) {
+        for (int i = threadIdx.x; i < start_rows; i += kColThreads) {
+            float* slot = reinterpret_cast<float*>(below + kColSlots + i);
+            const size_t row = (size_t)start_map[i] * ld + col0;
+#pragma unroll
+            for (int c = 0; c < CT; ++c) slot[c] = start[row + (c < columns ? c : columns - 1)];
+        }
     } else {
         for (int i = threadIdx.x; i < start_rows; i += kColThreads) {
             float* slot = reinterpret_cast<float*>(below + kColSlots + i);
@@ -1521,11 +1528,13 @@ __device__ __forceinline__ void col_bwd_layer(ColWalk& walk, const V* above, V* 
 }
 
 // Where the reverse kernel leaves its last layer's adjoints: the leaf gradients themselves (w_T != null, the last
-// layer is layer 0), or g_cols[B][n_last], column-major (a lane owns rows of one column, so row-major stores would be
+// layer is layer 0), or g_cols[B][g_T], column-major (a lane owns rows of one column, so row-major stores would be
 // 4 bytes per cache line; tb_to_rows_kernel transposes afterwards).
 struct ColBwdOut {
     float* g_cols;
-    int32_t n_last;
+    int32_t g_T, n_last;        // g_T: floats in a column of g_cols
+    float* keep;                // TopPlan: column-major buffer, as tb, that takes the adjoints of every layer from the keep_from-th below the top one on
+    int32_t keep_from;
     const float* wT;            // [V, ld] transposed leaf weights
     const int32_t *pos_row, *neg_row;
     float *dleaf, *dneg;
@@ -1598,7 +1607,8 @@ __device__ __forceinline__ void col_load(V* to, const float* from, ColColumns co
         for (int c = 0; c < CT; ++c) reinterpret_cast<float*>(to + rest)[c] = from[column(c) + rest];
 }
 
-template <int CT, bool REAL>
+// KEEP: ColBwdOut::keep takes the adjoints of every layer, by a wave that does nothing else (see col_fwd_kernel).
+template <int CT, bool REAL, bool KEEP>
 __global__ __launch_bounds__(kColThreads) void col_bwd_kernel(const ColLayer* __restrict__ top, int n_steps, int last_at,
                                                               int top_is_and, const Line* __restrict__ blocks, int n_blocks,
                                                               const Desc* __restrict__ tables, const float* __restrict__ dout,
@@ -1659,6 +1669,12 @@ __global__ __launch_bounds__(kColThreads) void col_bwd_kernel(const ColLayer* __
             for (int c = 0; c < CT; ++c) reinterpret_cast<float*>(to + kColSlots + i)[c] = from[c < columns ? c : columns - 1];
         }
     };
+    // t: depth of the one in hand under the top layer
+    const bool keeper = KEEP && wave == kTopBwdWaves;
+    auto keep_layer = [&](int t) {
+        if (t >= res.keep_from)
+            col_move<CT>(reinterpret_cast<const float*>(above + kColSlots), top[-t].n, res.keep + (size_t)col0 * T + top[-t].at, T, columns);
+    };
     int cache_low = 0;
     if (cached > 0) {
         // the cached layers follow one another in tb
@@ -1695,7 +1711,8 @@ __global__ __launch_bounds__(kColThreads) void col_bwd_kernel(const ColLayer* __
     for (; t + 1 < cached; ++t) {
         const V* owns = cache + (top[-1 - t].at - cache_low) - kColSlots;
         __syncthreads();
-        if (((t & 1) == 0) == (top_is_and != 0)) col_bwd_layer<REAL ? kRealAnd : kLogAnd>(walk, above, here, owns, ColRepair{});
+        if (keeper) keep_layer(t);
+        else if (((t & 1) == 0) == (top_is_and != 0)) col_bwd_layer<REAL ? kRealAnd : kLogAnd>(walk, above, here, owns, ColRepair{});
         else col_bwd_layer<REAL ? kRealOr : kLogOr>(walk, above, here, owns, repair_of(t + 1));
         V* tmp = above; above = here; here = tmp;
     }
@@ -1715,7 +1732,8 @@ __global__ __launch_bounds__(kColThreads) void col_bwd_kernel(const ColLayer* __
         }
         const V* owns = t < cached ? cache + (top[-1 - t].at - cache_low) - kColSlots : here;
         __syncthreads();
-        if (((t & 1) == 0) == (top_is_and != 0)) col_bwd_layer<REAL ? kRealAnd : kLogAnd>(walk, above, here, owns, ColRepair{});
+        if (keeper) keep_layer(t);
+        else if (((t & 1) == 0) == (top_is_and != 0)) col_bwd_layer<REAL ? kRealAnd : kLogAnd>(walk, above, here, owns, ColRepair{});
         else col_bwd_layer<REAL ? kRealOr : kLogOr>(walk, above, here, owns, repair_of(t + 1));
         __syncthreads();
         // the adjoints above are done with: their array takes the next step's own values
@@ -1742,7 +1760,7 @@ __global__ __launch_bounds__(kColThreads) void col_bwd_kernel(const ColLayer* __
     for (int c = 0; c < columns; ++c) {
         const int col = col0 + c;
         if (!res.wT) {
-            for (int r = threadIdx.x; r < res.n_last; r += kColThreads) res.g_cols[(size_t)col * res.n_last + r] = slots[r * CT + c];
+            for (int r = threadIdx.x; r < res.n_last; r += kColThreads) res.g_cols[(size_t)col * res.g_T + r] = slots[r * CT + c];
             continue;
         }
         for (int v = threadIdx.x; v < res.V; v += kColThreads) {
@@ -1759,17 +1777,18 @@ __global__ __launch_bounds__(kColThreads) void col_bwd_kernel(const ColLayer* __
     }
 }
 
-// cols[b * T + r] = rows[r, b] for r < n_rows, b < B: the rows of a layer of the activation buffer into the column-major
+// cols[b * T + r] = rows[r, b] (MAP: rows[map[r], b]) for r < n_rows, b < B: the rows of a layer of the activation buffer into the column-major
 // form in which a workgroup of the persistent forward kernel reads its column (32 x 32 tiles through LDS).
+template <bool MAP>
 __global__ __launch_bounds__(256) void rows_to_cols_kernel(const float* __restrict__ rows, int n_rows, int B, int ld,
-                                                           float* __restrict__ cols, int T) {
+                                                           float* __restrict__ cols, int T, const int32_t* __restrict__ map) {
     __shared__ float tile[32][33];
     const int r0 = blockIdx.x * 32, b0 = blockIdx.y * 32;
     const int tx = threadIdx.x & 31, ty = threadIdx.x >> 5;       // 32 x 8
 #pragma unroll
     for (int j = 0; j < 4; ++j) {
         const int r = r0 + ty + 8 * j, b = b0 + tx;
-        tile[ty + 8 * j][tx] = (r < n_rows && b < B) ? rows[(size_t)r * ld + b] : 0.0f;
+        tile[ty + 8 * j][tx] = (r < n_rows && b < B) ? rows[(size_t)(MAP ? map[r] : r) * ld + b] : 0.0f;
     }
     __syncthreads();
 #pragma unroll
@@ -1779,10 +1798,11 @@ __global__ __launch_bounds__(256) void rows_to_cols_kernel(const float* __restri
     }
 }
 
-// rows[r, b] = tb[b, first + r] for r < n_rows: values that the persistent forward kernel left in the
+// rows[r, b] (MAP: rows[map[r], b], where that is not negative) = tb[b, first + r] for r < n_rows: values that the persistent forward kernel left in the
 // column-major buffer, transposed into rows of the activation buffer through a 32 x 33 LDS tile.
+template <bool MAP>
 __global__ __launch_bounds__(256) void tb_to_rows_kernel(const float* __restrict__ tb, int T, int first, int n_rows,
-                                                         int B, int ld, float* __restrict__ rows) {
+                                                         int B, int ld, float* __restrict__ rows, const int32_t* __restrict__ map) {
     __shared__ float tile[32][33];
     const int r0 = blockIdx.x * 32, b0 = blockIdx.y * 32;
     const int tx = threadIdx.x & 31, ty = threadIdx.x >> 5;       // 32 x 8
@@ -1795,7 +1815,8 @@ __global__ __launch_bounds__(256) void tb_to_rows_kernel(const float* __restrict
 #pragma unroll
     for (int j = 0; j < 4; ++j) {
         const int r = r0 + ty + 8 * j, b = b0 + tx;
-        if (r < n_rows && b < ld) rows[(size_t)r * ld + b] = tile[tx][ty + 8 * j];
+        if (r < n_rows && b < ld)
+            if (const int row = MAP ? map[r] : r; row >= 0) rows[(size_t)row * ld + b] = tile[tx][ty + 8 * j];
     }
 }
 

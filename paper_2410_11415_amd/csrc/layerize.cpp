@@ -22,6 +22,9 @@ namespace {
 #endif
 constexpr int64_t kLatencyBoundEntries = 200000;     // see make_pass_plan
 constexpr int64_t kTaskMin = KLAY_TASK_MIN, kTaskMax = KLAY_TASK_MAX, kTaskDiv = KLAY_TASK_DIV;
+// The persistent kernels' rows of more parents than this come first in their layer.  (8, 16, 64 and no such limit measured on
+// 13 training steps: within 2%, 48 layers of 43000 nodes at B = 4 123.1 / 123.6 / 124.0 / 124.5 us)
+constexpr int32_t kManyParents = 16;
 enum : uint8_t { T_LIT = 0, T_AND = 1, T_OR = 2, T_TRUE = 3, T_FALSE = 4 };
 constexpr int ST_OK = 0, ST_INVAL = 1, ST_CYCLE = 2;
 
@@ -254,6 +257,7 @@ void make_cols(int64_t n, const int32_t* ptr, const int32_t* idx, const uint32_t
         for (; at < pieces.size() && used < waves; ++used) at = share_end(at, bound);
         if (at == pieces.size()) break;
     }
+    out.share = bound;
     const uint32_t pads = (uint32_t)pad | (uint32_t)pad << 16;
     size_t next = 0;
     for (int w = 0; w < kColWaves; ++w) {
@@ -525,12 +529,18 @@ int layerize(int32_t V, int64_t N, const uint8_t* node_type, const int32_t* node
     // persistent kernels can take (they need complete layers); B0 = 0 is the paper's layerization, B0 = L
     // has no chain nodes at all except the stand-ins that bring every root to the top layer.
     const int64_t rows_cap = opt.tail_rows_cap > 0 ? std::min<int64_t>(opt.tail_rows_cap, kTailRowsCap) : kTailRowsCap;
-    int32_t B0 = 0;
+    int32_t B0 = 0, top_first = 0;
     {
         std::vector<int64_t> full((size_t)L + 1, 0);       // layer sizes with all chain nodes
+        std::vector<int64_t> edges((size_t)L + 1, 0);      // and their edges
         for (int64_t c = 0; c < N; ++c)
-            if (reach[(size_t)c])
-                for (int32_t l = h[(size_t)c]; l <= need[(size_t)c]; ++l) ++full[(size_t)l];
+            if (reach[(size_t)c]) {
+                edges[(size_t)h[(size_t)c]] += child_ptr[c + 1] - child_ptr[c];
+                for (int32_t l = h[(size_t)c]; l <= need[(size_t)c]; ++l) {
+                    ++full[(size_t)l];
+                    edges[(size_t)l] += l > h[(size_t)c];
+                }
+            }
         if (opt.alias_chains) {
             B0 = L;
             if (!opt.no_tail) {
@@ -539,6 +549,14 @@ int layerize(int32_t V, int64_t N, const uint8_t* node_type, const int32_t* node
                        max_fan[(size_t)t - 1] <= kTailFanCap)
                     --t;
                 if (L - t + 1 >= 2) B0 = t - 1;            // a persistent kernel takes two layers or more
+                // further down rows are long (or a layer wide): the plan for those (TopPlan)
+                t = L + 1;
+                while (t - 1 >= 1 && full[(size_t)t - 1] <= rows_cap && full[(size_t)t - 2] <= rows_cap && edges[(size_t)t - 1] <= kTopEdges) --t;
+                int64_t stand_ins = 0;                      // of leaves
+                for (int64_t c = 0; c < N; ++c)
+                    if (reach[(size_t)c] && h[(size_t)c] == 0) stand_ins += need[(size_t)c];
+                if (t == 1 && stand_ins > kTopLeafStandIns) t = 2;
+                if (L - t + 1 >= 2 && t <= B0) top_first = t;
             }
         }
     }
@@ -560,6 +578,8 @@ int layerize(int32_t V, int64_t N, const uint8_t* node_type, const int32_t* node
             int64_t gates = 0;
             for (int64_t j = child_ptr[c]; j < child_ptr[c + 1]; ++j) gates += h[(size_t)child_idx[j]] > 0;
             cand[(size_t)c] = fi >= 1 && gates <= 1 && fi <= row_max;
+            // (a node that the persistent kernels may read or evaluate is written)
+            if (top_first > 0 && need[(size_t)c] >= top_first - 1) cand[(size_t)c] = 0;
         }
         // every parent has to be an OR row that stays short when it reads the children of its fused children
         for (int64_t p = 0; p < N; ++p) {
@@ -713,9 +733,6 @@ int layerize(int32_t V, int64_t N, const uint8_t* node_type, const int32_t* node
                     }
                 }
                 auto bucket = [](int32_t k) { int b = 0; while ((1 << b) < k) ++b; return b; };
-                // (8, 16, 64 and no such limit measured on 13 training steps: within 2%, 48 layers of 43000 nodes at B = 4
-                // 123.1 / 123.6 / 124.0 / 124.5 us)
-                constexpr int32_t kManyParents = 16;
                 std::stable_sort(order.begin(), order.end(), [&](int32_t a, int32_t b) {
                     const bool ma = fan_out[(size_t)a] > kManyParents, mb = fan_out[(size_t)b] > kManyParents;
                     if (ma != mb) return ma;
@@ -986,14 +1003,122 @@ int layerize(int32_t V, int64_t N, const uint8_t* node_type, const int32_t* node
     }
     plan.root_pos.resize((size_t)R);
     for (int32_t r = 0; r < R; ++r) plan.root_pos[(size_t)r] = at(roots[r], L);
-    {
-        const int64_t nt = plan.layers[(size_t)L].n;
-        plan.top_ptr.assign((size_t)nt + 1, 0);
-        plan.top_root.resize((size_t)R);
-        for (int32_t r = 0; r < R; ++r) ++plan.top_ptr[(size_t)plan.root_pos[(size_t)r] + 1];
-        for (int64_t i = 0; i < nt; ++i) plan.top_ptr[(size_t)i + 1] += plan.top_ptr[(size_t)i];
-        std::vector<int32_t> fill(plan.top_ptr.begin(), plan.top_ptr.end() - 1);
-        for (int32_t r = 0; r < R; ++r) plan.top_root[(size_t)fill[(size_t)plan.root_pos[(size_t)r]]++] = r;
+    // the roots that read each of the nt nodes of the top layer
+    auto roots_by_node = [&](int64_t nt, const std::vector<int32_t>& root_pos, std::vector<int32_t>& ptr, std::vector<int32_t>& root) {
+        ptr.assign((size_t)nt + 1, 0);
+        root.resize((size_t)R);
+        for (int32_t r = 0; r < R; ++r) ++ptr[(size_t)root_pos[(size_t)r] + 1];
+        for (int64_t i = 0; i < nt; ++i) ptr[(size_t)i + 1] += ptr[(size_t)i];
+        std::vector<int32_t> fill(ptr.begin(), ptr.end() - 1);
+        for (int32_t r = 0; r < R; ++r) root[(size_t)fill[(size_t)root_pos[(size_t)r]]++] = r;
+    };
+    roots_by_node(plan.layers[(size_t)L].n, plan.root_pos, plan.top_ptr, plan.top_root);
+    if (top_first > 0) {
+        // ------------------------------------------------------------ the narrow top with its chain nodes (TopPlan)
+        TopPlan& top = plan.top;
+        top.first = top_first;
+        top.levels.resize((size_t)(L - top_first + 2));
+        // slots: pos[base[c] + l] = position of node c (or of its stand-in) in level l
+        std::vector<int64_t> base((size_t)N, 0);
+        int64_t slots = 0;
+        for (int64_t c = 0; c < N; ++c)
+            if (reach[(size_t)c] && need[(size_t)c] >= top_first - 1) {
+                const int32_t low = std::max(h[(size_t)c], top_first - 1);
+                base[(size_t)c] = slots - low;
+                slots += need[(size_t)c] - low + 1;
+            }
+        std::vector<int32_t> pos((size_t)slots, -1);
+        auto slot = [&](int32_t c, int32_t l) -> int32_t& { return pos[(size_t)(base[(size_t)c] + l)]; };
+        std::vector<std::vector<int32_t>> nodes((size_t)L + 1);      // of each level, by id
+        for (int64_t c = 0; c < N; ++c)
+            if (reach[(size_t)c])
+                for (int32_t l = std::max(h[(size_t)c], top_first - 1); l <= need[(size_t)c]; ++l) nodes[(size_t)l].push_back((int32_t)c);
+        // f(child) for every child of c (of its stand-in) in level l
+        auto children = [&](int32_t c, int32_t l, auto f) {
+            if (l > h[(size_t)c]) f(c);
+            else for (int64_t j = child_ptr[c]; j < child_ptr[c + 1]; ++j) f(child_idx[j]);
+        };
+        auto fan_in = [&](int32_t c, int32_t l) -> int64_t { return l > h[(size_t)c] ? 1 : child_ptr[c + 1] - child_ptr[c]; };
+        auto bucket = [](int64_t k) { int b = 0; while ((int64_t)1 << b < k) ++b; return b; };
+        std::vector<int32_t> fan_out((size_t)N, 0);
+        for (int32_t l = top_first - 1; l <= L; ++l) {
+            TopPlan::Level& lev = top.level(l);
+            std::vector<int32_t>& order = nodes[(size_t)l];
+            // Rows that the reverse sweep leaves out come last.  Level 0 and the level below the plan are in the order of their
+            // activation rows; the others by length, as in the layers above alias_top.
+            auto left_out = [&](int32_t c) { return l < B0 && top_first > 1 && h[(size_t)c] < top_first; };
+            if (l < top_first) {
+                std::stable_sort(order.begin(), order.end(), [&](int32_t a, int32_t b) { return own_row(a) < own_row(b); });
+            } else {
+                if (l < L)
+                    for (int32_t p : nodes[(size_t)l + 1]) children(p, l + 1, [&](int32_t c) { ++fan_out[(size_t)c]; });
+                std::stable_sort(order.begin(), order.end(), [&](int32_t a, int32_t b) {
+                    if (left_out(a) != left_out(b)) return left_out(b);
+                    const bool ma = fan_out[(size_t)a] > kManyParents, mb = fan_out[(size_t)b] > kManyParents;
+                    if (ma != mb) return ma;
+                    const int ba = bucket(fan_in(a, l)), bb = bucket(fan_in(b, l));
+                    if (!ma && ba != bb) return ba > bb;
+                    return fan_out[(size_t)a] > fan_out[(size_t)b];
+                });
+                if (l < L)
+                    for (int32_t p : nodes[(size_t)l + 1]) children(p, l + 1, [&](int32_t c) { fan_out[(size_t)c] = 0; });
+            }
+            lev.n = (int64_t)order.size();
+            lev.at = top.rows;
+            for (int64_t r = 0; r < lev.n; ++r) {
+                const int32_t c = order[(size_t)r];
+                slot(c, l) = (int32_t)r;
+                lev.own.push_back(own_row(c));
+                lev.e += fan_in(c, l);
+                if (l < top_first || left_out(c)) continue;
+                ++lev.kept;
+                top.act_row.push_back(l >= B0 ? (int32_t)plan.row0[(size_t)l] + at(c, l) : l == h[(size_t)c] ? own_row(c) : -1);
+            }
+            if (l < top_first) {
+                lev.kept = lev.n;
+                continue;
+            }
+            top.rows += lev.kept;
+            lev.launches = plan.layers[(size_t)l].fwd.n_heavy > 0 ? 2 : 1;
+            // index vectors by parent, and by child over the kept rows of both levels
+            const TopPlan::Level& low = top.level(l - 1);
+            const bool is_and = (l & 1) != 0, down = l > top_first || top_first == 1;
+            std::vector<int32_t> fptr((size_t)lev.n + 1, 0), fsrc, bptr((size_t)low.kept + 1, 0);
+            fsrc.reserve((size_t)lev.e);
+            for (int64_t r = 0; r < lev.n; ++r) {
+                const size_t from = fsrc.size();
+                children(order[(size_t)r], l, [&](int32_t c) { fsrc.push_back(slot(c, l - 1)); });
+                std::sort(fsrc.begin() + (int64_t)from, fsrc.end());
+                fptr[(size_t)r + 1] = (int32_t)fsrc.size();
+            }
+            make_cols(lev.n, fptr.data(), fsrc.data(), nullptr, nullptr, kColFwdWaves, is_and ? kColPadAnd : kColPadOr,
+                      is_and ? kColFwdAnd : kColFwdOr, lev.fwd);
+            if (!down) continue;
+            for (int32_t s : fsrc)
+                if (s < low.kept) ++bptr[(size_t)s + 1];
+            for (int64_t i = 0; i < low.kept; ++i) bptr[(size_t)i + 1] += bptr[(size_t)i];
+            std::vector<int32_t> bsrc((size_t)bptr[(size_t)low.kept]), fill(bptr.begin(), bptr.end() - 1);
+            std::vector<uint32_t> flag(bsrc.size(), 0u), multi((size_t)(low.n + 31) / 32, 0u);
+            for (int64_t r = 0; r < lev.n; ++r)
+                for (int32_t j = fptr[(size_t)r]; j < fptr[(size_t)r + 1]; ++j) {
+                    const int32_t s = fsrc[(size_t)j];
+                    if (s >= low.kept) continue;
+                    flag[(size_t)fill[(size_t)s]] = !is_and && fptr[(size_t)r + 1] - fptr[(size_t)r] > 1 ? kWeightedEdge : 0u;
+                    bsrc[(size_t)fill[(size_t)s]++] = (int32_t)r;
+                }
+            if (is_and && l >= 3)
+                for (int64_t r = 0; r < low.n; ++r)
+                    if (fan_in(nodes[(size_t)l - 1][(size_t)r], l - 1) > 1) multi[(size_t)r >> 5] |= 1u << (r & 31);
+            make_cols(low.kept, bptr.data(), bsrc.data(), flag.data(), is_and && l >= 3 ? multi.data() : nullptr, kTopBwdWaves, kColPadAnd,
+                      is_and ? kColBwdAnd : kColBwdOr, lev.bwd);
+        }
+        const std::vector<int32_t>& last = nodes[(size_t)L];
+        top.multi.assign((last.size() + 31) / 32, 0u);
+        for (size_t r = 0; r < last.size(); ++r)
+            if (fan_in(last[r], L) > 1) top.multi[r >> 5] |= 1u << (r & 31);
+        top.root_pos.resize((size_t)R);
+        for (int32_t r = 0; r < R; ++r) top.root_pos[(size_t)r] = slot(roots[r], L);
+        roots_by_node((int64_t)last.size(), top.root_pos, top.top_ptr, top.top_root);
     }
     return ST_OK;
 }

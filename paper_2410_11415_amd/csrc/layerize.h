@@ -24,11 +24,17 @@ struct Options {
 
 // Layers at the top of the circuit with at most this many nodes are candidates for the persistent
 // kernels, which keep two layers of one batch column in LDS (values forward, adjoints in the reverse sweep):
-// 20000 rows is what two arrays in 160 KB hold.  A candidate layer has no row with more sources than kTailFanCap
-// (set when a lane walked a whole row; rows are cut over the lanes now, and a larger cap has not been measured); the nodes
-// below it may have any number of parents, up to kColRowEntries.
+// 20000 rows is what two arrays in 160 KB hold.  The layers above alias_top have no row with more sources than kTailFanCap;
+// the narrow layers of circuits with longer rows are a plan of their own (TopPlan), in which a layer has at most kTopEdges
+// edges.
 constexpr int64_t kTailRowsCap = 20000;
 constexpr int64_t kTailFanCap = 64;
+constexpr int64_t kTopEdges = 160000;
+// With more stand-ins of leaves than this the first layer is left to the launches: from layer 1 on the kernels evaluate the leaves
+// themselves and the reverse sweep has a row for every stand-in (8138 leaves, 23200 nodes in 30 layers, 120000 of these, us
+// at B = 64: forward 100, training step 200; from layer 2 on 89 and 179; 1120 leaves and 22000 of these: 125 and 286 against
+// 136 and 333).
+constexpr int64_t kTopLeafStandIns = 100000;
 
 // Waves of a workgroup of those kernels.
 constexpr int kColWaves = 16;
@@ -49,15 +55,17 @@ constexpr int kColWaves = 16;
 // The descriptors of a wave in a layer come in tables of 64: up to 63 runs and one of no rows (word 0 = 1: another
 // table follows, 0: the end).  The rows of a layer are cut into chunks and units by a shortest-path search over their
 // cost, and every wave gets a contiguous share of about the same cost, so that the waves reach the layer's barrier together.
-//   The forward kernel has one wave less for this: its last wave moves the values to the column-major buffer.
+//   The forward kernel has one wave less for this: its last wave moves the values to the column-major buffer.  So has
+// the reverse kernel over a TopPlan: it moves the adjoints.
 constexpr int kColSlots = 4, kColPadAnd = 0, kColPadOr = 1;
-constexpr int kColFwdWaves = kColWaves - 1, kColBwdWaves = kColWaves;
+constexpr int kColFwdWaves = kColWaves - 1, kColBwdWaves = kColWaves, kTopBwdWaves = kColWaves - 1;
 constexpr int kBlockWords = 512, kLineWords = 256, kDescWords = 2, kDescTable = 64;
 constexpr int64_t kColBlocksMax = (1 << 17) - 1;             // blocks of a unit: what the descriptor holds
 constexpr int64_t kColRowEntries = kColBlocksMax * 16 * 64;  // a row that takes a whole wave
 struct ColPlan {
     int32_t block_at[kColWaves + 1] = {}, table_at[kColWaves + 1] = {};   // first block / table of each wave
     std::vector<uint32_t> blocks, tables;
+    int64_t share = 0;               // bound on the cost of a wave's share (cycles)
 };
 
 // One gather-reduce pass set over a CSR whose rows are the outputs.
@@ -124,6 +132,30 @@ struct LayerPlan {
                                      // a fused AND child being replaced by its own children
 };
 
+// The narrow top of a circuit with long rows (power-law fan-ins), for the persistent kernels.  The layers of the circuit
+// plan itself stay padding-free there (a chain node would cost the ordinary launches a row for each layer it passes); this plan
+// holds the same nodes with the chain nodes that the kernels need, which exist only in their LDS.
+//   Level l holds the nodes of layer l and a stand-in for every lower node that is read from above l.  Its first `kept` rows are
+// those that the reverse sweep visits and whose values the forward kernel keeps; the rest are, at levels below alias_top, the
+// stand-ins of nodes below the plan, whose adjoints the launches below gather from the rows of their parents.
+struct TopPlan {
+    struct Level {
+        int64_t n = 0, kept = 0, e = 0;      // rows, rows kept, edges down to the level below
+        int64_t at = 0;                      // first entry in a column of the value buffer
+        int32_t launches = 0;                // kernel launches that the layer takes otherwise
+        std::vector<int32_t> own;            // activation row of the node a row stands for
+        ColPlan fwd, bwd;                    // bwd: the step into the level below (kept rows of both); empty at `first` unless that is 1
+    };
+    int32_t first = 0;                       // lowest layer it can take (0: there is no such plan)
+    std::vector<Level> levels;               // first - 1 .. num_layers
+    int64_t rows = 0;                        // kept rows of the levels first .. num_layers
+    std::vector<int32_t> act_row;            // [rows] the activation row whose value and adjoint a kept row is, or -1 (stand-ins that have none)
+    std::vector<uint32_t> multi;             // as LayerPlan::multi, rows of the top level
+    std::vector<int32_t> root_pos, top_ptr, top_root;    // as in CircuitPlan, positions in the top level
+    const Level& level(int32_t l) const { return levels[(size_t)(l - first + 1)]; }
+    Level& level(int32_t l) { return levels[(size_t)(l - first + 1)]; }
+};
+
 struct CircuitPlan {
     int32_t num_vars = 0, num_roots = 0, num_layers = 0;
     std::vector<LayerPlan> layers;       // 0 .. num_layers
@@ -151,6 +183,7 @@ struct CircuitPlan {
     bool alias = false;                  // alias_top > 0
     int64_t num_fused = 0;               // AND rows whose values the fused plans do not need
     std::vector<int64_t> row0;
+    TopPlan top;
 };
 
 // Status codes mirror klay_status (0 ok, 1 invalid, 2 cycle, 3 no memory).
