@@ -109,13 +109,13 @@ struct ColTail {
     int32_t n_blocks[2] = {0, 0};
     const klay::Desc* tables = nullptr;
     const int32_t *root_pos = nullptr, *top_ptr = nullptr, *top_root = nullptr;
+    std::vector<int32_t> launches;       // what the layers take otherwise
+    std::vector<int64_t> share;          // ColPlan::share of the forward streams
     // TopPlan only: activation row of every row (of level l from own_at[l] on), of every kept row; flags of the top level (null: no
-    // layer of OR nodes); what the layers take otherwise
+    // layer of OR nodes)
     const int32_t *own = nullptr, *act_row = nullptr;
     std::vector<int64_t> own_at;
     const uint32_t* multi = nullptr;
-    std::vector<int32_t> launches;
-    std::vector<int64_t> share;
 };
 
 struct Geometry {            // how a batch of B columns is mapped onto lanes
@@ -199,6 +199,8 @@ struct klay_circuit {
     int32_t last64_B = 0;
     int last64_semiring = 0;
     bool last64_neg_explicit = false;
+    const ColTail* last64_tail = nullptr;      // whose layers from last64_first on ran in the persistent kernel (null: none)
+    int32_t last64_first = 0;
     // profiling
     bool profiling = false;
     std::vector<EventRec> ev_fwd, ev_bwd;
@@ -529,6 +531,8 @@ void describe_tails(klay_circuit* c) {
             t.e[l] = lay.e;
             t.words[0][l] = (int64_t)lay.col_fwd.blocks.size();
             t.words[1][l] = (int64_t)lay.col_bwd.blocks.size();
+            t.launches[l] = lay.fwd.n_heavy > 0 ? 2 : 1;
+            t.share[l] = lay.col_fwd.share;
         }
     }
     if (p.top.first > 0) {
@@ -1038,7 +1042,9 @@ size_t enable_tail_lds() {
                                    reinterpret_cast<const void*>(&klay::col_bwd_kernel<2, false, false>), reinterpret_cast<const void*>(&klay::col_bwd_kernel<4, false, false>),
                                    reinterpret_cast<const void*>(&klay::col_bwd_kernel<1, true, false>), reinterpret_cast<const void*>(&klay::col_bwd_kernel<2, true, false>),
                                    reinterpret_cast<const void*>(&klay::col_bwd_kernel<4, true, false>), reinterpret_cast<const void*>(&klay::col_bwd_kernel<1, false, true>),
-                                   reinterpret_cast<const void*>(&klay::col_bwd_kernel<2, false, true>), reinterpret_cast<const void*>(&klay::col_bwd_kernel<4, false, true>)})
+                                   reinterpret_cast<const void*>(&klay::col_bwd_kernel<2, false, true>), reinterpret_cast<const void*>(&klay::col_bwd_kernel<4, false, true>),
+                                   reinterpret_cast<const void*>(&klay::f64::col_fwd_kernel), reinterpret_cast<const void*>(&klay::f64::col_bwd_kernel<false>),
+                                   reinterpret_cast<const void*>(&klay::f64::col_bwd_kernel<true>)})
             if (e == hipSuccess) e = hipFuncSetAttribute(kernel, hipFuncAttributeMaxDynamicSharedMemorySize, bytes);
         if (e == hipSuccess) return (size_t)bytes;
         (void)hipGetLastError();
@@ -1327,10 +1333,45 @@ void launch_prod_parent(const klay_circuit::RealLayer& r, int n, const float* be
 
 // ---- double-precision evaluation ---------------------------------------------------------------
 struct Workspace64 {
-    size_t act = 0, wT = 0, seg_rows = 0, g0 = 0, g1 = 0, g2 = 0, total = 0;   // offsets in doubles
+    size_t act = 0, wT = 0, seg_rows = 0, g0 = 0, g1 = 0, g2 = 0, tb = 0, gcols = 0, total = 0;   // offsets in doubles
 };
 
-Workspace64 workspace_layout64(const klay_circuit* c, int ld) {
+// The layers that the double-precision persistent kernels take at a batch of B: from `first` on (0: none), an odd layer, so that
+// the step below it is a plain sum that needs no values.  As choose_top (an OR layer's exponentials take the longer; a launch 4 us and
+// what it gathers and computes, 4e5 entries a us); the two directions take the same layers, and the reverse kernel has pairs of doubles
+// for every second one in the LDS.  From a TopPlan in part only up to 256 columns (92000 nodes with power-law fan-ins, training
+// step at B = 512 1667 us by launches, 1818 from layer 13 on).
+int choose64(const klay_circuit* c, const ColTail& t, int B) {
+    if (t.first <= 0 || c->tail_lds_bytes == 0) return 0;
+    const int L = c->plan.num_layers;
+    const bool top = &t == &c->top;
+    double inside = 0, outside = 0, best = 0;
+    int first = 0;
+    int64_t fwd[2] = {0, 0}, bwd[2] = {0, 0};
+    auto room = [](int64_t (&size)[2], int l, int64_t n) { size[l & 1] = std::max(size[l & 1], (n + klay::kColSlots + 3) / 4 * 4); };
+    room(fwd, L, t.n[(size_t)L]);
+    for (int l = L; l >= t.first; --l) {
+        room(bwd, l, t.kept[(size_t)l]);
+        room(fwd, l - 1, t.n[(size_t)l - 1]);
+        if (t.kept[(size_t)l] > (int64_t)klay::f64::kColOwn * klay::kColThreads) break;
+        const int64_t reverse = 2 * std::max(bwd[0], l == 1 ? (t.kept[0] + klay::kColSlots + 3) / 4 * 4 : 0) + bwd[1];
+        if ((size_t)std::max(fwd[0] + fwd[1], reverse) * sizeof(double) > c->tail_lds_bytes) break;
+        inside += (1900.0 + (l & 1 ? 1.0 : 3.0) * (double)t.share[(size_t)l]) / 2400.0;
+        outside += 4.0 * t.launches[(size_t)l] + (double)t.e[(size_t)l] * B / 4e5;
+        if ((l & 1) == 0 || l == L || (top && (l > c->plan.alias_top || (l > 1 && B > 256)))) continue;
+        // what a reverse sweep puts into rows: values and adjoints of all of them, or the adjoints of the first
+        const double transposed = l == 1 ? 0.0 : 4.0 + (double)(top ? 2 * (t.rows - t.at[(size_t)l]) : t.kept[(size_t)l]) * B * 4e-6;
+        const double saved = outside - ((B + 255) / 256) * (4.0 + inside) - transposed;
+        if (saved > best) {
+            best = saved;
+            first = l;
+        }
+    }
+    return first;
+}
+const ColTail& tail64(const klay_circuit* c) { return c->top.first > 0 ? c->top : c->tail; }
+
+Workspace64 workspace_layout64(const klay_circuit* c, int B, int ld) {
     const klay::CircuitPlan& p = c->plan;
     Workspace64 w;
     size_t off = 0;
@@ -1342,6 +1383,11 @@ Workspace64 workspace_layout64(const klay_circuit* c, int ld) {
     w.g0 = take((size_t)p.row0[(size_t)p.alias_top + 1] * ld);
     w.g1 = take((size_t)top_layer_rows(p) * ld);
     w.g2 = take((size_t)top_layer_rows(p) * ld);
+    // the persistent kernels' values, and the adjoints they leave to the launches, column-major
+    if (const int first = choose64(c, tail64(c), B); first > 0) {
+        w.tb = take((size_t)tail64(c).rows * B);
+        if (first > 1) w.gcols = take((size_t)tail64(c).rows * B);
+    }
     w.total = off;
     return w;
 }
@@ -1422,7 +1468,7 @@ klay_status forward64_impl(klay_circuit* c, const double* w, const double* wneg,
     const klay::CircuitPlan& p = c->plan;
     const int ld = B > 64 ? (B + 1) / 2 * 2 : B;       // even rows for two columns per lane
     c->have_fwd64 = false;
-    const Workspace64 lay = workspace_layout64(c, ld);
+    const Workspace64 lay = workspace_layout64(c, B, ld);
     const size_t bytes = lay.total * sizeof(double);
     if (bytes > c->ws64_bytes) {
         if (c->ws64) { KLAY_HIP(hipFree(c->ws64)); c->ws64 = nullptr; c->ws64_bytes = 0; }
@@ -1448,7 +1494,9 @@ klay_status forward64_impl(klay_circuit* c, const double* w, const double* wneg,
     if (c->false_row >= 0)
         hipLaunchKernelGGL(klay::f64::fill_row_kernel, row_grid, dim3(256), 0, s, act + (size_t)c->false_row * ld, ld,
                            log_domain ? (double)-INFINITY : 0.0);
-    for (int l = 1; l <= L; ++l) {
+    const ColTail& tail = tail64(c);
+    const int first = choose64(c, tail, B);
+    for (int l = 1; l <= (first > 0 ? first - 1 : L); ++l) {
         const DevLayer& d = c->dl[(size_t)l];
         const bool is_and = (l & 1) != 0;
         const int or_op = semiring == KLAY_MAXLOG ? klay::OP_MAX : klay::OP_LSE;
@@ -1457,13 +1505,26 @@ klay_status forward64_impl(klay_circuit* c, const double* w, const double* wneg,
         const double* below = l <= p.alias_top ? act : act + (size_t)c->dl[(size_t)l - 1].row0 * ld;
         run_pass_set64(op, op, d.fwd, below, nullptr, nullptr, act + (size_t)d.row0 * ld, seg_rows, B, ld, s);
     }
-    hipLaunchKernelGGL(klay::f64::root_out_kernel, dim3((unsigned)p.num_roots), dim3(256), 0, s,
-                       act + (size_t)c->dl[(size_t)L].row0 * ld, c->d_root_pos, (int)B, p.num_roots, ld, out);
+    if (first > 0) {
+        const bool top = &tail == &c->top;
+        int64_t size[2];
+        tail_lds(tail.n, first - 1, first - 1, size);
+        hipLaunchKernelGGL(klay::f64::col_fwd_kernel, dim3((unsigned)B), dim3(klay::kColThreads), (size_t)(size[0] + size[1]) * sizeof(double), s,
+                           tail.layers + (first - tail.first), L - first + 1, first & 1, tail.blocks[0], tail.n_blocks[0], tail.tables,
+                           top ? act : act + (size_t)c->dl[(size_t)first - 1].row0 * ld, (int)tail.n[(size_t)first - 1],
+                           top ? tail.own + tail.own_at[(size_t)first - 1] : nullptr, ld, (int)semiring, (int)size[0], ws + lay.tb, (int)tail.rows,
+                           tail.root_pos, p.num_roots, out);
+    } else {
+        hipLaunchKernelGGL(klay::f64::root_out_kernel, dim3((unsigned)p.num_roots), dim3(256), 0, s,
+                           act + (size_t)c->dl[(size_t)L].row0 * ld, c->d_root_pos, (int)B, p.num_roots, ld, out);
+    }
     KLAY_HIP(hipGetLastError());
     c->have_fwd64 = true;
     c->last64_B = B;
     c->last64_semiring = semiring;
     c->last64_neg_explicit = wneg != nullptr;
+    c->last64_tail = first > 0 ? &tail : nullptr;
+    c->last64_first = first;
     return KLAY_OK;
 }
 
@@ -1480,7 +1541,7 @@ klay_status backward64_impl(klay_circuit* c, const double* dout, double* dleaf, 
     hipStream_t s = static_cast<hipStream_t>(stream);
     const klay::CircuitPlan& p = c->plan;
     const int B = c->last64_B, ld = B > 64 ? (B + 1) / 2 * 2 : B;
-    const Workspace64 lay = workspace_layout64(c, ld);
+    const Workspace64 lay = workspace_layout64(c, B, ld);
     double* ws = static_cast<double*>(c->ws64);
     double* act = ws + lay.act;
     double* wT = ws + lay.wT;
@@ -1492,6 +1553,16 @@ klay_status backward64_impl(klay_circuit* c, const double* dout, double* dleaf, 
     const int leaf_mode = c->last64_neg_explicit ? 2 : (real ? 0 : 1);
     const dim3 leaf_grid((unsigned)std::max(V, 1), (unsigned)((B + 255) / 256));
     auto grow = [&](int l) { return G + (size_t)c->dl[(size_t)l].row0 * ld; };   // adjoint rows of a layer <= B0
+    // what the persistent kernel kept or left column-major, layers first .. last, into rows
+    auto to_rows = [&](const double* cols, int first, int last, double* rows) {
+        const ColTail& t = *c->last64_tail;
+        const int64_t from = t.at[(size_t)first], n = t.at[(size_t)last] + t.kept[(size_t)last] - from;
+        hipLaunchKernelGGL(klay::f64::cols_to_rows_kernel, dim3((unsigned)((n + 31) / 32), (unsigned)((ld + 31) / 32)), dim3(256), 0, s, cols, (int)t.rows,
+                           (int)from, (int)n, B, ld, rows, &t == &c->top ? t.act_row + from : nullptr);
+    };
+    const int tail_first = c->last64_tail ? c->last64_first : 0;
+    const bool top_plan = c->last64_tail == &c->top;
+    if (tail_first > 0 && real) to_rows(ws + lay.tb, tail_first, L, top_plan ? act : act + (size_t)c->dl[(size_t)tail_first].row0 * ld);
     // Same course as the fp32 sweep (see klay_backward's implementation): the layers above B0 one by one,
     // alternating between two buffers, the last of these steps writing the rows of layer B0 into G; then
     // the rows of the layers below B0, each gathering from its parents anywhere in G.
@@ -1528,9 +1599,50 @@ klay_status backward64_impl(klay_circuit* c, const double* dout, double* dleaf, 
             if (l & 1) prod_parent(l, act, grow(l));
         }
     } else {
-        hipLaunchKernelGGL(klay::f64::seed_kernel, dim3((unsigned)c->dl[(size_t)L].n), dim3(256), 0, s, dout, c->d_top_ptr,
-                           c->d_top_root, B, R, ld, L == B0 ? grow(L) : gcur);
-        for (int l = L; l > B0; --l) {
+        int from = L, low = B0 - 1;                  // the layers from .. B0 + 1 one by one, then the rows of the layers low .. 0
+        if (tail_first > 0) {
+            const ColTail& t = *c->last64_tail;
+            const int last = tail_first == 1 ? 0 : tail_first;
+            klay::f64::ColBwdOut res{};
+            res.n_last = (int32_t)t.kept[(size_t)last];
+            res.keep_from = L - B0;
+            if (last == 0) {
+                res.wT = wT;
+                res.pos_row = c->d_pos_row;
+                res.neg_row = c->d_neg_row;
+                res.dleaf = dleaf;
+                res.dneg = dneg;
+                res.V = V;
+                res.mode = leaf_mode;
+                res.ld = ld;
+            } else {
+                res.g_cols = ws + lay.gcols;
+            }
+            int64_t size[2] = {0, 0};
+            for (int l = last; l <= L; ++l) size[l & 1] = std::max(size[l & 1], (t.kept[(size_t)l] + klay::kColSlots + 3) / 4 * 4);
+            hipLaunchKernelGGL((last > 0 && top_plan ? klay::f64::col_bwd_kernel<true> : klay::f64::col_bwd_kernel<false>), dim3((unsigned)B),
+                               dim3(klay::kColThreads), (size_t)(2 * size[0] + size[1]) * sizeof(double), s, t.layers + (L - t.first), L - last,
+                               last > 0 ? (int)t.at[(size_t)last] : -1, L & 1, t.blocks[1], t.n_blocks[1], t.tables, dout, t.top_ptr, t.top_root, R,
+                               (int)(2 * size[0]), ws + lay.tb, (int)t.rows, res);
+            if (last == 0) {
+                KLAY_HIP(hipGetLastError());
+                return KLAY_OK;
+            }
+            if (top_plan) {
+                // the rows below gather from the adjoints and the values of their parents
+                to_rows(ws + lay.tb, last, B0, act);
+                to_rows(ws + lay.gcols, last, B0, G);
+                from = B0;
+                low = last - 1;
+            } else {
+                to_rows(ws + lay.gcols, last, last, gcur);
+                from = last;
+            }
+        } else {
+            hipLaunchKernelGGL(klay::f64::seed_kernel, dim3((unsigned)c->dl[(size_t)L].n), dim3(256), 0, s, dout, c->d_top_ptr,
+                               c->d_top_root, B, R, ld, L == B0 ? grow(L) : gcur);
+        }
+        for (int l = from; l > B0; --l) {
             const DevLayer& d = c->dl[(size_t)l];
             const DevLayer& below = c->dl[(size_t)l - 1];
             double* dst = l - 1 == B0 ? grow(B0) : gnext;
@@ -1541,7 +1653,7 @@ klay_status backward64_impl(klay_circuit* c, const double* dout, double* dleaf, 
                                act + (size_t)below.row0 * ld, dst, seg_rows, B, ld, s);
             std::swap(gcur, gnext);
         }
-        for (int l = B0 - 1; l >= 0; --l) {
+        for (int l = low; l >= 0; --l) {
             const DevPass& dp = c->dl[(size_t)l + 1].bwd;
             run_pass_set64(dp.has_weighted ? klay::OP_SOFTMAX_BWD : klay::OP_SUM, klay::OP_SUM, dp, G, act,
                            act + (size_t)c->dl[(size_t)l].row0 * ld, grow(l), seg_rows, B, ld, s);

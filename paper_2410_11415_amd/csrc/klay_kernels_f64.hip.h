@@ -1,6 +1,6 @@
 // Double-precision evaluation of the same launch plans (accuracy build): one generic gather-reduce
-// kernel, one or two batch columns per lane and as many rows per wave as that leaves room for, plus the small leaf / root / seed
-// kernels.  Same index arrays, same order of layers and the same split-row scheme as the fp32
+// kernel, one or two batch columns per lane and as many rows per wave as that leaves room for, persistent kernels for the narrow
+// layers, plus the small leaf / root / seed kernels.  Same index arrays, same order of layers and the same split-row scheme as the fp32
 // kernels (paper Section 4, Alg. 1 / Appendix C, Alg. 4); exp and log are the full-precision
 // library routines.  The rows are twice as long as in fp32 and OR layers pay a double-precision
 // exponential per edge.
@@ -273,6 +273,422 @@ __global__ void leaf_bwd_kernel(const double* __restrict__ g0, const double* __r
     }
     dleaf[(size_t)b * V + v] = d;
     if (mode == 2 && dneg) dneg[(size_t)b * V + v] = dn;
+}
+
+// ---------------------------------------------------------------------------------------------
+// Persistent kernels for the narrow layers, as the fp32 ones (see there; same streams of runs, one column per workgroup of 16
+// waves): a launch of pass_kernel over such a layer takes 4 to 7 us, of which the layer's arithmetic is a small part.  The
+// exponentials cost most here (a library exponential is about forty instructions), so a group of four entries that is padding in
+// all lanes is passed over, and a row of two entries takes one.
+//   The reverse kernel keeps the two-gather form of the softmax adjoint (a sum of G_r exp(N_c - N_r)): the rows of even layers (OR
+// nodes) are pairs (adjoint, value), those of odd layers a value that the adjoint replaces.
+//   us, a launch or two for every layer and now, forward and training step: 85000 nodes in 20 layers (the top 14 of them) at B = 33
+// 107 -> 84, 244 -> 203; 4500 nodes in 34 layers at B = 33 133 -> 58, 254 -> 125, at B = 512 208 -> 129, 411 -> 274; 20000 nodes
+// with power-law fan-ins in 16 layers at B = 100 154 -> 96, 263 -> 188.
+// ---------------------------------------------------------------------------------------------
+typedef double Pair __attribute__((ext_vector_type(2)));
+constexpr double kDblMax = 1.7976931348623157e308;
+__device__ __forceinline__ double finite(double m) { return fmin(fmax(m, -kDblMax), kDblMax); }
+
+template <int STEP>
+__device__ __forceinline__ double fly(double x) {
+    if (STEP < 4) {
+        const long long b = __double_as_longlong(x);
+        const float lo = klay::fly<STEP>(__int_as_float((int)b)), hi = klay::fly<STEP>(__int_as_float((int)(b >> 32)));
+        return __longlong_as_double((long long)(uint32_t)__float_as_int(lo) | (long long)__float_as_int(hi) << 32);
+    }
+    return __shfl_xor(x, 1 << STEP);
+}
+template <int OP>
+__device__ __forceinline__ double join(double a, double b) {
+    if (OP == OP_PROD) return a * b;
+    if (OP == OP_MAX || OP == OP_LSE) return fmax(a, b);          // (OP_LSE: the maxima)
+    return a + b;
+}
+template <int OP>
+__device__ __forceinline__ double col_fly(double x, int k) {
+    if (k >= 1) x = join<OP>(x, fly<0>(x));
+    if (k >= 2) x = join<OP>(x, fly<1>(x));
+    if (k >= 3) x = join<OP>(x, fly<2>(x));
+    if (k >= 4) x = join<OP>(x, fly<3>(x));
+    if (k >= 5) x = join<OP>(x, fly<4>(x));
+    if (k >= 6) x = join<OP>(x, fly<5>(x));
+    return x;
+}
+
+// Logsumexp: m = maximum so far (of those that are no NaN), s = sum of exp(x - finite(m)); a row with nothing above -inf is -inf, a
+// NaN in any other passes on (as in pass_kernel).
+__device__ __forceinline__ double lse_value(double m, double s) { return m == -INFINITY ? -INFINITY : m + log(s); }
+
+// rows of one entry, of two, of four
+template <int OP>
+__device__ __forceinline__ double col_one(double x) { return OP == OP_LSE || OP == OP_MAX ? fmax(x, -INFINITY) : x; }
+template <int OP>
+__device__ __forceinline__ double col_two(double x, double y) {
+    if (OP != OP_LSE) return OP == OP_MAX ? fmax(fmax(x, y), -INFINITY) : join<OP>(x, y);
+    return lse_value(fmax(fmax(x, y), -INFINITY), 1.0 + (x == y ? 1.0 : exp(-fabs(x - y))));
+}
+template <int OP>
+__device__ __forceinline__ double col_four(double x0, double x1, double x2, double x3) {
+    if (OP != OP_LSE) {
+        const double x = join<OP>(join<OP>(x0, x1), join<OP>(x2, x3));
+        return OP == OP_MAX ? fmax(x, -INFINITY) : x;
+    }
+    const double hi = fmax(fmax(fmax(x0, x1), fmax(x2, x3)), -INFINITY), m = finite(hi);
+    return lse_value(hi, (exp(x0 - m) + exp(x1 - m)) + (exp(x2 - m) + exp(x3 - m)));
+}
+
+template <int OP, int KIND>
+__device__ __forceinline__ void col_quarter(const double* below, uint32_t a, uint32_t b, double* out, int rows) {
+    const int lane = threadIdx.x & 63;
+    const double x0 = below[a & 0xFFFFu], x1 = below[a >> 16], x2 = below[b & 0xFFFFu], x3 = below[b >> 16];
+    if (KIND == 0) {
+        const double v[4] = {col_one<OP>(x0), col_one<OP>(x1), col_one<OP>(x2), col_one<OP>(x3)};
+#pragma unroll
+        for (int i = 0; i < 4; ++i)
+            if (lane + 64 * i < rows) out[64 * i] = v[i];
+    } else if (KIND == 1) {
+        const double v0 = col_two<OP>(x0, x1), v1 = col_two<OP>(x2, x3);
+        if (lane < rows) out[0] = v0;
+        if (lane + 64 < rows) out[64] = v1;
+    } else {
+        const double v = col_four<OP>(x0, x1, x2, x3);
+        if (lane < rows) out[0] = v;
+    }
+}
+
+// a run of kind 0, 1 or 2
+template <int OP, int KIND>
+__device__ __forceinline__ void col_fwd_short(ColWalk& walk, const double* below, double* out, int rows) {
+    constexpr int N = 4 >> KIND;                     // rows of a lane in a quarter of a block
+    out += threadIdx.x & 63;
+    for (; rows > 0; rows -= 256 * N, out += 256 * N) {
+        Line w0, w1;
+        walk.block(w0, w1);
+        col_quarter<OP, KIND>(below, w0.x, w0.y, out, rows);
+        if (rows > 64 * N) col_quarter<OP, KIND>(below, w0.z, w0.w, out + 64 * N, rows - 64 * N);
+        if (rows > 128 * N) {
+            col_quarter<OP, KIND>(below, w1.x, w1.y, out + 128 * N, rows - 128 * N);
+            if (rows > 192 * N) col_quarter<OP, KIND>(below, w1.z, w1.w, out + 192 * N, rows - 192 * N);
+        }
+    }
+}
+
+// four entries of a row that takes several lanes or lines, joined to what those before gave
+template <int OP>
+__device__ __forceinline__ void col_long4(const double* below, uint32_t a, uint32_t b, double& m, double& s) {
+    const double x0 = below[a & 0xFFFFu], x1 = below[a >> 16], x2 = below[b & 0xFFFFu], x3 = below[b >> 16];
+    if (OP == OP_LSE) {
+        const double hi = fmax(fmax(fmax(x0, x1), fmax(x2, x3)), m), m2 = finite(hi);
+        double t = (exp(x0 - m2) + exp(x1 - m2)) + (exp(x2 - m2) + exp(x3 - m2));
+        if (s != 0.0) t = fma(s, exp(m - m2), t);
+        s = t;
+        m = hi;
+    } else {
+        s = join<OP>(s, join<OP>(join<OP>(x0, x1), join<OP>(x2, x3)));
+    }
+}
+template <int OP>
+__device__ __forceinline__ void col_long(const double* below, Line w, uint32_t pads, double& m, double& s) {
+    col_long4<OP>(below, w.x, w.y, m, s);
+    if (__any(w.z != pads || w.w != pads)) col_long4<OP>(below, w.z, w.w, m, s);
+}
+
+template <int OP>
+__device__ __forceinline__ void col_fwd_layer(ColWalk& walk, const double* below, double* here, int pad) {
+    const int lane = threadIdx.x & 63;
+    const uint32_t pads = (uint32_t)pad | (uint32_t)pad << 16;
+    Desc table = walk.table();
+    ColRun run;
+    for (int i = 0; run.read(walk, table, i);) {
+        double* out = here + run.slot;
+        if (run.kind == 0) col_fwd_short<OP, 0>(walk, below, out, run.rows);
+        else if (run.kind == 1) col_fwd_short<OP, 1>(walk, below, out, run.rows);
+        else if (run.kind == 2) col_fwd_short<OP, 2>(walk, below, out, run.rows);
+        else {
+            const int r = lane >> run.k, per = 64 >> run.k;
+            const bool writes = (lane & ((1 << run.k) - 1)) == 0;
+            for (int rows = run.rows; rows > 0; rows -= per, out += per) {
+                double m = -INFINITY, s = OP == OP_LSE ? 0.0 : identity<OP>();
+                for (int b = 0; b < run.blocks; ++b) {
+                    Line w0, w1;
+                    walk.block(w0, w1);
+                    col_long<OP>(below, w0, pads, m, s);
+                    if (run.kind == 3) col_long<OP>(below, w1, pads, m, s);
+                }
+                if (OP == OP_LSE) {
+                    if (run.k > 0) {
+                        const double m2 = col_fly<OP_LSE>(m, run.k);
+                        s = col_fly<OP_SUM>(s == 0.0 ? 0.0 : s * exp(m - finite(m2)), run.k);
+                        m = m2;
+                    }
+                    s = lse_value(m, s);
+                } else {
+                    s = col_fly<OP>(s, run.k);
+                }
+                if (writes && r < rows) out[r] = s;
+            }
+        }
+    }
+}
+
+// a finished layer from LDS to the column-major buffer, by one wave (stride 2: the adjoints of pairs)
+template <int STRIDE>
+__device__ __forceinline__ void col_move(const double* values, int n, double* __restrict__ to) {
+#pragma unroll 8
+    for (int i = threadIdx.x & 63; i < n; i += 64) to[i] = values[(size_t)i * STRIDE];
+}
+
+// As the fp32 kernel of this name; start: rows of the activation buffer, start_map[i] or one after another.  tb: where the values
+// are kept, T doubles a column.
+__global__ __launch_bounds__(kColThreads) void col_fwd_kernel(const ColLayer* __restrict__ first, int n_layers, int first_is_and,
+                                                              const Line* __restrict__ blocks, int n_blocks, const Desc* __restrict__ tables,
+                                                              const double* __restrict__ start, int start_rows, const int32_t* __restrict__ start_map, int ld,
+                                                              int semiring, int size0, double* __restrict__ tb, int T,
+                                                              const int32_t* __restrict__ root_pos, int R, double* __restrict__ out) {
+    extern __shared__ double smem64[];
+    double* below = smem64;
+    double* here = below + size0;
+    const int lane = threadIdx.x & 63;
+    const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
+    const int col = (int)blockIdx.x;
+    const bool log_domain = semiring != 0;
+    ColWalk walk;
+    walk.start(blocks + (size_t)first->fwd_block[wave] * 128 + lane, tables + (size_t)first->fwd_table[wave] * kDescTable + lane);
+    if (gridDim.x >= 64) col_touch(blocks, n_blocks);
+    if (threadIdx.x < 2) {
+        double* a = threadIdx.x == 0 ? below : here;
+        a[kColPadAnd] = log_domain ? 0.0 : 1.0;
+        a[kColPadOr] = log_domain ? -INFINITY : 0.0;
+    }
+    for (int i = threadIdx.x; i < start_rows; i += kColThreads) below[kColSlots + i] = start[(size_t)(start_map ? start_map[i] : i) * ld + col];
+    double* tbc = tb + (size_t)col * T;
+    for (int t = 0; t < n_layers; ++t) {
+        const bool is_and = ((t & 1) == 0) == (first_is_and != 0);
+        __syncthreads();
+        if (wave == kColFwdWaves) {
+            if (t > 0) col_move<1>(below + kColSlots, first[t - 1].n, tbc + first[t - 1].at);
+        } else if (is_and) {
+            if (log_domain) col_fwd_layer<OP_SUM>(walk, below, here, kColPadAnd);
+            else col_fwd_layer<OP_PROD>(walk, below, here, kColPadAnd);
+        } else if (semiring == 1) col_fwd_layer<OP_LSE>(walk, below, here, kColPadOr);
+        else if (semiring == 2) col_fwd_layer<OP_MAX>(walk, below, here, kColPadOr);
+        else col_fwd_layer<OP_SUM>(walk, below, here, kColPadOr);
+        double* tmp = below; below = here; here = tmp;
+    }
+    __syncthreads();
+    if (wave == kColFwdWaves) col_move<1>(below + kColSlots, first[n_layers - 1].n, tbc + first[n_layers - 1].at);
+    for (int r = threadIdx.x; r < R; r += kColThreads) out[(size_t)col * R + r] = below[kColSlots + root_pos[r]];
+}
+
+// ---- reverse: rows of even layers are pairs, rows of odd layers single values
+template <bool OR> struct ColRows;
+template <> struct ColRows<true> {          // through an OR layer: from pairs into the rows of an AND layer
+    using Above = Pair;
+    using Here = double;
+    static __device__ __forceinline__ double own(const double* at) { return *at; }
+    static __device__ __forceinline__ void put(double* at, double g) { *at = g; }
+    static __device__ __forceinline__ double entry(const Pair* above, uint32_t e, double own) {
+        const Pair p = above[e & 0x7FFFu];
+        return !(e & 0x8000u) ? p.x : p.y == -INFINITY ? 0.0 : p.x * exp(own - p.y);
+    }
+};
+template <> struct ColRows<false> {         // through an AND layer: into pairs, whose value is there
+    using Above = double;
+    using Here = Pair;
+    static __device__ __forceinline__ double own(const Pair*) { return 0.0; }
+    static __device__ __forceinline__ void put(Pair* at, double g) { reinterpret_cast<double*>(at)[0] = g; }
+    static __device__ __forceinline__ double entry(const double* above, uint32_t e, double) { return above[e & 0x7FFFu]; }
+};
+
+template <bool OR, int KIND>
+__device__ __forceinline__ void col_bwd_quarter(const typename ColRows<OR>::Above* above, uint32_t a, uint32_t b, typename ColRows<OR>::Here* out, int rows) {
+    using Rows = ColRows<OR>;
+    constexpr int N = 4 >> KIND;
+    const int lane = threadIdx.x & 63;
+    const uint32_t e[4] = {a & 0xFFFFu, a >> 16, b & 0xFFFFu, b >> 16};
+    double v[4], own[N];
+#pragma unroll
+    for (int i = 0; i < N; ++i) own[i] = Rows::own(out + (lane + 64 * i < rows ? 64 * i : -lane));
+#pragma unroll
+    for (int i = 0; i < 4; ++i) v[i] = Rows::entry(above, e[i], own[i >> KIND]);
+#pragma unroll
+    for (int i = 0; i < N; ++i)
+        if (lane + 64 * i < rows) Rows::put(out + 64 * i, KIND == 0 ? v[i] : KIND == 1 ? v[2 * i] + v[2 * i + 1] : (v[0] + v[1]) + (v[2] + v[3]));
+}
+
+template <bool OR, int KIND>
+__device__ __forceinline__ void col_bwd_short(ColWalk& walk, const typename ColRows<OR>::Above* above, typename ColRows<OR>::Here* out, int rows) {
+    constexpr int N = 4 >> KIND;
+    out += threadIdx.x & 63;
+    for (; rows > 0; rows -= 256 * N, out += 256 * N) {
+        Line w0, w1;
+        walk.block(w0, w1);
+        col_bwd_quarter<OR, KIND>(above, w0.x, w0.y, out, rows);
+        if (rows > 64 * N) col_bwd_quarter<OR, KIND>(above, w0.z, w0.w, out + 64 * N, rows - 64 * N);
+        if (rows > 128 * N) {
+            col_bwd_quarter<OR, KIND>(above, w1.x, w1.y, out + 128 * N, rows - 128 * N);
+            if (rows > 192 * N) col_bwd_quarter<OR, KIND>(above, w1.z, w1.w, out + 192 * N, rows - 192 * N);
+        }
+    }
+}
+
+template <bool OR>
+__device__ __forceinline__ double col_bwd_line(const typename ColRows<OR>::Above* above, Line w, double own) {
+    using Rows = ColRows<OR>;
+    constexpr uint32_t pads = (uint32_t)kColPadAnd | (uint32_t)kColPadAnd << 16;
+    double s = (Rows::entry(above, w.x & 0xFFFFu, own) + Rows::entry(above, w.x >> 16, own)) + (Rows::entry(above, w.y & 0xFFFFu, own) + Rows::entry(above, w.y >> 16, own));
+    if (__any(w.z != pads || w.w != pads))
+        s += (Rows::entry(above, w.z & 0xFFFFu, own) + Rows::entry(above, w.z >> 16, own)) + (Rows::entry(above, w.w & 0xFFFFu, own) + Rows::entry(above, w.w >> 16, own));
+    return s;
+}
+
+template <bool OR>
+__device__ __forceinline__ void col_bwd_layer(ColWalk& walk, const typename ColRows<OR>::Above* above, typename ColRows<OR>::Here* here) {
+    using Rows = ColRows<OR>;
+    const int lane = threadIdx.x & 63;
+    Desc table = walk.table();
+    ColRun run;
+    for (int i = 0; run.read(walk, table, i);) {
+        typename Rows::Here* out = here + run.slot;
+        if (run.kind == 0) col_bwd_short<OR, 0>(walk, above, out, run.rows);
+        else if (run.kind == 1) col_bwd_short<OR, 1>(walk, above, out, run.rows);
+        else if (run.kind == 2) col_bwd_short<OR, 2>(walk, above, out, run.rows);
+        else {
+            const int r = lane >> run.k, per = 64 >> run.k;
+            const bool writes = (lane & ((1 << run.k) - 1)) == 0;
+            for (int rows = run.rows; rows > 0; rows -= per, out += per) {
+                const double own = Rows::own(out + (r < rows ? r : 0));
+                double s = 0.0;
+                for (int b = 0; b < run.blocks; ++b) {
+                    Line w0, w1;
+                    walk.block(w0, w1);
+                    double t = col_bwd_line<OR>(above, w0, own);
+                    if (run.kind == 3) t += col_bwd_line<OR>(above, w1, own);
+                    s += t;
+                }
+                s = col_fly<OP_SUM>(s, run.k);
+                if (writes && r < rows) Rows::put(out + r, s);
+            }
+        }
+    }
+}
+
+// Where the reverse kernel leaves the adjoints of its last layer: the leaf gradients (wT != null, the last layer is layer 0), or,
+// column-major, g_cols (T doubles a column, from `at` of a layer on).  KEEP: every layer's from the keep_from-th below the top one
+// on go there.
+struct ColBwdOut {
+    double* g_cols;
+    int32_t keep_from, n_last;
+    const double* wT;           // [V, ld]
+    const int32_t *pos_row, *neg_row;
+    double *dleaf, *dneg;
+    int32_t V, mode, ld;        // mode: as for leaf_bwd_kernel
+};
+
+// own values of a layer per thread (in registers, a step ahead): rows up to this many times 1024
+constexpr int kColOwn = 10;
+
+// Reverse sweep in the log semiring from the top layer down n_steps layers; the last one is an AND layer or layer 0.  LDS: `odd_at`
+// doubles of pairs for the even layers, then the odd layers.  tb: node values; those of the rows of a step are loaded during the
+// step before.
+template <bool KEEP>
+__global__ __launch_bounds__(kColThreads) void col_bwd_kernel(const ColLayer* __restrict__ top, int n_steps, int last_at, int top_is_and,
+                                                              const Line* __restrict__ blocks, int n_blocks, const Desc* __restrict__ tables,
+                                                              const double* __restrict__ dout, const int32_t* __restrict__ top_ptr,
+                                                              const int32_t* __restrict__ top_root, int R, int odd_at, const double* tb, int T, ColBwdOut res) {
+    extern __shared__ double smem64[];
+    Pair* const even = reinterpret_cast<Pair*>(smem64);
+    double* const odd = smem64 + odd_at;
+    const int lane = threadIdx.x & 63;
+    const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
+    const int col = (int)blockIdx.x;
+    const double* tbc = tb + (size_t)col * T;
+    ColWalk walk;
+    walk.start(blocks + (size_t)top->bwd_block[wave] * 128 + lane, tables + (size_t)top->bwd_table[wave] * kDescTable + lane);
+    if (gridDim.x >= 64) col_touch(blocks, n_blocks);
+    if (threadIdx.x == 0) {
+        even[kColPadAnd] = Pair{0.0, 0.0};
+        odd[kColPadAnd] = 0.0;
+    }
+    // own values of the rows of the t-th layer below the top one: how many and where (none for layer 0)
+    auto own_of = [&](int t, int& n, int& at) {
+        n = at = 0;
+        if (t < n_steps) { n = top[-t].n; at = top[-t].at; }
+        else if (t == n_steps && last_at >= 0) { n = res.n_last; at = last_at; }
+    };
+    auto is_odd = [&](int t) { return ((t & 1) == 0) == (top_is_and != 0); };
+    auto put_own = [&](int t, int i, double v) {
+        if (is_odd(t)) odd[kColSlots + i] = v;
+        else reinterpret_cast<double*>(even + kColSlots + i)[1] = v;
+    };
+    int n, at;
+    own_of(1, n, at);
+    for (int i = threadIdx.x; i < n; i += kColThreads) put_own(1, i, tbc[at + i]);
+    own_of(0, n, at);
+    for (int i = threadIdx.x; i < n; i += kColThreads) {      // adjoint seed of the top layer
+        double acc = 0.0;
+        for (int j = top_ptr[i]; j < top_ptr[i + 1]; ++j) acc += dout[(size_t)col * R + top_root[j]];
+        if (is_odd(0)) odd[kColSlots + i] = acc;
+        else even[kColSlots + i] = Pair{acc, tbc[at + i]};
+    }
+    auto keep_layer = [&](int t) {
+        if (t < res.keep_from) return;
+        double* to = res.g_cols + (size_t)col * T + top[-t].at;
+        if (is_odd(t)) col_move<1>(odd + kColSlots, top[-t].n, to);
+        else col_move<2>(reinterpret_cast<const double*>(even + kColSlots), top[-t].n, to);
+    };
+    for (int t = 0; t < n_steps; ++t) {
+        double own[kColOwn];
+        own_of(t + 2, n, at);
+#pragma unroll
+        for (int i = 0; i < kColOwn; ++i)
+            if (wave * 64 + i * kColThreads < n) own[i] = tbc[at + ((int)threadIdx.x + i * kColThreads < n ? (int)threadIdx.x + i * kColThreads : 0)];
+        __syncthreads();
+        if (KEEP && wave == kTopBwdWaves) keep_layer(t);
+        else if (is_odd(t)) col_bwd_layer<false>(walk, odd, even);
+        else col_bwd_layer<true>(walk, even, odd);
+        __syncthreads();
+#pragma unroll
+        for (int i = 0; i < kColOwn; ++i)
+            if ((int)threadIdx.x + i * kColThreads < n) put_own(t, (int)threadIdx.x + i * kColThreads, own[i]);
+    }
+    __syncthreads();
+    if (!res.wT) {
+        for (int r = threadIdx.x; r < res.n_last; r += kColThreads) res.g_cols[(size_t)col * T + last_at + r] = odd[kColSlots + r];
+        return;
+    }
+    for (int v = threadIdx.x; v < res.V; v += kColThreads) {
+        const int pr = res.pos_row[v], nr = res.neg_row[v];
+        double d = pr >= 0 ? even[kColSlots + pr].x : 0.0, dn = 0.0;
+        if (nr >= 0) {
+            const double gn = even[kColSlots + nr].x;
+            if (res.mode == 2) dn = gn;
+            else if (gn != 0.0) d += res.mode == 1 ? -gn / expm1(-res.wT[(size_t)v * res.ld + col]) : -gn;
+        }
+        res.dleaf[(size_t)col * res.V + v] = d;
+        if (res.mode == 2 && res.dneg) res.dneg[(size_t)col * res.V + v] = dn;
+    }
+}
+
+// rows[r, b] (map: rows[map[r], b], where that is not negative) = cols[b, first + r] for r < n_rows, through a 32 x 33 LDS tile
+__global__ __launch_bounds__(256) void cols_to_rows_kernel(const double* __restrict__ cols, int T, int first, int n_rows, int B, int ld,
+                                                           double* __restrict__ rows, const int32_t* __restrict__ map) {
+    __shared__ double tile[32][33];
+    const int r0 = blockIdx.x * 32, b0 = blockIdx.y * 32;
+    const int tx = threadIdx.x & 31, ty = threadIdx.x >> 5;       // 32 x 8
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+        const int b = b0 + ty + 8 * j, r = r0 + tx;
+        tile[ty + 8 * j][tx] = (b < B && r < n_rows) ? cols[(size_t)b * T + first + r] : 0.0;
+    }
+    __syncthreads();
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+        const int r = r0 + ty + 8 * j, b = b0 + tx;
+        if (r < n_rows && b < ld)
+            if (const int row = map ? map[r] : r; row >= 0) rows[(size_t)row * ld + b] = tile[tx][ty + 8 * j];
+    }
 }
 
 }  // namespace f64
