@@ -77,7 +77,7 @@ def kernel_symbol(cls, B, edges=False, fused_op=10):
              "leaf": "klay::leaf_fwd_kernel" if B > 32 else "klay::leaf_fwd_small_kernel", "bwd_leaf": "klay::leaf_bwd_kernel", "root": "klay::root_out_kernel",
              "seed": "klay::seed_kernel", "split": "klay::pass_kernel<*> (segments of split rows)",
              "combine": "klay::combine_kernel<*>" if B > 32 else "klay::combine_small_kernel<*>",
-             "main_combine": "klay::stream_combine_kernel<*>",
+             "main_combine": "klay::pass_combine_kernel<*>",
              "fwd_or_fused": "klay::stream_kernel<%d, %d>" % (fused_op, vec),
              "prod_edges": "klay::prod_parent_kernel<%d, %d>" % (vec, 64 if B > 32 else w_small)}
     return fixed.get(cls, cls)

@@ -107,7 +107,7 @@ typedef struct klay_info_t {
 /* Per-kernel-class timing of the most recent forward / backward call, filled only while
  * profiling is enabled.  Durations come from HIP events recorded on the caller's stream around
  * every single launch.  FWD_x / BWD_x are the main-row launches of a layer (one kernel each:
- * the streaming kernel for B > 32), SPLIT the segment launches of split rows, COMBINE their
+ * the streaming kernel for B > 64), SPLIT the segment launches of split rows, COMBINE their
  * combine launches, MAIN_COMBINE (any operation) the launches that take the main rows and the combine
  * rows of a layer together (32 < B <= 64, where the segments run in a launch of their own first),
  * FWD_OR_FUSED the forward launches of OR layers that read the children of fused AND rows (klay_options.no_fusion),

@@ -27,9 +27,9 @@ constexpr size_t kStaticWorkspaceBytes = KLAY_STATIC_WORKSPACE_BYTES;
 static __device__ __align__(256) unsigned char scratch[2 * kStaticWorkspaceBytes];
 
 // Layers with split rows and at most this many index entries run main rows and segments in one generic
-// launch (measured at B = 64 on the two power-law workloads, ms per step: this threshold 0.69 / 0.76, ten times
-// larger 0.66 / 0.80, every layer 0.68 / 0.92; with the layerization of unary chains throughout 60000 and
-// 150000 both gave 0.73 against 0.81 without the rule).
+// launch and the combine rows in another; larger ones the segments first, then main rows and combine rows.
+// (us with main rows and segments together throughout / this rule: the two power-law workloads of run_pass_set 914 / 882, 375 / 384; there
+// the segments are most of the work.)
 constexpr int64_t kSmallPassEntries = 100000;
 constexpr size_t kTailLdsMax = 160 * 1024;     // LDS of a gfx950 compute unit: the most a workgroup of the persistent kernels gets
 
@@ -75,6 +75,7 @@ struct DevPass {
     const uint32_t *idx = nullptr, *comb_idx = nullptr;
     int32_t n_main = 0, n_seg = 0, n_heavy = 0, n_tasks = 0, n_seg_tasks = 0;
     int32_t longest_comb = 0;                    // partial rows of the split row with most of them
+    int32_t n_comb_many = 0;                     // see PassPlan
     bool has_weighted = false;
     int64_t edges = 0;
     int64_t main_entries = 0, seg_entries = 0;   // index entries of light main rows / of segments
@@ -275,10 +276,9 @@ unsigned row_blocks(int64_t rows, int lanes) {
     return (unsigned)(((rows + per_block - 1) / per_block + 7) / 8 * 8);
 }
 
-// Launch one gather-reduce pass over `n_total` rows.
-void launch_pass(int op, klay::PassArgs a, hipStream_t s) {
+// Columns per lane of a generic launch over the rows row_begin .. n_total; sets the lanes per row.
+int deal_lanes(klay::PassArgs& a) {
     const int64_t rows = (int64_t)a.n_total - a.row_begin;
-    if (rows <= 0) return;
     // as many columns per lane as leave 8 waves for every compute unit: a smaller launch waits for its longest rows, and
     // a row takes less time the fewer columns a lane has
     int vec = a.B >= 4 ? 4 : (a.B >= 2 ? 2 : 1);
@@ -291,6 +291,14 @@ void launch_pass(int op, klay::PassArgs a, hipStream_t s) {
         for (a.lanes = 1; a.lanes < std::min(64, a.B); a.lanes *= 2) {}
     a.per_wave = 64 / a.lanes;
     a.inverse = row_inverse(a.lanes);
+    return vec;
+}
+
+// Launch one gather-reduce pass over `n_total` rows.
+void launch_pass(int op, klay::PassArgs a, hipStream_t s) {
+    const int64_t rows = (int64_t)a.n_total - a.row_begin;
+    if (rows <= 0) return;
+    const int vec = deal_lanes(a);
     dim3 grid(row_blocks(rows, a.lanes), (unsigned)((a.B + a.lanes * vec - 1) / (a.lanes * vec)));
     switch (op) {
     case klay::OP_SUM: launch_op<klay::OP_SUM>(a, vec, grid, s); break;
@@ -353,16 +361,15 @@ void launch_edge(int op, const DevPass& dp, const Geometry& g, const float* src,
     }
 }
 
-// Streaming kernel over the main rows of a pass and / or the segments of its split rows (batch
-// tiles of one wave: B > 32).  dst_seg is the base of the partial rows shifted by -n_main rows: segment rows are
+// Streaming kernel over the main rows of a pass and the segments of its split rows (batch
+// tiles of one wave, two or four columns per lane: B > 64).  dst_seg is the base of the partial rows shifted by -n_main rows: segment rows are
 // numbered after the main rows.
 template <int OP>
-void launch_stream_op(const DevPass& dp, bool main_rows, bool segments, const Geometry& g, const float* src,
+void launch_stream_op(const DevPass& dp, const Geometry& g, const float* src,
                       const float* src2, const float* own, float* dst, float* dst_seg, int B, hipStream_t s, int* zf) {
     const int2* tasks = reinterpret_cast<const int2*>(dp.tasks);
     const int2* seg_tasks = reinterpret_cast<const int2*>(dp.seg_tasks);
-    int n_tasks = main_rows ? dp.n_tasks : 0;
-    int n_seg_tasks = segments ? dp.n_seg_tasks : 0;
+    const int n_tasks = dp.n_tasks, n_seg_tasks = dp.n_seg_tasks;
     int64_t blocks = ((int64_t)n_tasks + n_seg_tasks + 3) / 4;
     blocks = (blocks + 7) / 8 * 8;
     // outputs larger than the L2s together (8 x 4 MB) are written with streaming stores
@@ -370,29 +377,27 @@ void launch_stream_op(const DevPass& dp, bool main_rows, bool segments, const Ge
     dim3 grid((unsigned)blocks, (unsigned)g.tiles);
     if (g.vec == 4)
         hipLaunchKernelGGL((klay::stream_kernel<OP, 4>), grid, dim3(256), 0, s, tasks, n_tasks, dp.idx, src, src2, own, dst, B, g.ld, nt, seg_tasks, n_seg_tasks, dst_seg, dp.seg_owner, dp.n_main, zf);
-    else if (g.vec == 2)
-        hipLaunchKernelGGL((klay::stream_kernel<OP, 2>), grid, dim3(256), 0, s, tasks, n_tasks, dp.idx, src, src2, own, dst, B, g.ld, nt, seg_tasks, n_seg_tasks, dst_seg, dp.seg_owner, dp.n_main, zf);
     else
-        hipLaunchKernelGGL((klay::stream_kernel<OP, 1>), grid, dim3(256), 0, s, tasks, n_tasks, dp.idx, src, src2, own, dst, B, g.ld, nt, seg_tasks, n_seg_tasks, dst_seg, dp.seg_owner, dp.n_main, zf);
+        hipLaunchKernelGGL((klay::stream_kernel<OP, 2>), grid, dim3(256), 0, s, tasks, n_tasks, dp.idx, src, src2, own, dst, B, g.ld, nt, seg_tasks, n_seg_tasks, dst_seg, dp.seg_owner, dp.n_main, zf);
 }
 
-void launch_stream(int op, const DevPass& dp, bool main_rows, bool segments, const Geometry& g, const float* src,
+void launch_stream(int op, const DevPass& dp, const Geometry& g, const float* src,
                    const float* src2, const float* own, float* dst, float* dst_seg, int B, hipStream_t s, int* zf) {
-    if ((main_rows ? dp.n_tasks : 0) + (segments ? dp.n_seg_tasks : 0) <= 0) return;
+    if (dp.n_tasks + dp.n_seg_tasks <= 0) return;
     switch (op) {
-    case klay::OP_SUM: launch_stream_op<klay::OP_SUM>(dp, main_rows, segments, g, src, src2, own, dst, dst_seg, B, s, zf); break;
-    case klay::OP_PROD: launch_stream_op<klay::OP_PROD>(dp, main_rows, segments, g, src, src2, own, dst, dst_seg, B, s, zf); break;
-    case klay::OP_LSE: launch_stream_op<klay::OP_LSE>(dp, main_rows, segments, g, src, src2, own, dst, dst_seg, B, s, zf); break;
-    case klay::OP_MAX: launch_stream_op<klay::OP_MAX>(dp, main_rows, segments, g, src, src2, own, dst, dst_seg, B, s, zf); break;
-    case klay::OP_PROD_BWD: launch_stream_op<klay::OP_PROD_BWD>(dp, main_rows, segments, g, src, src2, own, dst, dst_seg, B, s, zf); break;
-    case klay::OP_SUM_H: launch_stream_op<klay::OP_SUM_H>(dp, main_rows, segments, g, src, src2, own, dst, dst_seg, B, s, zf); break;
-    case klay::OP_SOFTMAX_H: launch_stream_op<klay::OP_SOFTMAX_H>(dp, main_rows, segments, g, src, src2, own, dst, dst_seg, B, s, zf); break;
-    case klay::OP_SUM_P: launch_stream_op<klay::OP_SUM_P>(dp, main_rows, segments, g, src, src2, own, dst, dst_seg, B, s, zf); break;
-    case klay::OP_PROD_BWD_P: launch_stream_op<klay::OP_PROD_BWD_P>(dp, main_rows, segments, g, src, src2, own, dst, dst_seg, B, s, zf); break;
-    case klay::OP_LSE2: launch_stream_op<klay::OP_LSE2>(dp, main_rows, segments, g, src, src2, own, dst, dst_seg, B, s, zf); break;
-    case klay::OP_MAX2: launch_stream_op<klay::OP_MAX2>(dp, main_rows, segments, g, src, src2, own, dst, dst_seg, B, s, zf); break;
-    case klay::OP_SUMPROD2: launch_stream_op<klay::OP_SUMPROD2>(dp, main_rows, segments, g, src, src2, own, dst, dst_seg, B, s, zf); break;
-    default: launch_stream_op<klay::OP_SOFTMAX_BWD>(dp, main_rows, segments, g, src, src2, own, dst, dst_seg, B, s, zf); break;
+    case klay::OP_SUM: launch_stream_op<klay::OP_SUM>(dp, g, src, src2, own, dst, dst_seg, B, s, zf); break;
+    case klay::OP_PROD: launch_stream_op<klay::OP_PROD>(dp, g, src, src2, own, dst, dst_seg, B, s, zf); break;
+    case klay::OP_LSE: launch_stream_op<klay::OP_LSE>(dp, g, src, src2, own, dst, dst_seg, B, s, zf); break;
+    case klay::OP_MAX: launch_stream_op<klay::OP_MAX>(dp, g, src, src2, own, dst, dst_seg, B, s, zf); break;
+    case klay::OP_PROD_BWD: launch_stream_op<klay::OP_PROD_BWD>(dp, g, src, src2, own, dst, dst_seg, B, s, zf); break;
+    case klay::OP_SUM_H: launch_stream_op<klay::OP_SUM_H>(dp, g, src, src2, own, dst, dst_seg, B, s, zf); break;
+    case klay::OP_SOFTMAX_H: launch_stream_op<klay::OP_SOFTMAX_H>(dp, g, src, src2, own, dst, dst_seg, B, s, zf); break;
+    case klay::OP_SUM_P: launch_stream_op<klay::OP_SUM_P>(dp, g, src, src2, own, dst, dst_seg, B, s, zf); break;
+    case klay::OP_PROD_BWD_P: launch_stream_op<klay::OP_PROD_BWD_P>(dp, g, src, src2, own, dst, dst_seg, B, s, zf); break;
+    case klay::OP_LSE2: launch_stream_op<klay::OP_LSE2>(dp, g, src, src2, own, dst, dst_seg, B, s, zf); break;
+    case klay::OP_MAX2: launch_stream_op<klay::OP_MAX2>(dp, g, src, src2, own, dst, dst_seg, B, s, zf); break;
+    case klay::OP_SUMPROD2: launch_stream_op<klay::OP_SUMPROD2>(dp, g, src, src2, own, dst, dst_seg, B, s, zf); break;
+    default: launch_stream_op<klay::OP_SOFTMAX_BWD>(dp, g, src, src2, own, dst, dst_seg, B, s, zf); break;
     }
 }
 
@@ -499,6 +504,7 @@ void bind_pass(DevPass& d, const klay::PassPlan& p, const PassOffsets& o, const 
     d.n_main = p.n_main;
     d.n_seg = p.n_seg;
     d.n_heavy = p.n_heavy;
+    d.n_comb_many = p.n_comb_many;
     for (int32_t h = 0; h < p.n_heavy; ++h) d.longest_comb = std::max(d.longest_comb, p.comb_ptr[(size_t)h + 1] - p.comb_ptr[(size_t)h]);
     d.edges = p.edges;
     // distinct source rows (for the compulsory-byte count of the profile)
@@ -712,15 +718,14 @@ double pass_min_bytes(int op, double entries, double rows, double n_src, int B) 
     return 4.0 * B * f * (n_src + rows) + 4.0 * (entries + rows);
 }
 
-// Combine pass of the split rows: a workgroup per split row for batches wider than 32 columns
-// (combine_kernel), the generic kernel otherwise.
+// Combine pass of the split rows for batches wider than 32 columns (combine_kernel); `many`: rows that take a workgroup each.
 template <int OP>
-void launch_combine_op(const klay::PassArgs& a, const Geometry& g, hipStream_t s) {
+void launch_combine_op(const klay::PassArgs& a, const Geometry& g, int32_t many, hipStream_t s) {
     constexpr int NW = 8;
-    dim3 grid((unsigned)a.n_main, (unsigned)g.tiles);
-    if (g.vec == 4) hipLaunchKernelGGL((klay::combine_kernel<OP, 4, NW>), grid, dim3(NW * 64), 0, s, a);
-    else if (g.vec == 2) hipLaunchKernelGGL((klay::combine_kernel<OP, 2, NW>), grid, dim3(NW * 64), 0, s, a);
-    else hipLaunchKernelGGL((klay::combine_kernel<OP, 1, NW>), grid, dim3(NW * 64), 0, s, a);
+    dim3 grid((unsigned)(many + (a.n_main - many + NW - 1) / NW), (unsigned)g.tiles);
+    if (g.vec == 4) hipLaunchKernelGGL((klay::combine_kernel<OP, 4, NW>), grid, dim3(NW * 64), 0, s, a, many);
+    else if (g.vec == 2) hipLaunchKernelGGL((klay::combine_kernel<OP, 2, NW>), grid, dim3(NW * 64), 0, s, a, many);
+    else hipLaunchKernelGGL((klay::combine_kernel<OP, 1, NW>), grid, dim3(NW * 64), 0, s, a, many);
 }
 
 // B <= 32: a workgroup of four waves per split row as well, 64 / W partial rows at a time in a wave, where a row has more than
@@ -741,7 +746,7 @@ void launch_combine_small(const klay::PassArgs& a, const Geometry& g, hipStream_
     }
 }
 
-void launch_combine(int op, const klay::PassArgs& a, const Geometry& g, int32_t longest, hipStream_t s) {
+void launch_combine(int op, const klay::PassArgs& a, const Geometry& g, int32_t longest, int32_t many, hipStream_t s) {
     if (a.n_main <= 0) return;
     if (g.w != 64 && longest <= kShortComb) {
         launch_pass(op, a, s);
@@ -760,48 +765,14 @@ void launch_combine(int op, const klay::PassArgs& a, const Geometry& g, int32_t 
         return;
     }
     switch (op) {
-    case klay::OP_SUM: launch_combine_op<klay::OP_SUM>(a, g, s); break;
-    case klay::OP_PROD: launch_combine_op<klay::OP_PROD>(a, g, s); break;
-    case klay::OP_LSE: launch_combine_op<klay::OP_LSE>(a, g, s); break;
-    case klay::OP_MAX: launch_combine_op<klay::OP_MAX>(a, g, s); break;
-    case klay::OP_SUM_H: launch_combine_op<klay::OP_SUM_H>(a, g, s); break;
-    case klay::OP_SUM_P: launch_combine_op<klay::OP_SUM_P>(a, g, s); break;
+    case klay::OP_SUM: launch_combine_op<klay::OP_SUM>(a, g, many, s); break;
+    case klay::OP_PROD: launch_combine_op<klay::OP_PROD>(a, g, many, s); break;
+    case klay::OP_LSE: launch_combine_op<klay::OP_LSE>(a, g, many, s); break;
+    case klay::OP_MAX: launch_combine_op<klay::OP_MAX>(a, g, many, s); break;
+    case klay::OP_SUM_H: launch_combine_op<klay::OP_SUM_H>(a, g, many, s); break;
+    case klay::OP_SUM_P: launch_combine_op<klay::OP_SUM_P>(a, g, many, s); break;
     default: launch_pass(op, a, s); break;
     }
-}
-
-// Main rows and combine rows in one launch (one column per lane; the segments have run in a launch before it).
-template <int OP, int COP>
-void launch_stream_combine_op(const DevPass& dp, const Geometry& g, const float* src, const float* src2, const float* own,
-                              float* dst, int B, hipStream_t s, int* zf, const klay::PassArgs& cmb) {
-    const int2* tasks = reinterpret_cast<const int2*>(dp.tasks);
-    int64_t blocks = ((int64_t)dp.n_tasks + 3) / 4;
-    blocks = (blocks + 7) / 8 * 8;
-    const int n_comb_blocks = (cmb.n_main + 7) / 8 * 8;
-    const int nt = (int64_t)dp.n_main * g.ld * 4 > (int64_t)64 << 20 ? 1 : 0;
-    dim3 grid((unsigned)(blocks + n_comb_blocks), (unsigned)g.tiles);
-    hipLaunchKernelGGL((klay::stream_combine_kernel<OP, COP, 1>), grid, dim3(256), 0, s, tasks, dp.n_tasks, dp.idx, src, src2,
-                       own, dst, B, g.ld, nt, dp.n_main, zf, n_comb_blocks, cmb);
-}
-
-// false: no such kernel for this pair of operations
-bool launch_stream_combine(int op, int combine_op, const DevPass& dp, const Geometry& g, const float* src,
-                           const float* src2, const float* own, float* dst, int B, hipStream_t s, int* zf,
-                           const klay::PassArgs& cmb) {
-    using namespace klay;
-#define KLAY_SC(A, C) \
-    if (op == A && combine_op == C) { launch_stream_combine_op<A, C>(dp, g, src, src2, own, dst, B, s, zf, cmb); return true; }
-    KLAY_SC(OP_SUM, OP_SUM)
-    KLAY_SC(OP_PROD, OP_PROD)
-    KLAY_SC(OP_LSE, OP_LSE)
-    KLAY_SC(OP_MAX, OP_MAX)
-    KLAY_SC(OP_SUM_H, OP_SUM_H)
-    KLAY_SC(OP_SOFTMAX_H, OP_SUM)
-    KLAY_SC(OP_SUM_P, OP_SUM_P)
-    KLAY_SC(OP_PROD_BWD, OP_SUM)
-    KLAY_SC(OP_PROD_BWD_P, OP_SUM_P)
-#undef KLAY_SC
-    return false;
 }
 
 klay::PassArgs combine_args(const DevPass& dp, const float* seg_rows, const float* own, float* dst, const Geometry& g,
@@ -823,15 +794,44 @@ klay::PassArgs combine_args(const DevPass& dp, const float* seg_rows, const floa
     return cmb;
 }
 
-bool stream_combine_pair(int op, int combine_op) {
+// The main rows and the combine rows of a layer in one launch (32 < B <= 64; its segments have run in a launch before it).
+template <int OP, int COP>
+void launch_pass_combine_op(klay::PassArgs a, const klay::PassArgs& cmb, int32_t many, hipStream_t s) {
+    const int vec = deal_lanes(a);
+    const int comb_blocks = (many + (cmb.n_main - many + 3) / 4 + 7) / 8 * 8;
+    dim3 grid(row_blocks(a.n_total, a.lanes) + (unsigned)comb_blocks);
+    if (vec == 4) hipLaunchKernelGGL((klay::pass_combine_kernel<OP, COP, 4>), grid, dim3(256), 0, s, a, comb_blocks, cmb, many);
+    else if (vec == 2) hipLaunchKernelGGL((klay::pass_combine_kernel<OP, COP, 2>), grid, dim3(256), 0, s, a, comb_blocks, cmb, many);
+    else hipLaunchKernelGGL((klay::pass_combine_kernel<OP, COP, 1>), grid, dim3(256), 0, s, a, comb_blocks, cmb, many);
+}
+
+bool pass_combine_pair(int op, int combine_op) {
     using namespace klay;
     return (op == combine_op && (op == OP_SUM || op == OP_PROD || op == OP_LSE || op == OP_MAX || op == OP_SUM_H || op == OP_SUM_P)) ||
            (op == OP_SOFTMAX_H && combine_op == OP_SUM) || (op == OP_PROD_BWD && combine_op == OP_SUM) ||
            (op == OP_PROD_BWD_P && combine_op == OP_SUM_P);
 }
 
-// One layer-level gather-reduce: main rows, segments of split rows, then the combine pass.  The main
-// launch is timed under `cls`, a separate segment launch under KLAY_K_SPLIT, the combine launch under KLAY_K_COMBINE.
+void launch_pass_combine(int op, const klay::PassArgs& a, const klay::PassArgs& cmb, int32_t many, hipStream_t s) {
+    using namespace klay;
+    switch (op) {
+    case OP_SUM: launch_pass_combine_op<OP_SUM, OP_SUM>(a, cmb, many, s); break;
+    case OP_PROD: launch_pass_combine_op<OP_PROD, OP_PROD>(a, cmb, many, s); break;
+    case OP_LSE: launch_pass_combine_op<OP_LSE, OP_LSE>(a, cmb, many, s); break;
+    case OP_MAX: launch_pass_combine_op<OP_MAX, OP_MAX>(a, cmb, many, s); break;
+    case OP_SUM_H: launch_pass_combine_op<OP_SUM_H, OP_SUM_H>(a, cmb, many, s); break;
+    case OP_SOFTMAX_H: launch_pass_combine_op<OP_SOFTMAX_H, OP_SUM>(a, cmb, many, s); break;
+    case OP_SUM_P: launch_pass_combine_op<OP_SUM_P, OP_SUM_P>(a, cmb, many, s); break;
+    case OP_PROD_BWD: launch_pass_combine_op<OP_PROD_BWD, OP_SUM>(a, cmb, many, s); break;
+    default: launch_pass_combine_op<OP_PROD_BWD_P, OP_SUM_P>(a, cmb, many, s); break;
+    }
+}
+
+// One layer-level gather-reduce: main rows and segments of split rows in one launch (timed under `cls`), then the combine
+// pass; in large layers at 32 < B <= 64 the segments first (KLAY_K_SPLIT), then main rows and combine rows (KLAY_K_MAIN_COMBINE).  B > 64: the streaming kernel, two or four columns per lane.  Below, the generic kernel (a lane group per row, up to
+// four columns per lane): a compute unit takes 16 cycles per vector memory instruction, so a wave that reads a row of at most 64 floats at a
+// time stays at a quarter of the rate (1e7 edges of power-law fan-ins, us with the streaming kernel, one column per lane / now: 1e6 nodes,
+// training step at B = 50 998 / 882; 290000 nodes, forward at B = 64 411 / 384).
 void run_pass_set(int op, int combine_op, const DevPass& dp, const float* src, const float* src2,
                   const float* own, float* dst, float* seg_rows, const Geometry& g, int B, hipStream_t s,
                   Profiler& prof, int cls, int* zero_flag = nullptr) {
@@ -852,71 +852,38 @@ void run_pass_set(int op, int combine_op, const DevPass& dp, const float* src, c
     a.B = B;
     a.ld = g.ld;
     const double light_rows = (double)dp.n_main - dp.n_heavy;
-    if (g.w == 64) {
-        // Tiles of two or four columns per lane: the segments of split rows ride in the same launch as
-        // the main rows (same streaming walk, output to partial rows).  One-column tiles (B <= 64) measured
-        // 9% faster through the generic kernel: separate launch.
-        const bool merged = dp.n_seg > 0 && g.vec >= 2;
-        float* seg_base = seg_rows - (ptrdiff_t)dp.n_main * g.ld;     // only indexed with rows >= n_main
-        if (!merged && dp.n_seg > 0 && dp.main_entries + dp.seg_entries <= kSmallPassEntries) {
-            // A small layer with split rows whose segments cannot ride in the streaming launch: main rows
-            // and segments in one launch of the generic kernel (a wave per row) instead of two launches.
-            // Such layers are bound by their launches, not by what the kernels move.
-            prof.begin(cls, pass_bytes(op, (double)(dp.main_entries + dp.seg_entries), light_rows + dp.n_seg, B),
-                       pass_min_bytes(op, (double)(dp.main_entries + dp.seg_entries), light_rows + dp.n_seg, (double)dp.n_src, B));
-            a.row_begin = 0;
-            launch_pass(op, a, s);
-            prof.end();
-        } else if (!merged && dp.n_seg > 0 && dp.n_heavy > 0 && dp.n_tasks > 0 && stream_combine_pair(op, combine_op)) {
-            // One column per lane and a layer too large for one generic launch: the segments first, then the
-            // main rows together with the combine rows (two launches instead of three).
-            prof.begin(KLAY_K_SPLIT, pass_bytes(op, (double)dp.seg_entries, (double)dp.n_seg, B),
-                       pass_min_bytes(op, (double)dp.seg_entries, (double)dp.n_seg, 0.0, B));
-            a.row_begin = dp.n_main;
-            launch_pass(op, a, s);
-            prof.end();
-            prof.begin(KLAY_K_MAIN_COMBINE,
-                       pass_bytes(op, (double)dp.main_entries, light_rows, B) + pass_bytes(combine_op, (double)dp.n_seg, (double)dp.n_heavy, B),
-                       pass_min_bytes(op, (double)dp.main_entries, light_rows, (double)dp.n_src, B) +
-                           pass_bytes(combine_op, (double)dp.n_seg, (double)dp.n_heavy, B));
-            launch_stream_combine(op, combine_op, dp, g, src, src2, own, dst, B, s, zero_flag,
-                                  combine_args(dp, seg_rows, own, dst, g, B, zero_flag));
-            prof.end();
-            return;
-        } else {
-        double bytes = pass_bytes(op, (double)dp.main_entries, light_rows, B);
-        if (merged) bytes += pass_bytes(op, (double)dp.seg_entries, (double)dp.n_seg, B);
-        // the distinct source rows are charged to the main launch, a separate segment launch only
-        // adds its index entries and the partial rows it writes
-        double min_bytes = pass_min_bytes(op, (double)dp.main_entries, light_rows, (double)dp.n_src, B);
-        if (merged) min_bytes += pass_min_bytes(op, (double)dp.seg_entries, (double)dp.n_seg, 0.0, B);
-        prof.begin(cls, bytes, min_bytes);
-        launch_stream(op, dp, true, merged, g, src, src2, own, dst, seg_base, B, s, zero_flag);
+    if (g.w == 64 && g.vec == 1 && dp.n_heavy > 0 && dp.main_entries + dp.seg_entries > kSmallPassEntries && light_rows > 0 && pass_combine_pair(op, combine_op)) {
+        prof.begin(KLAY_K_SPLIT, pass_bytes(op, (double)dp.seg_entries, (double)dp.n_seg, B),
+                   pass_min_bytes(op, (double)dp.seg_entries, (double)dp.n_seg, 0.0, B));
+        a.row_begin = dp.n_main;
+        launch_pass(op, a, s);
         prof.end();
-        if (dp.n_seg > 0 && !merged) {
-            prof.begin(KLAY_K_SPLIT, pass_bytes(op, (double)dp.seg_entries, (double)dp.n_seg, B),
-                       pass_min_bytes(op, (double)dp.seg_entries, (double)dp.n_seg, 0.0, B));
-            a.row_begin = dp.n_main;
-            launch_pass(op, a, s);
-            prof.end();
-        }
-        }
-    } else {
-        // small batches: main rows and segments in one launch (a lane group per row, or lanes = edges)
-        prof.begin(cls, pass_bytes(op, (double)(dp.main_entries + dp.seg_entries), light_rows + dp.n_seg, B),
-                   pass_min_bytes(op, (double)(dp.main_entries + dp.seg_entries), light_rows + dp.n_seg, (double)dp.n_src, B));
-        if (edges) {
-            launch_edge(op, dp, g, src, src2, own, dst, seg_rows - (ptrdiff_t)dp.n_main * g.ld, B, s, zero_flag);
-        } else {
-            a.row_begin = 0;
-            launch_pass(op, a, s);
-        }
+        prof.begin(KLAY_K_MAIN_COMBINE,
+                   pass_bytes(op, (double)dp.main_entries, light_rows, B) + pass_bytes(combine_op, (double)dp.n_seg, (double)dp.n_heavy, B),
+                   pass_min_bytes(op, (double)dp.main_entries, light_rows, (double)dp.n_src, B) +
+                       pass_bytes(combine_op, (double)dp.n_seg, (double)dp.n_heavy, B));
+        a.row_begin = 0;
+        a.n_total = dp.n_main;
+        launch_pass_combine(op, a, combine_args(dp, seg_rows, own, dst, g, B, zero_flag), dp.n_comb_many, s);
         prof.end();
+        return;
     }
+    prof.begin(cls, pass_bytes(op, (double)(dp.main_entries + dp.seg_entries), light_rows + dp.n_seg, B),
+               pass_min_bytes(op, (double)(dp.main_entries + dp.seg_entries), light_rows + dp.n_seg, (double)dp.n_src, B));
+    float* seg_base = seg_rows - (ptrdiff_t)dp.n_main * g.ld;     // only indexed with rows >= n_main
+    if (g.w == 64 && g.vec >= 2) {
+        launch_stream(op, dp, g, src, src2, own, dst, seg_base, B, s, zero_flag);
+    } else if (g.w != 64 && edges) {
+        launch_edge(op, dp, g, src, src2, own, dst, seg_base, B, s, zero_flag);
+    } else {
+        a.row_begin = 0;
+        launch_pass(op, a, s);
+    }
+    prof.end();
     if (dp.n_heavy > 0) {
         const klay::PassArgs cmb = combine_args(dp, seg_rows, own, dst, g, B, zero_flag);
         prof.begin(KLAY_K_COMBINE, pass_bytes(combine_op, (double)dp.n_seg, (double)dp.n_heavy, B));
-        launch_combine(combine_op, cmb, g, dp.longest_comb, s);
+        launch_combine(combine_op, cmb, g, dp.longest_comb, dp.n_comb_many, s);
         prof.end();
     }
 }

@@ -252,29 +252,28 @@ __device__ __forceinline__ float dead_value() {
 }
 
 // ---------------------------------------------------------------------------------------------
-// Streaming segmented gather-reduce for B > 32 (one wave spans the batch tile, VEC columns per
+// Streaming segmented gather-reduce for B > 64 (one wave spans the batch tile, VEC = 2 or 4 columns per
 // lane).  A task is a run of consecutive output rows with a bounded number of edges, fixed at
 // build time; the wave walks the task's edges in chunks of CH, keeps CH row gathers in flight,
 // prefetches the next chunk's index entries while they fly, and closes an output row whenever
 // an entry carries the end-of-row bit.  Everything that steers control flow is wave-uniform.
 // Index entries past a task's end are valid entries of later rows (or zero padding).
 // ---------------------------------------------------------------------------------------------
-// bx of nbx: the workgroup's place among the workgroups that walk tasks (nbx a multiple of 8, bx mod 8 the XCD
-// the workgroup runs on).
 template <int OP, int VEC>
-__device__ __forceinline__ void stream_body(int bx, int nbx, const int2* __restrict__ tasks, int n_tasks,
-                                            const uint32_t* __restrict__ idx, const float* __restrict__ src,
-                                            const float* __restrict__ src2, const float* __restrict__ own,
-                                            float* __restrict__ dst, int B, int ld, int stream_stores,
-                                            const int2* __restrict__ seg_tasks, int n_seg_tasks,
-                                            float* __restrict__ dst_seg, const int32_t* __restrict__ seg_owner,
-                                            int n_main, int* __restrict__ zero_flag) {
+__global__ __launch_bounds__(256) void stream_kernel(const int2* __restrict__ tasks, int n_tasks,
+                                                     const uint32_t* __restrict__ idx,
+                                                     const float* __restrict__ src,
+                                                     const float* __restrict__ src2,
+                                                     const float* __restrict__ own, float* __restrict__ dst,
+                                                     int B, int ld, int stream_stores,
+                                                     const int2* __restrict__ seg_tasks, int n_seg_tasks,
+                                                     float* __restrict__ dst_seg,
+                                                     const int32_t* __restrict__ seg_owner, int n_main,
+                                                     int* __restrict__ zero_flag) {
     // entries per chunk: measured on the headline workload, 4 (2 for the softmax adjoint, which loads
     // three rows per entry) beat 8 / 4 by 2%: the kernel is bandwidth-bound, fewer registers per wave
     // buy more resident waves
-    // With one column per lane (B <= 64) a row is 256 bytes and twice as many have to be in flight:
-    // 8 (4) measured 3% faster on the power-law workload at B = 64, 4% on the headline circuit at B = 64.
-    constexpr int CH = (OP == OP_SOFTMAX_BWD) ? (VEC == 1 ? 4 : 2) : (VEC == 1 ? 8 : 4);
+    constexpr int CH = OP == OP_SOFTMAX_BWD ? 2 : 4;
     static_assert(kGroupEnd == kWeighted, "the fused plans reuse this bit");
     // the walk needs the output row's own value
     constexpr bool OWN = OpTraits<OP>::own;
@@ -282,7 +281,7 @@ __device__ __forceinline__ void stream_body(int bx, int nbx, const int2* __restr
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int col = ((int)blockIdx.y * 64 + lane) * VEC;
     if (col >= B) return;
-    int t = xcd_block(bx, nbx) * 4 + wave;
+    int t = xcd_block((int)blockIdx.x, (int)gridDim.x) * 4 + wave;
     if (t >= n_tasks + n_seg_tasks) return;
     // tasks past the main list are segments of split rows: same walk, output rows go to scratch
     // (dst_seg is shifted so that segment row numbers, which continue after the main rows, index it)
@@ -381,21 +380,6 @@ __device__ __forceinline__ void stream_body(int bx, int nbx, const int2* __restr
         for (int i = 0; i < CH; ++i) ids[i] = nxt[i];
         j += CH;
     }
-}
-
-template <int OP, int VEC>
-__global__ __launch_bounds__(256) void stream_kernel(const int2* __restrict__ tasks, int n_tasks,
-                                                     const uint32_t* __restrict__ idx,
-                                                     const float* __restrict__ src,
-                                                     const float* __restrict__ src2,
-                                                     const float* __restrict__ own, float* __restrict__ dst,
-                                                     int B, int ld, int stream_stores,
-                                                     const int2* __restrict__ seg_tasks, int n_seg_tasks,
-                                                     float* __restrict__ dst_seg,
-                                                     const int32_t* __restrict__ seg_owner, int n_main,
-                                                     int* __restrict__ zero_flag) {
-    stream_body<OP, VEC>((int)blockIdx.x, (int)gridDim.x, tasks, n_tasks, idx, src, src2, own, dst, B, ld, stream_stores,
-                         seg_tasks, n_seg_tasks, dst_seg, seg_owner, n_main, zero_flag);
 }
 
 // ---------------------------------------------------------------------------------------------
@@ -639,14 +623,14 @@ __device__ __forceinline__ void arguments_now(const PassArgs& a) {
                  "s"(a.per_wave), "s"(a.row_begin), "s"(a.n_main), "s"(a.n_total), "s"(a.B), "s"(a.ld), "s"(gridDim.x));
 }
 
+// bx of nbx: the workgroup's place among those that take rows (nbx a multiple of 8, bx mod 8 the XCD the workgroup runs on)
 template <int OP, int VEC>
-__global__ __launch_bounds__(256) void pass_kernel(PassArgs a) {
+__device__ __forceinline__ void pass_body(int bx, int nbx, const PassArgs& a) {
     constexpr bool OWN = OpTraits<OP>::own;
-    arguments_now(a);
     int sub, colu;
     if (!lane_group(a, VEC, sub, colu)) return;
     const int col = colu <= a.B - VEC ? colu : a.B - VEC;
-    const int64_t row64 = ((int64_t)xcd_block((int)blockIdx.x, (int)gridDim.x) * 4 + (threadIdx.x >> 6)) * a.per_wave + sub + a.row_begin;
+    const int64_t row64 = ((int64_t)xcd_block(bx, nbx) * 4 + (threadIdx.x >> 6)) * a.per_wave + sub + a.row_begin;
     if (row64 >= a.n_total) return;
     const int row = (int)row64;
     const Offsets2 range = *reinterpret_cast<const Offsets2*>(a.ptr + row);
@@ -721,17 +705,25 @@ __global__ __launch_bounds__(256) void pass_kernel(PassArgs a) {
     store_cols<VEC>(out, o);
 }
 
+template <int OP, int VEC>
+__global__ __launch_bounds__(256) void pass_kernel(PassArgs a) {
+    arguments_now(a);
+    pass_body<OP, VEC>((int)blockIdx.x, (int)gridDim.x, a);
+}
+
 // ---------------------------------------------------------------------------------------------
-// Combine pass of split rows for B > 32: one workgroup of NW waves per split row.  The partial rows of a
-// split row (up to a few hundred for the widest rows) are dealt to the waves in chunks of 8, every wave
+// Combine pass of split rows for B > 32, NW waves in a workgroup.  A row of many partial rows (up to a few hundred; the first `many`
+// rows of the lists) takes a workgroup: its partial rows are dealt to the waves in chunks of 8, every wave
 // reduces its share with all its gathers of a chunk in flight, and wave 0 folds the NW states in wave
 // order (so the result does not depend on timing) and finishes the row like pass_kernel does.  A single
-// wave would walk the widest row 8 partial rows at a time, and the launch lasts as long as that walk.
+// wave would walk the widest row 8 partial rows at a time, and the launch lasts as long as that walk.  The
+// others, which are nearly all, take a wave: a workgroup for each of them is mostly waves that have no chunk, and a
+// barrier (9454 rows at B = 50 16.3 us, 7616 at B = 256 34.8).
 // Arguments as for pass_kernel's combine use: ptr / idx = combine lists, src = partial rows, out_row = the
 // rows to write, n_main = number of split rows.
 // ---------------------------------------------------------------------------------------------
 template <int OP, int VEC, int NW>
-__device__ __forceinline__ void combine_body(int row, const PassArgs& a) {
+__device__ __forceinline__ void combine_body(int bx, const PassArgs& a, int many) {
     constexpr int CH = 8;
     constexpr bool LSE = OP == OP_LSE;
     __shared__ float part_v[NW][64 * VEC];
@@ -740,11 +732,15 @@ __device__ __forceinline__ void combine_body(int row, const PassArgs& a) {
     const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
     const int colu = ((int)blockIdx.y * 64 + lane) * VEC;
     const int col = colu < a.B ? colu : 0;                 // lanes past the batch work on column 0 and store nothing
+    const bool shared = bx < many;
+    const int row = shared ? bx : many + (bx - many) * NW + wave;
+    if (row >= a.n_main) return;                           // (all waves of a shared row are there)
     const int beg = a.ptr[row], end = a.ptr[row + 1];
+    const int step = shared ? NW * CH : CH;
     float acc[VEC], mx[VEC];
 #pragma unroll
     for (int v = 0; v < VEC; ++v) { acc[v] = identity<OP>(); mx[v] = -INFINITY; }
-    for (int j = beg + wave * CH; j < end; j += NW * CH) {
+    for (int j = beg + (shared ? wave * CH : 0); j < end; j += step) {
         float x[CH][VEC];
 #pragma unroll
         for (int i = 0; i < CH; ++i)                         // padded list: always in bounds
@@ -756,28 +752,31 @@ __device__ __forceinline__ void combine_body(int row, const PassArgs& a) {
             for (int v = 0; v < VEC; ++v) { float none = 0.0f; accumulate<OP>(acc[v], mx[v], live ? x[i][v] : dead_value<OP>(), 0.0f, none, false); }
         }
     }
-    if (wave > 0) {
+    if (shared) {
+        if (wave > 0) {
 #pragma unroll
-        for (int v = 0; v < VEC; ++v) {
-            part_v[wave][lane * VEC + v] = acc[v];
-            if (LSE) part_m[wave][lane * VEC + v] = mx[v];
+            for (int v = 0; v < VEC; ++v) {
+                part_v[wave][lane * VEC + v] = acc[v];
+                if (LSE) part_m[wave][lane * VEC + v] = mx[v];
+            }
         }
-    }
-    __syncthreads();
-    if (wave > 0 || colu >= a.B) return;
-    for (int w = 1; w < NW; ++w) {
+        __syncthreads();
+        if (wave > 0) return;
+        for (int w = 1; w < NW; ++w) {
 #pragma unroll
-        for (int v = 0; v < VEC; ++v) {
-            const float ov = part_v[w][lane * VEC + v];
-            if (LSE) {
-                const float om = part_m[w][lane * VEC + v];
-                edge_combine<OP>(mx[v], acc[v], om, ov);
-            } else {
-                float unused = 0.0f;
-                edge_combine<OP>(acc[v], unused, ov, 0.0f);
+            for (int v = 0; v < VEC; ++v) {
+                const float ov = part_v[w][lane * VEC + v];
+                if (LSE) {
+                    const float om = part_m[w][lane * VEC + v];
+                    edge_combine<OP>(mx[v], acc[v], om, ov);
+                } else {
+                    float unused = 0.0f;
+                    edge_combine<OP>(acc[v], unused, ov, 0.0f);
+                }
             }
         }
     }
+    if (colu >= a.B) return;
     const int out_row = a.out_row[row];
     float o[VEC], nc[VEC];
 #pragma unroll
@@ -798,8 +797,16 @@ __device__ __forceinline__ void combine_body(int row, const PassArgs& a) {
 }
 
 template <int OP, int VEC, int NW>
-__global__ __launch_bounds__(NW * 64) void combine_kernel(PassArgs a) {
-    combine_body<OP, VEC, NW>((int)blockIdx.x, a);
+__global__ __launch_bounds__(NW * 64) void combine_kernel(PassArgs a, int many) {
+    combine_body<OP, VEC, NW>((int)blockIdx.x, a, many);
+}
+
+// 32 < B <= 64: the combine rows and the main rows of a large layer, after the launch of its segments.  The first n_comb_blocks
+// workgroups (a multiple of 8, so that the others keep their XCDs) take combine rows, the rest the main rows: neither waits for the other.
+template <int OP, int COP, int VEC>
+__global__ __launch_bounds__(256) void pass_combine_kernel(PassArgs a, int n_comb_blocks, PassArgs cmb, int many) {
+    if ((int)blockIdx.x < n_comb_blocks) combine_body<COP, 1, 4>((int)blockIdx.x, cmb, many);
+    else pass_body<OP, VEC>((int)blockIdx.x - n_comb_blocks, (int)gridDim.x - n_comb_blocks, a);
 }
 
 // The same for B <= 32 and split rows of many partial rows (kShortComb): W lanes (a power of two) hold the columns of a partial row, so a wave takes 64 / W partial rows at
@@ -854,27 +861,6 @@ __global__ __launch_bounds__(256) void combine_small_kernel(PassArgs a) {
         }
     }
     a.dst[(size_t)out_row * a.ld + c] = o;
-}
-
-// The main rows of a layer and the combine rows of its split rows in one launch, for the tiles whose segments
-// run in a launch of their own beforehand (one column per lane): the first n_comb_blocks workgroups (a multiple
-// of 8, so that the others keep their XCDs) take one combine row each, four waves per row, the rest walk the
-// tasks of the main rows.  One launch less per layer where the launches, not the bytes, set the time.
-template <int OP, int COP, int VEC>
-__global__ __launch_bounds__(256) void stream_combine_kernel(const int2* __restrict__ tasks, int n_tasks,
-                                                             const uint32_t* __restrict__ idx,
-                                                             const float* __restrict__ src,
-                                                             const float* __restrict__ src2,
-                                                             const float* __restrict__ own, float* __restrict__ dst,
-                                                             int B, int ld, int stream_stores, int n_main,
-                                                             int* __restrict__ zero_flag, int n_comb_blocks,
-                                                             PassArgs cmb) {
-    if ((int)blockIdx.x < n_comb_blocks) {
-        if ((int)blockIdx.x < cmb.n_main) combine_body<COP, VEC, 4>((int)blockIdx.x, cmb);
-    } else {
-        stream_body<OP, VEC>((int)blockIdx.x - n_comb_blocks, (int)gridDim.x - n_comb_blocks, tasks, n_tasks, idx, src,
-                             src2, own, dst, B, ld, stream_stores, nullptr, 0, nullptr, nullptr, n_main, zero_flag);
-    }
 }
 
 // ---------------------------------------------------------------------------------------------

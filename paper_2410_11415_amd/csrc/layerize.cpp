@@ -162,13 +162,17 @@ void make_pass_plan(int64_t n, const int32_t* ptr, const int32_t* idx_in, const 
     int64_t h = 0;
     std::vector<int32_t> owner_slot((size_t)n, -1);
     out.comb_ptr[0] = 0;
-    for (int64_t r = 0; r < n; ++r)
-        if (per_owner_count[(size_t)r] > 0) {
-            owner_slot[(size_t)r] = (int32_t)h;
-            out.comb_row[(size_t)h] = (int32_t)r;
-            out.comb_ptr[(size_t)h + 1] = out.comb_ptr[(size_t)h] + per_owner_count[(size_t)r];
-            ++h;
-        }
+    // those of many partial rows first: they take a workgroup each (combine_kernel)
+    for (const bool many : {true, false}) {
+        for (int64_t r = 0; r < n; ++r)
+            if (per_owner_count[(size_t)r] > 0 && (per_owner_count[(size_t)r] > kCombineWave) == many) {
+                owner_slot[(size_t)r] = (int32_t)h;
+                out.comb_row[(size_t)h] = (int32_t)r;
+                out.comb_ptr[(size_t)h + 1] = out.comb_ptr[(size_t)h] + per_owner_count[(size_t)r];
+                ++h;
+            }
+        if (many) out.n_comb_many = (int32_t)h;
+    }
     out.comb_idx.assign((size_t)n_seg + kIdxPad, 0u);
     std::vector<int32_t> fill(out.comb_ptr.begin(), out.comb_ptr.end() - 1);
     for (size_t sidx = 0; sidx < segs.size(); ++sidx) {

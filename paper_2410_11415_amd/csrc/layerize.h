@@ -89,10 +89,14 @@ constexpr uint32_t kGroupEnd = kWeightedEdge;
 constexpr int64_t kFusedRowMax = 24;
 constexpr int64_t kMaxRows = (int64_t)1 << 29;      // row ids fit the 29-bit source field
 constexpr int kIdxPad = 16;
+// Split rows of more partial rows than this take a workgroup each in the combine pass, the others a wave.
+constexpr int32_t kCombineWave = 16;
+
 struct PassPlan {
     int32_t n_main = 0;
     int32_t n_seg = 0;
     int32_t n_heavy = 0;
+    int32_t n_comb_many = 0;         // split rows of more than kCombineWave partial rows, the first ones of the combine lists
     int64_t edges = 0;
     std::vector<int32_t> ptr;        // [n_main + n_seg + 1]
     std::vector<uint32_t> idx;       // entries of all rows, zero padded by kIdxPad for chunked reads
