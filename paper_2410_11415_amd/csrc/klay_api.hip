@@ -827,8 +827,19 @@ void launch_pass_combine(int op, const klay::PassArgs& a, const klay::PassArgs& 
     }
 }
 
+// 64 < B <= 128: whether a pass takes the generic kernel, four columns per lane, instead of the streaming one, two.  Up to 84
+// columns three rows fit a wave, of which the streaming kernel would use 42 lanes at most.  Above, both use as many, and the
+// streaming kernel's balanced tasks win, except where most entries are segments, rows of one length.  (The plans of fused rows have no
+// generic kernel.)  Training steps, us, streaming / generic throughout / this rule: 800000 nodes B = 70 623 / 558 / 558, B = 100
+// 654 / 676 / 638, B = 128 705 / 720 / 691, real semiring B = 100 710 / 730 / 666; 1e6 nodes, 1e7 edges of power-law fan-ins B = 100
+// 1519 / 1405 / 1449, B = 128 1561 / 1462 / 1511.
+bool generic_pair(int op, const DevPass& dp, int B) {
+    if (op == klay::OP_LSE2 || op == klay::OP_MAX2 || op == klay::OP_SUMPROD2) return false;
+    return B <= 84 || dp.seg_entries > dp.main_entries;
+}
+
 // One layer-level gather-reduce: main rows and segments of split rows in one launch (timed under `cls`), then the combine
-// pass; in large layers at 32 < B <= 64 the segments first (KLAY_K_SPLIT), then main rows and combine rows (KLAY_K_MAIN_COMBINE).  B > 64: the streaming kernel, two or four columns per lane.  Below, the generic kernel (a lane group per row, up to
+// pass; in large layers at 32 < B <= 64 the segments first (KLAY_K_SPLIT), then main rows and combine rows (KLAY_K_MAIN_COMBINE).  B > 64: the streaming kernel, two or four columns per lane (see generic_pair).  Below, the generic kernel (a lane group per row, up to
 // four columns per lane): a compute unit takes 16 cycles per vector memory instruction, so a wave that reads a row of at most 64 floats at a
 // time stays at a quarter of the rate (1e7 edges of power-law fan-ins, us with the streaming kernel, one column per lane / now: 1e6 nodes,
 // training step at B = 50 998 / 882; 290000 nodes, forward at B = 64 411 / 384).
@@ -871,7 +882,7 @@ void run_pass_set(int op, int combine_op, const DevPass& dp, const float* src, c
     prof.begin(cls, pass_bytes(op, (double)(dp.main_entries + dp.seg_entries), light_rows + dp.n_seg, B),
                pass_min_bytes(op, (double)(dp.main_entries + dp.seg_entries), light_rows + dp.n_seg, (double)dp.n_src, B));
     float* seg_base = seg_rows - (ptrdiff_t)dp.n_main * g.ld;     // only indexed with rows >= n_main
-    if (g.w == 64 && g.vec >= 2) {
+    if (g.w == 64 && g.vec >= 2 && !(g.vec == 2 && generic_pair(op, dp, B))) {
         launch_stream(op, dp, g, src, src2, own, dst, seg_base, B, s, zero_flag);
     } else if (g.w != 64 && edges) {
         launch_edge(op, dp, g, src, src2, own, dst, seg_base, B, s, zero_flag);
