@@ -155,7 +155,8 @@ __device__ __forceinline__ int xcd_block(int bid, int nblocks) { return (bid & 7
 //                     (a sum node above, or a root's dout row) and is added as it is.  acc = sum of the plain entries, mx = sum of
 //                     the P_r that concern the child (-0 as long as there is none), divided by `own` once, in finish():
 //                     a division takes ten instructions, and one per entry and column bound the wide layers (800000
-//                     nodes at B = 256, training step 1251 -> 1190 us).
+//                     nodes at B = 256, training step 1251 -> 1192 us).  The P_r are added times a power of two that is
+//                     about 1 / own (share_scale), so that the sum stays in range wherever the quotients do.
 //   OP_SUM_P, OP_PROD_BWD_P   OP_SUM / OP_PROD_BWD whose output rows are AND nodes: the finished adjoint G
 //                     leaves as G * (the node's own value), lowest mantissa bit clear, which is the row P
 //                     above whenever the node has no zero child; where the own value is zero G is left
@@ -182,6 +183,14 @@ __device__ __forceinline__ float premultiply(float g, float n) {
     return n != 0.0f ? __uint_as_float(__float_as_uint(g * n) & ~1u) : g;
 }
 
+// The power of two by which the P_r of a child of value n are scaled before they are added: n times it is in [1/2, 1) (less
+// below 2^-126; from 2^126 on up to 4, where P_r / n is below 4), so a scaled P_r is in range wherever the quotient
+// P_r / n is, and scaling rounds nothing that the quotient would not.  1 for n = 0.
+__device__ __forceinline__ float share_scale(float n) {
+    const int bits = 0x7E800000 - (int)(__float_as_uint(n) & 0x7F800000u);
+    return n == 0.0f ? 1.0f : __uint_as_float((uint32_t)(bits > 0x00800000 ? bits : 0x00800000));
+}
+
 // one element of a running logsumexp: (mx, acc) = (maximum so far, sum of exp(x - mx)), one exp per element
 __device__ __forceinline__ void lse_step(float& acc, float& mx, float x) {
     // d is +inf on the first finite element (e = 0, acc = 1), -inf for an impossible child under a finite
@@ -194,7 +203,7 @@ __device__ __forceinline__ void lse_step(float& acc, float& mx, float x) {
 }
 
 // nc: the value of the output row itself where the operation needs it; OP_LSE2 / OP_MAX2 keep the sum of the
-// group in hand there (weighted = the entry closes its group).
+// group in hand there (weighted = the entry closes its group).  y: OP_SOFTMAX_BWD the parent's value, the P row ops share_scale(nc).
 template <int OP>
 __device__ __forceinline__ void accumulate(float& acc, float& mx, float x, float y, float& nc, bool weighted = true) {
     if (OP == OP_SUM_H || OP == OP_SUM_P) { acc += x; return; }
@@ -216,7 +225,7 @@ __device__ __forceinline__ void accumulate(float& acc, float& mx, float x, float
     if (OpTraits<OP>::shares) {
         const uint32_t bits = __float_as_uint(x);
         const bool mine = !weighted && ((bits & 1u) != 0) == (nc == 0.0f);
-        mx += mine ? __uint_as_float(bits & ~1u) : -0.0f;
+        mx = fmaf(mine ? __uint_as_float(bits & ~1u) : -0.0f, y, mx);
         acc += weighted ? x : 0.0f;
         return;
     }
@@ -231,9 +240,9 @@ __device__ __forceinline__ void accumulate(float& acc, float& mx, float x, float
 }
 
 template <int OP>
-__device__ __forceinline__ float finish(float acc, float mx, float nc = 0.0f) {
+__device__ __forceinline__ float finish(float acc, float mx, float nc = 0.0f, float scale = 1.0f) {
     // (no entry that concerns the row: no quotient, which a NaN value would make one)
-    if (OpTraits<OP>::shares) return acc + (nc != 0.0f && __float_as_uint(mx) != 0x80000000u ? mx / nc : mx);
+    if (OpTraits<OP>::shares) return acc + (nc != 0.0f && __float_as_uint(mx) != 0x80000000u ? mx / (nc * scale) : mx);
     if (OP == OP_LSE || OP == OP_LSE2) return (mx == -INFINITY) ? -INFINITY : mx + flog(acc);
     return acc;
 }
@@ -297,9 +306,9 @@ __global__ __launch_bounds__(256) void stream_kernel(const int2* __restrict__ ta
     const float* ownc = own + col;
     float* dstc = dst + col;
 
-    float acc[VEC], mx[VEC], nc[VEC];
+    float acc[VEC], mx[VEC], nc[VEC], scale[VEC];
 #pragma unroll
-    for (int v = 0; v < VEC; ++v) { acc[v] = identity<OP>(); mx[v] = identity2<OP>(); nc[v] = OP == OP_SUMPROD2 ? 1.0f : 0.0f; }
+    for (int v = 0; v < VEC; ++v) { acc[v] = identity<OP>(); mx[v] = identity2<OP>(); nc[v] = OP == OP_SUMPROD2 ? 1.0f : 0.0f; scale[v] = 1.0f; }
     bool fresh = true;                       // the next edge opens a new output row
     uint32_t ids[CH];
 #pragma unroll
@@ -351,18 +360,22 @@ __global__ __launch_bounds__(256) void stream_kernel(const int2* __restrict__ ta
             if (OWN) {
 #pragma unroll
                 for (int v = 0; v < VEC; ++v) nc[v] = (live && first[i]) ? z[i][v] : nc[v];
+                if (OpTraits<OP>::shares && live && first[i]) {
+#pragma unroll
+                    for (int v = 0; v < VEC; ++v) scale[v] = share_scale(nc[v]);
+                }
             }
 #pragma unroll
             for (int v = 0; v < VEC; ++v) {
                 const float xv = live ? x[i][v] : dead_value<OP>();
-                const float yv = OP == OP_SOFTMAX_BWD ? (live ? y[i][v] : -INFINITY) : 0.0f;
+                const float yv = OP == OP_SOFTMAX_BWD ? (live ? y[i][v] : -INFINITY) : scale[v];
                 accumulate<OP>(acc[v], mx[v], xv, yv, nc[v], OpTraits<OP>::shares ? !live || (ids[i] & kWeighted) != 0 : live && (ids[i] & kWeighted) != 0);
             }
             if (live && (ids[i] & kLast)) {
                 float o[VEC];
 #pragma unroll
                 for (int v = 0; v < VEC; ++v) {
-                    o[v] = finish<OP>(acc[v], mx[v], nc[v]);
+                    o[v] = finish<OP>(acc[v], mx[v], nc[v], scale[v]);
                     // the adjoint of an OR node with more than one child leaves in the one-gather form
                     if (OP == OP_SUM_H && !seg && (ids[i] & kRowFlag)) o[v] = encode_h(o[v], nc[v]);
                     if (OpTraits<OP>::premul && !seg) {
@@ -494,8 +507,8 @@ __global__ __launch_bounds__(256) void edge_kernel(const int2* __restrict__ task
                 vm = live ? ((id[i] & kWeighted) ? decode_h(x[i], z[i]) : x[i]) : 0.0f;
             } else if (OpTraits<OP>::shares) {
                 float plain = 0.0f, shared = identity2<OP>();
-                accumulate<OP>(plain, shared, x[i], 0.0f, z[i], (id[i] & kWeighted) != 0);
-                vm = live ? finish<OP>(plain, shared, z[i]) : 0.0f;
+                accumulate<OP>(plain, shared, x[i], share_scale(z[i]), z[i], (id[i] & kWeighted) != 0);
+                vm = live ? finish<OP>(plain, shared, z[i], share_scale(z[i])) : 0.0f;
             } else if (LSE) {
                 vm = live ? fmaxf(x[i], -INFINITY) : -INFINITY;
                 vs = live ? 1.0f : 0.0f;
@@ -605,10 +618,17 @@ __device__ __forceinline__ void accumulate4(float (&acc)[VEC], float (&mx)[VEC],
             acc[v] = fmaf(acc[v], term_exp(mx[v] - m), (term_exp(x0 - m) + term_exp(x1 - m)) + (term_exp(x2 - m) + term_exp(x3 - m)));
             mx[v] = hi;
         } else {
+            float scale = 0.0f;
+            if (OpTraits<OP>::shares) {
+                // (anew for every four entries: kept over the row it would cost a wave of occupancy at four columns per lane)
+                float n = nc[v];
+                asm volatile("" : "+v"(n));
+                scale = share_scale(n);
+            }
 #pragma unroll
             for (int i = 0; i < 4; ++i) {
                 const float xv = i < live ? x[i][v] : dead_value<OP>();
-                const float yv = OP == OP_SOFTMAX_BWD ? (i < live ? y[i][v] : -INFINITY) : 0.0f;
+                const float yv = OP == OP_SOFTMAX_BWD ? (i < live ? y[i][v] : -INFINITY) : scale;
                 accumulate<OP>(acc[v], mx[v], xv, yv, nc[v], OpTraits<OP>::shares ? i >= live || (e[i] & kWeighted) != 0 : i < live && (e[i] & kWeighted) != 0);
             }
         }
@@ -687,7 +707,7 @@ __device__ __forceinline__ void pass_body(int bx, int nbx, const PassArgs& a) {
     }
     float o[VEC];
 #pragma unroll
-    for (int v = 0; v < VEC; ++v) o[v] = OP == OP_LSE ? mx[v] + flog(acc[v]) : finish<OP>(acc[v], mx[v], nc[v]);
+    for (int v = 0; v < VEC; ++v) o[v] = OP == OP_LSE ? mx[v] + flog(acc[v]) : finish<OP>(acc[v], mx[v], nc[v], share_scale(nc[v]));
     if (OP == OP_SUM_H && row < a.n_main && (last & kRowFlag)) {
 #pragma unroll
         for (int v = 0; v < VEC; ++v) o[v] = encode_h(o[v], nc[v]);
