@@ -22,9 +22,7 @@
 // ends.  In host code the name below is only a handle for hipGetSymbolAddress; the kernels get the
 // address that call returned (kept per device in g_static_ws).
 constexpr size_t kStaticWorkspaceBytes = KLAY_STATIC_WORKSPACE_BYTES;
-// The second half is for the stage buffer of a TopPlan, which the limit of a call does not count: one level of the circuit,
-// never more rows than the activation rows in the first half.
-static __device__ __align__(256) unsigned char scratch[2 * kStaticWorkspaceBytes];
+static __device__ __align__(256) unsigned char scratch[kStaticWorkspaceBytes];
 
 // Layers with split rows and at most this many index entries run main rows and segments in one generic
 // launch and the combine rows in another; larger ones the segments first, then main rows and combine rows.
@@ -143,7 +141,8 @@ size_t align_floats(size_t n) { return (n + 63) / 64 * 64; }
 
 struct Workspace {
     size_t act = 0, wT = 0, seg_rows = 0, g0 = 0, g1 = 0, g2 = 0, tb = 0, stage = 0, flags = 0, total = 0;   // offsets in floats
-    size_t counted = 0, top_stage = 0, top_tb = 0, top_g = 0;      // the parts of a TopPlan follow the others (`counted` floats)
+    size_t top_tb = 0, top_g = 0;            // TopPlan: values and adjoints of its levels
+    size_t top_stage = 0, top_stage_n = 0;   // and the level below its first one, for the forward kernel to read (0 floats: it reads rows)
 };
 
 struct EventRec {
@@ -222,36 +221,51 @@ int64_t tail_stage_rows(const klay_circuit* c, int B);
 int choose_top(const klay_circuit* c, int B);
 int tail_columns(int B, const int64_t (&size)[2], size_t lds_bytes, bool reverse);
 
-Workspace workspace_layout(const klay_circuit* c, int B, bool need_bwd) {
+// Columns from which on the forward kernel reads the level below its first one from columns instead of its rows: fewer
+// are not worth the launch that makes columns of them.
+constexpr int kTopStageB = 17;
+
+// top: first layer that the persistent kernels take from the TopPlan (0: none).  A pass that nothing is kept for (need_bwd =
+// false) needs the same in both cases.
+Workspace workspace_layout(const klay_circuit* c, int B, bool need_bwd, int top) {
     const Geometry g = geometry(B);
     const klay::CircuitPlan& p = c->plan;
     Workspace w;
     size_t off = 0;
-    w.act = off; off += align_floats((size_t)p.num_nodes * g.ld);
-    w.wT = off; off += align_floats((size_t)std::max(1, p.num_vars) * g.ld);
+    auto take = [&](size_t n) { const size_t at = off; off += align_floats(n); return at; };
+    w.act = take((size_t)p.num_nodes * g.ld);
+    w.wT = take((size_t)std::max(1, p.num_vars) * g.ld);
     const int64_t seg = std::max(p.max_fwd_seg, need_bwd ? p.max_bwd_seg : 0);
-    w.seg_rows = off; off += align_floats((size_t)std::max<int64_t>(seg, 1) * g.ld);
-    // values of the tail layers, one run of tail_rows floats per batch column
-    w.tb = off; off += align_floats((size_t)c->tail_rows * (size_t)B);
-    // the layer below the persistent forward kernel's first one, column-major, for that kernel to read
-    w.stage = off; off += align_floats((size_t)tail_stage_rows(c, B) * (size_t)B);
+    w.seg_rows = take((size_t)std::max<int64_t>(seg, 1) * g.ld);
+    if (top > 0 && need_bwd) {
+        // values of the levels, column-major, and their adjoints where they go to rows afterwards
+        w.top_tb = take((size_t)c->top.rows * (size_t)B);
+        if (top > 1) w.top_g = take((size_t)c->top.rows * (size_t)B);
+    } else {
+        // values of the tail layers, one run of tail_rows floats per batch column
+        w.tb = take((size_t)c->tail_rows * (size_t)B);
+        // the layer below the persistent forward kernel's first one, column-major, for that kernel to read
+        w.stage = take((size_t)tail_stage_rows(c, B) * (size_t)B);
+    }
     if (need_bwd) {
         // adjoints: one row per node of the layers 0 .. alias_top, and two buffers of the widest layer above
         // them that the layer-by-layer part of the sweep alternates between
-        w.g0 = off; off += align_floats((size_t)p.row0[(size_t)p.alias_top + 1] * g.ld);
-        w.g1 = off; off += align_floats((size_t)top_layer_rows(p) * g.ld);
-        w.g2 = off; off += align_floats((size_t)top_layer_rows(p) * g.ld);
+        w.g0 = take((size_t)p.row0[(size_t)p.alias_top + 1] * g.ld);
+        w.g1 = take((size_t)top_layer_rows(p) * g.ld);
+        w.g2 = take((size_t)top_layer_rows(p) * g.ld);
         // one word per layer: the real-semiring sweep's "a node value of this product layer is zero" flags
-        w.flags = off; off += align_floats((size_t)p.num_layers + 1);
-    }
-    w.counted = off;
-    if (const int first = choose_top(c, B); first > 0) {
-        // the level below its first one, the values of the others, their adjoints: column-major
-        w.top_stage = off; off += align_floats((size_t)c->top.n[(size_t)first - 1] * (size_t)B);
-        w.top_tb = off; off += align_floats((size_t)c->top.rows * (size_t)B);
-        if (need_bwd) { w.top_g = off; off += align_floats((size_t)c->top.rows * (size_t)B); }
+        w.flags = take((size_t)p.num_layers + 1);
     }
     w.total = off;
+    if (top > 1 && B >= kTopStageB) {
+        // The level below the first one has no buffer of its own.  It takes the adjoint rows, which a forward pass does not use (its
+        // rows stand for as many nodes of the layers below `top`, each of which has one); without those the activation rows of the
+        // layers that stay in the kernel, where they are enough.
+        const size_t n = (size_t)c->top.n[(size_t)top - 1] * (size_t)B, rows = align_floats((size_t)p.row0[(size_t)top] * g.ld);
+        if (need_bwd) w.top_stage = w.g0;
+        else if (rows + n <= (size_t)p.num_nodes * g.ld) w.top_stage = w.act + rows;
+        if (w.top_stage) w.top_stage_n = n;
+    }
     return w;
 }
 
@@ -438,9 +452,8 @@ void release_events(klay_circuit* c) {
     c->ev_bwd.clear();
 }
 
-klay_status get_workspace(klay_circuit* c, int B, bool need_bwd, float** base, Workspace* lay) {
-    *lay = workspace_layout(c, B, need_bwd);
-    const size_t bytes = lay->total * sizeof(float);
+klay_status get_workspace(klay_circuit* c, size_t floats, float** base) {
+    const size_t bytes = floats * sizeof(float);
     if (c->ws_user) {
         if (bytes > c->ws_user_bytes)
             return fail(KLAY_ENOMEM, "caller workspace too small: need " + std::to_string(bytes) + " bytes");
@@ -451,12 +464,48 @@ klay_status get_workspace(klay_circuit* c, int B, bool need_bwd, float** base, W
         if (c->ws_own) { KLAY_HIP(hipFree(c->ws_own)); c->ws_own = nullptr; c->ws_own_bytes = 0; }
         if (hipMalloc(&c->ws_own, bytes) != hipSuccess) {
             (void)hipGetLastError();
+            c->ws_own = nullptr;
             return fail(KLAY_ENOMEM, "hipMalloc of " + std::to_string(bytes) + " workspace bytes failed");
         }
         c->ws_own_bytes = bytes;
     }
     *base = static_cast<float*>(c->ws_own);
     return KLAY_OK;
+}
+
+// The memory of a forward pass: the fixed array or the handle's workspace.  `top` becomes 0 where the TopPlan would need more than
+// there is and the pass without it does not; with_bwd: whether a reverse sweep can follow.
+klay_status forward_workspace(klay_circuit* c, int B, bool static_ws, int& top, bool& with_bwd, float** base, Workspace* lay) {
+    with_bwd = !static_ws;
+    if (static_ws || c->ws_user) {
+        const size_t have = (static_ws ? kStaticWorkspaceBytes : c->ws_user_bytes) / sizeof(float);
+        if (with_bwd && top > 0 && workspace_layout(c, B, true, top).total > have && workspace_layout(c, B, true, 0).total <= have) top = 0;
+        // the backward regions are part of the layout whenever the workspace can hold them
+        if (with_bwd && workspace_layout(c, B, true, top).total > have) with_bwd = false;
+        *lay = workspace_layout(c, B, with_bwd, top);
+        if (top > 1 && B >= kTopStageB && !lay->top_stage_n) {
+            const size_t n = (size_t)c->top.n[(size_t)top - 1] * (size_t)B;
+            if (lay->total + n <= have) {
+                lay->top_stage = lay->total;
+                lay->top_stage_n = n;
+            }
+        }
+        if (!static_ws) return get_workspace(c, lay->total, base);
+        if (lay->total > have)
+            return fail(KLAY_ENOMEM, "klay_forward_static: this circuit at B = " + std::to_string(B) + " needs " +
+                                         std::to_string(lay->total * sizeof(float)) + " workspace bytes, the fixed buffer holds " +
+                                         std::to_string(kStaticWorkspaceBytes));
+        KLAY_HIP(static_workspace(c->device, base));
+        return KLAY_OK;
+    }
+    *lay = workspace_layout(c, B, true, top);
+    klay_status st = get_workspace(c, lay->total, base);
+    if (st == KLAY_ENOMEM && top > 0) {
+        top = 0;
+        *lay = workspace_layout(c, B, true, 0);
+        st = get_workspace(c, lay->total, base);
+    }
+    return st;
 }
 
 // Packs host arrays into one buffer with 256-byte aligned starts; returns offsets in ints.
@@ -1088,11 +1137,8 @@ void launch_tail_fwd(const klay_circuit* c, const TailChoice& t, const float* ac
     launch_col_fwd(c, c->tail, t.first, start, start_T, nullptr, keep ? tb : nullptr, (int)buf.T, B, ld, semiring, leaf, out, s);
 }
 
-// Levels above which a workgroup reads the level below the first one from its rows: fewer columns are not worth the launch that
-// makes columns of them.
-constexpr int kTopStageB = 16;
-
-// The same over the TopPlan.  tb: as above, or null (the values are not kept).
+// The same over the TopPlan.  stage: room for the level below the first one, or null (the kernel reads its rows); tb: as above, or
+// null (the values are not kept).
 void launch_top_fwd(const klay_circuit* c, int first, const float* act, float* stage, float* tb, int B, int ld, int semiring, const klay::SlabLeaf& leaf,
                     float* out, hipStream_t s) {
     const int nb = (int)c->top.n[(size_t)first - 1];
@@ -1100,7 +1146,7 @@ void launch_top_fwd(const klay_circuit* c, int first, const float* act, float* s
     const int32_t* map = own;
     const float* start = act;
     int start_T = 0;
-    if (first > 1 && B > kTopStageB) {
+    if (stage) {
         dim3 tg((unsigned)((nb + 31) / 32), (unsigned)((B + 31) / 32));
         hipLaunchKernelGGL(klay::rows_to_cols_kernel<true>, tg, dim3(256), 0, s, act, nb, B, ld, stage, nb, own);
         start = stage;
@@ -1349,7 +1395,8 @@ int choose64(const klay_circuit* c, const ColTail& t, int B) {
 }
 const ColTail& tail64(const klay_circuit* c) { return c->top.first > 0 ? c->top : c->tail; }
 
-Workspace64 workspace_layout64(const klay_circuit* c, int B, int ld) {
+// first: of the layers of tail64 that the persistent kernels take (0: none)
+Workspace64 workspace_layout64(const klay_circuit* c, int B, int ld, int first) {
     const klay::CircuitPlan& p = c->plan;
     Workspace64 w;
     size_t off = 0;
@@ -1362,7 +1409,7 @@ Workspace64 workspace_layout64(const klay_circuit* c, int B, int ld) {
     w.g1 = take((size_t)top_layer_rows(p) * ld);
     w.g2 = take((size_t)top_layer_rows(p) * ld);
     // the persistent kernels' values, and the adjoints they leave to the launches, column-major
-    if (const int first = choose64(c, tail64(c), B); first > 0) {
+    if (first > 0) {
         w.tb = take((size_t)tail64(c).rows * B);
         if (first > 1) w.gcols = take((size_t)tail64(c).rows * B);
     }
@@ -1446,15 +1493,24 @@ klay_status forward64_impl(klay_circuit* c, const double* w, const double* wneg,
     const klay::CircuitPlan& p = c->plan;
     const int ld = B > 64 ? (B + 1) / 2 * 2 : B;       // even rows for two columns per lane
     c->have_fwd64 = false;
-    const Workspace64 lay = workspace_layout64(c, B, ld);
-    const size_t bytes = lay.total * sizeof(double);
-    if (bytes > c->ws64_bytes) {
+    const ColTail& tail = tail64(c);
+    int first = choose64(c, tail, B);
+    Workspace64 lay = workspace_layout64(c, B, ld, first);
+    if (lay.total * sizeof(double) > c->ws64_bytes) {
         if (c->ws64) { KLAY_HIP(hipFree(c->ws64)); c->ws64 = nullptr; c->ws64_bytes = 0; }
-        if (hipMalloc(&c->ws64, bytes) != hipSuccess) {
+        hipError_t e = hipMalloc(&c->ws64, lay.total * sizeof(double));
+        if (e != hipSuccess && first > 0) {          // the launches need less
             (void)hipGetLastError();
-            return fail(KLAY_ENOMEM, "hipMalloc of " + std::to_string(bytes) + " workspace bytes failed");
+            first = 0;
+            lay = workspace_layout64(c, B, ld, first);
+            e = hipMalloc(&c->ws64, lay.total * sizeof(double));
         }
-        c->ws64_bytes = bytes;
+        if (e != hipSuccess) {
+            (void)hipGetLastError();
+            c->ws64 = nullptr;
+            return fail(KLAY_ENOMEM, "hipMalloc of " + std::to_string(lay.total * sizeof(double)) + " workspace bytes failed");
+        }
+        c->ws64_bytes = lay.total * sizeof(double);
     }
     double* ws = static_cast<double*>(c->ws64);
     double* act = ws + lay.act;
@@ -1472,8 +1528,6 @@ klay_status forward64_impl(klay_circuit* c, const double* w, const double* wneg,
     if (c->false_row >= 0)
         hipLaunchKernelGGL(klay::f64::fill_row_kernel, row_grid, dim3(256), 0, s, act + (size_t)c->false_row * ld, ld,
                            log_domain ? (double)-INFINITY : 0.0);
-    const ColTail& tail = tail64(c);
-    const int first = choose64(c, tail, B);
     for (int l = 1; l <= (first > 0 ? first - 1 : L); ++l) {
         const DevLayer& d = c->dl[(size_t)l];
         const bool is_and = (l & 1) != 0;
@@ -1519,7 +1573,7 @@ klay_status backward64_impl(klay_circuit* c, const double* dout, double* dleaf, 
     hipStream_t s = static_cast<hipStream_t>(stream);
     const klay::CircuitPlan& p = c->plan;
     const int B = c->last64_B, ld = B > 64 ? (B + 1) / 2 * 2 : B;
-    const Workspace64 lay = workspace_layout64(c, B, ld);
+    const Workspace64 lay = workspace_layout64(c, B, ld, c->last64_tail ? c->last64_first : 0);
     double* ws = static_cast<double*>(c->ws64);
     double* act = ws + lay.act;
     double* wT = ws + lay.wT;
@@ -1874,7 +1928,8 @@ klay_status klay_root_positions(const klay_circuit* c, int32_t* position) {
 
 size_t klay_workspace_bytes(const klay_circuit* c, int32_t B, int need_backward) {
     if (!c || B < 1) return 0;
-    return workspace_layout(c, B, need_backward != 0).total * sizeof(float);
+    if (!need_backward) return workspace_layout(c, B, false, 0).total * sizeof(float);
+    return std::max(workspace_layout(c, B, true, 0).total, workspace_layout(c, B, true, choose_top(c, B)).total) * sizeof(float);
 }
 
 klay_status klay_set_workspace(klay_circuit* c, void* dev_ptr, size_t bytes) {
@@ -1932,21 +1987,14 @@ static klay_status forward_impl(klay_circuit* c, const float* leaf_weights, cons
     float* ws = nullptr;
     Workspace lay;
     if (!static_ws) c->have_fwd = false;     // a static call leaves the handle's own forward state alone
-    // the backward regions are part of the layout whenever the workspace can hold them
-    bool with_bwd = true;
-    if (static_ws) {
-        with_bwd = false;
-        lay = workspace_layout(c, B, false);
-        if (lay.counted * sizeof(float) > kStaticWorkspaceBytes)
-            return fail(KLAY_ENOMEM, "klay_forward_static: this circuit at B = " + std::to_string(B) + " needs " +
-                                         std::to_string(lay.counted * sizeof(float)) + " workspace bytes, the fixed buffer holds " +
-                                         std::to_string(kStaticWorkspaceBytes));
-        KLAY_HIP(static_workspace(c->device, &ws));
-    } else {
-        if (c->ws_user && workspace_layout(c, B, true).total * sizeof(float) > c->ws_user_bytes) with_bwd = false;
-        klay_status st = get_workspace(c, B, with_bwd, &ws, &lay);
-        if (st != KLAY_OK) return st;
-    }
+    // the top layers run in one persistent kernel; when that kernel starts at layer 1 it evaluates the
+    // leaf layer itself (a workgroup reads its own rows of the weight arrays)
+    int top_first = choose_top(c, B);
+    bool with_bwd = false;
+    klay_status st = forward_workspace(c, B, static_ws, top_first, with_bwd, &ws, &lay);
+    if (st != KLAY_OK) return st;
+    const TailChoice tail = top_first > 0 ? TailChoice() : choose_tail_fwd(c, B);
+    const bool fused_leaf = tail.first == 1 || top_first == 1;
 
     float* act = ws + lay.act;
     float* wT = ws + lay.wT;
@@ -1954,12 +2002,6 @@ static klay_status forward_impl(klay_circuit* c, const float* leaf_weights, cons
     const int L = p.num_layers;
     const int V = p.num_vars;
     Profiler prof(c, &c->ev_fwd, s, !static_ws);
-
-    // the top layers run in one persistent kernel; when that kernel starts at layer 1 it evaluates the
-    // leaf layer itself (a workgroup reads its own rows of the weight arrays)
-    const int top_first = choose_top(c, B);
-    const TailChoice tail = top_first > 0 ? TailChoice() : choose_tail_fwd(c, B);
-    const bool fused_leaf = tail.first == 1 || top_first == 1;
 
     // leaf layer
     if (!fused_leaf) {
@@ -2027,7 +2069,7 @@ static klay_status forward_impl(klay_circuit* c, const float* leaf_weights, cons
         prof.begin(KLAY_K_TAIL_FWD, tail_alg_bytes(which, first, B, false) + 8.0 * B * p.num_roots,
                    tail_min_bytes(which, first, B, false) + 4.0 * B * p.num_roots);
         if (top_first > 0)
-            launch_top_fwd(c, top_first, act, ws + lay.top_stage, static_ws ? nullptr : ws + lay.top_tb, B, g.ld, (int)semiring, leaf, out, s);
+            launch_top_fwd(c, top_first, act, lay.top_stage_n ? ws + lay.top_stage : nullptr, with_bwd ? ws + lay.top_tb : nullptr, B, g.ld, (int)semiring, leaf, out, s);
         else
             launch_tail_fwd(c, tail, act, ws + lay.tb, !static_ws, B, g.ld, (int)semiring, leaf, out, s);
         prof.end();
@@ -2073,8 +2115,8 @@ static klay_status backward_impl(klay_circuit* c, const float* dout, float* dlea
     const int B = c->last_B;
     const Geometry g = geometry(B);
     float* ws = nullptr;
-    Workspace lay;
-    klay_status st = get_workspace(c, B, true, &ws, &lay);
+    const Workspace lay = workspace_layout(c, B, true, c->last_top_first);
+    klay_status st = get_workspace(c, lay.total, &ws);
     if (st != KLAY_OK) return st;
     float* act = ws + lay.act;
     float* wT = ws + lay.wT;
