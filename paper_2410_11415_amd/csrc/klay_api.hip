@@ -2041,8 +2041,9 @@ static klay_status forward_impl(klay_circuit* c, const float* leaf_weights, cons
                         : op == klay::OP_MAX ? KLAY_K_FWD_MAX : KLAY_K_FWD_LSE;
         // up to alias_top child entries are rows of the whole buffer, above it of the layer below
         const float* below = l <= p.alias_top ? act : act + (size_t)c->dl[(size_t)l - 1].row0 * g.ld;
-        if (fused && is_and && d.n_fused > 0) {
-            // the fused rows are not evaluated: the OR rows above read their children
+        if (fused && is_and && d.n_fused > 0 && !(top_first > 0 && l >= top_first - 1)) {
+            // the fused rows are not evaluated: the OR rows above read their children (those of the layer that the TopPlan's
+            // kernel reads are)
             if (d.has_fwd_kept) run_pass_set(op, op, d.fwd_kept, below, nullptr, nullptr, act + (size_t)d.row0 * g.ld, seg_rows, g, B, s, prof, cls);
         } else if (fused && !is_and && d.has_fwd2) {
             run_pass_set(!log_domain ? klay::OP_SUMPROD2 : semiring == KLAY_MAXLOG ? klay::OP_MAX2 : klay::OP_LSE2, op, d.fwd2, below, nullptr, nullptr,
@@ -2138,7 +2139,7 @@ static klay_status backward_impl(klay_circuit* c, const float* dout, float* dlea
     if (c->last_fused) {
         // The forward pass ran the fused plans: the values of the fused AND rows, which this sweep needs, were
         // never written.  Evaluate those layers now (all their rows; the others come out the same again).
-        for (int l = 1; l < B0; l += 2) {
+        for (int l = 1; l < (c->last_top_first > 0 ? c->last_top_first - 1 : B0); l += 2) {
             const DevLayer& d = c->dl[(size_t)l];
             if (d.n_fused > 0)
                 run_pass_set(real ? klay::OP_PROD : klay::OP_SUM, real ? klay::OP_PROD : klay::OP_SUM, d.fwd, act, nullptr, nullptr,

@@ -582,8 +582,9 @@ int layerize(int32_t V, int64_t N, const uint8_t* node_type, const int32_t* node
             int64_t gates = 0;
             for (int64_t j = child_ptr[c]; j < child_ptr[c + 1]; ++j) gates += h[(size_t)child_idx[j]] > 0;
             cand[(size_t)c] = fi >= 1 && gates <= 1 && fi <= row_max;
-            // (a node that the persistent kernels may read or evaluate is written)
-            if (top_first > 0 && need[(size_t)c] >= top_first - 1) cand[(size_t)c] = 0;
+            // (a TopPlan from layer f on reads the nodes below f that are read from f - 1 or above: with fused rows that are read
+            // from the next layer only, those are the ones of layer f - 1, see klay_forward)
+            if (top_first > 0 && need[(size_t)c] >= top_first - 1 && need[(size_t)c] > h[(size_t)c]) cand[(size_t)c] = 0;
         }
         // every parent has to be an OR row that stays short when it reads the children of its fused children
         for (int64_t p = 0; p < N; ++p) {
@@ -598,8 +599,24 @@ int layerize(int32_t V, int64_t N, const uint8_t* node_type, const int32_t* node
             if (!any || ((h[(size_t)p] & 1) == 0 && len <= row_max)) continue;
             for (int64_t j = child_ptr[p]; j < child_ptr[p + 1]; ++j) cand[(size_t)child_idx[j]] |= 2;      // not through this parent
         }
+        // In the layers that a TopPlan may take, fused rows are for the batches that leave them to the launches; there a layer has to be wide and
+        // mostly fused.  (kTopFusedRows, kTopFusedShare; forward, us, no fused rows there / without the two limits / with: 41000 nodes in
+        // 24 layers, fan-ins up to 400, B = 1300 276 / 290 / 273, B = 2500 386 / 364 / 363; 24000 in 16 layers, up to 100, B = 1300
+        // 169 / 187 / 168; 58000 in 20 layers, up to 300, B = 1600 293 / 259 / 267; 51000 in 14 layers, up to 1952, 1 in 60 fused, B = 400
+        // 176 / 180 / 176.)
+        std::vector<int64_t> rows((size_t)L + 1, 0), rows_fused((size_t)L + 1, 0);
         for (int64_t c = 0; c < N; ++c)
-            if (cand[(size_t)c] == 1) { fused[(size_t)c] = 1; ++plan.num_fused; }
+            if (reach[(size_t)c]) {
+                ++rows[(size_t)h[(size_t)c]];
+                rows_fused[(size_t)h[(size_t)c]] += cand[(size_t)c] == 1;
+            }
+        for (int64_t c = 0; c < N; ++c) {
+            if (cand[(size_t)c] != 1) continue;
+            const size_t l = (size_t)h[(size_t)c];
+            if (top_first > 0 && need[(size_t)c] >= top_first - 1 && (rows[l] < kTopFusedRows || rows_fused[l] * kTopFusedShare < rows[l])) continue;
+            fused[(size_t)c] = 1;
+            ++plan.num_fused;
+        }
     }
 
     std::vector<int64_t> count((size_t)L + 1, 0);

@@ -87,6 +87,8 @@ constexpr uint32_t kGroupEnd = kWeightedEdge;
 // of 75% of the AND rows of the layered circuits fused, and the forward pass 3% slower: the long rows cost the
 // fused launches more than the shorter AND launches save.)
 constexpr int64_t kFusedRowMax = 24;
+// Layers that a TopPlan may take have fused rows from this many nodes on, if one in this many is fused.
+constexpr int64_t kTopFusedRows = 5000, kTopFusedShare = 4;
 constexpr int64_t kMaxRows = (int64_t)1 << 29;      // row ids fit the 29-bit source field
 constexpr int kIdxPad = 16;
 // Split rows of more partial rows than this take a workgroup each in the combine pass, the others a wave.
