@@ -155,8 +155,8 @@ __device__ __forceinline__ int xcd_block(int bid, int nblocks) { return (bid & 7
 //                     (a sum node above, or a root's dout row) and is added as it is.  acc = sum of the plain entries, mx = sum of
 //                     the P_r that concern the child (-0 as long as there is none), divided by `own` once, in finish():
 //                     a division takes ten instructions, and one per entry and column bound the wide layers (800000
-//                     nodes at B = 256, training step 1251 -> 1192 us).  The P_r are added times a power of two that is
-//                     about 1 / own (share_scale), so that the sum stays in range wherever the quotients do.
+//                     nodes at B = 256, training step 1251 -> 1185 us).  Where that sum may leave the range, the P_r are
+//                     added times a power of two that is about 1 / own (share_scale): it stays in range wherever the quotients do.
 //   OP_SUM_P, OP_PROD_BWD_P   OP_SUM / OP_PROD_BWD whose output rows are AND nodes: the finished adjoint G
 //                     leaves as G * (the node's own value), lowest mantissa bit clear, which is the row P
 //                     above whenever the node has no zero child; where the own value is zero G is left
@@ -203,7 +203,8 @@ __device__ __forceinline__ void lse_step(float& acc, float& mx, float x) {
 }
 
 // nc: the value of the output row itself where the operation needs it; OP_LSE2 / OP_MAX2 keep the sum of the
-// group in hand there (weighted = the entry closes its group).  y: OP_SOFTMAX_BWD the parent's value, the P row ops share_scale(nc).
+// group in hand there (weighted = the entry closes its group).  y: OP_SOFTMAX_BWD the parent's value, the P row ops share_scale(nc), or 1
+// (a single entry, or a sum that is then looked at).
 template <int OP>
 __device__ __forceinline__ void accumulate(float& acc, float& mx, float x, float y, float& nc, bool weighted = true) {
     if (OP == OP_SUM_H || OP == OP_SUM_P) { acc += x; return; }
@@ -306,9 +307,10 @@ __global__ __launch_bounds__(256) void stream_kernel(const int2* __restrict__ ta
     const float* ownc = own + col;
     float* dstc = dst + col;
 
-    float acc[VEC], mx[VEC], nc[VEC], scale[VEC];
+    float acc[VEC], mx[VEC], nc[VEC];
 #pragma unroll
-    for (int v = 0; v < VEC; ++v) { acc[v] = identity<OP>(); mx[v] = identity2<OP>(); nc[v] = OP == OP_SUMPROD2 ? 1.0f : 0.0f; scale[v] = 1.0f; }
+    for (int v = 0; v < VEC; ++v) { acc[v] = identity<OP>(); mx[v] = identity2<OP>(); nc[v] = OP == OP_SUMPROD2 ? 1.0f : 0.0f; }
+    float most = 0.0f;                       // P row ops: the largest sum of P rows
     bool fresh = true;                       // the next edge opens a new output row
     uint32_t ids[CH];
 #pragma unroll
@@ -360,22 +362,19 @@ __global__ __launch_bounds__(256) void stream_kernel(const int2* __restrict__ ta
             if (OWN) {
 #pragma unroll
                 for (int v = 0; v < VEC; ++v) nc[v] = (live && first[i]) ? z[i][v] : nc[v];
-                if (OpTraits<OP>::shares && live && first[i]) {
-#pragma unroll
-                    for (int v = 0; v < VEC; ++v) scale[v] = share_scale(nc[v]);
-                }
             }
 #pragma unroll
             for (int v = 0; v < VEC; ++v) {
                 const float xv = live ? x[i][v] : dead_value<OP>();
-                const float yv = OP == OP_SOFTMAX_BWD ? (live ? y[i][v] : -INFINITY) : scale[v];
+                const float yv = OP == OP_SOFTMAX_BWD ? (live ? y[i][v] : -INFINITY) : 1.0f;
                 accumulate<OP>(acc[v], mx[v], xv, yv, nc[v], OpTraits<OP>::shares ? !live || (ids[i] & kWeighted) != 0 : live && (ids[i] & kWeighted) != 0);
             }
             if (live && (ids[i] & kLast)) {
                 float o[VEC];
 #pragma unroll
                 for (int v = 0; v < VEC; ++v) {
-                    o[v] = finish<OP>(acc[v], mx[v], nc[v], scale[v]);
+                    if (OpTraits<OP>::shares) most = fmaxf(most, fabsf(mx[v]));
+                    o[v] = finish<OP>(acc[v], mx[v], nc[v]);
                     // the adjoint of an OR node with more than one child leaves in the one-gather form
                     if (OP == OP_SUM_H && !seg && (ids[i] & kRowFlag)) o[v] = encode_h(o[v], nc[v]);
                     if (OpTraits<OP>::premul && !seg) {
@@ -392,6 +391,37 @@ __global__ __launch_bounds__(256) void stream_kernel(const int2* __restrict__ ta
 #pragma unroll
         for (int i = 0; i < CH; ++i) ids[i] = nxt[i];
         j += CH;
+    }
+    if (!OpTraits<OP>::shares || !__any(most == INFINITY)) return;
+    // A sum of P rows left the range: the task's rows once more, every P row scaled before it is added.  (Rare; scaling always costs 7 to
+    // 10% where layers are narrow: 16000 nodes in 40 layers at B = 256, training step 373 us / 401.)
+    row = t0.x;
+    fresh = true;
+    for (j = t0.y; j < e1; ++j) {
+        const uint32_t id = idx[j];
+        const bool last = (id & kLast) != 0;
+        if (id != kSkip) {
+            if (fresh) {
+                load_vec<VEC>(nc, ownc + (size_t)(seg ? seg_owner[row - n_main] : row) * (size_t)ld);
+#pragma unroll
+                for (int v = 0; v < VEC; ++v) { acc[v] = identity<OP>(); mx[v] = identity2<OP>(); }
+            }
+            float x[VEC];
+            load_vec<VEC>(x, srcc + (size_t)(id & kIdMask) * (size_t)ld);
+#pragma unroll
+            for (int v = 0; v < VEC; ++v) accumulate<OP>(acc[v], mx[v], x[v], share_scale(nc[v]), nc[v], (id & kWeighted) != 0);
+            if (last) {
+                float o[VEC];
+#pragma unroll
+                for (int v = 0; v < VEC; ++v) {
+                    o[v] = finish<OP>(acc[v], mx[v], nc[v], share_scale(nc[v]));
+                    if (OpTraits<OP>::premul && !seg) o[v] = premultiply(o[v], nc[v]);
+                }
+                store_vec<VEC>(dstc + (size_t)row * (size_t)ld, o);
+            }
+        }
+        fresh = last;
+        row += last ? 1 : 0;
     }
 }
 
@@ -507,8 +537,8 @@ __global__ __launch_bounds__(256) void edge_kernel(const int2* __restrict__ task
                 vm = live ? ((id[i] & kWeighted) ? decode_h(x[i], z[i]) : x[i]) : 0.0f;
             } else if (OpTraits<OP>::shares) {
                 float plain = 0.0f, shared = identity2<OP>();
-                accumulate<OP>(plain, shared, x[i], share_scale(z[i]), z[i], (id[i] & kWeighted) != 0);
-                vm = live ? finish<OP>(plain, shared, z[i], share_scale(z[i])) : 0.0f;
+                accumulate<OP>(plain, shared, x[i], 1.0f, z[i], (id[i] & kWeighted) != 0);
+                vm = live ? finish<OP>(plain, shared, z[i]) : 0.0f;
             } else if (LSE) {
                 vm = live ? fmaxf(x[i], -INFINITY) : -INFINITY;
                 vs = live ? 1.0f : 0.0f;
