@@ -288,6 +288,13 @@ klay_status klay_root_positions(const klay_circuit* c, int32_t* position);
  * persistent kernels' buffers depend on which layers fit). */
 size_t klay_workspace_bytes(const klay_circuit* c, int32_t B, int need_backward);
 
+/* Which layers a forward pass over B columns gives to the persistent kernels: *first_layer and all above it (0: none, every layer is
+ * launched by itself), *plan = 1: the layers of the circuit as klay_layer_csr shows them, 2: the narrow top of a circuit with long
+ * rows, whose chain nodes exist in those kernels only, 0 with *first_layer = 0.  double_precision: klay_forward_f64; training: the previous
+ * forward pass of the handle was followed by a backward pass.  Handles built with device = -1 answer as for klay_workspace_bytes. */
+klay_status klay_persistent_layers(const klay_circuit* c, int32_t B, klay_semiring semiring, int32_t double_precision, int32_t training,
+                                   int32_t* first_layer, int32_t* plan);
+
 /* Use caller device memory (256-byte aligned) as workspace instead of library-owned memory;
  * dev_ptr = NULL returns to library-owned memory.  The caller keeps ownership. */
 klay_status klay_set_workspace(klay_circuit* c, void* dev_ptr, size_t bytes);

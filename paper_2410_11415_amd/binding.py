@@ -27,7 +27,7 @@ EXPORTS = ("klay_build", "klay_build_ex", "klay_forward", "klay_backward", "klay
            "klay_layer_csr", "klay_layer_nodes", "klay_workspace_bytes", "klay_set_workspace",
            "klay_set_profiling", "klay_get_profile", "klay_destroy", "klay_last_error", "klay_builder_create",
            "klay_builder_add", "klay_builder_finish", "klay_builder_destroy", "klay_forward_lits", "klay_backward_lits", "klay_root_positions", "klay_forward_f64",
-           "klay_backward_f64", "klay_forward_static")
+           "klay_backward_f64", "klay_forward_static", "klay_persistent_layers")
 
 
 class KlayError(RuntimeError):
@@ -111,6 +111,8 @@ def load():
     lib.klay_root_positions.argtypes = [vp, vp]
     lib.klay_workspace_bytes.restype = ctypes.c_size_t
     lib.klay_workspace_bytes.argtypes = [vp, i32, ctypes.c_int]
+    lib.klay_persistent_layers.restype = ctypes.c_int
+    lib.klay_persistent_layers.argtypes = [vp, i32, ctypes.c_int, i32, i32, ctypes.POINTER(i32), ctypes.POINTER(i32)]
     lib.klay_set_workspace.restype = ctypes.c_int
     lib.klay_set_workspace.argtypes = [vp, vp, ctypes.c_size_t]
     lib.klay_set_profiling.restype = ctypes.c_int
@@ -309,6 +311,12 @@ class Circuit:
 
     def workspace_bytes(self, B: int, need_backward: bool = True) -> int:
         return int(load().klay_workspace_bytes(self._h, int(B), int(need_backward)))
+
+    def persistent_layers(self, B: int, semiring=KLAY_LOG, double_precision: bool = False, training: bool = False):
+        """(first layer, plan) that a forward pass over B columns gives to the persistent kernels: see include/klay.h"""
+        first, plan = ctypes.c_int32(), ctypes.c_int32()
+        _check(load().klay_persistent_layers(self._h, int(B), int(semiring), int(double_precision), int(training), ctypes.byref(first), ctypes.byref(plan)))
+        return first.value, plan.value
 
     def set_workspace(self, tensor):
         """Use a caller-owned torch CUDA tensor as workspace (None: back to library-owned memory)."""

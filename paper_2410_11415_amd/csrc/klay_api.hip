@@ -218,7 +218,7 @@ int64_t top_layer_rows(const klay::CircuitPlan& p) {
 }
 
 int64_t tail_stage_rows(const klay_circuit* c, int B);
-int choose_top(const klay_circuit* c, int B);
+int choose_top(const klay_circuit* c, int B, bool real_training = false);
 int tail_columns(int B, const int64_t (&size)[2], size_t lds_bytes, bool reverse);
 
 // Columns from which on the forward kernel reads the level below its first one from columns instead of its rows: fewer
@@ -498,9 +498,10 @@ klay_status forward_workspace(klay_circuit* c, int B, bool static_ws, int& top, 
         KLAY_HIP(static_workspace(c->device, base));
         return KLAY_OK;
     }
+    // (room for either way at once: a later pass over this batch, which may be captured, allocates nothing)
     *lay = workspace_layout(c, B, true, top);
-    klay_status st = get_workspace(c, lay->total, base);
-    if (st == KLAY_ENOMEM && top > 0) {
+    klay_status st = get_workspace(c, c->top.first > 0 ? klay_workspace_bytes(c, B, 1) / sizeof(float) : lay->total, base);
+    if (st == KLAY_ENOMEM) {
         top = 0;
         *lay = workspace_layout(c, B, true, 0);
         st = get_workspace(c, lay->total, base);
@@ -995,6 +996,8 @@ TailChoice choose_tail(const klay_circuit* c, int ct) {
     return t;
 }
 
+TailChoice choose_tail_fwd(const klay_circuit* c, int B) { return choose_tail(c, tail_ct(B, 4)); }
+
 // The first layer that the forward kernel takes from the TopPlan at a batch of B (0: none, the layers of the plan itself go the
 // other ways): the choice with the least time by a rough account.  In the persistent kernels a layer takes the time of its longest
 // wave and about 2000 cycles; a launch takes 3.5 us and what it gathers, from the caches, at 10 TB/s.  us, launches throughout / this
@@ -1005,18 +1008,25 @@ TailChoice choose_tail(const klay_circuit* c, int ct) {
 // First layers above 1 only up to B = 1024: 23200 nodes in 30 layers at B = 2000 536 / 483 (2), but 1080 / 1181 in training.  (The
 // reverse kernel could leave the sweep to the launches earlier; that gains at most 8%, 92000 nodes training B = 1 284 against 259,
 // and loses for B >= 64.)
-int choose_top(const klay_circuit* c, int B) {
+// (Layers of the plan itself that the persistent kernel would take otherwise, choose_tail_fwd, count as launches here.  With what that kernel saves
+// counted, no choice is another one: 37 circuits with such layers, 29 batches of 1 to 4000 columns.)
+// real_training: a forward pass in the real semiring in a training loop.  Its reverse sweep goes by launches over rows that the values of all
+// levels are put into first, and without the reverse kernel for the layers of the plan itself (7: a row of theirs for rows of levels).  Training
+// step, us, launches / TopPlan: 27000 nodes in 42 layers (20 of the plan itself) B = 256 442 / 385, B = 400 406 / 415, B = 1000 429 / 689; 21000
+// nodes in 44 layers B = 513 858 / 797, B = 1000 708 / 854; 16000 nodes in 30 layers B = 1000 465 / 361.
+int choose_top(const klay_circuit* c, int B, bool real_training) {
     const ColTail& t = c->top;
     if (t.first <= 0 || c->tail_lds_bytes == 0) return 0;
     const int L = c->plan.num_layers;
     double inside = 0, outside = 0, best = 0;          // us of the layers from l on, in the kernel and outside; what the best choice saves
-    int first = 0;
+    int first = 0, launches = 0, first_launches = 0;   // first: of the best choice
     int64_t size[2] = {0, 0};                          // as tail_lds
     auto room = [&](int l) { size[l & 1] = std::max(size[l & 1], (t.n[(size_t)l] + klay::kColSlots + 3) / 4 * 4); };
     room(L);
     for (int l = L; l >= t.first; --l) {
         inside += (2000.0 + (double)t.share[(size_t)l]) / 2000.0;
         outside += 3.5 * t.launches[(size_t)l] + (double)t.e[(size_t)l] * B / 2.5e6;
+        launches += t.launches[(size_t)l];
         room(l - 1);
         if (l > std::min(c->plan.alias_top, L - 1)) continue;
         if ((size_t)(size[0] + size[1]) * sizeof(float) > c->tail_lds_bytes) break;
@@ -1028,12 +1038,12 @@ int choose_top(const klay_circuit* c, int B) {
         if (saved > best && (l == 1 || B <= 1024)) {
             best = saved;
             first = l;
+            first_launches = launches;
         }
     }
+    if (first > 0 && real_training && (double)(t.rows - t.at[(size_t)first] + 7 * c->tail_rows) * B > 1.4e6 * first_launches) return 0;
     return first;
 }
-
-TailChoice choose_tail_fwd(const klay_circuit* c, int B) { return choose_tail(c, tail_ct(B, 4)); }
 
 // Rows of the layer below the forward kernel's first one if that layer gets a place in the column-major buffer (where
 // the kernel reads it as one run per column, and the reverse kernel its values): where ct arrays of its length fit the
@@ -1932,6 +1942,24 @@ size_t klay_workspace_bytes(const klay_circuit* c, int32_t B, int need_backward)
     return std::max(workspace_layout(c, B, true, 0).total, workspace_layout(c, B, true, choose_top(c, B)).total) * sizeof(float);
 }
 
+klay_status klay_persistent_layers(const klay_circuit* c, int32_t B, klay_semiring semiring, int32_t double_precision, int32_t training,
+                                   int32_t* first_layer, int32_t* plan) {
+    if (!c || !first_layer || !plan) return fail(KLAY_EINVAL, "klay_persistent_layers: null argument");
+    if (B < 1) return fail(KLAY_EINVAL, "klay_persistent_layers: B must be >= 1");
+    if (semiring != KLAY_REAL && semiring != KLAY_LOG && semiring != KLAY_MAXLOG)
+        return fail(KLAY_EINVAL, "klay_persistent_layers: unknown semiring");
+    if (double_precision) {
+        *first_layer = choose64(c, tail64(c), B);
+        *plan = *first_layer == 0 ? 0 : &tail64(c) == &c->top ? 2 : 1;
+    } else if ((*first_layer = choose_top(c, B, semiring == KLAY_REAL && training != 0)) > 0) {
+        *plan = 2;
+    } else {
+        *first_layer = choose_tail_fwd(c, B).first;
+        *plan = *first_layer > 0 ? 1 : 0;
+    }
+    return KLAY_OK;
+}
+
 klay_status klay_set_workspace(klay_circuit* c, void* dev_ptr, size_t bytes) {
     if (!c) return fail(KLAY_EINVAL, "klay_set_workspace: null handle");
     if (dev_ptr && (reinterpret_cast<uintptr_t>(dev_ptr) & 255u))
@@ -1989,7 +2017,7 @@ static klay_status forward_impl(klay_circuit* c, const float* leaf_weights, cons
     if (!static_ws) c->have_fwd = false;     // a static call leaves the handle's own forward state alone
     // the top layers run in one persistent kernel; when that kernel starts at layer 1 it evaluates the
     // leaf layer itself (a workgroup reads its own rows of the weight arrays)
-    int top_first = choose_top(c, B);
+    int top_first = choose_top(c, B, semiring == KLAY_REAL && !static_ws && c->bwd_followed);
     bool with_bwd = false;
     klay_status st = forward_workspace(c, B, static_ws, top_first, with_bwd, &ws, &lay);
     if (st != KLAY_OK) return st;

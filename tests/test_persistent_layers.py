@@ -1,0 +1,87 @@
+"""Which layers go to the persistent kernels, by batch, semiring and direction (host-only handles): where both plans are there, and where
+the reverse sweep cannot follow the forward kernel."""
+import pytest
+
+from klay_synth.circuits import layered_random
+from paper_2410_11415_amd import KLAY_LOG, KLAY_MAXLOG, KLAY_REAL, Circuit, KlayError
+
+NONE, LAYERS, TOP = 0, 1, 2
+
+
+def handle(*args, **options):
+    seed, num_vars, depth, gates, fanin, groups = args
+    return Circuit(*layered_random(seed, num_vars, depth, gates, fanin=fanin, groups=groups).arrays(), device=-1, **options)
+
+
+@pytest.fixture(scope="module")
+def both():
+    """27000 nodes in 42 layers, the upper 20 of which have no long rows"""
+    return handle(1010, 1596, 42, 7055, ("zipf", 1.73, 152), 4)
+
+
+def test_the_log_semiring_takes_the_top_plan(both):
+    info = both.info()
+    assert 0 < info["alias_top_layer"] < info["num_layers"] and info["tail_first_layer"] == info["alias_top_layer"] + 1
+    for batch in (1, 64, 256, 513, 1000):
+        for training in (False, True):
+            for semiring in (KLAY_LOG, KLAY_MAXLOG):
+                assert both.persistent_layers(batch, semiring, training=training) == (1, TOP)
+
+
+@pytest.mark.parametrize("batch,plan", [(1, TOP), (64, TOP), (256, TOP), (768, LAYERS), (1000, LAYERS)])
+def test_a_training_loop_in_the_real_semiring_takes_it_where_that_pays_for_the_rows(both, batch, plan):
+    """us, launches / TopPlan: B = 256 442 / 385, B = 768 418 / 608, B = 1000 429 / 689"""
+    assert both.persistent_layers(batch, KLAY_REAL) == (1, TOP)
+    assert both.persistent_layers(batch, KLAY_REAL, training=True)[1] == plan
+
+
+def test_no_long_rows_and_no_persistent_kernels():
+    k = handle(3, 60, 10, 3000, ("geom", 2.0), 1)
+    assert k.persistent_layers(5) == (k.info()["tail_first_layer"], LAYERS)
+    assert k.persistent_layers(5, KLAY_REAL, training=True)[1] == LAYERS
+    k = handle(3, 60, 10, 3000, ("geom", 2.0), 1, no_tail=True)
+    assert k.persistent_layers(5) == (0, NONE) and k.persistent_layers(5, double_precision=True) == (0, NONE)
+    with pytest.raises(KlayError):
+        k.persistent_layers(0)
+
+
+@pytest.mark.gpu
+def test_a_real_training_loop_changes_over_and_can_be_captured_after_one_step():
+    """the first step runs the TopPlan, the following ones the layers of the plan itself, in the workspace of the first"""
+    import numpy as np
+    import torch
+
+    from klay_synth import leaf_probs
+    from tests.gpu_util import assert_grad_close, assert_real_close, oracle_eval
+    c, B = layered_random(4, 300, 10, 9000, fanin=("zipf", 2.2, 90), groups=2, num_roots=20), 600
+    k = Circuit(*c.arrays(), device=0)
+    assert k.persistent_layers(B, KLAY_REAL)[1] == TOP and k.persistent_layers(B, KLAY_REAL, training=True)[1] == LAYERS
+    k.set_profiling(True)
+    p = leaf_probs(7, B, c.num_vars, ("uniform", 0.5, 0.95))
+    p[::5, 3] = 0.0
+    d = np.ones((B, c.roots.shape[0]), np.float32)
+    ref, rgrad = oracle_eval(c, p, KLAY_REAL, d, or_levels=k.num_layers // 2)
+    w, dout = torch.from_numpy(p.astype(np.float32)).cuda(), torch.from_numpy(d).cuda()
+    out, grad = k.forward(w, KLAY_REAL), k.backward(dout)
+    assert k.get_profile()["tail_bwd"]["launches"] == 0
+    assert_real_close(out.cpu().numpy(), ref, "first step")
+    assert_grad_close(grad.cpu().numpy(), rgrad, "first step", real=True)
+    k.set_profiling(False)
+    out2, grad2 = torch.empty_like(out), torch.empty_like(grad)
+    side, graph = torch.cuda.Stream(), torch.cuda.CUDAGraph()
+    with torch.cuda.stream(side):
+        with torch.cuda.graph(graph, stream=side):
+            k.forward(w, KLAY_REAL, out=out2, stream=side)
+            k.backward(dout, dleaf=grad2, stream=side)
+    for _ in range(3):
+        out2.zero_()
+        grad2.zero_()
+        graph.replay()
+        torch.cuda.synchronize()
+        assert_real_close(out2.cpu().numpy(), ref, "replay")
+        assert_grad_close(grad2.cpu().numpy(), rgrad, "replay", real=True)
+    k.set_profiling(True)
+    k.forward(w, KLAY_REAL)
+    k.backward(dout)
+    assert k.get_profile()["tail_bwd"]["launches"] == 1
+    k.close()
