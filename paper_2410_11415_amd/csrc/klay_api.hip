@@ -196,6 +196,7 @@ struct klay_circuit {
     void* ws64 = nullptr;
     size_t ws64_bytes = 0;
     bool have_fwd64 = false;
+    bool bwd64_followed = false;               // the last double-precision forward pass was followed by a backward pass
     int32_t last64_B = 0;
     int last64_semiring = 0;
     bool last64_neg_explicit = false;
@@ -1371,15 +1372,19 @@ struct Workspace64 {
 };
 
 // The layers that the double-precision persistent kernels take at a batch of B: from `first` on (0: none), an odd layer, so that
-// the step below it is a plain sum that needs no values.  As choose_top (an OR layer's exponentials take the longer; a launch 4 us and
-// what it gathers and computes, 4e5 entries a us); the two directions take the same layers, and the reverse kernel has pairs of doubles
-// for every second one in the LDS.  From a TopPlan in part only up to 256 columns (92000 nodes with power-law fan-ins, training
-// step at B = 512 1667 us by launches, 1818 from layer 13 on).
-int choose64(const klay_circuit* c, const ColTail& t, int B) {
+// the step below it is a plain sum that needs no values; the two directions take the same layers.  The choice that saves most by a rough
+// account: a workgroup takes the time of the longest wave of each layer, 256 workgroups at a time, and moves the values; a launch takes
+// its time and what it gathers and writes.  (us, fitted to 11 circuits of 16 to 60 layers taken from layer 1 on, B = 1 to 2000, within 6 and 11%.)
+// In a training loop (`training`) both directions count.  The real semiring's sweep goes by launches, on rows that the values are
+// put into first.  us, launches / layer 1 on / this rule: 21000 nodes in 44 layers, forward B = 1000 508 / 477 / 477, B = 2000 762 / 942 / 762, training
+// B = 300 596 / 516 / 516, B = 513 698 / 826 / 698, real training B = 400 792 / 849 / 792.
+// From a TopPlan in part only up to 256 columns (92000 nodes with power-law fan-ins, training step at B = 512 1667 us by launches,
+// 1818 from layer 13 on).
+int choose64(const klay_circuit* c, const ColTail& t, int B, bool real, bool training) {
     if (t.first <= 0 || c->tail_lds_bytes == 0) return 0;
-    const int L = c->plan.num_layers;
+    const int L = c->plan.num_layers, turns = (B + 255) / 256;
     const bool top = &t == &c->top;
-    double inside = 0, outside = 0, best = 0;
+    double inside[2] = {0, 0}, work[2] = {0, 0}, launches = 0, best = 0;       // [1]: reverse sweep
     int first = 0;
     int64_t fwd[2] = {0, 0}, bwd[2] = {0, 0};
     auto room = [](int64_t (&size)[2], int l, int64_t n) { size[l & 1] = std::max(size[l & 1], (n + klay::kColSlots + 3) / 4 * 4); };
@@ -1390,13 +1395,27 @@ int choose64(const klay_circuit* c, const ColTail& t, int B) {
         if (t.kept[(size_t)l] > (int64_t)klay::f64::kColOwn * klay::kColThreads) break;
         const int64_t reverse = 2 * std::max(bwd[0], l == 1 ? (t.kept[0] + klay::kColSlots + 3) / 4 * 4 : 0) + bwd[1];
         if ((size_t)std::max(fwd[0] + fwd[1], reverse) * sizeof(double) > c->tail_lds_bytes) break;
-        inside += (1900.0 + (l & 1 ? 1.0 : 3.0) * (double)t.share[(size_t)l]) / 2400.0;
-        outside += 4.0 * t.launches[(size_t)l] + (double)t.e[(size_t)l] * B / 4e5;
+        const klay::LayerPlan& lay = c->plan.layers[(size_t)l];
+        const double share = (double)t.share[(size_t)l], e = (double)lay.e * B, n = (double)lay.n * B;
+        inside[0] += (l & 1 ? 0.40e-3 : 1.60e-3) * share;
+        inside[1] += (l & 1 ? 0.13e-3 : 2.38e-3) * share;
+        work[0] += 0.86e-6 * e + 3.66e-6 * n;
+        work[1] += 1.35e-6 * e + 4.29e-6 * n;
+        launches += t.launches[(size_t)l];
         if ((l & 1) == 0 || l == L || (top && (l > c->plan.alias_top || (l > 1 && B > 256)))) continue;
+        const double values = (double)(t.rows - t.at[(size_t)l]) * B;
         // what a reverse sweep puts into rows: values and adjoints of all of them, or the adjoints of the first
-        const double transposed = l == 1 ? 0.0 : 4.0 + (double)(top ? 2 * (t.rows - t.at[(size_t)l]) : t.kept[(size_t)l]) * B * 4e-6;
-        const double saved = outside - ((B + 255) / 256) * (4.0 + inside) - transposed;
-        if (saved > best) {
+        const double transposed = l == 1 ? 0.0 : 4.0 + (top ? 2 * values : (double)t.kept[(size_t)l] * B) * 4e-6;
+        const double leaves = l == 1 ? 60e-6 * c->plan.num_vars * B : 0.0;
+        double outside = 4.1 * launches + work[0] + leaves, saved = outside - 3.0 - turns * inside[0] - 1.6e-6 * values;
+        if (training && real) {
+            saved -= 0.7 * launches + 4.2e-6 * values;
+        } else if (training) {
+            const double reverse_launches = (top ? 2.7 : 4.15) * launches + work[1];
+            outside += reverse_launches;
+            saved += reverse_launches - turns * inside[1] - 2.1e-6 * values - transposed;
+        }
+        if (saved > best && saved > 0.05 * outside) {          // (not on a few percent of a rough account)
             best = saved;
             first = l;
         }
@@ -1504,23 +1523,29 @@ klay_status forward64_impl(klay_circuit* c, const double* w, const double* wneg,
     const int ld = B > 64 ? (B + 1) / 2 * 2 : B;       // even rows for two columns per lane
     c->have_fwd64 = false;
     const ColTail& tail = tail64(c);
-    int first = choose64(c, tail, B);
+    int first = choose64(c, tail, B, semiring == KLAY_REAL, c->bwd64_followed);
     Workspace64 lay = workspace_layout64(c, B, ld, first);
-    if (lay.total * sizeof(double) > c->ws64_bytes) {
+    // room for the choices of all passes over this batch at once: a later one, which may be captured, allocates nothing
+    size_t room = lay.total;
+    if (tail.first > 0)
+        for (const auto& [real, training] : {std::pair(false, false), std::pair(false, true), std::pair(true, true)})
+            room = std::max(room, workspace_layout64(c, B, ld, choose64(c, tail, B, real, training)).total);
+    if (room * sizeof(double) > c->ws64_bytes) {
         if (c->ws64) { KLAY_HIP(hipFree(c->ws64)); c->ws64 = nullptr; c->ws64_bytes = 0; }
-        hipError_t e = hipMalloc(&c->ws64, lay.total * sizeof(double));
-        if (e != hipSuccess && first > 0) {          // the launches need less
+        hipError_t e = hipMalloc(&c->ws64, room * sizeof(double));
+        if (e != hipSuccess && tail.first > 0) {     // the launches need less
             (void)hipGetLastError();
             first = 0;
             lay = workspace_layout64(c, B, ld, first);
-            e = hipMalloc(&c->ws64, lay.total * sizeof(double));
+            room = lay.total;
+            e = hipMalloc(&c->ws64, room * sizeof(double));
         }
         if (e != hipSuccess) {
             (void)hipGetLastError();
             c->ws64 = nullptr;
-            return fail(KLAY_ENOMEM, "hipMalloc of " + std::to_string(lay.total * sizeof(double)) + " workspace bytes failed");
+            return fail(KLAY_ENOMEM, "hipMalloc of " + std::to_string(room * sizeof(double)) + " workspace bytes failed");
         }
-        c->ws64_bytes = lay.total * sizeof(double);
+        c->ws64_bytes = room * sizeof(double);
     }
     double* ws = static_cast<double*>(c->ws64);
     double* act = ws + lay.act;
@@ -1562,6 +1587,7 @@ klay_status forward64_impl(klay_circuit* c, const double* w, const double* wneg,
     }
     KLAY_HIP(hipGetLastError());
     c->have_fwd64 = true;
+    c->bwd64_followed = false;
     c->last64_B = B;
     c->last64_semiring = semiring;
     c->last64_neg_explicit = wneg != nullptr;
@@ -1580,6 +1606,7 @@ klay_status backward64_impl(klay_circuit* c, const double* dout, double* dleaf, 
     if (dneg && !c->last64_neg_explicit)
         return fail(KLAY_ESTATE, "klay_backward_f64: dneg given, but the forward pass had no weights for the negated literals");
     KLAY_HIP(hipSetDevice(c->device));
+    c->bwd64_followed = true;
     hipStream_t s = static_cast<hipStream_t>(stream);
     const klay::CircuitPlan& p = c->plan;
     const int B = c->last64_B, ld = B > 64 ? (B + 1) / 2 * 2 : B;
@@ -1949,7 +1976,7 @@ klay_status klay_persistent_layers(const klay_circuit* c, int32_t B, klay_semiri
     if (semiring != KLAY_REAL && semiring != KLAY_LOG && semiring != KLAY_MAXLOG)
         return fail(KLAY_EINVAL, "klay_persistent_layers: unknown semiring");
     if (double_precision) {
-        *first_layer = choose64(c, tail64(c), B);
+        *first_layer = choose64(c, tail64(c), B, semiring == KLAY_REAL, training != 0);
         *plan = *first_layer == 0 ? 0 : &tail64(c) == &c->top ? 2 : 1;
     } else if ((*first_layer = choose_top(c, B, semiring == KLAY_REAL && training != 0)) > 0) {
         *plan = 2;

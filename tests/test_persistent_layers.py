@@ -35,6 +35,17 @@ def test_a_training_loop_in_the_real_semiring_takes_it_where_that_pays_for_the_r
     assert both.persistent_layers(batch, KLAY_REAL, training=True)[1] == plan
 
 
+@pytest.mark.parametrize("batch,forward,training,real", [
+    (1, TOP, TOP, TOP), (64, TOP, TOP, TOP), (256, TOP, TOP, TOP), (400, TOP, TOP, NONE), (513, TOP, NONE, NONE), (1000, TOP, NONE, NONE),
+    (2000, NONE, NONE, NONE)])
+def test_double_precision_takes_it_where_the_turns_of_256_columns_are_short_enough(both, batch, forward, training, real):
+    """us, launches / TopPlan: forward B = 1000 462 / 345, B = 2000 696 / 790; training B = 850 782 / 816; real training B = 400 722 / 745"""
+    assert both.persistent_layers(batch, KLAY_LOG, True) == ((1, forward) if forward else (0, NONE))
+    assert both.persistent_layers(batch, KLAY_MAXLOG, True)[1] == both.persistent_layers(batch, KLAY_REAL, True)[1] == forward
+    assert both.persistent_layers(batch, KLAY_LOG, True, training=True)[1] == training
+    assert both.persistent_layers(batch, KLAY_REAL, True, training=True)[1] == real
+
+
 def test_no_long_rows_and_no_persistent_kernels():
     k = handle(3, 60, 10, 3000, ("geom", 2.0), 1)
     assert k.persistent_layers(5) == (k.info()["tail_first_layer"], LAYERS)
@@ -43,6 +54,41 @@ def test_no_long_rows_and_no_persistent_kernels():
     assert k.persistent_layers(5) == (0, NONE) and k.persistent_layers(5, double_precision=True) == (0, NONE)
     with pytest.raises(KlayError):
         k.persistent_layers(0)
+
+
+@pytest.mark.gpu
+def test_a_double_precision_training_loop_changes_over_and_can_be_captured_after_one_step():
+    import numpy as np
+    import torch
+
+    from klay_synth import leaf_probs
+    from oracle import oracle
+    c, B = layered_random(1010, 200, 42, 5000, fanin=("zipf", 1.73, 152), groups=1), 520
+    k = Circuit(*c.arrays(), device=0)
+    assert k.persistent_layers(B, KLAY_LOG, True) == (1, TOP) and k.persistent_layers(B, KLAY_LOG, True, training=True) == (0, NONE)
+    w = np.log(leaf_probs(7, B, c.num_vars, ("uniform", 0.05, 0.95)).astype(np.float64))
+    d = np.random.default_rng(5).normal(size=(B, c.roots.shape[0]))
+    ref, rgrad = oracle.forward(*c.arrays(), w, 1, nthreads=8), oracle.backward(*c.arrays(), w, 1, d, nthreads=8)
+    mass = oracle.backward(*c.arrays(), w, 1, d, nthreads=8, path_mass=True)
+
+    def close(out, grad):
+        np.testing.assert_allclose(out.cpu().numpy(), ref, rtol=0, atol=1e-11 * max(1.0, np.abs(ref).max()))
+        assert np.all(np.abs(grad.cpu().numpy() - rgrad) <= 1e-10 * np.maximum(1.0, mass))
+
+    tw, td = torch.from_numpy(w).cuda(), torch.from_numpy(d).cuda()
+    close(k.forward_f64(tw), k.backward_f64(td))
+    side, graph = torch.cuda.Stream(), torch.cuda.CUDAGraph()
+    with torch.cuda.stream(side):
+        with torch.cuda.graph(graph, stream=side):
+            out = k.forward_f64(tw, stream=side)
+            grad = k.backward_f64(td, stream=side)
+    for _ in range(3):
+        out.zero_()
+        grad.zero_()
+        graph.replay()
+        torch.cuda.synchronize()
+        close(out, grad)
+    k.close()
 
 
 @pytest.mark.gpu
