@@ -648,17 +648,10 @@ __device__ __forceinline__ void accumulate4(float (&acc)[VEC], float (&mx)[VEC],
             acc[v] = fmaf(acc[v], term_exp(mx[v] - m), (term_exp(x0 - m) + term_exp(x1 - m)) + (term_exp(x2 - m) + term_exp(x3 - m)));
             mx[v] = hi;
         } else {
-            float scale = 0.0f;
-            if (OpTraits<OP>::shares) {
-                // (anew for every four entries: kept over the row it would cost a wave of occupancy at four columns per lane)
-                float n = nc[v];
-                asm volatile("" : "+v"(n));
-                scale = share_scale(n);
-            }
 #pragma unroll
             for (int i = 0; i < 4; ++i) {
                 const float xv = i < live ? x[i][v] : dead_value<OP>();
-                const float yv = OP == OP_SOFTMAX_BWD ? (i < live ? y[i][v] : -INFINITY) : scale;
+                const float yv = OP == OP_SOFTMAX_BWD ? (i < live ? y[i][v] : -INFINITY) : 1.0f;
                 accumulate<OP>(acc[v], mx[v], xv, yv, nc[v], OpTraits<OP>::shares ? i >= live || (e[i] & kWeighted) != 0 : i < live && (e[i] & kWeighted) != 0);
             }
         }
@@ -737,7 +730,26 @@ __device__ __forceinline__ void pass_body(int bx, int nbx, const PassArgs& a) {
     }
     float o[VEC];
 #pragma unroll
-    for (int v = 0; v < VEC; ++v) o[v] = OP == OP_LSE ? mx[v] + flog(acc[v]) : finish<OP>(acc[v], mx[v], nc[v], share_scale(nc[v]));
+    for (int v = 0; v < VEC; ++v) o[v] = OP == OP_LSE ? mx[v] + flog(acc[v]) : finish<OP>(acc[v], mx[v], nc[v]);
+    if (OpTraits<OP>::shares) {
+        // a sum of P rows out of range: the row once more, as in the streaming kernel
+        float most = fabsf(mx[0]);
+#pragma unroll
+        for (int v = 1; v < VEC; ++v) most = fmaxf(most, fabsf(mx[v]));
+        if (most == INFINITY) {
+#pragma unroll
+            for (int v = 0; v < VEC; ++v) { acc[v] = identity<OP>(); mx[v] = identity2<OP>(); }
+            for (int k = range.x; k < end; ++k) {
+                const uint32_t id = a.idx[k];
+                float x[VEC];
+                load_cols<VEC>(x, a.src + (size_t)(id & kIdMask) * a.ld + col);
+#pragma unroll
+                for (int v = 0; v < VEC; ++v) accumulate<OP>(acc[v], mx[v], x[v], share_scale(nc[v]), nc[v], (id & kWeighted) != 0);
+            }
+#pragma unroll
+            for (int v = 0; v < VEC; ++v) o[v] = finish<OP>(acc[v], mx[v], nc[v], share_scale(nc[v]));
+        }
+    }
     if (OP == OP_SUM_H && row < a.n_main && (last & kRowFlag)) {
 #pragma unroll
         for (int v = 0; v < VEC; ++v) o[v] = encode_h(o[v], nc[v]);
