@@ -1523,7 +1523,7 @@ klay_status forward64_impl(klay_circuit* c, const double* w, const double* wneg,
     const int ld = B > 64 ? (B + 1) / 2 * 2 : B;       // even rows for two columns per lane
     c->have_fwd64 = false;
     const ColTail& tail = tail64(c);
-    int first = choose64(c, tail, B, semiring == KLAY_REAL, c->bwd64_followed);
+    int first = choose64(c, tail, B, semiring == KLAY_REAL, c->bwd64_followed && semiring != KLAY_MAXLOG);
     Workspace64 lay = workspace_layout64(c, B, ld, first);
     // room for the choices of all passes over this batch at once: a later one, which may be captured, allocates nothing
     size_t room = lay.total;
@@ -1976,7 +1976,7 @@ klay_status klay_persistent_layers(const klay_circuit* c, int32_t B, klay_semiri
     if (semiring != KLAY_REAL && semiring != KLAY_LOG && semiring != KLAY_MAXLOG)
         return fail(KLAY_EINVAL, "klay_persistent_layers: unknown semiring");
     if (double_precision) {
-        *first_layer = choose64(c, tail64(c), B, semiring == KLAY_REAL, training != 0);
+        *first_layer = choose64(c, tail64(c), B, semiring == KLAY_REAL, training != 0 && semiring != KLAY_MAXLOG);
         *plan = *first_layer == 0 ? 0 : &tail64(c) == &c->top ? 2 : 1;
     } else if ((*first_layer = choose_top(c, B, semiring == KLAY_REAL && training != 0)) > 0) {
         *plan = 2;
