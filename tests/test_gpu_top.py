@@ -29,7 +29,8 @@ def test_top_plan_matches_the_oracle(klay, which, cap, B):  # noqa: F811
     k.set_profiling(True)
     gpu_eval(k, as_inputs(p, True), LOG, np.ones((B, c.roots.shape[0]), np.float32))
     prof = k.get_profile()
-    assert prof["tail_fwd"]["launches"] == 1 and prof["tail_bwd"]["launches"] == 1, "the top plan ran"
+    assert prof["tail_fwd"]["launches"] == 1 and prof["tail_bwd"]["launches"] == 1, "a persistent kernel ran"
+    assert k.persistent_layers(B, LOG)[1] == 2, "of the top plan"
     k.close()
     check_both(klay, c, p, semirings=(LOG,), what="top %s cap %d B=%d" % (which, cap, B), tail_rows_cap=cap)
     check_max(klay, c, p, what="top %s max B=%d" % (which, B))
@@ -38,10 +39,14 @@ def test_top_plan_matches_the_oracle(klay, which, cap, B):  # noqa: F811
 @pytest.mark.parametrize("which", ["whole", "part"])
 def test_top_plan_in_the_real_semiring_with_zeros_and_ones(klay, which):  # noqa: F811
     """forward in the plan, reverse sweep by the launches from the values that are put back into rows"""
-    c = layered_random(6, num_vars=30, depth=8, num_gates=1200 if which == "whole" else 26000, fanin=("zipf", 2.2, 120), groups=1, num_roots=7)
+    c = layered_random(6, num_vars=30, depth=8, num_gates=1200 if which == "whole" else 26000, fanin=("zipf", 1.8 if which == "whole" else 2.2, 120),
+                       groups=1, num_roots=7)
     p = leaf_probs(3, 33, c.num_vars, ("uniform", 0.2, 0.8))
     p[:, 3] = 0.0
     p[1::3, 5] = 1.0
+    k = build(klay, c)
+    assert k.persistent_layers(33, REAL)[1] == 2
+    k.close()
     check_both(klay, c, p, semirings=(REAL,), what="top real %s" % which)
 
 
