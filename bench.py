@@ -15,6 +15,7 @@ import argparse
 import ctypes
 import json
 import os
+import re
 import sys
 import time
 
@@ -56,24 +57,25 @@ def load_traffic(workload, batch, semiring, backward, chains):
 
 
 def kernel_symbol(cls, B, edges=False, fused_op=10):
-    """rocprofv3's name for the kernel behind a profiling class (template arguments as it prints them)."""
+    """rocprofv3's name for the kernel behind a profiling class (template arguments as it prints them; * where a launch's size or the
+    circuit decides)."""
     vec = 4 if B > 128 else (2 if B > 64 else 1)
     ops = {"fwd_sum": 0, "bwd_sum": 0, "fwd_prod": 1, "fwd_lse": 2, "bwd_softmax": 3, "fwd_max": 4, "bwd_prod": 5,
            "bwd_sum_enc": 6, "bwd_softmax_one": 7, "bwd_sum_mul": 8, "bwd_prod_mul": 9}
-    if cls in ops:
-        if B > 32:
-            return "klay::stream_kernel<%d, %d>" % (ops[cls], vec)
-        w = 1
-        while w < B:
-            w *= 2
-        return "klay::edge_kernel<%d, %d>" % (ops[cls], w) if edges else "klay::pass_kernel<%d, *>" % ops[cls]
     w_small = 1
     while w_small < B:
         w_small *= 2
-    # (above 256 columns a launch of the persistent kernels has 1, 2 or 4 of them per workgroup, as its layers fit)
+    if cls in ops:
+        if B > 128:
+            return "klay::stream_kernel<%d, %d>" % (ops[cls], vec)
+        if B > 84:                       # the latter where most entries are segments of split rows
+            return "klay::stream_kernel<%d, %d> / klay::pass_kernel<%d, *>" % (ops[cls], vec, ops[cls])
+        return "klay::edge_kernel<%d, %d>" % (ops[cls], w_small) if edges and B <= 32 else "klay::pass_kernel<%d, *>" % ops[cls]
+    # (above 256 columns a launch of the persistent kernels has 1, 2 or 4 of them per workgroup, as its layers fit; the last argument of
+    # the reverse kernel: it leaves every layer's adjoints)
     columns = "1" if B <= 256 else "*"
     fixed = {"tail_fwd": "klay::col_fwd_kernel<%s>" % columns,
-             "tail_bwd": "klay::col_bwd_kernel<%s, %s>" % (columns, "true" if fused_op == 12 else "false"),
+             "tail_bwd": "klay::col_bwd_kernel<%s, %s>" % (columns, "true, false" if fused_op == 12 else "false, *"),
              "leaf": "klay::leaf_fwd_kernel" if B > 32 else "klay::leaf_fwd_small_kernel", "bwd_leaf": "klay::leaf_bwd_kernel", "root": "klay::root_out_kernel",
              "seed": "klay::seed_kernel", "split": "klay::pass_kernel<*> (segments of split rows)",
              "combine": "klay::combine_kernel<*>" if B > 32 else "klay::combine_small_kernel<*>",
@@ -81,6 +83,13 @@ def kernel_symbol(cls, B, edges=False, fused_op=10):
              "fwd_or_fused": "klay::stream_kernel<%d, %d>" % (fused_op, vec),
              "prod_edges": "klay::prod_parent_kernel<%d, %d>" % (vec, 64 if B > 32 else w_small)}
     return fixed.get(cls, cls)
+
+
+def measured_kernel(per_kernel, symbol):
+    """The traffic table's entry for a kernel_symbol name; None unless exactly one kernel of the table goes by it."""
+    pattern = "|".join(re.escape(s).replace(r"\*", r"[^>]*") for s in symbol.split(" / "))
+    found = [v for k, v in per_kernel.items() if re.fullmatch(pattern, k)]
+    return found[0] if len(found) == 1 else None
 
 
 class HipEvents:
@@ -280,8 +289,9 @@ def main():
         measured = load_traffic(args.workload, B, semiring_name, backward, bool(args.unary_chains))
     per_launch_s = d["ms"] * 1e-3 / max(1, d["launches"])
     traffic = None
-    if measured and dom in measured["per_kernel"]:
-        traffic = measured["per_kernel"][dom]["fetch_bytes"] + measured["per_kernel"][dom]["write_bytes"]
+    if measured and measured_kernel(measured["per_kernel"], dom):
+        m = measured_kernel(measured["per_kernel"], dom)
+        traffic = m["fetch_bytes"] + m["write_bytes"]
     no_reuse_GBs = d["alg_bytes"] / max(1, d["launches"]) / per_launch_s / 1e9 if per_launch_s > 0 else 0.0
     compulsory_GBs = d["min_bytes"] / max(1, d["launches"]) / per_launch_s / 1e9 if per_launch_s > 0 else 0.0
     if traffic is not None:
@@ -298,8 +308,8 @@ def main():
         e = {"classes": g["classes"], "ms_per_step": round(g["ms"] / prof_steps, 4), "launches_per_step": g["launches"] // prof_steps,
              "no_reuse_model_GBs": round(g["alg_bytes"] / t / 1e9) if t > 0 else None,
              "compulsory_GBs": round(g["min_bytes"] / t / 1e9) if t > 0 else None, "traffic_GBs": None}
-        if measured and sym in measured["per_kernel"] and t > 0:
-            m = measured["per_kernel"][sym]
+        m = measured_kernel(measured["per_kernel"], sym) if measured else None
+        if m and t > 0:
             e["traffic_GBs"] = round((m["fetch_bytes"] + m["write_bytes"]) * g["launches"] / t / 1e9)
         if e["no_reuse_model_GBs"] and e["no_reuse_model_GBs"] > HBM_PEAK_GBS:
             e["note"] = "the no-reuse model counts L2 hits as memory reads: above the HBM peak, so not a traffic figure"

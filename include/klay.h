@@ -106,8 +106,9 @@ typedef struct klay_info_t {
 
 /* Per-kernel-class timing of the most recent forward / backward call, filled only while
  * profiling is enabled.  Durations come from HIP events recorded on the caller's stream around
- * every single launch.  FWD_x / BWD_x are the main-row launches of a layer (one kernel each:
- * the streaming kernel for B > 64), SPLIT the segment launches of split rows, COMBINE their
+ * every single launch.  FWD_x / BWD_x are the main-row launches of a layer, mostly with the segments of its
+ * split rows (one kernel each: the generic row kernel up to 84 columns and, where most entries are segments, up
+ * to 128, the streaming kernel otherwise), SPLIT segment launches of their own, COMBINE the
  * combine launches, MAIN_COMBINE (any operation) the launches that take the main rows and the combine
  * rows of a layer together (32 < B <= 64, where the segments run in a launch of their own first),
  * FWD_OR_FUSED the forward launches of OR layers that read the children of fused AND rows (klay_options.no_fusion),
@@ -239,7 +240,8 @@ klay_status klay_backward_lits(klay_circuit* c, const float* dout, float* dpos, 
 /*
  * klay_forward_f64 / klay_backward_f64 -- the same evaluation in double precision, for circuits whose
  * log-values outgrow what fp32 resolves and as an on-device accuracy reference for the fp32 kernels.
- * Same launch plans, a plain (untuned) gather-reduce kernel, the full-precision exp / log.
+ * Same launch plans, kernels of their own (a generic gather-reduce kernel, persistent kernels for the narrow
+ * layers: klay_persistent_layers), the full-precision exp / log.
  *   pos_weights, neg_weights, out, dout, dpos, dneg   as for klay_forward_lits / klay_backward_lits,
  *                 in double; neg_weights = NULL derives the negated literals from pos_weights, and
  *                 dneg must then be NULL as well.

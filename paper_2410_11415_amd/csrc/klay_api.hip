@@ -26,8 +26,8 @@ static __device__ __align__(256) unsigned char scratch[kStaticWorkspaceBytes];
 
 // Layers with split rows and at most this many index entries run main rows and segments in one generic
 // launch and the combine rows in another; larger ones the segments first, then main rows and combine rows.
-// (us with main rows and segments together throughout / this rule: the two power-law workloads of run_pass_set 914 / 882, 375 / 384; there
-// the segments are most of the work.)
+// (32 < B <= 64.  us, together throughout / this rule: 1e6 nodes with power-law fan-ins, training step at B = 50 914 / 882; 290000 nodes, 1e7
+// edges, forward at B = 64 375 / 384.  The line looks at a layer's size alone, and is 2% off where the segments are most of a large layer.)
 constexpr int64_t kSmallPassEntries = 100000;
 constexpr size_t kTailLdsMax = 160 * 1024;     // LDS of a gfx950 compute unit: the most a workgroup of the persistent kernels gets
 
@@ -883,7 +883,7 @@ void launch_pass_combine(int op, const klay::PassArgs& a, const klay::PassArgs& 
 // streaming kernel's balanced tasks win, except where most entries are segments, rows of one length.  (The plans of fused rows have no
 // generic kernel.)  Training steps, us, streaming / generic throughout / this rule: 800000 nodes B = 70 623 / 558 / 558, B = 100
 // 654 / 676 / 638, B = 128 705 / 720 / 691, real semiring B = 100 710 / 730 / 666; 1e6 nodes, 1e7 edges of power-law fan-ins B = 100
-// 1519 / 1405 / 1449, B = 128 1561 / 1462 / 1511.
+// 1519 / 1405 / 1449, B = 128 1561 / 1462 / 1511.  (The last two: what gains there by the generic kernel are long rows that are not split, too.)
 bool generic_pair(int op, const DevPass& dp, int B) {
     if (op == klay::OP_LSE2 || op == klay::OP_MAX2 || op == klay::OP_SUMPROD2) return false;
     return B <= 84 || dp.seg_entries > dp.main_entries;
