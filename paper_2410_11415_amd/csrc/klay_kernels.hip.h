@@ -310,7 +310,7 @@ __global__ __launch_bounds__(256) void stream_kernel(const int2* __restrict__ ta
     float acc[VEC], mx[VEC], nc[VEC];
 #pragma unroll
     for (int v = 0; v < VEC; ++v) { acc[v] = identity<OP>(); mx[v] = identity2<OP>(); nc[v] = OP == OP_SUMPROD2 ? 1.0f : 0.0f; }
-    float most = 0.0f;                       // P row ops: the largest sum of P rows
+    bool beyond = false;                     // P row ops: a sum of P rows is not finite
     bool fresh = true;                       // the next edge opens a new output row
     uint32_t ids[CH];
 #pragma unroll
@@ -373,7 +373,7 @@ __global__ __launch_bounds__(256) void stream_kernel(const int2* __restrict__ ta
                 float o[VEC];
 #pragma unroll
                 for (int v = 0; v < VEC; ++v) {
-                    if (OpTraits<OP>::shares) most = fmaxf(most, fabsf(mx[v]));
+                    if (OpTraits<OP>::shares) beyond |= !(fabsf(mx[v]) < INFINITY);
                     o[v] = finish<OP>(acc[v], mx[v], nc[v]);
                     // the adjoint of an OR node with more than one child leaves in the one-gather form
                     if (OP == OP_SUM_H && !seg && (ids[i] & kRowFlag)) o[v] = encode_h(o[v], nc[v]);
@@ -392,8 +392,8 @@ __global__ __launch_bounds__(256) void stream_kernel(const int2* __restrict__ ta
         for (int i = 0; i < CH; ++i) ids[i] = nxt[i];
         j += CH;
     }
-    if (!OpTraits<OP>::shares || !__any(most == INFINITY)) return;
-    // A sum of P rows left the range: the task's rows once more, every P row scaled before it is added.  (Rare; scaling always costs 7 to
+    if (!OpTraits<OP>::shares || !__any(beyond)) return;
+    // A sum of P rows left the range (or is NaN, as one that did and met an infinite row): the task's rows once more, every P row scaled before it is added.  (Rare; scaling always costs 7 to
     // 10% where layers are narrow: 16000 nodes in 40 layers at B = 256, training step 373 us / 401.)
     row = t0.x;
     fresh = true;
@@ -733,10 +733,10 @@ __device__ __forceinline__ void pass_body(int bx, int nbx, const PassArgs& a) {
     for (int v = 0; v < VEC; ++v) o[v] = OP == OP_LSE ? mx[v] + flog(acc[v]) : finish<OP>(acc[v], mx[v], nc[v]);
     if (OpTraits<OP>::shares) {
         // a sum of P rows out of range: the row once more, as in the streaming kernel
-        float most = fabsf(mx[0]);
+        bool beyond = false;
 #pragma unroll
-        for (int v = 1; v < VEC; ++v) most = fmaxf(most, fabsf(mx[v]));
-        if (most == INFINITY) {
+        for (int v = 0; v < VEC; ++v) beyond |= !(fabsf(mx[v]) < INFINITY);
+        if (beyond) {
 #pragma unroll
             for (int v = 0; v < VEC; ++v) { acc[v] = identity<OP>(); mx[v] = identity2<OP>(); }
             for (int k = range.x; k < end; ++k) {

@@ -74,6 +74,30 @@ def test_values_at_the_ends_of_the_range(batch, unary, options):
 
 
 @pytest.mark.parametrize("options", [{"no_tail": True}, {"no_tail": True, "heavy_fan": 6, "min_segment": 5},
+                                     {"no_tail": True, "small_batch_edges": True}])
+@pytest.mark.parametrize("every_column", [False, True])
+@pytest.mark.parametrize("batch", [3, 31, 50, 100, 300])
+def test_an_infinite_adjoint_beside_a_sum_out_of_range(batch, every_column, options):
+    """P rows of 2e38 each over a value of 1e20, and one of -inf: -inf, as the sum of the quotients, not inf - inf"""
+    import paper_2410_11415_amd as klay
+    c, hub = products([4, 20, 40, 200], False)
+    p = np.full((batch, c.num_vars), 2e18, np.float32)
+    p[:, :4] = 1e20
+    dout = np.ones((batch, hub.size), np.float32)
+    down = (np.arange(batch) % 3 > 0) | every_column       # the other columns stay finite
+    for h in range(4):
+        gate = np.flatnonzero(hub == h)[[-1, len(hub[hub == h]) // 2]]
+        dout[np.ix_(down, gate[:1 + h % 2])] = -np.inf
+    k = klay.Circuit(*c.arrays(), device=0, no_merge=True, **options)
+    out, grad = gpu_eval(k, p, klay.KLAY_REAL, dout)
+    k.close()
+    assert (grad[down, :4] == -np.inf).all()
+    n = np.array([4, 20, 40, 200])
+    # (roundings: product, adjoint times value, an ulp, the sum, the quotient)
+    assert (np.abs(grad[~down, :4] / (2e18 * n) - 1.0) < (0.5 * n + 4) * 2.0 ** -23).all()
+
+
+@pytest.mark.parametrize("options", [{"no_tail": True}, {"no_tail": True, "heavy_fan": 6, "min_segment": 5},
                                      {"no_tail": True, "small_batch_edges": True}, {}])
 @pytest.mark.parametrize("batch", [7, 32, 33, 66, 131, 257])
 def test_each_number_of_zero_children_beside_plain_entries(batch, options):
