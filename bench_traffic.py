@@ -45,6 +45,7 @@ RUNS = collections.OrderedDict([
     ("layered_1m_b1", ["--workload", "layered_1m", "--batch", "1"]),
     ("powerlaw_10m", ["--workload", "powerlaw_10m"]),
     ("powerlaw_1m_nodes", ["--workload", "powerlaw_1m_nodes"]),
+    ("powerlaw_1m_nodes_fwd_bwd", ["--workload", "powerlaw_1m_nodes", "--batch", "50", "--backward", "on"]),
     ("layered_100k", ["--workload", "layered_100k"]),
     ("tiny_ddnnf", ["--workload", "tiny_ddnnf"]),
 ])
