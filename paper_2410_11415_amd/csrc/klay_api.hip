@@ -65,6 +65,9 @@ klay_status fail(klay_status s, const std::string& msg) {
             return fail(KLAY_EHIP, std::string(#call) + ": " + hipGetErrorString(e__));        \
     } while (0)
 
+// Roots that one wave of the persistent forward kernel reads at the end; more are read by all, which then stay until then.
+constexpr int32_t kRootsOneWave = 256;
+
 constexpr size_t kAlignInts = 64;   // 256-byte alignment of every uploaded array
 
 struct DevPass {
@@ -107,6 +110,9 @@ struct ColTail {
     const klay::Line* blocks[2] = {nullptr, nullptr};
     int32_t n_blocks[2] = {0, 0};
     const klay::Desc* tables = nullptr;
+    const klay::Line* units[2] = {nullptr, nullptr};
+    int32_t n_units[2] = {0, 0};
+    int32_t narrow[2] = {0, 0};          // forward: the layers from this one on are narrow (L + 1: none); reverse: the steps from the layers down to this one
     const int32_t *root_pos = nullptr, *top_ptr = nullptr, *top_root = nullptr;
     std::vector<int32_t> launches;       // what the layers take otherwise
     std::vector<int64_t> share;          // ColPlan::share of the forward streams
@@ -165,7 +171,6 @@ struct klay_circuit {
                   *d_top_root = nullptr;
     int32_t true_row = -1, false_row = -1;
     ColTail tail, top;                         // what the persistent kernels may run: layers of the plan, and of its TopPlan
-    const int32_t* d_leaf_code = nullptr;      // layer 0: literal / constant code of every row
     size_t tail_lds_bytes = 0;                 // LDS a workgroup of the persistent kernels may use (0: kernels unusable)
     int64_t tail_rows = 0;                     // T: rows of all tail candidate layers (one column of the tail buffer)
     int32_t last_tail_first = 0;               // first layer the last forward ran in the persistent kernel (0: none)
@@ -620,11 +625,11 @@ klay_status upload(klay_circuit* c) {
     const int L = p.num_layers;
     // Streams of the persistent kernels: per wave and direction the lines and descriptors of all candidate layers
     // back to back, in the order the sweep visits them.
-    struct TailOffsets { size_t layers = 0, blocks[2] = {0, 0}, tables = 0; };
+    struct TailOffsets { size_t layers = 0, blocks[2] = {0, 0}, units[2] = {0, 0}, tables = 0; };
     auto pack_tail = [&](ColTail& t, auto plan_of) {
         TailOffsets o;
         std::vector<klay::ColLayer> starts((size_t)(L - t.first + 1));
-        std::vector<uint32_t> blocks[2], tables;
+        std::vector<uint32_t> blocks[2], units[2], tables;
         for (int l = t.first; l <= L; ++l) {
             starts[(size_t)(l - t.first)].n = (int32_t)t.kept[(size_t)l];
             starts[(size_t)(l - t.first)].at = (int32_t)t.at[(size_t)l];
@@ -644,12 +649,43 @@ klay_status upload(klay_circuit* c) {
                     tables.insert(tables.end(), cp.tables.begin() + (size_t)cp.table_at[w] * kTableWords,
                                   cp.tables.begin() + (size_t)cp.table_at[w + 1] * kTableWords);
                 }
+            // the narrow layers at the top, as units: dealt to the waves in turn, an empty one for a wave that has none
+            const int step_waves = !backward ? klay::kColFwdWaves : &t == &c->top ? klay::kTopBwdWaves : klay::kColBwdWaves;
+            int32_t& narrow = t.narrow[backward];
+            for (narrow = L + 1; narrow > t.first && !plan_of(narrow - 1, backward).units.empty(); --narrow) {}
+            std::vector<uint32_t>& us = units[backward];
+            for (int w = 0; w < klay::kColWaves; ++w) {
+                auto add = [&](uint32_t bits) {       // an empty unit
+                    for (int i = 0; i < klay::kUnitWords; ++i) us.push_back(i % 4 ? 0u : bits | (uint32_t)klay::kUnitIdleSlot);
+                };
+                auto count = [&](int l) { return (int)(plan_of(l, backward).units.size() / klay::kUnitWords); };
+                int until = L;                        // forward: a wave stops after its last rows
+                if (!backward && w > 0 && p.num_roots <= kRootsOneWave)
+                    while (until >= narrow && count(until) <= w) --until;
+                for (int step = 0; step <= L - narrow; ++step) {
+                    const int l = backward ? L - step : narrow + step;
+                    klay::ColLayer& at = starts[(size_t)(l - t.first)];
+                    (backward ? at.bwd_unit : at.fwd_unit)[w] = (int32_t)(us.size() / klay::kUnitWords);
+                    if (l > until) continue;          // (the unit that ends it)
+                    const uint32_t kind = (l & 1) == 0 ? klay::kUnitOr : 0u;
+                    if (w >= step_waves || w >= count(l)) add(klay::kUnitNew | klay::kUnitIdle | kind);
+                    else
+                        for (int u = w; u < count(l); u += step_waves) {
+                            const uint32_t* from = plan_of(l, backward).units.data() + (size_t)u * klay::kUnitWords;
+                            us.insert(us.end(), from, from + klay::kUnitWords);
+                            for (int i = 0; i < klay::kUnitWords; i += 4) us[us.size() - (size_t)klay::kUnitWords + (size_t)i] |= kind | (u == w ? klay::kUnitNew : 0u);
+                        }
+                }
+                add(klay::kUnitEnd);
+            }
+            t.n_units[backward] = (int32_t)(us.size() / klay::kUnitWords);
+            us.resize(us.size() + (size_t)klay::kUnitsAhead * klay::kUnitWords, 0u);      // read ahead
             t.n_blocks[backward] = (int32_t)(out.size() / klay::kBlockWords);
             out.resize(out.size() + klay::kBlockWords, 0u);      // the waves read one block and one table ahead
         }
         tables.resize(tables.size() + kTableWords, 0u);
         static_assert(sizeof(klay::ColLayer) % sizeof(int32_t) == 0, "must pack into ints");
-        for (int i = 0; i < 2; ++i) o.blocks[i] = pk.add(blocks[i]);
+        for (int i = 0; i < 2; ++i) { o.blocks[i] = pk.add(blocks[i]); o.units[i] = pk.add(units[i]); }
         o.tables = pk.add(tables);
         o.layers = pk.add(reinterpret_cast<const int32_t*>(starts.data()), starts.size() * sizeof(klay::ColLayer) / sizeof(int32_t));
         return o;
@@ -672,7 +708,6 @@ klay_status upload(klay_circuit* c) {
         o_top_top_root = pk.add(top.top_root);
         o_top_multi = pk.add(top.multi);
     }
-    const size_t o_leaf_code = pk.add(p.leaf_code);
     std::vector<PassOffsets> fo((size_t)L + 1), bo((size_t)L + 1), fko((size_t)L + 1), f2o((size_t)L + 1);
     for (int l = 1; l <= L; ++l) {
         fo[(size_t)l] = pack_pass(pk, p.layers[(size_t)l].fwd);
@@ -730,7 +765,10 @@ klay_status upload(klay_circuit* c) {
     c->d_top_root = base + o_troot;
     auto bind_tail = [&](ColTail& t, const TailOffsets& o) {
         t.layers = reinterpret_cast<const klay::ColLayer*>(base + o.layers);
-        for (int i = 0; i < 2; ++i) t.blocks[i] = reinterpret_cast<const klay::Line*>(base + o.blocks[i]);
+        for (int i = 0; i < 2; ++i) {
+            t.blocks[i] = reinterpret_cast<const klay::Line*>(base + o.blocks[i]);
+            t.units[i] = reinterpret_cast<const klay::Line*>(base + o.units[i]);
+        }
         t.tables = reinterpret_cast<const klay::Desc*>(base + o.tables);
     };
     if (c->tail.first > 0) {
@@ -748,7 +786,6 @@ klay_status upload(klay_circuit* c) {
         c->top.top_root = base + o_top_top_root;
         if ((L & 1) == 0) c->top.multi = reinterpret_cast<const uint32_t*>(base + o_top_multi);
     }
-    c->d_leaf_code = base + o_leaf_code;
     return KLAY_OK;
 }
 
@@ -1125,8 +1162,10 @@ void launch_col_fwd(const klay_circuit* c, const ColTail& t, int first, const fl
     int64_t size[2];
     tail_lds(t.n, first - 1, first - 1, size);
     const int ct = tail_columns(B, size, c->tail_lds_bytes, false);
+    const int n_layers = c->plan.num_layers - first + 1, wide = std::min(n_layers, std::max(0, t.narrow[0] - first));
     hipLaunchKernelGGL((ct == 4 ? klay::col_fwd_kernel<4> : ct == 2 ? klay::col_fwd_kernel<2> : klay::col_fwd_kernel<1>), dim3((unsigned)((B + ct - 1) / ct)), dim3(klay::kColThreads),
-                       (size_t)(size[0] + size[1]) * ct * sizeof(float), s, t.layers + (first - t.first), c->plan.num_layers - first + 1, first & 1, t.blocks[0], t.n_blocks[0], t.tables, start,
+                       (size_t)(size[0] + size[1]) * ct * sizeof(float), s, t.layers + (first - t.first), n_layers, first & 1, t.blocks[0], t.n_blocks[0], t.tables,
+                       t.units[0], t.n_units[0], wide, (int)(wide < n_layers && c->plan.num_roots <= kRootsOneWave), start,
                        (int)t.n[(size_t)first - 1], start_T, start_map, B, ld, semiring, (int)size[0], tb, T, leaf, t.root_pos, c->plan.num_roots, out);
 }
 
@@ -1197,11 +1236,12 @@ void launch_tail_bwd(const klay_circuit* c, const ColTail& tail, int last, int l
         }
         cached = L - l + 1;
     }
+    const int narrow = std::max(0, std::min({L - tail.narrow[1] + 1, cached - 1, 64}));
     auto* kernel = real ? (ct == 4 ? klay::col_bwd_kernel<4, true, false> : ct == 2 ? klay::col_bwd_kernel<2, true, false> : klay::col_bwd_kernel<1, true, false>)
                    : res.keep ? (ct == 4 ? klay::col_bwd_kernel<4, false, true> : ct == 2 ? klay::col_bwd_kernel<2, false, true> : klay::col_bwd_kernel<1, false, true>)
                               : (ct == 4 ? klay::col_bwd_kernel<4, false, false> : ct == 2 ? klay::col_bwd_kernel<2, false, false> : klay::col_bwd_kernel<1, false, false>);
     hipLaunchKernelGGL(kernel, dim3((unsigned)((B + ct - 1) / ct)), dim3(klay::kColThreads),
-                       (size_t)words * ct * sizeof(float), s, tail.layers + (L - tail.first), L - last, last_at, L & 1, tail.blocks[1], tail.n_blocks[1], tail.tables, dout, tail.top_ptr,
+                       (size_t)words * ct * sizeof(float), s, tail.layers + (L - tail.first), L - last, last_at, L & 1, tail.blocks[1], tail.n_blocks[1], tail.tables, tail.units[1], narrow, dout, tail.top_ptr,
                        tail.top_root, p.num_roots, B, ld, (int)size[0], cached, cache_at, tb, T, top_multi, res, real ? *real : klay::ColReal{});
 }
 
@@ -2114,11 +2154,13 @@ static klay_status forward_impl(klay_circuit* c, const float* leaf_weights, cons
         if (fused_leaf) {
             leaf.w = leaf_weights;
             leaf.wneg = neg_weights;
-            leaf.leaf_code = c->d_leaf_code;
+            leaf.pos_row = c->d_pos_row;
+            leaf.neg_row = c->d_neg_row;
+            leaf.true_row = c->true_row;
+            leaf.false_row = c->false_row;
             leaf.wT = wT;
             leaf.act0 = act;
             leaf.V = V;
-            leaf.n0 = (int32_t)p.layers[0].n;
         }
         const ColTail& which = top_first > 0 ? c->top : c->tail;
         const int first = top_first > 0 ? top_first : tail.first;

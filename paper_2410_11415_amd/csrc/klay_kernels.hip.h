@@ -944,7 +944,7 @@ __global__ __launch_bounds__(256) void combine_small_kernel(PassArgs a) {
 //   Measured against one lane per row, chunks dealt in turn and a running logsumexp (forward / forward + backward, log
 // semiring): 85000 nodes, 263000 edges, 20 layers at B = 128: 52 -> 42 us / 211 -> 100 us (there the reverse kernel
 // could not take layers with nodes of more than 64 parents); 467 nodes, 22 layers at B = 4: 19.5 -> 16.6 us.  A
-// narrow layer costs about 2000 cycles of dependent steps, a wide one 5 ns per 64 entries.
+// wide layer costs about 5 ns per 64 entries, a narrow one cost 2000 cycles of dependent steps and costs 700 as units (ColUnits).
 //   A lane owns rows of few batch columns, so writing values into the row-major activation buffer
 // would cost one cache line per lane.  The values go to a column-major buffer tb[column][T] instead
 // (T = rows of all candidate layers), where consecutive lanes write consecutive floats; the reverse
@@ -958,6 +958,7 @@ struct ColLayer {
     int32_t n, at;
     int32_t fwd_block[kColWaves], fwd_table[kColWaves];
     int32_t bwd_block[kColWaves], bwd_table[kColWaves];
+    int32_t fwd_unit[kColWaves], bwd_unit[kColWaves];        // narrow layers: the waves' first units
 };
 
 typedef uint32_t Line __attribute__((ext_vector_type(4)));       // a lane's 16 bytes of a line
@@ -1132,20 +1133,38 @@ __device__ __forceinline__ V col_four(V x0, V x1, V x2, V x3) {
     return hi + flog((term_exp(x0 - m) + term_exp(x1 - m)) + (term_exp(x2 - m) + term_exp(x3 - m)));
 }
 
-// Reads one word of every 128 bytes of the blocks, shared out among the workgroups of an XCD (every eighth one), so that
+// Reads one word of every 128 bytes of the blocks and units, shared out among the workgroups of an XCD (every eighth one), so that
 // they are in its L2 when the waves get to them: the workgroups walk the layers in step, and without this the first
 // one to reach a block would wait for the memory behind the L2, a few thousand cycles, at every layer (1m nodes at B = 256:
-// 413 -> 390 us; a few workgroups alone read more than they save, so only from 64 on).
-__device__ __forceinline__ void col_touch(const Line* blocks, int n_blocks) {
-    const uint32_t* words = reinterpret_cast<const uint32_t*>(blocks);
-    const int n = n_blocks * 16, share = ((int)gridDim.x + 7) / 8 * kColThreads;
-    for (int i = ((int)blockIdx.x / 8) * kColThreads + (int)threadIdx.x; i < n; i += 4 * share) {
-        uint32_t x[4];
-#pragma unroll
-        for (int j = 0; j < 4; ++j) x[j] = words[(size_t)(i + j * share < n ? i + j * share : i) * 32];
-        asm volatile("" ::"v"(x[0] | x[1] | x[2] | x[3]));
+// 413 -> 390 us; a few workgroups alone read more than they save, so only from 64 on).  In the forward kernel by the wave that has nothing else to
+// do in the first layer; the others wait for it only where they wait anyway (kernel alone, with 16-byte loads of the layer below the first one, us:
+// 85000 nodes B = 128 37.8 -> 36.8, 800000 nodes B = 1 37.2 -> 33.5).
+template <int N> struct ColTouch {
+    const uint32_t* words;
+    int n, at, step;
+    uint32_t x[N];
+    // `thread` of the `threads` of this workgroup that take part
+    __device__ __forceinline__ void ask(const Line* lines, int n_kb, int thread, int threads) {
+        words = reinterpret_cast<const uint32_t*>(lines);
+        n = n_kb * 8;
+        step = ((int)gridDim.x + 7) / 8 * threads;
+        at = (int)blockIdx.x / 8 * threads + thread;
+        more();
     }
-}
+    __device__ __forceinline__ void more() {
+#pragma unroll
+        for (int j = 0; j < N; ++j) x[j] = words[(size_t)(at + j * step < n ? at + j * step : 0) * 32];
+        at += N * step;
+    }
+    __device__ __forceinline__ void finish() {
+        for (;;) {
+#pragma unroll
+            for (int j = 0; j < N; ++j) asm volatile("" ::"v"(x[j]));
+            if (!__any(at < n)) return;
+            more();
+        }
+    }
+};
 
 // The values of the rows that two words (four entries) of a lane stand for: four rows of one entry, two of two, one of four.
 template <int OP, int KIND, class V>
@@ -1272,6 +1291,106 @@ __device__ __forceinline__ void col_fwd_layer(ColWalk& walk, const V* below, V* 
     }
 }
 
+// The narrow layers (ColPlan::units).  A run of the walk above costs a wave 600 cycles before its first row (descriptor, branches,
+// a block that was asked for one block ago), more than all the work of a layer of a few hundred rows.  A unit says everything itself and was
+// asked for four units ago, so what is left is the barrier, the gathers and the sum.  Kernel alone, us, runs throughout / units up to
+// 30 / 60 / 90 of them in a layer: 467 nodes in 22 layers at B = 4 16.3 / 9.7 / 9.7 / 9.7; 85000 nodes in 20 layers at B = 128 41.1 / 36.8 / 35.2 /
+// 35.1; 800000 nodes, 26 of 40 layers in the kernel, B = 1 42.8 / 33.5 / 31.3 / 32.4, B = 256 53.8 / 45.9 / 44.7 / 44.3; the reverse kernel there at
+// B = 10 65.9 / - / 59.2.
+struct ColUnits {
+    const Line* q;
+    Line r[kUnitsAhead];
+    __device__ __forceinline__ void start(const Line* units) {
+        q = units;
+#pragma unroll
+        for (int i = 0; i < kUnitsAhead; ++i) r[i] = q[64 * i];
+        q += 64 * kUnitsAhead;
+    }
+    // r[i] has been worked off
+    __device__ __forceinline__ void next(int i) {
+        r[i] = *q;
+        q += 64;
+    }
+};
+
+// reduce over the 2^lanes lanes of a row, k the most of the unit
+template <int OP, class V>
+__device__ __forceinline__ V unit_fly(V x, int lanes, int k) {
+    x = lanes >= 1 ? col_join<OP>(x, fly<0>(x)) : x;
+    x = lanes >= 2 ? col_join<OP>(x, fly<1>(x)) : x;
+    if (k > 2) {
+        x = lanes >= 3 ? col_join<OP>(x, fly<2>(x)) : x;
+        x = lanes >= 4 ? col_join<OP>(x, fly<3>(x)) : x;
+    }
+    if (k > 4) {
+        x = lanes >= 5 ? col_join<OP>(x, fly<4>(x)) : x;
+        x = lanes >= 6 ? col_join<OP>(x, fly<5>(x)) : x;
+    }
+    return x;
+}
+
+// the value of a lane's row
+template <int OP, class V>
+__device__ __forceinline__ V col_fwd_row(const V* below, Line w, uint32_t head) {
+    const int lanes = (int)(w.x >> kUnitLanesAt) & 7, k = (int)(head >> kUnitLanesAt) & 7;
+    const V x0 = col_at(below, w.y & 0xFFFFu), x1 = col_at(below, w.y >> 16), x2 = col_at(below, w.z & 0xFFFFu);
+    V m = V(-INFINITY), s;
+    if (head & kUnitShort) {
+        if constexpr (OP == OP_LSE || OP == OP_MAX) {
+            m = bigger(max3(x0, x1, x2), m);
+            if (OP == OP_MAX) return m;
+            const V f = finite(m);
+            s = (term_exp(x0 - f) + term_exp(x1 - f)) + term_exp(x2 - f);
+            return m + flog(s);
+        }
+        return col_join<OP>(col_join<OP>(x0, x1), x2);
+    }
+    const V x3 = col_at(below, w.z >> 16), x4 = col_at(below, w.w & 0xFFFFu), x5 = col_at(below, w.w >> 16);
+    if constexpr (OP == OP_LSE || OP == OP_MAX) {
+        m = bigger(max3(max3(x0, x1, x2), x3, max3(x4, x5, m)), m);
+        if (k > 0) m = unit_fly<OP>(m, lanes, k);
+        if (OP == OP_MAX) return m;
+        const V f = finite(m);
+        s = ((term_exp(x0 - f) + term_exp(x1 - f)) + (term_exp(x2 - f) + term_exp(x3 - f))) + (term_exp(x4 - f) + term_exp(x5 - f));
+        if (k > 0) s = unit_fly<OP_SUM>(s, lanes, k);
+        return m + flog(s);
+    }
+    s = col_join<OP>(col_join<OP>(col_join<OP>(x0, x1), col_join<OP>(x2, x3)), col_join<OP>(x4, x5));
+    return k > 0 ? unit_fly<OP>(s, lanes, k) : s;
+}
+
+// one unit; true: the wave has no further rows
+template <int AND, int OR, class V>
+__device__ __forceinline__ bool col_fwd_unit(Line w, V*& below, V*& here) {
+    const uint32_t head = (uint32_t)__builtin_amdgcn_readfirstlane((int)w.x);
+    if (head & kUnitEnd) return true;
+    if (head & kUnitNew) {
+        __syncthreads();
+        V* tmp = below; below = here; here = tmp;
+    }
+    if (head & kUnitIdle) return false;
+    V* out = here + (w.x & kUnitSlot);
+    if (head & kUnitOr) *out = col_fwd_row<OR>(below, w, head);
+    else *out = col_fwd_row<AND>(below, w, head);
+    return false;
+}
+
+// the wave's units of the narrow layers; `below` ends as the last one's values
+template <int AND, int OR, class V>
+__device__ __forceinline__ void col_fwd_units(const Line* units, V*& below, V*& here) {
+    ColUnits walk;
+    walk.start(units);
+    V* tmp = below; below = here; here = tmp;            // (as after a layer)
+    for (bool done = false; !done;) {
+#pragma unroll
+        for (int i = 0; i < kUnitsAhead; ++i) {
+            if ((done = col_fwd_unit<AND, OR>(walk.r[i], below, here))) break;
+            walk.next(i);
+        }
+    }
+    below = here;
+}
+
 // a finished layer's values from LDS to the column-major buffer, by one wave, 16 bytes a lane
 __device__ __forceinline__ void col_move(const float* values, int n, float* __restrict__ to) {
     typedef float f4u __attribute__((ext_vector_type(4), aligned(4)));
@@ -1315,24 +1434,69 @@ __device__ __forceinline__ float log1mexp_f(float x) {
     return x > -0.69314718f ? logf(-expm1f(x)) : log1pf(-expf(x));
 }
 
+// Where the values of the CT columns of a workgroup are in the column-major buffer: T floats apart, `columns` of them there (one
+// that is not: the last one again).
+struct ColColumns {
+    int T, columns;
+    __device__ __forceinline__ int operator()(int c) const { return (c < columns ? c : columns - 1) * T; }
+};
+
+// four rows of the columns to their slots
+typedef float Float4u __attribute__((ext_vector_type(4), aligned(4)));
+template <int CT, class V>
+__device__ __forceinline__ void col_put4(V* to, const Float4u (&v)[CT]) {
+    float x[4 * CT];
+#pragma unroll
+    for (int j = 0; j < 4; ++j)
+#pragma unroll
+        for (int c = 0; c < CT; ++c) x[j * CT + c] = v[c][j];
+#pragma unroll
+    for (int i = 0; i < CT; ++i) reinterpret_cast<float4*>(to)[i] = make_float4(x[4 * i], x[4 * i + 1], x[4 * i + 2], x[4 * i + 3]);
+}
+
+// n node values of the columns into LDS, 16-byte aligned, up to twenty values of a column per thread in flight (at one column a layer of
+// kTailRowsCap rows)
+template <int CT, class V>
+__device__ __forceinline__ void col_load(V* to, const float* from, ColColumns column, int n) {
+    constexpr int kFlight = CT == 4 ? 2 : CT == 2 ? 4 : 5;
+    const int whole = n / 4 * 4;
+    for (int i0 = 4 * (int)threadIdx.x; i0 < whole; i0 += 4 * kFlight * kColThreads) {
+        Float4u v[kFlight][CT];
+#pragma unroll
+        for (int j = 0; j < kFlight; ++j) {
+            const int i = i0 + 4 * j * kColThreads < whole ? i0 + 4 * j * kColThreads : i0;
+#pragma unroll
+            for (int c = 0; c < CT; ++c) v[j][c] = *reinterpret_cast<const Float4u*>(from + column(c) + i);
+        }
+#pragma unroll
+        for (int j = 0; j < kFlight; ++j) col_put4<CT>(to + (i0 + 4 * j * kColThreads < whole ? i0 + 4 * j * kColThreads : i0), v[j]);
+    }
+    const int rest = whole + (int)threadIdx.x;
+    if (rest < n)
+        for (int c = 0; c < CT; ++c) reinterpret_cast<float*>(to + rest)[c] = from[column(c) + rest];
+}
+
 // Arguments of the leaf layer when the persistent kernel evaluates it itself (its first layer is
 // layer 1): a workgroup reads its own rows of the leaf-weight arrays, which are contiguous.
 struct SlabLeaf {
     const float* w;             // [B, V] leaf weights (null: the leaf layer was evaluated by leaf_fwd_kernel)
     const float* wneg;          // [B, V] weights of the negated literals, or null
-    const int32_t* leaf_code;   // [n_0] +(v+1), -(v+1), INT32_MAX (true), INT32_MIN (false)
+    const int32_t *pos_row, *neg_row;    // [V] layer-0 row of each literal or -1
     float* wT;                  // [V, ld] transposed leaf weights kept for the reverse sweep
     float* act0;                // [n_0, ld] rows of layer 0 in the activation buffer
-    int32_t V, n0;
+    int32_t V, true_row, false_row;      // rows of the constants or -1
 };
 
 // LDS: two value arrays, slots kColSlots + position; size0 floats for the layer below the first one and every second
 // layer from there, the rest for the others.  start_rows / start_at: the layer below the first one (start_rows of them),
 // column-major, start_T floats a column, if start_T > 0 (and start_map is null), otherwise rows of the activation buffer (start_map[i], or null: one after another).
 // tb (or null): every layer's values are kept there.  CT: columns of a workgroup.
+// wide: so many layers before the narrow ones (n_layers: there are none), whose units end a wave early (leaves != 0) where the first wave alone reads the
+// roots.
 template <int CT>
 __global__ __launch_bounds__(kColThreads) void col_fwd_kernel(const ColLayer* __restrict__ first, int n_layers, int first_is_and,
                                                               const Line* __restrict__ blocks, int n_blocks, const Desc* __restrict__ tables,
+                                                              const Line* __restrict__ units, int n_units, int wide, int leaves,
                                                               const float* __restrict__ start, int start_rows, int start_T, const int32_t* __restrict__ start_map,
                                                               int B, int ld, int semiring, int size0, float* __restrict__ tb, int T,
                                                               SlabLeaf leaf, const int32_t* __restrict__ root_pos, int R,
@@ -1346,8 +1510,9 @@ __global__ __launch_bounds__(kColThreads) void col_fwd_kernel(const ColLayer* __
     const int col0 = (int)blockIdx.x * CT, columns = B - col0 < CT ? B - col0 : CT;      // (a column that is not there repeats the last one)
     const bool log_domain = semiring != 0;
     ColWalk walk;
-    walk.start(blocks + (size_t)first->fwd_block[wave] * 128 + lane, tables + (size_t)first->fwd_table[wave] * kDescTable + lane);
-    if (gridDim.x >= 64) col_touch(blocks, n_blocks);
+    if (wide > 0) walk.start(blocks + (size_t)first->fwd_block[wave] * 128 + lane, tables + (size_t)first->fwd_table[wave] * kDescTable + lane);
+    const int root = leaves ? lane : (int)threadIdx.x, root_step = leaves ? 64 : kColThreads;
+    const int root_at = root < R ? root_pos[root] : 0;               // (asked for early: far away at the end)
     if (threadIdx.x < 2) {
         // identities of the two kinds of layers, in the slots that padding names
         V* a = threadIdx.x == 0 ? below : here;
@@ -1355,68 +1520,71 @@ __global__ __launch_bounds__(kColThreads) void col_fwd_kernel(const ColLayer* __
         a[kColPadOr] = V(log_domain ? -INFINITY : 0.0f);
     }
     if (leaf.w) {
-        // leaf layer into LDS; the transposed weights and the rows of layer 0 also go to global memory
+        // Leaf layer into LDS, by variable (by row the weight would be asked for only when the row's literal has arrived); the transposed weights and the rows of layer 0 also go to global memory
         // for the reverse sweep (every column of [0, ld): the last workgroup zeroes the padding columns)
-        for (int i = threadIdx.x; i < leaf.n0; i += kColThreads) {
-            const int code = leaf.leaf_code[i];
-            float* slot = reinterpret_cast<float*>(below + kColSlots + i);
+        auto put = [&](int row, int c, float x) {
+            reinterpret_cast<float*>(below + kColSlots + row)[c] = x;
+            if (!tb || c >= columns) return;
+            leaf.act0[(size_t)row * ld + col0 + c] = x;
+            if (col0 + c == B - 1)
+                for (int b = B; b < ld; ++b) leaf.act0[(size_t)row * ld + b] = 0.0f;
+        };
+        for (int v = threadIdx.x; v < leaf.V; v += kColThreads) {
+            const int pr = leaf.pos_row[v], nr = leaf.neg_row[v];
+            float x[CT], y[CT];
 #pragma unroll
             for (int c = 0; c < CT; ++c) {
-                const int col = col0 + (c < columns ? c : columns - 1);
-                float v;
-                if (code == INT32_MAX) v = log_domain ? 0.0f : 1.0f;
-                else if (code == INT32_MIN) v = log_domain ? -INFINITY : 0.0f;
-                else {
-                    const int var = (code > 0 ? code : -code) - 1;
-                    const size_t at = (size_t)col * leaf.V + var;
-                    if (code > 0) v = leaf.w[at];
-                    else if (leaf.wneg) v = leaf.wneg[at];
-                    else v = log_domain ? log1mexp_f(leaf.w[at]) : 1.0f - leaf.w[at];
-                }
-                slot[c] = v;
-                if (tb) {
-                    leaf.act0[(size_t)i * ld + col] = v;
-                    if (col == B - 1)
-                        for (int b = B; b < ld; ++b) leaf.act0[(size_t)i * ld + b] = 0.0f;
-                }
+                const size_t at = (size_t)(col0 + (c < columns ? c : columns - 1)) * leaf.V + v;
+                x[c] = leaf.w[at];
+                y[c] = leaf.wneg ? leaf.wneg[at] : 0.0f;
+            }
+#pragma unroll
+            for (int c = 0; c < CT; ++c) {
+                if (pr >= 0) put(pr, c, x[c]);
+                if (nr >= 0) put(nr, c, leaf.wneg ? y[c] : log_domain ? log1mexp_f(x[c]) : 1.0f - x[c]);
+                if (!tb || c >= columns) continue;
+                leaf.wT[(size_t)v * ld + col0 + c] = x[c];
+                if (col0 + c == B - 1)
+                    for (int b = B; b < ld; ++b) leaf.wT[(size_t)v * ld + b] = 0.0f;
             }
         }
-        if (tb)
-            for (int v = threadIdx.x; v < leaf.V; v += kColThreads)
-                for (int c = 0; c < columns; ++c) {
-                    const int col = col0 + c;
-                    leaf.wT[(size_t)v * ld + col] = leaf.w[(size_t)col * leaf.V + v];
-                    if (col == B - 1)
-                        for (int b = B; b < ld; ++b) leaf.wT[(size_t)v * ld + b] = 0.0f;
-                }
-    } else if (start_map) {
+        if (threadIdx.x < CT) {
+            if (leaf.true_row >= 0) put(leaf.true_row, (int)threadIdx.x, log_domain ? 0.0f : 1.0f);
+            if (leaf.false_row >= 0) put(leaf.false_row, (int)threadIdx.x, log_domain ? -INFINITY : 0.0f);
+        }
+    } else if (start_map || start_T == 0) {
+#pragma unroll 4
         for (int i = threadIdx.x; i < start_rows; i += kColThreads) {
             float* slot = reinterpret_cast<float*>(below + kColSlots + i);
-            const size_t row = (size_t)start_map[i] * ld + col0;
+            const size_t row = (size_t)(start_map ? start_map[i] : i) * ld + col0;
 #pragma unroll
             for (int c = 0; c < CT; ++c) slot[c] = start[row + (c < columns ? c : columns - 1)];
         }
     } else {
-        for (int i = threadIdx.x; i < start_rows; i += kColThreads) {
-            float* slot = reinterpret_cast<float*>(below + kColSlots + i);
-#pragma unroll
-            for (int c = 0; c < CT; ++c) {
-                const int col = col0 + (c < columns ? c : columns - 1);
-                slot[c] = start_T > 0 ? start[(size_t)col * start_T + i] : start[(size_t)i * ld + col];
-            }
-        }
+        col_load<CT>(below + kColSlots, start + (size_t)col0 * start_T, ColColumns{start_T, columns}, start_rows);
     }
     float* tbc = tb ? tb + (size_t)col0 * T : nullptr;
     if (wave == kColFwdWaves) {
         // the wave that keeps the values, a layer behind the others (in a wave that computes, the wait for the next
         // lines would wait for the stores as well)
+        const bool touch = gridDim.x >= 64 && wide > 0;
+        ColTouch<8> blocks_ahead;
+        ColTouch<2> units_ahead;
+        if (touch) {
+            blocks_ahead.ask(blocks, 2 * n_blocks, lane, 64);
+            units_ahead.ask(units, n_units, lane, 64);
+        }
         for (int t = 0; t < n_layers; ++t) {
             __syncthreads();
+            if (touch && t == 0) {
+                blocks_ahead.finish();
+                units_ahead.finish();
+            }
             if (tbc && t > 0) col_move<CT>(reinterpret_cast<const float*>(below + kColSlots), first[t - 1].n, tbc + first[t - 1].at, T, columns);
             V* tmp = below; below = here; here = tmp;
         }
     } else {
-        for (int t = 0; t < n_layers; ++t) {
+        for (int t = 0; t < wide; ++t) {
             const bool is_and = ((t & 1) == 0) == (first_is_and != 0);
             __syncthreads();
             if (is_and) {
@@ -1427,12 +1595,24 @@ __global__ __launch_bounds__(kColThreads) void col_fwd_kernel(const ColLayer* __
             else col_fwd_layer<OP_SUM>(walk, below, here);
             V* tmp = below; below = here; here = tmp;
         }
+        if (wide < n_layers) {
+            const Line* own = units + (size_t)first[wide].fwd_unit[wave] * 64 + lane;
+            if (semiring == 1) col_fwd_units<OP_SUM, OP_LSE>(own, below, here);
+            else if (semiring == 2) col_fwd_units<OP_SUM, OP_MAX>(own, below, here);
+            else col_fwd_units<OP_PROD, OP_SUM>(own, below, here);
+            if (leaves && wave > 0) {
+                // (the barriers count the waves that are there; what this one wrote has to be in the LDS before)
+                __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
+                return;
+            }
+        }
     }
     __syncthreads();
     if (wave == kColFwdWaves && tbc) col_move<CT>(reinterpret_cast<const float*>(below + kColSlots), first[n_layers - 1].n, tbc + first[n_layers - 1].at, T, columns);
     // roots: the top layer is in LDS
-    for (int r = threadIdx.x; r < R; r += kColThreads) {
-        const float* slot = reinterpret_cast<const float*>(below + kColSlots + root_pos[r]);
+    if (leaves && wave > 0) return;
+    for (int r = root; r < R; r += root_step) {
+        const float* slot = reinterpret_cast<const float*>(below + kColSlots + (r == root ? root_at : root_pos[r]));
         for (int c = 0; c < columns; ++c) out[(size_t)(col0 + c) * R + r] = slot[c];
     }
 }
@@ -1603,6 +1783,25 @@ __device__ __forceinline__ void col_bwd_layer(ColWalk& walk, const V* above, V* 
     }
 }
 
+// The same for a unit of a narrow layer; own: the values of the rows by slot
+template <int MODE, class V>
+__device__ __forceinline__ void col_bwd_row(const V* above, V* here, const V* owns, Line w, uint32_t head, const ColRepair& repair) {
+    const uint32_t slot = w.x & kUnitSlot;
+    const int lanes = (int)(w.x >> kUnitLanesAt) & 7, k = (int)(head >> kUnitLanesAt) & 7;
+    const V own = owns[slot];
+    ColSum<MODE, V> acc = col_pair<MODE>(above, w.y, own);
+    if (head & kUnitShort) {
+        acc = acc + col_entry<MODE>(above, w.z & 0xFFFFu, own);
+    } else {
+        acc = (acc + col_pair<MODE>(above, w.z, own)) + col_pair<MODE>(above, w.w, own);
+        if (k > 0) {
+            acc.a = unit_fly<OP_SUM>(acc.a, lanes, k);
+            if (MODE == kRealAnd) acc.b = unit_fly<OP_SUM>(acc.b, lanes, k);
+        }
+    }
+    if (slot != kUnitIdleSlot) here[slot] = col_finish<MODE>(acc, own, (w.x & kUnitRow) != 0, repair, (int)slot - kColSlots);
+}
+
 // Where the reverse kernel leaves its last layer's adjoints: the leaf gradients themselves (w_T != null, the last
 // layer is layer 0), or g_cols[B][g_T], column-major (a lane owns rows of one column, so row-major stores would be
 // 4 bytes per cache line; tb_to_rows_kernel transposes afterwards).
@@ -1642,52 +1841,13 @@ struct ColReal {
 // (two and four columns: where no layer is longer)
 template <int CT> constexpr int kColOwn = CT == 1 ? (int)((kTailRowsCap + 4 * kColThreads - 1) / (4 * kColThreads)) : CT == 2 ? 3 : 1;
 
-// Where the values of the CT columns of a workgroup are in the column-major buffer: T floats apart, `columns` of them there (one
-// that is not: the last one again).
-struct ColColumns {
-    int T, columns;
-    __device__ __forceinline__ int operator()(int c) const { return (c < columns ? c : columns - 1) * T; }
-};
-
-// four rows of the columns to their slots
-typedef float Float4u __attribute__((ext_vector_type(4), aligned(4)));
-template <int CT, class V>
-__device__ __forceinline__ void col_put4(V* to, const Float4u (&v)[CT]) {
-    float x[4 * CT];
-#pragma unroll
-    for (int j = 0; j < 4; ++j)
-#pragma unroll
-        for (int c = 0; c < CT; ++c) x[j * CT + c] = v[c][j];
-#pragma unroll
-    for (int i = 0; i < CT; ++i) reinterpret_cast<float4*>(to)[i] = make_float4(x[4 * i], x[4 * i + 1], x[4 * i + 2], x[4 * i + 3]);
-}
-
-// n node values of the columns into LDS, 16-byte aligned, sixteen values of a column per thread in flight
-template <int CT, class V>
-__device__ __forceinline__ void col_load(V* to, const float* from, ColColumns column, int n) {
-    constexpr int kFlight = CT == 4 ? 2 : 4;
-    const int whole = n / 4 * 4;
-    for (int i0 = 4 * (int)threadIdx.x; i0 < whole; i0 += 4 * kFlight * kColThreads) {
-        Float4u v[kFlight][CT];
-#pragma unroll
-        for (int j = 0; j < kFlight; ++j) {
-            const int i = i0 + 4 * j * kColThreads < whole ? i0 + 4 * j * kColThreads : i0;
-#pragma unroll
-            for (int c = 0; c < CT; ++c) v[j][c] = *reinterpret_cast<const Float4u*>(from + column(c) + i);
-        }
-#pragma unroll
-        for (int j = 0; j < kFlight; ++j) col_put4<CT>(to + (i0 + 4 * j * kColThreads < whole ? i0 + 4 * j * kColThreads : i0), v[j]);
-    }
-    const int rest = whole + (int)threadIdx.x;
-    if (rest < n)
-        for (int c = 0; c < CT; ++c) reinterpret_cast<float*>(to + rest)[c] = from[column(c) + rest];
-}
-
+// narrow: so many steps from the top layer down go by units (at most 64, all of them with cached own values).
 // KEEP: ColBwdOut::keep takes the adjoints of every layer, by a wave that does nothing else (see col_fwd_kernel).
 template <int CT, bool REAL, bool KEEP>
 __global__ __launch_bounds__(kColThreads) void col_bwd_kernel(const ColLayer* __restrict__ top, int n_steps, int last_at,
                                                               int top_is_and, const Line* __restrict__ blocks, int n_blocks,
-                                                              const Desc* __restrict__ tables, const float* __restrict__ dout,
+                                                              const Desc* __restrict__ tables, const Line* __restrict__ units, int narrow,
+                                                              const float* __restrict__ dout,
                                                               const int32_t* __restrict__ top_ptr, const int32_t* __restrict__ top_root,
                                                               int R, int B, int ld, int size0, int cached, int cache_at,
                                                               const float* tb, int T,
@@ -1703,8 +1863,11 @@ __global__ __launch_bounds__(kColThreads) void col_bwd_kernel(const ColLayer* __
     const float* tbc = tb + (size_t)col0 * T;
     const ColColumns column{T, columns};
     ColWalk walk;
-    walk.start(blocks + (size_t)top->bwd_block[wave] * 128 + lane, tables + (size_t)top->bwd_table[wave] * kDescTable + lane);
-    if (gridDim.x >= 64) col_touch(blocks, n_blocks);
+    walk.start(blocks + (size_t)top[-narrow].bwd_block[wave] * 128 + lane, tables + (size_t)top[-narrow].bwd_table[wave] * kDescTable + lane);
+    ColUnits walk_units;
+    if (narrow > 0) walk_units.start(units + (size_t)top->bwd_unit[wave] * 64 + lane);
+    ColTouch<2> blocks_ahead;
+    if (gridDim.x >= 64) blocks_ahead.ask(blocks, 2 * n_blocks, (int)threadIdx.x, kColThreads);
     auto value_at = [&](int at) {
         if constexpr (CT == 1) {
             return tbc[at];
@@ -1783,7 +1946,44 @@ __global__ __launch_bounds__(kColThreads) void col_bwd_kernel(const ColLayer* __
         if (!REAL && top_multi && ((top_multi[i >> 5] >> (i & 31)) & 1u)) acc = each([](float a, float b) { return encode_h(a, b); }, acc, value_at(top_at + i));
         above[kColSlots + i] = acc;
     }
+    if (gridDim.x >= 64) blocks_ahead.finish();
     int t = 0;
+    if (narrow > 0) {
+        if (keeper) {
+            for (; t < narrow; ++t) {
+                __syncthreads();
+                keep_layer(t);
+                V* tmp = above; above = here; here = tmp;
+            }
+        } else {
+            // (where the own values of a step are, a lane each: scalar loads would share their wait counter with the gathers)
+            const int ats = top[-1 - (lane < narrow ? lane : 0)].at;
+            const V* owns = cache;
+            t = -1;
+            V* tmp = above; above = here; here = tmp;        // (as after a step)
+            for (bool done = false; !done;) {
+#pragma unroll
+                for (int i = 0; i < kUnitsAhead; ++i) {
+                    const Line w = walk_units.r[i];
+                    const uint32_t head = (uint32_t)__builtin_amdgcn_readfirstlane((int)w.x);
+                    if (head & (kUnitNew | kUnitEnd)) {
+                        if (t + 1 == narrow) { done = true; break; }
+                        ++t;
+                        owns = cache + (__builtin_amdgcn_readlane(ats, t) - cache_low) - kColSlots;
+                        __syncthreads();
+                        tmp = above; above = here; here = tmp;
+                    }
+                    if (!(head & kUnitIdle)) {
+                        if (head & kUnitOr) col_bwd_row<REAL ? kRealOr : kLogOr>(above, here, owns, w, head, REAL ? repair_of(t + 1) : ColRepair{});
+                        else col_bwd_row<REAL ? kRealAnd : kLogAnd>(above, here, owns, w, head, ColRepair{});
+                    }
+                    walk_units.next(i);
+                }
+            }
+            ++t;
+            tmp = above; above = here; here = tmp;
+        }
+    }
     for (; t + 1 < cached; ++t) {
         const V* owns = cache + (top[-1 - t].at - cache_low) - kColSlots;
         __syncthreads();

@@ -455,7 +455,11 @@ __global__ __launch_bounds__(kColThreads) void col_fwd_kernel(const ColLayer* __
     const bool log_domain = semiring != 0;
     ColWalk walk;
     walk.start(blocks + (size_t)first->fwd_block[wave] * 128 + lane, tables + (size_t)first->fwd_table[wave] * kDescTable + lane);
-    if (gridDim.x >= 64) col_touch(blocks, n_blocks);
+    if (gridDim.x >= 64) {
+        ColTouch<4> blocks_ahead;
+        blocks_ahead.ask(blocks, 2 * n_blocks, (int)threadIdx.x, kColThreads);
+        blocks_ahead.finish();
+    }
     if (threadIdx.x < 2) {
         double* a = threadIdx.x == 0 ? below : here;
         a[kColPadAnd] = log_domain ? 0.0 : 1.0;
@@ -606,7 +610,11 @@ __global__ __launch_bounds__(kColThreads) void col_bwd_kernel(const ColLayer* __
     const double* tbc = tb + (size_t)col * T;
     ColWalk walk;
     walk.start(blocks + (size_t)top->bwd_block[wave] * 128 + lane, tables + (size_t)top->bwd_table[wave] * kDescTable + lane);
-    if (gridDim.x >= 64) col_touch(blocks, n_blocks);
+    if (gridDim.x >= 64) {
+        ColTouch<4> blocks_ahead;
+        blocks_ahead.ask(blocks, 2 * n_blocks, (int)threadIdx.x, kColThreads);
+        blocks_ahead.finish();
+    }
     if (threadIdx.x == 0) {
         even[kColPadAnd] = Pair{0.0, 0.0};
         odd[kColPadAnd] = 0.0;

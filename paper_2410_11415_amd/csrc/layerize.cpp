@@ -317,6 +317,45 @@ void make_cols(int64_t n, const int32_t* ptr, const int32_t* idx, const uint32_t
     }
     out.block_at[kColWaves] = (int32_t)(out.blocks.size() / kBlockWords);
     out.table_at[kColWaves] = (int32_t)(out.tables.size() / (kDescTable * kDescWords));
+    make_units(n, ptr, idx, flags, row_bits, pad, kNarrowUnits, out.units);
+}
+
+void make_units(int64_t n, const int32_t* ptr, const int32_t* idx, const uint32_t* flags, const uint32_t* row_bits, int pad, int most,
+                std::vector<uint32_t>& units) {
+    units.clear();
+    // rows by class: 2^k lanes, from the most down to one, then the short ones
+    std::vector<int32_t> by_class[8];
+    int64_t lanes = 0;
+    for (int64_t r = 0; r < n; ++r) {
+        const int64_t fan = ptr[r + 1] - ptr[r];
+        int k = 0;
+        while (((int64_t)kUnitEntries << k) < fan) ++k;
+        lanes += (int64_t)1 << std::min(k, 6);
+        if (k > 6 || lanes > (int64_t)most * 64) return;
+        by_class[fan <= kUnitEntries / 2 ? 7 : 6 - k].push_back((int32_t)r);
+    }
+    units.resize((size_t)((lanes + 63) / 64) * kUnitWords);
+    for (size_t i = 0; i < units.size(); ++i) units[i] = i % 4 ? (uint32_t)pad | (uint32_t)pad << 16 : (uint32_t)kUnitIdleSlot;
+    int64_t at = 0;
+    for (int c = 0; c < 8; ++c)
+        for (int32_t r : by_class[c]) {
+            const int k = c < 7 ? 6 - c : 0;
+            const bool flagged = row_bits && ((row_bits[(size_t)r >> 5] >> (r & 31)) & 1u);
+            for (int64_t sub = 0; sub < (int64_t)1 << k; ++sub) {
+                uint32_t* lane = units.data() + (size_t)(at + sub) * 4;
+                lane[0] = (uint32_t)(kColSlots + r) | (uint32_t)k << kUnitLanesAt | (flagged ? kUnitRow : 0u);
+                for (int64_t i = 0; i < kUnitEntries; ++i) {
+                    const int64_t j = ptr[r] + sub + (i << k);
+                    if (j >= ptr[r + 1]) break;
+                    const uint32_t entry = (uint32_t)(kColSlots + idx[j]) | (flags && (flags[j] & kWeightedEdge) ? 0x8000u : 0u);
+                    uint32_t& word = lane[1 + i / 2];
+                    word = i & 1 ? (word & 0xFFFFu) | entry << 16 : (word & 0xFFFF0000u) | entry;
+                }
+            }
+            // (classes in falling order keep a row's lanes together and aligned)
+            if (c == 7 && at % 64 == 0) units[(size_t)at * 4] |= kUnitShort;
+            at += (int64_t)1 << k;
+        }
 }
 
 int layerize(int32_t V, int64_t N, const uint8_t* node_type, const int32_t* node_lit,

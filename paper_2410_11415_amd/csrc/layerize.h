@@ -62,11 +62,24 @@ constexpr int kColFwdWaves = kColWaves - 1, kColBwdWaves = kColWaves, kTopBwdWav
 constexpr int kBlockWords = 512, kLineWords = 256, kDescWords = 2, kDescTable = 64;
 constexpr int64_t kColBlocksMax = (1 << 17) - 1;             // blocks of a unit: what the descriptor holds
 constexpr int64_t kColRowEntries = kColBlocksMax * 16 * 64;  // a row that takes a whole wave
+//   A narrow layer (at most kNarrowUnits units) has a second form, for which the waves need no tables and whose next pieces
+// they fetch four ahead: units of 64 lanes x 16 bytes.  A lane's first word: LDS slot of its row (kUnitIdleSlot: none), log2 of the
+// lanes that its row takes (kUnitLanes, up to 64), kUnitRow if the row is flagged (see above); the others are kUnitEntries entries, dealt
+// to the lanes of a row in turn.  Rows of several lanes come first, then those of more than three entries, then the others; a unit
+// without rows of more than three entries a lane says so in its first lane (kUnitShort), whose row takes as many lanes as any
+// of the unit.  What the streams add, in every lane: kUnitNew (the first unit of a layer), kUnitOr (of an OR layer), kUnitIdle (no
+// rows), kUnitEnd (the wave has no further rows).
 struct ColPlan {
     int32_t block_at[kColWaves + 1] = {}, table_at[kColWaves + 1] = {};   // first block / table of each wave
     std::vector<uint32_t> blocks, tables;
     int64_t share = 0;               // bound on the cost of a wave's share (cycles)
+    std::vector<uint32_t> units;     // empty: the layer is none of the narrow ones
 };
+constexpr int kUnitEntries = 6, kUnitWords = 256, kUnitIdleSlot = 2, kUnitsAhead = 4;
+constexpr uint32_t kUnitSlot = 0x7FFFu, kUnitRow = 1u << 18, kUnitShort = 1u << 19, kUnitNew = 1u << 20, kUnitOr = 1u << 21, kUnitIdle = 1u << 22,
+                   kUnitEnd = 1u << 23;
+constexpr int kUnitLanesAt = 15;     // three bits
+constexpr int kNarrowUnits = 60;     // (30, 60 and 90 measured, see ColUnits)
 
 // One gather-reduce pass set over a CSR whose rows are the outputs.
 //   rows [0, n_main)                 write output row i; a split row holds the single entry kSkip
@@ -207,8 +220,12 @@ void make_pass_plan(int64_t n, const int32_t* ptr, const int32_t* idx, const Opt
 
 // Runs (see ColPlan) of a CSR of n rows for `waves` waves.  pad: slot that padding names; step: whose costs to
 // cut by.  flags and row_bits as for make_pass_plan.
+// The units of a narrow layer are part of it.
 enum ColStep { kColFwdAnd, kColFwdOr, kColBwdAnd, kColBwdOr };
 void make_cols(int64_t n, const int32_t* ptr, const int32_t* idx, const uint32_t* flags, const uint32_t* row_bits,
                int waves, int pad, ColStep step, ColPlan& out);
+// The units of a layer (see ColPlan), none if they are more than `most`.
+void make_units(int64_t n, const int32_t* ptr, const int32_t* idx, const uint32_t* flags, const uint32_t* row_bits, int pad, int most,
+                std::vector<uint32_t>& units);
 
 }  // namespace klay
