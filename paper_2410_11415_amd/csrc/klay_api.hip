@@ -74,6 +74,8 @@ struct DevPass {
     const int32_t *ptr = nullptr, *seg_owner = nullptr, *comb_ptr = nullptr, *comb_row = nullptr, *tasks = nullptr,
                   *seg_tasks = nullptr;
     const uint32_t *idx = nullptr, *comb_idx = nullptr;
+    const int32_t *out_row = nullptr, *entry_row = nullptr;      // of a plan without left-out rows (compact_pass)
+    int32_t n_light = 0;                         // main rows that are evaluated as such
     int32_t n_main = 0, n_seg = 0, n_heavy = 0, n_tasks = 0, n_seg_tasks = 0;
     int32_t longest_comb = 0;                    // partial rows of the split row with most of them
     int32_t n_comb_many = 0;                     // see PassPlan
@@ -395,10 +397,13 @@ void launch_stream_op(const DevPass& dp, const Geometry& g, const float* src,
     // outputs larger than the L2s together (8 x 4 MB) are written with streaming stores
     const int nt = (int64_t)dp.n_main * g.ld * 4 > (int64_t)64 << 20 ? 1 : 0;
     dim3 grid((unsigned)blocks, (unsigned)g.tiles);
-    if (g.vec == 4)
-        hipLaunchKernelGGL((klay::stream_kernel<OP, 4>), grid, dim3(256), 0, s, tasks, n_tasks, dp.idx, src, src2, own, dst, B, g.ld, nt, seg_tasks, n_seg_tasks, dst_seg, dp.seg_owner, dp.n_main, zf);
-    else
-        hipLaunchKernelGGL((klay::stream_kernel<OP, 2>), grid, dim3(256), 0, s, tasks, n_tasks, dp.idx, src, src2, own, dst, B, g.ld, nt, seg_tasks, n_seg_tasks, dst_seg, dp.seg_owner, dp.n_main, zf);
+    auto launch = [&](auto kernel) {
+        hipLaunchKernelGGL(kernel, grid, dim3(256), 0, s, tasks, n_tasks, dp.idx, dp.entry_row, src, src2, own, dst, B, g.ld, nt, seg_tasks, n_seg_tasks, dst_seg, dp.seg_owner, dp.n_main, zf);
+    };
+    if constexpr (OP == klay::OP_SUM || OP == klay::OP_PROD) {
+        if (dp.entry_row) return g.vec == 4 ? launch(klay::stream_kernel<OP, 4, true>) : launch(klay::stream_kernel<OP, 2, true>);
+    }
+    g.vec == 4 ? launch(klay::stream_kernel<OP, 4, false>) : launch(klay::stream_kernel<OP, 2, false>);
 }
 
 void launch_stream(int op, const DevPass& dp, const Geometry& g, const float* src,
@@ -543,7 +548,7 @@ PassOffsets pack_pass(Packer& pk, const klay::PassPlan& p) {
     return o;
 }
 
-void bind_pass(DevPass& d, const klay::PassPlan& p, const PassOffsets& o, const int32_t* base) {
+void bind_pass(DevPass& d, const klay::PassPlan& p, const PassOffsets& o, const int32_t* base, bool compact = false) {
     d.ptr = base + o.ptr;
     d.idx = reinterpret_cast<const uint32_t*>(base + o.idx);
     d.seg_owner = base + o.seg_owner;
@@ -555,7 +560,12 @@ void bind_pass(DevPass& d, const klay::PassPlan& p, const PassOffsets& o, const 
     d.seg_tasks = base + o.seg_tasks;
     d.n_seg_tasks = p.n_seg_tasks;
     d.has_weighted = p.has_weighted;
-    d.main_entries = (int64_t)p.ptr[(size_t)p.n_main] - p.n_heavy;
+    d.n_light = p.n_main;
+    d.main_entries = p.ptr[(size_t)p.n_main];
+    if (!compact) {              // (a split row is one entry)
+        d.n_light -= p.n_heavy;
+        d.main_entries -= p.n_heavy;
+    }
     d.seg_entries = (int64_t)p.ptr[(size_t)p.n_main + (size_t)p.n_seg] - p.ptr[(size_t)p.n_main];
     d.n_main = p.n_main;
     d.n_seg = p.n_seg;
@@ -708,11 +718,20 @@ klay_status upload(klay_circuit* c) {
         o_top_top_root = pk.add(top.top_root);
         o_top_multi = pk.add(top.multi);
     }
+    struct Compact { klay::PassPlan plan; size_t out_row = 0, entry_row = 0; };
+    std::vector<Compact> kept((size_t)L + 1);           // the AND layers' plans without the fused rows
     std::vector<PassOffsets> fo((size_t)L + 1), bo((size_t)L + 1), fko((size_t)L + 1), f2o((size_t)L + 1);
     for (int l = 1; l <= L; ++l) {
         fo[(size_t)l] = pack_pass(pk, p.layers[(size_t)l].fwd);
         bo[(size_t)l] = pack_pass(pk, p.layers[(size_t)l].bwd);
-        if (!p.layers[(size_t)l].fwd_kept.ptr.empty()) fko[(size_t)l] = pack_pass(pk, p.layers[(size_t)l].fwd_kept);
+        if (!p.layers[(size_t)l].fwd_kept.ptr.empty()) {
+            Compact& k = kept[(size_t)l];
+            std::vector<int32_t> out_row, entry_row;
+            klay::compact_pass(p.layers[(size_t)l].fwd_kept, k.plan, out_row, entry_row);
+            fko[(size_t)l] = pack_pass(pk, k.plan);
+            k.out_row = pk.add(out_row);
+            k.entry_row = pk.add(entry_row);
+        }
         if (!p.layers[(size_t)l].fwd2.ptr.empty()) f2o[(size_t)l] = pack_pass(pk, p.layers[(size_t)l].fwd2);
     }
     std::vector<size_t> mo((size_t)L + 1, 0);
@@ -745,7 +764,12 @@ klay_status upload(klay_circuit* c) {
             bind_pass(d.bwd, p.layers[(size_t)l].bwd, bo[(size_t)l], base);
             const klay::LayerPlan& lp = p.layers[(size_t)l];
             d.n_fused = lp.n_fused;
-            if (!lp.fwd_kept.ptr.empty()) { bind_pass(d.fwd_kept, lp.fwd_kept, fko[(size_t)l], base); d.has_fwd_kept = true; }
+            if (!lp.fwd_kept.ptr.empty()) {
+                bind_pass(d.fwd_kept, kept[(size_t)l].plan, fko[(size_t)l], base, true);
+                d.fwd_kept.out_row = base + kept[(size_t)l].out_row;
+                d.fwd_kept.entry_row = base + kept[(size_t)l].entry_row;
+                d.has_fwd_kept = true;
+            }
             if (!lp.fwd2.ptr.empty()) { bind_pass(d.fwd2, lp.fwd2, f2o[(size_t)l], base); d.has_fwd2 = true; }
             if ((l & 1) == 0) {
                 d.multi = reinterpret_cast<const uint32_t*>(base + mo[(size_t)l]);
@@ -943,14 +967,14 @@ void run_pass_set(int op, int combine_op, const DevPass& dp, const float* src, c
     a.src2 = src2;
     a.own = own;
     a.seg_owner = dp.seg_owner;
-    a.out_row = nullptr;
+    a.out_row = dp.out_row;
     a.dst = dst;
     a.dst_seg = seg_rows;
     a.n_main = dp.n_main;
     a.n_total = dp.n_main + dp.n_seg;
     a.B = B;
     a.ld = g.ld;
-    const double light_rows = (double)dp.n_main - dp.n_heavy;
+    const double light_rows = (double)dp.n_light;
     if (g.w == 64 && g.vec == 1 && dp.n_heavy > 0 && dp.main_entries + dp.seg_entries > kSmallPassEntries && light_rows > 0 && pass_combine_pair(op, combine_op)) {
         prof.begin(KLAY_K_SPLIT, pass_bytes(op, (double)dp.seg_entries, (double)dp.n_seg, B),
                    pass_min_bytes(op, (double)dp.seg_entries, (double)dp.n_seg, 0.0, B));

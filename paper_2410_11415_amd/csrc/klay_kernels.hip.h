@@ -269,9 +269,12 @@ __device__ __forceinline__ float dead_value() {
 // an entry carries the end-of-row bit.  Everything that steers control flow is wave-uniform.
 // Index entries past a task's end are valid entries of later rows (or zero padding).
 // ---------------------------------------------------------------------------------------------
-template <int OP, int VEC>
+// MAPPED: the main rows are not numbered through; entry_row says which one an entry belongs to (compact_pass).  For the AND layers without their
+// fused rows, whose skip entries, one a row, were most of what the walk read (seven layers of 811k nodes, three of four AND rows
+// fused, us: four columns a lane, B = 256 87 -> 77, which is the rate of what is left; two, B = 100 64 -> 55).
+template <int OP, int VEC, bool MAPPED>
 __global__ __launch_bounds__(256) void stream_kernel(const int2* __restrict__ tasks, int n_tasks,
-                                                     const uint32_t* __restrict__ idx,
+                                                     const uint32_t* __restrict__ idx, const int32_t* __restrict__ entry_row,
                                                      const float* __restrict__ src,
                                                      const float* __restrict__ src2,
                                                      const float* __restrict__ own, float* __restrict__ dst,
@@ -313,8 +316,14 @@ __global__ __launch_bounds__(256) void stream_kernel(const int2* __restrict__ ta
     bool beyond = false;                     // P row ops: a sum of P rows is not finite
     bool fresh = true;                       // the next edge opens a new output row
     uint32_t ids[CH];
+    int to[CH];
+    static_assert(!(MAPPED && OWN), "the value of a row is looked up by its number");
+    const int32_t* row_of = seg ? nullptr : entry_row;
 #pragma unroll
     for (int i = 0; i < CH; ++i) ids[i] = idx[j + i];
+    if (MAPPED && !seg)
+#pragma unroll
+        for (int i = 0; i < CH; ++i) to[i] = row_of[j + i];
 
     while (j < e1) {
         const int n = e1 - j;
@@ -322,7 +331,7 @@ __global__ __launch_bounds__(256) void stream_kernel(const int2* __restrict__ ta
         bool first[CH];
 #pragma unroll
         for (int i = 0; i < CH; ++i) {
-            rws[i] = row;
+            rws[i] = MAPPED && !seg ? to[i] : row;
             first[i] = fresh;
             if (i < n) {
                 fresh = (ids[i] & kLast) != 0;
@@ -352,6 +361,9 @@ __global__ __launch_bounds__(256) void stream_kernel(const int2* __restrict__ ta
         uint32_t nxt[CH];
 #pragma unroll
         for (int i = 0; i < CH; ++i) nxt[i] = idx[j + CH + i];       // padded: always readable
+        if (MAPPED && !seg)
+#pragma unroll
+            for (int i = 0; i < CH; ++i) to[i] = row_of[j + CH + i];
         // s_waitcnt vmcnt(0) (scalar prefetch left in flight): the gathers are complete on every
         // path from here on, so no later register reuse has to wait on them again.
         __builtin_amdgcn_s_waitcnt(kWaitVmcnt0);

@@ -37,6 +37,24 @@ int32_t segment_len(int64_t k, const Options& opt) {
     int64_t s = std::min<int64_t>(kMaxSegment, (int64_t)std::ceil(std::sqrt((double)k)));
     return (int32_t)std::max<int64_t>(s, std::max(1, opt.min_segment));
 }
+// tasks over the rows r_begin .. r_end: close a task once it holds `target` entries (or 64 rows)
+int32_t cut_tasks(const std::vector<int32_t>& ptr, int64_t r_begin, int64_t r_end, std::vector<int32_t>& tasks) {
+    const int64_t entries = ptr[(size_t)r_end] - ptr[(size_t)r_begin];
+    const int64_t target = std::min<int64_t>(kTaskMax, std::max<int64_t>(kTaskMin, entries / kTaskDiv));
+    tasks.clear();
+    int64_t r = r_begin;
+    while (r < r_end) {
+        tasks.push_back((int32_t)r);
+        tasks.push_back(ptr[(size_t)r]);
+        int64_t r1 = r;
+        while (r1 < r_end && r1 - r < 64 && ptr[(size_t)r1] - ptr[(size_t)r] < target) ++r1;
+        r = r1;
+    }
+    const int32_t count = (int32_t)(tasks.size() / 2);
+    tasks.push_back((int32_t)r_end);
+    tasks.push_back(ptr[(size_t)r_end]);
+    return count;
+}
 }  // namespace
 
 void make_pass_plan(int64_t n, const int32_t* ptr, const int32_t* idx_in, const Options& opt, PassPlan& out,
@@ -122,25 +140,7 @@ void make_pass_plan(int64_t n, const int32_t* ptr, const int32_t* idx_in, const 
         }
     }
     out.ptr[(size_t)n] = w;
-    // tasks: close a task once it holds `target` entries (or 64 rows)
-    auto cut_tasks = [&](int64_t r_begin, int64_t r_end, std::vector<int32_t>& tasks) -> int32_t {
-        const int64_t entries = out.ptr[(size_t)r_end] - out.ptr[(size_t)r_begin];
-        const int64_t target = std::min<int64_t>(kTaskMax, std::max<int64_t>(kTaskMin, entries / kTaskDiv));
-        tasks.clear();
-        int64_t r = r_begin;
-        while (r < r_end) {
-            tasks.push_back((int32_t)r);
-            tasks.push_back(out.ptr[(size_t)r]);
-            int64_t r1 = r;
-            while (r1 < r_end && r1 - r < 64 && out.ptr[(size_t)r1] - out.ptr[(size_t)r] < target) ++r1;
-            r = r1;
-        }
-        const int32_t count = (int32_t)(tasks.size() / 2);
-        tasks.push_back((int32_t)r_end);
-        tasks.push_back(out.ptr[(size_t)r_end]);
-        return count;
-    };
-    out.n_tasks = cut_tasks(0, n, out.tasks);
+    out.n_tasks = cut_tasks(out.ptr, 0, n, out.tasks);
     if (n_heavy == 0) return;
     // Segments of all split rows, ordered by the first source they read: segments that read the
     // same stretch of source rows then run next to each other (and on the same XCD), so the
@@ -185,7 +185,30 @@ void make_pass_plan(int64_t n, const int32_t* ptr, const int32_t* idx_in, const 
     }
     for (int64_t hh = 0; hh < n_heavy; ++hh)
         out.comb_idx[(size_t)out.comb_ptr[(size_t)hh + 1] - 1] |= row_flag(out.comb_row[(size_t)hh]);
-    out.n_seg_tasks = cut_tasks(n, n + n_seg, out.seg_tasks);
+    out.n_seg_tasks = cut_tasks(out.ptr, n, n + n_seg, out.seg_tasks);
+}
+
+void compact_pass(const PassPlan& in, PassPlan& out, std::vector<int32_t>& out_row, std::vector<int32_t>& entry_row) {
+    out = in;
+    out.ptr.assign(1, 0);
+    out.idx.clear();
+    out_row.clear();
+    entry_row.clear();
+    for (int32_t r = 0; r < in.n_main; ++r) {
+        const int32_t from = in.ptr[(size_t)r], to = in.ptr[(size_t)r + 1];
+        if (to == from + 1 && in.idx[(size_t)from] == kSkipRow) continue;
+        out_row.push_back(r);
+        out.idx.insert(out.idx.end(), in.idx.begin() + from, in.idx.begin() + to);
+        entry_row.insert(entry_row.end(), (size_t)(to - from), r);
+        out.ptr.push_back((int32_t)out.idx.size());
+    }
+    out.n_main = (int32_t)out_row.size();
+    const int32_t shift = in.ptr[(size_t)in.n_main] - (int32_t)out.idx.size();
+    out.idx.insert(out.idx.end(), in.idx.begin() + in.ptr[(size_t)in.n_main], in.idx.end());       // segments and padding
+    for (int32_t i = 1; i <= in.n_seg; ++i) out.ptr.push_back(in.ptr[(size_t)in.n_main + (size_t)i] - shift);
+    entry_row.insert(entry_row.end(), (size_t)kIdxPad, 0);
+    out.n_tasks = cut_tasks(out.ptr, 0, out.n_main, out.tasks);
+    if (out.n_seg > 0) out.n_seg_tasks = cut_tasks(out.ptr, out.n_main, out.n_main + out.n_seg, out.seg_tasks);
 }
 
 void make_cols(int64_t n, const int32_t* ptr, const int32_t* idx, const uint32_t* flags, const uint32_t* row_bits,

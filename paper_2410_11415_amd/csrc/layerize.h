@@ -218,6 +218,11 @@ int layerize(int32_t num_vars, int64_t num_nodes, const uint8_t* node_type, cons
 void make_pass_plan(int64_t n, const int32_t* ptr, const int32_t* idx, const Options& opt, PassPlan& out,
                     const uint32_t* flags = nullptr, const uint32_t* row_bits = nullptr, const uint8_t* skip = nullptr);
 
+// A plan without the main rows that it leaves out (kSkipRow entries), for launches: `out` numbers the others from 0 on (segments after
+// them, as in any plan; the combine rows keep their numbers), out_row[i] is the row that row i of `out` writes, entry_row[j] the one
+// that main entry j belongs to (padded like the entries).
+void compact_pass(const PassPlan& in, PassPlan& out, std::vector<int32_t>& out_row, std::vector<int32_t>& entry_row);
+
 // Runs (see ColPlan) of a CSR of n rows for `waves` waves.  pad: slot that padding names; step: whose costs to
 // cut by.  flags and row_bits as for make_pass_plan.
 // The units of a narrow layer are part of it.
