@@ -75,6 +75,8 @@ struct DevPass {
                   *seg_tasks = nullptr;
     const uint32_t *idx = nullptr, *comb_idx = nullptr;
     const int32_t *out_row = nullptr, *entry_row = nullptr;      // of a plan without left-out rows (compact_pass)
+    const int32_t *stream_tasks = nullptr, *stream_seg_tasks = nullptr;      // of the streaming kernel
+    int32_t n_stream_tasks = 0, n_stream_seg_tasks = 0;
     int32_t n_light = 0;                         // main rows that are evaluated as such
     int32_t n_main = 0, n_seg = 0, n_heavy = 0, n_tasks = 0, n_seg_tasks = 0;
     int32_t longest_comb = 0;                    // partial rows of the split row with most of them
@@ -389,17 +391,29 @@ void launch_edge(int op, const DevPass& dp, const Geometry& g, const float* src,
 template <int OP>
 void launch_stream_op(const DevPass& dp, const Geometry& g, const float* src,
                       const float* src2, const float* own, float* dst, float* dst_seg, int B, hipStream_t s, int* zf) {
-    const int2* tasks = reinterpret_cast<const int2*>(dp.tasks);
-    const int2* seg_tasks = reinterpret_cast<const int2*>(dp.seg_tasks);
-    const int n_tasks = dp.n_tasks, n_seg_tasks = dp.n_seg_tasks;
-    int64_t blocks = ((int64_t)n_tasks + n_seg_tasks + 3) / 4;
+    int64_t blocks = ((int64_t)dp.n_stream_tasks + dp.n_stream_seg_tasks + 3) / 4;
     blocks = (blocks + 7) / 8 * 8;
     // outputs larger than the L2s together (8 x 4 MB) are written with streaming stores
-    const int nt = (int64_t)dp.n_main * g.ld * 4 > (int64_t)64 << 20 ? 1 : 0;
+    klay::StreamArgs a{};
+    a.tasks = dp.stream_tasks;
+    a.seg_tasks = dp.stream_seg_tasks;
+    a.idx = dp.idx;
+    a.entry_row = dp.entry_row;
+    a.src = src;
+    a.src2 = src2;
+    a.own = own;
+    a.dst = dst;
+    a.dst_seg = dst_seg;
+    a.seg_owner = dp.seg_owner;
+    a.zero_flag = zf;
+    a.n_tasks = dp.n_stream_tasks;
+    a.n_seg_tasks = dp.n_stream_seg_tasks;
+    a.B = B;
+    a.ld = g.ld;
+    a.stream_stores = (int64_t)dp.n_main * g.ld * 4 > (int64_t)64 << 20 ? 1 : 0;
+    a.n_main = dp.n_main;
     dim3 grid((unsigned)blocks, (unsigned)g.tiles);
-    auto launch = [&](auto kernel) {
-        hipLaunchKernelGGL(kernel, grid, dim3(256), 0, s, tasks, n_tasks, dp.idx, dp.entry_row, src, src2, own, dst, B, g.ld, nt, seg_tasks, n_seg_tasks, dst_seg, dp.seg_owner, dp.n_main, zf);
-    };
+    auto launch = [&](auto kernel) { hipLaunchKernelGGL(kernel, grid, dim3(256), 0, s, a); };
     if constexpr (OP == klay::OP_SUM || OP == klay::OP_PROD) {
         if (dp.entry_row) return g.vec == 4 ? launch(klay::stream_kernel<OP, 4, true>) : launch(klay::stream_kernel<OP, 2, true>);
     }
@@ -408,7 +422,7 @@ void launch_stream_op(const DevPass& dp, const Geometry& g, const float* src,
 
 void launch_stream(int op, const DevPass& dp, const Geometry& g, const float* src,
                    const float* src2, const float* own, float* dst, float* dst_seg, int B, hipStream_t s, int* zf) {
-    if (dp.n_tasks + dp.n_seg_tasks <= 0) return;
+    if (dp.n_stream_tasks + dp.n_stream_seg_tasks <= 0) return;
     switch (op) {
     case klay::OP_SUM: launch_stream_op<klay::OP_SUM>(dp, g, src, src2, own, dst, dst_seg, B, s, zf); break;
     case klay::OP_PROD: launch_stream_op<klay::OP_PROD>(dp, g, src, src2, own, dst, dst_seg, B, s, zf); break;
@@ -533,7 +547,7 @@ struct Packer {
     }
 };
 
-struct PassOffsets { size_t ptr, idx, seg_owner, comb_ptr, comb_idx, comb_row, tasks, seg_tasks; };
+struct PassOffsets { size_t ptr, idx, seg_owner, comb_ptr, comb_idx, comb_row, tasks, seg_tasks, stream_tasks, stream_seg_tasks; int32_t n_stream_tasks, n_stream_seg_tasks; };
 
 PassOffsets pack_pass(Packer& pk, const klay::PassPlan& p) {
     PassOffsets o;
@@ -545,6 +559,11 @@ PassOffsets pack_pass(Packer& pk, const klay::PassPlan& p) {
     o.comb_row = pk.add(p.comb_row);
     o.tasks = pk.add(p.tasks);
     o.seg_tasks = pk.add(p.seg_tasks);
+    const std::vector<int32_t> main = klay::stream_tasks(p, 0, p.n_main), seg = klay::stream_tasks(p, p.n_main, (int64_t)p.n_main + p.n_seg);
+    o.stream_tasks = pk.add(main);
+    o.stream_seg_tasks = pk.add(seg);
+    o.n_stream_tasks = (int32_t)(main.size() / 4);
+    o.n_stream_seg_tasks = (int32_t)(seg.size() / 4);
     return o;
 }
 
@@ -559,6 +578,10 @@ void bind_pass(DevPass& d, const klay::PassPlan& p, const PassOffsets& o, const 
     d.n_tasks = p.n_tasks;
     d.seg_tasks = base + o.seg_tasks;
     d.n_seg_tasks = p.n_seg_tasks;
+    d.stream_tasks = base + o.stream_tasks;
+    d.stream_seg_tasks = base + o.stream_seg_tasks;
+    d.n_stream_tasks = o.n_stream_tasks;
+    d.n_stream_seg_tasks = o.n_stream_seg_tasks;
     d.has_weighted = p.has_weighted;
     d.n_light = p.n_main;
     d.main_entries = p.ptr[(size_t)p.n_main];

@@ -11,6 +11,8 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include <type_traits>
+
 #include "layerize.h"
 
 namespace klay {
@@ -202,6 +204,16 @@ __device__ __forceinline__ void lse_step(float& acc, float& mx, float x) {
     mx = up ? x : mx;
 }
 
+// the same for the first element of a row (acc = 0, mx = -inf before)
+template <int VEC>
+__device__ __forceinline__ void lse_first(float (&acc)[VEC], float (&mx)[VEC], const float (&x)[VEC]) {
+#pragma unroll
+    for (int v = 0; v < VEC; ++v) {
+        mx[v] = bigger(x[v], -INFINITY);      // (NaN: an impossible child)
+        acc[v] = 1.0f;
+    }
+}
+
 // nc: the value of the output row itself where the operation needs it; OP_LSE2 / OP_MAX2 keep the sum of the
 // group in hand there (weighted = the entry closes its group).  y: OP_SOFTMAX_BWD the parent's value, the P row ops share_scale(nc), or 1
 // (a single entry, or a sum that is then looked at).
@@ -264,162 +276,228 @@ __device__ __forceinline__ float dead_value() {
 // ---------------------------------------------------------------------------------------------
 // Streaming segmented gather-reduce for B > 64 (one wave spans the batch tile, VEC = 2 or 4 columns per
 // lane).  A task is a run of consecutive output rows with a bounded number of edges, fixed at
-// build time; the wave walks the task's edges in chunks of CH, keeps CH row gathers in flight,
-// prefetches the next chunk's index entries while they fly, and closes an output row whenever
-// an entry carries the end-of-row bit.  Everything that steers control flow is wave-uniform.
-// Index entries past a task's end are valid entries of later rows (or zero padding).
-// ---------------------------------------------------------------------------------------------
+// build time (stream_tasks); the wave walks the task's edges in chunks of CH, closes an output row whenever
+// an entry carries the end-of-row bit, and has the gathers of the next chunk on their way while it works on one, the entries of
+// the one after that, too.  Everything that steers control flow is wave-uniform and branches; entries past the task's end
+// are valid entries of later rows (or zero padding) that nothing is done with.
+//   What bounds it: where the children fit the caches, the scalar unit (one instruction a cycle for the whole compute unit; 26 of them an
+// entry with addresses summed per lane, skip entries and every entry tested against the task's end, now 11) and the vector instructions
+// of a logsumexp (a row's first element takes two instead of ten a column); where they do not, what misses the L2.  With one
+// chunk in flight, all of it waited for / as it is, us a pass: 811k nodes forward B = 256 368 / 334, (max, +) B = 100 246 / 188, real
+// training step B = 256 1185 / 1149; 3e6 nodes, training step B = 256 3656 / 3500.  (The P row ops wait for each chunk: with two of them in
+// flight they need more than 64 registers, 298 -> 313 us of that real step.)
 // MAPPED: the main rows are not numbered through; entry_row says which one an entry belongs to (compact_pass).  For the AND layers without their
 // fused rows, whose skip entries, one a row, were most of what the walk read (seven layers of 811k nodes, three of four AND rows
 // fused, us: four columns a lane, B = 256 87 -> 77, which is the rate of what is left; two, B = 100 64 -> 55).
+// ---------------------------------------------------------------------------------------------
+// index vectors that a wave reads as a whole, with scalar loads (nothing writes them while a kernel runs)
+template <class T> using Scalars = const __attribute__((address_space(4))) T*;
+template <class T>
+__device__ __forceinline__ Scalars<T> scalars(const T* p) { return (Scalars<T>)p; }
+
+struct StreamArgs {
+    const int32_t *tasks, *seg_tasks;   // main rows; segments of split rows: first row, its first entry, the ends of both
+    const uint32_t* idx;
+    const int32_t* entry_row;           // MAPPED
+    const float *src, *src2, *own;      // as PassArgs
+    float *dst, *dst_seg;               // dst_seg: the scratch rows shifted by -n_main rows
+    const int32_t* seg_owner;
+    int* zero_flag;
+    int32_t n_tasks, n_seg_tasks, B, ld, stream_stores, n_main;
+};
+
 template <int OP, int VEC, bool MAPPED>
-__global__ __launch_bounds__(256) void stream_kernel(const int2* __restrict__ tasks, int n_tasks,
-                                                     const uint32_t* __restrict__ idx, const int32_t* __restrict__ entry_row,
-                                                     const float* __restrict__ src,
-                                                     const float* __restrict__ src2,
-                                                     const float* __restrict__ own, float* __restrict__ dst,
-                                                     int B, int ld, int stream_stores,
-                                                     const int2* __restrict__ seg_tasks, int n_seg_tasks,
-                                                     float* __restrict__ dst_seg,
-                                                     const int32_t* __restrict__ seg_owner, int n_main,
-                                                     int* __restrict__ zero_flag) {
-    // entries per chunk: measured on the headline workload, 4 (2 for the softmax adjoint, which loads
-    // three rows per entry) beat 8 / 4 by 2%: the kernel is bandwidth-bound, fewer registers per wave
-    // buy more resident waves
-    constexpr int CH = OP == OP_SOFTMAX_BWD ? 2 : 4;
+__global__ __launch_bounds__(256) void stream_kernel(StreamArgs a) {
+    constexpr bool OWN = OpTraits<OP>::own, TWO = OP == OP_SOFTMAX_BWD;
+    constexpr int CH = TWO ? 2 : 4;         // entries per chunk
+    constexpr bool PIPE = !OpTraits<OP>::shares;
     static_assert(kGroupEnd == kWeighted, "the fused plans reuse this bit");
-    // the walk needs the output row's own value
-    constexpr bool OWN = OpTraits<OP>::own;
+    static_assert(!(MAPPED && OWN), "the value of a row is looked up by its number");
     const int lane = threadIdx.x & 63;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int col = ((int)blockIdx.y * 64 + lane) * VEC;
-    if (col >= B) return;
+    if (col >= a.B) return;
     int t = xcd_block((int)blockIdx.x, (int)gridDim.x) * 4 + wave;
-    if (t >= n_tasks + n_seg_tasks) return;
+    if (t >= a.n_tasks + a.n_seg_tasks) return;
     // tasks past the main list are segments of split rows: same walk, output rows go to scratch
-    // (dst_seg is shifted so that segment row numbers, which continue after the main rows, index it)
-    const bool seg = t >= n_tasks;
-    if (seg) { t -= n_tasks; tasks = seg_tasks; dst = dst_seg; stream_stores = 0; }
-    const int2 t0 = tasks[t], t1 = tasks[t + 1];
-    int row = t0.x;
-    int j = t0.y;
-    const int e1 = t1.y;
-    const int last_row = t1.x - 1;
-    const float* srcc = src + col;
-    const float* src2c = src2 + col;
-    const float* ownc = own + col;
-    float* dstc = dst + col;
+    const bool seg = t >= a.n_tasks;
+    if (seg) t -= a.n_tasks;
+    const Scalars<int32_t> task = scalars((seg ? a.seg_tasks : a.tasks) + 4 * (size_t)t);
+    const int2 t0 = make_int2(task[0], task[1]), t1 = make_int2(task[2], task[3]);
+    const Scalars<uint32_t> idx = scalars(a.idx + t0.y);
+    const Scalars<int32_t> row_of = scalars(MAPPED ? a.entry_row + t0.y : nullptr);
+    const Scalars<int32_t> owner = scalars(a.seg_owner);
+    int left = t1.y - t0.y;                 // entries
+    const uint32_t row_bytes = (uint32_t)a.ld * 4u;
+    uint32_t lane_bytes = (uint32_t)col * 4u;
+    float* const dst = seg ? a.dst_seg : a.dst;
+    const bool nt = !seg && a.stream_stores != 0;
+    // One address for the wave and an offset of the lane's own: scalar work in place of 64-bit sums in vector registers.  (The first
+    // statement keeps the compiler from adding base and lane first, the second from widening the offset once, after which it no longer sees
+    // that 32 bits are enough.)
+    auto at = [&](const float* rows, uint32_t row) {
+        uint64_t p = reinterpret_cast<uint64_t>(rows) + (uint64_t)row * row_bytes;
+        asm("" : "+s"(p));
+        asm volatile("" : "+v"(lane_bytes));
+        return (float*)(reinterpret_cast<__attribute__((address_space(1))) char*>(p) + lane_bytes);
+    };
+
+    struct Ids {
+        uint32_t id[CH];
+        int to[MAPPED ? CH : 1];
+    };
+    struct Chunk {
+        float x[CH][VEC], y[TWO ? CH : 1][VEC], z[OWN ? CH : 1][VEC];
+    };
+    int row = t0.x, row_ahead = t0.x;       // the next row to finish; the row of the next entry to gather
+    auto load_ids = [&](int j) {            // (readable past the end)
+        Ids r;
+#pragma unroll
+        for (int i = 0; i < CH; ++i) r.id[i] = idx[j + i];
+        if constexpr (MAPPED)
+#pragma unroll
+            for (int i = 0; i < CH; ++i) r.to[i] = row_of[j + i];
+        return r;
+    };
+    auto gather_one = [&](Chunk& c, int i, uint32_t id, uint32_t own_id) {
+        load_vec<VEC>(c.x[i], at(a.src, id & kIdMask));
+        // an unweighted edge needs no parent value: re-read the row just requested (an L1 hit)
+        if constexpr (TWO) load_vec<VEC>(c.y[i], at((id & kWeighted) ? a.src2 : a.src, id & kIdMask));
+        if constexpr (OWN) {
+            // (a segment of a split row works with the value of the row that owns it, if with any)
+            int own_row = row_ahead < t1.x ? row_ahead : t1.x - 1;
+            if (seg) own_row = OpTraits<OP>::seg_own ? owner[own_row - a.n_main] : 0;
+            load_vec<VEC>(c.z[i], at(a.own, (uint32_t)own_row));
+            row_ahead += (int)(own_id >> 31);
+        }
+    };
+    // n entries are the task's; in place of those past it the chunk's first row again
+    auto gather = [&](Chunk& c, const Ids& ids, int n) {
+#pragma unroll
+        for (int i = 0; i < CH; ++i) gather_one(c, i, i == 0 || i < n ? ids.id[i] : ids.id[0], ids.id[i]);
+    };
 
     float acc[VEC], mx[VEC], nc[VEC];
 #pragma unroll
     for (int v = 0; v < VEC; ++v) { acc[v] = identity<OP>(); mx[v] = identity2<OP>(); nc[v] = OP == OP_SUMPROD2 ? 1.0f : 0.0f; }
     bool beyond = false;                     // P row ops: a sum of P rows is not finite
-    bool fresh = true;                       // the next edge opens a new output row
-    uint32_t ids[CH];
-    int to[CH];
-    static_assert(!(MAPPED && OWN), "the value of a row is looked up by its number");
-    const int32_t* row_of = seg ? nullptr : entry_row;
-#pragma unroll
-    for (int i = 0; i < CH; ++i) ids[i] = idx[j + i];
-    if (MAPPED && !seg)
-#pragma unroll
-        for (int i = 0; i < CH; ++i) to[i] = row_of[j + i];
-
-    while (j < e1) {
-        const int n = e1 - j;
-        int rws[CH];
-        bool first[CH];
+    bool fresh = true;                       // the row in hand has nothing yet
+    auto consume = [&](const Chunk& c, const Ids& ids, int n, auto whole) {
 #pragma unroll
         for (int i = 0; i < CH; ++i) {
-            rws[i] = MAPPED && !seg ? to[i] : row;
-            first[i] = fresh;
-            if (i < n) {
-                fresh = (ids[i] & kLast) != 0;
-                row += fresh ? 1 : 0;
+            if (!decltype(whole)::value && i >= n) break;
+            const uint32_t id = ids.id[i];
+            const bool weighted = (id & kWeighted) != 0;
+            if constexpr (OP == OP_LSE) {
+                if (fresh) lse_first<VEC>(acc, mx, c.x[i]);
+                else
+#pragma unroll
+                    for (int v = 0; v < VEC; ++v) lse_step(acc[v], mx[v], c.x[i][v]);
+                fresh = false;
+            } else if constexpr (OP == OP_LSE2 || OP == OP_MAX2 || OP == OP_SUMPROD2) {
+#pragma unroll
+                for (int v = 0; v < VEC; ++v) nc[v] = OP == OP_SUMPROD2 ? nc[v] * c.x[i][v] : nc[v] + c.x[i][v];
+                if (weighted) {
+                    if constexpr (OP == OP_LSE2) {
+                        if (fresh) lse_first<VEC>(acc, mx, nc);
+                        else
+#pragma unroll
+                            for (int v = 0; v < VEC; ++v) lse_step(acc[v], mx[v], nc[v]);
+                        fresh = false;
+                    }
+#pragma unroll
+                    for (int v = 0; v < VEC; ++v) {
+                        if (OP == OP_MAX2) acc[v] = bigger(nc[v], acc[v]);
+                        if (OP == OP_SUMPROD2) acc[v] += nc[v];
+                        nc[v] = OP == OP_SUMPROD2 ? 1.0f : 0.0f;
+                    }
+                }
+            } else {
+                if constexpr (OWN) {
+                    if (fresh)
+#pragma unroll
+                        for (int v = 0; v < VEC; ++v) nc[v] = c.z[i][v];
+                    fresh = false;
+                }
+#pragma unroll
+                for (int v = 0; v < VEC; ++v) accumulate<OP>(acc[v], mx[v], c.x[i][v], TWO ? c.y[i][v] : 1.0f, nc[v], weighted);
             }
-        }
-        // All CH gathers are issued unconditionally (entries past the task's end or kSkip are
-        // redirected to valid rows and their data ignored): loads under wave-uniform branches
-        // would make the compiler drain the memory pipeline before each of them.
-        float x[CH][VEC], y[CH][VEC], z[CH][VEC];
-#pragma unroll
-        for (int i = 0; i < CH; ++i) {
-            const uint32_t srow = (ids[i] == kSkip) ? 0u : (ids[i] & kIdMask);
-            const size_t off = (size_t)srow * (size_t)ld;
-            load_vec<VEC>(x[i], srcc + off);
-            if (OP == OP_SOFTMAX_BWD) {
-                // an unweighted edge needs no parent value: re-read the row just requested (an L1 hit)
-                load_vec<VEC>(y[i], ((ids[i] & kWeighted) && ids[i] != kSkip ? src2c : srcc) + off);
-            }
-            if (OWN) {
-                // (a segment of a split row works with the value of the row that owns it, if with any)
-                int orow = rws[i] < last_row ? rws[i] : last_row;
-                if (seg) orow = OpTraits<OP>::seg_own ? seg_owner[orow - n_main] : 0;
-                load_vec<VEC>(z[i], ownc + (size_t)orow * (size_t)ld);
-            }
-        }
-        uint32_t nxt[CH];
-#pragma unroll
-        for (int i = 0; i < CH; ++i) nxt[i] = idx[j + CH + i];       // padded: always readable
-        if (MAPPED && !seg)
-#pragma unroll
-            for (int i = 0; i < CH; ++i) to[i] = row_of[j + CH + i];
-        // s_waitcnt vmcnt(0) (scalar prefetch left in flight): the gathers are complete on every
-        // path from here on, so no later register reuse has to wait on them again.
-        __builtin_amdgcn_s_waitcnt(kWaitVmcnt0);
-#pragma unroll
-        for (int i = 0; i < CH; ++i) {
-            // branch-free accumulation: a dead entry contributes the identity
-            const bool live = (i < n) && (ids[i] != kSkip);
-            if (OWN) {
-#pragma unroll
-                for (int v = 0; v < VEC; ++v) nc[v] = (live && first[i]) ? z[i][v] : nc[v];
-            }
-#pragma unroll
-            for (int v = 0; v < VEC; ++v) {
-                const float xv = live ? x[i][v] : dead_value<OP>();
-                const float yv = OP == OP_SOFTMAX_BWD ? (live ? y[i][v] : -INFINITY) : 1.0f;
-                accumulate<OP>(acc[v], mx[v], xv, yv, nc[v], OpTraits<OP>::shares ? !live || (ids[i] & kWeighted) != 0 : live && (ids[i] & kWeighted) != 0);
-            }
-            if (live && (ids[i] & kLast)) {
+            if (id & kLast) {
                 float o[VEC];
 #pragma unroll
                 for (int v = 0; v < VEC; ++v) {
                     if (OpTraits<OP>::shares) beyond |= !(fabsf(mx[v]) < INFINITY);
                     o[v] = finish<OP>(acc[v], mx[v], nc[v]);
                     // the adjoint of an OR node with more than one child leaves in the one-gather form
-                    if (OP == OP_SUM_H && !seg && (ids[i] & kRowFlag)) o[v] = encode_h(o[v], nc[v]);
+                    if (OP == OP_SUM_H && !seg && (id & kRowFlag)) o[v] = encode_h(o[v], nc[v]);
                     if (OpTraits<OP>::premul && !seg) {
-                        if (nc[v] == 0.0f && zero_flag) *zero_flag = 1;          // this layer needs prod_parent_kernel's repair
+                        if (nc[v] == 0.0f && a.zero_flag) *a.zero_flag = 1;          // this layer needs prod_parent_kernel's repair
                         o[v] = premultiply(o[v], nc[v]);
                     }
                     acc[v] = identity<OP>();
                     mx[v] = identity2<OP>();
                 }
-                if (stream_stores) store_vec_stream<VEC>(dstc + (size_t)rws[i] * (size_t)ld, o);
-                else store_vec<VEC>(dstc + (size_t)rws[i] * (size_t)ld, o);
+                const int out = MAPPED && !seg ? ids.to[i] : row;
+                float* to = at(dst, (uint32_t)out);
+                if (nt) store_vec_stream<VEC>(to, o);
+                else store_vec<VEC>(to, o);
+                ++row;
+                fresh = true;
             }
         }
-#pragma unroll
-        for (int i = 0; i < CH; ++i) ids[i] = nxt[i];
-        j += CH;
+    };
+    int j = 0;
+    Ids i0 = load_ids(0), i1 = load_ids(CH);
+    if constexpr (PIPE) {
+        Chunk c0, c1;
+        gather(c0, i0, left);
+        for (;;) {
+            const Ids i2 = load_ids(j + 2 * CH);
+            if (left <= CH) { consume(c0, i0, left, std::false_type()); break; }
+            gather(c1, i1, left - CH);
+            consume(c0, i0, CH, std::true_type());
+            left -= CH;
+            const Ids i3 = load_ids(j + 3 * CH);
+            if (left <= CH) { consume(c1, i1, left, std::false_type()); break; }
+            gather(c0, i2, left - CH);
+            consume(c1, i1, CH, std::true_type());
+            left -= CH;
+            j += 2 * CH;
+            i0 = i2;
+            i1 = i3;
+        }
+    } else {
+        Chunk c;
+        for (;;) {
+            gather(c, i0, left);
+            const Ids i2 = load_ids(j + 2 * CH);
+            // s_waitcnt vmcnt(0) (scalar prefetch left in flight): the gathers are complete on every
+            // path from here on, so no later register reuse has to wait on them again.
+            __builtin_amdgcn_s_waitcnt(kWaitVmcnt0);
+            if (left <= CH) { consume(c, i0, left, std::false_type()); break; }
+            consume(c, i0, CH, std::true_type());
+            i0 = i1;
+            i1 = i2;
+            left -= CH;
+            j += CH;
+        }
     }
     if (!OpTraits<OP>::shares || !__any(beyond)) return;
     // A sum of P rows left the range (or is NaN, as one that did and met an infinite row): the task's rows once more, every P row scaled before it is added.  (Rare; scaling always costs 7 to
     // 10% where layers are narrow: 16000 nodes in 40 layers at B = 256, training step 373 us / 401.)
     row = t0.x;
     fresh = true;
-    for (j = t0.y; j < e1; ++j) {
-        const uint32_t id = idx[j];
+    for (int k = 0; k < t1.y - t0.y; ++k) {
+        const uint32_t id = idx[k];
         const bool last = (id & kLast) != 0;
-        if (id != kSkip) {
+        {
             if (fresh) {
-                load_vec<VEC>(nc, ownc + (size_t)(seg ? seg_owner[row - n_main] : row) * (size_t)ld);
+                load_vec<VEC>(nc, at(a.own, (uint32_t)(seg ? owner[row - a.n_main] : row)));
 #pragma unroll
                 for (int v = 0; v < VEC; ++v) { acc[v] = identity<OP>(); mx[v] = identity2<OP>(); }
             }
             float x[VEC];
-            load_vec<VEC>(x, srcc + (size_t)(id & kIdMask) * (size_t)ld);
+            load_vec<VEC>(x, at(a.src, id & kIdMask));
 #pragma unroll
             for (int v = 0; v < VEC; ++v) accumulate<OP>(acc[v], mx[v], x[v], share_scale(nc[v]), nc[v], (id & kWeighted) != 0);
             if (last) {
@@ -429,7 +507,7 @@ __global__ __launch_bounds__(256) void stream_kernel(const int2* __restrict__ ta
                     o[v] = finish<OP>(acc[v], mx[v], nc[v], share_scale(nc[v]));
                     if (OpTraits<OP>::premul && !seg) o[v] = premultiply(o[v], nc[v]);
                 }
-                store_vec<VEC>(dstc + (size_t)row * (size_t)ld, o);
+                store_vec<VEC>(at(dst, (uint32_t)row), o);
             }
         }
         fresh = last;

@@ -22,6 +22,9 @@ namespace {
 #endif
 constexpr int64_t kLatencyBoundEntries = 200000;     // see make_pass_plan
 constexpr int64_t kTaskMin = KLAY_TASK_MIN, kTaskMax = KLAY_TASK_MAX, kTaskDiv = KLAY_TASK_DIV;
+// Of the streaming kernel, whose waves read ahead: what they work on at one time is smaller and more of it is read a second time from the L2
+// (3e6 nodes at B = 256, training step with at most 64 / 32 / 16 entries 3550 / 3538 / 3516 us).
+constexpr int64_t kStreamTaskMax = 16;
 // The persistent kernels' rows of more parents than this come first in their layer.  (8, 16, 64 and no such limit measured on
 // 13 training steps: within 2%, 48 layers of 43000 nodes at B = 4 123.1 / 123.6 / 124.0 / 124.5 us)
 constexpr int32_t kManyParents = 16;
@@ -37,10 +40,11 @@ int32_t segment_len(int64_t k, const Options& opt) {
     int64_t s = std::min<int64_t>(kMaxSegment, (int64_t)std::ceil(std::sqrt((double)k)));
     return (int32_t)std::max<int64_t>(s, std::max(1, opt.min_segment));
 }
+int64_t task_target(int64_t entries) { return std::min<int64_t>(kTaskMax, std::max<int64_t>(kTaskMin, entries / kTaskDiv)); }
+
 // tasks over the rows r_begin .. r_end: close a task once it holds `target` entries (or 64 rows)
 int32_t cut_tasks(const std::vector<int32_t>& ptr, int64_t r_begin, int64_t r_end, std::vector<int32_t>& tasks) {
-    const int64_t entries = ptr[(size_t)r_end] - ptr[(size_t)r_begin];
-    const int64_t target = std::min<int64_t>(kTaskMax, std::max<int64_t>(kTaskMin, entries / kTaskDiv));
+    const int64_t target = task_target(ptr[(size_t)r_end] - ptr[(size_t)r_begin]);
     tasks.clear();
     int64_t r = r_begin;
     while (r < r_end) {
@@ -186,6 +190,20 @@ void make_pass_plan(int64_t n, const int32_t* ptr, const int32_t* idx_in, const 
     for (int64_t hh = 0; hh < n_heavy; ++hh)
         out.comb_idx[(size_t)out.comb_ptr[(size_t)hh + 1] - 1] |= row_flag(out.comb_row[(size_t)hh]);
     out.n_seg_tasks = cut_tasks(out.ptr, n, n + n_seg, out.seg_tasks);
+}
+
+std::vector<int32_t> stream_tasks(const PassPlan& p, int64_t from, int64_t to) {
+    const int64_t target = std::min(kStreamTaskMax, task_target(p.ptr[(size_t)to] - p.ptr[(size_t)from]));
+    std::vector<int32_t> tasks;
+    auto skipped = [&](int64_t r) { return p.ptr[(size_t)r + 1] == p.ptr[(size_t)r] + 1 && p.idx[(size_t)p.ptr[(size_t)r]] == kSkipRow; };
+    for (int64_t r = from; r < to;) {
+        if (skipped(r)) { ++r; continue; }
+        int64_t end = r;
+        while (end < to && end - r < 64 && p.ptr[(size_t)end] - p.ptr[(size_t)r] < target && !skipped(end)) ++end;
+        for (int64_t x : {r, (int64_t)p.ptr[(size_t)r], end, (int64_t)p.ptr[(size_t)end]}) tasks.push_back((int32_t)x);
+        r = end;
+    }
+    return tasks;
 }
 
 void compact_pass(const PassPlan& in, PassPlan& out, std::vector<int32_t>& out_row, std::vector<int32_t>& entry_row) {

@@ -223,6 +223,10 @@ void make_pass_plan(int64_t n, const int32_t* ptr, const int32_t* idx, const Opt
 // that main entry j belongs to (padded like the entries).
 void compact_pass(const PassPlan& in, PassPlan& out, std::vector<int32_t>& out_row, std::vector<int32_t>& entry_row);
 
+// Tasks of the streaming kernel over the rows from .. to of a plan: (first row, its first entry, end of the rows, of the entries) of
+// runs of rows with a bounded number of entries and without kSkipRow entries.
+std::vector<int32_t> stream_tasks(const PassPlan& p, int64_t from, int64_t to);
+
 // Runs (see ColPlan) of a CSR of n rows for `waves` waves.  pad: slot that padding names; step: whose costs to
 // cut by.  flags and row_bits as for make_pass_plan.
 // The units of a narrow layer are part of it.

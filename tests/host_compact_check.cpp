@@ -48,6 +48,29 @@ int main() {
                 for (int32_t i = 0; i <= count; ++i) CHECK(t[2 * (size_t)i + 1] == out.ptr[(size_t)t[2 * (size_t)i]] && (i == 0 || t[2 * (size_t)i] > t[2 * (size_t)i - 2]), "task");
             }
         }
+    // the streaming kernel's tasks: every row that is no skip entry in one of them, in order, and bounded
+    for (int64_t n : {1, 2, 50, 4000, 300000}) {
+        klay::PassPlan p;
+        std::vector<int32_t> ptr{0}, idx;
+        for (int64_t r = 0; r < n; ++r) {
+            for (int64_t k = rng() % 40 == 0 ? 60 : 1 + (int64_t)(rng() % 5); k > 0; --k) idx.push_back((int32_t)(rng() % 1000));
+            ptr.push_back((int32_t)idx.size());
+        }
+        klay::make_pass_plan(n, ptr.data(), idx.data(), klay::Options(), p);
+        for (int part = 0; part < 2; ++part) {
+            const int64_t from = part ? n : 0, to = part ? n + p.n_seg : n;
+            const std::vector<int32_t> t = klay::stream_tasks(p, from, to);
+            int64_t row = from;
+            auto skipped = [&](int64_t r) { return p.idx[(size_t)p.ptr[(size_t)r]] == klay::kSkipRow; };
+            for (size_t i = 0; i < t.size(); i += 4) {
+                for (; row < t[i]; ++row) CHECK(skipped(row), "row %lld in no task", (long long)row);
+                CHECK(t[i] == row && t[i + 2] > t[i] && t[i + 2] <= to && t[i + 1] == p.ptr[(size_t)t[i]] && t[i + 3] == p.ptr[(size_t)t[i + 2]], "task");
+                CHECK(t[i + 3] > t[i + 1] && p.ptr[(size_t)t[i + 2] - 1] - t[i + 1] < 16, "entries of a task before its last row");
+                for (; row < t[i + 2]; ++row) CHECK(!skipped(row), "a skip entry in a task");
+            }
+            for (; row < to; ++row) CHECK(skipped(row), "row %lld in no task", (long long)row);
+        }
+    }
     CHECK(rows_out > 1000 && split > 1000, "rows of both kinds");
     std::printf("ok: %ld rows, %ld without entries\n", rows_out, split);
     return 0;
