@@ -562,8 +562,8 @@ PassOffsets pack_pass(Packer& pk, const klay::PassPlan& p) {
     const std::vector<int32_t> main = klay::stream_tasks(p, 0, p.n_main), seg = klay::stream_tasks(p, p.n_main, (int64_t)p.n_main + p.n_seg);
     o.stream_tasks = pk.add(main);
     o.stream_seg_tasks = pk.add(seg);
-    o.n_stream_tasks = (int32_t)(main.size() / 4);
-    o.n_stream_seg_tasks = (int32_t)(seg.size() / 4);
+    o.n_stream_tasks = (int32_t)(main.size() / klay::kTaskWords);
+    o.n_stream_seg_tasks = (int32_t)(seg.size() / klay::kTaskWords);
     return o;
 }
 

@@ -196,12 +196,12 @@ __device__ __forceinline__ float share_scale(float n) {
 // one element of a running logsumexp: (mx, acc) = (maximum so far, sum of exp(x - mx)), one exp per element
 __device__ __forceinline__ void lse_step(float& acc, float& mx, float x) {
     // d is +inf on the first finite element (e = 0, acc = 1), -inf for an impossible child under a finite
-    // maximum (e = 0), and NaN only for -inf - -inf and for a NaN, where the maximum of NaN and 0 is 0 and the comparison fails
+    // maximum (e = 0), and NaN only for -inf - -inf and for a NaN, where the clamp of the exponential makes it 0 and the comparison fails
     const float d = x - mx;
-    const float e = fmaxf(fexp(-fabsf(d)), 0.0f);
+    const float e = term_exp(-fabsf(d));
     const bool up = d > 0.0f;                                 // the same as x > mx
     acc = up ? fmaf(acc, e, 1.0f) : acc + e;
-    mx = up ? x : mx;
+    mx = bigger(x, mx);
 }
 
 // the same for the first element of a row (acc = 0, mx = -inf before)
@@ -278,7 +278,7 @@ __device__ __forceinline__ float dead_value() {
 // lane).  A task is a run of consecutive output rows with a bounded number of edges, fixed at
 // build time (stream_tasks); the wave walks the task's edges in chunks of CH, closes an output row whenever
 // an entry carries the end-of-row bit, and has the gathers of the next chunk on their way while it works on one, the entries of
-// the one after that, too.  Everything that steers control flow is wave-uniform and branches; entries past the task's end
+// the one after that, too; the first ones come with the task.  Everything that steers control flow is wave-uniform and branches; entries past the task's end
 // are valid entries of later rows (or zero padding) that nothing is done with.
 //   What bounds it: where the children fit the caches, the scalar unit (one instruction a cycle for the whole compute unit; 26 of them an
 // entry with addresses summed per lane, skip entries and every entry tested against the task's end, now 11) and the vector instructions
@@ -296,7 +296,7 @@ template <class T>
 __device__ __forceinline__ Scalars<T> scalars(const T* p) { return (Scalars<T>)p; }
 
 struct StreamArgs {
-    const int32_t *tasks, *seg_tasks;   // main rows; segments of split rows: first row, its first entry, the ends of both
+    const int32_t *tasks, *seg_tasks;   // main rows; segments of split rows (see stream_tasks)
     const uint32_t* idx;
     const int32_t* entry_row;           // MAPPED
     const float *src, *src2, *own;      // as PassArgs
@@ -322,7 +322,7 @@ __global__ __launch_bounds__(256) void stream_kernel(StreamArgs a) {
     // tasks past the main list are segments of split rows: same walk, output rows go to scratch
     const bool seg = t >= a.n_tasks;
     if (seg) t -= a.n_tasks;
-    const Scalars<int32_t> task = scalars((seg ? a.seg_tasks : a.tasks) + 4 * (size_t)t);
+    const Scalars<int32_t> task = scalars((seg ? a.seg_tasks : a.tasks) + kTaskWords * (size_t)t);
     const int2 t0 = make_int2(task[0], task[1]), t1 = make_int2(task[2], task[3]);
     const Scalars<uint32_t> idx = scalars(a.idx + t0.y);
     const Scalars<int32_t> row_of = scalars(MAPPED ? a.entry_row + t0.y : nullptr);
@@ -427,15 +427,15 @@ __global__ __launch_bounds__(256) void stream_kernel(StreamArgs a) {
 #pragma unroll
                 for (int v = 0; v < VEC; ++v) {
                     if (OpTraits<OP>::shares) beyond |= !(fabsf(mx[v]) < INFINITY);
-                    o[v] = finish<OP>(acc[v], mx[v], nc[v]);
+                    // (logsumexp: the sum is at least 1 here, see lse_first, so that a row of impossible children needs no test)
+                    o[v] = OP == OP_LSE || OP == OP_LSE2 ? mx[v] + flog(acc[v]) : finish<OP>(acc[v], mx[v], nc[v]);
                     // the adjoint of an OR node with more than one child leaves in the one-gather form
                     if (OP == OP_SUM_H && !seg && (id & kRowFlag)) o[v] = encode_h(o[v], nc[v]);
                     if (OpTraits<OP>::premul && !seg) {
                         if (nc[v] == 0.0f && a.zero_flag) *a.zero_flag = 1;          // this layer needs prod_parent_kernel's repair
                         o[v] = premultiply(o[v], nc[v]);
                     }
-                    acc[v] = identity<OP>();
-                    mx[v] = identity2<OP>();
+                    if (OP != OP_LSE && OP != OP_LSE2) { acc[v] = identity<OP>(); mx[v] = identity2<OP>(); }
                 }
                 const int out = MAPPED && !seg ? ids.to[i] : row;
                 float* to = at(dst, (uint32_t)out);
@@ -447,7 +447,13 @@ __global__ __launch_bounds__(256) void stream_kernel(StreamArgs a) {
         }
     };
     int j = 0;
-    Ids i0 = load_ids(0), i1 = load_ids(CH);
+    Ids i0, i1;                             // (with the task itself: one read less before the first gather)
+    static_assert(kTaskHead + 2 * CH <= kTaskWords, "two chunks");
+#pragma unroll
+    for (int i = 0; i < CH; ++i) { i0.id[i] = (uint32_t)task[kTaskHead + i]; i1.id[i] = (uint32_t)task[kTaskHead + CH + i]; }
+    if constexpr (MAPPED)
+#pragma unroll
+        for (int i = 0; i < CH; ++i) { i0.to[i] = row_of[i]; i1.to[i] = row_of[CH + i]; }
     if constexpr (PIPE) {
         Chunk c0, c1;
         gather(c0, i0, left);

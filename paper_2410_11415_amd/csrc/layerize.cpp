@@ -201,6 +201,7 @@ std::vector<int32_t> stream_tasks(const PassPlan& p, int64_t from, int64_t to) {
         int64_t end = r;
         while (end < to && end - r < 64 && p.ptr[(size_t)end] - p.ptr[(size_t)r] < target && !skipped(end)) ++end;
         for (int64_t x : {r, (int64_t)p.ptr[(size_t)r], end, (int64_t)p.ptr[(size_t)end]}) tasks.push_back((int32_t)x);
+        for (int i = 0; i < kTaskWords - kTaskHead; ++i) tasks.push_back((int32_t)p.idx[(size_t)p.ptr[(size_t)r] + (size_t)i]);      // (padded)
         r = end;
     }
     return tasks;

@@ -224,7 +224,9 @@ void make_pass_plan(int64_t n, const int32_t* ptr, const int32_t* idx, const Opt
 void compact_pass(const PassPlan& in, PassPlan& out, std::vector<int32_t>& out_row, std::vector<int32_t>& entry_row);
 
 // Tasks of the streaming kernel over the rows from .. to of a plan: (first row, its first entry, end of the rows, of the entries) of
-// runs of rows with a bounded number of entries and without kSkipRow entries.
+// runs of rows with a bounded number of entries and without kSkipRow entries, and in the same kTaskWords words the first entries (as
+// idx has them from there on): a wave that has its task can gather.
+constexpr int kTaskWords = 16, kTaskHead = 4;
 std::vector<int32_t> stream_tasks(const PassPlan& p, int64_t from, int64_t to);
 
 // Runs (see ColPlan) of a CSR of n rows for `waves` waves.  pad: slot that padding names; step: whose costs to

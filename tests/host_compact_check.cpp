@@ -62,7 +62,8 @@ int main() {
             const std::vector<int32_t> t = klay::stream_tasks(p, from, to);
             int64_t row = from;
             auto skipped = [&](int64_t r) { return p.idx[(size_t)p.ptr[(size_t)r]] == klay::kSkipRow; };
-            for (size_t i = 0; i < t.size(); i += 4) {
+            for (size_t i = 0; i < t.size(); i += klay::kTaskWords) {
+                for (int e = klay::kTaskHead; e < klay::kTaskWords; ++e) CHECK((uint32_t)t[i + (size_t)e] == p.idx[(size_t)t[i + 1] + (size_t)(e - klay::kTaskHead)], "entry of a task");
                 for (; row < t[i]; ++row) CHECK(skipped(row), "row %lld in no task", (long long)row);
                 CHECK(t[i] == row && t[i + 2] > t[i] && t[i + 2] <= to && t[i + 1] == p.ptr[(size_t)t[i]] && t[i + 3] == p.ptr[(size_t)t[i + 2]], "task");
                 CHECK(t[i + 3] > t[i + 1] && p.ptr[(size_t)t[i + 2] - 1] - t[i + 1] < 16, "entries of a task before its last row");
