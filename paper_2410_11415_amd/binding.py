@@ -339,9 +339,12 @@ class Circuit:
     # -- evaluation
     @staticmethod
     def _stream(stream):
+        if stream is not None:
+            return stream.cuda_stream
         import torch
-        s = torch.cuda.current_stream() if stream is None else stream
-        return s.cuda_stream
+        # the handle of torch.cuda.current_stream(), whose Stream object costs 3 us, in autograd's backward thread over 10 (training
+        # step of 467 nodes through CircuitLayer, host time 112 -> 81 us)
+        return torch._C._cuda_getCurrentRawStream(torch._C._cuda_getDevice())
 
     def forward(self, leaf_weights, semiring=KLAY_LOG, out=None, stream=None, neg_weights=None):
         """leaf_weights: torch float32 CUDA tensor [B, V], contiguous.  Returns out [B, R].
