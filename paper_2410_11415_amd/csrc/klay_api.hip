@@ -289,9 +289,13 @@ uint32_t row_inverse(int lanes) { return (uint32_t)((65536 + lanes - 1) / lanes)
 
 template <int OP>
 void launch_op(const klay::PassArgs& a, int vec, dim3 grid, hipStream_t s) {
-    if (vec == 4) hipLaunchKernelGGL((klay::pass_kernel<OP, 4>), grid, dim3(256), 0, s, a);
-    else if (vec == 2) hipLaunchKernelGGL((klay::pass_kernel<OP, 2>), grid, dim3(256), 0, s, a);
-    else hipLaunchKernelGGL((klay::pass_kernel<OP, 1>), grid, dim3(256), 0, s, a);
+    auto launch = [&](auto kernel) { hipLaunchKernelGGL(kernel, grid, dim3(256), 0, s, a); };
+    if constexpr (OP == klay::OP_LSE) {
+        // segments alone (see pass_body; with one column a lane the launch is a small one, bound by its latency)
+        if (a.row_begin > 0 && a.row_begin == a.n_main && vec > 1)
+            return vec == 4 ? launch(klay::pass_kernel<OP, 4, true>) : launch(klay::pass_kernel<OP, 2, true>);
+    }
+    vec == 4 ? launch(klay::pass_kernel<OP, 4, false>) : vec == 2 ? launch(klay::pass_kernel<OP, 2, false>) : launch(klay::pass_kernel<OP, 1, false>);
 }
 
 // workgroups of 4 waves for `rows` rows, a multiple of 8 (see xcd_block)

@@ -754,6 +754,51 @@ __device__ __forceinline__ void accumulate4(float (&acc)[VEC], float (&mx)[VEC],
     }
 }
 
+// Logsumexp of many terms: the state of a row is (mx, acc) = (maximum so far, sum of 2^(x log2(e) - lse_scale(mx))), one fused
+// multiply-add and one exponential per term.  lse_scale is a float at or just above mx log2(e), so that no term leaves [0, 1];
+// by how much, lse_value takes off again.  Beyond kLseFlat, where an ulp of mx is 16, a row is its maximum (the logarithm of fewer
+// than 2980 terms rounds away; a segment has 24 unless a longer minimum is asked for); that leaves out infinite maxima as well, whose scale is no number.
+constexpr float kLseFlat = 134217728.0f, kLseUp = 2.384185791015625e-7f;
+__device__ __forceinline__ float lse_scale(float m) {
+    float p = m * kLog2e;
+    asm("" : "+v"(p));                                 // (a product of its own: one that is fused into a later sum is another number)
+    return fmaf(fabsf(m), kLseUp, p);
+}
+__device__ __forceinline__ float unit_exp2(float x) { return __builtin_amdgcn_fmed3f(__builtin_amdgcn_exp2f(x), 0.0f, 1.0f); }
+__device__ __forceinline__ float lse_term(float x, float scale) { return unit_exp2(fmaf(x, kLog2e, -scale)); }
+__device__ __forceinline__ float lse_value(float acc, float mx) {
+    const float over = fmaf(mx, kLog2e, -lse_scale(mx));
+    return fabsf(mx) > kLseFlat ? mx : fmaf(__builtin_amdgcn_logf(acc) - over, kLn2, mx);
+}
+
+// N terms of every column joined to the state of its row: all of them (FULL), or the first `live`.  first: nothing came before.
+template <int VEC, int N, bool FULL>
+__device__ __forceinline__ void lse_join(float (&acc)[VEC], float (&mx)[VEC], const float (&x)[N][VEC], int live, bool first) {
+    float sum[VEC], scale[VEC], hi[VEC];
+#pragma unroll
+    for (int v = 0; v < VEC; ++v) {
+        float t[N];
+#pragma unroll
+        for (int i = 0; i < N; ++i) t[i] = FULL || i < live ? x[i][v] : -INFINITY;
+        hi[v] = mx[v];
+#pragma unroll
+        for (int i = 0; i < N; i += 2) hi[v] = max3(t[i], t[i + 1], hi[v]);
+        scale[v] = lse_scale(hi[v]);
+#pragma unroll
+        for (int i = 0; i < N; ++i) t[i] = lse_term(t[i], scale[v]);
+#pragma unroll
+        for (int d = 1; d < N; d *= 2)
+#pragma unroll
+            for (int i = 0; i < N; i += 2 * d) t[i] += t[i + d];
+        sum[v] = t[0];
+    }
+    if (!first)
+#pragma unroll
+        for (int v = 0; v < VEC; ++v) sum[v] = fmaf(acc[v], unit_exp2(lse_scale(mx[v]) - scale[v]), sum[v]);
+#pragma unroll
+    for (int v = 0; v < VEC; ++v) { acc[v] = sum[v]; mx[v] = hi[v]; }
+}
+
 // All arguments in one go: left to the compiler their reads sit behind the branches before their first use, one line after
 // another, and a launch of few rows is a chain of such reads (with the entries, see below, us: 2800 nodes max B = 5, 39
 // launches, 121 -> 116; 800000 nodes B = 1 108 -> 105, training B = 10 289 -> 281).
@@ -763,7 +808,14 @@ __device__ __forceinline__ void arguments_now(const PassArgs& a) {
 }
 
 // bx of nbx: the workgroup's place among those that take rows (nbx a multiple of 8, bx mod 8 the XCD the workgroup runs on)
-template <int OP, int VEC>
+// LONG: the segments of split logsumexp rows, 24 entries for the most part, in a launch of their own.  They run from the caches, and what
+// bounds them is the vector unit: per entry and column a select, a share of two maxima per four, a subtraction, a product, an exponential
+// (four instructions' time), a sum, and per four entries a rescaling of what came before.  Eight entries a step, without the selects,
+// without a rescaling before the first step, one fused multiply-add in front of the exponential: 24 entries take about 177 instructions a
+// column instead of 250.  Power-law fan-ins, 1e7 edges, B = 64, the six launches, us: 45.1 30.2 22.0 16.0 10.7 9.1 -> 37.2 26.1 19.4 13.7 9.7
+// 8.1; whole pass 376 -> 361.  (Not for the main rows beside combine rows, most of which are shorter: 58.4 -> 58.2, 14.2 -> 13.6, 17.0 -> 17.7 in
+// two circuits; nor, without its logsumexp, for the other ops: 62 -> 62 for the longest launch of sums.)
+template <int OP, int VEC, bool LONG>
 __device__ __forceinline__ void pass_body(int bx, int nbx, const PassArgs& a) {
     constexpr bool OWN = OpTraits<OP>::own;
     int sub, colu;
@@ -791,6 +843,40 @@ __device__ __forceinline__ void pass_body(int bx, int nbx, const PassArgs& a) {
 #pragma unroll
     for (int v = 0; v < VEC; ++v) { acc[v] = identity<OP>(); mx[v] = identity2<OP>(); }
     uint32_t last = 0;
+    if constexpr (LONG) {
+        static_assert(OP == OP_LSE, "the other ops gain nothing");
+        bool first = true;
+        auto gather = [&](uint32_t e, float (&to)[VEC]) { load_cols<VEC>(to, a.src + (size_t)(e & kIdMask) * a.ld + col); };
+        // as long as every row of the wave has eight entries left: nothing to test per entry
+        while (__all(j + 8 <= end)) {
+            float x[8][VEC];
+#pragma unroll
+            for (int i = 0; i < 8; ++i) gather(i < 4 ? e0[i] : e1[i - 4], x[i]);
+            j += 8;
+            e0 = *reinterpret_cast<const Entries4*>(a.idx + j);
+            e1 = *reinterpret_cast<const Entries4*>(a.idx + j + 4);
+            lse_join<VEC, 8, true>(acc, mx, x, 8, first);
+            first = false;
+        }
+        while (__any(j < end)) {
+            float x0[4][VEC], x1[4][VEC];
+            const bool second = __any(j + 4 < end), more = __any(j + 8 < end);
+#pragma unroll
+            for (int i = 0; i < 4; ++i) gather(j + i < end ? e0[i] : 0u, x0[i]);
+            if (second)
+#pragma unroll
+                for (int i = 0; i < 4; ++i) gather(j + 4 + i < end ? e1[i] : 0u, x1[i]);
+            if (more) {
+                const int at = j + 8 < end ? j + 8 : range.x;    // (a row that has ended reads its first entries again)
+                e0 = *reinterpret_cast<const Entries4*>(a.idx + at);
+                e1 = *reinterpret_cast<const Entries4*>(a.idx + at + 4);
+            }
+            if (j < end) lse_join<VEC, 4, false>(acc, mx, x0, end - j, first);
+            if (second && j + 4 < end) lse_join<VEC, 4, false>(acc, mx, x1, end - j - 4, false);
+            j += 8;
+            first = false;
+        }
+    } else
     for (;;) {
         float x0[4][VEC], x1[4][VEC], y0[4][VEC], y1[4][VEC];
         auto gather = [&](Entries4 e, float (&x)[4][VEC], float (&y)[4][VEC]) {
@@ -826,7 +912,7 @@ __device__ __forceinline__ void pass_body(int bx, int nbx, const PassArgs& a) {
     }
     float o[VEC];
 #pragma unroll
-    for (int v = 0; v < VEC; ++v) o[v] = OP == OP_LSE ? mx[v] + flog(acc[v]) : finish<OP>(acc[v], mx[v], nc[v]);
+    for (int v = 0; v < VEC; ++v) o[v] = OP == OP_LSE ? (LONG ? lse_value(acc[v], mx[v]) : mx[v] + flog(acc[v])) : finish<OP>(acc[v], mx[v], nc[v]);
     if (OpTraits<OP>::shares) {
         // a sum of P rows out of range: the row once more, as in the streaming kernel
         bool beyond = false;
@@ -863,10 +949,10 @@ __device__ __forceinline__ void pass_body(int bx, int nbx, const PassArgs& a) {
     store_cols<VEC>(out, o);
 }
 
-template <int OP, int VEC>
+template <int OP, int VEC, bool LONG>
 __global__ __launch_bounds__(256) void pass_kernel(PassArgs a) {
     arguments_now(a);
-    pass_body<OP, VEC>((int)blockIdx.x, (int)gridDim.x, a);
+    pass_body<OP, VEC, LONG>((int)blockIdx.x, (int)gridDim.x, a);
 }
 
 // ---------------------------------------------------------------------------------------------
@@ -964,7 +1050,7 @@ __global__ __launch_bounds__(NW * 64) void combine_kernel(PassArgs a, int many) 
 template <int OP, int COP, int VEC>
 __global__ __launch_bounds__(256) void pass_combine_kernel(PassArgs a, int n_comb_blocks, PassArgs cmb, int many) {
     if ((int)blockIdx.x < n_comb_blocks) combine_body<COP, 1, 4>((int)blockIdx.x, cmb, many);
-    else pass_body<OP, VEC>((int)blockIdx.x - n_comb_blocks, (int)gridDim.x - n_comb_blocks, a);
+    else pass_body<OP, VEC, false>((int)blockIdx.x - n_comb_blocks, (int)gridDim.x - n_comb_blocks, a);
 }
 
 // The same for B <= 32 and split rows of many partial rows (kShortComb): W lanes (a power of two) hold the columns of a partial row, so a wave takes 64 / W partial rows at
