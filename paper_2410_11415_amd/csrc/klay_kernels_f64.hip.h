@@ -84,7 +84,8 @@ __device__ __forceinline__ void load_cols(double (&x)[VEC], const double* p) {
 // each, as in the fp32 kernels, leaves the longest rows to one XCD where rows are sorted by length: 37000 nodes at B = 258
 // 163 against 130 us, 322000 nodes, training step at B = 395 2522 against 2243).
 //   ONE: a wave has one row (more than half of its lanes), so offsets and entries are the same for all lanes and come by
-// scalar loads.
+// scalar loads, and so does the number of entries that are left: no exponential is taken for those past the end (a library exponential is
+// about forty instructions, and most rows have two entries; 85000 nodes, training step at B = 33 198.1 -> 195.9 us).
 template <int OP, int VEC, bool ONE>
 __global__ __launch_bounds__(256) void pass_kernel(PassArgs a) {
     constexpr bool TWO = OP != OP_SOFTMAX_BWD;        // (two values per entry: four entries are enough registers)
@@ -130,13 +131,22 @@ __global__ __launch_bounds__(256) void pass_kernel(PassArgs a) {
                                  v3 = live > 3 ? x[3][v] : -INFINITY;
                     const double hi = fmax(fmax(fmax(v0, v1), fmax(v2, v3)), mx[v]);
                     const double m = fmin(fmax(hi, -1.7976931348623157e308), 1.7976931348623157e308);      // finite: no inf - inf
-                    double t = (exp(v0 - m) + exp(v1 - m)) + (exp(v2 - m) + exp(v3 - m));
+                    double t;
+                    if (ONE && live == 1) t = exp(v0 - m);
+                    else if (ONE && live == 2 && mx[v] == -INFINITY) {
+                        // nothing before: the larger of the two is the maximum, whose term is 1 (a NaN is the other one)
+                        t = (hi == m ? 1.0 : hi > m ? INFINITY : 0.0) + exp((v0 == hi ? v1 : v0) - m);
+                    } else if (ONE && live <= 3) {
+                        t = exp(v0 - m) + exp(v1 - m);
+                        if (live == 3) t += exp(v2 - m);
+                    } else t = (exp(v0 - m) + exp(v1 - m)) + (exp(v2 - m) + exp(v3 - m));
                     if (mx[v] != -INFINITY) t = fma(acc[v], exp(mx[v] - m), t);
                     acc[v] = t;
                     mx[v] = m;
                 } else {
 #pragma unroll
                     for (int i = 0; i < 4; ++i) {
+                        if (ONE && OP == OP_SOFTMAX_BWD && i >= live) break;
                         const double dead = OP == OP_PROD ? 1.0 : (OP == OP_MAX ? -INFINITY : 0.0);
                         accumulate<OP>(acc[v], mx[v], i < live ? x[i][v] : dead,
                                        OP == OP_SOFTMAX_BWD ? (i < live ? y[i][v] : -INFINITY) : 0.0, nc[v], (e[i] & kWeighted) != 0);
