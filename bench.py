@@ -67,9 +67,9 @@ def kernel_symbol(cls, B, edges=False, fused_op=10):
         w_small *= 2
     if cls in ops:
         if B > 128:
-            return "klay::stream_kernel<%d, %d>" % (ops[cls], vec)
+            return "klay::stream_kernel<%d, %d, *>" % (ops[cls], vec)
         if B > 84:                       # the latter where most entries are segments of split rows
-            return "klay::stream_kernel<%d, %d> / klay::pass_kernel<%d, *>" % (ops[cls], vec, ops[cls])
+            return "klay::stream_kernel<%d, %d, *> / klay::pass_kernel<%d, *>" % (ops[cls], vec, ops[cls])
         return "klay::edge_kernel<%d, %d>" % (ops[cls], w_small) if edges and B <= 32 else "klay::pass_kernel<%d, *>" % ops[cls]
     # (above 256 columns a launch of the persistent kernels has 1, 2 or 4 of them per workgroup, as its layers fit; the last argument of
     # the reverse kernel: it leaves every layer's adjoints)
@@ -80,7 +80,7 @@ def kernel_symbol(cls, B, edges=False, fused_op=10):
              "seed": "klay::seed_kernel", "split": "klay::pass_kernel<*> (segments of split rows)",
              "combine": "klay::combine_kernel<*>" if B > 32 else "klay::combine_small_kernel<*>",
              "main_combine": "klay::pass_combine_kernel<*>",
-             "fwd_or_fused": "klay::stream_kernel<%d, %d>" % (fused_op, vec),
+             "fwd_or_fused": "klay::stream_kernel<%d, %d, false>" % (fused_op, vec),
              "prod_edges": "klay::prod_parent_kernel<%d, %d>" % (vec, 64 if B > 32 else w_small)}
     return fixed.get(cls, cls)
 
