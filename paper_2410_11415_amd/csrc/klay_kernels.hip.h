@@ -309,7 +309,8 @@ struct StreamArgs {
 template <int OP, int VEC, bool MAPPED>
 __global__ __launch_bounds__(256) void stream_kernel(StreamArgs a) {
     constexpr bool OWN = OpTraits<OP>::own, TWO = OP == OP_SOFTMAX_BWD;
-    constexpr int CH = TWO ? 2 : 4;         // entries per chunk
+    constexpr int CH = TWO ? 2 : kStreamChunk;         // entries per chunk
+    static_assert(CH <= kStreamChunk && kStreamChunk - 1 + 2 * kStreamChunk <= kIdxPad, "what is read past a task's end (stream_reads)");
     constexpr bool PIPE = !OpTraits<OP>::shares;
     static_assert(kGroupEnd == kWeighted, "the fused plans reuse this bit");
     static_assert(!(MAPPED && OWN), "the value of a row is looked up by its number");
@@ -325,7 +326,7 @@ __global__ __launch_bounds__(256) void stream_kernel(StreamArgs a) {
     const Scalars<int32_t> task = scalars((seg ? a.seg_tasks : a.tasks) + kTaskWords * (size_t)t);
     const int2 t0 = make_int2(task[0], task[1]), t1 = make_int2(task[2], task[3]);
     const Scalars<uint32_t> idx = scalars(a.idx + t0.y);
-    const Scalars<int32_t> row_of = scalars(MAPPED ? a.entry_row + t0.y : nullptr);
+    const Scalars<int32_t> row_of = scalars(MAPPED ? static_cast<const int32_t*>(task_entry_rows(a.idx, a.entry_row, t0.y, seg)) : nullptr);
     const Scalars<int32_t> owner = scalars(a.seg_owner);
     int left = t1.y - t0.y;                 // entries
     const uint32_t row_bytes = (uint32_t)a.ld * 4u;

@@ -228,6 +228,15 @@ void compact_pass(const PassPlan& in, PassPlan& out, std::vector<int32_t>& out_r
 // idx has them from there on): a wave that has its task can gather.
 constexpr int kTaskWords = 16, kTaskHead = 4;
 std::vector<int32_t> stream_tasks(const PassPlan& p, int64_t from, int64_t to);
+// Entries that a wave reads of a task, from the first one on: the chunk in hand and two more, which it asks for before it knows whether
+// the task has them.
+constexpr int kStreamChunk = 4;
+constexpr int64_t stream_reads(int64_t entries) { return (entries + kStreamChunk - 1) / kStreamChunk * kStreamChunk + 2 * kStreamChunk; }
+// Where it reads as many output rows of them, in a plan of compact_pass.  The rows of a segment are not looked up, and entry_row ends with
+// the main entries: a wave that has one reads the entries themselves in their place, without a branch.
+constexpr const void* task_entry_rows(const uint32_t* idx, const int32_t* entry_row, int32_t first, bool segment) {
+    return segment ? static_cast<const void*>(idx + first) : entry_row + first;
+}
 
 // Runs (see ColPlan) of a CSR of n rows for `waves` waves.  pad: slot that padding names; step: whose costs to
 // cut by.  flags and row_bits as for make_pass_plan.
