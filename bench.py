@@ -71,10 +71,11 @@ def kernel_symbol(cls, B, edges=False, fused_op=10):
         if B > 84:                       # the latter where most entries are segments of split rows
             return "klay::stream_kernel<%d, %d, *> / klay::pass_kernel<%d, *>" % (ops[cls], vec, ops[cls])
         return "klay::edge_kernel<%d, %d>" % (ops[cls], w_small) if edges and B <= 32 else "klay::pass_kernel<%d, *>" % ops[cls]
-    # (above 256 columns a launch of the persistent kernels has 1, 2 or 4 of them per workgroup, as its layers fit; the last argument of
+    # (above 256 columns a launch of the persistent kernels has 1, 2 or 4 of them per workgroup, as its layers fit; the forward kernel's last
+    # argument: its leaf layer goes through a list of variables; the last argument of
     # the reverse kernel: it leaves every layer's adjoints)
     columns = "1" if B <= 256 else "*"
-    fixed = {"tail_fwd": "klay::col_fwd_kernel<%s>" % columns,
+    fixed = {"tail_fwd": "klay::col_fwd_kernel<%s, *>" % columns,
              "tail_bwd": "klay::col_bwd_kernel<%s, %s>" % (columns, "true, false" if fused_op == 12 else "false, *"),
              "leaf": "klay::leaf_fwd_kernel" if B > 32 else "klay::leaf_fwd_small_kernel", "bwd_leaf": "klay::leaf_bwd_kernel", "root": "klay::root_out_kernel",
              "seed": "klay::seed_kernel", "split": "klay::pass_kernel<*> (segments of split rows)",

@@ -1664,8 +1664,8 @@ __device__ __forceinline__ void col_load(V* to, const float* from, ColColumns co
 struct SlabLeaf {
     const float* w;             // [B, V] leaf weights (null: the leaf layer was evaluated by leaf_fwd_kernel)
     const float* wneg;          // [B, V] weights of the negated literals, or null
-    const int32_t *pos_row, *neg_row;    // [V] layer-0 row of each literal or -1
-    float* wT;                  // [V, ld] transposed leaf weights kept for the reverse sweep
+    const int32_t *pos_row, *neg_row;    // [V] layer-0 row of each literal or -1; LISTED: of some variables alone, the two arrays and these variables' numbers one after another
+    float* wT;                  // [V, ld] transposed leaf weights kept for the reverse sweep (which reads those of variables with a negated literal)
     float* act0;                // [n_0, ld] rows of layer 0 in the activation buffer
     int32_t V, true_row, false_row;      // rows of the constants or -1
 };
@@ -1676,7 +1676,9 @@ struct SlabLeaf {
 // tb (or null): every layer's values are kept there.  CT: columns of a workgroup.
 // wide: so many layers before the narrow ones (n_layers: there are none), whose units end a wave early (leaves != 0) where the first wave alone reads the
 // roots.
-template <int CT>
+// LISTED: the leaf layer goes through a list of variables (leaf_list).  (A kernel of its own: the test for a list costs the others 0.4 us of 34, 85000
+// nodes at B = 128.)
+template <int CT, bool LISTED>
 __global__ __launch_bounds__(kColThreads) void col_fwd_kernel(const ColLayer* __restrict__ first, int n_layers, int first_is_and,
                                                               const Line* __restrict__ blocks, int n_blocks, const Desc* __restrict__ tables,
                                                               const Line* __restrict__ units, int n_units, int wide, int leaves,
@@ -1712,8 +1714,9 @@ __global__ __launch_bounds__(kColThreads) void col_fwd_kernel(const ColLayer* __
             if (col0 + c == B - 1)
                 for (int b = B; b < ld; ++b) leaf.act0[(size_t)row * ld + b] = 0.0f;
         };
-        for (int v = threadIdx.x; v < leaf.V; v += kColThreads) {
-            const int pr = leaf.pos_row[v], nr = leaf.neg_row[v];
+        const int n_vars = LISTED ? (int)(leaf.neg_row - leaf.pos_row) : leaf.V;
+        for (int i = threadIdx.x; i < n_vars; i += kColThreads) {
+            const int pr = leaf.pos_row[i], nr = leaf.neg_row[i], v = LISTED ? leaf.neg_row[n_vars + i] : i;
             float x[CT], y[CT];
 #pragma unroll
             for (int c = 0; c < CT; ++c) {
