@@ -1566,8 +1566,10 @@ Workspace64 workspace_layout64(const klay_circuit* c, int B, int ld, int first) 
 // exponential and a wave has room for the row (up to 64 columns): those passes wait for arithmetic, and twice the waves
 // hide it (85000 nodes at B = 33, per launch: logsumexp 8.0 us with two and 6.8 with one, plain sums 5.1 us with one and 4.4 with
 // two).
+// rows, entries: of the launch (segments are rows); short rows have a kernel of their own (see f64::pass_kernel).
+constexpr int64_t kShortRows64 = 6;
 template <int OP>
-void launch_pass64(klay::f64::PassArgs a, hipStream_t s) {
+void launch_pass64(klay::f64::PassArgs a, int64_t rows, int64_t entries, hipStream_t s) {
     if (a.n_total <= 0) return;
     const bool arithmetic = OP == klay::OP_LSE || OP == klay::OP_SOFTMAX_BWD;
     const int vec = a.B == 1 || (arithmetic && a.B <= 64) || (int64_t)a.n_total * row_lanes(a.B, 2) < 64 * kFillWaves ? 1 : 2;
@@ -1575,21 +1577,22 @@ void launch_pass64(klay::f64::PassArgs a, hipStream_t s) {
     a.per_wave = 64 / a.lanes;
     a.inverse = row_inverse(a.lanes);
     const dim3 grid(row_blocks(a.n_total, a.lanes), (unsigned)((a.B + a.lanes * vec - 1) / (a.lanes * vec)));
-    const bool one = a.per_wave == 1;
-    if (vec == 2 && one) hipLaunchKernelGGL((klay::f64::pass_kernel<OP, 2, true>), grid, dim3(256), 0, s, a);
-    else if (vec == 2) hipLaunchKernelGGL((klay::f64::pass_kernel<OP, 2, false>), grid, dim3(256), 0, s, a);
-    else if (one) hipLaunchKernelGGL((klay::f64::pass_kernel<OP, 1, true>), grid, dim3(256), 0, s, a);
-    else hipLaunchKernelGGL((klay::f64::pass_kernel<OP, 1, false>), grid, dim3(256), 0, s, a);
+    auto launch = [&](auto kernel) { hipLaunchKernelGGL(kernel, grid, dim3(256), 0, s, a); };
+    if (a.per_wave > 1) return vec == 2 ? launch(klay::f64::pass_kernel<OP, 2, false, false>) : launch(klay::f64::pass_kernel<OP, 1, false, false>);
+    if constexpr (OP == klay::OP_LSE) {
+        if (entries <= kShortRows64 * rows) return vec == 2 ? launch(klay::f64::pass_kernel<OP, 2, true, true>) : launch(klay::f64::pass_kernel<OP, 1, true, true>);
+    }
+    vec == 2 ? launch(klay::f64::pass_kernel<OP, 2, true, false>) : launch(klay::f64::pass_kernel<OP, 1, true, false>);
 }
 
-void launch_pass64(int op, const klay::f64::PassArgs& a, hipStream_t s) {
+void launch_pass64(int op, const klay::f64::PassArgs& a, int64_t rows, int64_t entries, hipStream_t s) {
     switch (op) {
-    case klay::OP_SUM: launch_pass64<klay::OP_SUM>(a, s); break;
-    case klay::OP_PROD: launch_pass64<klay::OP_PROD>(a, s); break;
-    case klay::OP_LSE: launch_pass64<klay::OP_LSE>(a, s); break;
-    case klay::OP_MAX: launch_pass64<klay::OP_MAX>(a, s); break;
-    case klay::OP_PROD_BWD: launch_pass64<klay::OP_PROD_BWD>(a, s); break;
-    default: launch_pass64<klay::OP_SOFTMAX_BWD>(a, s); break;
+    case klay::OP_SUM: launch_pass64<klay::OP_SUM>(a, rows, entries, s); break;
+    case klay::OP_PROD: launch_pass64<klay::OP_PROD>(a, rows, entries, s); break;
+    case klay::OP_LSE: launch_pass64<klay::OP_LSE>(a, rows, entries, s); break;
+    case klay::OP_MAX: launch_pass64<klay::OP_MAX>(a, rows, entries, s); break;
+    case klay::OP_PROD_BWD: launch_pass64<klay::OP_PROD_BWD>(a, rows, entries, s); break;
+    default: launch_pass64<klay::OP_SOFTMAX_BWD>(a, rows, entries, s); break;
     }
 }
 
@@ -1610,7 +1613,7 @@ void run_pass_set64(int op, int combine_op, const DevPass& dp, const double* src
     a.n_total = dp.n_main + dp.n_seg;
     a.B = B;
     a.ld = ld;
-    launch_pass64(op, a, s);
+    launch_pass64(op, a, (int64_t)dp.n_light + dp.n_seg, dp.main_entries + dp.seg_entries, s);
     if (dp.n_heavy > 0) {
         klay::f64::PassArgs cmb{};
         cmb.ptr = dp.comb_ptr;
@@ -1622,7 +1625,7 @@ void run_pass_set64(int op, int combine_op, const DevPass& dp, const double* src
         cmb.n_total = dp.n_heavy;
         cmb.B = B;
         cmb.ld = ld;
-        launch_pass64(combine_op, cmb, s);
+        launch_pass64(combine_op, cmb, dp.n_heavy, dp.n_seg, s);
     }
 }
 

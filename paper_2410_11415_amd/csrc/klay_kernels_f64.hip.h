@@ -84,10 +84,14 @@ __device__ __forceinline__ void load_cols(double (&x)[VEC], const double* p) {
 // each, as in the fp32 kernels, leaves the longest rows to one XCD where rows are sorted by length: 37000 nodes at B = 258
 // 163 against 130 us, 322000 nodes, training step at B = 395 2522 against 2243).
 //   ONE: a wave has one row (more than half of its lanes), so offsets and entries are the same for all lanes and come by
-// scalar loads, and so does the number of entries that are left: no exponential is taken for those past the end (a library exponential is
-// about forty instructions, and most rows have two entries; 85000 nodes, training step at B = 33 198.1 -> 195.9 us).
-template <int OP, int VEC, bool ONE>
+// scalar loads, and so does the number of entries that are left: no exponential is taken for those past the end of a row of softmax terms (a library
+// exponential is about forty instructions), nor, SHORT, of logsumexp terms, where a row of two takes one.  SHORT where the rows of the launch have at
+// most kShortRows64 entries on average, since the branches cost longer rows more than they save (forward, us, always four / SHORT: 85000 nodes, 3.5
+// entries a row, B = 33 81.6 / 80.4, B = 130 145.9 / 141.4; 160000 nodes of 5.3, B = 33 140.3 / 140.0; power-law fan-ins, 8 and 12 a row, B = 40
+// 234.0 / 244.8 and 359.3 / 376.0).
+template <int OP, int VEC, bool ONE, bool SHORT>
 __global__ __launch_bounds__(256) void pass_kernel(PassArgs a) {
+    static_assert(!SHORT || (ONE && OP == OP_LSE), "the other ops have one form");
     constexpr bool TWO = OP != OP_SOFTMAX_BWD;        // (two values per entry: four entries are enough registers)
     constexpr int STEP = TWO ? 8 : 4;
     int sub, colu;
@@ -132,11 +136,11 @@ __global__ __launch_bounds__(256) void pass_kernel(PassArgs a) {
                     const double hi = fmax(fmax(fmax(v0, v1), fmax(v2, v3)), mx[v]);
                     const double m = fmin(fmax(hi, -1.7976931348623157e308), 1.7976931348623157e308);      // finite: no inf - inf
                     double t;
-                    if (ONE && live == 1) t = exp(v0 - m);
-                    else if (ONE && live == 2 && mx[v] == -INFINITY) {
+                    if (SHORT && live == 1) t = exp(v0 - m);
+                    else if (SHORT && live == 2 && mx[v] == -INFINITY) {
                         // nothing before: the larger of the two is the maximum, whose term is 1 (a NaN is the other one)
                         t = (hi == m ? 1.0 : hi > m ? INFINITY : 0.0) + exp((v0 == hi ? v1 : v0) - m);
-                    } else if (ONE && live <= 3) {
+                    } else if (SHORT && live <= 3) {
                         t = exp(v0 - m) + exp(v1 - m);
                         if (live == 3) t += exp(v2 - m);
                     } else t = (exp(v0 - m) + exp(v1 - m)) + (exp(v2 - m) + exp(v3 - m));

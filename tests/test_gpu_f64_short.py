@@ -1,5 +1,6 @@
-"""Rows of 1 to 13 entries in the double-precision generic kernel (GPU), a wave to a row (33 to 64 columns) and several rows to a wave, with
-NaN, infinite and extreme weights, against numpy: a NaN passes on, except from a row whose other children are all impossible."""
+"""Rows of 1 to 13 entries in the double-precision generic kernel (GPU), a wave to a row (33 to 64 columns, one per lane, and 65 to 128, two) and
+several rows to a wave, alone (seven entries a row on average) and among many of two, where a wave with one row takes no exponential past its
+end; with NaN, infinite and extreme weights, against numpy: a NaN passes on, except from a row whose other children are all impossible."""
 import numpy as np
 import pytest
 
@@ -9,12 +10,14 @@ pytestmark = pytest.mark.gpu
 VARS = 40
 
 
-@pytest.mark.parametrize("batch", [20, 33, 50, 64])
-def test_short_rows(batch):
+@pytest.mark.parametrize("batch", [20, 33, 50, 64, 67, 128])
+@pytest.mark.parametrize("pairs", [0, 4000])
+def test_short_rows(batch, pairs):
     import torch
     import paper_2410_11415_amd as klay
     rng = np.random.default_rng(batch)
     kids = [rng.choice(VARS, size=n, replace=False) for n in range(1, 14) for _ in range(30)]
+    kids += [rng.choice(VARS, size=2, replace=False) for _ in range(pairs)]
     kids += [np.array([0, 1]), np.array([1, 0]), np.array([2, 0]), np.array([0, 2])]
     b = CircuitBuilder(VARS)
     lits = [b.lit(v) for v in range(VARS)]
