@@ -343,8 +343,11 @@ class Circuit:
             return stream.cuda_stream
         import torch
         # the handle of torch.cuda.current_stream(), whose Stream object costs 3 us, in autograd's backward thread over 10 (training
-        # step of 467 nodes through CircuitLayer, host time 112 -> 81 us)
-        return torch._C._cuda_getCurrentRawStream(torch._C._cuda_getDevice())
+        # step of 467 nodes through CircuitLayer, host time 112 -> 81 us), where this torch has functions for it
+        raw, device = getattr(torch._C, "_cuda_getCurrentRawStream", None), getattr(torch._C, "_cuda_getDevice", None)
+        if raw is None or device is None:
+            return torch.cuda.current_stream().cuda_stream
+        return raw(device())
 
     def forward(self, leaf_weights, semiring=KLAY_LOG, out=None, stream=None, neg_weights=None):
         """leaf_weights: torch float32 CUDA tensor [B, V], contiguous.  Returns out [B, R].
