@@ -80,6 +80,7 @@ struct DevPass {
     int32_t n_light = 0;                         // main rows that are evaluated as such
     int32_t n_main = 0, n_seg = 0, n_heavy = 0, n_tasks = 0, n_seg_tasks = 0;
     int32_t longest_comb = 0;                    // partial rows of the split row with most of them
+    int32_t longest_seg = 0;                     // entries of the longest segment
     int32_t n_comb_many = 0;                     // see PassPlan
     bool has_weighted = false;
     int64_t edges = 0;
@@ -290,11 +291,12 @@ int row_lanes(int B, int vec) { return std::min(64, (B + vec - 1) / vec); }
 uint32_t row_inverse(int lanes) { return (uint32_t)((65536 + lanes - 1) / lanes); }
 
 template <int OP>
-void launch_op(const klay::PassArgs& a, int vec, dim3 grid, hipStream_t s) {
+void launch_op(const klay::PassArgs& a, int vec, dim3 grid, hipStream_t s, int32_t longest_seg = 0) {
     auto launch = [&](auto kernel) { hipLaunchKernelGGL(kernel, grid, dim3(256), 0, s, a); };
     if constexpr (OP == klay::OP_LSE) {
-        // segments alone (see pass_body; with one column a lane the launch is a small one, bound by its latency)
-        if (a.row_begin > 0 && a.row_begin == a.n_main && vec > 1)
+        // segments alone (see pass_body; with one column a lane the launch is a small one, bound by its latency), unless a longer minimum was asked for
+        // than lse_value has room for
+        if (a.row_begin > 0 && a.row_begin == a.n_main && vec > 1 && longest_seg < klay::kLseFlatTerms)
             return vec == 4 ? launch(klay::pass_kernel<OP, 4, true>) : launch(klay::pass_kernel<OP, 2, true>);
     }
     vec == 4 ? launch(klay::pass_kernel<OP, 4, false>) : vec == 2 ? launch(klay::pass_kernel<OP, 2, false>) : launch(klay::pass_kernel<OP, 1, false>);
@@ -324,8 +326,8 @@ int deal_lanes(klay::PassArgs& a) {
     return vec;
 }
 
-// Launch one gather-reduce pass over `n_total` rows.
-void launch_pass(int op, klay::PassArgs a, hipStream_t s) {
+// Launch one gather-reduce pass over `n_total` rows.  longest_seg: entries of the longest segment, where there are segments alone.
+void launch_pass(int op, klay::PassArgs a, hipStream_t s, int32_t longest_seg = 0) {
     const int64_t rows = (int64_t)a.n_total - a.row_begin;
     if (rows <= 0) return;
     const int vec = deal_lanes(a);
@@ -333,7 +335,7 @@ void launch_pass(int op, klay::PassArgs a, hipStream_t s) {
     switch (op) {
     case klay::OP_SUM: launch_op<klay::OP_SUM>(a, vec, grid, s); break;
     case klay::OP_PROD: launch_op<klay::OP_PROD>(a, vec, grid, s); break;
-    case klay::OP_LSE: launch_op<klay::OP_LSE>(a, vec, grid, s); break;
+    case klay::OP_LSE: launch_op<klay::OP_LSE>(a, vec, grid, s, longest_seg); break;
     case klay::OP_MAX: launch_op<klay::OP_MAX>(a, vec, grid, s); break;
     case klay::OP_PROD_BWD: launch_op<klay::OP_PROD_BWD>(a, vec, grid, s); break;
     case klay::OP_SUM_H: launch_op<klay::OP_SUM_H>(a, vec, grid, s); break;
@@ -601,6 +603,7 @@ void bind_pass(DevPass& d, const klay::PassPlan& p, const PassOffsets& o, const 
     d.n_heavy = p.n_heavy;
     d.n_comb_many = p.n_comb_many;
     for (int32_t h = 0; h < p.n_heavy; ++h) d.longest_comb = std::max(d.longest_comb, p.comb_ptr[(size_t)h + 1] - p.comb_ptr[(size_t)h]);
+    for (int32_t i = p.n_main; i < p.n_main + p.n_seg; ++i) d.longest_seg = std::max(d.longest_seg, p.ptr[(size_t)i + 1] - p.ptr[(size_t)i]);
     d.edges = p.edges;
     // distinct source rows (for the compulsory-byte count of the profile)
     uint32_t max_id = 0;
@@ -1027,7 +1030,7 @@ void run_pass_set(int op, int combine_op, const DevPass& dp, const float* src, c
         prof.begin(KLAY_K_SPLIT, pass_bytes(op, (double)dp.seg_entries, (double)dp.n_seg, B),
                    pass_min_bytes(op, (double)dp.seg_entries, (double)dp.n_seg, 0.0, B));
         a.row_begin = dp.n_main;
-        launch_pass(op, a, s);
+        launch_pass(op, a, s, dp.longest_seg);
         prof.end();
         prof.begin(KLAY_K_MAIN_COMBINE,
                    pass_bytes(op, (double)dp.main_entries, light_rows, B) + pass_bytes(combine_op, (double)dp.n_seg, (double)dp.n_heavy, B),

@@ -758,8 +758,9 @@ __device__ __forceinline__ void accumulate4(float (&acc)[VEC], float (&mx)[VEC],
 // Logsumexp of many terms: the state of a row is (mx, acc) = (maximum so far, sum of 2^(x log2(e) - lse_scale(mx))), one fused
 // multiply-add and one exponential per term.  lse_scale is a float at or just above mx log2(e), so that no term leaves [0, 1];
 // by how much, lse_value takes off again.  Beyond kLseFlat, where an ulp of mx is 16, a row is its maximum (the logarithm of fewer
-// than 2980 terms rounds away; a segment has 24 unless a longer minimum is asked for); that leaves out infinite maxima as well, whose scale is no number.
+// than kLseFlatTerms = e^8 terms rounds away; a segment has 24 unless a longer minimum is asked for); that leaves out infinite maxima as well, whose scale is no number.
 constexpr float kLseFlat = 134217728.0f, kLseUp = 2.384185791015625e-7f;
+constexpr int32_t kLseFlatTerms = 2980;
 __device__ __forceinline__ float lse_scale(float m) {
     float p = m * kLog2e;
     asm("" : "+v"(p));                                 // (a product of its own: one that is fused into a later sum is another number)

@@ -57,3 +57,24 @@ def test_segments(batch, segment):
     # Two stages, each with an ulp of the value; and in the logarithm of the sum: the exponent of a term that counts (up to 2^5) rounded
     # to 2^-24 of itself, and fewer than 32 sums and products in a row of half an ulp each
     np.testing.assert_allclose(got[~inf], ref[~inf], rtol=4 * 2.0 ** -24, atol=64 * 2.0 ** -24)
+
+
+def test_segments_of_thousands():
+    """Beyond 2^27, where an ulp is 16, the logarithm of 2980 equal terms does not round away any more."""
+    import torch
+    import paper_2410_11415_amd as klay
+    from klay_synth.circuits import LIT, OR
+    variables, rows, segment = 6200, 2060, 3000            # two segments a row, enough of them for two columns per lane
+    fan = np.array([2 * segment] * rows + [2])             # (and a row that is not split)
+    child = np.concatenate([(np.arange(k) * 7 + r) % variables for r, k in enumerate(fan)]).astype(np.int32)
+    n = variables + len(fan)
+    node_type = np.array([LIT] * variables + [OR] * len(fan), dtype=np.uint8)
+    lit = np.concatenate([np.arange(1, variables + 1), np.zeros(len(fan))]).astype(np.int32)
+    ptr = np.concatenate([np.zeros(variables + 1), np.cumsum(fan)]).astype(np.int64)
+    k = klay.Circuit(variables, node_type, lit, ptr, child, np.arange(variables, n, dtype=np.int32), device=0, no_tail=True, min_segment=segment)
+    assert k.info()["num_split_rows"] >= rows
+    x = np.float32(1.03 * 2 ** 27)
+    got = k.forward(torch.full((64, variables), float(x), device="cuda"), klay.KLAY_LOG).cpu().numpy()
+    k.close()
+    assert (got[:, :rows] == x + np.float32(16)).all()     # 8.7 more, of an ulp of 16
+    assert (got[:, rows] == x).all()
