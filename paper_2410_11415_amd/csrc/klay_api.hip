@@ -557,16 +557,19 @@ struct Packer {
 
 struct PassOffsets { size_t ptr, idx, seg_owner, comb_ptr, comb_idx, comb_row, tasks, seg_tasks, stream_tasks, stream_seg_tasks; int32_t n_stream_tasks, n_stream_seg_tasks; };
 
-PassOffsets pack_pass(Packer& pk, const klay::PassPlan& p) {
-    PassOffsets o;
+// edge_tasks: the plan may go by launch_edge
+PassOffsets pack_pass(Packer& pk, const klay::PassPlan& p, bool edge_tasks) {
+    PassOffsets o{};
     o.ptr = pk.add(p.ptr);
     o.idx = pk.add(p.idx);
     o.seg_owner = pk.add(p.seg_owner);
     o.comb_ptr = pk.add(p.comb_ptr);
     o.comb_idx = pk.add(p.comb_idx);
     o.comb_row = pk.add(p.comb_row);
-    o.tasks = pk.add(p.tasks);
-    o.seg_tasks = pk.add(p.seg_tasks);
+    if (edge_tasks) {
+        o.tasks = pk.add(p.tasks);
+        o.seg_tasks = pk.add(p.seg_tasks);
+    }
     const std::vector<int32_t> main = klay::stream_tasks(p, 0, p.n_main), seg = klay::stream_tasks(p, p.n_main, (int64_t)p.n_main + p.n_seg);
     o.stream_tasks = pk.add(main);
     o.stream_seg_tasks = pk.add(seg);
@@ -771,17 +774,17 @@ klay_status upload(klay_circuit* c) {
     std::vector<Compact> kept((size_t)L + 1);           // the AND layers' plans without the fused rows
     std::vector<PassOffsets> fo((size_t)L + 1), bo((size_t)L + 1), fko((size_t)L + 1), f2o((size_t)L + 1);
     for (int l = 1; l <= L; ++l) {
-        fo[(size_t)l] = pack_pass(pk, p.layers[(size_t)l].fwd);
-        bo[(size_t)l] = pack_pass(pk, p.layers[(size_t)l].bwd);
+        fo[(size_t)l] = pack_pass(pk, p.layers[(size_t)l].fwd, c->small_batch_edges);
+        bo[(size_t)l] = pack_pass(pk, p.layers[(size_t)l].bwd, c->small_batch_edges);
         if (!p.layers[(size_t)l].fwd_kept.ptr.empty()) {
             Compact& k = kept[(size_t)l];
             std::vector<int32_t> out_row, entry_row;
             klay::compact_pass(p.layers[(size_t)l].fwd_kept, k.plan, out_row, entry_row);
-            fko[(size_t)l] = pack_pass(pk, k.plan);
+            fko[(size_t)l] = pack_pass(pk, k.plan, false);
             k.out_row = pk.add(out_row);
             k.entry_row = pk.add(entry_row);
         }
-        if (!p.layers[(size_t)l].fwd2.ptr.empty()) f2o[(size_t)l] = pack_pass(pk, p.layers[(size_t)l].fwd2);
+        if (!p.layers[(size_t)l].fwd2.ptr.empty()) f2o[(size_t)l] = pack_pass(pk, p.layers[(size_t)l].fwd2, false);
     }
     std::vector<size_t> mo((size_t)L + 1, 0);
     for (int l = 2; l <= L; l += 2) mo[(size_t)l] = pk.add(p.layers[(size_t)l].multi);
@@ -1416,7 +1419,7 @@ klay_status ensure_real_bwd(klay_circuit* c) {
             klay::make_pass_plan(lay.n, lptr.data(), gsrc.data() + gptr[(size_t)a], opt, o.plan, gflag.data() + gptr[(size_t)a]);
             if (o.plan.n_seg > p.max_bwd_seg)
                 return fail(KLAY_EINVAL, "klay_backward: split plan of the real-semiring sweep exceeds the workspace");
-            o.pass = pack_pass(pk, o.plan);
+            o.pass = pack_pass(pk, o.plan, c->small_batch_edges);
         }
     }
     size_t o_ptr = 0, o_child = 0;

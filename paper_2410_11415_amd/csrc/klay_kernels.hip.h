@@ -533,7 +533,7 @@ __global__ __launch_bounds__(256) void stream_kernel(StreamArgs a) {
 //     shuffles; a lane knows its segment's start from the ballot of the end-of-row bits, so only values
 //     travel); the lane groups that hold a row's last entry store the row, the part of a row that is
 //     still open stays behind as the last lane group's partial.
-// Same task lists and index entries as the streaming kernel (a wave takes `span` consecutive tasks);
+// Same index entries as the streaming kernel, task lists of its own (PassPlan::tasks; a wave takes `span` consecutive ones);
 // tasks past the main list are the segments of split rows.  The log-domain OR reduction travels as
 // (maximum, sum of exp(x - maximum)) pairs.
 // ---------------------------------------------------------------------------------------------

@@ -226,8 +226,9 @@ void compact_pass(const PassPlan& in, PassPlan& out, std::vector<int32_t>& out_r
     out.idx.insert(out.idx.end(), in.idx.begin() + in.ptr[(size_t)in.n_main], in.idx.end());       // segments and padding
     for (int32_t i = 1; i <= in.n_seg; ++i) out.ptr.push_back(in.ptr[(size_t)in.n_main + (size_t)i] - shift);
     entry_row.insert(entry_row.end(), (size_t)kIdxPad, 0);
-    out.n_tasks = cut_tasks(out.ptr, 0, out.n_main, out.tasks);
-    if (out.n_seg > 0) out.n_seg_tasks = cut_tasks(out.ptr, out.n_main, out.n_main + out.n_seg, out.seg_tasks);
+    out.tasks.clear();
+    out.seg_tasks.clear();
+    out.n_tasks = out.n_seg_tasks = 0;
 }
 
 void make_cols(int64_t n, const int32_t* ptr, const int32_t* idx, const uint32_t* flags, const uint32_t* row_bits,

@@ -90,7 +90,8 @@ constexpr int kNarrowUnits = 60;     // (30, 60 and 90 measured, see ColUnits)
 // the last entry of a row bit 29 may flag the output row itself (reverse sweep into an OR layer: the row
 // is an OR node with more than one child, whose adjoint is stored in the one-gather form).
 // tasks: runs of consecutive main rows with a bounded edge count, as (first row, first edge)
-// pairs with a closing (n_main, main edge count) pair: the unit of work of one wave.
+// pairs with a closing (n_main, main edge count) pair: the unit of work of a wave of the edge kernel (the streaming
+// kernel's: stream_tasks).
 constexpr uint32_t kLastEdge = 0x80000000u, kWeightedEdge = 0x40000000u, kRowFlag = 0x20000000u, kSkipRow = 0xFFFFFFFFu;
 // In the fused plans (LayerPlan::fwd2) that bit means something else: kGroupEnd on the last entry of a group.  The
 // entries of a group are combined by the AND operation, the group results are the children of the OR row.
@@ -219,8 +220,8 @@ void make_pass_plan(int64_t n, const int32_t* ptr, const int32_t* idx, const Opt
                     const uint32_t* flags = nullptr, const uint32_t* row_bits = nullptr, const uint8_t* skip = nullptr);
 
 // A plan without the main rows that it leaves out (kSkipRow entries), for launches: `out` numbers the others from 0 on (segments after
-// them, as in any plan; the combine rows keep their numbers), out_row[i] is the row that row i of `out` writes, entry_row[j] the one
-// that main entry j belongs to (padded like the entries).
+// them, as in any plan; the combine rows keep their numbers; no tasks of the edge kernel), out_row[i] is the row that row i of `out` writes,
+// entry_row[j] the one that main entry j belongs to (padded like the entries).
 void compact_pass(const PassPlan& in, PassPlan& out, std::vector<int32_t>& out_row, std::vector<int32_t>& entry_row);
 
 // Tasks of the streaming kernel over the rows from .. to of a plan: (first row, its first entry, end of the rows, of the entries) of
