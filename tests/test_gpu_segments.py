@@ -1,21 +1,40 @@
 """Segments of split logsumexp rows in a launch of their own (GPU): 33 to 64 columns, two and four per lane, segments shorter and longer than
-the eight entries a step takes, against numpy in double, over ordinary weights and over those at the ends of the range."""
+the eight entries a step takes and of whole steps, against numpy in double, over ordinary weights and over those at the ends of the range."""
 import numpy as np
 import pytest
 
 from klay_synth.circuits import CircuitBuilder
 
 pytestmark = pytest.mark.gpu
-VARS, ROWS = 512, 1200
+VARS = 512
+FILL = 64 * 2048             # lanes from which on a lane takes more columns
+SMALL = 100000               # entries up to which segments and main rows go together
+
+# fan-in of the split rows, shortest segment asked for, the entries of a whole segment that come of it
+SHAPES = [((43, 49), 5, 7), ((50, 64), 5, 8), ((65, 81), 5, 9), ((197, 225), 5, 15), ((226, 256), 5, 16), ((257, 289), 5, 17), ((201, 219), 24, 24), ((201, 219), 32, 32)]
 
 
-def circuit(rng):
-    """1200 OR gates of 201 to 219 literals each (more than 10^5 entries: not a small launch), and some of two"""
+def cases():
+    for batch in (33, 34, 47, 50, 61, 64):
+        for columns in (2, 4):
+            for fans, least, length in SHAPES:
+                per_row = -(-sum(fans) // 2 // length)
+                segments = int(1.04 * max(FILL / -(-batch // columns), SMALL * per_row / (sum(fans) / 2))) + 40
+                if columns == 4 or segments * -(-batch // 4) < FILL:
+                    yield pytest.param(batch, columns, fans, least, length, segments, id="%d-%d-%d" % (batch, columns, length))
+
+
+def circuit(rng, fans, length, segments):
+    """OR gates of as many literals, so many segments in all, and some of two literals"""
     b = CircuitBuilder(VARS)
-    kids = [rng.choice(VARS, size=int(rng.integers(201, 220)), replace=False) for _ in range(ROWS)]
+    kids, count = [], 0
+    while count < segments:
+        kids.append(rng.choice(VARS, size=int(rng.integers(fans[0], fans[1] + 1)), replace=False))
+        count += -(-len(kids[-1]) // length)
+    entries = sum(len(row) for row in kids)
     kids += [rng.choice(VARS, size=2, replace=False) for _ in range(20)]
     lits = [b.lit(v) for v in range(VARS)]
-    return b.finish([b.or_(*[lits[v] for v in row]) for row in kids]), kids
+    return b.finish([b.or_(*[lits[v] for v in row]) for row in kids]), kids, count, entries
 
 
 def reference(w, kids):
@@ -28,15 +47,13 @@ def reference(w, kids):
     return out
 
 
-@pytest.mark.parametrize("batch", [33, 34, 47, 50, 61, 64])
-@pytest.mark.parametrize("segment", [24, 9, 5])
-def test_segments(batch, segment):
+@pytest.mark.parametrize("batch,columns,fans,least,length,segments", cases())
+def test_segments(batch, columns, fans, least, length, segments):
     import torch
     import paper_2410_11415_amd as klay
-    rng = np.random.default_rng(batch + segment)
-    c, kids = circuit(rng)
-    k = klay.Circuit(*c.arrays(), device=0, no_tail=True, heavy_fan=40, min_segment=segment)
-    assert k.info()["num_split_rows"] >= ROWS
+    rng = np.random.default_rng(batch + length)
+    c, kids, count, entries = circuit(rng, fans, length, segments)
+    k = klay.Circuit(*c.arrays(), device=0, no_tail=True, heavy_fan=40, min_segment=least)
     w = -rng.exponential(10.0, size=(batch, VARS)).astype(np.float32)
     w[1] *= 1e4                                            # one term outweighs the others, of any size
     w[2] = -7e4 - rng.random(VARS)                         # large values close together: the sum counts
@@ -50,8 +67,13 @@ def test_segments(batch, segment):
     w[8:][(u >= 0.3) & (u < 0.4)] = np.nan
     w[8, 5] = np.inf
     ref = reference(w.astype(np.float64), kids)
+    k.set_profiling(True)
     got = k.forward(torch.from_numpy(w).cuda(), klay.KLAY_LOG).cpu().numpy().astype(np.float64)
+    split = k.get_profile()["split"]
     k.close()
+    # a launch of segments, as many and as long as meant, with as many columns per lane
+    assert split["launches"] == 1 and split["alg_bytes"] == 4 * (batch + 1) * (entries + count)
+    assert count * -(-batch // columns) >= FILL and (columns == 4 or count * -(-batch // 4) < FILL)
     inf = np.isinf(ref)
     np.testing.assert_array_equal(got[inf], ref[inf])
     # Two stages, each with an ulp of the value; and in the logarithm of the sum: the exponent of a term that counts (up to 2^5) rounded
