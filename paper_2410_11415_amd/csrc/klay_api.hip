@@ -1116,11 +1116,13 @@ TailChoice choose_tail_fwd(const klay_circuit* c, int B) { return choose_tail(c,
 
 // The first layer that the forward kernel takes from the TopPlan at a batch of B (0: none, the layers of the plan itself go the
 // other ways): the choice with the least time by a rough account.  In the persistent kernels a layer takes the time of its longest
-// wave and about 2000 cycles; a launch takes 3.5 us and what it gathers, from the caches, at 10 TB/s.  us, launches throughout / this
+// wave and about 2000 cycles, as it does where it goes by runs (units, which came later, take 700, so that the account is against the kernel
+// where the top is narrow); a launch takes 3.5 us and what it gathers, from the caches, at 10 TB/s.  us, launches throughout / this
 // choice (first layer), forward and training step:
-//   290000 nodes in 30 layers, 1e7 edges, B = 1 230 / 206 (13), 412 / 368; B = 64 457 / 411 (13), 965 / 900; B = 500 1895 / 1777 (16),
-//   3830 / 3670; 92000 nodes in 40 layers, 1e6 edges, B = 1 178 / 116 (1), 325 / 284; B = 64 243 / 125, 484 / 286; B = 1000 646 / 492,
-//   1277 / 1178; 20000 nodes in 16 layers, 1.7e5 edges, B = 64 87 / 35 (1), 174 / 80.
+//   290000 nodes in 30 layers, 1e7 edges, B = 1 240 / 199 (13), 408 / 356; B = 64 422 / 361 (13), 806 / 716; B = 500 1540 / 1445 (16),
+//   3597 / 3468; 92000 nodes in 40 layers, 1.2e6 edges, B = 1 289 / 139 (3), 468 / 293; B = 64 322 / 151 (3), 536 / 333; B = 1000 740 / 566 (17),
+//   1464 / 1323; 30000 nodes in 24 layers, 2.3e5 edges, B = 64 129 / 45 (1), 244 / 107.
+// The rest of this comment was measured before there were units.
 // First layers above 1 only up to B = 1024: 23200 nodes in 30 layers at B = 2000 536 / 483 (2), but 1080 / 1181 in training.  (The
 // reverse kernel could leave the sweep to the launches earlier; that gains at most 8%, 92000 nodes training B = 1 284 against 259,
 // and loses for B >= 64.)

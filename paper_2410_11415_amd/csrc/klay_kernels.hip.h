@@ -285,9 +285,10 @@ __device__ __forceinline__ float dead_value() {
 // of a logsumexp (a row's first element takes two instead of ten a column); where they do not, what misses the L2.  With one
 // chunk in flight, all of it waited for / as it is, us a pass: 811k nodes forward B = 256 368 / 334, (max, +) B = 100 246 / 188, real
 // training step B = 256 1185 / 1149; 3e6 nodes, training step B = 256 3656 / 3500.  (The P row ops wait for each chunk: with two of them in
-// flight they need more than 64 registers, 298 -> 313 us of that real step.)
+// flight, a value of the output row beside every entry, they take 145 registers a lane at four columns, three waves a SIMD, with one 68, seven: 298 -> 313
+// us of that real step.)
 // MAPPED: the main rows are not numbered through; entry_row says which one an entry belongs to (compact_pass).  For the AND layers without their
-// fused rows, whose skip entries, one a row, were most of what the walk read (seven layers of 811k nodes, three of four AND rows
+// fused rows; left in as a skip entry a row, these were most of what the walk read (seven layers of 811k nodes, three of four AND rows
 // fused, us: four columns a lane, B = 256 87 -> 77, which is the rate of what is left; two, B = 100 64 -> 55).
 // ---------------------------------------------------------------------------------------------
 // index vectors that a wave reads as a whole, with scalar loads (nothing writes them while a kernel runs)
@@ -2016,7 +2017,7 @@ struct ColReal {
 // Reverse sweep over the same layers: seeds the top layer's adjoints from dout and walks n_steps layers
 // down.  LDS: the adjoints of the layer in hand and of the one below, size0 floats for the top layer and every second
 // one from there.  Node values come from the column-major buffer tb, once per row, and are far away (a read of them
-// takes about 2000 cycles, twice as long as a narrow layer): those of the first `cached` steps are loaded at once to
+// takes about 2000 cycles, three times as long as a layer of units): those of the first `cached` steps are loaded at once to
 // cache_at, into LDS that only later steps use or that lies behind both arrays (launch_tail_bwd; 67000 nodes in 48 layers of
 // about 1400, log training step at B = 4: 143 -> 116 us by what lies behind, 29000 nodes in 30 layers 91 -> 68); from there
 // on those of the next step's rows are fetched into registers during a step (up to kColOwn times four per thread: any

@@ -147,7 +147,7 @@ struct LayerPlan {
     // it, is "fused": the forward plans below never read its value, so a forward sweep that uses them does not
     // have to write it.
     int64_t n_fused = 0;             // AND layers: so many of the rows are fused
-    PassPlan fwd_kept;               // AND layers with fused rows: fwd with those rows left out (kSkipRow entries)
+    PassPlan fwd_kept;               // AND layers with fused rows: fwd with those rows left out (kSkipRow entries; launches have it without them, compact_pass)
     PassPlan fwd2;                   // OR layers that read fused rows: every child is a group of entries (kGroupEnd),
                                      // a fused AND child being replaced by its own children
 };
