@@ -56,7 +56,7 @@ def load_traffic(workload, batch, semiring, backward, chains):
     return table.get("runs", {}).get(key)
 
 
-def kernel_symbol(cls, B, edges=False, fused_op=10):
+def kernel_symbol(cls, B, edges=False, fused_op=10, backward=False):
     """rocprofv3's name for the kernel behind a profiling class (template arguments as it prints them; * where a launch's size or the
     circuit decides)."""
     vec = 4 if B > 128 else (2 if B > 64 else 1)
@@ -66,10 +66,12 @@ def kernel_symbol(cls, B, edges=False, fused_op=10):
     while w_small < B:
         w_small *= 2
     if cls in ops:
+        # (the last argument: AND layers as a list of the kept rows, which a loop with backward passes runs in its first step alone)
+        kept = "false" if backward else "*"
         if B > 128:
-            return "klay::stream_kernel<%d, %d, *>" % (ops[cls], vec)
+            return "klay::stream_kernel<%d, %d, %s>" % (ops[cls], vec, kept)
         if B > 84:                       # the latter where most entries are segments of split rows
-            return "klay::stream_kernel<%d, %d, *> / klay::pass_kernel<%d, *>" % (ops[cls], vec, ops[cls])
+            return "klay::stream_kernel<%d, %d, %s> / klay::pass_kernel<%d, *>" % (ops[cls], vec, kept, ops[cls])
         return "klay::edge_kernel<%d, %d>" % (ops[cls], w_small) if edges and B <= 32 else "klay::pass_kernel<%d, *>" % ops[cls]
     # (above 256 columns a launch of the persistent kernels has 1, 2 or 4 of them per workgroup, as its layers fit; the forward kernel's last
     # argument: its leaf layer goes through a list of variables; the last argument of
@@ -275,7 +277,7 @@ def main():
     for name, c in classes.items():
         if not c["launches"]:
             continue
-        g = by_symbol.setdefault(kernel_symbol(name, B, args.small_batch_edges, {pkg.KLAY_LOG: 10, pkg.KLAY_MAXLOG: 11, pkg.KLAY_REAL: 12}[semiring]), {"ms": 0.0, "launches": 0, "alg_bytes": 0.0, "min_bytes": 0.0,
+        g = by_symbol.setdefault(kernel_symbol(name, B, args.small_batch_edges, {pkg.KLAY_LOG: 10, pkg.KLAY_MAXLOG: 11, pkg.KLAY_REAL: 12}[semiring], backward), {"ms": 0.0, "launches": 0, "alg_bytes": 0.0, "min_bytes": 0.0,
                                                           "classes": []})
         for f in ("ms", "launches", "alg_bytes", "min_bytes"):
             g[f] += c[f]
